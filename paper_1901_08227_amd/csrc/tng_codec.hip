@@ -21,6 +21,7 @@ namespace {
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr uint32_t kFusedScaleRows = 8;  // at most this many rows of partial maxima are reduced by the quantiser itself
 constexpr int kLoadsPerLane = 4;  // float4 loads per lane and worker in the quantiser tile
+constexpr uint64_t kWaveTileElements = (uint64_t)kWave * kLoadsPerLane * 4;  // coordinates per wavefront tile
 constexpr uint32_t kMaxGridX = 1u << 20;
 
 __global__ __launch_bounds__(kBlock) void fill_u32_kernel(uint32_t* p, uint64_t n, uint32_t v) {
@@ -123,6 +124,19 @@ struct RefTile {
       const float4 r = STREAM ? load_stream(ref2 + i) : ref2[i];
       r2 = make_float4(clamp_ref(r.x, eps), clamp_ref(r.y, eps), clamp_ref(r.z, eps), clamp_ref(r.w, eps));
     }
+  }
+  // The same for a float4 that may reach past the end of the row (d elements).  What lies beyond takes operands
+  // under which a gradient of 0 normalises to 0 (see row_load_fill): it adds nothing to a maximum and codes to 0.
+  __device__ __forceinline__ void load_ragged(const float4* ref, const float4* ref2, uint64_t i, uint64_t d, float eps) {
+    if (NORM == kNormSub || NORM == kNormComb) r1 = load4_within(reinterpret_cast<const float*>(ref), 4 * i, d, 0.f);
+    else if (NORM == kNormQuot) r1 = load4_within(reinterpret_cast<const float*>(ref), 4 * i, d, 1.f);
+    else r1 = make_float4(0.f, 0.f, 0.f, 0.f);
+    r2 = make_float4(1.f, 1.f, 1.f, 1.f);
+    if (NORM == kNormComb) r2 = load4_within(reinterpret_cast<const float*>(ref2), 4 * i, d, 1.f);
+    if (NORM == kNormQuot)
+      r1 = make_float4(clamp_ref(r1.x, eps), clamp_ref(r1.y, eps), clamp_ref(r1.z, eps), clamp_ref(r1.w, eps));
+    if (NORM == kNormComb)
+      r2 = make_float4(clamp_ref(r2.x, eps), clamp_ref(r2.y, eps), clamp_ref(r2.z, eps), clamp_ref(r2.w, eps));
   }
   // Every worker divides by the same clamped reference (Eq. 2 and the combined form): the scale and the
   // quantise pass take its binary64 reciprocal once per coordinate and multiply per worker
@@ -240,6 +254,17 @@ __device__ __forceinline__ float4 load_row_stream(const v4f_u_t* p) {
   const v4f_u_t v = __builtin_nontemporal_load(p);
   return make_float4(v.x, v.y, v.z, v.w);
 }
+// A wavefront's tile lies inside the row (every tile but the last) or is ragged: then each float4 is checked
+// against the end of the row, and what lies beyond is filled with the value that normalises to 0 -- 0 itself, and
+// the worker's mean for the mean reference (RefTile::load_ragged supplies the references).  Rows whose length is
+// no multiple of 4 need no launches of their own that way (they took one element-by-element launch per pass:
+// scale, quantise, decode, each as long as a small kernel and one row of partial maxima more).  The ragged tile
+// has workgroups of its own behind the others (tail_workgroups: one wavefront per worker, so that it is no longer
+// than any other tile's work on one worker; one wavefront walking the workers one by one took 10 us at the end of
+// a launch).
+__device__ __forceinline__ float4 load_row_ragged(const GradRows& g, uint32_t m, uint64_t iv, uint64_t d, float fill) {
+  return load4_within(g.base + (uint64_t)m * g.pitch, 4 * iv, d, fill);
+}
 
 // ------------------------------------------------------------------------------------------
 // Pass 1: R_m = max_e |v_{m,e}|   (section "Gradient Compression": R = max_d |v_d|)
@@ -250,62 +275,51 @@ __device__ __forceinline__ float4 load_row_stream(const v4f_u_t* p) {
 // reference tile stays in registers.
 constexpr int kAbsmaxLoads = 4;
 
-template <int NORM, bool FULL>
 __device__ __forceinline__ void absmax_load(const v4f_u_t* __restrict__ row, const uint64_t (&iv)[kAbsmaxLoads],
-                                            uint64_t nvec, float4 (&x)[kAbsmaxLoads]) {
+                                            float4 (&x)[kAbsmaxLoads]) {
 #pragma unroll
-  for (int j = 0; j < kAbsmaxLoads; ++j) {
-    if (FULL || iv[j] < nvec) {
-      x[j] = load_row_stream(row + iv[j]);
-    } else {
-      x[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-  }
+  for (int j = 0; j < kAbsmaxLoads; ++j) x[j] = load_row_stream(row + iv[j]);
 }
 
-template <int NORM, bool FULL, bool RECIP>
+template <int NORM, bool RECIP>
 __device__ __forceinline__ float absmax_reduce(const float4 (&x)[kAbsmaxLoads], const RefTile<NORM> (&rt)[kAbsmaxLoads],
-                                               const uint64_t (&iv)[kAbsmaxLoads], uint64_t nvec, float mu) {
+                                               float mu) {
   if (RECIP) {
     double mx64 = 0.0;
 #pragma unroll
-    for (int j = 0; j < kAbsmaxLoads; ++j) {
-      if (FULL || iv[j] < nvec) mx64 = fmax(mx64, absmax4_by_reciprocal<NORM>(x[j], rt[j]));
-    }
+    for (int j = 0; j < kAbsmaxLoads; ++j) mx64 = fmax(mx64, absmax4_by_reciprocal<NORM>(x[j], rt[j]));
     if (!(mx64 > 0.0 && mx64 < 0x1p-125)) return (float)mx64;
     // else (a tile whose quotients are all tiny): once more with the divisions themselves
   }
   float mx = 0.f;
 #pragma unroll
   for (int j = 0; j < kAbsmaxLoads; ++j) {
-    if (FULL || iv[j] < nvec) {
-      const float a0 = fabsf(normalize_w<NORM>(x[j].x, rt[j].r1.x, rt[j].r2.x, mu));
-      const float a1 = fabsf(normalize_w<NORM>(x[j].y, rt[j].r1.y, rt[j].r2.y, mu));
-      const float a2 = fabsf(normalize_w<NORM>(x[j].z, rt[j].r1.z, rt[j].r2.z, mu));
-      const float a3 = fabsf(normalize_w<NORM>(x[j].w, rt[j].r1.w, rt[j].r2.w, mu));
-      mx = fmaxf(mx, fmaxf(fmaxf(a0, a1), fmaxf(a2, a3)));
-    }
+    const float a0 = fabsf(normalize_w<NORM>(x[j].x, rt[j].r1.x, rt[j].r2.x, mu));
+    const float a1 = fabsf(normalize_w<NORM>(x[j].y, rt[j].r1.y, rt[j].r2.y, mu));
+    const float a2 = fabsf(normalize_w<NORM>(x[j].z, rt[j].r1.z, rt[j].r2.z, mu));
+    const float a3 = fabsf(normalize_w<NORM>(x[j].w, rt[j].r1.w, rt[j].r2.w, mu));
+    mx = fmaxf(mx, fmaxf(fmaxf(a0, a1), fmaxf(a2, a3)));
   }
   return mx;
 }
 
-template <int NORM, int MC, bool FULL>
+template <int NORM, int MC>
 __device__ __forceinline__ void absmax_rows(const GradRows& g, const RefTile<NORM> (&rt)[kAbsmaxLoads],
-                                            const uint64_t (&iv)[kAbsmaxLoads], uint64_t nvec, uint32_t m0,
-                                            uint32_t M, const float* __restrict__ means, float (&mx)[MC]) {
+                                            const uint64_t (&iv)[kAbsmaxLoads], uint32_t m0, uint32_t M,
+                                            const float* __restrict__ means, float (&mx)[MC]) {
   constexpr int L = kAbsmaxLoads;
   float4 xa[L], xb[L];
   // rows past M (only when MC does not divide M) repeat the last row, which leaves its maximum unchanged
   auto row = [&](int mm) { return g.row(min(m0 + (uint32_t)mm, M - 1)); };
   auto mean_of = [&](int mm) { return NORM == kNormMean ? means[min(m0 + (uint32_t)mm, M - 1)] : 0.f; };
-  absmax_load<NORM, FULL>(row(0), iv, nvec, xa);
+  absmax_load(row(0), iv, xa);
 #pragma unroll
   for (int mm = 0; mm < MC; mm += 2) {
-    if (mm + 1 < MC) absmax_load<NORM, FULL>(row(mm + 1), iv, nvec, xb);
-    mx[mm] = fmaxf(mx[mm], absmax_reduce<NORM, FULL, kByReciprocal<NORM, MC>>(xa, rt, iv, nvec, mean_of(mm)));
+    if (mm + 1 < MC) absmax_load(row(mm + 1), iv, xb);
+    mx[mm] = fmaxf(mx[mm], absmax_reduce<NORM, kByReciprocal<NORM, MC>>(xa, rt, mean_of(mm)));
     if (mm + 1 < MC) {
-      if (mm + 2 < MC) absmax_load<NORM, FULL>(row(mm + 2), iv, nvec, xa);
-      mx[mm + 1] = fmaxf(mx[mm + 1], absmax_reduce<NORM, FULL, kByReciprocal<NORM, MC>>(xb, rt, iv, nvec, mean_of(mm + 1)));
+      if (mm + 2 < MC) absmax_load(row(mm + 2), iv, xa);
+      mx[mm + 1] = fmaxf(mx[mm + 1], absmax_reduce<NORM, kByReciprocal<NORM, MC>>(xb, rt, mean_of(mm + 1)));
     }
   }
 }
@@ -313,7 +327,7 @@ __device__ __forceinline__ void absmax_rows(const GradRows& g, const RefTile<NOR
 template <int NORM, int MC>
 __global__ __launch_bounds__(kBlock) void absmax_vec_kernel(GradRows g, const float4* __restrict__ ref4,
                                                             const float4* __restrict__ ref24,
-                                                            float* partials, uint64_t nvec,
+                                                            float* partials, uint64_t d, uint32_t main_blocks,
                                                             uint32_t M, float eps, const float* __restrict__ means) {
   constexpr int L = kAbsmaxLoads;
   constexpr uint64_t kWaveTile = (uint64_t)kWave * L;
@@ -322,46 +336,36 @@ __global__ __launch_bounds__(kBlock) void absmax_vec_kernel(GradRows g, const fl
   float mx[MC];
 #pragma unroll
   for (int mm = 0; mm < MC; ++mm) mx[mm] = 0.f;
-  const uint64_t ntiles = (nvec + kWaveTile - 1) / kWaveTile;  // wavefront tiles
-  for (uint64_t tile = (uint64_t)blockIdx.x * kWavesPerBlock + wave; tile < ntiles;
-       tile += (uint64_t)gridDim.x * kWavesPerBlock) {
-    RefTile<NORM> rt[L];
-    uint64_t iv[L];
-    const bool full = (tile + 1) * kWaveTile <= nvec;  // wave-uniform
+  const uint64_t ntiles = d / (4 * kWaveTile);  // whole wavefront tiles
+  if (blockIdx.x < main_blocks) {
+    for (uint64_t tile = (uint64_t)blockIdx.x * kWavesPerBlock + wave; tile < ntiles;
+         tile += (uint64_t)main_blocks * kWavesPerBlock) {
+      RefTile<NORM> rt[L];
+      uint64_t iv[L];
 #pragma unroll
-    for (int j = 0; j < L; ++j) {
-      iv[j] = tile * kWaveTile + (uint64_t)j * kWave + lane;
-      if (full || iv[j] < nvec) {
+      for (int j = 0; j < L; ++j) {
+        iv[j] = tile * kWaveTile + (uint64_t)j * kWave + lane;
         rt[j].load(ref4, ref24, iv[j], eps);
         if (kByReciprocal<NORM, MC>) rt[j].reciprocals();
       }
+      absmax_rows<NORM, MC>(g, rt, iv, m0, M, means, mx);
     }
-    if (full) {
-      absmax_rows<NORM, MC, true>(g, rt, iv, nvec, m0, M, means, mx);
-    } else {
-      absmax_rows<NORM, MC, false>(g, rt, iv, nvec, m0, M, means, mx);
+  } else {
+    const uint32_t at = (blockIdx.x - main_blocks) * kWavesPerBlock + (uint32_t)wave, m = min(m0 + at, M - 1);
+    const float mu = NORM == kNormMean ? means[m] : 0.f;
+    RefTile<NORM> rt[L];
+    float4 x[L];
+#pragma unroll
+    for (int j = 0; j < L; ++j) {
+      const uint64_t iv = ntiles * kWaveTile + (uint64_t)j * kWave + lane;
+      rt[j].load_ragged(ref4, ref24, iv, d, eps);
+      x[j] = load_row_ragged(g, m, iv, d, mu);
     }
+    const float v = absmax_reduce<NORM, false>(x, rt, mu);
+#pragma unroll
+    for (int mm = 0; mm < MC; ++mm) mx[mm] = (uint32_t)mm == at ? v : 0.f;
   }
   block_max_to_partials<MC>(mx, m0, M, partials);
-}
-
-template <int NORM>
-__global__ __launch_bounds__(kBlock) void absmax_scalar_kernel(const float* __restrict__ g,
-                                                               const float* __restrict__ ref,
-                                                               const float* __restrict__ ref2,
-                                                               float* partials, uint64_t first, uint64_t d,
-                                                               uint32_t M, float eps,
-                                                               const float* __restrict__ means) {
-  const uint32_t m = blockIdx.y;
-  const float mu = NORM == kNormMean ? means[m] : 0.f;
-  float mx[1] = {0.f};
-  const uint64_t stride = (uint64_t)gridDim.x * kBlock;
-  for (uint64_t e = first + (uint64_t)blockIdx.x * kBlock + threadIdx.x; e < d; e += stride) {
-    float r1, r2;
-    load_ref_scalar<NORM>(ref, ref2, e, eps, r1, r2);
-    mx[0] = fmaxf(mx[0], fabsf(normalize_w<NORM>(g[(uint64_t)m * d + e], r1, r2, mu)));
-  }
-  block_max_to_partials<1>(mx, m, M, partials);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -374,30 +378,22 @@ __global__ __launch_bounds__(kBlock) void absmax_scalar_kernel(const float* __re
 // index and reading LDS back as 32-bit words gives each lane whole words to store, contiguously.
 // ------------------------------------------------------------------------------------------
 // Everything a lane keeps across the worker loop of the quantiser: its four float4 positions and
-// the reference operands there.  FULL: the wavefront's whole tile lies inside the row, no bounds
-// checks (all tiles but the last).
+// the reference operands there.
 template <int NORM>
 struct QuantLane {
   RefTile<NORM> rt[kLoadsPerLane];
   uint64_t iv[kLoadsPerLane];
-  bool ok[kLoadsPerLane];
 };
 
-template <int NORM, bool FULL>
+template <int NORM>
 __device__ __forceinline__ void load_worker_tile(const QuantLane<NORM>& q, const GradRows& g, uint32_t m,
                                                  float4 (&x)[kLoadsPerLane]) {
 #pragma unroll
-  for (int j = 0; j < kLoadsPerLane; ++j) {
-    if (FULL || q.ok[j]) {
-      x[j] = load_row_stream(g.row(m) + q.iv[j]);
-    } else {
-      x[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-  }
+  for (int j = 0; j < kLoadsPerLane; ++j) x[j] = load_row_stream(g.row(m) + q.iv[j]);
 }
 
 // Codes of one worker for this lane's 16 coordinates: four fragments of 4 codes each.
-template <int NORM, int BITS, bool FULL, bool RECIP>
+template <int NORM, int BITS, bool RECIP>
 __device__ __forceinline__ void quantize_worker_tile(const QuantLane<NORM>& q, const float4 (&x)[kLoadsPerLane],
                                                      float R, float mu, uint32_t m, uint32_t iter, uint32_t k0,
                                                      uint32_t k1, uint32_t (&frag)[kLoadsPerLane]) {
@@ -409,16 +405,13 @@ __device__ __forceinline__ void quantize_worker_tile(const QuantLane<NORM>& q, c
   const float inv_r = 1.0f / R;
 #pragma unroll
   for (int j = 0; j < kLoadsPerLane; ++j) {
-    frag[j] = 0u;
-    if (FULL || q.ok[j]) {
-      const U32x4 rnd = philox4x32_10((uint32_t)q.iv[j], m, iter, 0u, k0, k1);
-      const float4 v = normalize4<NORM, RECIP>(x[j], q.rt[j], mu);
-      const uint32_t c0 = quantize_code<BITS>(v.x, inv_r, rnd.x);
-      const uint32_t c1 = quantize_code<BITS>(v.y, inv_r, rnd.y);
-      const uint32_t c2 = quantize_code<BITS>(v.z, inv_r, rnd.z);
-      const uint32_t c3 = quantize_code<BITS>(v.w, inv_r, rnd.w);
-      frag[j] = c0 | (c1 << BITS) | (c2 << (2 * BITS)) | (c3 << (3 * BITS));
-    }
+    const U32x4 rnd = philox4x32_10((uint32_t)q.iv[j], m, iter, 0u, k0, k1);
+    const float4 v = normalize4<NORM, RECIP>(x[j], q.rt[j], mu);
+    const uint32_t c0 = quantize_code<BITS>(v.x, inv_r, rnd.x);
+    const uint32_t c1 = quantize_code<BITS>(v.y, inv_r, rnd.y);
+    const uint32_t c2 = quantize_code<BITS>(v.z, inv_r, rnd.z);
+    const uint32_t c3 = quantize_code<BITS>(v.w, inv_r, rnd.w);
+    frag[j] = c0 | (c1 << BITS) | (c2 << (2 * BITS)) | (c3 << (3 * BITS));
   }
 }
 
@@ -514,10 +507,10 @@ __device__ __forceinline__ float fused_scale(const FusedScale& f, uint32_t m, ui
   return v;
 }
 
-template <int NORM, int BITS, int WPW, int SLOTS, bool FULL, bool FUSED, bool DEFER>
+template <int NORM, int BITS, int WPW, int SLOTS, bool FUSED, bool DEFER>
 __device__ __forceinline__ void quantize_rows(const QuantLane<NORM>& q, FragmentBuffer<WPW, SLOTS>& lds, int wave, int lane,
                                               const GradRows& g, const float* __restrict__ scales,
-                                              uint32_t* __restrict__ codes, uint64_t nvec, uint64_t words,
+                                              uint32_t* __restrict__ codes, uint64_t words,
                                               uint64_t word_base, uint32_t m0, uint32_t m_end, uint32_t iter,
                                               uint32_t k0, uint32_t k1, const float* __restrict__ means,
                                               const FusedScale& fs, uint32_t M) {
@@ -532,7 +525,7 @@ __device__ __forceinline__ void quantize_rows(const QuantLane<NORM>& q, Fragment
     return FUSED ? fused_scale(fs, m, M, blockIdx.x == 0 && threadIdx.x == 0) : scales[m];
   };
   float ra = scale_of(m0), mua = mean_of(m0), rb = 0.f, mub = 0.f;
-  load_worker_tile<NORM, FULL>(q, g, m0, xa);
+  load_worker_tile<NORM>(q, g, m0, xa);
   // Steady state: both prefetches of a trip are unconditional.  A load issued under a condition
   // makes the compiler wait for all outstanding loads where the paths join (it cannot count what
   // is in flight), which would drain the prefetch before the arithmetic it is meant to overlap.
@@ -540,14 +533,14 @@ __device__ __forceinline__ void quantize_rows(const QuantLane<NORM>& q, Fragment
   for (; m + 2 < m_end; m += 2) {
     rb = scale_of(m + 1);
     mub = mean_of(m + 1);
-    load_worker_tile<NORM, FULL>(q, g, m + 1, xb);
-    quantize_worker_tile<NORM, BITS, FULL, kByReciprocal<NORM, SLOTS>>(q, xa, ra, mua, m, iter, k0, k1, frag);
+    load_worker_tile<NORM>(q, g, m + 1, xb);
+    quantize_worker_tile<NORM, BITS, kByReciprocal<NORM, SLOTS>>(q, xa, ra, mua, m, iter, k0, k1, frag);
     store_packed<BITS, WPW, SLOTS, DEFER>(lds, DEFER ? (int)(m - m0) : 0, wave, lane, frag, codes + (uint64_t)m * words, word_base,
                                           words);
     ra = scale_of(m + 2);
     mua = mean_of(m + 2);
-    load_worker_tile<NORM, FULL>(q, g, m + 2, xa);
-    quantize_worker_tile<NORM, BITS, FULL, kByReciprocal<NORM, SLOTS>>(q, xb, rb, mub, m + 1, iter, k0, k1, frag);
+    load_worker_tile<NORM>(q, g, m + 2, xa);
+    quantize_worker_tile<NORM, BITS, kByReciprocal<NORM, SLOTS>>(q, xb, rb, mub, m + 1, iter, k0, k1, frag);
     store_packed<BITS, WPW, SLOTS, DEFER>(lds, DEFER ? (int)(m + 1 - m0) : 0, wave, lane, frag,
                                           codes + (uint64_t)(m + 1) * words, word_base, words);
   }
@@ -555,25 +548,26 @@ __device__ __forceinline__ void quantize_rows(const QuantLane<NORM>& q, Fragment
   if (m + 1 < m_end) {
     rb = scale_of(m + 1);
     mub = mean_of(m + 1);
-    load_worker_tile<NORM, FULL>(q, g, m + 1, xb);
-    quantize_worker_tile<NORM, BITS, FULL, kByReciprocal<NORM, SLOTS>>(q, xa, ra, mua, m, iter, k0, k1, frag);
+    load_worker_tile<NORM>(q, g, m + 1, xb);
+    quantize_worker_tile<NORM, BITS, kByReciprocal<NORM, SLOTS>>(q, xa, ra, mua, m, iter, k0, k1, frag);
     store_packed<BITS, WPW, SLOTS, DEFER>(lds, DEFER ? (int)(m - m0) : 0, wave, lane, frag, codes + (uint64_t)m * words, word_base,
                                           words);
-    quantize_worker_tile<NORM, BITS, FULL, kByReciprocal<NORM, SLOTS>>(q, xb, rb, mub, m + 1, iter, k0, k1, frag);
+    quantize_worker_tile<NORM, BITS, kByReciprocal<NORM, SLOTS>>(q, xb, rb, mub, m + 1, iter, k0, k1, frag);
     store_packed<BITS, WPW, SLOTS, DEFER>(lds, DEFER ? (int)(m + 1 - m0) : 0, wave, lane, frag,
                                           codes + (uint64_t)(m + 1) * words, word_base, words);
   } else {
-    quantize_worker_tile<NORM, BITS, FULL, kByReciprocal<NORM, SLOTS>>(q, xa, ra, mua, m, iter, k0, k1, frag);
+    quantize_worker_tile<NORM, BITS, kByReciprocal<NORM, SLOTS>>(q, xa, ra, mua, m, iter, k0, k1, frag);
     store_packed<BITS, WPW, SLOTS, DEFER>(lds, DEFER ? (int)(m - m0) : 0, wave, lane, frag, codes + (uint64_t)m * words, word_base,
                                           words);
   }
   if (DEFER) flush_packed<WPW, SLOTS>(lds, wave, lane, codes, words, word_base, m0, m_end - m0);
 }
 
+// (128 registers, four wavefronts per SIMD, but for the combined form, whose two references do not fit that)
 template <int NORM, int BITS, int MC, bool FUSED>
-__global__ __launch_bounds__(kBlock) void quantize_pack_vec_kernel(
+__global__ __launch_bounds__(kBlock, NORM == kNormComb ? 3 : 4) void quantize_pack_vec_kernel(
     GradRows g, const float4* __restrict__ ref4, const float4* __restrict__ ref24,
-    const float* __restrict__ scales, uint32_t* __restrict__ codes, uint64_t nvec, uint64_t words,
+    const float* __restrict__ scales, uint32_t* __restrict__ codes, uint64_t d, uint64_t words, uint32_t main_blocks,
     uint32_t M, float eps, uint32_t k0, uint32_t k1, uint32_t iter, const float* __restrict__ means,
     FusedScale fs, const uint32_t* __restrict__ skip_if_set) {
   constexpr int L = kLoadsPerLane;
@@ -582,33 +576,37 @@ __global__ __launch_bounds__(kBlock) void quantize_pack_vec_kernel(
   // the codes come from the candidate slots instead (quantize_candidates_kernel) when that word is set
   if (skip_if_set != nullptr && skip_if_set[0] != 0u) return;
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  const uint64_t wave_tile = (uint64_t)blockIdx.x * kWavesPerBlock + wave;
-  const uint64_t word_base = wave_tile * WPW;
-
+  const uint64_t ntiles = d / kWaveTileElements;  // whole wavefront tiles
+  const uint32_t m0 = blockIdx.y * MC;
+  const uint32_t m_end = min(m0 + MC, M);
+  uint64_t wave_tile = (uint64_t)blockIdx.x * kWavesPerBlock + wave;
   QuantLane<NORM> q;
+  if (blockIdx.x < main_blocks) {
+    if (wave_tile >= ntiles) return;  // whole wavefronts of the last workgroup; nothing below meets the others
 #pragma unroll
-  for (int j = 0; j < L; ++j) {
-    q.iv[j] = wave_tile * (kWave * L) + (uint64_t)j * kWave + lane;
-    q.ok[j] = q.iv[j] < nvec;
-    if (q.ok[j]) {
+    for (int j = 0; j < L; ++j) {
+      q.iv[j] = wave_tile * (kWave * L) + (uint64_t)j * kWave + lane;
       q.rt[j].load(ref4, ref24, q.iv[j], eps);
       if (kByReciprocal<NORM, MC>) q.rt[j].reciprocals();
     }
-  }
-
-  const uint32_t m0 = blockIdx.y * MC;
-  const uint32_t m_end = min(m0 + MC, M);
-  if ((wave_tile + 1) * (kWave * L) <= nvec) {  // wave-uniform
-    if (MC > 1 && words % 4 == 0 && (reinterpret_cast<uintptr_t>(codes) & 15u) == 0) {  // 16-byte aligned rows
-      quantize_rows<NORM, BITS, WPW, MC, true, FUSED, true>(q, lds, wave, lane, g, scales, codes, nvec, words,
-                                                            word_base, m0, m_end, iter, k0, k1, means, fs, M);
-    } else {
-      quantize_rows<NORM, BITS, WPW, MC, true, FUSED, false>(q, lds, wave, lane, g, scales, codes, nvec, words,
-                                                             word_base, m0, m_end, iter, k0, k1, means, fs, M);
-    }
+    // (the 16-byte stores at the end of the workgroup take words at any 4-byte boundary)
+    quantize_rows<NORM, BITS, WPW, MC, FUSED, (MC > 1)>(q, lds, wave, lane, g, scales, codes, words, wave_tile * WPW, m0,
+                                                        m_end, iter, k0, k1, means, fs, M);
   } else {
-    quantize_rows<NORM, BITS, WPW, MC, false, FUSED, false>(q, lds, wave, lane, g, scales, codes, nvec, words,
-                                                            word_base, m0, m_end, iter, k0, k1, means, fs, M);
+    const uint32_t m = m0 + (blockIdx.x - main_blocks) * kWavesPerBlock + (uint32_t)wave;
+    if (m >= m_end) return;
+    const float R = FUSED ? fused_scale(fs, m, M, blockIdx.x == 0 && threadIdx.x == 0) : scales[m];
+    const float mu = NORM == kNormMean ? means[m] : 0.f;
+    float4 x[L];
+    uint32_t frag[L];
+#pragma unroll
+    for (int j = 0; j < L; ++j) {
+      q.iv[j] = ntiles * (kWave * L) + (uint64_t)j * kWave + lane;
+      q.rt[j].load_ragged(ref4, ref24, q.iv[j], d, eps);
+      x[j] = load_row_ragged(g, m, q.iv[j], d, mu);
+    }
+    quantize_worker_tile<NORM, BITS, false>(q, x, R, mu, m, iter, k0, k1, frag);
+    store_packed<BITS, WPW, MC, false>(lds, 0, wave, lane, frag, codes + (uint64_t)m * words, ntiles * WPW, words);
   }
 }
 
@@ -1026,76 +1024,22 @@ __global__ __launch_bounds__(kBlock) void quantize_candidates_kernel(
 #pragma unroll
       for (int j = 0; j < L; ++j) {
         q.iv[j] = tile * (kWave * L) + (uint64_t)j * kWave + lane;
-        q.ok[j] = true;
         q.rt[j].load(ref4, ref24, q.iv[j], eps);
       }
       float4 x[L];
       uint32_t frag[L];
-      load_worker_tile<NORM, true>(q, g, m, x);
-      quantize_worker_tile<NORM, 2, true, false>(q, x, R, 0.f, m, iter, k0, k1, frag);
+      load_worker_tile<NORM>(q, g, m, x);
+      quantize_worker_tile<NORM, 2, false>(q, x, R, 0.f, m, iter, k0, k1, frag);
       store_packed<2, WPW, MC, true>(lds, slot, wave, lane, frag, codes, word_base, words);
     }
   }
   flush_packed<WPW, MC>(lds, wave, lane, codes, words, word_base, m0, m_end - m0);
 }
 
-// Any d (rows need not be 16-byte aligned): one thread per packed word.
-template <int NORM, int BITS>
-__global__ __launch_bounds__(kBlock) void quantize_pack_scalar_kernel(
-    const float* __restrict__ g, const float* __restrict__ ref, const float* __restrict__ ref2,
-    const float* __restrict__ scales, uint32_t* __restrict__ codes, uint64_t first_word, uint64_t d,
-    uint64_t words, uint32_t M, float eps, uint32_t k0, uint32_t k1, uint32_t iter,
-    const float* __restrict__ means, FusedScale fs) {
-  constexpr int PER = 32 / BITS;
-  const uint32_t m = blockIdx.y;
-  const float mu = NORM == kNormMean ? means[m] : 0.f;
-  const float R = fs.rows != 0 ? fused_scale(fs, m, M, blockIdx.x == 0 && threadIdx.x == 0) : scales[m];
-  const float inv_r = R != 0.f ? 1.0f / R : 0.f;
-  const uint64_t stride = (uint64_t)gridDim.x * kBlock;
-  for (uint64_t wi = first_word + (uint64_t)blockIdx.x * kBlock + threadIdx.x; wi < words; wi += stride) {
-    uint32_t word = 0u;
-    if (R != 0.f) {
-#pragma unroll 1
-      for (int q = 0; q < PER / 4; ++q) {
-        const uint64_t e0 = wi * PER + (uint64_t)q * 4;
-        if (e0 >= d) break;
-        const U32x4 rnd = philox4x32_10((uint32_t)(e0 >> 2), m, iter, 0u, k0, k1);
-        const uint32_t rw[4] = {rnd.x, rnd.y, rnd.z, rnd.w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const uint64_t e = e0 + k;
-          if (e < d) {
-            float r1, r2;
-            load_ref_scalar<NORM>(ref, ref2, e, eps, r1, r2);
-            const float v = normalize_w<NORM>(g[(uint64_t)m * d + e], r1, r2, mu);
-            word |= quantize_code<BITS>(v, inv_r, rw[k]) << ((q * 4 + k) * BITS);
-          }
-        }
-      }
-    }
-    codes[(uint64_t)m * words + wi] = word;
-  }
-}
-
 // ------------------------------------------------------------------------------------------
 // Server: decode, average over workers in worker order, de-normalise (Eq. 1 / Eq. 2), and
 // optionally w <- w - lr * v and reference <- v in the same pass.
 // ------------------------------------------------------------------------------------------
-constexpr int kScaleChunk = 256;
-
-template <int BITS>
-__device__ __forceinline__ void stage_scales(const float* __restrict__ scales, uint32_t m_base, uint32_t M,
-                                             float* sR, float* sStep) {
-  constexpr float S = (float)((1 << (BITS - 1)) - 1);
-  __syncthreads();
-  if (threadIdx.x < kScaleChunk && m_base + threadIdx.x < M) {
-    const float R = scales[m_base + threadIdx.x];
-    sR[threadIdx.x] = R;
-    sStep[threadIdx.x] = R / S;
-  }
-  __syncthreads();
-}
-
 // A workgroup owns a tile of kDecodeLoads * 256 float4 (4096 coordinates).  Per worker the tile's
 // packed codes are 256 (ternary) or 512 (4-bit) consecutive words: each thread fetches one or two
 // of them with coalesced streaming loads, kDecodeWorkers workers at a time, and the words are
@@ -1108,8 +1052,8 @@ constexpr int kDecodeWorkers = 8;
 template <int NORM, int BITS, int V, bool STREAM_CODES>
 __global__ __launch_bounds__(kBlock) void decode_vec_kernel(
     const uint32_t* __restrict__ codes, const float* __restrict__ scales, const float4* ref4,
-    const float4* __restrict__ ref24, float4* __restrict__ vbar4, float4* w4, float4* refout4,
-    uint64_t nvec, uint64_t words, uint32_t M, float eps, float inv_m, float lr, const float* __restrict__ means) {
+    const float4* __restrict__ ref24, float4* __restrict__ vbar4, float4* w4, float* refout,
+    uint64_t d, uint64_t words, uint32_t M, float eps, float inv_m, float lr, const float* __restrict__ means) {
   constexpr int MCH = kDecodeWorkers;
   constexpr int FPW = 32 / (4 * BITS);     // 4-code fragments per packed word: 4 (ternary) or 2
   constexpr int WPT = (V + FPW - 1) / FPW; // packed words per thread and worker (some threads idle when V < FPW)
@@ -1175,25 +1119,32 @@ __global__ __launch_bounds__(kBlock) void decode_vec_kernel(
 #pragma unroll
   for (int v = 0; v < V; ++v) {
     const uint64_t i = vec_base + (uint64_t)v * kBlock + threadIdx.x;
-    if (i < nvec) {
+    if (4 * i < d) {
+      const bool whole = 4 * i + 4 <= d;  // all but the last float4 of a row whose length is no multiple of 4
       RefTile<NORM> rt;
-      rt.load(ref4, ref24, i, eps);
+      if (whole)
+        rt.load(ref4, ref24, i, eps);
+      else
+        rt.load_ragged(ref4, ref24, i, d, eps);
       float4 o;
       o.x = denormalize<NORM>(acc[v].x * inv_m, rt.r1.x, rt.r2.x);
       o.y = denormalize<NORM>(acc[v].y * inv_m, rt.r1.y, rt.r2.y);
       o.z = denormalize<NORM>(acc[v].z * inv_m, rt.r1.z, rt.r2.z);
       o.w = denormalize<NORM>(acc[v].w * inv_m, rt.r1.w, rt.r2.w);
-      store_stream(vbar4 + i, o);
+      if (whole)
+        store_stream(vbar4 + i, o);
+      else
+        store4_within(reinterpret_cast<float*>(vbar4), 4 * i, d, o);
       if (w4 != nullptr) {
-        float4 w = load_stream(w4 + i);
+        float4 w = whole ? load_stream(w4 + i) : load4_within(reinterpret_cast<const float*>(w4), 4 * i, d, 0.f);
         const float px = lr * o.x, py = lr * o.y, pz = lr * o.z, pw = lr * o.w;
         w.x = w.x - px;
         w.y = w.y - py;
         w.z = w.z - pz;
         w.w = w.w - pw;
-        w4[i] = w;
+        store4_within(reinterpret_cast<float*>(w4), 4 * i, d, w);
       }
-      if (refout4 != nullptr) refout4[i] = o;
+      if (refout != nullptr) store4_within(refout, 4 * i, d, o);  // (a slot of the history ring starts at any 4-byte boundary)
     }
   }
 }
@@ -1327,42 +1278,6 @@ __global__ __launch_bounds__(kBlock) void single_pass_kernel(
     }
     if (refout4 != nullptr) refout4[q] = o;
   }
-}
-
-template <int NORM, int BITS>
-__global__ __launch_bounds__(kBlock) void decode_scalar_kernel(
-    const uint32_t* __restrict__ codes, const float* __restrict__ scales, const float* ref,
-    const float* __restrict__ ref2, float* __restrict__ vbar, float* __restrict__ w, float* refout, uint64_t first,
-    uint64_t d, uint64_t words, uint32_t M, float eps, float inv_m, float lr, const float* __restrict__ means) {
-  __shared__ float sR[kScaleChunk], sStep[kScaleChunk];
-  constexpr int PER = 32 / BITS;
-  constexpr uint32_t MASK = (1u << BITS) - 1u;
-  const uint64_t e = first + (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-  const bool active = e < d;
-  const uint64_t wi = e / PER;
-  const uint32_t sh = (uint32_t)(e % PER) * BITS;
-  float acc = 0.f;
-  for (uint32_t m_base = 0; m_base < M; m_base += kScaleChunk) {
-    stage_scales<BITS>(scales, m_base, M, sR, sStep);
-    if (active) {
-      const uint32_t cnt = min((uint32_t)kScaleChunk, M - m_base);
-      for (uint32_t mm = 0; mm < cnt; ++mm) {
-        const uint32_t word = codes[(uint64_t)(m_base + mm) * words + wi];
-        const float val = decode_code<BITS>((word >> sh) & MASK, sR[mm], sStep[mm]);
-        acc = acc + (NORM == kNormMean ? means[m_base + mm] + val : val);
-      }
-    }
-  }
-  if (!active) return;
-  float r1, r2;
-  load_ref_scalar<NORM>(ref, ref2, e, eps, r1, r2);
-  const float v = denormalize<NORM>(acc * inv_m, r1, r2);
-  vbar[e] = v;
-  if (w != nullptr) {
-    const float p = lr * v;
-    w[e] = w[e] - p;
-  }
-  if (refout != nullptr) refout[e] = v;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1636,18 +1551,9 @@ inline int pick_workers_per_block(uint32_t M, uint64_t tiles, double repeat_cost
   return best;
 }
 
-// How many leading coordinates of every row the vector kernels take: all of them when d is a
-// multiple of 4, else the largest multiple of 16 (whole packed words for either code width); the
-// scalar kernels finish the rest of each row.  0: scalar kernels only (the shared operands are not
-// 16-byte aligned).
 inline bool aligned16_or_null(const void* a, const void* b, const void* c = nullptr, const void* e = nullptr) {
   auto al = [](const void* p) { return p == nullptr || (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
   return al(a) && al(b) && al(c) && al(e);
-}
-inline uint64_t vector_part(uint64_t d, const void* a, const void* b, const void* c = nullptr,
-                            const void* e = nullptr) {
-  if (!aligned16_or_null(a, b, c, e)) return 0;
-  return d % 4 == 0 ? d : d - d % 16;
 }
 
 inline bool vec_ok(uint64_t d, const void* a, const void* b, const void* c) {
@@ -1655,18 +1561,21 @@ inline bool vec_ok(uint64_t d, const void* a, const void* b, const void* c) {
   return d % 4 == 0 && al(a) && al(b) && al(c);
 }
 
+// Workgroups behind the others that take the ragged last wavefront tile of mc workers, a worker per wavefront.
+inline uint32_t tail_workgroups(uint64_t d, int mc) {
+  return d % kWaveTileElements == 0 ? 0u : (uint32_t)((mc + kWavesPerBlock - 1) / kWavesPerBlock);
+}
+
 template <int NORM, int MC>
-hipError_t absmax_vec_launch(const CodecShape& c, uint64_t dv, const float* g, const float* gref, const float* gref2,
+hipError_t absmax_vec_launch(const CodecShape& c, const float* g, const float* gref, const float* gref2,
                              float* partials, uint32_t* nblocks, hipStream_t s) {
-  const uint64_t nvec = dv / 4;
-  const uint32_t per_y = div_up_u32(nvec, (uint64_t)kBlock * kAbsmaxLoads);
-  const uint32_t cap = kAbsmaxMaxBlocks - 1;  // one row of partials is kept for the rows' scalar remainder
-  const uint32_t gx = per_y < cap ? per_y : cap;
-  *nblocks = gx;
-  dim3 grid(gx, (c.M + MC - 1) / MC);
-  hipLaunchKernelGGL((absmax_vec_kernel<NORM, MC>), grid, dim3(kBlock), 0, s, GradRows{g, c.d},
-                     reinterpret_cast<const float4*>(gref), reinterpret_cast<const float4*>(gref2), partials, nvec,
-                     c.M, c.eps, c.means);
+  const uint32_t tail = tail_workgroups(c.d, MC);
+  const uint64_t per_y = (c.d / kWaveTileElements + kWavesPerBlock - 1) / kWavesPerBlock;
+  const uint32_t main_blocks = (uint32_t)(per_y < kAbsmaxMaxBlocks - tail ? per_y : kAbsmaxMaxBlocks - tail);
+  *nblocks = main_blocks + tail;
+  dim3 grid(*nblocks, (c.M + MC - 1) / MC);
+  hipLaunchKernelGGL((absmax_vec_kernel<NORM, MC>), grid, dim3(kBlock), 0, s, GradRows{g, c.d}, reinterpret_cast<const float4*>(gref),
+                     reinterpret_cast<const float4*>(gref2), partials, c.d, main_blocks, c.M, c.eps, c.means);
   return hipGetLastError();
 }
 
@@ -1782,27 +1691,11 @@ hipError_t absmax_dispatch(const CodecShape& c, const float* g, const float* gre
                            float* partials, float* scales, hipStream_t s) {
   uint32_t nblocks = 0;
   hipError_t e;
-  const uint64_t dv = vector_part(c.d, gref, gref2);
-  if (dv != 0) {
-    const int mc = pick_workers_per_block(c.M, (dv / 4 + kBlock * kAbsmaxLoads - 1) / (kBlock * kAbsmaxLoads), 0.3);
-    switch (mc) {
-      case 8: e = absmax_vec_launch<NORM, 8>(c, dv, g, gref, gref2, partials, &nblocks, s); break;
-      case 4: e = absmax_vec_launch<NORM, 4>(c, dv, g, gref, gref2, partials, &nblocks, s); break;
-      case 2: e = absmax_vec_launch<NORM, 2>(c, dv, g, gref, gref2, partials, &nblocks, s); break;
-      default: e = absmax_vec_launch<NORM, 1>(c, dv, g, gref, gref2, partials, &nblocks, s); break;
-    }
-    if (e == hipSuccess && dv < c.d) {  // the last d - dv < 16 coordinates of every row: one more row of partials
-      hipLaunchKernelGGL((absmax_scalar_kernel<NORM>), dim3(1, c.M), dim3(kBlock), 0, s, g, gref, gref2,
-                         partials + (uint64_t)nblocks * c.M, dv, c.d, c.M, c.eps, c.means);
-      nblocks += 1;
-      e = hipGetLastError();
-    }
-  } else {
-    const uint32_t per_y = div_up_u32(c.d, kBlock);
-    nblocks = per_y < kAbsmaxMaxBlocks ? per_y : kAbsmaxMaxBlocks;
-    hipLaunchKernelGGL((absmax_scalar_kernel<NORM>), dim3(nblocks, c.M), dim3(kBlock), 0, s, g, gref, gref2,
-                       partials, (uint64_t)0, c.d, c.M, c.eps, c.means);
-    e = hipGetLastError();
+  switch (pick_workers_per_block(c.M, div_up_u32(c.d, (uint64_t)kBlock * kAbsmaxLoads * 4), 0.3)) {
+    case 8: e = absmax_vec_launch<NORM, 8>(c, g, gref, gref2, partials, &nblocks, s); break;
+    case 4: e = absmax_vec_launch<NORM, 4>(c, g, gref, gref2, partials, &nblocks, s); break;
+    case 2: e = absmax_vec_launch<NORM, 2>(c, g, gref, gref2, partials, &nblocks, s); break;
+    default: e = absmax_vec_launch<NORM, 1>(c, g, gref, gref2, partials, &nblocks, s); break;
   }
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(absmax_finish_kernel, dim3(c.M), dim3(kBlock), 0, s, partials, nblocks, c.M, scales);
@@ -1810,15 +1703,15 @@ hipError_t absmax_dispatch(const CodecShape& c, const float* g, const float* gre
 }
 
 template <int NORM, int BITS, int MC, bool FUSED>
-hipError_t quantize_vec_launch(const CodecShape& c, uint64_t dv, uint32_t iter, const float* g, const float* gref,
+hipError_t quantize_vec_launch(const CodecShape& c, uint32_t iter, const float* g, const float* gref,
                                const float* gref2, const float* scales, uint32_t* codes, const FusedScale& fs,
                                hipStream_t s, const uint32_t* skip_if_set = nullptr) {
-  const uint64_t nvec = dv / 4;
-  const uint64_t tiles = (nvec + kBlock * kLoadsPerLane - 1) / (kBlock * kLoadsPerLane);
-  dim3 grid((uint32_t)tiles, (c.M + MC - 1) / MC);
-  hipLaunchKernelGGL((quantize_pack_vec_kernel<NORM, BITS, MC, FUSED>), grid, dim3(kBlock), 0, s, GradRows{g, c.d},
-                     reinterpret_cast<const float4*>(gref), reinterpret_cast<const float4*>(gref2), scales, codes, nvec,
-                     c.words, c.M, c.eps, c.k0, c.k1, iter, c.means, fs, skip_if_set);
+  const uint32_t tail = tail_workgroups(c.d, MC);
+  const uint32_t main_blocks = (uint32_t)((c.d / kWaveTileElements + kWavesPerBlock - 1) / kWavesPerBlock);
+  dim3 grid(main_blocks + tail, (c.M + MC - 1) / MC);
+  hipLaunchKernelGGL((quantize_pack_vec_kernel<NORM, BITS, MC, FUSED>), grid, dim3(kBlock), 0, s, GradRows{g, c.d}, reinterpret_cast<const float4*>(gref),
+                     reinterpret_cast<const float4*>(gref2), scales, codes, c.d, c.words, main_blocks, c.M, c.eps, c.k0,
+                     c.k1, iter, c.means, fs, skip_if_set);
   return hipGetLastError();
 }
 
@@ -1829,41 +1722,23 @@ template <int NORM, int BITS>
 hipError_t quantize_dispatch(const CodecShape& c, uint32_t iter, const float* g, const float* gref,
                              const float* gref2, float* scales, uint32_t* codes, const float* partials,
                              uint32_t fused_rows, hipStream_t s, const uint32_t* skip_if_set) {
-  const uint64_t dv = vector_part(c.d, gref, gref2);
-  const bool vec = dv != 0;
-  const uint64_t tiles = (dv / 4 + kBlock * kLoadsPerLane - 1) / (kBlock * kLoadsPerLane);
-  const int mc = vec ? pick_workers_per_block(c.M, tiles, 0.0, 16) : 1;
+  constexpr uint64_t kTile = (uint64_t)kBlock * kLoadsPerLane * 4;
+  const int mc = pick_workers_per_block(c.M, (c.d + kTile - 1) / kTile, 0.0, 16);
   FusedScale fs{partials, fused_rows, scales};
-  if (fused_rows > kFusedScaleRows || (fused_rows > 0 && (mc != 1 || dv != c.d))) {
+  if (fused_rows > kFusedScaleRows || (fused_rows > 0 && mc != 1)) {
     hipLaunchKernelGGL(absmax_finish_kernel, dim3(c.M), dim3(kBlock), 0, s, partials, fused_rows, c.M, scales);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     fs.rows = 0;
   }
-  if (vec) {
-    hipError_t e;
-    if (fs.rows > 0) {
-      e = quantize_vec_launch<NORM, BITS, 1, true>(c, dv, iter, g, gref, gref2, scales, codes, fs, s);
-    } else {
-      switch (mc) {
-        case 16: e = quantize_vec_launch<NORM, BITS, 16, false>(c, dv, iter, g, gref, gref2, scales, codes, fs, s, skip_if_set); break;
-        case 8: e = quantize_vec_launch<NORM, BITS, 8, false>(c, dv, iter, g, gref, gref2, scales, codes, fs, s, skip_if_set); break;
-        case 4: e = quantize_vec_launch<NORM, BITS, 4, false>(c, dv, iter, g, gref, gref2, scales, codes, fs, s, skip_if_set); break;
-        case 2: e = quantize_vec_launch<NORM, BITS, 2, false>(c, dv, iter, g, gref, gref2, scales, codes, fs, s, skip_if_set); break;
-        default: e = quantize_vec_launch<NORM, BITS, 1, false>(c, dv, iter, g, gref, gref2, scales, codes, fs, s, skip_if_set); break;
-      }
-    }
-    if (e != hipSuccess || dv == c.d) return e;
-    // the last d - dv < 16 coordinates of every row: their one or two packed words, after the vector pass
-    hipLaunchKernelGGL((quantize_pack_scalar_kernel<NORM, BITS>), dim3(1, c.M), dim3(kBlock), 0, s, g, gref, gref2,
-                       scales, codes, dv * BITS / 32, c.d, c.words, c.M, c.eps, c.k0, c.k1, iter, c.means, fs);
-    return hipGetLastError();
+  if (fs.rows > 0) return quantize_vec_launch<NORM, BITS, 1, true>(c, iter, g, gref, gref2, scales, codes, fs, s);
+  switch (mc) {
+    case 16: return quantize_vec_launch<NORM, BITS, 16, false>(c, iter, g, gref, gref2, scales, codes, fs, s, skip_if_set);
+    case 8: return quantize_vec_launch<NORM, BITS, 8, false>(c, iter, g, gref, gref2, scales, codes, fs, s, skip_if_set);
+    case 4: return quantize_vec_launch<NORM, BITS, 4, false>(c, iter, g, gref, gref2, scales, codes, fs, s, skip_if_set);
+    case 2: return quantize_vec_launch<NORM, BITS, 2, false>(c, iter, g, gref, gref2, scales, codes, fs, s, skip_if_set);
+    default: return quantize_vec_launch<NORM, BITS, 1, false>(c, iter, g, gref, gref2, scales, codes, fs, s, skip_if_set);
   }
-  const uint32_t per_y = div_up_u32(c.words, kBlock);
-  dim3 grid(per_y < 65536u ? per_y : 65536u, c.M);
-  hipLaunchKernelGGL((quantize_pack_scalar_kernel<NORM, BITS>), grid, dim3(kBlock), 0, s, g, gref, gref2,
-                     scales, codes, (uint64_t)0, c.d, c.words, c.M, c.eps, c.k0, c.k1, iter, c.means, fs);
-  return hipGetLastError();
 }
 
 template <int NORM, int BITS>
@@ -1871,38 +1746,27 @@ hipError_t decode_dispatch(const CodecShape& c, const uint32_t* codes, const flo
                            const float* gref2, float* vbar, float* w, float lr, float* ref_out,
                            hipStream_t s) {
   const float inv_m = 1.0f / (float)c.M;
-  const uint64_t dv = vector_part(c.d, gref, gref2, vbar, w) != 0 ? vector_part(c.d, ref_out, nullptr) : 0;
-  if (dv != 0) {
-    const uint64_t nvec = dv / 4;
-    const uint64_t big_tiles = (nvec + kBlock * kDecodeLoads - 1) / (kBlock * kDecodeLoads);
-    // Codes that fit the 256 MiB last-level cache were just written by the quantiser and are rewritten
-    // by the next iteration: ordinary loads keep the lines resident (measured 4 % faster, and the
-    // following quantise pass too); larger code arrays are streamed (measured 17 % faster at 512 MiB).
-    const bool stream_codes = (uint64_t)c.M * c.words * sizeof(uint32_t) > (256ull << 20);
+  const uint64_t nvec = (c.d + 3) / 4;
+  const uint64_t big_tiles = (nvec + kBlock * kDecodeLoads - 1) / (kBlock * kDecodeLoads);
+  // Codes that fit the 256 MiB last-level cache were just written by the quantiser and are rewritten
+  // by the next iteration: ordinary loads keep the lines resident (measured 4 % faster, and the
+  // following quantise pass too); larger code arrays are streamed (measured 17 % faster at 512 MiB).
+  const bool stream_codes = (uint64_t)c.M * c.words * sizeof(uint32_t) > (256ull << 20);
 #define TNG_DECODE_LAUNCH(V, SC, GRID)                                                                          \
   hipLaunchKernelGGL((decode_vec_kernel<NORM, BITS, V, SC>), dim3((uint32_t)(GRID)), dim3(kBlock), 0, s, codes,  \
                      scales, reinterpret_cast<const float4*>(gref), reinterpret_cast<const float4*>(gref2),      \
-                     reinterpret_cast<float4*>(vbar), reinterpret_cast<float4*>(w),                              \
-                     reinterpret_cast<float4*>(ref_out), nvec, c.words, c.M, c.eps, inv_m, lr, c.means)
-    if (big_tiles >= 2048) {
-      if (stream_codes) {
-        TNG_DECODE_LAUNCH(kDecodeLoads, true, big_tiles);
-      } else {
-        TNG_DECODE_LAUNCH(kDecodeLoads, false, big_tiles);
-      }
-    } else {  // few coordinates: small tiles so that every compute unit still gets work
-      TNG_DECODE_LAUNCH(1, false, (nvec + kBlock - 1) / kBlock);
+                     reinterpret_cast<float4*>(vbar), reinterpret_cast<float4*>(w), ref_out, c.d, c.words, c.M,  \
+                     c.eps, inv_m, lr, c.means)
+  if (big_tiles >= 2048) {
+    if (stream_codes) {
+      TNG_DECODE_LAUNCH(kDecodeLoads, true, big_tiles);
+    } else {
+      TNG_DECODE_LAUNCH(kDecodeLoads, false, big_tiles);
     }
-#undef TNG_DECODE_LAUNCH
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || dv == c.d) return e;
-    hipLaunchKernelGGL((decode_scalar_kernel<NORM, BITS>), dim3(1), dim3(kBlock), 0, s, codes, scales, gref, gref2, vbar,
-                       w, ref_out, dv, c.d, c.words, c.M, c.eps, inv_m, lr, c.means);  // the last d - dv < 16
-    return hipGetLastError();
+  } else {  // few coordinates: small tiles so that every compute unit still gets work
+    TNG_DECODE_LAUNCH(1, false, (nvec + kBlock - 1) / kBlock);
   }
-  const uint64_t blocks = (c.d + kBlock - 1) / kBlock;
-  hipLaunchKernelGGL((decode_scalar_kernel<NORM, BITS>), dim3((uint32_t)blocks), dim3(kBlock), 0, s, codes,
-                     scales, gref, gref2, vbar, w, ref_out, (uint64_t)0, c.d, c.words, c.M, c.eps, inv_m, lr, c.means);
+#undef TNG_DECODE_LAUNCH
   return hipGetLastError();
 }
 

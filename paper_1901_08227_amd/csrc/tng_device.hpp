@@ -73,6 +73,34 @@ __device__ __forceinline__ void store4_any(float* p, uint64_t i, const float4& x
   reinterpret_cast<v4f_u_t*>(p)[i] = v;
 }
 
+// Elements e0 .. e0 + 3 as an ordinary (cached) load.
+__device__ __forceinline__ float4 load4_at(const float* p, uint64_t e0) {
+  const v4f_u_t v = *reinterpret_cast<const v4f_u_t*>(p + e0);
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+
+// Elements e0 .. e0 + 3 of an array of d floats (any 4-byte alignment), `fill` in place of those past its end: four
+// loads at indexes held inside the array, none under a branch, so that several of these are in flight together.
+__device__ __forceinline__ float4 load4_within(const float* p, uint64_t e0, uint64_t d, float fill) {
+  float v[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v[k] = p[min(e0 + k, d - 1)];
+#pragma unroll
+  for (int k = 0; k < 4; ++k) v[k] = e0 + k < d ? v[k] : fill;
+  return make_float4(v[0], v[1], v[2], v[3]);
+}
+
+// The store that goes with it: elements past the end are left out.
+__device__ __forceinline__ void store4_within(float* p, uint64_t e0, uint64_t d, const float4& x) {
+  if (e0 + 4 <= d) {
+    store4_any(p, e0 / 4, x);
+  } else {
+    if (e0 < d) p[e0] = x.x;
+    if (e0 + 1 < d) p[e0 + 1] = x.y;
+    if (e0 + 2 < d) p[e0 + 2] = x.z;
+  }
+}
+
 // The same as a streaming (non-temporal) load: shard rows are touched once per pass.
 __device__ __forceinline__ float4 load4_stream(GlobalPtr<float> p, uint64_t i) {
   const v4f_t v = __builtin_nontemporal_load(reinterpret_cast<GlobalPtr<v4f_t>>(p) + i);

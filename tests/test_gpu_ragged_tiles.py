@@ -1,0 +1,29 @@
+"""The ragged last wavefront tile (1024 coordinates) of a row in the scale, quantise and decode kernels: it has
+workgroups of its own, a worker per wavefront, next to whole tiles that take 1 to 16 workers per workgroup."""
+import pytest
+
+from gpu_util import make_ctx
+from paper_1901_08227_amd import binding as B
+from test_gpu_codec import NORMS, _check_encode_decode, _inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("norm", NORMS)
+@pytest.mark.parametrize("d", [2, 1021, 1023, 1025, 4095, 4097, 5122])
+def test_edges_of_the_last_tile(d, norm):
+    for M, bits in [(1, 2), (9, 4)]:
+        g, gref, gref2 = _inputs(M, d, seed=d + M)
+        ctx = make_ctx(d, M, bits, norm, seed=d + 3)
+        _check_encode_decode(ctx, 3, g, gref, gref2, "last tile")
+        ctx.close()
+
+
+@pytest.mark.parametrize("M,log2d", [(2, 23), (5, 22), (8, 23), (16, 23)])  # 2, 4 (a short group), 8 and 16 workers per workgroup
+def test_ragged_tail_behind_grouped_workers(M, log2d):
+    d = (1 << log2d) + 1024 + 3
+    for bits, norm in [(2, B.NORM_SUB), (4, B.NORM_QUOT)]:
+        g, gref, gref2 = _inputs(M, d, seed=M)
+        ctx = make_ctx(d, M, bits, norm, seed=M)
+        _check_encode_decode(ctx, 1, g, gref, gref2, "grouped workers")
+        ctx.close()
