@@ -66,12 +66,19 @@ __device__ __forceinline__ float absmax4(const ScaleFusion& f, const float4& g, 
                fmaxf(fabsf(normalize_dyn(f.norm, g.z, r1.z, r2.z, f.eps)), fabsf(normalize_dyn(f.norm, g.w, r1.w, r2.w, f.eps))));
 }
 
-__device__ __forceinline__ void load_refs4(const ScaleFusion& f, uint64_t q, float4& r1, float4& r2) {
+// References of elements e0 .. e0 + 3 (any 4-byte alignment).
+__device__ __forceinline__ void load_refs4(const ScaleFusion& f, uint64_t e0, float4& r1, float4& r2) {
   r1 = make_float4(0.f, 0.f, 0.f, 0.f);
   r2 = make_float4(1.f, 1.f, 1.f, 1.f);
-  if (f.norm != kNormNone) r1 = reinterpret_cast<const float4*>(f.gref)[q];
-  if (f.norm == kNormComb) r2 = reinterpret_cast<const float4*>(f.gref2)[q];
+  if (f.norm != kNormNone) r1 = load4_at(f.gref, e0);
+  if (f.norm == kNormComb) r2 = load4_at(f.gref2, e0);
 }
+
+// A thread owns the four columns 4 q .. 4 q + 3 of a row of d >= 4; the last thread of a row whose length is no
+// multiple of 4 takes the last four instead and repeats up to three columns of its neighbour's, with the same
+// operations and so the same results.  (The last d mod 4 columns had launches of their own: 14 us for three columns
+// at a minibatch of 128, one dependent load per row.)
+__device__ __forceinline__ uint64_t first_column(uint64_t q, uint64_t d) { return 4 * q + 4 <= d ? 4 * q : d - 4; }
 
 // The same two helpers with the kind of normalisation known at compile time: no branch around the loads,
 // so the compiler can count them (see the pipelined CSR gradient kernel).
@@ -174,16 +181,16 @@ __global__ __launch_bounds__(kBlock) void logreg_dense_grad_kernel(const float* 
                                                                    const float* __restrict__ resid,
                                                                    const float* __restrict__ w,
                                                                    float* __restrict__ g, uint64_t d,
-                                                                   uint64_t first_col, uint32_t batch, float inv_b,
-                                                                   float l2, ScaleFusion fuse) {
+                                                                   uint32_t batch, float inv_b, float l2,
+                                                                   ScaleFusion fuse) {
   __shared__ float sR[kBlock];
   __shared__ uint32_t sRow[kBlock];
   __shared__ float red[16];
   const uint32_t m = blockIdx.y;
   const GlobalPtr<float> X = as_global(Xs[m]);
-  const uint64_t col = first_col + (uint64_t)blockIdx.x * kBlock + threadIdx.x;  // float4 (VEC) or float index
-  const uint64_t ncol = VEC ? d / 4 : d;
-  const bool active = col < ncol;
+  const uint64_t index = (uint64_t)blockIdx.x * kBlock + threadIdx.x;  // float4 (VEC) or float index
+  const bool active = index < (VEC ? (d + 3) / 4 : d);
+  const uint64_t col = VEC ? first_column(index, d) : index;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   for (uint32_t base = 0; base < batch; base += kBlock) {
     __syncthreads();
@@ -197,7 +204,7 @@ __global__ __launch_bounds__(kBlock) void logreg_dense_grad_kernel(const float* 
       if (VEC) {
 #pragma unroll 8
         for (uint32_t i = 0; i < cnt; ++i) {
-          const float4 xv = load4_stream_any(X + (uint64_t)sRow[i] * d, col);
+          const float4 xv = load4_stream_any(X + (uint64_t)sRow[i] * d + col, 0);
           const float r = sR[i];
           acc.x = __builtin_fmaf(r, xv.x, acc.x);
           acc.y = __builtin_fmaf(r, xv.y, acc.y);
@@ -213,13 +220,13 @@ __global__ __launch_bounds__(kBlock) void logreg_dense_grad_kernel(const float* 
   float amax = 0.f;
   if (active) {
     if (VEC) {
-      const float4 wv = reinterpret_cast<const float4*>(w)[col];
+      const float4 wv = load4_at(w, col);
       float4 o;
       o.x = __builtin_fmaf(l2, wv.x, acc.x * inv_b);
       o.y = __builtin_fmaf(l2, wv.y, acc.y * inv_b);
       o.z = __builtin_fmaf(l2, wv.z, acc.z * inv_b);
       o.w = __builtin_fmaf(l2, wv.w, acc.w * inv_b);
-      store4_any(g + (uint64_t)m * d, col, o);
+      store4_any(g + (uint64_t)m * d + col, 0, o);
       if (FUSE) {
         float4 r1, r2;
         load_refs4(fuse, col, r1, r2);
@@ -254,8 +261,9 @@ __global__ __launch_bounds__(kSplitThreads) void logreg_dense_grad_split_kernel(
   const uint32_t m = blockIdx.y;
   const uint32_t tx = threadIdx.x % COLS, rg = threadIdx.x / COLS;
   const GlobalPtr<float> X = as_global(Xs[m]);
-  const uint64_t col = (uint64_t)blockIdx.x * COLS + tx;  // float4 index
-  const bool active = col < d / 4;
+  const uint64_t index = (uint64_t)blockIdx.x * COLS + tx;  // float4 index
+  const bool active = index < (d + 3) / 4;
+  const uint64_t col = first_column(index, d);
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   for (uint32_t base = 0; base < batch; base += kBlock) {
     __syncthreads();
@@ -268,7 +276,7 @@ __global__ __launch_bounds__(kSplitThreads) void logreg_dense_grad_split_kernel(
       const uint32_t cnt = min((uint32_t)kBlock, batch - base);
 #pragma unroll 8
       for (uint32_t i = rg; i < cnt; i += RG) {
-        const float4 xv = load4_stream(X + (uint64_t)sRow[i] * d, col);
+        const float4 xv = load4_stream_any(X + (uint64_t)sRow[i] * d + col, 0);
         const float r = sR[i];
         acc.x = __builtin_fmaf(r, xv.x, acc.x);
         acc.y = __builtin_fmaf(r, xv.y, acc.y);
@@ -289,13 +297,13 @@ __global__ __launch_bounds__(kSplitThreads) void logreg_dense_grad_split_kernel(
       acc.z = acc.z + p.z;
       acc.w = acc.w + p.w;
     }
-    const float4 wv = reinterpret_cast<const float4*>(w)[col];
+    const float4 wv = load4_at(w, col);
     float4 o;
     o.x = __builtin_fmaf(l2, wv.x, acc.x * inv_b);
     o.y = __builtin_fmaf(l2, wv.y, acc.y * inv_b);
     o.z = __builtin_fmaf(l2, wv.z, acc.z * inv_b);
     o.w = __builtin_fmaf(l2, wv.w, acc.w * inv_b);
-    reinterpret_cast<float4*>(g + (uint64_t)m * d)[col] = o;
+    store4_any(g + (uint64_t)m * d + col, 0, o);
     if (FUSE) {
       float4 r1, r2;
       load_refs4(fuse, col, r1, r2);
@@ -517,7 +525,7 @@ __global__ __launch_bounds__(kBlock) void logreg_dense_parts_kernel(const float*
     reinterpret_cast<float4*>(g + (uint64_t)m * d)[col] = o;
     if (FUSE) {
       float4 r1, r2;
-      load_refs4(fuse, col, r1, r2);
+      load_refs4(fuse, 4 * col, r1, r2);
       amax = absmax4(fuse, o, r1, r2);
     }
   }
@@ -1025,7 +1033,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_kernel(const int32_t* co
   float4 r1[kPer], r2[kPer];
   if (FUSE) {
 #pragma unroll
-    for (int k = 0; k < kPer; ++k) load_refs4(fuse, c0 / 4 + (uint32_t)k * kCsrThreads + threadIdx.x, r1[k], r2[k]);
+    for (int k = 0; k < kPer; ++k) load_refs4(fuse, c0 + 4 * ((uint32_t)k * kCsrThreads + threadIdx.x), r1[k], r2[k]);
   }
   const CsrEntries<PAIRS> e(cols[m], vals[m]);
   const uint32_t group = threadIdx.x / kCsrLanes, gl = threadIdx.x % kCsrLanes;
@@ -1432,52 +1440,37 @@ __device__ __forceinline__ float4 gaussian4(const NoiseGen& gen, uint64_t block,
   return make_float4(gen.sigma * (ra * ca), gen.sigma * (ra * sa), gen.sigma * (rb * cb), gen.sigma * (rb * sb));
 }
 
-__global__ __launch_bounds__(kBlock) void rosenbrock_kernel(const float* __restrict__ x,
-                                                            const float* __restrict__ noise, NoiseGen gen,
-                                                            float* __restrict__ g, uint64_t first, uint64_t d,
-                                                            uint32_t M) {
-  const uint64_t stride = (uint64_t)gridDim.x * kBlock;
-  for (uint64_t i = first + (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < d; i += stride) {
-    const float base = rosenbrock_component(i > 0 ? x[i - 1] : 0.f, x[i], i + 1 < d ? x[i + 1] : 0.f, i > 0, i + 1 < d);
-    for (uint32_t m = 0; m < M; ++m) {
-      const uint64_t o = (uint64_t)m * d + i;
-      if (gen.sigma > 0.f) {
-        const float4 z = gaussian4(gen, i >> 2, m);
-        const uint32_t c = (uint32_t)(i & 3);
-        g[o] = base + (c == 0 ? z.x : c == 1 ? z.y : c == 2 ? z.z : z.w);
-      } else {
-        g[o] = noise != nullptr ? base + noise[o] : base;
-      }
-    }
-  }
-}
-
-// The first 4 * (d / 4) coordinates: a thread owns 4 consecutive ones; the gradient is computed once
-// and reused for all workers, the noise is streamed with 16-byte loads (rows of noise and g start at
-// any 4-byte boundary when d is not a multiple of 4).
-template <bool FUSE>
+// A thread owns 4 consecutive coordinates; the gradient is computed once and reused for all workers, the noise is
+// streamed with 16-byte loads (rows of noise and g start at any 4-byte boundary when d is not a multiple of 4).  The
+// last thread of such a row (TAIL) has fewer than 4: what lies beyond is read as 0, kept out of the maximum and not
+// stored.  (A variant of its own: its checks cost whole rows 5 % at d = 2^20, M = 8.)
+template <bool FUSE, bool TAIL>
 __global__ __launch_bounds__(kBlock) void rosenbrock_vec_kernel(const float* __restrict__ x,
                                                                 const float* __restrict__ noise, NoiseGen gen,
                                                                 float* __restrict__ g, uint64_t d, uint32_t M,
                                                                 ScaleFusion fuse) {
   constexpr int MC = 8;  // workers per trip: their noise loads are all in flight before the first is used
   __shared__ float red[kWavesPerBlock][MC];
-  const uint64_t nvec = d / 4;
+  const uint64_t nvec = (d + 3) / 4;
   const uint64_t q = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
   const bool active = q < nvec;
   const uint64_t qc = active ? q : nvec - 1;  // idle threads of the last workgroup repeat its last float4 (and store nothing)
   float4 base, r1, r2;
   {
-    const float4 xv = reinterpret_cast<const float4*>(x)[qc];
+    const float4 xv = TAIL ? load4_within(x, 4 * qc, d, 0.f) : reinterpret_cast<const float4*>(x)[qc];
     const bool first = qc == 0, last = 4 * qc + 4 >= d;
     const float xl = first ? 0.f : x[4 * qc - 1];
     const float xr = last ? 0.f : x[4 * qc + 4];
-    base.x = rosenbrock_component(xl, xv.x, xv.y, !first, true);
-    base.y = rosenbrock_component(xv.x, xv.y, xv.z, true, true);
-    base.z = rosenbrock_component(xv.y, xv.z, xv.w, true, true);
+    base.x = rosenbrock_component(xl, xv.x, xv.y, !first, !TAIL || 4 * qc + 1 < d);
+    base.y = rosenbrock_component(xv.x, xv.y, xv.z, true, !TAIL || 4 * qc + 2 < d);
+    base.z = rosenbrock_component(xv.y, xv.z, xv.w, true, !TAIL || 4 * qc + 3 < d);
     base.w = rosenbrock_component(xv.z, xv.w, xr, true, !last);
-    r1 = r2 = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (FUSE) load_refs4(fuse, qc, r1, r2);
+    r1 = make_float4(0.f, 0.f, 0.f, 0.f);
+    r2 = make_float4(1.f, 1.f, 1.f, 1.f);
+    if (FUSE && fuse.norm != kNormNone)
+      r1 = TAIL ? load4_within(fuse.gref, 4 * qc, d, 1.f) : reinterpret_cast<const float4*>(fuse.gref)[qc];
+    if (FUSE && fuse.norm == kNormComb)
+      r2 = TAIL ? load4_within(fuse.gref2, 4 * qc, d, 1.f) : reinterpret_cast<const float4*>(fuse.gref2)[qc];
   }
   const bool from_tensor = !(gen.sigma > 0.f) && noise != nullptr;
   const bool generated = gen.sigma > 0.f;
@@ -1486,7 +1479,8 @@ __global__ __launch_bounds__(kBlock) void rosenbrock_vec_kernel(const float* __r
     if (from_tensor) {
 #pragma unroll
       for (int k = 0; k < MC; ++k)  // worker index clamped: a load, never a branch
-        n[k] = load4_stream_any(as_global(noise) + (uint64_t)min(m0 + k, M - 1) * d, qc);
+        n[k] = TAIL ? load4_within(noise + (uint64_t)min(m0 + k, M - 1) * d, 4 * qc, d, 0.f)
+                    : load4_stream_any(as_global(noise) + (uint64_t)min(m0 + k, M - 1) * d, qc);
     }
     float amax[MC];
 #pragma unroll
@@ -1502,8 +1496,20 @@ __global__ __launch_bounds__(kBlock) void rosenbrock_vec_kernel(const float* __r
           o.w = base.w + n[k].w;
         }
         if (active) {
-          store4_any(g + (uint64_t)(m0 + k) * d, q, o);
-          if (FUSE) amax[k] = absmax4(fuse, o, r1, r2);
+          if (TAIL)
+            store4_within(g + (uint64_t)(m0 + k) * d, 4 * q, d, o);
+          else
+            store4_any(g + (uint64_t)(m0 + k) * d, q, o);
+          if (FUSE) {
+            float4 v = o;
+            if (TAIL && 4 * q + 4 > d) {  // 0 (or the reference itself, which the difference forms take to 0) past the end
+              const float none = fuse.norm == kNormSub || fuse.norm == kNormComb ? 1.f : 0.f;
+              if (4 * q + 1 >= d) v.y = none;
+              if (4 * q + 2 >= d) v.z = none;
+              v.w = none;
+            }
+            amax[k] = absmax4(fuse, v, r1, r2);
+          }
         }
       }
     }
@@ -1598,9 +1604,8 @@ hipError_t launch_logreg_dense_grad(const LogregData& p, uint64_t d, uint32_t M,
     return hipGetLastError();
   }
   // Rows of X and of g start at any 4-byte boundary when d is not a multiple of 4: the vector kernels
-  // read and write them with 16-byte accesses that assume no more, over the first 4 * (d / 4) columns.
-  const bool vec = d >= 4 && aligned16(w);
-  const bool whole = d % 4 == 0;
+  // read and write them with 16-byte accesses that assume no more.
+  const bool vec = d >= 4;
   const float inv_b = 1.0f / (float)batch;
   dim3 grid_r(batch, M);
   if (vec && (uint64_t)M * (batch / 4) >= 1024) {  // enough rows to keep the chip busy four at a time
@@ -1611,12 +1616,11 @@ hipError_t launch_logreg_dense_grad(const LogregData& p, uint64_t d, uint32_t M,
                        d, batch, k0, k1, iter);
   }
   if (vec) {
-    dim3 grid_g((uint32_t)((d / 4 + kBlock - 1) / kBlock), M);
-    // the fused scale pass sees the vector part only, so it needs all of d there
-    const bool can_fuse = whole && fuse != nullptr && fused_rows != nullptr && grid_g.x <= kAbsmaxMaxBlocks &&
-                          aligned16(fuse->gref) && aligned16(fuse->gref2);
-    if (whole && aligned16(g)) {  // a handful of workgroups: split the rows
-      const uint32_t narrow = (uint32_t)((d / 4 + 31) / 32);
+    const uint64_t nvec = (d + 3) / 4;
+    dim3 grid_g((uint32_t)((nvec + kBlock - 1) / kBlock), M);
+    const bool can_fuse = fuse != nullptr && fused_rows != nullptr && grid_g.x <= kAbsmaxMaxBlocks;
+    {  // a handful of workgroups: split the rows
+      const uint32_t narrow = (uint32_t)((nvec + 31) / 32);
 #define TNG_SPLIT(COLS, GX, F)                                                                                        \
   hipLaunchKernelGGL((logreg_dense_grad_split_kernel<COLS, F>), dim3(GX, M), dim3(kSplitThreads), 0, s, p.X, idx, resid, \
                      w, g, d, batch, inv_b, l2, F ? *fuse : ScaleFusion{})
@@ -1642,21 +1646,18 @@ hipError_t launch_logreg_dense_grad(const LogregData& p, uint64_t d, uint32_t M,
     }
     if (can_fuse) {
       hipLaunchKernelGGL((logreg_dense_grad_kernel<true, true>), grid_g, dim3(kBlock), 0, s, p.X, idx, resid, w, g, d,
-                         (uint64_t)0, batch, inv_b, l2, *fuse);
+                         batch, inv_b, l2, *fuse);
       *fused_rows = grid_g.x;
     } else {
       hipLaunchKernelGGL((logreg_dense_grad_kernel<true, false>), grid_g, dim3(kBlock), 0, s, p.X, idx, resid, w, g, d,
-                         (uint64_t)0, batch, inv_b, l2, ScaleFusion{});
+                         batch, inv_b, l2, ScaleFusion{});
     }
-    if (!whole)  // the last d mod 4 columns
-      hipLaunchKernelGGL((logreg_dense_grad_kernel<false, false>), dim3(1, M), dim3(kBlock), 0, s, p.X, idx, resid, w, g,
-                         d, 4 * (d / 4), batch, inv_b, l2, ScaleFusion{});
   } else {
     hipLaunchKernelGGL((logreg_dense_resid_kernel<false, 1>), grid_r, dim3(kBlock), 0, s, p.X, p.y, p.n_rows, idx, w,
                        resid, d, batch, k0, k1, iter);
     dim3 grid_g((uint32_t)((d + kBlock - 1) / kBlock), M);
     hipLaunchKernelGGL((logreg_dense_grad_kernel<false, false>), grid_g, dim3(kBlock), 0, s, p.X, idx, resid, w, g, d,
-                       (uint64_t)0, batch, inv_b, l2, ScaleFusion{});
+                       batch, inv_b, l2, ScaleFusion{});
   }
   return hipGetLastError();
 }
@@ -1824,25 +1825,12 @@ hipError_t launch_logreg_csr_grad(const LogregData& p, uint64_t d, uint32_t M, u
 hipError_t launch_rosenbrock_grad(uint64_t d, uint32_t M, const float* x, const float* noise, NoiseGen gen, float* g,
                                   const ScaleFusion* fuse, uint32_t* fused_rows, hipStream_t s) {
   if (fused_rows != nullptr) *fused_rows = 0;
-  if (d >= 4 && aligned16(x)) {
-    const uint64_t nvec = d / 4;
-    const uint32_t blocks = (uint32_t)((nvec + kBlock - 1) / kBlock);
-    // the fused scale pass sees the vector part only, so it needs all of d there
-    if (d % 4 == 0 && fuse != nullptr && fused_rows != nullptr && blocks <= kAbsmaxMaxBlocks && aligned16(fuse->gref) &&
-        aligned16(fuse->gref2)) {
-      hipLaunchKernelGGL(rosenbrock_vec_kernel<true>, dim3(blocks), dim3(kBlock), 0, s, x, noise, gen, g, d, M, *fuse);
-      *fused_rows = blocks;
-    } else {
-      hipLaunchKernelGGL(rosenbrock_vec_kernel<false>, dim3(blocks), dim3(kBlock), 0, s, x, noise, gen, g, d, M,
-                         ScaleFusion{});
-    }
-    if (d % 4 != 0)  // the last d mod 4 coordinates
-      hipLaunchKernelGGL(rosenbrock_kernel, dim3(1), dim3(kBlock), 0, s, x, noise, gen, g, 4 * nvec, d, M);
-    return hipGetLastError();
-  }
-  const uint64_t bx = (d + kBlock - 1) / kBlock;
-  hipLaunchKernelGGL(rosenbrock_kernel, dim3((uint32_t)(bx < 16384 ? bx : 16384)), dim3(kBlock), 0, s, x, noise, gen,
-                     g, (uint64_t)0, d, M);
+  const uint32_t blocks = (uint32_t)(((d + 3) / 4 + kBlock - 1) / kBlock);
+  const bool fused = fuse != nullptr && fused_rows != nullptr && blocks <= kAbsmaxMaxBlocks;
+  auto kernel = d % 4 == 0 ? (fused ? rosenbrock_vec_kernel<true, false> : rosenbrock_vec_kernel<false, false>)
+                           : (fused ? rosenbrock_vec_kernel<true, true> : rosenbrock_vec_kernel<false, true>);
+  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), 0, s, x, noise, gen, g, d, M, fused ? *fuse : ScaleFusion{});
+  if (fused) *fused_rows = blocks;
   return hipGetLastError();
 }
 
