@@ -204,17 +204,15 @@ bool single_pass_ok(const tng_ctx* ctx, const float* g, const float* gref, const
   return ctx->prof_slots == 0 && tng::single_pass_applies(ctx->shape, g, gref, ctx->gref2, vbar, w, ref_out);
 }
 
-// fused_rows > 0: a gradient kernel has already left that many rows of partial maxima in the
-// workspace, only their reduction remains of the scale pass.
-tng_status encode_impl(tng_ctx* ctx, uint32_t iter, const float* g, const float* gref, uint32_t* codes,
-                       float* scales, uint32_t fused_rows = 0) {
-  if (fused_rows == 0 && single_pass_ok(ctx, g, gref, nullptr, nullptr, nullptr))  // tiny problems: one launch
-    return hip_status(tng::launch_single_pass(ctx->shape, iter, g, gref, ctx->gref2, scales, codes, false, nullptr,
-                                              nullptr, 0.f, nullptr, ctx->stream));
-  const uint64_t call = ctx->enc_calls++;
-  mark(ctx, call, 0);
+// The scale pass.  fused_rows > 0: a gradient kernel has already left that many rows of partial maxima in the
+// workspace, only their reduction remains.  On return *rows is the number of rows of partial maxima whose reduction
+// is left to the next launch (0: scales is complete; the pass leaves at most max_left of its own), and
+// *by_candidates tells that the candidate slots hold what the quantise pass needs.
+tng_status scale_impl(tng_ctx* ctx, uint32_t iter, const float* g, const float* gref, const uint32_t* codes,
+                      float* scales, uint32_t fused_rows, uint32_t max_left, uint32_t* rows, bool* by_candidates) {
   hipError_t e = hipSuccess;
-  bool by_candidates = false;
+  *rows = 0;
+  *by_candidates = false;
   const bool mean_ref = ctx->cfg.norm == TNG_NORM_MEAN;
   if (mean_ref) {  // the worker's own reference comes first; the maximum of |g - mu| comes out of the same pass
     e = tng::launch_worker_means(ctx->shape, g, ctx->sums, ctx->shape.means,
@@ -226,26 +224,44 @@ tng_status encode_impl(tng_ctx* ctx, uint32_t iter, const float* g, const float*
   } else if (ctx->cfg.scale == TNG_SCALE_L2) {
     e = tng::launch_l2_scales(ctx->shape, g, gref, ctx->gref2, ctx->sums, scales, ctx->stream);
   } else if (fused_rows > 0) {
-    // the reduction of the fused partial maxima is left to the quantise launch
+    *rows = fused_rows;
   } else if (ctx->cand != nullptr && tng::candidates_apply(ctx->shape, g, gref, ctx->gref2, codes)) {
     // long rows of ternary codes: the scale pass also picks out the elements that can code non-zero, and the
     // quantise pass works from those instead of reading g again
-    by_candidates = true;
+    *by_candidates = true;
     e = tng::launch_absmax_candidates(ctx->shape, iter, g, gref, ctx->gref2, ctx->partials, ctx->cand, scales,
                                       ctx->stream);
   } else {
-    e = tng::launch_absmax(ctx->shape, g, gref, ctx->gref2, ctx->partials, scales, ctx->stream);
+    e = tng::launch_absmax(ctx->shape, g, gref, ctx->gref2, ctx->partials, scales, max_left, rows, ctx->stream);
   }
-  if (e != hipSuccess) return TNG_ERR_HIP;
-  mark(ctx, call, 1);
-  const bool fused = fused_rows > 0 && !mean_ref && ctx->cfg.scale == TNG_SCALE_MAX;
-  if (by_candidates)
-    e = tng::launch_quantize_candidates(ctx->shape, iter, g, gref, ctx->gref2, scales, ctx->cand, codes, ctx->stream);
-  else
-    e = tng::launch_quantize_pack(ctx->shape, iter, g, gref, ctx->gref2, scales, codes, ctx->partials,
-                                  fused ? fused_rows : 0u, ctx->stream);
-  mark(ctx, call, 2);
   return hip_status(e);
+}
+
+tng_status quantize_impl(tng_ctx* ctx, uint32_t iter, const float* g, const float* gref, uint32_t* codes, float* scales,
+                         uint32_t rows, bool by_candidates) {
+  if (by_candidates)
+    return hip_status(tng::launch_quantize_candidates(ctx->shape, iter, g, gref, ctx->gref2, scales, ctx->cand, codes,
+                                                      ctx->stream));
+  return hip_status(tng::launch_quantize_pack(ctx->shape, iter, g, gref, ctx->gref2, scales, codes, ctx->partials, rows,
+                                              ctx->stream));
+}
+
+tng_status encode_impl(tng_ctx* ctx, uint32_t iter, const float* g, const float* gref, uint32_t* codes,
+                       float* scales, uint32_t fused_rows = 0) {
+  if (fused_rows == 0 && single_pass_ok(ctx, g, gref, nullptr, nullptr, nullptr))  // tiny problems: one launch
+    return hip_status(tng::launch_single_pass(ctx->shape, iter, g, gref, ctx->gref2, scales, codes, false, nullptr,
+                                              nullptr, 0.f, nullptr, ctx->stream));
+  const uint64_t call = ctx->enc_calls++;
+  uint32_t rows = 0;
+  bool by_candidates = false;
+  mark(ctx, call, 0);
+  tng_status s = scale_impl(ctx, iter, g, gref, codes, scales, fused_rows, tng::quantize_fused_rows(ctx->shape), &rows,
+                            &by_candidates);
+  if (s != TNG_OK) return s;
+  mark(ctx, call, 1);
+  s = quantize_impl(ctx, iter, g, gref, codes, scales, rows, by_candidates);
+  mark(ctx, call, 2);
+  return s;
 }
 
 tng_status decode_impl(tng_ctx* ctx, const uint32_t* codes, const float* scales, const float* gref, float* vbar,
@@ -660,7 +676,21 @@ tng_status tng_step(tng_ctx* ctx, uint32_t iter, float* w, float* gref, float* g
     s = hip_status(tng::launch_single_pass(ctx->shape, iter, g, gref, ctx->gref2, scales, codes, true, vbar, w, c.lr,
                                            ref_out, ctx->stream));
     if (s != TNG_OK) return s;
-  } else {
+  } else if (ctx->prof_slots == 0 && tng::quantize_decode_applies(ctx->shape)) {
+    uint32_t rows = 0;
+    bool by_candidates = false;
+    s = scale_impl(ctx, iter, g, gref, codes, scales, fused_rows, tng::quantize_decode_rows(ctx->shape), &rows,
+                   &by_candidates);
+    if (s != TNG_OK) return s;
+    if (by_candidates) {
+      s = quantize_impl(ctx, iter, g, gref, codes, scales, rows, true);
+      if (s == TNG_OK) s = decode_impl(ctx, codes, scales, gref, vbar, w, ref_out);
+    } else {
+      s = hip_status(tng::launch_quantize_decode(ctx->shape, iter, g, gref, ctx->gref2, scales, codes, ctx->partials,
+                                                 rows, vbar, w, c.lr, ref_out, ctx->stream));
+    }
+    if (s != TNG_OK) return s;
+  } else {  // the separate passes, which timing events mark one by one
     s = encode_impl(ctx, iter, g, gref, codes, scales, fused_rows);
     if (s != TNG_OK) return s;
     s = decode_impl(ctx, codes, scales, gref, vbar, w, ref_out);

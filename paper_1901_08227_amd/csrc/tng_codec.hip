@@ -19,7 +19,7 @@ namespace tng {
 namespace {
 
 constexpr int kWavesPerBlock = kBlock / kWave;
-constexpr uint32_t kFusedScaleRows = 8;  // at most this many rows of partial maxima are reduced by the quantiser itself
+constexpr uint32_t kFusedScaleRows = 256;  // at most this many rows of partial maxima are reduced by the quantiser itself
 constexpr int kLoadsPerLane = 4;  // float4 loads per lane and worker in the quantiser tile
 constexpr uint64_t kWaveTileElements = (uint64_t)kWave * kLoadsPerLane * 4;  // coordinates per wavefront tile
 constexpr uint32_t kMaxGridX = 1u << 20;
@@ -490,9 +490,9 @@ __device__ __forceinline__ void flush_packed(FragmentBuffer<WPW, SLOTS>& lds, in
 // Worker loop of one wavefront tile, software pipelined two workers per trip so that the two
 // register sets swap roles without copies: the loads of worker m+1 are in flight while the codes
 // of worker m are computed.
-// Small problems: the scale pass was fused into the gradient kernel and left only a few rows of
-// per-workgroup maxima (partials[row][m]); the quantiser then takes their maximum itself instead of
-// waiting for a reduction kernel of its own, and the first workgroup publishes scales[m].
+// Small problems: the scale pass left at most kFusedScaleRows rows of per-workgroup maxima (partials[row][m]);
+// the quantiser then takes their maximum itself, a row per lane, instead of waiting for a reduction kernel of its
+// own, and the first workgroup publishes scales[m].
 struct FusedScale {
   const float* partials;
   uint32_t rows;
@@ -501,7 +501,8 @@ struct FusedScale {
 
 __device__ __forceinline__ float fused_scale(const FusedScale& f, uint32_t m, uint32_t M, bool publish) {
   float v = 0.f;
-  for (uint32_t b = 0; b < f.rows; ++b) v = fmaxf(v, f.partials[(uint64_t)b * M + m]);
+  for (uint32_t b = threadIdx.x % kWave; b < f.rows; b += kWave) v = fmaxf(v, f.partials[(uint64_t)b * M + m]);
+  v = wave_max_nonneg(v);
   v = v < FLT_MIN ? 0.f : v;
   if (publish) f.out[m] = v;
   return v;
@@ -1150,6 +1151,244 @@ __global__ __launch_bounds__(kBlock) void decode_vec_kernel(
 }
 
 // ------------------------------------------------------------------------------------------
+// Workers and server in one launch (tng_step): quantise and pack every worker's part of a tile and, with the codes
+// still at hand, decode, average, de-normalise and update.
+//
+// What bounds an iteration of a small problem is the number of its launches (2.5 to 4 us each, whatever they
+// do); what a larger one saves is the second trip of the codes and the references through memory.  A thread
+// owns one float4 of coordinates and walks the workers, kTailWorkers rows of loads in flight.  (Requesting the row
+// eight workers further as soon as one is used measured no faster: 465 against 444 us at d = 2^24, M = 16.)
+// Iterations with given gradients, the separate launches against this one: d = 10007, M = 8, 4-bit 26.4 -> 8.9 us;
+// d = 2^18, M = 8 16.6 -> 9.6; d = 2^20, M = 8 24.4 -> 24.5; d = 4e6, M = 8 82.6 -> 70.8; d = 2^24, M = 64, 4-bit
+// 1792 -> 1673.
+// The scales come from the partial maxima of the scale pass (partials[rows][M], reduced by every workgroup for
+// itself: rows * M <= kTailPartials floats, a few KiB out of the L2) or, rows == 0, from scales.
+// ------------------------------------------------------------------------------------------
+constexpr int kTailWorkers = 8;
+constexpr uint32_t kTailMaxWorkers = 64;
+constexpr uint32_t kTailPartials = 2048;
+
+// The M <= kTailMaxWorkers scales (as bits) for the whole workgroup; the first workgroup publishes them.
+__device__ __forceinline__ void reduce_scales(uint32_t* sScale, float* scales, const float* partials, uint32_t rows,
+                                              uint32_t M) {
+  if (threadIdx.x < M) sScale[threadIdx.x] = rows != 0 ? 0u : __float_as_uint(scales[threadIdx.x]);
+  __syncthreads();
+  if (rows == 0) return;
+  const uint32_t used = kBlock / M * M;  // a thread stays with one worker
+  if (threadIdx.x < used) {
+    float v = 0.f;
+#pragma unroll 8
+    for (uint32_t i = threadIdx.x; i < rows * M; i += used) v = fmaxf(v, partials[i]);
+    atomicMax(&sScale[threadIdx.x % M], __float_as_uint(v < FLT_MIN ? 0.f : v));  // non-negative: ordered as integers
+  }
+  __syncthreads();
+  if (blockIdx.x == 0 && threadIdx.x < M) scales[threadIdx.x] = __uint_as_float(sScale[threadIdx.x]);
+}
+
+template <int NORM, int BITS>
+__global__ __launch_bounds__(kBlock) void quantize_decode_kernel(
+    GradRows g, const float4* ref4, const float4* __restrict__ ref24, float* __restrict__ scales,
+    uint32_t* __restrict__ codes, uint64_t d, uint64_t words, uint32_t M, float eps, uint32_t k0, uint32_t k1,
+    uint32_t iter, const float* __restrict__ means, const float* __restrict__ partials, uint32_t rows,
+    float4* __restrict__ vbar4, float4* w4, float* refout, float inv_m, float lr) {
+  constexpr int MC = kTailWorkers;
+  constexpr int WPW = kWave * 4 * BITS / 32;  // packed words per wavefront and worker
+  constexpr float S = (float)((1 << (BITS - 1)) - 1);
+  constexpr bool RECIP = NORM == kNormQuot || NORM == kNormComb;
+  __shared__ FragmentBuffer<WPW, MC> lds;
+  __shared__ uint32_t sScale[kTailMaxWorkers];
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const uint64_t q = (uint64_t)blockIdx.x * kBlock + threadIdx.x;  // the thread's float4
+  const uint64_t wave_tile = (uint64_t)blockIdx.x * kWavesPerBlock + wave;
+  const bool whole = (wave_tile + 1) * (kWave * 4) <= d;  // the wavefront's 256 coordinates lie inside the row
+
+  float4 x[MC];
+  auto load_rows = [&](uint32_t m0) {  // rows past M repeat the last one: no load under a condition
+    if (whole) {
+#pragma unroll
+      for (int mm = 0; mm < MC; ++mm) x[mm] = load_row_stream(g.row(min(m0 + (uint32_t)mm, M - 1)) + q);
+    } else {
+#pragma unroll
+      for (int mm = 0; mm < MC; ++mm) {
+        const uint32_t m = min(m0 + (uint32_t)mm, M - 1);
+        x[mm] = load_row_ragged(g, m, q, d, NORM == kNormMean ? means[m] : 0.f);
+      }
+    }
+  };
+  load_rows(0);
+  RefTile<NORM> rt;
+  float4 w = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (whole) {
+    rt.load(ref4, ref24, q, eps);
+    w = load_stream(w4 + q);
+  } else {
+    rt.load_ragged(ref4, ref24, q, d, eps);
+    w = load4_within(reinterpret_cast<const float*>(w4), 4 * q, d, 0.f);
+  }
+
+  reduce_scales(sScale, scales, partials, rows, M);
+  rt.reciprocals();
+
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (uint32_t m0 = 0; m0 < M; m0 += MC) {
+    if (m0 != 0) load_rows(m0);
+    const uint32_t count = min((uint32_t)MC, M - m0);
+#pragma unroll
+    for (int mm = 0; mm < MC; ++mm) {
+      if ((uint32_t)mm < count) {
+        const uint32_t m = m0 + (uint32_t)mm;
+        const float R = __uint_as_float(sScale[m]);
+        const float mu = NORM == kNormMean ? means[m] : 0.f;
+        const float4 v = normalize4<NORM, RECIP>(x[mm], rt, mu);
+        uint32_t frag = 0u;
+        float4 val = make_float4(0.f, 0.f, 0.f, 0.f);  // what the server decodes
+        if (R != 0.f) {
+          const float inv_r = 1.0f / R, step = R / S;
+          const U32x4 rnd = philox4x32_10((uint32_t)q, m, iter, 0u, k0, k1);
+          const uint32_t c0 = quantize_and_value<BITS>(v.x, inv_r, rnd.x, R, step, val.x);
+          const uint32_t c1 = quantize_and_value<BITS>(v.y, inv_r, rnd.y, R, step, val.y);
+          const uint32_t c2 = quantize_and_value<BITS>(v.z, inv_r, rnd.z, R, step, val.z);
+          const uint32_t c3 = quantize_and_value<BITS>(v.w, inv_r, rnd.w, R, step, val.w);
+          frag = c0 | (c1 << BITS) | (c2 << (2 * BITS)) | (c3 << (3 * BITS));
+        }
+        if (BITS == 2)
+          lds.b8[mm][wave][lane] = (uint8_t)frag;
+        else
+          lds.b16[mm][wave][lane] = (uint16_t)frag;
+        if (NORM == kNormMean) val = make_float4(mu + val.x, mu + val.y, mu + val.z, mu + val.w);
+        acc.x = acc.x + val.x;  // in worker order
+        acc.y = acc.y + val.y;
+        acc.z = acc.z + val.z;
+        acc.w = acc.w + val.w;
+      }
+    }
+    wave_lds_fence();
+    for (uint32_t i = (uint32_t)lane; i < count * WPW; i += kWave) {
+      const uint32_t mm = i / WPW, j = i % WPW;
+      const uint64_t wi = wave_tile * WPW + j;
+      if (wi < words) store_word_through(codes + (uint64_t)(m0 + mm) * words + wi, lds.b32[mm][wave][j]);
+    }
+    wave_lds_fence();
+  }
+
+  float4 o;
+  o.x = denormalize<NORM>(acc.x * inv_m, rt.r1.x, rt.r2.x);
+  o.y = denormalize<NORM>(acc.y * inv_m, rt.r1.y, rt.r2.y);
+  o.z = denormalize<NORM>(acc.z * inv_m, rt.r1.z, rt.r2.z);
+  o.w = denormalize<NORM>(acc.w * inv_m, rt.r1.w, rt.r2.w);
+  const float px = lr * o.x, py = lr * o.y, pz = lr * o.z, pw = lr * o.w;
+  w.x = w.x - px;
+  w.y = w.y - py;
+  w.z = w.z - pz;
+  w.w = w.w - pw;
+  if (whole) {
+    store_stream(vbar4 + q, o);
+    w4[q] = w;
+  } else {
+    store4_within(reinterpret_cast<float*>(vbar4), 4 * q, d, o);
+    store4_within(reinterpret_cast<float*>(w4), 4 * q, d, w);
+  }
+  if (refout != nullptr) store4_within(refout, 4 * q, d, o);  // (a slot of the history ring starts at any 4-byte boundary)
+}
+
+// The same where the coordinates alone leave the chip idle: a workgroup takes 256 coordinates, its wavefronts a
+// worker each in turn (a wavefront of the kernel above walks all M workers, 0.6 us each), and once the codes of
+// all workers are in LDS every thread decodes one coordinate, in worker order, by a table of the values.
+template <int NORM, int BITS>
+__global__ __launch_bounds__(kBlock) void quantize_decode_split_kernel(
+    GradRows g, const float* ref, const float* __restrict__ ref2, float* __restrict__ scales,
+    uint32_t* __restrict__ codes, uint64_t d, uint64_t words, uint32_t M, float eps, uint32_t k0, uint32_t k1,
+    uint32_t iter, const float* __restrict__ means, const float* __restrict__ partials, uint32_t rows,
+    float* __restrict__ vbar, float* w, float* refout, float inv_m, float lr) {
+  constexpr int MC = 4;                       // rows of loads in flight per wavefront
+  constexpr int WPW = kWave * 4 * BITS / 32;  // packed words per workgroup and worker
+  constexpr int TAB = 1 << BITS;
+  constexpr uint32_t MASK = (1u << BITS) - 1u;
+  constexpr float S = (float)((1 << (BITS - 1)) - 1);
+  __shared__ union {
+    lds_u8 b8[kTailMaxWorkers][kWave];
+    lds_u16 b16[kTailMaxWorkers][kWave];
+    lds_u32 b32[kTailMaxWorkers][WPW];
+  } buf;
+  __shared__ uint32_t sScale[kTailMaxWorkers];
+  __shared__ float table[kTailMaxWorkers * TAB];
+  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const uint64_t q = (uint64_t)blockIdx.x * kWave + lane;  // the lane's float4
+  const uint64_t e = (uint64_t)blockIdx.x * kBlock + threadIdx.x;  // the coordinate that the thread decodes
+  const bool whole = ((uint64_t)blockIdx.x + 1) * kBlock <= d;
+
+  float4 x[MC];
+  auto load_rows = [&](uint32_t i0) {  // the wavefront's workers number i0 .. i0 + MC - 1
+#pragma unroll
+    for (int i = 0; i < MC; ++i) {
+      const uint32_t m = min((i0 + i) * kWavesPerBlock + (uint32_t)wave, M - 1);
+      x[i] = whole ? load_row_stream(g.row(m) + q) : load_row_ragged(g, m, q, d, NORM == kNormMean ? means[m] : 0.f);
+    }
+  };
+  load_rows(0);
+  RefTile<NORM> rt;
+  if (whole)
+    rt.load(reinterpret_cast<const float4*>(ref), reinterpret_cast<const float4*>(ref2), q, eps);
+  else
+    rt.load_ragged(reinterpret_cast<const float4*>(ref), reinterpret_cast<const float4*>(ref2), q, d, eps);
+  const uint64_t ec = min(e, d - 1);
+  float r1, r2;
+  load_ref_scalar<NORM>(ref, ref2, ec, eps, r1, r2);
+  const float w0 = w[ec];
+  reduce_scales(sScale, scales, partials, rows, M);
+  for (uint32_t i = threadIdx.x; i < M * TAB; i += kBlock) {
+    const float R = __uint_as_float(sScale[i / TAB]);
+    const float val = decode_code<BITS>(i % TAB, R, R / S);
+    table[i] = NORM == kNormMean ? means[i / TAB] + val : val;
+  }
+
+  for (uint32_t i0 = 0; i0 * kWavesPerBlock < M; i0 += MC) {
+    if (i0 != 0) load_rows(i0);
+#pragma unroll
+    for (int i = 0; i < MC; ++i) {
+      const uint32_t m = (i0 + i) * kWavesPerBlock + (uint32_t)wave;
+      if (m < M) {
+        const float R = __uint_as_float(sScale[m]);
+        uint32_t frag = 0u;
+        if (R != 0.f) {
+          const float inv_r = 1.0f / R;
+          const U32x4 rnd = philox4x32_10((uint32_t)q, m, iter, 0u, k0, k1);
+          const float4 v = normalize4<NORM, false>(x[i], rt, NORM == kNormMean ? means[m] : 0.f);
+          const uint32_t c0 = quantize_code<BITS>(v.x, inv_r, rnd.x);
+          const uint32_t c1 = quantize_code<BITS>(v.y, inv_r, rnd.y);
+          const uint32_t c2 = quantize_code<BITS>(v.z, inv_r, rnd.z);
+          const uint32_t c3 = quantize_code<BITS>(v.w, inv_r, rnd.w);
+          frag = c0 | (c1 << BITS) | (c2 << (2 * BITS)) | (c3 << (3 * BITS));
+        }
+        if (BITS == 2)
+          buf.b8[m][lane] = (uint8_t)frag;
+        else
+          buf.b16[m][lane] = (uint16_t)frag;
+      }
+    }
+  }
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < M * WPW; i += kBlock) {
+    const uint32_t m = i / WPW, j = i % WPW;
+    const uint64_t wi = (uint64_t)blockIdx.x * WPW + j;
+    if (wi < words) store_word_through(codes + (uint64_t)m * words + wi, buf.b32[m][j]);
+  }
+  float acc = 0.f;
+#pragma unroll 8
+  for (uint32_t m = 0; m < M; ++m) {
+    const uint32_t f = BITS == 2 ? (uint32_t)buf.b8[m][threadIdx.x >> 2] : (uint32_t)buf.b16[m][threadIdx.x >> 2];
+    acc = acc + table[m * TAB + ((f >> (BITS * (threadIdx.x & 3u))) & MASK)];
+  }
+  if (e < d) {
+    const float o = denormalize<NORM>(acc * inv_m, r1, r2);
+    const float p = lr * o;
+    vbar[e] = o;
+    w[e] = w0 - p;
+    if (refout != nullptr) refout[e] = o;
+  }
+}
+
+// ------------------------------------------------------------------------------------------
 // One workgroup for tiny problems (d <= 4 * kBlock): scale, quantise and pack, and (DECODE) the
 // server side as well, in one launch.
 //
@@ -1688,7 +1927,7 @@ hipError_t quantize_candidates_dispatch(const CodecShape& c, uint32_t iter, cons
 
 template <int NORM>
 hipError_t absmax_dispatch(const CodecShape& c, const float* g, const float* gref, const float* gref2,
-                           float* partials, float* scales, hipStream_t s) {
+                           float* partials, float* scales, uint32_t max_left, uint32_t* left_rows, hipStream_t s) {
   uint32_t nblocks = 0;
   hipError_t e;
   switch (pick_workers_per_block(c.M, div_up_u32(c.d, (uint64_t)kBlock * kAbsmaxLoads * 4), 0.3)) {
@@ -1698,6 +1937,10 @@ hipError_t absmax_dispatch(const CodecShape& c, const float* g, const float* gre
     default: e = absmax_vec_launch<NORM, 1>(c, g, gref, gref2, partials, &nblocks, s); break;
   }
   if (e != hipSuccess) return e;
+  if (nblocks <= max_left) {
+    *left_rows = nblocks;
+    return hipSuccess;
+  }
   hipLaunchKernelGGL(absmax_finish_kernel, dim3(c.M), dim3(kBlock), 0, s, partials, nblocks, c.M, scales);
   return hipGetLastError();
 }
@@ -1715,6 +1958,11 @@ hipError_t quantize_vec_launch(const CodecShape& c, uint32_t iter, const float* 
   return hipGetLastError();
 }
 
+inline int quantize_workers_per_block(const CodecShape& c) {
+  constexpr uint64_t kTile = (uint64_t)kBlock * kLoadsPerLane * 4;
+  return pick_workers_per_block(c.M, (c.d + kTile - 1) / kTile, 0.0, 16);
+}
+
 // fused_rows > 0: scales is an output and the scale is taken from the first fused_rows rows of
 // partials (see FusedScale); only problems small enough for one worker per workgroup go that way,
 // larger ones get the reduction kernel first.
@@ -1722,8 +1970,7 @@ template <int NORM, int BITS>
 hipError_t quantize_dispatch(const CodecShape& c, uint32_t iter, const float* g, const float* gref,
                              const float* gref2, float* scales, uint32_t* codes, const float* partials,
                              uint32_t fused_rows, hipStream_t s, const uint32_t* skip_if_set) {
-  constexpr uint64_t kTile = (uint64_t)kBlock * kLoadsPerLane * 4;
-  const int mc = pick_workers_per_block(c.M, (c.d + kTile - 1) / kTile, 0.0, 16);
+  const int mc = quantize_workers_per_block(c);
   FusedScale fs{partials, fused_rows, scales};
   if (fused_rows > kFusedScaleRows || (fused_rows > 0 && mc != 1)) {
     hipLaunchKernelGGL(absmax_finish_kernel, dim3(c.M), dim3(kBlock), 0, s, partials, fused_rows, c.M, scales);
@@ -1822,13 +2069,14 @@ hipError_t launch_absmax_finish(const float* partials, uint32_t nblocks, uint32_
 }
 
 hipError_t launch_absmax(const CodecShape& c, const float* g, const float* gref, const float* gref2,
-                         float* partials, float* scales, hipStream_t s) {
+                         float* partials, float* scales, uint32_t max_left, uint32_t* left_rows, hipStream_t s) {
+  *left_rows = 0;
   switch (c.norm) {
-    case kNormNone: return absmax_dispatch<kNormNone>(c, g, nullptr, nullptr, partials, scales, s);
-    case kNormSub: return absmax_dispatch<kNormSub>(c, g, gref, nullptr, partials, scales, s);
-    case kNormQuot: return absmax_dispatch<kNormQuot>(c, g, gref, nullptr, partials, scales, s);
-    case kNormMean: return absmax_dispatch<kNormMean>(c, g, nullptr, nullptr, partials, scales, s);
-    default: return absmax_dispatch<kNormComb>(c, g, gref, gref2, partials, scales, s);
+    case kNormNone: return absmax_dispatch<kNormNone>(c, g, nullptr, nullptr, partials, scales, max_left, left_rows, s);
+    case kNormSub: return absmax_dispatch<kNormSub>(c, g, gref, nullptr, partials, scales, max_left, left_rows, s);
+    case kNormQuot: return absmax_dispatch<kNormQuot>(c, g, gref, nullptr, partials, scales, max_left, left_rows, s);
+    case kNormMean: return absmax_dispatch<kNormMean>(c, g, nullptr, nullptr, partials, scales, max_left, left_rows, s);
+    default: return absmax_dispatch<kNormComb>(c, g, gref, gref2, partials, scales, max_left, left_rows, s);
   }
 }
 
@@ -1970,6 +2218,62 @@ hipError_t launch_quantize_pack(const CodecShape& c, uint32_t iter, const float*
     default: TNG_Q(kNormComb, gref, gref2);
   }
 #undef TNG_Q
+}
+
+uint32_t quantize_fused_rows(const CodecShape& c) { return quantize_workers_per_block(c) == 1 ? kFusedScaleRows : 0; }
+
+namespace {
+// A workgroup per 256 coordinates with the workers dealt to its wavefronts, or a thread per float4 that walks the
+// workers?  The first up to one wavefront of coordinates per SIMD (d = 2^18; iteration with given gradients, M = 16,
+// 4-bit, quotient: 14.7 against 17.9 us), and from 17 workers on at any length, where the second has too few loads
+// in flight (d = 2^22, M = 32: 218 against 235 us; d = 2^24, M = 64: 1673 against 1699); the second everywhere else
+// (d = 2^20, M = 8: 24.5 against 28.0 us; d = 2^24, M = 8: 247 against 275).
+inline bool tail_by_wavefronts(const CodecShape& c) { return c.d <= (1u << 18) || c.M > 16; }
+template <int NORM, int BITS>
+hipError_t quantize_decode_dispatch(const CodecShape& c, uint32_t iter, const float* g, const float* gref,
+                                    const float* gref2, float* scales, uint32_t* codes, const float* partials,
+                                    uint32_t rows, float* vbar, float* w, float lr, float* ref_out, hipStream_t s) {
+  if (tail_by_wavefronts(c)) {
+    hipLaunchKernelGGL((quantize_decode_split_kernel<NORM, BITS>), dim3((uint32_t)((c.d + kBlock - 1) / kBlock)),
+                       dim3(kBlock), 0, s, GradRows{g, c.d}, gref, gref2, scales, codes, c.d, c.words, c.M, c.eps, c.k0,
+                       c.k1, iter, c.means, partials, rows, vbar, w, ref_out, 1.0f / (float)c.M, lr);
+    return hipGetLastError();
+  }
+  const uint32_t blocks = (uint32_t)(((c.d + 3) / 4 + kBlock - 1) / kBlock);
+  hipLaunchKernelGGL((quantize_decode_kernel<NORM, BITS>), dim3(blocks), dim3(kBlock), 0, s, GradRows{g, c.d},
+                     reinterpret_cast<const float4*>(gref), reinterpret_cast<const float4*>(gref2), scales, codes, c.d,
+                     c.words, c.M, c.eps, c.k0, c.k1, iter, c.means, partials, rows, reinterpret_cast<float4*>(vbar),
+                     reinterpret_cast<float4*>(w), ref_out, 1.0f / (float)c.M, lr);
+  return hipGetLastError();
+}
+}  // namespace
+
+bool quantize_decode_applies(const CodecShape& c) { return c.M <= kTailMaxWorkers; }
+
+uint32_t quantize_decode_rows(const CodecShape& c) { return kTailPartials / c.M; }
+
+hipError_t launch_quantize_decode(const CodecShape& c, uint32_t iter, const float* g, const float* gref,
+                                  const float* gref2, float* scales, uint32_t* codes, const float* partials,
+                                  uint32_t rows, float* vbar, float* w, float lr, float* ref_out, hipStream_t s) {
+  if (!quantize_decode_applies(c)) return hipErrorInvalidValue;
+  if (rows > quantize_decode_rows(c)) {
+    const hipError_t e = launch_absmax_finish(partials, rows, c.M, scales, s);
+    if (e != hipSuccess) return e;
+    rows = 0;
+  }
+#define TNG_QD(NORM, R1, R2)                                                                                          \
+  return c.bits == 2 ? quantize_decode_dispatch<NORM, 2>(c, iter, g, R1, R2, scales, codes, partials, rows, vbar, w,  \
+                                                         lr, ref_out, s)                                              \
+                     : quantize_decode_dispatch<NORM, 4>(c, iter, g, R1, R2, scales, codes, partials, rows, vbar, w,  \
+                                                         lr, ref_out, s)
+  switch (c.norm) {
+    case kNormNone: TNG_QD(kNormNone, nullptr, nullptr);
+    case kNormSub: TNG_QD(kNormSub, gref, nullptr);
+    case kNormQuot: TNG_QD(kNormQuot, gref, nullptr);
+    case kNormMean: TNG_QD(kNormMean, nullptr, nullptr);
+    default: TNG_QD(kNormComb, gref, gref2);
+  }
+#undef TNG_QD
 }
 
 namespace {

@@ -247,6 +247,25 @@ __device__ __forceinline__ float decode_code(uint32_t code, float r, float step)
   return (neg && level != 0u) ? -mag : mag;
 }
 
+// quantize_code and, in val, decode_code of its result (up to the sign of a zero, which no sum that starts at +0
+// shows): the level is at hand as a number and the sign as that of v.
+template <int BITS>
+__device__ __forceinline__ uint32_t quantize_and_value(float v, float inv_r, uint32_t word, float r, float step, float& val) {
+  constexpr float S = (float)((1 << (BITS - 1)) - 1);
+  if (BITS == 2) {
+    const bool one = uniform24(word) < fabsf(v) * inv_r;
+    val = one ? copysignf(r, v) : 0.0f;
+    return one ? ((__float_as_uint(v) >> 30) & 2u) | 1u : 0u;
+  }
+  const float x = fminf(fabsf(v) * inv_r, 1.0f) * S;
+  const float lo = floorf(x);
+  const float level = uniform24(word) < x - lo ? lo + 1.0f : lo;
+  const float mag = level == S ? r : step * level;
+  const bool neg = v < 0.0f;
+  val = neg ? -mag : mag;
+  return (uint32_t)level | (neg && level != 0.0f ? 1u << (BITS - 1) : 0u);
+}
+
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, kWave));

@@ -30,9 +30,10 @@ hipError_t launch_rng_draws(uint32_t k0, uint32_t k1, uint32_t iter, uint32_t wo
 constexpr uint32_t kAbsmaxMaxBlocks = 4096;
 
 // scales[m] = max_e |normalize(g[m][e])|, 0 when below FLT_MIN.  partials: device scratch of
-// kAbsmaxMaxBlocks * M floats.  Two launches: partial maxima per workgroup, then one reduction.
+// kAbsmaxMaxBlocks * M floats.  Two launches: partial maxima per workgroup, then one reduction; where the partial
+// maxima are at most max_left rows, the reduction is left to the next launch (*left_rows rows, else 0).
 hipError_t launch_absmax(const CodecShape& c, const float* g, const float* gref, const float* gref2,
-                         float* partials, float* scales, hipStream_t s);
+                         float* partials, float* scales, uint32_t max_left, uint32_t* left_rows, hipStream_t s);
 // Order-pinned float64 sums per worker (4096-element chunks of 256 strided lanes, chunks in groups of
 // 256, everything added in index order).  sums: device scratch of tree_sum_scratch(d, M) doubles.
 // launch_worker_means: means[m] = float(sum_e g[m][e] / d); if scales != nullptr also
@@ -86,6 +87,17 @@ hipError_t launch_quantize_pack(const CodecShape& c, uint32_t iter, const float*
 hipError_t launch_decode(const CodecShape& c, const uint32_t* codes, const float* scales,
                          const float* gref, const float* gref2, float* vbar, float* w, float lr,
                          float* ref_out, hipStream_t s);
+
+// Rows of partial maxima that launch_quantize_pack reduces without a launch of its own (0: none).
+uint32_t quantize_fused_rows(const CodecShape& c);
+
+// launch_quantize_pack and launch_decode (with w) in one launch, bit for bit: for tng_step.  rows > 0: that many rows
+// of partial maxima instead of scales, as fused_rows above; up to quantize_decode_rows of them are reduced inside.
+bool quantize_decode_applies(const CodecShape& c);
+uint32_t quantize_decode_rows(const CodecShape& c);
+hipError_t launch_quantize_decode(const CodecShape& c, uint32_t iter, const float* g, const float* gref,
+                                  const float* gref2, float* scales, uint32_t* codes, const float* partials,
+                                  uint32_t rows, float* vbar, float* w, float lr, float* ref_out, hipStream_t s);
 
 // Tiny problems (d <= 1024 and a multiple of 4, M <= 16, largest-magnitude scale, no per-worker mean,
 // 16-byte aligned operands): scale, quantise and pack in ONE single-workgroup launch, and with

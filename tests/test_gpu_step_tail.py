@@ -1,0 +1,41 @@
+"""Quantise, decode and update in one launch (tng_step): either kernel at the edges of its tiles (256 coordinates per
+wavefront or workgroup), of its groups of workers (4 and 8) and of the rule that chooses, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import tng_oracle as O
+from gpu_util import DEV, buffers, make_ctx, oracle_cfg, u32
+from paper_1901_08227_amd import binding as B
+from test_gpu_codec import _inputs
+
+pytestmark = pytest.mark.gpu
+
+ALL = [(n, B.SCALE_MAX) for n in (B.NORM_NONE, B.NORM_SUB, B.NORM_QUOT, B.NORM_COMB, B.NORM_MEAN)] + [(B.NORM_SUB, B.SCALE_L2)]
+
+
+@pytest.mark.parametrize("d,M", [(1, 1), (2, 3), (255, 64), (256, 17), (1023, 5), (1028, 16), (5001, 33), (70001, 64),
+                                 (1 << 18, 8), ((1 << 18) + 1, 8), ((1 << 18) + 254, 9), ((1 << 18) + 1024, 16),
+                                 ((1 << 18) + 257, 17), ((1 << 19) + 3, 7), (4099, 65)])
+def test_step_equals_the_oracle(d, M):
+    for i, (norm, scale) in enumerate(ALL):
+        bits = 2 + 2 * ((i + d) % 2)
+        g, gref, gref2 = _inputs(M, d, seed=d + i)
+        g, gref, gref2 = g.to(DEV), gref.to(DEV).clone(), gref2.to(DEV)
+        if M > 2:
+            g[2] = gref  # a worker with nothing to send (Eq. 1): its scale is 0
+        ctx = make_ctx(d, M, bits, norm, seed=d, lr=0.05, ref_period=1, scale=scale, problem=B.PROB_EXTERNAL)
+        if norm == B.NORM_COMB:
+            ctx.set_second_reference(gref2)
+        if norm == B.NORM_MEAN:
+            means = torch.zeros(M, device=DEV)
+            ctx.set_worker_means(means)
+        buf = buffers(ctx)
+        w = torch.linspace(-1.0, 1.0, d, device=DEV)
+        want = O.step(oracle_cfg(ctx), 3, w.cpu().numpy(), gref.cpu().numpy(), g.cpu().numpy(), gref2.cpu().numpy())
+        ctx.step(3, w, gref, g, buf["codes"], buf["scales"], buf["vbar"])
+        torch.cuda.synchronize()
+        got = (w.cpu().numpy(), gref.cpu().numpy(), u32(buf["codes"]), buf["scales"].cpu().numpy(), buf["vbar"].cpu().numpy())
+        for name, a, b in zip(("iterate", "reference", "codes", "scales", "average"), got, want):
+            assert np.array_equal(a, b), f"d={d} M={M} norm={norm} scale={scale} bits={bits}: {name}"
+        ctx.close()
