@@ -242,7 +242,7 @@ __global__ __launch_bounds__(kBlock) void logreg_dense_grad_kernel(const float* 
   }
 }
 
-// The same for problems with few columns (a handful of workgroups in all): 1024 threads, COLS float4
+// The same for problems with few columns: 1024 threads, COLS float4
 // columns times RG row groups; the minibatch rows are dealt round-robin to the row groups, which run
 // side by side, and their partial sums are added in the fixed order ((p0 + p1) + p2) + ...  Cuts the
 // chain of dependent row fetches to 1/RG; narrow column blocks (32 x 32) also spread a tiny problem
@@ -1619,30 +1619,24 @@ hipError_t launch_logreg_dense_grad(const LogregData& p, uint64_t d, uint32_t M,
     const uint64_t nvec = (d + 3) / 4;
     dim3 grid_g((uint32_t)((nvec + kBlock - 1) / kBlock), M);
     const bool can_fuse = fuse != nullptr && fused_rows != nullptr && grid_g.x <= kAbsmaxMaxBlocks;
-    {  // a handful of workgroups: split the rows
-      const uint32_t narrow = (uint32_t)((nvec + 31) / 32);
-#define TNG_SPLIT(COLS, GX, F)                                                                                        \
-  hipLaunchKernelGGL((logreg_dense_grad_split_kernel<COLS, F>), dim3(GX, M), dim3(kSplitThreads), 0, s, p.X, idx, resid, \
-                     w, g, d, batch, inv_b, l2, F ? *fuse : ScaleFusion{})
-      if (narrow <= 8 && batch >= 64) {  // d <= 1024; up to 8 rows of fused maxima are reduced by the quantiser itself
-        if (can_fuse) {
-          TNG_SPLIT(32, narrow, true);
-          *fused_rows = narrow;
-        } else {
-          TNG_SPLIT(32, narrow, false);
-        }
-        return hipGetLastError();
-      }
-      if ((uint64_t)grid_g.x * M <= 128 && batch >= 16) {
-        if (can_fuse) {
-          TNG_SPLIT(256, grid_g.x, true);
-          *fused_rows = grid_g.x;
-        } else {
-          TNG_SPLIT(256, grid_g.x, false);
-        }
-        return hipGetLastError();
-      }
-#undef TNG_SPLIT
+    // A thread per float4 column leaves loads too few and chains of dependent rows too long where the columns of all
+    // workers are few: the rows are split between row groups then, in blocks of 32, 64 or 128 columns as there are
+    // more of them.  Iterations with blocks of 32 / 64 / 128 / 256 columns / unsplit: d = 1500, M = 4, B = 64 13.9 /
+    // 14.7 / 14.9 / 17.1 / - us; d = 2048, M = 32, B = 256 35.8 / 34.6 / 36.9 / 45.3 / -; d = 10007, M = 8, B = 128
+    // 31.4 / 28.0 / 26.5 / 31.0 / -; M = 32, B = 512 249 / 230 / 231 / 248 / 243; d = 65535, M = 16, B = 200 362 /
+    // 326 / 323 / 321 / 318; few rows to split: d = 65535, M = 4, B = 16 39 / 31 / 28.0 / 27.9 / 27.2.
+    const uint64_t columns = nvec * M;
+    if (batch >= 16 && (columns <= (batch >= 64 ? 3u << 16 : 1u << 15) || (batch >= 64 && nvec <= 256))) {
+      const uint32_t block = columns < 2048 || nvec <= 256 ? 32 : columns <= 16384 ? 64 : 128;
+      const dim3 grid((uint32_t)((nvec + block - 1) / block), M);
+      const bool fused = fuse != nullptr && fused_rows != nullptr && grid.x <= kAbsmaxMaxBlocks;
+      const ScaleFusion f = fused ? *fuse : ScaleFusion{};
+      auto kernel = block == 32   ? (fused ? logreg_dense_grad_split_kernel<32, true> : logreg_dense_grad_split_kernel<32, false>)
+                    : block == 64 ? (fused ? logreg_dense_grad_split_kernel<64, true> : logreg_dense_grad_split_kernel<64, false>)
+                                  : (fused ? logreg_dense_grad_split_kernel<128, true> : logreg_dense_grad_split_kernel<128, false>);
+      hipLaunchKernelGGL(kernel, grid, dim3(kSplitThreads), 0, s, p.X, idx, resid, w, g, d, batch, inv_b, l2, f);
+      if (fused) *fused_rows = grid.x;
+      return hipGetLastError();
     }
     if (can_fuse) {
       hipLaunchKernelGGL((logreg_dense_grad_kernel<true, true>), grid_g, dim3(kBlock), 0, s, p.X, idx, resid, w, g, d,
