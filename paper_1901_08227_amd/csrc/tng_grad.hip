@@ -1428,23 +1428,59 @@ __device__ __forceinline__ float rosenbrock_component(float xp, float xi, float 
   return base;
 }
 
-// Four standard normal deviates times sigma from one Philox block (Box-Muller; see NoiseGen).  The
-// angle is handed to sincospi as the exact number 2 u2, so there is no argument-reduction error.
+// sqrt(-2 ln u1) for u1 = ((word >> 8) + 1) 2^-24 in (0, 1]: the hardware's binary logarithm times -2 ln 2 (in two
+// parts), then the square root by its reciprocal and one correction.  The argument is 0 or between 2^-23 and 34, so
+// neither needs the library functions' care for subnormals, infinities and NaNs.
+__device__ __forceinline__ float gaussian_radius(uint32_t word) {
+  const float u = (float)((word >> 8) + 1u) * 0x1p-24f;
+  const float l = __builtin_amdgcn_logf(u);
+  const float x = __builtin_fmaf(l, -0x1.62e43p+0f, l * 0x1.05c61p-28f);
+  const float y = __builtin_amdgcn_rsqf(x);
+  const float root = x * y;
+  const float r = __builtin_fmaf(__builtin_fmaf(-root, root, x), 0.5f * y, root);
+  return x > 0.f ? r : 0.f;
+}
+
+// sin and cos of 2 pi u2, u2 = (word >> 8) 2^-24.  The word's top bits are the quadrant, what is left of it is t in
+// [-1/2, 1/2) quarter turns, exactly; sin(pi t / 2) and cos(pi t / 2) are polynomials fitted to the least largest
+// relative error, the leading term of each in two parts.  Against the library functions over all 2^24 words, in
+// units of 2^-24: sine and cosine 0.75 at most, 0.25 in the mean square (0.85 and 0.25), the radius above 2.14 and
+// 0.585 times its size (the same).
+__device__ __forceinline__ void sincos_turn(uint32_t word, float& sine, float& cosine) {
+  const float t = (float)(int32_t)((word << 2) & 0xFFFFFC00u) * 0x1p-32f;
+  const float q = t * t;
+  float ps = __builtin_fmaf(q, -0x1.2dc84cp-8f, 0x1.466004p-4f);
+  ps = __builtin_fmaf(q, ps, -0x1.4abbbep-1f);
+  ps = __builtin_fmaf(q, ps, -0x1.777a5cp-25f);
+  const float s = __builtin_fmaf(t, 0x1.921fb6p+0f, t * ps);
+  float pc = __builtin_fmaf(q, 0x1.d4a424p-11f, -0x1.55b1e0p-6f);
+  pc = __builtin_fmaf(q, pc, 0x1.03c1b0p-2f);
+  const float c0 = __builtin_fmaf(q, -0x1.3bd3ccp+0f, 1.0f);
+  const float rest = __builtin_fmaf(q, -0x1.3bd3ccp+0f, 1.0f - c0);
+  const float c = c0 + __builtin_fmaf(q, q * pc, rest);
+  const uint32_t turn = word + 0x20000000u;  // quadrant in the top two bits
+  const bool odd = (turn & 0x40000000u) != 0u;
+  sine = __uint_as_float(__float_as_uint(odd ? c : s) ^ (turn & 0x80000000u));
+  cosine = __uint_as_float(__float_as_uint(odd ? s : c) ^ ((turn + 0x40000000u) & 0x80000000u));
+}
+
+// Four standard normal deviates times sigma from one Philox block (Box-Muller; see NoiseGen).
 __device__ __forceinline__ float4 gaussian4(const NoiseGen& gen, uint64_t block, uint32_t m) {
   const U32x4 r = philox4x32_10((uint32_t)block, m, gen.iter, 2u, gen.k0, gen.k1);
-  const float ua = (float)((r.x >> 8) + 1u) * 0x1p-24f, ub = (float)((r.z >> 8) + 1u) * 0x1p-24f;
-  const float ra = sqrtf(-2.0f * logf(ua)), rb = sqrtf(-2.0f * logf(ub));
+  const float ra = gaussian_radius(r.x), rb = gaussian_radius(r.z);
   float sa, ca, sb, cb;
-  sincospif(2.0f * uniform24(r.y), &sa, &ca);
-  sincospif(2.0f * uniform24(r.w), &sb, &cb);
+  sincos_turn(r.y, sa, ca);
+  sincos_turn(r.w, sb, cb);
   return make_float4(gen.sigma * (ra * ca), gen.sigma * (ra * sa), gen.sigma * (rb * cb), gen.sigma * (rb * sb));
 }
 
 // A thread owns 4 consecutive coordinates; the gradient is computed once and reused for all workers, the noise is
 // streamed with 16-byte loads (rows of noise and g start at any 4-byte boundary when d is not a multiple of 4).  The
 // last thread of such a row (TAIL) has fewer than 4: what lies beyond is read as 0, kept out of the maximum and not
-// stored.  (A variant of its own: its checks cost whole rows 5 % at d = 2^20, M = 8.)
-template <bool FUSE, bool TAIL>
+// stored.  (A variant of its own: its checks cost whole rows 5 % at d = 2^20, M = 8.)  With generated noise (GEN) the
+// kernel is bound by the vector unit -- Philox, logarithm, root, sine and cosine for every element -- so the kind of
+// normalisation is a template argument too, and nothing in the worker loop branches.
+template <int NORM, bool FUSE, bool TAIL, bool GEN>
 __global__ __launch_bounds__(kBlock) void rosenbrock_vec_kernel(const float* __restrict__ x,
                                                                 const float* __restrict__ noise, NoiseGen gen,
                                                                 float* __restrict__ g, uint64_t d, uint32_t M,
@@ -1467,13 +1503,12 @@ __global__ __launch_bounds__(kBlock) void rosenbrock_vec_kernel(const float* __r
     base.w = rosenbrock_component(xv.z, xv.w, xr, true, !last);
     r1 = make_float4(0.f, 0.f, 0.f, 0.f);
     r2 = make_float4(1.f, 1.f, 1.f, 1.f);
-    if (FUSE && fuse.norm != kNormNone)
+    if (FUSE && NORM != kNormNone)
       r1 = TAIL ? load4_within(fuse.gref, 4 * qc, d, 1.f) : reinterpret_cast<const float4*>(fuse.gref)[qc];
-    if (FUSE && fuse.norm == kNormComb)
+    if (FUSE && NORM == kNormComb)
       r2 = TAIL ? load4_within(fuse.gref2, 4 * qc, d, 1.f) : reinterpret_cast<const float4*>(fuse.gref2)[qc];
   }
-  const bool from_tensor = !(gen.sigma > 0.f) && noise != nullptr;
-  const bool generated = gen.sigma > 0.f;
+  const bool from_tensor = !GEN && noise != nullptr;
   for (uint32_t m0 = 0; m0 < M; m0 += MC) {
     float4 n[MC];
     if (from_tensor) {
@@ -1488,8 +1523,8 @@ __global__ __launch_bounds__(kBlock) void rosenbrock_vec_kernel(const float* __r
       amax[k] = 0.f;
       if (m0 + k < M) {
         float4 o = base;
-        if (generated) n[k] = gaussian4(gen, qc, m0 + k);
-        if (generated || from_tensor) {
+        if (GEN) n[k] = gaussian4(gen, qc, m0 + k);
+        if (GEN || from_tensor) {
           o.x = base.x + n[k].x;
           o.y = base.y + n[k].y;
           o.z = base.z + n[k].z;
@@ -1503,12 +1538,12 @@ __global__ __launch_bounds__(kBlock) void rosenbrock_vec_kernel(const float* __r
           if (FUSE) {
             float4 v = o;
             if (TAIL && 4 * q + 4 > d) {  // 0 (or the reference itself, which the difference forms take to 0) past the end
-              const float none = fuse.norm == kNormSub || fuse.norm == kNormComb ? 1.f : 0.f;
+              const float none = NORM == kNormSub || NORM == kNormComb ? 1.f : 0.f;
               if (4 * q + 1 >= d) v.y = none;
               if (4 * q + 2 >= d) v.z = none;
               v.w = none;
             }
-            amax[k] = absmax4(fuse, v, r1, r2);
+            amax[k] = absmax4_t<NORM>(fuse, v, r1, r2);
           }
         }
       }
@@ -1821,9 +1856,27 @@ hipError_t launch_rosenbrock_grad(uint64_t d, uint32_t M, const float* x, const 
   if (fused_rows != nullptr) *fused_rows = 0;
   const uint32_t blocks = (uint32_t)(((d + 3) / 4 + kBlock - 1) / kBlock);
   const bool fused = fuse != nullptr && fused_rows != nullptr && blocks <= kAbsmaxMaxBlocks;
-  auto kernel = d % 4 == 0 ? (fused ? rosenbrock_vec_kernel<true, false> : rosenbrock_vec_kernel<false, false>)
-                           : (fused ? rosenbrock_vec_kernel<true, true> : rosenbrock_vec_kernel<false, true>);
-  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), 0, s, x, noise, gen, g, d, M, fused ? *fuse : ScaleFusion{});
+  const bool generated = gen.sigma > 0.f;
+  const ScaleFusion f = fused ? *fuse : ScaleFusion{};
+#define TNG_ROSENBROCK(NORM, F)                                                                                       \
+  do {                                                                                                                \
+    auto kernel = d % 4 == 0 ? (generated ? rosenbrock_vec_kernel<NORM, F, false, true>                               \
+                                          : rosenbrock_vec_kernel<NORM, F, false, false>)                             \
+                             : (generated ? rosenbrock_vec_kernel<NORM, F, true, true>                                \
+                                          : rosenbrock_vec_kernel<NORM, F, true, false>);                             \
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), 0, s, x, noise, gen, g, d, M, f);                          \
+  } while (0)
+  if (!fused) {
+    TNG_ROSENBROCK(kNormNone, false);
+  } else {
+    switch (fuse->norm) {
+      case kNormSub: TNG_ROSENBROCK(kNormSub, true); break;
+      case kNormQuot: TNG_ROSENBROCK(kNormQuot, true); break;
+      case kNormComb: TNG_ROSENBROCK(kNormComb, true); break;
+      default: TNG_ROSENBROCK(kNormNone, true); break;
+    }
+  }
+#undef TNG_ROSENBROCK
   if (fused) *fused_rows = blocks;
   return hipGetLastError();
 }
