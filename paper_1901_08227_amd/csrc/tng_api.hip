@@ -304,10 +304,8 @@ tng_status local_grad_impl(tng_ctx* ctx, uint32_t iter, const float* w, float* g
     case TNG_PROB_LOGREG_CSR: {
       if (!ctx->have_csr) return TNG_ERR_BAD_STATE;
       const tng::LogregData p = logreg_tables(ctx);
-      e = tng::launch_minibatch_indices(k0, k1, iter, c.M, c.batch, p.n_rows, ctx->idx, ctx->stream);
-      if (e != hipSuccess) return TNG_ERR_HIP;
-      e = tng::launch_logreg_csr_grad(p, c.d, c.M, c.batch, c.l2, ctx->idx, ctx->rowbase, ctx->bounds, ctx->zpart,
-                                      ctx->resid, w, g, fuse, fused_rows, ctx->stream);
+      e = tng::launch_logreg_csr_grad(p, c.d, c.M, c.batch, c.l2, k0, k1, iter, ctx->idx, ctx->rowbase, ctx->bounds,
+                                      ctx->zpart, ctx->resid, w, g, fuse, fused_rows, ctx->stream);
       return hip_status(e);
     }
     case TNG_PROB_ROSENBROCK:
@@ -661,18 +659,16 @@ tng_status tng_step(tng_ctx* ctx, uint32_t iter, float* w, float* gref, float* g
   // where the decode pass leaves a second copy of the decoded average: its slot of the history ring
   // (window average), or the reference itself when it is refreshed now (last average)
   float* ref_out = window ? ctx->history + (uint64_t)slot * c.d : (refresh_now(c, iter) ? gref : nullptr);
-  // tiny problems: everything after the gradient in one launch
-  const bool single = single_pass_ok(ctx, g, gref, vbar, w, ref_out);
   uint32_t fused_rows = 0;
   if (c.problem != TNG_PROB_EXTERNAL) {
     const tng::ScaleFusion fuse{c.norm, c.quot_eps, gref, ctx->gref2, ctx->partials};
     // the maximum can ride along with the gradient kernel; a scale that needs the row mean or an
     // ordered sum cannot
-    const bool can_fuse = !single && c.norm != TNG_NORM_MEAN && c.scale == TNG_SCALE_MAX;
+    const bool can_fuse = c.norm != TNG_NORM_MEAN && c.scale == TNG_SCALE_MAX;
     s = local_grad_impl(ctx, iter, w, g, can_fuse ? &fuse : nullptr, can_fuse ? &fused_rows : nullptr);
     if (s != TNG_OK) return s;
   }
-  if (single) {
+  if (fused_rows == 0 && single_pass_ok(ctx, g, gref, vbar, w, ref_out)) {  // tiny problems: scales and the rest in one launch
     s = hip_status(tng::launch_single_pass(ctx->shape, iter, g, gref, ctx->gref2, scales, codes, true, vbar, w, c.lr,
                                            ref_out, ctx->stream));
     if (s != TNG_OK) return s;

@@ -1407,6 +1407,141 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_workers_kernel(const int
   if (threadIdx.x == 0) store_maximum(m_end - 1);
 }
 
+// ------------------------------------------------------------------------------------------
+// CSR logistic regression with few columns: two launches.
+//
+// With w small enough for every L2 the dot products need no column tiles: a wavefront takes a minibatch row,
+// gathers w, and leaves what the gradient pass needs of the row (residual over B, start, tile bounds) -- one
+// launch in place of four (row ids, bounds, dot products, their sum).  The gradient pass then has as many
+// workgroups as fill the chip: each owns 2^sub_shift columns of a tile in LDS and reads the tile's whole row
+// segments (out of the L2: 2^(tile_shift - sub_shift) workgroups read the same ones), adding those that are its own.
+// ------------------------------------------------------------------------------------------
+template <bool PAIRS, bool INDEX>
+__global__ __launch_bounds__(kBlock) void csr_rows_kernel(const int64_t* const* __restrict__ rowptrs,
+                                                          const int32_t* const* __restrict__ cols,
+                                                          const float* const* __restrict__ vals,
+                                                          const float* const* __restrict__ ys,
+                                                          const uint64_t* __restrict__ n_rows,
+                                                          const uint32_t* const* __restrict__ index,
+                                                          const float* __restrict__ w, uint32_t* __restrict__ idx,
+                                                          int64_t* __restrict__ rowbase, uint32_t* __restrict__ bounds,
+                                                          float* __restrict__ resid, uint32_t batch, uint32_t ntiles,
+                                                          uint32_t tile_shift, float inv_b, uint32_t k0, uint32_t k1,
+                                                          uint32_t iter) {
+  const uint32_t m = blockIdx.y, lane = threadIdx.x % kWave;
+  const uint32_t i = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * kWavesPerBlock + threadIdx.x / kWave));
+  if (i >= batch) return;  // whole wavefronts; no workgroup barrier below
+  const uint32_t row = (uint32_t)__builtin_amdgcn_readfirstlane((int)minibatch_row(k0, k1, iter, m, i, n_rows[m]));
+  const int64_t a = as_global(rowptrs[m])[row];
+  const uint32_t nnz = (uint32_t)(as_global(rowptrs[m])[row + 1] - a);
+  const float y = as_global(ys[m])[row];
+  const CsrEntries<PAIRS> e(cols[m], PAIRS ? nullptr : vals[m]);
+  uint32_t* __restrict__ out = bounds + (uint64_t)m * (ntiles + 1) * batch + i;
+  if (INDEX) {
+    const GlobalPtr<uint32_t> src = as_global(index[m]) + (uint64_t)row * (ntiles + 1);
+    for (uint32_t t = lane; t <= ntiles; t += kWave) out[(uint64_t)t * batch] = src[t];
+  }
+  float acc = 0.f;
+#pragma unroll 4
+  for (uint32_t k = lane; k < nnz; k += kWave) {
+    int32_t c;
+    float v;
+    e.load(a + k, c, v);
+    acc = __builtin_fmaf(v, w[c], acc);
+    if (!INDEX) {  // entry k opens every tile after the tile of entry k - 1 up to its own
+      const uint32_t prev = k == 0 ? 0u : ((uint32_t)e.col(a + k - 1) >> tile_shift) + 1u;
+      for (uint32_t t = prev; t <= ((uint32_t)c >> tile_shift); ++t) out[(uint64_t)t * batch] = k;
+    }
+  }
+  if (!INDEX) {  // and the end of the row every tile after its last entry's
+    const uint32_t prev = nnz == 0 ? 0u : ((uint32_t)e.col(a + nnz - 1) >> tile_shift) + 1u;
+    for (uint32_t t = prev + lane; t <= ntiles; t += kWave) out[(uint64_t)t * batch] = nnz;
+  }
+  const float z = wave_sum(acc);
+  if (lane == 0) {
+    const uint64_t o = (uint64_t)m * batch + i;
+    idx[o] = row;
+    rowbase[o] = a;
+    resid[o] = logistic_residual(z, y) * inv_b;
+  }
+}
+
+constexpr uint32_t kCsrMinSubShift = 10;  // a column per thread
+template <bool PAIRS>
+__global__ __launch_bounds__(kCsrThreads) void csr_grad_sub_kernel(const int32_t* const* __restrict__ cols,
+                                                                   const float* const* __restrict__ vals,
+                                                                   const int64_t* __restrict__ rowbase,
+                                                                   const uint32_t* __restrict__ bounds,
+                                                                   const float* __restrict__ resid,
+                                                                   const float* __restrict__ w, float* __restrict__ g,
+                                                                   uint64_t d, uint32_t batch, uint32_t ntiles,
+                                                                   uint32_t tile_shift, uint32_t sub_shift, float l2,
+                                                                   bool fused, ScaleFusion fuse) {
+  extern __shared__ double gtile[];  // g over the workgroup's columns, accumulated in fp64
+  __shared__ __align__(16) int64_t sLo[kCsrRows];
+  __shared__ __align__(16) uint32_t sLen[kCsrRows];
+  __shared__ float sR[kCsrRows];
+  __shared__ float red[kCsrThreads / kWave];
+  const uint32_t m = blockIdx.y;
+  const uint32_t T = 1u << sub_shift;
+  const uint32_t c0 = blockIdx.x << sub_shift;  // (d < 2^32 here)
+  const uint32_t t = blockIdx.x >> (tile_shift - sub_shift);
+  for (uint32_t j = threadIdx.x; j < T; j += kCsrThreads) gtile[j] = 0.0;
+  const CsrEntries<PAIRS> e(cols[m], vals[m]);
+  const uint32_t group = threadIdx.x / kCsrLanes, gl = threadIdx.x % kCsrLanes;
+  auto add = [&](int32_t c, float v, float r) {
+    const uint32_t at = (uint32_t)c - c0;  // (columns left of c0 wrap to far beyond T)
+    if (at < T) atomicAdd(&gtile[at], (double)(r * v));
+  };
+  for (uint32_t first = 0; first < batch; first += kCsrRows) {
+    const uint32_t count = min((uint32_t)kCsrRows, batch - first);
+    __syncthreads();
+    csr_stage_segments(rowbase, bounds, m, batch, ntiles, t, first, count, sLo, sLen);
+    for (uint32_t j = threadIdx.x; j < count; j += kCsrThreads) sR[j] = resid[(uint64_t)m * batch + first + j];
+    __syncthreads();
+    const uint32_t j0 = group * kCsrUnroll;
+    CsrBatch b;
+    csr_load_batch(e, sLo, sLen, j0, count, gl, b);
+    float r[kCsrUnroll];
+#pragma unroll
+    for (int u = 0; u < kCsrUnroll; ++u) r[u] = b.len[u] != 0 ? sR[j0 + u] : 0.f;
+#pragma unroll
+    for (int u = 0; u < kCsrUnroll; ++u)
+      if (gl < b.len[u]) add(b.col[u], b.val[u], r[u]);
+#pragma unroll
+    for (int u = 0; u < kCsrUnroll; ++u) {
+      if (b.len[u] > (uint32_t)kCsrLanes) {  // segments longer than the lane group
+        const int64_t lo = sLo[j0 + u];
+        for (uint32_t k = gl + kCsrLanes; k < b.len[u]; k += kCsrLanes) {
+          int32_t ck;
+          float vk;
+          e.load(lo + k, ck, vk);
+          add(ck, vk, r[u]);
+        }
+      }
+    }
+  }
+  __syncthreads();
+  float* __restrict__ out = g + (uint64_t)m * d;
+  float amax = 0.f;
+  for (uint32_t j = threadIdx.x; j < T; j += kCsrThreads) {
+    const uint64_t c = (uint64_t)c0 + j;
+    if (c < d) {
+      const float o = l2 != 0.f ? __builtin_fmaf(l2, w[c], (float)gtile[j]) : (float)gtile[j];
+      out[c] = o;
+      if (fused) {
+        const float r1 = fuse.norm != kNormNone ? fuse.gref[c] : 0.f;
+        const float r2 = fuse.norm == kNormComb ? fuse.gref2[c] : 1.f;
+        amax = fmaxf(amax, fabsf(normalize_dyn(fuse.norm, o, r1, r2, fuse.eps)));
+      }
+    }
+  }
+  if (fused) {
+    amax = block_max(amax, red);
+    if (threadIdx.x == 0) fuse.partials[(uint64_t)blockIdx.x * gridDim.y + m] = amax;
+  }
+}
+
 // Chain Rosenbrock gradient ("Nonconvex Problems", d-dimensional form) plus per-worker noise.
 // Fixed expression tree, one rounding per operation:
 //   a = x[i+1] - x[i]*x[i];  t1 = (-400*x[i])*a;  t2 = -2*(1 - x[i])        (i < d-1)
@@ -1738,6 +1873,35 @@ namespace {
 // (d = 2^24, 64 workers, minibatch 512; 5.18 ms with one tile per workgroup).
 constexpr uint32_t kCsrRun = 16;
 
+// The two launches for few columns (see csr_rows_kernel), up to 2^21 columns of all workers.  Beyond, w no longer
+// comes cheaply out of the L2 and the repeated segments cost more than the launches.  Iterations at 0.1 % density, the
+// column tiles against these: d = 2^14, M = 8, B = 128 39 -> 14.6 us; d = 2^16, M = 8, B = 512 46 -> 18.5, M = 33
+// 58 -> 49, M = 64 65 -> 71; d = 2^18, M = 8 55 -> 37, M = 64 110 -> 202; d = 2^19, M = 16 66 -> 113.
+bool csr_few_columns(uint64_t d, uint32_t M) { return d * M <= (1ull << 21); }
+
+template <bool PAIRS>
+hipError_t csr_few_columns_launches(const LogregData& p, uint64_t d, uint32_t M, uint32_t batch, float l2, uint32_t k0,
+                                    uint32_t k1, uint32_t iter, uint32_t* idx, int64_t* rowbase, uint32_t* bounds,
+                                    float* z, const float* w, float* g, const ScaleFusion* fuse, uint32_t* fused_rows,
+                                    hipStream_t s) {
+  const uint32_t shift = csr_tile_shift(d), ntiles = csr_tiles(d);
+  const float inv_b = 1.0f / (float)batch;
+  const dim3 rows((batch + kWavesPerBlock - 1) / kWavesPerBlock, M);
+  auto kernel = p.tile_index != nullptr ? csr_rows_kernel<PAIRS, true> : csr_rows_kernel<PAIRS, false>;
+  hipLaunchKernelGGL(kernel, rows, dim3(kBlock), 0, s, p.rowptr, p.col, p.val, p.y, p.n_rows, p.tile_index, w, idx,
+                     rowbase, bounds, z, batch, ntiles, shift, inv_b, k0, k1, iter);
+  // columns per workgroup: 2^12, halved until there is one workgroup per compute unit (twice as many: 24 against 18.5 us
+  // at d = 2^16, M = 8)
+  uint32_t sub = shift < 12 ? shift : 12;
+  while (sub > kCsrMinSubShift && ((d + (1ull << sub) - 1) >> sub) * M < 256) --sub;
+  const dim3 grid((uint32_t)((d + (1ull << sub) - 1) >> sub), M);
+  const bool fused = fuse != nullptr && fused_rows != nullptr && grid.x <= kAbsmaxMaxBlocks;
+  hipLaunchKernelGGL(csr_grad_sub_kernel<PAIRS>, grid, dim3(kCsrThreads), sizeof(double) << sub, s, p.col, p.val, rowbase,
+                     bounds, z, w, g, d, batch, ntiles, shift, sub, l2, fused, fused ? *fuse : ScaleFusion{});
+  if (fused) *fused_rows = grid.x;
+  return hipGetLastError();
+}
+
 template <bool PAIRS>
 hipError_t csr_grad_launches(const LogregData& p, uint64_t d, uint32_t M, uint32_t batch, float l2, const uint32_t* idx,
                              int64_t* rowbase, uint32_t* bounds, float* zpart, float* z, const float* w, float* g,
@@ -1842,11 +2006,18 @@ hipError_t csr_grad_launches(const LogregData& p, uint64_t d, uint32_t M, uint32
 
 }  // namespace
 
-hipError_t launch_logreg_csr_grad(const LogregData& p, uint64_t d, uint32_t M, uint32_t batch, float l2,
-                                  const uint32_t* idx, int64_t* rowbase, uint32_t* bounds, float* zpart, float* z,
-                                  const float* w, float* g, const ScaleFusion* fuse, uint32_t* fused_rows,
-                                  hipStream_t s) {
+hipError_t launch_logreg_csr_grad(const LogregData& p, uint64_t d, uint32_t M, uint32_t batch, float l2, uint32_t k0,
+                                  uint32_t k1, uint32_t iter, uint32_t* idx, int64_t* rowbase, uint32_t* bounds,
+                                  float* zpart, float* z, const float* w, float* g, const ScaleFusion* fuse,
+                                  uint32_t* fused_rows, hipStream_t s) {
   if (fused_rows != nullptr) *fused_rows = 0;
+  if (csr_few_columns(d, M))
+    return p.pairs ? csr_few_columns_launches<true>(p, d, M, batch, l2, k0, k1, iter, idx, rowbase, bounds, z, w, g, fuse,
+                                                    fused_rows, s)
+                   : csr_few_columns_launches<false>(p, d, M, batch, l2, k0, k1, iter, idx, rowbase, bounds, z, w, g,
+                                                     fuse, fused_rows, s);
+  const hipError_t e = launch_minibatch_indices(k0, k1, iter, M, batch, p.n_rows, idx, s);
+  if (e != hipSuccess) return e;
   return p.pairs ? csr_grad_launches<true>(p, d, M, batch, l2, idx, rowbase, bounds, zpart, z, w, g, fuse, fused_rows, s)
                  : csr_grad_launches<false>(p, d, M, batch, l2, idx, rowbase, bounds, zpart, z, w, g, fuse, fused_rows, s);
 }

@@ -149,10 +149,11 @@ hipError_t launch_csr_validate_rowptr(const LogregData& p, uint32_t M, uint64_t 
 hipError_t launch_csr_validate_cols(const LogregData& p, uint64_t d, uint32_t M, uint64_t max_rows, uint32_t* flag,
                                     hipStream_t s);
 hipError_t launch_csr_tile_index(const LogregData& p, uint64_t d, uint32_t M, uint64_t max_rows, hipStream_t s);
-hipError_t launch_logreg_csr_grad(const LogregData& p, uint64_t d, uint32_t M, uint32_t batch, float l2,
-                                  const uint32_t* idx, int64_t* rowbase, uint32_t* bounds, float* zpart, float* z,
-                                  const float* w, float* g, const ScaleFusion* fuse, uint32_t* fused_rows,
-                                  hipStream_t s);
+// The minibatch row ids of iteration iter are drawn inside (Philox key k0, k1) and left in idx.
+hipError_t launch_logreg_csr_grad(const LogregData& p, uint64_t d, uint32_t M, uint32_t batch, float l2, uint32_t k0,
+                                  uint32_t k1, uint32_t iter, uint32_t* idx, int64_t* rowbase, uint32_t* bounds,
+                                  float* zpart, float* z, const float* w, float* g, const ScaleFusion* fuse,
+                                  uint32_t* fused_rows, hipStream_t s);
 // Gaussian noise made on the device (sigma > 0): element e of worker m at iteration iter is
 // sigma * z, z from the Box-Muller transform of the Philox block (e >> 2, m, iter, 2): words 0, 1
 // give z for e & 3 = 0 (cosine) and 1 (sine), words 2, 3 for e & 3 = 2 and 3;
