@@ -2248,7 +2248,17 @@ hipError_t quantize_decode_dispatch(const CodecShape& c, uint32_t iter, const fl
 }
 }  // namespace
 
-bool quantize_decode_applies(const CodecShape& c) { return c.M <= kTailMaxWorkers; }
+// Where the one launch is faster than the separate ones: always while launches set the time (d <= 2^18); beyond, the
+// thread per float4 needs three workers to have loads enough in flight (iteration with given gradients, no
+// normalisation, d = 2^25, M = 1 144 us apart, 185 in one launch) and takes more than eight of them in trips that drain
+// (d = 2^22, M = 16 115 / 123; d = 2^24, M = 12 364 / 330), and the workers by wavefront are ahead only where the
+// reference is subtracted (d = 2^23, M = 20: 308 / 297; quotient 318 / 341).
+bool quantize_decode_applies(const CodecShape& c) {
+  if (c.M > kTailMaxWorkers) return false;
+  if (c.M > 16) return c.norm == kNormSub ? c.d <= (1u << 18) || c.d >= (1u << 23) : c.d <= (1u << 17);
+  if (c.M > 8) return c.d <= (1u << 20) || c.d >= (1u << 23);
+  return c.M > 2 || c.d <= (1u << 20);
+}
 
 uint32_t quantize_decode_rows(const CodecShape& c) { return kTailPartials / c.M; }
 
