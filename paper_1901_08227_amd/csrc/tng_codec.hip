@@ -324,6 +324,22 @@ __device__ __forceinline__ void absmax_rows(const GradRows& g, const RefTile<NOR
   }
 }
 
+// The maximum over the lane's part of the ragged last wavefront tile of worker m.
+template <int NORM>
+__device__ __forceinline__ float absmax_ragged_tile(const GradRows& g, const float4* ref4, const float4* ref24, uint32_t m,
+                                                    uint64_t d, float eps, float mu) {
+  constexpr int L = kAbsmaxLoads;
+  RefTile<NORM> rt[L];
+  float4 x[L];
+#pragma unroll
+  for (int j = 0; j < L; ++j) {
+    const uint64_t iv = d / kWaveTileElements * (kWave * L) + (uint64_t)j * kWave + threadIdx.x % kWave;
+    rt[j].load_ragged(ref4, ref24, iv, d, eps);
+    x[j] = load_row_ragged(g, m, iv, d, mu);
+  }
+  return absmax_reduce<NORM, false>(x, rt, mu);
+}
+
 template <int NORM, int MC>
 __global__ __launch_bounds__(kBlock) void absmax_vec_kernel(GradRows g, const float4* __restrict__ ref4,
                                                             const float4* __restrict__ ref24,
@@ -352,16 +368,7 @@ __global__ __launch_bounds__(kBlock) void absmax_vec_kernel(GradRows g, const fl
     }
   } else {
     const uint32_t at = (blockIdx.x - main_blocks) * kWavesPerBlock + (uint32_t)wave, m = min(m0 + at, M - 1);
-    const float mu = NORM == kNormMean ? means[m] : 0.f;
-    RefTile<NORM> rt[L];
-    float4 x[L];
-#pragma unroll
-    for (int j = 0; j < L; ++j) {
-      const uint64_t iv = ntiles * kWaveTile + (uint64_t)j * kWave + lane;
-      rt[j].load_ragged(ref4, ref24, iv, d, eps);
-      x[j] = load_row_ragged(g, m, iv, d, mu);
-    }
-    const float v = absmax_reduce<NORM, false>(x, rt, mu);
+    const float v = absmax_ragged_tile<NORM>(g, ref4, ref24, m, d, eps, NORM == kNormMean ? means[m] : 0.f);
 #pragma unroll
     for (int mm = 0; mm < MC; ++mm) mx[mm] = (uint32_t)mm == at ? v : 0.f;
   }
@@ -564,8 +571,33 @@ __device__ __forceinline__ void quantize_rows(const QuantLane<NORM>& q, Fragment
   if (DEFER) flush_packed<WPW, SLOTS>(lds, wave, lane, codes, words, word_base, m0, m_end - m0);
 }
 
+// The ragged last wavefront tile of worker m: a wavefront of its own.
+template <int NORM, int BITS, int WPW, int SLOTS>
+__device__ __forceinline__ void quantize_ragged_tile(FragmentBuffer<WPW, SLOTS>& lds, int wave, int lane, const GradRows& g,
+                                                     const float4* ref4, const float4* ref24, float R, float mu,
+                                                     uint32_t* __restrict__ codes, uint64_t d, uint64_t words, uint32_t m,
+                                                     float eps, uint32_t iter, uint32_t k0, uint32_t k1) {
+  constexpr int L = kLoadsPerLane;
+  const uint64_t tile = d / kWaveTileElements;
+  QuantLane<NORM> q;
+  float4 x[L];
+  uint32_t frag[L];
+#pragma unroll
+  for (int j = 0; j < L; ++j) {
+    q.iv[j] = tile * (kWave * L) + (uint64_t)j * kWave + lane;
+    q.rt[j].load_ragged(ref4, ref24, q.iv[j], d, eps);
+    x[j] = load_row_ragged(g, m, q.iv[j], d, mu);
+  }
+  quantize_worker_tile<NORM, BITS, false>(q, x, R, mu, m, iter, k0, k1, frag);
+  store_packed<BITS, WPW, SLOTS, false>(lds, 0, wave, lane, frag, codes + (uint64_t)m * words, tile * WPW, words);
+}
+
+// LOOP: the kernel behind the candidate coder, which returns at once when the codes come from the slots
+// (skip_if_set) but for the ragged last tile, which has none: at most kLoopBlocks workgroups per group of workers, each walking its share of the tiles (returning
+// from 32768 workgroups took 9 us at d = 2^27).
 // (128 registers, four wavefronts per SIMD, but for the combined form, whose two references do not fit that)
-template <int NORM, int BITS, int MC, bool FUSED>
+constexpr uint32_t kLoopBlocks = 4096;
+template <int NORM, int BITS, int MC, bool FUSED, bool LOOP>
 __global__ __launch_bounds__(kBlock, NORM == kNormComb ? 3 : 4) void quantize_pack_vec_kernel(
     GradRows g, const float4* __restrict__ ref4, const float4* __restrict__ ref24,
     const float* __restrict__ scales, uint32_t* __restrict__ codes, uint64_t d, uint64_t words, uint32_t main_blocks,
@@ -574,40 +606,35 @@ __global__ __launch_bounds__(kBlock, NORM == kNormComb ? 3 : 4) void quantize_pa
   constexpr int L = kLoadsPerLane;
   constexpr int WPW = kWave * L * 4 * BITS / 32;  // packed words per wavefront tile
   __shared__ __attribute__((aligned(16))) FragmentBuffer<WPW, MC> lds;
-  // the codes come from the candidate slots instead (quantize_candidates_kernel) when that word is set
-  if (skip_if_set != nullptr && skip_if_set[0] != 0u) return;
+  if (LOOP && blockIdx.x < main_blocks && skip_if_set[0] != 0u) return;
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const uint64_t ntiles = d / kWaveTileElements;  // whole wavefront tiles
   const uint32_t m0 = blockIdx.y * MC;
   const uint32_t m_end = min(m0 + MC, M);
-  uint64_t wave_tile = (uint64_t)blockIdx.x * kWavesPerBlock + wave;
-  QuantLane<NORM> q;
   if (blockIdx.x < main_blocks) {
-    if (wave_tile >= ntiles) return;  // whole wavefronts of the last workgroup; nothing below meets the others
+    uint64_t wave_tile = (uint64_t)blockIdx.x * kWavesPerBlock + wave;
+    if (!LOOP && wave_tile >= ntiles) return;  // whole wavefronts of the last workgroup; nothing below meets the others
+    do {
+      if (LOOP && wave_tile >= ntiles) return;
+      QuantLane<NORM> q;
 #pragma unroll
-    for (int j = 0; j < L; ++j) {
-      q.iv[j] = wave_tile * (kWave * L) + (uint64_t)j * kWave + lane;
-      q.rt[j].load(ref4, ref24, q.iv[j], eps);
-      if (kByReciprocal<NORM, MC>) q.rt[j].reciprocals();
-    }
-    // (the 16-byte stores at the end of the workgroup take words at any 4-byte boundary)
-    quantize_rows<NORM, BITS, WPW, MC, FUSED, (MC > 1)>(q, lds, wave, lane, g, scales, codes, words, wave_tile * WPW, m0,
-                                                        m_end, iter, k0, k1, means, fs, M);
+      for (int j = 0; j < L; ++j) {
+        q.iv[j] = wave_tile * (kWave * L) + (uint64_t)j * kWave + lane;
+        q.rt[j].load(ref4, ref24, q.iv[j], eps);
+        if (kByReciprocal<NORM, MC>) q.rt[j].reciprocals();
+      }
+      // (the 16-byte stores at the end of the workgroup take words at any 4-byte boundary)
+      quantize_rows<NORM, BITS, WPW, MC, FUSED, (MC > 1)>(q, lds, wave, lane, g, scales, codes, words, wave_tile * WPW, m0,
+                                                          m_end, iter, k0, k1, means, fs, M);
+      wave_tile += (uint64_t)main_blocks * kWavesPerBlock;
+      if (LOOP) wave_lds_fence();
+    } while (LOOP);
   } else {
     const uint32_t m = m0 + (blockIdx.x - main_blocks) * kWavesPerBlock + (uint32_t)wave;
     if (m >= m_end) return;
     const float R = FUSED ? fused_scale(fs, m, M, blockIdx.x == 0 && threadIdx.x == 0) : scales[m];
-    const float mu = NORM == kNormMean ? means[m] : 0.f;
-    float4 x[L];
-    uint32_t frag[L];
-#pragma unroll
-    for (int j = 0; j < L; ++j) {
-      q.iv[j] = ntiles * (kWave * L) + (uint64_t)j * kWave + lane;
-      q.rt[j].load_ragged(ref4, ref24, q.iv[j], d, eps);
-      x[j] = load_row_ragged(g, m, q.iv[j], d, mu);
-    }
-    quantize_worker_tile<NORM, BITS, false>(q, x, R, mu, m, iter, k0, k1, frag);
-    store_packed<BITS, WPW, MC, false>(lds, 0, wave, lane, frag, codes + (uint64_t)m * words, ntiles * WPW, words);
+    quantize_ragged_tile<NORM, BITS>(lds, wave, lane, g, ref4, ref24, R, NORM == kNormMean ? means[m] : 0.f, codes, d,
+                                     words, m, eps, iter, k0, k1);
   }
 }
 
@@ -631,8 +658,10 @@ __global__ __launch_bounds__(kBlock, NORM == kNormComb ? 3 : 4) void quantize_pa
 // draw.  Everything else is cleared, and the words are packed.  A slot that overflowed (a tile with more
 // than kCandCap candidates) sends its tile through the ordinary path.  The codes are those of the two-pass
 // coder bit for bit; what changes is that g is read once: 4 + 4/M bytes per element instead of 8 + 8/M.
-// Used for 2-bit codes with the largest-magnitude scale when every wavefront tile is a full one
-// (d a multiple of 1024) and the row is long enough for the second read to come from memory.
+// Used for 2-bit codes with the largest-magnitude scale when the row is long enough for the second read to come from
+// memory; the ragged last tile of a row has no slots, the scale pass and the ordinary quantiser take it in
+// workgroups of their own (encode + decode at d = 2^25 + 3, M = 5: 333 us by two passes, 262 this way; d = 2^26 + 1, M = 1:
+// 263 / 225).
 // ------------------------------------------------------------------------------------------
 constexpr int kCandCap = 127;         // candidates a slot holds; word 0 of a slot is their count
 constexpr int kSlotEntries = 128;     // 32-bit words per slot: 512 bytes per worker and wavefront tile
@@ -730,7 +759,7 @@ __global__ __launch_bounds__(kBlock) void sample_finish_kernel(const float* __re
 template <int NORM, int MC>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) void absmax_select_kernel(GradRows g, const float4* __restrict__ ref4,
                                                                const float4* __restrict__ ref24, float* partials,
-                                                               uint64_t nvec, uint32_t M, float eps,
+                                                               uint64_t d, uint32_t main_blocks, uint32_t M, float eps,
                                                                const float* __restrict__ sample_max,
                                                                const uint32_t* __restrict__ select_ok,
                                                                uint32_t* __restrict__ slots,
@@ -764,7 +793,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
   float mx[MC];
 #pragma unroll
   for (int mm = 0; mm < MC; ++mm) mx[mm] = 0.f;
-  const uint64_t ntiles = nvec / kWaveTile;  // every tile is a full one
+  const uint64_t ntiles = d / kWaveTileElements;  // whole wavefront tiles
+  if (blockIdx.x >= main_blocks) {  // the ragged last tile: its maximum only, the quantise pass codes it from g
+    const uint32_t at = (blockIdx.x - main_blocks) * kWavesPerBlock + (uint32_t)wave;
+    const float v = absmax_ragged_tile<NORM>(g, ref4, ref24, min(m0 + at, M - 1), d, eps, 0.f);
+#pragma unroll
+    for (int mm = 0; mm < MC; ++mm) mx[mm] = (uint32_t)mm == at ? v : 0.f;
+    block_max_to_partials<MC>(mx, m0, M, partials);
+    if (threadIdx.x == 0) overflowed[(uint64_t)blockIdx.y * gridDim.x + blockIdx.x] = 0u;
+    return;
+  }
   const uint32_t lane4 = 4u * (uint32_t)lane;
   // The lower bound R^ of a worker's scale is the maximum over the sample of its row.  The test
   //   u < fl(|v| fl(1 / R^)),  u = (word >> 8) 2^-24,
@@ -883,7 +921,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
       if ((uint32_t)(item - 1) < count) worker(b, item - 1, tile);
     }
   };
-  const uint64_t stride = (uint64_t)gridDim.x * kWavesPerBlock;
+  const uint64_t stride = (uint64_t)main_blocks * kWavesPerBlock;
   uint64_t tile = (uint64_t)blockIdx.x * kWavesPerBlock + wave;
   if (tile < ntiles) {
     float4 b0[L], b1[L], b2[L];
@@ -953,7 +991,7 @@ __global__ __launch_bounds__(kBlock) void absmax_finish_vote_kernel(const float*
 template <int NORM, int MC>
 __global__ __launch_bounds__(kBlock) void quantize_candidates_kernel(
     GradRows g, const float4* __restrict__ ref4, const float4* __restrict__ ref24, const float* __restrict__ scales,
-    const uint32_t* __restrict__ slots, uint32_t* __restrict__ codes, uint64_t nvec, uint64_t words, uint32_t M,
+    const uint32_t* __restrict__ slots, uint32_t* __restrict__ codes, uint64_t d, uint64_t words, uint32_t M,
     float eps, uint32_t k0, uint32_t k1, uint32_t iter, const uint32_t* __restrict__ use_slots,
     const uint32_t* __restrict__ select_ok) {
   constexpr int L = kLoadsPerLane;
@@ -962,12 +1000,12 @@ __global__ __launch_bounds__(kBlock) void quantize_candidates_kernel(
   __shared__ __attribute__((aligned(16))) FragmentBuffer<WPW, MC> lds;
   if (use_slots[0] == 0u) return;  // too many tiles overflowed: the ordinary quantiser runs instead
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-  const uint64_t ntiles = nvec / (kWave * L);
+  const uint64_t ntiles = d / kWaveTileElements;
+  const uint32_t m0 = blockIdx.y * MC;
+  const uint32_t m_end = min(m0 + MC, M);
   const uint64_t tile = (uint64_t)blockIdx.x * kWavesPerBlock + wave;
   if (tile >= ntiles) return;  // whole wavefronts; nothing below meets the other wavefronts
   const uint64_t word_base = tile * WPW;
-  const uint32_t m0 = blockIdx.y * MC;
-  const uint32_t m_end = min(m0 + MC, M);
   // Counts and the first 64 words of all the workers' slots are requested at once (a slot rarely holds
   // more: the rest is fetched when its count says so), so that the workgroup waits for memory once and not
   // once per worker.  Words past a slot's count are whatever an earlier call left there and are not used.
@@ -1858,7 +1896,11 @@ hipError_t absmax_candidates_dispatch(const CodecShape& c, uint32_t iter, const 
                                       const float* gref2, float* partials, const CandidateScratch& cs, float* scales,
                                       hipStream_t s) {
   const uint64_t nvec = c.d / 4;
-  const int mc = pick_workers_per_block(c.M, (nvec + kBlock * kAbsmaxLoads - 1) / (kBlock * kAbsmaxLoads), 0.3);
+  // Fives where the workers come out even that way: the reference and five rows are two rounds of the three buffers, and
+  // the group of 5 or 9 workers fetches no row twice.
+  int mc = pick_workers_per_block(c.M, (nvec + kBlock * kAbsmaxLoads - 1) / (kBlock * kAbsmaxLoads), 0.3);
+  const uint32_t groups = (c.M + 7) / 8;
+  if (mc == 8 && (c.M + groups - 1) / groups <= 5) mc = 5;
   uint32_t nblocks = 0;
   hipError_t e;
   // the sample: every kSampleStride-th wavefront tile of every row
@@ -1872,15 +1914,18 @@ hipError_t absmax_candidates_dispatch(const CodecShape& c, uint32_t iter, const 
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(sample_finish_kernel, dim3(c.M), dim3(kBlock), 0, s, cs.sample_partials, cs.sample_sums, nsample,
                      c.M, (float)(sample_tiles * (kWave * kAbsmaxLoads * 4)), cs.sample_max, cs.select_ok);
-  const uint32_t per_y = div_up_u32(nvec, (uint64_t)kBlock * kAbsmaxLoads);
-  const uint32_t cap = kAbsmaxMaxBlocks - 1;
-  nblocks = per_y < cap ? per_y : cap;
+  const uint32_t tail = tail_workgroups(c.d, mc);
+  const uint32_t per_y = div_up_u32(row_tiles, kWavesPerBlock);
+  const uint32_t cap = kAbsmaxMaxBlocks - 1 - tail;
+  const uint32_t main_blocks = per_y < cap ? per_y : cap;
+  nblocks = main_blocks + tail;
 #define TNG_SELECT(MC)                                                                                              \
   hipLaunchKernelGGL((absmax_select_kernel<NORM, MC>), dim3(nblocks, (c.M + MC - 1) / MC), dim3(kBlock), 0, s,      \
                      GradRows{g, c.d}, reinterpret_cast<const float4*>(gref), reinterpret_cast<const float4*>(gref2), \
-                     partials, nvec, c.M, c.eps, cs.sample_max, cs.select_ok, cs.slots, cs.overflowed, c.k0, c.k1, iter)
+                     partials, c.d, main_blocks, c.M, c.eps, cs.sample_max, cs.select_ok, cs.slots, cs.overflowed, c.k0, c.k1, iter)
   switch (mc) {
     case 8: TNG_SELECT(8); break;
+    case 5: TNG_SELECT(5); break;
     case 4: TNG_SELECT(4); break;
     case 2: TNG_SELECT(2); break;
     default: TNG_SELECT(1); break;
@@ -1903,15 +1948,15 @@ template <int NORM>
 hipError_t quantize_candidates_dispatch(const CodecShape& c, uint32_t iter, const float* g, const float* gref,
                                         const float* gref2, const float* scales, const CandidateScratch& cs,
                                         uint32_t* codes, hipStream_t s) {
-  const uint64_t nvec = c.d / 4;
-  const uint64_t tiles = (nvec + kBlock * kLoadsPerLane - 1) / (kBlock * kLoadsPerLane);  // workgroups of 4 wavefront tiles
-  const int mc = pick_workers_per_block(c.M, tiles, 0.0, 16);
+  const uint64_t tiles = (c.d / kWaveTileElements + kWavesPerBlock - 1) / kWavesPerBlock;  // workgroups of 4 wavefront tiles
+  const int mc = pick_workers_per_block(c.M, tiles, 0.0, 8);  // (no reference to share between more: M = 16, d = 2^24 387 us
+                                                                       // per iteration with 16, 373 with 8)
 #define TNG_QC(MC)                                                                                                   \
-  hipLaunchKernelGGL((quantize_candidates_kernel<NORM, MC>), dim3((uint32_t)tiles, (c.M + MC - 1) / MC), dim3(kBlock), 0, \
+  hipLaunchKernelGGL((quantize_candidates_kernel<NORM, MC>),                                                           \
+                     dim3((uint32_t)tiles, (c.M + MC - 1) / MC), dim3(kBlock), 0,             \
                      s, GradRows{g, c.d}, reinterpret_cast<const float4*>(gref), reinterpret_cast<const float4*>(gref2), \
-                     scales, cs.slots, codes, nvec, c.words, c.M, c.eps, c.k0, c.k1, iter, cs.use_slots, cs.select_ok)
+                     scales, cs.slots, codes, c.d, c.words, c.M, c.eps, c.k0, c.k1, iter, cs.use_slots, cs.select_ok)
   switch (mc) {
-    case 16: TNG_QC(16); break;
     case 8: TNG_QC(8); break;
     case 4: TNG_QC(4); break;
     case 2: TNG_QC(2); break;
@@ -1920,7 +1965,8 @@ hipError_t quantize_candidates_dispatch(const CodecShape& c, uint32_t iter, cons
 #undef TNG_QC
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  // the ordinary quantiser right behind it: one of the two returns at once, by the vote of the scale pass
+  // the ordinary quantiser right behind it: one of the two returns at once, by the vote of the scale pass (the ragged
+  // last tile is the ordinary one's either way: in the kernel above it cost the registers of a wavefront per SIMD)
   return quantize_dispatch<NORM, 2>(c, iter, g, gref, gref2, const_cast<float*>(scales), codes, nullptr, 0, s,
                                     cs.use_slots);
 }
@@ -1945,14 +1991,15 @@ hipError_t absmax_dispatch(const CodecShape& c, const float* g, const float* gre
   return hipGetLastError();
 }
 
-template <int NORM, int BITS, int MC, bool FUSED>
+template <int NORM, int BITS, int MC, bool FUSED, bool LOOP>
 hipError_t quantize_vec_launch(const CodecShape& c, uint32_t iter, const float* g, const float* gref,
                                const float* gref2, const float* scales, uint32_t* codes, const FusedScale& fs,
                                hipStream_t s, const uint32_t* skip_if_set = nullptr) {
   const uint32_t tail = tail_workgroups(c.d, MC);
-  const uint32_t main_blocks = (uint32_t)((c.d / kWaveTileElements + kWavesPerBlock - 1) / kWavesPerBlock);
+  uint32_t main_blocks = (uint32_t)((c.d / kWaveTileElements + kWavesPerBlock - 1) / kWavesPerBlock);
+  if (LOOP && main_blocks > kLoopBlocks) main_blocks = kLoopBlocks;
   dim3 grid(main_blocks + tail, (c.M + MC - 1) / MC);
-  hipLaunchKernelGGL((quantize_pack_vec_kernel<NORM, BITS, MC, FUSED>), grid, dim3(kBlock), 0, s, GradRows{g, c.d}, reinterpret_cast<const float4*>(gref),
+  hipLaunchKernelGGL((quantize_pack_vec_kernel<NORM, BITS, MC, FUSED, LOOP>), grid, dim3(kBlock), 0, s, GradRows{g, c.d}, reinterpret_cast<const float4*>(gref),
                      reinterpret_cast<const float4*>(gref2), scales, codes, c.d, c.words, main_blocks, c.M, c.eps, c.k0,
                      c.k1, iter, c.means, fs, skip_if_set);
   return hipGetLastError();
@@ -1978,14 +2025,20 @@ hipError_t quantize_dispatch(const CodecShape& c, uint32_t iter, const float* g,
     if (e != hipSuccess) return e;
     fs.rows = 0;
   }
-  if (fs.rows > 0) return quantize_vec_launch<NORM, BITS, 1, true>(c, iter, g, gref, gref2, scales, codes, fs, s);
+  if (fs.rows > 0) return quantize_vec_launch<NORM, BITS, 1, true, false>(c, iter, g, gref, gref2, scales, codes, fs, s);
+  constexpr bool kLoop = BITS == 2 && (NORM == kNormNone || NORM == kNormSub);  // what the candidate coder takes
+#define TNG_QUANTIZE(MC)                                                                                                \
+  return kLoop && skip_if_set != nullptr                                                                                \
+             ? quantize_vec_launch<NORM, BITS, MC, false, kLoop>(c, iter, g, gref, gref2, scales, codes, fs, s, skip_if_set) \
+             : quantize_vec_launch<NORM, BITS, MC, false, false>(c, iter, g, gref, gref2, scales, codes, fs, s)
   switch (mc) {
-    case 16: return quantize_vec_launch<NORM, BITS, 16, false>(c, iter, g, gref, gref2, scales, codes, fs, s, skip_if_set);
-    case 8: return quantize_vec_launch<NORM, BITS, 8, false>(c, iter, g, gref, gref2, scales, codes, fs, s, skip_if_set);
-    case 4: return quantize_vec_launch<NORM, BITS, 4, false>(c, iter, g, gref, gref2, scales, codes, fs, s, skip_if_set);
-    case 2: return quantize_vec_launch<NORM, BITS, 2, false>(c, iter, g, gref, gref2, scales, codes, fs, s, skip_if_set);
-    default: return quantize_vec_launch<NORM, BITS, 1, false>(c, iter, g, gref, gref2, scales, codes, fs, s, skip_if_set);
+    case 16: TNG_QUANTIZE(16);
+    case 8: TNG_QUANTIZE(8);
+    case 4: TNG_QUANTIZE(4);
+    case 2: TNG_QUANTIZE(2);
+    default: TNG_QUANTIZE(1);
   }
+#undef TNG_QUANTIZE
 }
 
 template <int NORM, int BITS>
@@ -2176,10 +2229,10 @@ hipError_t launch_l2_scales(const CodecShape& c, const float* g, const float* gr
 }
 
 size_t candidate_scratch_bytes(const CodecShape& c) {
-  // 2-bit codes, largest-magnitude scale, a shared reference or none, whole wavefront tiles, and enough
+  // 2-bit codes, largest-magnitude scale, a shared reference or none, and enough
   // elements (2^26: 256 MiB of gradients) for the extra launches of the sample to be noise
   // (not the quotient forms: there |v| is near 1 everywhere and a third of the elements code non-zero)
-  if (c.bits != 2 || c.scale_l2 != 0 || (c.norm != kNormNone && c.norm != kNormSub) || c.d % 1024 != 0) return 0;
+  if (c.bits != 2 || c.scale_l2 != 0 || (c.norm != kNormNone && c.norm != kNormSub)) return 0;
   if ((uint64_t)c.M * c.d < (1ull << 26) || c.d / 1024 < 4 * (uint64_t)kSampleStride) return 0;
   return candidate_head_bytes(c.M) + (size_t)c.M * (c.d / 1024) * kSlotEntries * sizeof(uint32_t);
 }

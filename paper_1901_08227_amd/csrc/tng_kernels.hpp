@@ -51,7 +51,7 @@ hipError_t launch_l2_scales(const CodecShape& c, const float* g, const float* gr
 // out to be (tested against a lower bound of it), and the quantise pass codes those from the slots instead
 // of reading g again; same codes and scales as launch_absmax + launch_quantize_pack, bit for bit.
 // candidate_scratch_bytes: device scratch needed (256-byte aligned), 0 where the path does not apply
-// (other code widths, scales and normalisations, rows that are not whole tiles, small problems);
+// (other code widths, scales and normalisations, small problems);
 // candidates_apply: whether it may be used for these operands (scratch size non-zero, 16-byte alignment).
 size_t candidate_scratch_bytes(const CodecShape& c);
 bool candidates_apply(const CodecShape& c, const float* g, const float* gref, const float* gref2, const uint32_t* codes);

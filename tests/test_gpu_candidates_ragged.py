@@ -1,0 +1,47 @@
+"""The ternary coder that reads the gradients once, on rows that are not whole tiles of 1024 coordinates: the ragged
+last tile in workgroups of its own next to 1 to 16 workers per workgroup, with the slots in use, with single rows too
+dense for them, and with the call left to the ordinary quantiser, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import DEV, buffers, make_ctx, oracle_cfg, say, u32
+from oracle import tng_oracle as O
+from paper_1901_08227_amd import binding as B
+from test_gpu_candidates import _encode_one, _inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def check(M, d, norm, g, gref, it, scale=B.SCALE_MAX):
+    say(f"candidates d={d} M={M} norm={norm} scale={scale}")
+    ctx = make_ctx(d, M, 2, norm, seed=d, scale=scale)
+    buf = buffers(ctx)
+    ctx.normalize_encode(it, g, gref, buf["codes"], buf["scales"])
+    ctx.decode_aggregate(buf["codes"], buf["scales"], gref, buf["vbar"])
+    torch.cuda.synchronize()
+    cfg = oracle_cfg(ctx)
+    ctx.close()
+    rh, codes, scales = gref.cpu().numpy(), u32(buf["codes"]), buf["scales"].cpu().numpy()
+    for m in range(M):
+        want, R = _encode_one(cfg, it, m, g[m].cpu().numpy(), rh, rh)
+        assert scales[m] == R and np.array_equal(codes[m], want), f"worker {m}: scale {scales[m]} of {R}"
+    assert np.array_equal(buf["vbar"].cpu().numpy(), O.decode_aggregate(cfg, codes, scales, rh, d, rh, None))
+
+
+@pytest.mark.parametrize("M,d,norm", [(1, (1 << 26) + 1, B.NORM_SUB), (2, (1 << 25) + 1023, B.NORM_NONE),
+                                      (3, (1 << 25) + 514, B.NORM_SUB), (5, (1 << 24) + 4099, B.NORM_SUB),
+                                      (9, (1 << 23) + 4, B.NORM_NONE), (17, (1 << 22) + 255, B.NORM_SUB)])
+def test_ragged_rows(M, d, norm):
+    g, gref, _ = _inputs(M, d, seed=M)
+    g[M - 1, d - 1] += 3.0 * (g[M - 1] - gref).abs().max()  # the last worker's scale is set in the ragged tile
+    check(M, d, norm, g, gref, 4)
+
+
+@pytest.mark.parametrize("dense", [(2,), tuple(range(33))])
+def test_dense_rows(dense):
+    M, d = 33, (1 << 21) + 333
+    g, gref, _ = _inputs(M, d, seed=5)
+    for m in dense:
+        g[m] = gref + torch.randn(d, device=DEV, generator=torch.Generator(device=DEV).manual_seed(m))
+    check(M, d, B.NORM_SUB, g, gref, 4)
