@@ -221,6 +221,10 @@ tng_status scale_impl(tng_ctx* ctx, uint32_t iter, const float* g, const float* 
   }
   if (mean_ref && ctx->cfg.scale == TNG_SCALE_MAX) {
     // nothing left of the scale pass
+  } else if (ctx->cfg.scale == TNG_SCALE_L2 && ctx->cand != nullptr &&
+             tng::candidates_apply(ctx->shape, g, gref, ctx->gref2, codes)) {
+    *by_candidates = true;
+    e = tng::launch_l2_candidates(ctx->shape, iter, g, gref, ctx->sums, ctx->cand, scales, ctx->stream);
   } else if (ctx->cfg.scale == TNG_SCALE_L2) {
     e = tng::launch_l2_scales(ctx->shape, g, gref, ctx->gref2, ctx->sums, scales, ctx->stream);
   } else if (fused_rows > 0) {

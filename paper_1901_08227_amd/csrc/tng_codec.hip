@@ -658,7 +658,7 @@ __global__ __launch_bounds__(kBlock, NORM == kNormComb ? 3 : 4) void quantize_pa
 // draw.  Everything else is cleared, and the words are packed.  A slot that overflowed (a tile with more
 // than kCandCap candidates) sends its tile through the ordinary path.  The codes are those of the two-pass
 // coder bit for bit; what changes is that g is read once: 4 + 4/M bytes per element instead of 8 + 8/M.
-// Used for 2-bit codes with the largest-magnitude scale when the row is long enough for the second read to come from
+// Used for 2-bit codes when the row is long enough for the second read to come from
 // memory; the ragged last tile of a row has no slots, the scale pass and the ordinary quantiser take it in
 // workgroups of their own (encode + decode at d = 2^25 + 3, M = 5: 333 us by two passes, 262 this way; d = 2^26 + 1, M = 1:
 // 263 / 225).
@@ -673,8 +673,11 @@ constexpr uint32_t kCandPosMask = 0x3FFu;  // low 10 bits of a candidate word: p
 // of the row's elements that will be candidates -- P(u < |v| / R^) averaged over the elements -- so it tells
 // beforehand whether the slots can hold them.  One worker per workgroup row (blockIdx.y); partial results per
 // workgroup, reduced by sample_finish_kernel.
+constexpr uint32_t kL2OverflowCounts = kBlock;  // counters that the workgroups of l2_select_kernel share
 constexpr float kDenseLimit = 0.10f;  // 1024 elements x 0.10 + two standard deviations fill a slot of kCandCap
-template <int NORM>
+// L2: the bound is of the row's 2-norm instead, from the sum of squares over the sample in binary64 (the partial
+// results are the workgroups' own norms).
+template <int NORM, bool L2>
 __global__ __launch_bounds__(kBlock) void sample_stats_kernel(GradRows g, const float4* __restrict__ ref4,
                                                               float* __restrict__ part_max,
                                                               float* __restrict__ part_sum, uint64_t nvec, uint32_t M) {
@@ -685,7 +688,9 @@ __global__ __launch_bounds__(kBlock) void sample_stats_kernel(GradRows g, const 
   const uint32_t m = blockIdx.y;
   const uint64_t ntiles = nvec / kWaveTile;  // whole tiles only
   const v4f_u_t* row = g.row(m);
+  __shared__ double squares[kWavesPerBlock];
   float amax = 0.f, asum = 0.f;
+  double sq = 0.0;
   for (uint64_t tile = ((uint64_t)blockIdx.x * kWavesPerBlock + wave) * kSampleStride; tile < ntiles;
        tile += (uint64_t)gridDim.x * kWavesPerBlock * kSampleStride) {
     float4 x[L], r[L];
@@ -699,15 +704,21 @@ __global__ __launch_bounds__(kBlock) void sample_stats_kernel(GradRows g, const 
     for (int j = 0; j < L; ++j) {
       const float a0 = fabsf(x[j].x - r[j].x), a1 = fabsf(x[j].y - r[j].y);
       const float a2 = fabsf(x[j].z - r[j].z), a3 = fabsf(x[j].w - r[j].w);
-      amax = fmaxf(fmaxf(amax, fmaxf(a0, a1)), fmaxf(a2, a3));
+      if (L2)
+        sq += ((double)a0 * a0 + (double)a1 * a1) + ((double)a2 * a2 + (double)a3 * a3);
+      else
+        amax = fmaxf(fmaxf(amax, fmaxf(a0, a1)), fmaxf(a2, a3));
       asum += (a0 + a1) + (a2 + a3);
     }
   }
   amax = wave_max(amax);
   asum = wave_sum(asum);
+  if (L2)
+    for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off, kWave);
   if (lane == 0) {
     red[0][wave] = amax;
     red[1][wave] = asum;
+    squares[wave] = sq;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -716,7 +727,9 @@ __global__ __launch_bounds__(kBlock) void sample_stats_kernel(GradRows g, const 
     for (int k = 1; k < kWavesPerBlock; ++k) {
       mx = fmaxf(mx, red[0][k]);
       sm += red[1][k];
+      sq += squares[k];
     }
+    if (L2) mx = (float)sqrt(sq);
     part_max[(uint64_t)blockIdx.x * M + m] = mx;
     part_sum[(uint64_t)blockIdx.x * M + m] = sm;
   }
@@ -726,22 +739,34 @@ __global__ __launch_bounds__(kBlock) void sample_stats_kernel(GradRows g, const 
 // select_ok[m] = 1 when the sample says that the row's candidates fit the slots, else 0: the scale pass then
 // takes that worker's part as an ordinary scale pass and the quantise pass takes its tiles through the
 // ordinary path, without the slots.  sampled = elements of a row in the sample.  One workgroup per worker.
+// L2: R^ is the norm of the workgroups' norms, made smaller by 2^-10 of itself, which is more than all roundings on the way
+// here and in the row's own ordered sum can come to.
+template <bool L2>
 __global__ __launch_bounds__(kBlock) void sample_finish_kernel(const float* __restrict__ part_max,
                                                                const float* __restrict__ part_sum, uint32_t nblocks,
                                                                uint32_t M, float sampled, float* __restrict__ sample_max,
-                                                               uint32_t* __restrict__ select_ok) {
+                                                               uint32_t* __restrict__ select_ok,
+                                                               uint32_t* __restrict__ overflowed) {
+  if (L2 && blockIdx.x == 0) overflowed[threadIdx.x] = 0u;  // l2_select_kernel adds to these
   __shared__ float red[2][kWavesPerBlock];
+  __shared__ double squares[kWavesPerBlock];
   const uint32_t m = blockIdx.x;
   float mx = 0.f, sm = 0.f;
+  double sq = 0.0;
   for (uint32_t b = threadIdx.x; b < nblocks; b += kBlock) {
-    mx = fmaxf(mx, part_max[(uint64_t)b * M + m]);
+    const float p = part_max[(uint64_t)b * M + m];
+    mx = fmaxf(mx, p);
+    sq += (double)p * p;
     sm += part_sum[(uint64_t)b * M + m];
   }
   mx = wave_max(mx);
   sm = wave_sum(sm);
+  if (L2)
+    for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off, kWave);
   if (threadIdx.x % kWave == 0) {
     red[0][threadIdx.x / kWave] = mx;
     red[1][threadIdx.x / kWave] = sm;
+    squares[threadIdx.x / kWave] = sq;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -749,11 +774,88 @@ __global__ __launch_bounds__(kBlock) void sample_finish_kernel(const float* __re
     for (int k = 1; k < kWavesPerBlock; ++k) {
       mx = fmaxf(mx, red[0][k]);
       sm += red[1][k];
+      sq += squares[k];
     }
+    if (L2) mx = (float)sqrt(sq) * (1.0f - 0x1p-10f);
     sample_max[m] = mx < FLT_MIN ? 0.f : mx;
     // (a sum that is no number, or an infinite one, compares false: the slots are then not used)
     select_ok[m] = sm <= kDenseLimit * sampled * mx ? 1u : 0u;
   }
+}
+
+// Staging of one worker's candidates in a wavefront tile: the count and up to kCandCap candidates (value word and
+// draw), one word that takes everything beyond the capacity, then a word per lane for the elements that are no
+// candidates.
+constexpr uint32_t kStageSink = kSlotEntries, kStageDump = kSlotEntries + 2, kStageWords = kStageDump + kWave;
+
+// The lower bound R^ of a worker's scale, as the factor of the candidates' test
+//   u < fl(|v| fl(1 / R^)),  u = (word >> 8) 2^-24,
+// which is made in three operations and from above:  float(word) < |v| c1 + 258  with
+// c1 = fl(fl(1 / R^) 2^32 (1 + 2^-20)).  It holds whenever the exact test does (then word < 2^32 fl(|v| / R^) + 256;
+// converting the word and the two roundings on the right move either side by less than 2^-23 relatively,
+// which the factor 1 + 2^-20 and the 2 added to 256 cover) and passes 2^-20 more elements than it: the
+// quantise pass codes a candidate exactly, so more is harmless.  Below 2^-90 no bound is claimed (c1 would
+// overflow): every non-zero element is a candidate.
+__device__ __forceinline__ float candidate_factor(float r_hat) {
+  return r_hat >= 0x1p-90f ? (1.0f / r_hat) * (0x1p32f * (1.0f + 0x1p-20f)) : INFINITY;
+}
+
+// The candidates of one float4 per lane (load j of the tile) go behind the base - 1 staged before.  FEW: candidates
+// are rare, most float4 of a whole wavefront hold none.
+template <bool FEW>
+__device__ __forceinline__ void stage_candidates(uint32_t* stage, uint32_t* draws, const float4& v, const U32x4& rnd,
+                                                 float c1, int j, int lane, uint32_t& base) {
+  const float vv[4] = {v.x, v.y, v.z, v.w};
+  const uint32_t rr[4] = {rnd.x, rnd.y, rnd.z, rnd.w};
+  bool cand[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) cand[c] = (float)rr[c] < __builtin_fmaf(fabsf(vv[c]), c1, 258.0f);
+  if (FEW && __builtin_amdgcn_ballot_w64((int)cand[0] | (int)cand[1] | (int)cand[2] | (int)cand[3]) == 0ull) return;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(cand[c]);
+    const uint32_t pos = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                                          __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+    // Every lane writes, the others into a word of their own behind the candidates': a store under a
+    // condition would end the basic block at every element, and the sixteen elements of a lane could not
+    // overlap.  Candidates beyond the slot's capacity (the slot is then not used) share one word.
+    const uint32_t at = cand[c] ? min(pos, kStageSink) : kStageDump + (uint32_t)lane;
+    stage[at] = (__float_as_uint(vv[c]) & ~kCandPosMask) | (uint32_t)(256 * j + c) | 4u * (uint32_t)lane;
+    draws[at] = rr[c];
+    base += (uint32_t)__builtin_popcountll(mask);
+  }
+}
+
+// The staged candidates (base - 1 of them) to their slot; false where they do not fit (only the count is written).
+__device__ __forceinline__ bool write_slot(uint32_t* stage, const uint32_t* draws, uint32_t base, int lane, uint32_t* slot_words) {
+  if (lane == 0) stage[0] = base - 1;  // candidates found (more than kCandCap: the slot is not used)
+  wave_lds_fence();
+  // Words to write, the count included (8 bytes per lane, the last one whatever the staging area holds);
+  // of a slot that overflowed only the count.  (The slots cost about 0.15 ms per launch -- 0.2 GB next to
+  // 4.8 GB of reads -- and pieces rounded up to whole 128-byte lines, 16-byte stores or a quarter fewer bytes
+  // all measured the same; half of it remains when the stores never leave the caches.  The cache policy does
+  // matter: plain stores +0.03 ms, non-temporal ones +0.08 ms.)
+  const bool fits = base <= (uint32_t)kSlotEntries;
+  const uint32_t used = fits ? base : 1u;
+  if (2u * (uint32_t)lane < used) {  // one store instruction covers the slot: 8 bytes per lane, device-coherent policy
+    // What goes into the slot for a candidate is not v but tau = |v| / u (u its 24-bit draw), the scale up
+    // to which it codes non-zero, to 13 bits of the significand: the quantise pass then compares the row's
+    // scale with tau and needs neither the draw nor the value.  The reciprocal is taken here, for the two
+    // candidates of the lane, not for every element of the tile.  u = 0 gives an infinite tau (or none, for
+    // v = 0), which the quantise pass takes as "look at the value".
+    const uint2 vw = *reinterpret_cast<const uint2*>(&stage[2 * lane]);
+    const uint2 dw = *reinterpret_cast<const uint2*>(&draws[2 * lane]);
+    auto entry = [](uint32_t value_word, uint32_t draw) {
+      const float tau = __uint_as_float(value_word & 0x7FFFFC00u) * (__builtin_amdgcn_rcpf((float)(draw >> 8)) * 0x1p24f);
+      return (__float_as_uint(tau) & 0x7FFFFC00u) | (value_word & 0x800003FFu);
+    };
+    const uint32_t e0 = lane == 0 ? vw.x : entry(vw.x, dw.x);  // word 0 of the slot is the count
+    const uint64_t two = ((uint64_t)entry(vw.y, dw.y) << 32) | e0;
+    uint64_t* slot = reinterpret_cast<uint64_t*>(slot_words);
+    __hip_atomic_store(slot + (uint32_t)lane, two, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  wave_lds_fence();
+  return fits;
 }
 
 template <int NORM, int MC>
@@ -777,11 +879,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
   // in flight per wavefront.  (Measured 2 % faster than two buffers that drained at the end of every tile:
   // the pass is bound neither by the depth of its prefetch nor by its arithmetic.)
   constexpr int kItems = (MC + 1 + 2) / 3 * 3;
-  // staging per wavefront: the count and up to kCandCap candidates (value word and draw), one word that takes
-  // everything beyond the capacity, then a word per lane for the elements that are no candidates
-  constexpr uint32_t kStageSink = kSlotEntries, kStageDump = kSlotEntries + 2;
-  __shared__ __attribute__((aligned(16))) uint32_t stage[kWavesPerBlock][kStageDump + kWave];
-  __shared__ __attribute__((aligned(16))) uint32_t draws[kWavesPerBlock][kStageDump + kWave];
+  __shared__ __attribute__((aligned(16))) uint32_t stage[kWavesPerBlock][kStageWords];
+  __shared__ __attribute__((aligned(16))) uint32_t draws[kWavesPerBlock][kStageWords];
   __shared__ __attribute__((aligned(16))) float4 refs[kWavesPerBlock][L][kWave];
   __shared__ uint32_t over[kWavesPerBlock];
   // the wavefront's number as a value the compiler knows to be the same in every lane: tile numbers, row and
@@ -803,21 +902,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
     if (threadIdx.x == 0) overflowed[(uint64_t)blockIdx.y * gridDim.x + blockIdx.x] = 0u;
     return;
   }
-  const uint32_t lane4 = 4u * (uint32_t)lane;
-  // The lower bound R^ of a worker's scale is the maximum over the sample of its row.  The test
-  //   u < fl(|v| fl(1 / R^)),  u = (word >> 8) 2^-24,
-  // is made in three operations and from above:  float(word) < |v| c1 + 258  with
-  // c1 = fl(fl(1 / R^) 2^32 (1 + 2^-20)).  It holds whenever the exact test does (then word < 2^32 fl(|v| / R^) + 256;
-  // converting the word and the two roundings on the right move either side by less than 2^-23 relatively,
-  // which the factor 1 + 2^-20 and the 2 added to 256 cover) and passes 2^-20 more elements than it: the
-  // quantise pass codes a candidate exactly, so more is harmless.  Below 2^-90 no bound is claimed (c1 would
-  // overflow): every non-zero element is a candidate.
   float c1[MC];
   bool select[MC];  // the sample found the worker's row too dense for the slots: only its maximum is taken
 #pragma unroll
   for (int mm = 0; mm < MC; ++mm) {
-    const float r_hat = sample_max[min(m0 + (uint32_t)mm, M - 1)];
-    c1[mm] = r_hat >= 0x1p-90f ? (1.0f / r_hat) * (0x1p32f * (1.0f + 0x1p-20f)) : INFINITY;
+    c1[mm] = candidate_factor(sample_max[min(m0 + (uint32_t)mm, M - 1)]);
     select[mm] = select_ok[min(m0 + (uint32_t)mm, M - 1)] != 0u;
   }
   // one worker's part of the tile: its maximum, and its candidates into the slot
@@ -849,52 +938,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
       amax = max3_abs(v.z, v.w, max3_abs(v.x, v.y, amax));
       const uint64_t iv = tile * kWaveTile + (uint64_t)(j * kWave + lane);
       const U32x4 rnd = philox4x32_10((uint32_t)iv, m, iter, 0u, k0, k1);
-      const float vv[4] = {v.x, v.y, v.z, v.w};
-      const uint32_t rr[4] = {rnd.x, rnd.y, rnd.z, rnd.w};
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const bool cand = (float)rr[c] < __builtin_fmaf(fabsf(vv[c]), c1[mm], 258.0f);
-        const uint64_t mask = __builtin_amdgcn_ballot_w64(cand);
-        const uint32_t pos = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
-                                                              __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-        // Every lane writes, the others into a word of their own behind the candidates': a store under a
-        // condition would end the basic block at every element, and the sixteen elements of a lane could not
-        // overlap.  Candidates beyond the slot's capacity (the slot is then not used) share one word.
-        const uint32_t at = cand ? min(pos, kStageSink) : kStageDump + (uint32_t)lane;
-        stage[wave][at] = (__float_as_uint(vv[c]) & ~kCandPosMask) | (uint32_t)(256 * j + c) | lane4;
-        draws[wave][at] = rr[c];
-        base += (uint32_t)__builtin_popcountll(mask);
-      }
+      stage_candidates<false>(stage[wave], draws[wave], v, rnd, c1[mm], j, lane, base);
     }
     mx[mm] = fmaxf(mx[mm], amax);
-    if (lane == 0) stage[wave][0] = base - 1;  // candidates found (more than kCandCap: the slot is not used)
-    wave_lds_fence();
-    // Words to write, the count included (8 bytes per lane, the last one whatever the staging area holds);
-    // of a slot that overflowed only the count.  (The slots cost about 0.15 ms per launch -- 0.2 GB next to
-    // 4.8 GB of reads -- and pieces rounded up to whole 128-byte lines, 16-byte stores or a quarter fewer bytes
-    // all measured the same; half of it remains when the stores never leave the caches.  The cache policy does
-    // matter: plain stores +0.03 ms, non-temporal ones +0.08 ms.)
-    const bool fits = base <= (uint32_t)kSlotEntries;
-    nover += fits ? 0u : 1u;
-    const uint32_t used = fits ? base : 1u;
-    if (2u * lane < used) {  // one store instruction covers the slot: 8 bytes per lane, device-coherent policy
-      // What goes into the slot for a candidate is not v but tau = |v| / u (u its 24-bit draw), the scale up
-      // to which it codes non-zero, to 13 bits of the significand: the quantise pass then compares the row's
-      // scale with tau and needs neither the draw nor the value.  The reciprocal is taken here, for the two
-      // candidates of the lane, not for every element of the tile.  u = 0 gives an infinite tau (or none, for
-      // v = 0), which the quantise pass takes as "look at the value".
-      const uint2 vw = *reinterpret_cast<const uint2*>(&stage[wave][2 * lane]);
-      const uint2 dw = *reinterpret_cast<const uint2*>(&draws[wave][2 * lane]);
-      auto entry = [](uint32_t value_word, uint32_t draw) {
-        const float tau = __uint_as_float(value_word & 0x7FFFFC00u) * (__builtin_amdgcn_rcpf((float)(draw >> 8)) * 0x1p24f);
-        return (__float_as_uint(tau) & 0x7FFFFC00u) | (value_word & 0x800003FFu);
-      };
-      const uint32_t e0 = lane == 0 ? vw.x : entry(vw.x, dw.x);  // word 0 of the slot is the count
-      const uint64_t two = ((uint64_t)entry(vw.y, dw.y) << 32) | e0;
-      uint64_t* slot = reinterpret_cast<uint64_t*>(slots + ((uint64_t)m * ntiles + tile) * kSlotEntries);
-      __hip_atomic_store(slot + (uint32_t)lane, two, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    wave_lds_fence();
+    if (!write_slot(stage[wave], draws[wave], base, lane, slots + ((uint64_t)m * ntiles + tile) * kSlotEntries)) nover += 1u;
   };
   // Every request is made whatever the tile (a load under a branch could not be counted by the waits that
   // follow it): past the wavefront's last tile all lanes read the first float4 of this tile's part again.
@@ -963,15 +1010,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
   }
 }
 
-// The reduction of the scale pass's partial maxima (workgroups 0 .. M - 1, one per worker) and, in one more
+// The reduction of the scale pass's partial maxima (workgroups 0 .. finish - 1, one per worker: M, or 0 where the scale
+// is no maximum) and, in one more
 // workgroup, whether the slots are worth using: at most one tile in fifty may have overflowed (such tiles go
 // through a plain, unpipelined form of the ordinary path).  use_slots[0] = 1 or 0.
 __global__ __launch_bounds__(kBlock) void absmax_finish_vote_kernel(const float* __restrict__ partials, uint32_t nblocks,
-                                                                    uint32_t M, float* __restrict__ scales,
+                                                                    uint32_t M, uint32_t finish, float* __restrict__ scales,
                                                                     const uint32_t* __restrict__ overflowed, uint32_t n,
                                                                     uint64_t tiles_in_all,
                                                                     uint32_t* __restrict__ use_slots) {
-  if (blockIdx.x < M) {
+  if (blockIdx.x < finish) {
     absmax_finish_worker(partials, nblocks, M, scales, blockIdx.x);
     return;
   }
@@ -991,8 +1039,8 @@ __global__ __launch_bounds__(kBlock) void absmax_finish_vote_kernel(const float*
 template <int NORM, int MC>
 __global__ __launch_bounds__(kBlock) void quantize_candidates_kernel(
     GradRows g, const float4* __restrict__ ref4, const float4* __restrict__ ref24, const float* __restrict__ scales,
-    const uint32_t* __restrict__ slots, uint32_t* __restrict__ codes, uint64_t d, uint64_t words, uint32_t M,
-    float eps, uint32_t k0, uint32_t k1, uint32_t iter, const uint32_t* __restrict__ use_slots,
+    const uint32_t* __restrict__ slots, uint32_t* __restrict__ codes, uint64_t d, uint64_t words, uint64_t slot_tiles,
+    uint32_t M, float eps, uint32_t k0, uint32_t k1, uint32_t iter, const uint32_t* __restrict__ use_slots,
     const uint32_t* __restrict__ select_ok) {
   constexpr int L = kLoadsPerLane;
   constexpr int WPW = kWave * L * 4 * 2 / 32;  // 64 packed words per wavefront tile
@@ -1025,8 +1073,9 @@ __global__ __launch_bounds__(kBlock) void quantize_candidates_kernel(
     const int slot = mm;
     const float R = scales[m];
     const uint32_t* __restrict__ sl = slots + ((uint64_t)m * ntiles + tile) * kSlotEntries;
-    // (a worker whose row the sample found too dense has no slots: its tiles take the ordinary path)
-    const uint32_t n = R == 0.f ? 0u : select_ok[m] != 0u ? cnt[mm] : (uint32_t)kCandCap + 1u;
+    // (a worker whose row the sample found too dense has no slots, and a tile beyond the last whole chunk of the l2
+    // scale's sums has none: they take the ordinary path)
+    const uint32_t n = R == 0.f ? 0u : select_ok[m] != 0u && tile < slot_tiles ? cnt[mm] : (uint32_t)kCandCap + 1u;
     if (n <= (uint32_t)kCandCap) {
       lds.b32[slot][wave][lane] = 0u;
       wave_lds_fence();
@@ -1739,6 +1788,116 @@ __global__ __launch_bounds__(kBlock) void l2_chunk_kernel(GradRows g, const floa
   }
 }
 
+// The chunk sums of the squares and, in the same pass over g, the candidates of the ternary coder (see
+// absmax_select_kernel; here hardly an element is one: the scale is sqrt(d) times the typical |v|).  A workgroup takes
+// a chunk of up to kL2SelectWorkers workers, its wavefronts a worker each in turn; the chunk's reference is in LDS, and the
+// lane sums of all workers are added up in order at the end, a worker per lane (by one lane per worker and wavefront, as
+// above, these additions are as many instructions as all others).  Encode + decode at d = 2^24, M = 16: 500 us by two
+// passes, 366 this way (this kernel 255 for 1.14 GB: the vector unit's time for draws, squares and tests as much as
+// memory's).  A wavefront's fetches, a tile of a worker each, rotate
+// through three buffers.
+constexpr int kL2SelectWorkers = 8;
+template <int NORM>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) void l2_select_kernel(
+    GradRows g, const float4* __restrict__ ref4, double* __restrict__ chunk_sums, uint64_t ntiles, uint64_t nchunks,
+    uint32_t M, const float* __restrict__ sample_max, const uint32_t* __restrict__ select_ok,
+    uint32_t* __restrict__ slots, uint32_t* __restrict__ overflowed, uint32_t k0, uint32_t k1, uint32_t iter) {
+  static_assert(NORM == kNormNone || NORM == kNormSub, "the coder that reads g once: no divisor reference");
+  constexpr int L = kLoadsPerLane;                       // rows of 64 float4 per tile
+  constexpr int T = kTreeChunk / (int)kWaveTileElements;  // tiles per chunk
+  constexpr int V = kTreeChunk / 4;                      // float4 per chunk
+  constexpr int kSumStride = kTreeLanes + 2;             // two binary64 of padding: the lanes' reads fall on different banks
+  __shared__ __attribute__((aligned(16))) uint32_t stage[kWavesPerBlock][kStageWords];
+  __shared__ __attribute__((aligned(16))) uint32_t draws[kWavesPerBlock][kStageWords];
+  __shared__ __attribute__((aligned(16))) float4 refs[NORM == kNormSub ? V : 1];
+  __shared__ __attribute__((aligned(16))) double sums[kL2SelectWorkers][kSumStride];
+  __shared__ uint32_t over[kWavesPerBlock];
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = threadIdx.x % kWave;
+  const uint64_t chunk = blockIdx.x;
+  const uint32_t m0 = blockIdx.y * kL2SelectWorkers;
+  const uint32_t count = min((uint32_t)kL2SelectWorkers, M - m0);
+  if (NORM == kNormSub) {
+    float4 r[V / kBlock];
+#pragma unroll
+    for (int k = 0; k < V / kBlock; ++k) r[k] = load_stream(ref4 + chunk * V + k * kBlock + threadIdx.x);
+#pragma unroll
+    for (int k = 0; k < V / kBlock; ++k) refs[k * kBlock + threadIdx.x] = r[k];
+  }
+  // item i of the wavefront: tile i mod T of its worker number i / T; past the last one the last is fetched again
+  const uint32_t items = count > (uint32_t)wave ? ((count - (uint32_t)wave + kWavesPerBlock - 1) / kWavesPerBlock) * T : 0u;
+  auto request = [&](float4 (&b)[L], uint32_t item) {
+    const uint32_t it = min(item, items - 1);
+    const v4f_u_t* p = g.row(m0 + (uint32_t)wave + it / T * kWavesPerBlock) + chunk * V + (uint64_t)(it % T) * (L * kWave);
+#pragma unroll
+    for (int j = 0; j < L; ++j) b[j] = load_row_stream(p + (uint32_t)(j * kWave + lane));
+  };
+  float4 b0[L], b1[L], b2[L];
+  if (items != 0) {
+    request(b0, 0);
+    request(b1, 1);
+  }
+  __syncthreads();  // the reference is in LDS
+  uint32_t nover = 0;
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  float c1 = 0.f;
+  bool select = false;
+  auto work = [&](const float4 (&x)[L], uint32_t item) {
+    const uint32_t mm = (uint32_t)wave + item / T * kWavesPerBlock, m = m0 + mm, t = item % T;
+    if (t == 0) {
+      acc[0] = acc[1] = acc[2] = acc[3] = 0.0;
+      c1 = candidate_factor(sample_max[m]);
+      select = select_ok[m] != 0u;
+    }
+    uint32_t base = 1;  // word 0 of the slot is the count
+#pragma unroll
+    for (int j = 0; j < L; ++j) {
+      float4 v = x[j];
+      const uint32_t at = (t * L + (uint32_t)j) * kWave + (uint32_t)lane;
+      if (NORM == kNormSub) {
+        const float4 r = refs[at];
+        v = make_float4(x[j].x - r.x, x[j].y - r.y, x[j].z - r.z, x[j].w - r.w);
+      }
+      const double t0 = (double)v.x, t1 = (double)v.y, t2 = (double)v.z, t3 = (double)v.w;
+      acc[0] = __builtin_fma(t0, t0, acc[0]);  // the square of a binary32 value is exact in binary64: one rounding either way
+      acc[1] = __builtin_fma(t1, t1, acc[1]);
+      acc[2] = __builtin_fma(t2, t2, acc[2]);
+      acc[3] = __builtin_fma(t3, t3, acc[3]);
+      if (select) {  // (the same for the whole wavefront)
+        const U32x4 rnd = philox4x32_10((uint32_t)(chunk * V) + at, m, iter, 0u, k0, k1);
+        stage_candidates<true>(stage[wave], draws[wave], v, rnd, c1, j, lane, base);
+      }
+    }
+    if (!select || !write_slot(stage[wave], draws[wave], base, lane, slots + ((uint64_t)m * ntiles + chunk * T + t) * kSlotEntries))
+      nover += 1u;
+    if (t == T - 1) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sums[mm][4 * lane + i] = acc[i];
+    }
+  };
+  for (uint32_t i = 0; i < items; i += 3) {
+    request(b2, i + 2);
+    work(b0, i);
+    request(b0, i + 3);
+    if (i + 1 < items) work(b1, i + 1);
+    request(b1, i + 4);
+    if (i + 2 < items) work(b2, i + 2);
+  }
+  if (lane == 0) over[wave] = nover;
+  __syncthreads();
+  if (threadIdx.x < count) {
+    double total = 0.0;
+#pragma unroll 16
+    for (int j = 0; j < kTreeLanes; ++j) total = total + sums[threadIdx.x][j];
+    chunk_sums[(uint64_t)(m0 + threadIdx.x) * nchunks + chunk] = total;
+  }
+  if (threadIdx.x == 0) {
+    uint32_t total = 0;
+#pragma unroll
+    for (int k = 0; k < kWavesPerBlock; ++k) total += over[k];
+    if (total != 0u) atomicAdd(&overflowed[blockIdx.x % kL2OverflowCounts], total);
+  }
+}
+
 // One workgroup per worker: group sums (thread q adds the chunks of groups q, q + 256, ... in order),
 // then thread 0 adds the groups in order.  MEAN: out[m] = float(total / d), and, when chunk_minmax is
 // given, scales[m] = max |g - out[m]| from the smallest and the largest element.  Otherwise
@@ -1891,6 +2050,21 @@ inline CandidateScratch candidate_scratch(const CodecShape& c, void* scratch) {
   return cs;
 }
 
+// The sample: every kSampleStride-th whole wavefront tile of every row.
+template <int NORM, bool L2>
+hipError_t sample_launch(const CodecShape& c, const float* g, const float* gref, const CandidateScratch& cs, hipStream_t s) {
+  const uint64_t sample_tiles = (c.d / kWaveTileElements + kSampleStride - 1) / kSampleStride;
+  uint32_t nsample = div_up_u32(sample_tiles, kWavesPerBlock);
+  if (nsample > kAbsmaxMaxBlocks) nsample = kAbsmaxMaxBlocks;
+  hipLaunchKernelGGL((sample_stats_kernel<NORM, L2>), dim3(nsample, c.M), dim3(kBlock), 0, s, GradRows{g, c.d},
+                     reinterpret_cast<const float4*>(gref), cs.sample_partials, cs.sample_sums, c.d / 4, c.M);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(sample_finish_kernel<L2>, dim3(c.M), dim3(kBlock), 0, s, cs.sample_partials, cs.sample_sums, nsample,
+                     c.M, (float)(sample_tiles * kWaveTileElements), cs.sample_max, cs.select_ok, cs.overflowed);
+  return hipGetLastError();
+}
+
 template <int NORM>
 hipError_t absmax_candidates_dispatch(const CodecShape& c, uint32_t iter, const float* g, const float* gref,
                                       const float* gref2, float* partials, const CandidateScratch& cs, float* scales,
@@ -1903,17 +2077,9 @@ hipError_t absmax_candidates_dispatch(const CodecShape& c, uint32_t iter, const 
   if (mc == 8 && (c.M + groups - 1) / groups <= 5) mc = 5;
   uint32_t nblocks = 0;
   hipError_t e;
-  // the sample: every kSampleStride-th wavefront tile of every row
-  const uint64_t row_tiles = nvec / (kWave * kAbsmaxLoads);
-  const uint64_t sample_tiles = (row_tiles + kSampleStride - 1) / kSampleStride;
-  uint32_t nsample = div_up_u32(sample_tiles, kWavesPerBlock);
-  if (nsample > kAbsmaxMaxBlocks) nsample = kAbsmaxMaxBlocks;
-  hipLaunchKernelGGL((sample_stats_kernel<NORM>), dim3(nsample, c.M), dim3(kBlock), 0, s, GradRows{g, c.d},
-                     reinterpret_cast<const float4*>(gref), cs.sample_partials, cs.sample_sums, nvec, c.M);
-  e = hipGetLastError();
+  e = sample_launch<NORM, false>(c, g, gref, cs, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(sample_finish_kernel, dim3(c.M), dim3(kBlock), 0, s, cs.sample_partials, cs.sample_sums, nsample,
-                     c.M, (float)(sample_tiles * (kWave * kAbsmaxLoads * 4)), cs.sample_max, cs.select_ok);
+  const uint64_t row_tiles = c.d / kWaveTileElements;
   const uint32_t tail = tail_workgroups(c.d, mc);
   const uint32_t per_y = div_up_u32(row_tiles, kWavesPerBlock);
   const uint32_t cap = kAbsmaxMaxBlocks - 1 - tail;
@@ -1933,7 +2099,7 @@ hipError_t absmax_candidates_dispatch(const CodecShape& c, uint32_t iter, const 
 #undef TNG_SELECT
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(absmax_finish_vote_kernel, dim3(c.M + 1), dim3(kBlock), 0, s, partials, nblocks, c.M, scales,
+  hipLaunchKernelGGL(absmax_finish_vote_kernel, dim3(c.M + 1), dim3(kBlock), 0, s, partials, nblocks, c.M, c.M, scales,
                      cs.overflowed, nblocks * ((c.M + (uint32_t)mc - 1) / (uint32_t)mc),
                      (uint64_t)c.M * (nvec / (kWave * kAbsmaxLoads)), cs.use_slots);
   return hipGetLastError();
@@ -1949,13 +2115,14 @@ hipError_t quantize_candidates_dispatch(const CodecShape& c, uint32_t iter, cons
                                         const float* gref2, const float* scales, const CandidateScratch& cs,
                                         uint32_t* codes, hipStream_t s) {
   const uint64_t tiles = (c.d / kWaveTileElements + kWavesPerBlock - 1) / kWavesPerBlock;  // workgroups of 4 wavefront tiles
+  const uint64_t slot_tiles = c.scale_l2 ? c.d / kTreeChunk * (kTreeChunk / kWaveTileElements) : c.d / kWaveTileElements;
   const int mc = pick_workers_per_block(c.M, tiles, 0.0, 8);  // (no reference to share between more: M = 16, d = 2^24 387 us
                                                                        // per iteration with 16, 373 with 8)
 #define TNG_QC(MC)                                                                                                   \
   hipLaunchKernelGGL((quantize_candidates_kernel<NORM, MC>),                                                           \
                      dim3((uint32_t)tiles, (c.M + MC - 1) / MC), dim3(kBlock), 0,             \
                      s, GradRows{g, c.d}, reinterpret_cast<const float4*>(gref), reinterpret_cast<const float4*>(gref2), \
-                     scales, cs.slots, codes, c.d, c.words, c.M, c.eps, c.k0, c.k1, iter, cs.use_slots, cs.select_ok)
+                     scales, cs.slots, codes, c.d, c.words, slot_tiles, c.M, c.eps, c.k0, c.k1, iter, cs.use_slots, cs.select_ok)
   switch (mc) {
     case 8: TNG_QC(8); break;
     case 4: TNG_QC(4); break;
@@ -2140,13 +2307,32 @@ size_t tree_sum_scratch(uint64_t d, uint32_t M) {
 }
 
 namespace {
+// The ragged last chunk of every row.
+template <int NORM>
+hipError_t l2_last_chunk_launch(const CodecShape& c, const float* g, const float* gref, const float* gref2, double* sums,
+                                uint64_t whole, uint64_t nchunks, hipStream_t s) {
+  auto kernel = c.d % 4 == 0 ? tree_chunk_kernel<NORM, true, true, false> : tree_chunk_kernel<NORM, true, false, false>;
+  hipLaunchKernelGGL(kernel, dim3(1, c.M), dim3(kBlock), 0, s, g, gref, gref2, c.means, sums, nullptr, c.d, whole, nchunks,
+                     nchunks, c.eps, c.M, 1u);
+  return hipGetLastError();
+}
+
+// Group and row sums from the chunk sums (behind them: the chunks' extremes, then room for the group sums).
+template <bool MEAN>
+hipError_t tree_finish_launch(const CodecShape& c, double* sums, const float2* minmax, uint64_t nchunks, uint64_t ngroups,
+                              float* out, float* scales, hipStream_t s) {
+  double* group_sums = sums + 2 * nchunks * c.M;
+  hipLaunchKernelGGL(tree_finish_kernel<MEAN>, dim3(c.M), dim3(kBlock), 0, s, sums, group_sums, minmax, nchunks, ngroups,
+                     c.d, out, scales);
+  return hipGetLastError();
+}
+
 template <int NORM, bool SQUARE, bool MINMAX>
 hipError_t tree_sum_launch(const CodecShape& c, const float* g, const float* gref, const float* gref2, double* sums,
                            float* out, float* scales, hipStream_t s) {
   const uint64_t nchunks = (c.d + kTreeChunk - 1) / kTreeChunk;
   const uint64_t ngroups = (nchunks + kTreeGroup - 1) / kTreeGroup;
   float2* minmax = reinterpret_cast<float2*>(sums + nchunks * c.M);
-  double* group_sums = sums + 2 * nchunks * c.M;
   const uint32_t gx = (uint32_t)((nchunks + kWavesPerBlock - 1) / kWavesPerBlock);
   constexpr bool kSharedRef = NORM == kNormSub || NORM == kNormQuot || NORM == kNormComb;
   const uint64_t whole = c.d / kTreeChunk;  // chunks that lie inside the rows entirely
@@ -2171,19 +2357,10 @@ hipError_t tree_sum_launch(const CodecShape& c, const float* g, const float* gre
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (whole < nchunks) {  // the ragged last chunk of every row
-      if (c.d % 4 == 0) {
-        hipLaunchKernelGGL((tree_chunk_kernel<NORM, SQUARE, true, false>), dim3(1, c.M), dim3(kBlock), 0, s, g, gref,
-                           gref2, c.means, sums, minmax, c.d, whole, nchunks, nchunks, c.eps, c.M, 1u);
-      } else {
-        hipLaunchKernelGGL((tree_chunk_kernel<NORM, SQUARE, false, false>), dim3(1, c.M), dim3(kBlock), 0, s, g, gref,
-                           gref2, c.means, sums, minmax, c.d, whole, nchunks, nchunks, c.eps, c.M, 1u);
-      }
-      e = hipGetLastError();
+      e = l2_last_chunk_launch<NORM>(c, g, gref, gref2, sums, whole, nchunks, s);
       if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL((tree_finish_kernel<false>), dim3(c.M), dim3(kBlock), 0, s, sums, group_sums, nullptr, nchunks,
-                       ngroups, c.d, out, scales);
-    return hipGetLastError();
+    return tree_finish_launch<false>(c, sums, nullptr, nchunks, ngroups, out, scales, s);
   }
   // workers per workgroup: as many as leave 2048 workgroups (only worth it when a reference is shared)
   uint32_t wpb = 1;
@@ -2205,9 +2382,31 @@ hipError_t tree_sum_launch(const CodecShape& c, const float* g, const float* gre
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((tree_finish_kernel<!SQUARE>), dim3(c.M), dim3(kBlock), 0, s, sums, group_sums,
-                     MINMAX ? minmax : nullptr, nchunks, ngroups, c.d, out, scales);
-  return hipGetLastError();
+  return tree_finish_launch<!SQUARE>(c, sums, MINMAX ? minmax : nullptr, nchunks, ngroups, out, scales, s);
+}
+
+template <int NORM>
+hipError_t l2_candidates_launch(const CodecShape& c, uint32_t iter, const float* g, const float* gref, double* sums,
+                                const CandidateScratch& cs, float* scales, hipStream_t s) {
+  const uint64_t nchunks = (c.d + kTreeChunk - 1) / kTreeChunk, ngroups = (nchunks + kTreeGroup - 1) / kTreeGroup;
+  const uint64_t whole = c.d / kTreeChunk;  // chunks that lie inside the rows entirely
+  hipError_t e = sample_launch<NORM, true>(c, g, gref, cs, s);
+  if (e != hipSuccess) return e;
+  const dim3 grid((uint32_t)whole, (c.M + kL2SelectWorkers - 1) / kL2SelectWorkers);
+  hipLaunchKernelGGL(l2_select_kernel<NORM>, grid, dim3(kBlock), 0, s, GradRows{g, c.d},
+                     reinterpret_cast<const float4*>(gref), sums, c.d / kWaveTileElements, nchunks, c.M, cs.sample_max,
+                     cs.select_ok, cs.slots, cs.overflowed, c.k0, c.k1, iter);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if (whole < nchunks) {
+    e = l2_last_chunk_launch<NORM>(c, g, gref, nullptr, sums, whole, nchunks, s);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(absmax_finish_vote_kernel, dim3(1), dim3(kBlock), 0, s, nullptr, 0u, c.M, 0u, scales, cs.overflowed,
+                     kL2OverflowCounts, (uint64_t)c.M * whole * (kTreeChunk / kWaveTileElements), cs.use_slots);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return tree_finish_launch<false>(c, sums, nullptr, nchunks, ngroups, scales, nullptr, s);
 }
 }  // namespace
 
@@ -2229,10 +2428,12 @@ hipError_t launch_l2_scales(const CodecShape& c, const float* g, const float* gr
 }
 
 size_t candidate_scratch_bytes(const CodecShape& c) {
-  // 2-bit codes, largest-magnitude scale, a shared reference or none, and enough
+  // 2-bit codes, a shared reference or none, and enough
   // elements (2^26: 256 MiB of gradients) for the extra launches of the sample to be noise
   // (not the quotient forms: there |v| is near 1 everywhere and a third of the elements code non-zero)
-  if (c.bits != 2 || c.scale_l2 != 0 || (c.norm != kNormNone && c.norm != kNormSub)) return 0;
+  if (c.bits != 2 || (c.norm != kNormNone && c.norm != kNormSub)) return 0;
+  // (the l2 scale: nor fewer workers than a workgroup has wavefronts)
+  if (c.scale_l2 != 0 && c.M < (uint32_t)kWavesPerBlock) return 0;
   if ((uint64_t)c.M * c.d < (1ull << 26) || c.d / 1024 < 4 * (uint64_t)kSampleStride) return 0;
   return candidate_head_bytes(c.M) + (size_t)c.M * (c.d / 1024) * kSlotEntries * sizeof(uint32_t);
 }
@@ -2247,6 +2448,13 @@ hipError_t launch_absmax_candidates(const CodecShape& c, uint32_t iter, const fl
   const CandidateScratch cs = candidate_scratch(c, scratch);
   if (c.norm == kNormSub) return absmax_candidates_dispatch<kNormSub>(c, iter, g, gref, nullptr, partials, cs, scales, s);
   return absmax_candidates_dispatch<kNormNone>(c, iter, g, nullptr, nullptr, partials, cs, scales, s);
+}
+
+hipError_t launch_l2_candidates(const CodecShape& c, uint32_t iter, const float* g, const float* gref, double* sums,
+                                void* scratch, float* scales, hipStream_t s) {
+  const CandidateScratch cs = candidate_scratch(c, scratch);
+  if (c.norm == kNormSub) return l2_candidates_launch<kNormSub>(c, iter, g, gref, sums, cs, scales, s);
+  return l2_candidates_launch<kNormNone>(c, iter, g, nullptr, sums, cs, scales, s);
 }
 
 hipError_t launch_quantize_candidates(const CodecShape& c, uint32_t iter, const float* g, const float* gref,

@@ -46,7 +46,7 @@ hipError_t launch_worker_means(const CodecShape& c, const float* g, double* sums
 hipError_t launch_l2_scales(const CodecShape& c, const float* g, const float* gref, const float* gref2, double* sums,
                             float* scales, hipStream_t s);
 
-// The ternary coder that reads g once (2-bit codes, largest-magnitude scale): the scale pass also keeps,
+// The ternary coder that reads g once (2-bit codes): the scale pass also keeps,
 // per worker and tile of 1024 coordinates, the few elements that can code non-zero whatever the scale turns
 // out to be (tested against a lower bound of it), and the quantise pass codes those from the slots instead
 // of reading g again; same codes and scales as launch_absmax + launch_quantize_pack, bit for bit.
@@ -57,6 +57,9 @@ size_t candidate_scratch_bytes(const CodecShape& c);
 bool candidates_apply(const CodecShape& c, const float* g, const float* gref, const float* gref2, const uint32_t* codes);
 hipError_t launch_absmax_candidates(const CodecShape& c, uint32_t iter, const float* g, const float* gref,
                                     const float* gref2, float* partials, void* scratch, float* scales, hipStream_t s);
+// The same for the l2 scale (sums: as for launch_l2_scales).
+hipError_t launch_l2_candidates(const CodecShape& c, uint32_t iter, const float* g, const float* gref, double* sums,
+                                void* scratch, float* scales, hipStream_t s);
 hipError_t launch_quantize_candidates(const CodecShape& c, uint32_t iter, const float* g, const float* gref,
                                       const float* gref2, const float* scales, void* scratch, uint32_t* codes,
                                       hipStream_t s);

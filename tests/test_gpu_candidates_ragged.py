@@ -45,3 +45,24 @@ def test_dense_rows(dense):
     for m in dense:
         g[m] = gref + torch.randn(d, device=DEV, generator=torch.Generator(device=DEV).manual_seed(m))
     check(M, d, B.NORM_SUB, g, gref, 4)
+
+
+@pytest.mark.parametrize("M,d,norm", [(4, 1 << 24, B.NORM_SUB), (5, (1 << 24) + 4096 * 3, B.NORM_NONE), (9, 1 << 23, B.NORM_SUB),
+                                      (20, (1 << 22) + 1027, B.NORM_SUB), (8, (1 << 23) + 4092, B.NORM_NONE)])
+def test_l2_scale(M, d, norm):
+    g, gref, _ = _inputs(M, d, seed=M)
+    gen = torch.Generator(device=DEV).manual_seed(M)
+    v = g - gref
+    v[0, 1024 * 77:1024 * 79] *= 1e6  # nearly the whole norm in two tiles that the sample does not visit: they overflow
+    v[1] = 0.0
+    v[2] = (torch.rand(d, generator=gen, device=DEV) - 0.5) * 1e-38  # a norm near the smallest normal number
+    v[3, 5000:] = 0.0  # a row of few elements that the sample sees: too dense where it is not zero
+    check(M, d, norm, (v + gref if norm == B.NORM_SUB else v).contiguous(), gref, 2, B.SCALE_L2)
+
+
+def test_l2_scale_outside_the_sample():
+    # rows that are zero wherever the sample looks: no bound, every non-zero element is a candidate and most tiles overflow
+    M, d = 8, 1 << 23
+    v = torch.randn((M, d), device=DEV, generator=torch.Generator(device=DEV).manual_seed(1))
+    v.view(M, -1, 1024)[:, ::128] = 0.0
+    check(M, d, B.NORM_NONE, v, v[0].clone(), 2, B.SCALE_L2)
