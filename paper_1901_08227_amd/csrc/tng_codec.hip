@@ -1898,27 +1898,44 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
   }
 }
 
-// One workgroup per worker: group sums (thread q adds the chunks of groups q, q + 256, ... in order),
-// then thread 0 adds the groups in order.  MEAN: out[m] = float(total / d), and, when chunk_minmax is
+// One workgroup per worker: the chunk sums come to LDS kFinishGroups groups at a time, in whole lines (a thread per
+// group that fetched its 256 chunk sums one after the other took 25 us at d = 2^24; 8 this way), a thread adds a group in
+// order, and thread 0 the groups in order.  MEAN: out[m] = float(total / d), and, when chunk_minmax is
 // given, scales[m] = max |g - out[m]| from the smallest and the largest element.  Otherwise
 // out[m] = float(sqrt(total)), 0 when below FLT_MIN.  Division and square root of binary64 are
 // correctly rounded on the device, so the float32 result is the same as on any IEEE host.
+constexpr int kFinishGroups = 16;
 template <bool MEAN>
 __global__ __launch_bounds__(kBlock) void tree_finish_kernel(const double* __restrict__ chunk_sums,
-                                                             double* __restrict__ group_sums,
                                                              const float2* __restrict__ chunk_minmax,
                                                              uint64_t nchunks, uint64_t ngroups, uint64_t d,
                                                              float* __restrict__ out, float* __restrict__ scales) {
   __shared__ float red_lo[kWavesPerBlock], red_hi[kWavesPerBlock];
+  __shared__ double part[kFinishGroups][kTreeGroup + 1];  // (one of padding: the groups' threads read different banks)
+  __shared__ double group[kFinishGroups];
   const uint32_t m = blockIdx.x;
   const double* __restrict__ cs = chunk_sums + (uint64_t)m * nchunks;
-  double* __restrict__ gs = group_sums + (uint64_t)m * ngroups;
-  for (uint64_t q = threadIdx.x; q < ngroups; q += kBlock) {
-    const uint64_t c0 = q * kTreeGroup;
-    const uint64_t c1 = c0 + kTreeGroup < nchunks ? c0 + kTreeGroup : nchunks;
-    double a = 0.0;
-    for (uint64_t c = c0; c < c1; ++c) a = a + cs[c];
-    gs[q] = a;
+  double total = 0.0;  // thread 0
+  for (uint64_t q0 = 0; q0 < ngroups; q0 += kFinishGroups) {
+    const uint64_t c0 = q0 * kTreeGroup;
+    const uint32_t n = (uint32_t)min((uint64_t)(kFinishGroups * kTreeGroup), nchunks - c0);
+    __syncthreads();  // the batch before has been added
+#pragma unroll
+    for (int k = 0; k < kFinishGroups; ++k) {
+      const uint32_t i = (uint32_t)k * kTreeGroup + threadIdx.x;
+      part[k][threadIdx.x] = i < n ? cs[c0 + i] : 0.0;
+    }
+    __syncthreads();
+    if (threadIdx.x < (uint32_t)kFinishGroups) {
+      const uint32_t first = threadIdx.x * kTreeGroup, count = first < n ? min((uint32_t)kTreeGroup, n - first) : 0u;
+      double a = 0.0;
+#pragma unroll 16
+      for (uint32_t c = 0; c < count; ++c) a = a + part[threadIdx.x][c];
+      group[threadIdx.x] = a;
+    }
+    wave_lds_fence();  // (the groups' threads and thread 0 are one wavefront)
+    if (threadIdx.x == 0)
+      for (uint32_t q = 0; q < (uint32_t)kFinishGroups && q0 + q < ngroups; ++q) total = total + group[q];
   }
   if (MEAN && chunk_minmax != nullptr) {
     float lo = INFINITY, hi = -INFINITY;
@@ -1934,11 +1951,8 @@ __global__ __launch_bounds__(kBlock) void tree_finish_kernel(const double* __res
       red_hi[threadIdx.x / kWave] = hi;
     }
   }
-  __threadfence_block();
   __syncthreads();
   if (threadIdx.x == 0) {
-    double total = 0.0;
-    for (uint64_t q = 0; q < ngroups; ++q) total = total + gs[q];
     if (MEAN) {
       const float mu = (float)(total / (double)d);
       out[m] = mu;
@@ -2317,13 +2331,12 @@ hipError_t l2_last_chunk_launch(const CodecShape& c, const float* g, const float
   return hipGetLastError();
 }
 
-// Group and row sums from the chunk sums (behind them: the chunks' extremes, then room for the group sums).
+// The row sums from the chunk sums.
 template <bool MEAN>
 hipError_t tree_finish_launch(const CodecShape& c, double* sums, const float2* minmax, uint64_t nchunks, uint64_t ngroups,
                               float* out, float* scales, hipStream_t s) {
-  double* group_sums = sums + 2 * nchunks * c.M;
-  hipLaunchKernelGGL(tree_finish_kernel<MEAN>, dim3(c.M), dim3(kBlock), 0, s, sums, group_sums, minmax, nchunks, ngroups,
-                     c.d, out, scales);
+  hipLaunchKernelGGL(tree_finish_kernel<MEAN>, dim3(c.M), dim3(kBlock), 0, s, sums, minmax, nchunks, ngroups, c.d, out,
+                     scales);
   return hipGetLastError();
 }
 
