@@ -206,10 +206,11 @@ bool single_pass_ok(const tng_ctx* ctx, const float* g, const float* gref, const
 
 // The scale pass.  fused_rows > 0: a gradient kernel has already left that many rows of partial maxima in the
 // workspace, only their reduction remains.  On return *rows is the number of rows of partial maxima whose reduction
-// is left to the next launch (0: scales is complete; the pass leaves at most max_left of its own), and
+// is left to the next launch (0: scales is complete; the pass leaves at most max_left of its own), and, if slots_ok,
 // *by_candidates tells that the candidate slots hold what the quantise pass needs.
 tng_status scale_impl(tng_ctx* ctx, uint32_t iter, const float* g, const float* gref, const uint32_t* codes,
-                      float* scales, uint32_t fused_rows, uint32_t max_left, uint32_t* rows, bool* by_candidates) {
+                      float* scales, uint32_t fused_rows, uint32_t max_left, bool slots_ok, uint32_t* rows,
+                      bool* by_candidates) {
   hipError_t e = hipSuccess;
   *rows = 0;
   *by_candidates = false;
@@ -229,7 +230,7 @@ tng_status scale_impl(tng_ctx* ctx, uint32_t iter, const float* g, const float* 
     e = tng::launch_l2_scales(ctx->shape, g, gref, ctx->gref2, ctx->sums, scales, ctx->stream);
   } else if (fused_rows > 0) {
     *rows = fused_rows;
-  } else if (ctx->cand != nullptr && tng::candidates_apply(ctx->shape, g, gref, ctx->gref2, codes)) {
+  } else if (slots_ok && ctx->cand != nullptr && tng::candidates_apply(ctx->shape, g, gref, ctx->gref2, codes)) {
     // long rows of ternary codes: the scale pass also picks out the elements that can code non-zero, and the
     // quantise pass works from those instead of reading g again
     *by_candidates = true;
@@ -259,7 +260,7 @@ tng_status encode_impl(tng_ctx* ctx, uint32_t iter, const float* g, const float*
   uint32_t rows = 0;
   bool by_candidates = false;
   mark(ctx, call, 0);
-  tng_status s = scale_impl(ctx, iter, g, gref, codes, scales, fused_rows, tng::quantize_fused_rows(ctx->shape), &rows,
+  tng_status s = scale_impl(ctx, iter, g, gref, codes, scales, fused_rows, tng::quantize_fused_rows(ctx->shape), true, &rows,
                             &by_candidates);
   if (s != TNG_OK) return s;
   mark(ctx, call, 1);
@@ -679,7 +680,11 @@ tng_status tng_step(tng_ctx* ctx, uint32_t iter, float* w, float* gref, float* g
   } else if (ctx->prof_slots == 0 && tng::quantize_decode_applies(ctx->shape)) {
     uint32_t rows = 0;
     bool by_candidates = false;
-    s = scale_impl(ctx, iter, g, gref, codes, scales, fused_rows, tng::quantize_decode_rows(ctx->shape), &rows,
+    // The candidate slots save the second read of g, one launch the second trip of the codes and the reference: at 2^26
+    // to 2^27 gradients the latter is ahead with 5 to 16 workers (d = 2^24, M = 8: 244 against 287 us; d = 2^25, M = 8:
+    // 504 against 498; d = 2^24, M = 4: 164 against 152).
+    const bool slots_ok = c.M <= 4 || c.M > 16 || (uint64_t)c.M * c.d > (1ull << 27);
+    s = scale_impl(ctx, iter, g, gref, codes, scales, fused_rows, tng::quantize_decode_rows(ctx->shape), slots_ok, &rows,
                    &by_candidates);
     if (s != TNG_OK) return s;
     if (by_candidates) {
