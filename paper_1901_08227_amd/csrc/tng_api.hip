@@ -30,7 +30,7 @@ struct tng_ctx {
   float noise_sigma;      // > 0: Gaussian noise is generated on the device instead
   const float* gref2;     // second reference of the combined normalisation
   float* history;         // [ref_window][d] ring of decoded averages (window-average reference)
-  float* parts;           // dense problem, wide rows: partial gradients [M][splits][d] of the one-pass kernel, or null
+  float* parts;           // dense problem: partial gradients [M][splits][d] of the one-pass kernels, or null
   uint32_t* check;        // CSR problem: flag word of tng_validate_csr, then uint64[M] entry counts at +256 bytes
   double* sums;           // chunk and group sums of the order-pinned row sums (mean reference, l2 scale)
   void* cand;             // scratch of the ternary coder that reads g once (candidate slots), or null
@@ -119,9 +119,9 @@ Partition partition(const tng_config* c) {
     off += round_up(tng::tree_sum_scratch(c->d, c->M) * sizeof(double));
   p.check_off = off;  // tng_validate_csr: a flag word and the per-worker entry counts
   if (c->problem == TNG_PROB_LOGREG_CSR) off += round_up(256 + (size_t)c->M * sizeof(uint64_t));
-  p.parts_off = off;  // dense problem, wide rows: per-workgroup partial gradients of the one-pass kernel
+  p.parts_off = off;  // dense problem: per-workgroup partial gradients of the one-pass kernels
   if (c->problem == TNG_PROB_LOGREG_DENSE)
-    off += round_up((size_t)tng::dense_row_splits(c->d, c->M, c->batch) * c->M * c->d * sizeof(float));
+    off += round_up(tng::dense_parts_floats(c->d, c->M, c->batch) * sizeof(float));
   p.cand_off = off;  // ternary coder that reads g once: sample maxima and candidate slots
   p.cand_bytes = tng::candidate_scratch_bytes(shape_of(c));
   off += round_up(p.cand_bytes);
@@ -664,6 +664,14 @@ tng_status tng_step(tng_ctx* ctx, uint32_t iter, float* w, float* gref, float* g
   // where the decode pass leaves a second copy of the decoded average: its slot of the history ring
   // (window average), or the reference itself when it is refreshed now (last average)
   float* ref_out = window ? ctx->history + (uint64_t)slot * c.d : (refresh_now(c, iter) ? gref : nullptr);
+  if (c.problem == TNG_PROB_LOGREG_DENSE && ctx->prof_slots == 0 && ctx->parts != nullptr && c.norm != TNG_NORM_MEAN &&
+      c.scale == TNG_SCALE_MAX && tng::dense_small_splits(c.d, c.M, c.batch) != 0) {
+    s = hip_status(tng::launch_dense_small_step(logreg_tables(ctx), ctx->shape, c.batch, c.l2, iter, ctx->idx, ctx->parts,
+                                                w, g, gref, ctx->gref2, scales, codes, vbar, c.lr, ref_out, ctx->stream));
+    if (s == TNG_OK && window && refresh_now(c, iter))
+      s = hip_status(tng::launch_window_mean(ctx->history, c.ref_window, (slot + 1) % c.ref_window, c.d, gref, ctx->stream));
+    return s;
+  }
   uint32_t fused_rows = 0;
   if (c.problem != TNG_PROB_EXTERNAL) {
     const tng::ScaleFusion fuse{c.norm, c.quot_eps, gref, ctx->gref2, ctx->partials};

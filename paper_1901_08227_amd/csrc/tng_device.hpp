@@ -288,6 +288,19 @@ __device__ __forceinline__ float wave_max_nonneg(float x) {
   return __uint_as_float((uint32_t)__builtin_amdgcn_readlane(v, 63));
 }
 
+// The sum over the wavefront, the same value in every lane, by the lane moves of wave_max_nonneg.
+__device__ __forceinline__ float wave_sum_uniform(float v) {
+#define TNG_MOVED(CTRL, ROWS) __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, ROWS, 0xF, false))
+  v += TNG_MOVED(0xB1, 0xF);
+  v += TNG_MOVED(0x4E, 0xF);
+  v += TNG_MOVED(0x141, 0xF);
+  v += TNG_MOVED(0x140, 0xF);
+  v += TNG_MOVED(0x142, 0xA);  // rows 1 and 3, the others add 0
+  v += TNG_MOVED(0x143, 0xC);
+#undef TNG_MOVED
+  return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), 63));
+}
+
 // max(|a|, |b|, c) in one instruction (the magnitudes are taken by the operand modifiers).
 __device__ __forceinline__ float max3_abs(float a, float b, float c) {
   float r;

@@ -316,6 +316,172 @@ __global__ __launch_bounds__(kSplitThreads) void logreg_dense_grad_split_kernel(
   }
 }
 
+// ------------------------------------------------------------------------------------------
+// Dense problems whose gradients fit one workgroup (M * d <= 4096): what bounds an iteration is its launches, about 4.4 us
+// of the host each, so there are two.  The first takes the rows once: a thread keeps its float4 column of kSmallRows
+// rows in registers between the dot products and the accumulation, and a workgroup leaves the partial gradient of its
+// share of a worker's minibatch (parts[m][s][4 ceil(d / 4)], zero past d).  The second, one workgroup, adds those in
+// order and (STEP) does all the rest of the iteration: a thread has one float4 of one worker.
+// Iterations, three launches against these two: d = 1000, M = 4, B = 64 13.8 -> 12.1 us (5.1 + 6.8: the one workgroup
+// reads 128 KiB of partial gradients), B = 512 23.5 -> 17.7; d = 64, M = 1, B = 8 13.2 -> 9.6 (the launches); d = 100, M = 32,
+// B = 512 35.6 -> 19.3.  More rows per trip mean fewer partial gradients: 4 rows 12.9, 8 rows 12.1 us at d = 1000.
+// ------------------------------------------------------------------------------------------
+constexpr int kSmallRows = 8;
+
+// Columns 4 q .. 4 q + 3 of a row of d >= 4, 0 past its end.
+__device__ __forceinline__ float4 load4_row_end(GlobalPtr<float> row, uint32_t q, uint32_t d) {
+  const uint32_t col = min(4 * q, d - 4), past = 4 * q - col;  // columns of the float4 that lie past the end
+  const float4 v = load4_stream_any(row + col, 0);
+  return make_float4(past == 0 ? v.x : past == 1 ? v.y : past == 2 ? v.z : v.w,
+                     past == 0 ? v.y : past == 1 ? v.z : past == 2 ? v.w : 0.f,
+                     past == 0 ? v.z : past == 1 ? v.w : 0.f, past == 0 ? v.w : 0.f);
+}
+
+__global__ __launch_bounds__(kBlock) void logreg_dense_small_kernel(const float* const* __restrict__ Xs,
+                                                                    const float* const* __restrict__ ys,
+                                                                    const uint64_t* __restrict__ n_rows,
+                                                                    uint32_t* __restrict__ idx,
+                                                                    const float* __restrict__ w,
+                                                                    float4* __restrict__ parts, uint32_t d,
+                                                                    uint32_t batch, uint32_t k0, uint32_t k1,
+                                                                    uint32_t iter) {
+  __shared__ float red[2][kSmallRows][kWavesPerBlock];
+  const uint32_t m = blockIdx.y, s = blockIdx.x, S = gridDim.x, t = threadIdx.x;
+  const uint32_t nvec = (d + 3) / 4;
+  const uint32_t q = min(t, nvec - 1);  // idle threads fetch the last column
+  const GlobalPtr<float> X = as_global(Xs[m]), y = as_global(ys[m]);
+  const uint64_t n = n_rows[m];
+  const float4 wv = t < nvec ? load4_row_end(as_global(w), q, d) : make_float4(0.f, 0.f, 0.f, 0.f);
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  uint32_t parity = 0;
+  for (uint32_t i0 = s; i0 < batch; i0 += S * kSmallRows, parity ^= 1u) {
+    // lane r draws row r of the trip; a short last trip fetches its first row in place of those that it lacks
+    const uint32_t mine = i0 + (t % kSmallRows) * S;
+    const uint32_t drawn = minibatch_row(k0, k1, iter, m, mine < batch ? mine : i0, n);
+    if (t < (uint32_t)kSmallRows && mine < batch) idx[(uint64_t)m * batch + mine] = drawn;
+    const float label = y[drawn];
+    float4 x[kSmallRows];
+#pragma unroll
+    for (int r = 0; r < kSmallRows; ++r)
+      x[r] = load4_row_end(X + (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)drawn, r) * d, q, d);
+#pragma unroll
+    for (int r = 0; r < kSmallRows; ++r) {
+      const float p = __builtin_fmaf(x[r].x, wv.x, x[r].y * wv.y) + __builtin_fmaf(x[r].z, wv.z, x[r].w * wv.w);
+      const float z = wave_sum_uniform(t < nvec ? p : 0.f);
+      if (t % kWave == 0) red[parity][r][t / kWave] = z;
+    }
+    __syncthreads();  // (two sets of slots alternate: one barrier per trip is enough)
+    // lane r of every wavefront makes the residual of row r
+    float z = red[parity][t % kSmallRows][0];
+#pragma unroll
+    for (int k = 1; k < kWavesPerBlock; ++k) z += red[parity][t % kSmallRows][k];
+    const float residual = logistic_residual(z, label);
+#pragma unroll
+    for (int r = 0; r < kSmallRows; ++r) {
+      if (i0 + (uint32_t)r * S >= batch) break;
+      const float res = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(residual), r));
+      acc.x = __builtin_fmaf(res, x[r].x, acc.x);
+      acc.y = __builtin_fmaf(res, x[r].y, acc.y);
+      acc.z = __builtin_fmaf(res, x[r].z, acc.z);
+      acc.w = __builtin_fmaf(res, x[r].w, acc.w);
+    }
+  }
+  if (t < nvec) parts[((uint64_t)m * S + s) * nvec + t] = acc;
+}
+
+typedef uint8_t __attribute__((may_alias)) lds_byte;
+typedef uint16_t __attribute__((may_alias)) lds_half;
+constexpr uint32_t kSmallThreads = 1024;
+template <int NORM, int BITS, bool STEP>
+__global__ __launch_bounds__(kSmallThreads) void logreg_dense_small_finish_kernel(
+    const float4* __restrict__ parts, uint32_t S, float* w, float* __restrict__ g, uint32_t d, uint32_t M, float inv_b,
+    float l2, const float* gref, const float* gref2, float eps, float* __restrict__ scales, uint32_t* __restrict__ codes,
+    uint32_t words, uint32_t k0, uint32_t k1, uint32_t iter, float* __restrict__ vbar, float* refout, float inv_m,
+    float lr) {
+  __shared__ float4 value[STEP ? kSmallThreads : 1];
+  __shared__ uint32_t packed[STEP ? kSmallThreads : 1];  // [M][words]
+  __shared__ uint32_t top[STEP ? kSmallThreads : 1];     // the workers' scales as bits
+  const uint32_t nvec = (d + 3) / 4, t = threadIdx.x;
+  const bool active = t < M * nvec;
+  const uint32_t m = active ? t / nvec : M - 1, q = active ? t % nvec : nvec - 1;
+  if (STEP) packed[t] = top[t] = 0u;
+  float4 acc = parts[(uint64_t)m * S * nvec + q];
+#pragma unroll 8
+  for (uint32_t s = 1; s < S; ++s) {
+    const float4 v = parts[((uint64_t)m * S + s) * nvec + q];
+    acc.x += v.x;
+    acc.y += v.y;
+    acc.z += v.z;
+    acc.w += v.w;
+  }
+  // (asked for ahead of the parts, the iterate and the references cost 4 us at 32 parts)
+  const float4 wv = load4_within(w, 4 * q, d, 0.f);
+  const float4 o = make_float4(__builtin_fmaf(l2, wv.x, acc.x * inv_b), __builtin_fmaf(l2, wv.y, acc.y * inv_b),
+                               __builtin_fmaf(l2, wv.z, acc.z * inv_b), __builtin_fmaf(l2, wv.w, acc.w * inv_b));
+  if (active) store4_within(g + (uint64_t)m * d, 4 * q, d, o);
+  if (!STEP) return;
+
+  float4 r1 = make_float4(0.f, 0.f, 0.f, 0.f), r2 = make_float4(1.f, 1.f, 1.f, 1.f);
+  if (NORM == kNormSub || NORM == kNormComb) r1 = load4_within(gref, 4 * q, d, 0.f);
+  if (NORM == kNormQuot) {
+    r1 = load4_within(gref, 4 * q, d, 1.f);
+    r1 = make_float4(clamp_ref(r1.x, eps), clamp_ref(r1.y, eps), clamp_ref(r1.z, eps), clamp_ref(r1.w, eps));
+  }
+  if (NORM == kNormComb) {
+    r2 = load4_within(gref2, 4 * q, d, 1.f);
+    r2 = make_float4(clamp_ref(r2.x, eps), clamp_ref(r2.y, eps), clamp_ref(r2.z, eps), clamp_ref(r2.w, eps));
+  }
+  const float4 v = make_float4(normalize<NORM>(o.x, r1.x, r2.x), normalize<NORM>(o.y, r1.y, r2.y),
+                               normalize<NORM>(o.z, r1.z, r2.z), normalize<NORM>(o.w, r1.w, r2.w));
+  // (past the end the gradient is 0 and its references such that it normalises to 0)
+  const float amax = active ? fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))) : 0.f;
+  __syncthreads();
+  const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane((int)m);
+  if ((uint32_t)__builtin_amdgcn_readlane((int)m, kWave - 1) == first) {  // one worker's wavefront
+    const float wmax = wave_max_nonneg(amax);
+    if (t % kWave == 0) atomicMax(&top[first], __float_as_uint(wmax));
+  } else {
+    atomicMax(&top[m], __float_as_uint(amax));
+  }
+  __syncthreads();
+  const float R = __uint_as_float(top[m]) < 0x1p-126f ? 0.f : __uint_as_float(top[m]);
+  if (active && q == 0) scales[m] = R;
+  float4 val = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (active && R != 0.f) {
+    constexpr float LEVELS = (float)((1 << (BITS - 1)) - 1);
+    const float inv_r = 1.0f / R, step = R / LEVELS;
+    const U32x4 rnd = philox4x32_10(q, m, iter, 0u, k0, k1);
+    const uint32_t c0 = quantize_and_value<BITS>(v.x, inv_r, rnd.x, R, step, val.x);
+    const uint32_t c1 = quantize_and_value<BITS>(v.y, inv_r, rnd.y, R, step, val.y);
+    const uint32_t c2 = quantize_and_value<BITS>(v.z, inv_r, rnd.z, R, step, val.z);
+    const uint32_t c3 = quantize_and_value<BITS>(v.w, inv_r, rnd.w, R, step, val.w);
+    const uint32_t frag = c0 | (c1 << BITS) | (c2 << (2 * BITS)) | (c3 << (3 * BITS));
+    if (BITS == 2)
+      reinterpret_cast<lds_byte*>(packed + m * words)[q] = (uint8_t)frag;
+    else
+      reinterpret_cast<lds_half*>(packed + m * words)[q] = (uint16_t)frag;
+  }
+  value[t] = val;
+  __syncthreads();
+  if (t < M * words) store_word_through(codes + t, packed[t]);
+  if (t < nvec) {  // the server: m = 0 here, so q, the references and w are those of the thread's float4
+    float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (uint32_t k = 0; k < M; ++k) {
+      const float4 p = value[k * nvec + t];
+      sum.x = sum.x + p.x;
+      sum.y = sum.y + p.y;
+      sum.z = sum.z + p.z;
+      sum.w = sum.w + p.w;
+    }
+    const float4 u = make_float4(denormalize<NORM>(sum.x * inv_m, r1.x, r2.x), denormalize<NORM>(sum.y * inv_m, r1.y, r2.y),
+                                 denormalize<NORM>(sum.z * inv_m, r1.z, r2.z), denormalize<NORM>(sum.w * inv_m, r1.w, r2.w));
+    const float px = lr * u.x, py = lr * u.y, pz = lr * u.z, pw = lr * u.w;
+    store4_within(vbar, 4 * t, d, u);
+    store4_within(w, 4 * t, d, make_float4(wv.x - px, wv.y - py, wv.z - pz, wv.w - pw));
+    if (refout != nullptr) store4_within(refout, 4 * t, d, u);
+  }
+}
+
 // One pass over the minibatch rows for wide dense problems (4096 <= d / 4 <= 16384 float4 columns): a
 // workgroup takes whole rows, one at a time, and KEEPS the row on chip between the two uses it has -- the
 // dot product z = x . w, and, once sigma(z) - y is known, the accumulation r x into the workgroup's
@@ -1724,11 +1890,67 @@ uint32_t dense_row_splits(uint64_t d, uint32_t M, uint32_t batch) {
   return S < batch ? S : batch;
 }
 
+uint32_t dense_small_splits(uint64_t d, uint32_t M, uint32_t batch) {
+  if (d < 4 || d > 4 * (uint64_t)kBlock || (d + 3) / 4 * M > kSmallThreads) return 0;
+  const uint32_t trips = (batch + kSmallRows - 1) / kSmallRows;
+  return trips < 32 ? trips : 32;
+}
+
+size_t dense_parts_floats(uint64_t d, uint32_t M, uint32_t batch) {
+  const uint32_t small = dense_small_splits(d, M, batch);
+  if (small != 0) return (size_t)small * M * ((d + 3) / 4 * 4);
+  return (size_t)dense_row_splits(d, M, batch) * M * d;
+}
+
+namespace {
+hipError_t dense_small_rows_launch(const LogregData& p, uint64_t d, uint32_t M, uint32_t batch, uint32_t k0, uint32_t k1,
+                                   uint32_t iter, uint32_t* idx, float* parts, const float* w, hipStream_t s) {
+  hipLaunchKernelGGL(logreg_dense_small_kernel, dim3(dense_small_splits(d, M, batch), M), dim3(kBlock), 0, s, p.X, p.y,
+                     p.n_rows, idx, w, reinterpret_cast<float4*>(parts), (uint32_t)d, batch, k0, k1, iter);
+  return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_dense_small_step(const LogregData& p, const CodecShape& c, uint32_t batch, float l2, uint32_t iter,
+                                   uint32_t* idx, float* parts, float* w, float* g, const float* gref, const float* gref2,
+                                   float* scales, uint32_t* codes, float* vbar, float lr, float* ref_out, hipStream_t s) {
+  const uint32_t S = dense_small_splits(c.d, c.M, batch);
+  if (S == 0 || parts == nullptr || c.norm == kNormMean || c.scale_l2 != 0) return hipErrorInvalidValue;
+  const hipError_t e = dense_small_rows_launch(p, c.d, c.M, batch, c.k0, c.k1, iter, idx, parts, w, s);
+  if (e != hipSuccess) return e;
+#define TNG_SMALL(NORM)                                                                                              \
+  do {                                                                                                               \
+    auto kernel = c.bits == 2 ? logreg_dense_small_finish_kernel<NORM, 2, true>                                      \
+                              : logreg_dense_small_finish_kernel<NORM, 4, true>;                                     \
+    hipLaunchKernelGGL(kernel, dim3(1), dim3(kSmallThreads), 0, s, reinterpret_cast<const float4*>(parts), S, w, g,  \
+                       (uint32_t)c.d, c.M, 1.0f / (float)batch, l2, gref, gref2, c.eps, scales, codes,               \
+                       (uint32_t)c.words, c.k0, c.k1, iter, vbar, ref_out, 1.0f / (float)c.M, lr);                   \
+  } while (0)
+  switch (c.norm) {
+    case kNormSub: TNG_SMALL(kNormSub); break;
+    case kNormQuot: TNG_SMALL(kNormQuot); break;
+    case kNormComb: TNG_SMALL(kNormComb); break;
+    default: TNG_SMALL(kNormNone); break;
+  }
+#undef TNG_SMALL
+  return hipGetLastError();
+}
+
 hipError_t launch_logreg_dense_grad(const LogregData& p, uint64_t d, uint32_t M, uint32_t batch, float l2,
                                     uint32_t k0, uint32_t k1, uint32_t iter, uint32_t* idx, float* resid,
                                     float* parts, const float* w, float* g, const ScaleFusion* fuse,
                                     uint32_t* fused_rows, hipStream_t s) {
   if (fused_rows != nullptr) *fused_rows = 0;
+  const uint32_t small = parts != nullptr ? dense_small_splits(d, M, batch) : 0;
+  if (small != 0) {  // the gradient that launch_dense_small_step makes, bit for bit
+    const hipError_t e = dense_small_rows_launch(p, d, M, batch, k0, k1, iter, idx, parts, w, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((logreg_dense_small_finish_kernel<kNormNone, 2, false>), dim3(1), dim3(kSmallThreads), 0, s,
+                       reinterpret_cast<const float4*>(parts), small, const_cast<float*>(w), g, (uint32_t)d, M,
+                       1.0f / (float)batch, l2, nullptr, nullptr, 0.f, nullptr, nullptr, 0u, k0, k1, iter, nullptr, nullptr,
+                       0.f, 0.f);
+    return hipGetLastError();
+  }
   const uint32_t S = parts != nullptr && aligned16(w) && aligned16(g) ? dense_row_splits(d, M, batch) : 0;
   if (S != 0) {
     const int nv = d <= 16384 ? 8 : d <= 32768 ? 16 : 32;

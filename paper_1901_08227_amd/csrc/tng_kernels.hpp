@@ -126,9 +126,16 @@ struct LogregData {
 hipError_t launch_minibatch_indices(uint32_t k0, uint32_t k1, uint32_t iter, uint32_t M, uint32_t batch,
                                     const uint64_t* n_rows, uint32_t* idx, hipStream_t s);
 // The minibatch row ids of iteration iter are drawn inside (Philox key k0, k1) and left in idx.
-// parts: device scratch of dense_row_splits(d, M, batch) * M * d floats (per-workgroup partial gradients of
-// the one-pass kernel for wide rows), or nullptr; dense_row_splits returns 0 where that kernel does not apply.
+// parts: device scratch of dense_parts_floats(d, M, batch) floats (per-workgroup partial gradients of the one-pass
+// kernels for wide rows and for tiny problems), or nullptr; the splits are 0 where those kernels do not apply.
 uint32_t dense_row_splits(uint64_t d, uint32_t M, uint32_t batch);
+uint32_t dense_small_splits(uint64_t d, uint32_t M, uint32_t batch);
+size_t dense_parts_floats(uint64_t d, uint32_t M, uint32_t batch);
+// A whole iteration of a tiny dense problem (dense_small_splits != 0, largest-magnitude scale, no per-worker mean) in two
+// launches: the gradient of launch_logreg_dense_grad, then scales, codes, average and updates.
+hipError_t launch_dense_small_step(const LogregData& p, const CodecShape& c, uint32_t batch, float l2, uint32_t iter,
+                                   uint32_t* idx, float* parts, float* w, float* g, const float* gref, const float* gref2,
+                                   float* scales, uint32_t* codes, float* vbar, float lr, float* ref_out, hipStream_t s);
 hipError_t launch_logreg_dense_grad(const LogregData& p, uint64_t d, uint32_t M, uint32_t batch, float l2,
                                     uint32_t k0, uint32_t k1, uint32_t iter, uint32_t* idx, float* resid,
                                     float* parts, const float* w, float* g, const ScaleFusion* fuse,
