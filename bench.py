@@ -104,8 +104,8 @@ def time_codec(torch, B, g, gref, bits, norm, steps, warmup, seed, scale=0):
     # elements that can code non-zero and the quantise pass codes those, so g is read once; what the quantise
     # pass must move is then the packed codes (the candidate words, a few percent of the elements, are the
     # method's own overhead and are not counted as algorithmic bytes)
-    single_read = (bits == 2 and scale == B.SCALE_MAX and norm in (B.NORM_NONE, B.NORM_SUB)
-                   and d % 1024 == 0 and M * d >= 1 << 26 and d // 1024 >= 512)
+    single_read = (bits == 2 and (scale == B.SCALE_MAX or M >= 4) and norm in (B.NORM_NONE, B.NORM_SUB)
+                   and M * d >= 1 << 26 and d // 1024 >= 512)
     if single_read:
         b_quant = 4 * M * words
     return {
