@@ -19,7 +19,8 @@ namespace tng {
 namespace {
 
 constexpr int kWavesPerBlock = kBlock / kWave;
-constexpr uint32_t kFusedScaleRows = 256;  // at most this many rows of partial maxima are reduced by the quantiser itself
+constexpr uint32_t kFusedScaleRows = 256;  // at most this many rows of partial maxima are reduced by the quantiser itself,
+constexpr uint64_t kFusedScaleReads = 1u << 18;  // and as many as keep it to this many reads of memory lines in all
 constexpr int kLoadsPerLane = 4;  // float4 loads per lane and worker in the quantiser tile
 constexpr uint64_t kWaveTileElements = (uint64_t)kWave * kLoadsPerLane * 4;  // coordinates per wavefront tile
 constexpr uint32_t kMaxGridX = 1u << 20;
@@ -2191,6 +2192,15 @@ inline int quantize_workers_per_block(const CodecShape& c) {
   return pick_workers_per_block(c.M, (c.d + kTile - 1) / kTile, 0.0, 16);
 }
 
+// Rows of partial maxima that the quantiser reduces by itself: every wavefront reads one line per row, so a launch of many
+// wavefronts pays more for them than a launch of its own costs (4 us): encode + decode at d = 25000, M = 4 18.2 -> 14.9 us,
+// d = 2^18, M = 8 (131072 reads) 18.1 -> 14.6, but d = 4e5, M = 40 (1.5 million) 40.7 -> 46.8.
+inline uint32_t fused_scale_rows(const CodecShape& c) {
+  if (quantize_workers_per_block(c) != 1) return 0;
+  const uint64_t wavefronts = (c.d / kWaveTileElements + 1) * c.M, rows = kFusedScaleReads / wavefronts;
+  return rows < kFusedScaleRows ? (uint32_t)rows : kFusedScaleRows;
+}
+
 // fused_rows > 0: scales is an output and the scale is taken from the first fused_rows rows of
 // partials (see FusedScale); only problems small enough for one worker per workgroup go that way,
 // larger ones get the reduction kernel first.
@@ -2200,7 +2210,7 @@ hipError_t quantize_dispatch(const CodecShape& c, uint32_t iter, const float* g,
                              uint32_t fused_rows, hipStream_t s, const uint32_t* skip_if_set) {
   const int mc = quantize_workers_per_block(c);
   FusedScale fs{partials, fused_rows, scales};
-  if (fused_rows > kFusedScaleRows || (fused_rows > 0 && mc != 1)) {
+  if (fused_rows > fused_scale_rows(c)) {
     hipLaunchKernelGGL(absmax_finish_kernel, dim3(c.M), dim3(kBlock), 0, s, partials, fused_rows, c.M, scales);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -2494,7 +2504,7 @@ hipError_t launch_quantize_pack(const CodecShape& c, uint32_t iter, const float*
 #undef TNG_Q
 }
 
-uint32_t quantize_fused_rows(const CodecShape& c) { return quantize_workers_per_block(c) == 1 ? kFusedScaleRows : 0; }
+uint32_t quantize_fused_rows(const CodecShape& c) { return fused_scale_rows(c); }
 
 namespace {
 // A workgroup per 256 coordinates with the workers dealt to its wavefronts, or a thread per float4 that walks the
