@@ -368,6 +368,7 @@ __global__ __launch_bounds__(kBlock) void absmax_vec_kernel(GradRows g, const fl
       absmax_rows<NORM, MC>(g, rt, iv, m0, M, means, mx);
     }
   } else {
+    if ((blockIdx.x - main_blocks) * kWavesPerBlock >= (uint32_t)MC) return;  // idle (workgroups_per_group)
     const uint32_t at = (blockIdx.x - main_blocks) * kWavesPerBlock + (uint32_t)wave, m = min(m0 + at, M - 1);
     const float v = absmax_ragged_tile<NORM>(g, ref4, ref24, m, d, eps, NORM == kNormMean ? means[m] : 0.f);
 #pragma unroll
@@ -2017,6 +2018,19 @@ inline uint32_t tail_workgroups(uint64_t d, int mc) {
   return d % kWaveTileElements == 0 ? 0u : (uint32_t)((mc + kWavesPerBlock - 1) / kWavesPerBlock);
 }
 
+// Workgroups per group of workers where the ragged tile has some of its own.  Workgroups go to the eight compute dies in
+// turn, so their number decides how many of the dies' L2s a tile's reference passes through as the groups follow one
+// another: all of them if it is odd (encode + decode at 40 workers, 4-bit: d = 98 * 4096 40.0 us, 97 * 4096 42.4, 99 * 4096
+// 43.1).  The ragged tile's made it odd or even as it came; idle ones behind them make it a multiple of 4: two dies per
+// tile.  d = 400000, M = 40, 4-bit: as it came 44.3 us, a multiple of 2 40.1, of 4 40.1, of 8 40.7; d = 10^6 + 3, M = 16,
+// quotient: 49.7 / 46.4 / 42.5 / 42.7; d = 100003, M = 33 (26 workgroups): 17.1 / 17.1 / 17.1 / 21.2, where one die in eight
+// gets a third more than the others.
+constexpr uint32_t kGroupMultiple = 4;
+inline uint32_t workgroups_per_group(uint32_t main_blocks, uint32_t tail, uint32_t groups) {
+  const uint32_t n = main_blocks + tail;
+  return tail == 0 || groups == 1 ? n : (n + kGroupMultiple - 1) / kGroupMultiple * kGroupMultiple;
+}
+
 template <int NORM, int MC>
 hipError_t absmax_vec_launch(const CodecShape& c, const float* g, const float* gref, const float* gref2,
                              float* partials, uint32_t* nblocks, hipStream_t s) {
@@ -2024,7 +2038,8 @@ hipError_t absmax_vec_launch(const CodecShape& c, const float* g, const float* g
   const uint64_t per_y = (c.d / kWaveTileElements + kWavesPerBlock - 1) / kWavesPerBlock;
   const uint32_t main_blocks = (uint32_t)(per_y < kAbsmaxMaxBlocks - tail ? per_y : kAbsmaxMaxBlocks - tail);
   *nblocks = main_blocks + tail;
-  dim3 grid(*nblocks, (c.M + MC - 1) / MC);
+  const uint32_t groups = (c.M + MC - 1) / MC;
+  const dim3 grid(workgroups_per_group(main_blocks, tail, groups), groups);
   hipLaunchKernelGGL((absmax_vec_kernel<NORM, MC>), grid, dim3(kBlock), 0, s, GradRows{g, c.d}, reinterpret_cast<const float4*>(gref),
                      reinterpret_cast<const float4*>(gref2), partials, c.d, main_blocks, c.M, c.eps, c.means);
   return hipGetLastError();
@@ -2180,7 +2195,8 @@ hipError_t quantize_vec_launch(const CodecShape& c, uint32_t iter, const float* 
   const uint32_t tail = tail_workgroups(c.d, MC);
   uint32_t main_blocks = (uint32_t)((c.d / kWaveTileElements + kWavesPerBlock - 1) / kWavesPerBlock);
   if (LOOP && main_blocks > kLoopBlocks) main_blocks = kLoopBlocks;
-  dim3 grid(main_blocks + tail, (c.M + MC - 1) / MC);
+  const uint32_t groups = (c.M + MC - 1) / MC;
+  const dim3 grid(workgroups_per_group(main_blocks, tail, groups), groups);
   hipLaunchKernelGGL((quantize_pack_vec_kernel<NORM, BITS, MC, FUSED, LOOP>), grid, dim3(kBlock), 0, s, GradRows{g, c.d}, reinterpret_cast<const float4*>(gref),
                      reinterpret_cast<const float4*>(gref2), scales, codes, c.d, c.words, main_blocks, c.M, c.eps, c.k0,
                      c.k1, iter, c.means, fs, skip_if_set);
