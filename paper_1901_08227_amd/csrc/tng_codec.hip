@@ -597,10 +597,12 @@ __device__ __forceinline__ void quantize_ragged_tile(FragmentBuffer<WPW, SLOTS>&
 // LOOP: the kernel behind the candidate coder, which returns at once when the codes come from the slots
 // (skip_if_set) but for the ragged last tile, which has none: at most kLoopBlocks workgroups per group of workers, each walking its share of the tiles (returning
 // from 32768 workgroups took 9 us at d = 2^27).
-// (128 registers, four wavefronts per SIMD, but for the combined form, whose two references do not fit that)
+// 128 registers, four wavefronts per SIMD, but for the combined form, whose two references do not fit that, and the
+// quotient form in groups of 4, which takes 130: a spilled register is reloaded in the pipelined loop, where the reload
+// waits for every load in flight.
 constexpr uint32_t kLoopBlocks = 4096;
 template <int NORM, int BITS, int MC, bool FUSED, bool LOOP>
-__global__ __launch_bounds__(kBlock, NORM == kNormComb ? 3 : 4) void quantize_pack_vec_kernel(
+__global__ __launch_bounds__(kBlock, NORM == kNormComb || (NORM == kNormQuot && MC == 4) ? 3 : 4) void quantize_pack_vec_kernel(
     GradRows g, const float4* __restrict__ ref4, const float4* __restrict__ ref24,
     const float* __restrict__ scales, uint32_t* __restrict__ codes, uint64_t d, uint64_t words, uint32_t main_blocks,
     uint32_t M, float eps, uint32_t k0, uint32_t k1, uint32_t iter, const float* __restrict__ means,
@@ -609,7 +611,11 @@ __global__ __launch_bounds__(kBlock, NORM == kNormComb ? 3 : 4) void quantize_pa
   constexpr int WPW = kWave * L * 4 * BITS / 32;  // packed words per wavefront tile
   __shared__ __attribute__((aligned(16))) FragmentBuffer<WPW, MC> lds;
   if (LOOP && blockIdx.x < main_blocks && skip_if_set[0] != 0u) return;
-  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  // The quotient and combined forms lack registers: there the wavefront's number is a value the compiler knows to be the
+  // same in every lane, which makes row addresses scalar (encode + decode at d = 2^27, M = 8, quotient: 4-bit 1852 us with 2
+  // spilled registers, 1837 this way; 2-bit 1746 / 1729).
+  const int wave = kByReciprocal<NORM, MC> ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)) : (int)(threadIdx.x / kWave);
+  const int lane = threadIdx.x % kWave;
   const uint64_t ntiles = d / kWaveTileElements;  // whole wavefront tiles
   const uint32_t m0 = blockIdx.y * MC;
   const uint32_t m_end = min(m0 + MC, M);
