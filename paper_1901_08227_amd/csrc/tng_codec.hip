@@ -1989,17 +1989,21 @@ inline uint32_t div_up_u32(uint64_t a, uint64_t b) {
   return (uint32_t)(q > kMaxGridX ? kMaxGridX : q);
 }
 
-// Workers handled inside one workgroup (8, 4, 2 or 1; the last group of a row of workgroups may be
+// Workers handled inside one workgroup (16, 8, 4, 2 or 1; the last group of a row of workgroups may be
 // short).  A group reads the shared reference once, so fewer groups mean less traffic; a short group
 // costs the scale pass repeated loads of its last row (cache hits: repeat_cost 0.3 of a row there,
 // nothing in the quantiser, which stops at the last worker).  At least 2048 workgroups are kept to
-// fill 256 compute units.
-inline int pick_workers_per_block(uint32_t M, uint64_t tiles, double repeat_cost, int mc_max = 8) {
+// fill 256 compute units.  fives: groups of 5 as well, for absmax_select_kernel, where the reference and five rows are two
+// rounds of its three buffers; chosen for 5, 9, 10, 17 to 20 and 25 workers of long rows (encode + decode at d = 2^25: M = 5 293 us
+// in a group of 8, 250 in one of 5; M = 9 450 in groups of 4, 414 in groups of 5; M = 10 476 / 433; d = 2^24: M = 20
+// 425 / 411, M = 25 534 in groups of 8, 515).
+inline int pick_workers_per_block(uint32_t M, uint64_t tiles, double repeat_cost, int mc_max = 8, bool fives = false) {
   int best = 1;
   double best_cost = (double)M;
-  for (int mc = 2; mc <= mc_max; mc *= 2) {
+  for (const int mc : {2, 4, 5, 8, 16}) {
     const uint32_t groups = (M + mc - 1) / mc;
-    if (tiles * groups < 2048 || (mc > 8 && M <= 8)) break;
+    if (mc == 5 && !fives) continue;
+    if (mc > mc_max || tiles * groups < 2048 || (mc > 8 && M <= 8)) break;
     const double cost = groups + repeat_cost * (groups * mc - M);
     if (cost <= best_cost) {
       best = mc;
@@ -2106,11 +2110,7 @@ hipError_t absmax_candidates_dispatch(const CodecShape& c, uint32_t iter, const 
                                       const float* gref2, float* partials, const CandidateScratch& cs, float* scales,
                                       hipStream_t s) {
   const uint64_t nvec = c.d / 4;
-  // Fives where the workers come out even that way: the reference and five rows are two rounds of the three buffers, and
-  // the group of 5 or 9 workers fetches no row twice.
-  int mc = pick_workers_per_block(c.M, (nvec + kBlock * kAbsmaxLoads - 1) / (kBlock * kAbsmaxLoads), 0.3);
-  const uint32_t groups = (c.M + 7) / 8;
-  if (mc == 8 && (c.M + groups - 1) / groups <= 5) mc = 5;
+  const int mc = pick_workers_per_block(c.M, (nvec + kBlock * kAbsmaxLoads - 1) / (kBlock * kAbsmaxLoads), 0.3, 8, true);
   uint32_t nblocks = 0;
   hipError_t e;
   e = sample_launch<NORM, false>(c, g, gref, cs, s);

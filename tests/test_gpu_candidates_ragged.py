@@ -66,3 +66,9 @@ def test_l2_scale_outside_the_sample():
     v = torch.randn((M, d), device=DEV, generator=torch.Generator(device=DEV).manual_seed(1))
     v.view(M, -1, 1024)[:, ::128] = 0.0
     check(M, d, B.NORM_NONE, v, v[0].clone(), 2, B.SCALE_L2)
+
+
+@pytest.mark.parametrize("M,d,norm", [(10, 1 << 23, B.NORM_SUB), (9, 1 << 23, B.NORM_SUB), (20, (1 << 22) + 1029, B.NORM_NONE)])
+def test_groups_of_five_workers(M, d, norm):
+    g, gref, _ = _inputs(M, d, seed=M)
+    check(M, d, norm, g, gref, 4)
