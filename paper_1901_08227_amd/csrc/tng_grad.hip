@@ -1586,14 +1586,17 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_workers_kernel(const int
 // ------------------------------------------------------------------------------------------
 // CSR logistic regression with few columns: two launches.
 //
-// With w small enough for every L2 the dot products need no column tiles: a wavefront takes a minibatch row,
-// gathers w, and leaves what the gradient pass needs of the row (residual over B, start, tile bounds) -- one
+// With w small enough for every L2 the dot products need no column tiles: a wavefront (or sixteen, of few rows) takes a
+// minibatch row, gathers w, and leaves what the gradient pass needs of the row (residual over B, start, tile bounds) -- one
 // launch in place of four (row ids, bounds, dot products, their sum).  The gradient pass then has as many
 // workgroups as fill the chip: each owns 2^sub_shift columns of a tile in LDS and reads the tile's whole row
 // segments (out of the L2: 2^(tile_shift - sub_shift) workgroups read the same ones), adding those that are its own.
 // ------------------------------------------------------------------------------------------
-template <bool PAIRS, bool INDEX>
-__global__ __launch_bounds__(kBlock) void csr_rows_kernel(const int64_t* const* __restrict__ rowptrs,
+// WAVES: wavefronts per row.  A lane adds at most kCsrChain products in a row, as many as in a tile of the other
+// dot-product passes: a row of 2^20 entries would be chains of 2^14 otherwise.
+constexpr uint32_t kCsrChain = 512;
+template <bool PAIRS, bool INDEX, int WAVES>
+__global__ __launch_bounds__(WAVES == 1 ? kBlock : WAVES * kWave) void csr_rows_kernel(const int64_t* const* __restrict__ rowptrs,
                                                           const int32_t* const* __restrict__ cols,
                                                           const float* const* __restrict__ vals,
                                                           const float* const* __restrict__ ys,
@@ -1604,9 +1607,12 @@ __global__ __launch_bounds__(kBlock) void csr_rows_kernel(const int64_t* const* 
                                                           float* __restrict__ resid, uint32_t batch, uint32_t ntiles,
                                                           uint32_t tile_shift, float inv_b, uint32_t k0, uint32_t k1,
                                                           uint32_t iter) {
-  const uint32_t m = blockIdx.y, lane = threadIdx.x % kWave;
-  const uint32_t i = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * kWavesPerBlock + threadIdx.x / kWave));
-  if (i >= batch) return;  // whole wavefronts; no workgroup barrier below
+  constexpr uint32_t kLanes = WAVES * kWave;  // lanes per row
+  __shared__ float red[WAVES];
+  const uint32_t m = blockIdx.y, lane = threadIdx.x % kLanes;
+  const uint32_t i = WAVES == 1 ? (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * kWavesPerBlock + threadIdx.x / kWave))
+                                : blockIdx.x;
+  if (i >= batch) return;  // whole wavefronts, which meet no workgroup barrier (with several per row i < batch)
   const uint32_t row = (uint32_t)__builtin_amdgcn_readfirstlane((int)minibatch_row(k0, k1, iter, m, i, n_rows[m]));
   const int64_t a = as_global(rowptrs[m])[row];
   const uint32_t nnz = (uint32_t)(as_global(rowptrs[m])[row + 1] - a);
@@ -1615,25 +1621,37 @@ __global__ __launch_bounds__(kBlock) void csr_rows_kernel(const int64_t* const* 
   uint32_t* __restrict__ out = bounds + (uint64_t)m * (ntiles + 1) * batch + i;
   if (INDEX) {
     const GlobalPtr<uint32_t> src = as_global(index[m]) + (uint64_t)row * (ntiles + 1);
-    for (uint32_t t = lane; t <= ntiles; t += kWave) out[(uint64_t)t * batch] = src[t];
+    for (uint32_t t = lane; t <= ntiles; t += kLanes) out[(uint64_t)t * batch] = src[t];
   }
   float acc = 0.f;
+  for (uint64_t first = 0; first < nnz; first += kCsrChain * kLanes) {
+    const uint32_t end = (uint32_t)min((uint64_t)nnz, first + kCsrChain * kLanes);
+    float part = 0.f;
 #pragma unroll 4
-  for (uint32_t k = lane; k < nnz; k += kWave) {
-    int32_t c;
-    float v;
-    e.load(a + k, c, v);
-    acc = __builtin_fmaf(v, w[c], acc);
-    if (!INDEX) {  // entry k opens every tile after the tile of entry k - 1 up to its own
-      const uint32_t prev = k == 0 ? 0u : ((uint32_t)e.col(a + k - 1) >> tile_shift) + 1u;
-      for (uint32_t t = prev; t <= ((uint32_t)c >> tile_shift); ++t) out[(uint64_t)t * batch] = k;
+    for (uint32_t k = (uint32_t)first + lane; k < end; k += kLanes) {
+      int32_t c;
+      float v;
+      e.load(a + k, c, v);
+      part = __builtin_fmaf(v, w[c], part);
+      if (!INDEX) {  // entry k opens every tile after the tile of entry k - 1 up to its own
+        const uint32_t prev = k == 0 ? 0u : ((uint32_t)e.col(a + k - 1) >> tile_shift) + 1u;
+        for (uint32_t t = prev; t <= ((uint32_t)c >> tile_shift); ++t) out[(uint64_t)t * batch] = k;
+      }
     }
+    acc += part;
   }
   if (!INDEX) {  // and the end of the row every tile after its last entry's
     const uint32_t prev = nnz == 0 ? 0u : ((uint32_t)e.col(a + nnz - 1) >> tile_shift) + 1u;
-    for (uint32_t t = prev + lane; t <= ntiles; t += kWave) out[(uint64_t)t * batch] = nnz;
+    for (uint32_t t = prev + lane; t <= ntiles; t += kLanes) out[(uint64_t)t * batch] = nnz;
   }
-  const float z = wave_sum(acc);
+  float z = wave_sum(acc);
+  if (WAVES > 1) {
+    if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = z;
+    __syncthreads();
+    z = red[0];
+#pragma unroll
+    for (int k = 1; k < WAVES; ++k) z += red[k];
+  }
   if (lane == 0) {
     const uint64_t o = (uint64_t)m * batch + i;
     idx[o] = row;
@@ -2108,7 +2126,9 @@ constexpr uint32_t kCsrRun = 16;
 // The two launches for few columns (see csr_rows_kernel), up to 2^21 columns of all workers.  Beyond, w no longer
 // comes cheaply out of the L2 and the repeated segments cost more than the launches.  Iterations at 0.1 % density, the
 // column tiles against these: d = 2^14, M = 8, B = 128 39 -> 14.6 us; d = 2^16, M = 8, B = 512 46 -> 18.5, M = 33
-// 58 -> 49, M = 64 65 -> 71; d = 2^18, M = 8 55 -> 37, M = 64 110 -> 202; d = 2^19, M = 16 66 -> 113.
+// 58 -> 49, M = 64 65 -> 71; d = 2^18, M = 8 55 -> 37, M = 64 110 -> 202; d = 2^19, M = 16 66 -> 113.  Denser rows are
+// further ahead, though a segment is read by several workgroups (the column tiles have too few): d = 2^14, M = 8, 10 %
+// 790 -> 276; d = 2^16, M = 8, 1 / 10 / 25 % 154 -> 58 / 1503 -> 410 / 3957 -> 1038; d = 2^18, M = 8, 10 % 1600 -> 1025.
 bool csr_few_columns(uint64_t d, uint32_t M) { return d * M <= (1ull << 21); }
 
 template <bool PAIRS>
@@ -2118,9 +2138,17 @@ hipError_t csr_few_columns_launches(const LogregData& p, uint64_t d, uint32_t M,
                                     hipStream_t s) {
   const uint32_t shift = csr_tile_shift(d), ntiles = csr_tiles(d);
   const float inv_b = 1.0f / (float)batch;
-  const dim3 rows((batch + kWavesPerBlock - 1) / kWavesPerBlock, M);
-  auto kernel = p.tile_index != nullptr ? csr_rows_kernel<PAIRS, true> : csr_rows_kernel<PAIRS, false>;
-  hipLaunchKernelGGL(kernel, rows, dim3(kBlock), 0, s, p.rowptr, p.col, p.val, p.y, p.n_rows, p.tile_index, w, idx,
+  // Few rows: sixteen wavefronts take one, or the walk of a single wavefront over a long row sets the time (d = 2^21, M = 1,
+  // 209715 entries a row: B = 1 776 -> 230 us, column tiles 369; B = 16 1143 -> 630; d = 2^18, M = 8, 26214 entries, B = 1
+  // 132 -> 71, column tiles 98).  Short rows lose nothing by it up to 512 of them (d = 2^18, M = 8, B = 64, 262 entries 30.2
+  // -> 29.6), many do: d = 2^16, M = 8, B = 512, 66 entries 18.5 -> 32.2; nor are there long rows of few columns: d = 2^14,
+  // M = 8, B = 64, 16 entries 14.5 -> 15.1.
+  constexpr int kFewRowsWaves = kCsrThreads / kWave;
+  const bool few_rows = (uint64_t)batch * M <= 512 && d >= (1u << 16);
+  const dim3 rows(few_rows ? batch : (batch + kWavesPerBlock - 1) / kWavesPerBlock, M);
+  auto kernel = p.tile_index != nullptr ? (few_rows ? csr_rows_kernel<PAIRS, true, kFewRowsWaves> : csr_rows_kernel<PAIRS, true, 1>)
+                                        : (few_rows ? csr_rows_kernel<PAIRS, false, kFewRowsWaves> : csr_rows_kernel<PAIRS, false, 1>);
+  hipLaunchKernelGGL(kernel, rows, dim3(few_rows ? kCsrThreads : kBlock), 0, s, p.rowptr, p.col, p.val, p.y, p.n_rows, p.tile_index, w, idx,
                      rowbase, bounds, z, batch, ntiles, shift, inv_b, k0, k1, iter);
   // columns per workgroup: 2^12, halved until there is one workgroup per compute unit (twice as many: 24 against 18.5 us
   // at d = 2^16, M = 8)

@@ -20,7 +20,10 @@ pytestmark = pytest.mark.gpu
     # one column more than the rule takes, and the pipelines over tiles (M = 1, two references) and workers
     ((1 << 18) + 1, 8, 40, B.NORM_SUB, 1e-3, False, True), (130 << 14, 1, 40, B.NORM_SUB, 0.0, True, True),
     (22 << 14, 7, 130, B.NORM_COMB, 0.0, True, False), (22 << 14, 7, 130, B.NORM_QUOT, 0.0, False, True),
-    (22 << 14, 7, 600, B.NORM_NONE, 0.0, True, True), (200, 10500, 2, B.NORM_SUB, 0.0, False, True)])
+    (22 << 14, 7, 600, B.NORM_NONE, 0.0, True, True), (200, 10500, 2, B.NORM_SUB, 0.0, False, True),
+    # 512 minibatch rows in all (sixteen wavefronts each), and more rows or fewer columns than that takes
+    (1 << 16, 8, 64, B.NORM_SUB, 0.0, True, True), (70001, 8, 64, B.NORM_SUB, 0.0, False, False),
+    (70001, 9, 57, B.NORM_SUB, 0.0, False, True), (65535, 8, 64, B.NORM_SUB, 0.0, True, False)])
 def test_gradient_and_step(d, M, batch, norm, l2, index, pairs):
     n, seed = 30 if M < 100 else 2, 31
     longest = min(d, 3000)
@@ -55,3 +58,25 @@ def test_gradient_and_step(d, M, batch, norm, l2, index, pairs):
     for name, a, b in zip(("iterate", "reference", "codes", "scales", "average"), got, want):
         assert np.array_equal(a, b), name
     ctx.close()
+
+
+@pytest.mark.parametrize("M,batch", [(2, 3), (4, 160)])  # sixteen wavefronts per row, one
+def test_chains_of_long_rows(M, batch):
+    """One row per worker, every column stored, all products the same: the roundings of a running sum then all go one
+    way.  The chains are of 512 additions, whatever the length of the row (512 and 2^19 / 2^15 roundings of at most 2^-24
+    of the sum, 32 for the sums over lanes and wavefronts and the products; sigma changes by a quarter of that; 8
+    roundings from the residual to the gradient)."""
+    d, c = 1 << 19, np.float32(1.313 / (1 << 19))
+    row = (torch.tensor([0, d], dtype=torch.int64, device=DEV), torch.arange(d, dtype=torch.int32, device=DEV),
+           torch.ones(d, device=DEV), torch.ones(1, device=DEV))
+    ctx = make_ctx(d, M, 2, B.NORM_SUB, seed=1, batch=batch, problem=B.PROB_LOGREG_CSR)
+    set_csr(ctx, [row] * M, True)
+    g = torch.empty((M, d), device=DEV)
+    ctx.local_grad(0, torch.full((d,), float(c), device=DEV), g)
+    torch.cuda.synchronize()
+    ctx.close()
+    z = float(c) * d
+    want = 1.0 / (1.0 + np.exp(-z)) - 1.0
+    bound = (0.25 * z * (512 + d / 2 ** 15 + 32) + 8 * abs(want)) * 2.0 ** -24
+    worst = np.abs(g.cpu().numpy().astype(np.float64) - want).max()
+    assert worst <= bound, f"{worst} > {bound}"
