@@ -369,8 +369,11 @@ __global__ __launch_bounds__(kBlock) void absmax_vec_kernel(GradRows g, const fl
     }
   } else {
     if ((blockIdx.x - main_blocks) * kWavesPerBlock >= (uint32_t)MC) return;  // idle (workgroups_per_group)
-    const uint32_t at = (blockIdx.x - main_blocks) * kWavesPerBlock + (uint32_t)wave, m = min(m0 + at, M - 1);
-    const float v = absmax_ragged_tile<NORM>(g, ref4, ref24, m, d, eps, NORM == kNormMean ? means[m] : 0.f);
+    const uint32_t at = (blockIdx.x - main_blocks) * kWavesPerBlock + (uint32_t)wave, m = m0 + at;
+    // (wavefronts beyond the group's workers have nothing to fetch: other workers' tiles in them were 4.6 of the pass's 11.2
+    // us at d = 9000, M = 800)
+    const bool mine = at < (uint32_t)MC && m < M;
+    const float v = mine ? absmax_ragged_tile<NORM>(g, ref4, ref24, m, d, eps, NORM == kNormMean ? means[m] : 0.f) : 0.f;
 #pragma unroll
     for (int mm = 0; mm < MC; ++mm) mx[mm] = (uint32_t)mm == at ? v : 0.f;
   }
