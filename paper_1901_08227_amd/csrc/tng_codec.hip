@@ -2037,11 +2037,13 @@ inline uint32_t tail_workgroups(uint64_t d, int mc) {
 // 43.1).  The ragged tile's made it odd or even as it came; idle ones behind them make it a multiple of 4: two dies per
 // tile.  d = 400000, M = 40, 4-bit: as it came 44.3 us, a multiple of 2 40.1, of 4 40.1, of 8 40.7; d = 10^6 + 3, M = 16,
 // quotient: 49.7 / 46.4 / 42.5 / 42.7; d = 100003, M = 33 (26 workgroups): 17.1 / 17.1 / 17.1 / 21.2, where one die in eight
-// gets a third more than the others.
+// gets a third more than the others.  Below 64 the reference is too short to
+// matter and the idle ones cost (d = 80000, M = 200 (21 workgroups) 61.5 us, 63.2 with 24; d = 5000, M = 1000, mean 170 with
+// 2, 179 with 4).
 constexpr uint32_t kGroupMultiple = 4;
 inline uint32_t workgroups_per_group(uint32_t main_blocks, uint32_t tail, uint32_t groups) {
   const uint32_t n = main_blocks + tail;
-  return tail == 0 || groups == 1 ? n : (n + kGroupMultiple - 1) / kGroupMultiple * kGroupMultiple;
+  return tail == 0 || groups == 1 || n < 64 ? n : (n + kGroupMultiple - 1) / kGroupMultiple * kGroupMultiple;
 }
 
 template <int NORM, int MC>
