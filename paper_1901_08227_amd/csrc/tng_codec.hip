@@ -1909,35 +1909,42 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
   }
 }
 
-// One workgroup per worker: the chunk sums come to LDS kFinishGroups groups at a time, in whole lines (a thread per
-// group that fetched its 256 chunk sums one after the other took 25 us at d = 2^24; 8 this way), a thread adds a group in
+// One workgroup per worker: the chunk sums come to LDS GROUPS groups at a time, in whole lines (a thread per
+// group that fetched its 256 chunk sums one after the other took 26 us at d = 2^24 and 39 at d = 2^27, 5 and 19 this way; 16
+// groups at a time with loads under a branch, each waited for before the next, 8 and 56), a thread adds a group in
 // order, and thread 0 the groups in order.  MEAN: out[m] = float(total / d), and, when chunk_minmax is
 // given, scales[m] = max |g - out[m]| from the smallest and the largest element.  Otherwise
 // out[m] = float(sqrt(total)), 0 when below FLT_MIN.  Division and square root of binary64 are
 // correctly rounded on the device, so the float32 result is the same as on any IEEE host.
-constexpr int kFinishGroups = 16;
-template <bool MEAN>
+// GROUPS: 64, a lane of the first wavefront each (131 KB of LDS), or 16 or 1 where a row has no more (d = 5000, 1000 workers,
+// whose workgroups then share the compute units: encode + decode 177 us; with 64 groups 4 us more).
+template <bool MEAN, int GROUPS>
 __global__ __launch_bounds__(kBlock) void tree_finish_kernel(const double* __restrict__ chunk_sums,
                                                              const float2* __restrict__ chunk_minmax,
                                                              uint64_t nchunks, uint64_t ngroups, uint64_t d,
                                                              float* __restrict__ out, float* __restrict__ scales) {
+  constexpr int kLoads = GROUPS < 16 ? GROUPS : 16;  // in flight per thread
   __shared__ float red_lo[kWavesPerBlock], red_hi[kWavesPerBlock];
-  __shared__ double part[kFinishGroups][kTreeGroup + 1];  // (one of padding: the groups' threads read different banks)
-  __shared__ double group[kFinishGroups];
+  __shared__ double part[GROUPS][kTreeGroup + 1];  // (one of padding: the groups' threads read different banks)
+  __shared__ double group[GROUPS];
   const uint32_t m = blockIdx.x;
   const double* __restrict__ cs = chunk_sums + (uint64_t)m * nchunks;
   double total = 0.0;  // thread 0
-  for (uint64_t q0 = 0; q0 < ngroups; q0 += kFinishGroups) {
+  for (uint64_t q0 = 0; q0 < ngroups; q0 += GROUPS) {
     const uint64_t c0 = q0 * kTreeGroup;
-    const uint32_t n = (uint32_t)min((uint64_t)(kFinishGroups * kTreeGroup), nchunks - c0);
+    const uint32_t n = (uint32_t)min((uint64_t)(GROUPS * kTreeGroup), nchunks - c0);
     __syncthreads();  // the batch before has been added
 #pragma unroll
-    for (int k = 0; k < kFinishGroups; ++k) {
-      const uint32_t i = (uint32_t)k * kTreeGroup + threadIdx.x;
-      part[k][threadIdx.x] = i < n ? cs[c0 + i] : 0.0;
+    for (int k0 = 0; k0 < GROUPS; k0 += kLoads) {
+      if ((uint32_t)k0 * kTreeGroup >= n) break;
+      double v[kLoads];  // (past the end the last one again, which is not added: no load under a branch)
+#pragma unroll
+      for (int k = 0; k < kLoads; ++k) v[k] = cs[c0 + min((uint32_t)(k0 + k) * kTreeGroup + threadIdx.x, n - 1)];
+#pragma unroll
+      for (int k = 0; k < kLoads; ++k) part[k0 + k][threadIdx.x] = v[k];
     }
     __syncthreads();
-    if (threadIdx.x < (uint32_t)kFinishGroups) {
+    if (threadIdx.x < (uint32_t)GROUPS) {
       const uint32_t first = threadIdx.x * kTreeGroup, count = first < n ? min((uint32_t)kTreeGroup, n - first) : 0u;
       double a = 0.0;
 #pragma unroll 16
@@ -1946,7 +1953,7 @@ __global__ __launch_bounds__(kBlock) void tree_finish_kernel(const double* __res
     }
     wave_lds_fence();  // (the groups' threads and thread 0 are one wavefront)
     if (threadIdx.x == 0)
-      for (uint32_t q = 0; q < (uint32_t)kFinishGroups && q0 + q < ngroups; ++q) total = total + group[q];
+      for (uint32_t q = 0; q < (uint32_t)GROUPS && q0 + q < ngroups; ++q) total = total + group[q];
   }
   if (MEAN && chunk_minmax != nullptr) {
     float lo = INFINITY, hi = -INFINITY;
@@ -2372,7 +2379,10 @@ hipError_t l2_last_chunk_launch(const CodecShape& c, const float* g, const float
 template <bool MEAN>
 hipError_t tree_finish_launch(const CodecShape& c, double* sums, const float2* minmax, uint64_t nchunks, uint64_t ngroups,
                               float* out, float* scales, hipStream_t s) {
-  hipLaunchKernelGGL(tree_finish_kernel<MEAN>, dim3(c.M), dim3(kBlock), 0, s, sums, minmax, nchunks, ngroups, c.d, out,
+  auto kernel = ngroups == 1   ? tree_finish_kernel<MEAN, 1>
+                : ngroups <= 16 ? tree_finish_kernel<MEAN, 16>
+                                : tree_finish_kernel<MEAN, 64>;
+  hipLaunchKernelGGL(kernel, dim3(c.M), dim3(kBlock), 0, s, sums, minmax, nchunks, ngroups, c.d, out,
                      scales);
   return hipGetLastError();
 }
