@@ -597,14 +597,14 @@ __device__ __forceinline__ void quantize_ragged_tile(FragmentBuffer<WPW, SLOTS>&
   store_packed<BITS, WPW, SLOTS, false>(lds, 0, wave, lane, frag, codes + (uint64_t)m * words, tile * WPW, words);
 }
 
-// LOOP: the kernel behind the candidate coder, which returns at once when the codes come from the slots
-// (skip_if_set) but for the ragged last tile, which has none: at most kLoopBlocks workgroups per group of workers, each walking its share of the tiles (returning
-// from 32768 workgroups took 9 us at d = 2^27).
+// skip_if_set: behind the candidate coder, all but the ragged tile's workgroups (which has no slots) return at once when
+// that word says that the codes come from the slots.  (Returning from 32768 workgroups takes 9 us at d = 2^27; 4096 that
+// walk the tiles return in 3, but where the rows are too dense for the slots they quantise slower: encode + decode at
+// d = 2^27, M = 8, Gaussian residuals 1763 us, 1822 that way.)
 // 128 registers, four wavefronts per SIMD, but for the combined form, whose two references do not fit that, and the
 // quotient form in groups of 4, which takes 130: a spilled register is reloaded in the pipelined loop, where the reload
 // waits for every load in flight.
-constexpr uint32_t kLoopBlocks = 4096;
-template <int NORM, int BITS, int MC, bool FUSED, bool LOOP>
+template <int NORM, int BITS, int MC, bool FUSED>
 __global__ __launch_bounds__(kBlock, NORM == kNormComb || (NORM == kNormQuot && MC == 4) ? 3 : 4) void quantize_pack_vec_kernel(
     GradRows g, const float4* __restrict__ ref4, const float4* __restrict__ ref24,
     const float* __restrict__ scales, uint32_t* __restrict__ codes, uint64_t d, uint64_t words, uint32_t main_blocks,
@@ -613,7 +613,7 @@ __global__ __launch_bounds__(kBlock, NORM == kNormComb || (NORM == kNormQuot && 
   constexpr int L = kLoadsPerLane;
   constexpr int WPW = kWave * L * 4 * BITS / 32;  // packed words per wavefront tile
   __shared__ __attribute__((aligned(16))) FragmentBuffer<WPW, MC> lds;
-  if (LOOP && blockIdx.x < main_blocks && skip_if_set[0] != 0u) return;
+  if (skip_if_set != nullptr && blockIdx.x < main_blocks && skip_if_set[0] != 0u) return;
   // The quotient and combined forms lack registers: there the wavefront's number is a value the compiler knows to be the
   // same in every lane, which makes row addresses scalar (encode + decode at d = 2^27, M = 8, quotient: 4-bit 1852 us with 2
   // spilled registers, 1837 this way; 2-bit 1746 / 1729).
@@ -623,23 +623,18 @@ __global__ __launch_bounds__(kBlock, NORM == kNormComb || (NORM == kNormQuot && 
   const uint32_t m0 = blockIdx.y * MC;
   const uint32_t m_end = min(m0 + MC, M);
   if (blockIdx.x < main_blocks) {
-    uint64_t wave_tile = (uint64_t)blockIdx.x * kWavesPerBlock + wave;
-    if (!LOOP && wave_tile >= ntiles) return;  // whole wavefronts of the last workgroup; nothing below meets the others
-    do {
-      if (LOOP && wave_tile >= ntiles) return;
-      QuantLane<NORM> q;
+    const uint64_t wave_tile = (uint64_t)blockIdx.x * kWavesPerBlock + wave;
+    if (wave_tile >= ntiles) return;  // whole wavefronts of the last workgroup; nothing below meets the others
+    QuantLane<NORM> q;
 #pragma unroll
-      for (int j = 0; j < L; ++j) {
-        q.iv[j] = wave_tile * (kWave * L) + (uint64_t)j * kWave + lane;
-        q.rt[j].load(ref4, ref24, q.iv[j], eps);
-        if (kByReciprocal<NORM, MC>) q.rt[j].reciprocals();
-      }
-      // (the 16-byte stores at the end of the workgroup take words at any 4-byte boundary)
-      quantize_rows<NORM, BITS, WPW, MC, FUSED, (MC > 1)>(q, lds, wave, lane, g, scales, codes, words, wave_tile * WPW, m0,
-                                                          m_end, iter, k0, k1, means, fs, M);
-      wave_tile += (uint64_t)main_blocks * kWavesPerBlock;
-      if (LOOP) wave_lds_fence();
-    } while (LOOP);
+    for (int j = 0; j < L; ++j) {
+      q.iv[j] = wave_tile * (kWave * L) + (uint64_t)j * kWave + lane;
+      q.rt[j].load(ref4, ref24, q.iv[j], eps);
+      if (kByReciprocal<NORM, MC>) q.rt[j].reciprocals();
+    }
+    // (the 16-byte stores at the end of the workgroup take words at any 4-byte boundary)
+    quantize_rows<NORM, BITS, WPW, MC, FUSED, (MC > 1)>(q, lds, wave, lane, g, scales, codes, words, wave_tile * WPW, m0,
+                                                        m_end, iter, k0, k1, means, fs, M);
   } else {
     const uint32_t m = m0 + (blockIdx.x - main_blocks) * kWavesPerBlock + (uint32_t)wave;
     if (m >= m_end) return;
@@ -2206,16 +2201,15 @@ hipError_t absmax_dispatch(const CodecShape& c, const float* g, const float* gre
   return hipGetLastError();
 }
 
-template <int NORM, int BITS, int MC, bool FUSED, bool LOOP>
+template <int NORM, int BITS, int MC, bool FUSED>
 hipError_t quantize_vec_launch(const CodecShape& c, uint32_t iter, const float* g, const float* gref,
                                const float* gref2, const float* scales, uint32_t* codes, const FusedScale& fs,
                                hipStream_t s, const uint32_t* skip_if_set = nullptr) {
   const uint32_t tail = tail_workgroups(c.d, MC);
-  uint32_t main_blocks = (uint32_t)((c.d / kWaveTileElements + kWavesPerBlock - 1) / kWavesPerBlock);
-  if (LOOP && main_blocks > kLoopBlocks) main_blocks = kLoopBlocks;
+  const uint32_t main_blocks = (uint32_t)((c.d / kWaveTileElements + kWavesPerBlock - 1) / kWavesPerBlock);
   const uint32_t groups = (c.M + MC - 1) / MC;
   const dim3 grid(workgroups_per_group(main_blocks, tail, groups), groups);
-  hipLaunchKernelGGL((quantize_pack_vec_kernel<NORM, BITS, MC, FUSED, LOOP>), grid, dim3(kBlock), 0, s, GradRows{g, c.d}, reinterpret_cast<const float4*>(gref),
+  hipLaunchKernelGGL((quantize_pack_vec_kernel<NORM, BITS, MC, FUSED>), grid, dim3(kBlock), 0, s, GradRows{g, c.d}, reinterpret_cast<const float4*>(gref),
                      reinterpret_cast<const float4*>(gref2), scales, codes, c.d, c.words, main_blocks, c.M, c.eps, c.k0,
                      c.k1, iter, c.means, fs, skip_if_set);
   return hipGetLastError();
@@ -2250,12 +2244,9 @@ hipError_t quantize_dispatch(const CodecShape& c, uint32_t iter, const float* g,
     if (e != hipSuccess) return e;
     fs.rows = 0;
   }
-  if (fs.rows > 0) return quantize_vec_launch<NORM, BITS, 1, true, false>(c, iter, g, gref, gref2, scales, codes, fs, s);
-  constexpr bool kLoop = BITS == 2 && (NORM == kNormNone || NORM == kNormSub);  // what the candidate coder takes
-#define TNG_QUANTIZE(MC)                                                                                                \
-  return kLoop && skip_if_set != nullptr                                                                                \
-             ? quantize_vec_launch<NORM, BITS, MC, false, kLoop>(c, iter, g, gref, gref2, scales, codes, fs, s, skip_if_set) \
-             : quantize_vec_launch<NORM, BITS, MC, false, false>(c, iter, g, gref, gref2, scales, codes, fs, s)
+  if (fs.rows > 0) return quantize_vec_launch<NORM, BITS, 1, true>(c, iter, g, gref, gref2, scales, codes, fs, s);
+#define TNG_QUANTIZE(MC) \
+  return quantize_vec_launch<NORM, BITS, MC, false>(c, iter, g, gref, gref2, scales, codes, fs, s, skip_if_set)
   switch (mc) {
     case 16: TNG_QUANTIZE(16);
     case 8: TNG_QUANTIZE(8);
