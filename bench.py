@@ -100,11 +100,12 @@ def time_codec(torch, B, g, gref, bits, norm, steps, warmup, seed, scale=0):
     b_quant = 4 * M * d + b_ref + 4 * M * words
     b_dec = 4 * M * words + b_ref + 4 * d
     two_pass = b_scale + b_quant + b_dec
-    # long rows of ternary codes (Eq. 1 or no normalisation, largest-magnitude scale): the scale pass keeps the
+    # long rows of ternary codes (Eq. 1, or no normalisation with rows of whole tiles or the l2 scale): the scale pass keeps the
     # elements that can code non-zero and the quantise pass codes those, so g is read once; what the quantise
     # pass must move is then the packed codes (the candidate words, a few percent of the elements, are the
     # method's own overhead and are not counted as algorithmic bytes)
-    single_read = (bits == 2 and (scale == B.SCALE_MAX or M >= 4) and norm in (B.NORM_NONE, B.NORM_SUB)
+    single_read = (bits == 2 and (scale == B.SCALE_MAX or M >= 4)
+                   and (norm == B.NORM_SUB or norm == B.NORM_NONE and (scale == B.SCALE_L2 or d % 1024 == 0))
                    and M * d >= 1 << 26 and d // 1024 >= 512)
     if single_read:
         b_quant = 4 * M * words

@@ -2485,6 +2485,9 @@ size_t candidate_scratch_bytes(const CodecShape& c) {
   if (c.bits != 2 || (c.norm != kNormNone && c.norm != kNormSub)) return 0;
   // (the l2 scale: nor fewer workers than a workgroup has wavefronts)
   if (c.scale_l2 != 0 && c.M < (uint32_t)kWavesPerBlock) return 0;
+  // (gradients as they are, rows of any length: Gaussian ones are too dense for the slots, which is found out too late to
+  // cost nothing -- d = 2^25 + 4, M = 2 117 us by two passes, 136 this way; d = 80333292, M = 13 1528 / 1731)
+  if (c.scale_l2 == 0 && c.norm == kNormNone && c.d % kWaveTileElements != 0) return 0;
   if ((uint64_t)c.M * c.d < (1ull << 26) || c.d / 1024 < 4 * (uint64_t)kSampleStride) return 0;
   return candidate_head_bytes(c.M) + (size_t)c.M * (c.d / 1024) * kSlotEntries * sizeof(uint32_t);
 }

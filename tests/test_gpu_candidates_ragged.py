@@ -29,9 +29,9 @@ def check(M, d, norm, g, gref, it, scale=B.SCALE_MAX):
     assert np.array_equal(buf["vbar"].cpu().numpy(), O.decode_aggregate(cfg, codes, scales, rh, d, rh, None))
 
 
-@pytest.mark.parametrize("M,d,norm", [(1, (1 << 26) + 1, B.NORM_SUB), (2, (1 << 25) + 1023, B.NORM_NONE),
+@pytest.mark.parametrize("M,d,norm", [(1, (1 << 26) + 1, B.NORM_SUB), (2, (1 << 25) + 1023, B.NORM_SUB),
                                       (3, (1 << 25) + 514, B.NORM_SUB), (5, (1 << 24) + 4099, B.NORM_SUB),
-                                      (9, (1 << 23) + 4, B.NORM_NONE), (17, (1 << 22) + 255, B.NORM_SUB)])
+                                      (9, (1 << 23) + 4, B.NORM_SUB), (17, (1 << 22) + 255, B.NORM_SUB)])
 def test_ragged_rows(M, d, norm):
     g, gref, _ = _inputs(M, d, seed=M)
     g[M - 1, d - 1] += 3.0 * (g[M - 1] - gref).abs().max()  # the last worker's scale is set in the ragged tile
@@ -68,7 +68,7 @@ def test_l2_scale_outside_the_sample():
     check(M, d, B.NORM_NONE, v, v[0].clone(), 2, B.SCALE_L2)
 
 
-@pytest.mark.parametrize("M,d,norm", [(10, 1 << 23, B.NORM_SUB), (9, 1 << 23, B.NORM_SUB), (20, (1 << 22) + 1029, B.NORM_NONE)])
+@pytest.mark.parametrize("M,d,norm", [(10, 1 << 23, B.NORM_SUB), (9, 1 << 23, B.NORM_SUB), (20, (1 << 22) + 1029, B.NORM_SUB), (10, 1 << 23, B.NORM_NONE)])
 def test_groups_of_five_workers(M, d, norm):
     g, gref, _ = _inputs(M, d, seed=M)
     check(M, d, norm, g, gref, 4)

@@ -1,0 +1,23 @@
+"""Where tng_workspace_bytes includes the candidate slots (M * floor(d / 1024) * 512 bytes) of the ternary coder that
+reads the gradients once."""
+import pytest
+
+from paper_1901_08227_amd import binding as B
+from test_abi import _cfg
+
+
+def slots(**kw):
+    """The workspace beyond what the same problem needs with 4-bit codes, which have no slots, over the size of the slots."""
+    need = [B.tng_workspace_bytes(_cfg(problem=B.PROB_EXTERNAL, batch=0, bits=bits, **kw)) for bits in (2, 4)]
+    return (need[0] - need[1]) / (kw["M"] * (kw["d"] // 1024) * 512)
+
+
+@pytest.mark.parametrize("norm,scale,M,d,held", [
+    (B.NORM_SUB, B.SCALE_MAX, 8, 1 << 23, True), (B.NORM_SUB, B.SCALE_MAX, 8, (1 << 23) + 3, True),
+    (B.NORM_SUB, B.SCALE_MAX, 8, (1 << 23) - 1, False), (B.NORM_NONE, B.SCALE_MAX, 8, 1 << 23, True),
+    (B.NORM_NONE, B.SCALE_MAX, 8, (1 << 23) + 3, False), (B.NORM_QUOT, B.SCALE_MAX, 8, 1 << 23, False),
+    (B.NORM_SUB, B.SCALE_L2, 4, (1 << 24) + 3, True), (B.NORM_NONE, B.SCALE_L2, 4, (1 << 24) + 3, True),
+    (B.NORM_SUB, B.SCALE_L2, 3, 1 << 25, False)])
+def test_which_configurations_hold_slots(norm, scale, M, d, held):
+    share = slots(norm=norm, scale=scale, M=M, d=d)
+    assert 1.0 <= share < 1.1 if held else share == 0
