@@ -276,10 +276,14 @@ __device__ __forceinline__ float4 load_row_ragged(const GradRows& g, uint32_t m,
 // reference tile stays in registers.
 constexpr int kAbsmaxLoads = 4;
 
-__device__ __forceinline__ void absmax_load(const v4f_u_t* __restrict__ row, const uint64_t (&iv)[kAbsmaxLoads],
+// Worker m's part of the tile.  Past the last worker (in a short group) every lane fetches the same float4 instead: a load,
+// never a branch, and no memory to wait for; nothing is made of it.
+__device__ __forceinline__ void absmax_load(const GradRows& g, uint32_t m, uint32_t M, const uint64_t (&iv)[kAbsmaxLoads],
                                             float4 (&x)[kAbsmaxLoads]) {
+  const uint64_t keep = m < M ? ~0ull : 0ull;
+  const v4f_u_t* row = g.row(min(m, M - 1));
 #pragma unroll
-  for (int j = 0; j < kAbsmaxLoads; ++j) x[j] = load_row_stream(row + iv[j]);
+  for (int j = 0; j < kAbsmaxLoads; ++j) x[j] = load_row_stream(row + (iv[j] & keep));
 }
 
 template <int NORM, bool RECIP>
@@ -310,16 +314,14 @@ __device__ __forceinline__ void absmax_rows(const GradRows& g, const RefTile<NOR
                                             const float* __restrict__ means, float (&mx)[MC]) {
   constexpr int L = kAbsmaxLoads;
   float4 xa[L], xb[L];
-  // rows past M (only when MC does not divide M) repeat the last row, which leaves its maximum unchanged
-  auto row = [&](int mm) { return g.row(min(m0 + (uint32_t)mm, M - 1)); };
   auto mean_of = [&](int mm) { return NORM == kNormMean ? means[min(m0 + (uint32_t)mm, M - 1)] : 0.f; };
-  absmax_load(row(0), iv, xa);
+  absmax_load(g, m0, M, iv, xa);
 #pragma unroll
   for (int mm = 0; mm < MC; mm += 2) {
-    if (mm + 1 < MC) absmax_load(row(mm + 1), iv, xb);
+    if (mm + 1 < MC) absmax_load(g, m0 + mm + 1, M, iv, xb);
     mx[mm] = fmaxf(mx[mm], absmax_reduce<NORM, kByReciprocal<NORM, MC>>(xa, rt, mean_of(mm)));
     if (mm + 1 < MC) {
-      if (mm + 2 < MC) absmax_load(row(mm + 2), iv, xa);
+      if (mm + 2 < MC) absmax_load(g, m0 + mm + 2, M, iv, xa);
       mx[mm + 1] = fmaxf(mx[mm + 1], absmax_reduce<NORM, kByReciprocal<NORM, MC>>(xb, rt, mean_of(mm + 1)));
     }
   }
