@@ -685,7 +685,7 @@ tng_status tng_step(tng_ctx* ctx, uint32_t iter, float* w, float* gref, float* g
     s = hip_status(tng::launch_single_pass(ctx->shape, iter, g, gref, ctx->gref2, scales, codes, true, vbar, w, c.lr,
                                            ref_out, ctx->stream));
     if (s != TNG_OK) return s;
-  } else if (ctx->prof_slots == 0 && tng::quantize_decode_applies(ctx->shape)) {
+  } else if (ctx->prof_slots == 0 && tng::quantize_decode_applies(ctx->shape, fused_rows > 0)) {
     uint32_t rows = 0;
     bool by_candidates = false;
     // The candidate slots save the second read of g, one launch the second trip of the codes and the reference: at 2^26

@@ -2565,13 +2565,19 @@ hipError_t quantize_decode_dispatch(const CodecShape& c, uint32_t iter, const fl
 }
 }  // namespace
 
-// Where the one launch is faster than the separate ones: always while launches set the time (d <= 2^18); beyond, the
+// Where the one launch is faster than the separate ones: while launches set the time (d <= 2^18; 2^17 with more than 16
+// workers that subtract no reference); never with more workers than its table holds; beyond, the
 // thread per float4 needs three workers to have loads enough in flight (iteration with given gradients, no
 // normalisation, d = 2^25, M = 1 144 us apart, 185 in one launch) and takes more than eight of them in trips that drain
 // (d = 2^22, M = 16 115 / 123; d = 2^24, M = 12 364 / 330), and the workers by wavefront are ahead only where the
-// reference is subtracted (d = 2^23, M = 20: 308 / 297; quotient 318 / 341).
-bool quantize_decode_applies(const CodecShape& c) {
+// reference is subtracted (d = 2^23, M = 20: 308 / 297; quotient 318 / 341).  Without a reference to read again it
+// saves less behind a scale pass for the largest magnitude: d = 2^20, M = 4 14.8 / 13.0, M = 8 19.8 / 21.8; d = 2^21,
+// M = 3 19.2 / 21.4, M = 8 33.3 / 35.2; d = 2^23, M = 4 75 / 76, M = 8 129 / 117; d = 2^24, M = 3 118 / 123; not where the
+// gradient kernel left the maxima (Rosenbrock, d = 2^20, M = 8 30.9 / 25.9; d = 2^21, M = 4 32.7 / 29.0).
+bool quantize_decode_applies(const CodecShape& c, bool maxima_left) {
   if (c.M > kTailMaxWorkers) return false;
+  const bool small = c.d <= (1u << 20) && c.d * c.M <= (1u << 22);
+  if (c.norm == kNormNone && c.scale_l2 == 0 && !maxima_left && !small && (c.M <= 4 || c.d < (1u << 22))) return false;
   if (c.M > 16) return c.norm == kNormSub ? c.d <= (1u << 18) || c.d >= (1u << 23) : c.d <= (1u << 17);
   if (c.M > 8) return c.d <= (1u << 20) || c.d >= (1u << 23);
   return c.M > 2 || c.d <= (1u << 20);
@@ -2582,7 +2588,7 @@ uint32_t quantize_decode_rows(const CodecShape& c) { return kTailPartials / c.M;
 hipError_t launch_quantize_decode(const CodecShape& c, uint32_t iter, const float* g, const float* gref,
                                   const float* gref2, float* scales, uint32_t* codes, const float* partials,
                                   uint32_t rows, float* vbar, float* w, float lr, float* ref_out, hipStream_t s) {
-  if (!quantize_decode_applies(c)) return hipErrorInvalidValue;
+  if (c.M > kTailMaxWorkers) return hipErrorInvalidValue;
   if (rows > quantize_decode_rows(c)) {
     const hipError_t e = launch_absmax_finish(partials, rows, c.M, scales, s);
     if (e != hipSuccess) return e;

@@ -96,7 +96,8 @@ uint32_t quantize_fused_rows(const CodecShape& c);
 
 // launch_quantize_pack and launch_decode (with w) in one launch, bit for bit: for tng_step.  rows > 0: that many rows
 // of partial maxima instead of scales, as fused_rows above; up to quantize_decode_rows of them are reduced inside.
-bool quantize_decode_applies(const CodecShape& c);
+// quantize_decode_applies: where that is the faster way; maxima_left: the gradient kernel has left the partial maxima.
+bool quantize_decode_applies(const CodecShape& c, bool maxima_left);
 uint32_t quantize_decode_rows(const CodecShape& c);
 hipError_t launch_quantize_decode(const CodecShape& c, uint32_t iter, const float* g, const float* gref,
                                   const float* gref2, float* scales, uint32_t* codes, const float* partials,
