@@ -2490,6 +2490,9 @@ size_t candidate_scratch_bytes(const CodecShape& c) {
   // (gradients as they are, rows of any length: Gaussian ones are too dense for the slots, which is found out too late to
   // cost nothing -- d = 2^25 + 4, M = 2 117 us by two passes, 136 this way; d = 80333292, M = 13 1528 / 1731)
   if (c.scale_l2 == 0 && c.norm == kNormNone && c.d % kWaveTileElements != 0) return 0;
+  // (the slots are an eighth of the gradients: up to 4 GiB for rows of any length and for the l2 scale, so that what fits the
+  // card by two passes still does)
+  if ((c.scale_l2 != 0 || c.d % kWaveTileElements != 0) && (uint64_t)c.M * c.d > (1ull << 33)) return 0;
   if ((uint64_t)c.M * c.d < (1ull << 26) || c.d / 1024 < 4 * (uint64_t)kSampleStride) return 0;
   return candidate_head_bytes(c.M) + (size_t)c.M * (c.d / 1024) * kSlotEntries * sizeof(uint32_t);
 }

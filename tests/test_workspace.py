@@ -17,7 +17,11 @@ def slots(**kw):
     (B.NORM_SUB, B.SCALE_MAX, 8, (1 << 23) - 1, False), (B.NORM_NONE, B.SCALE_MAX, 8, 1 << 23, True),
     (B.NORM_NONE, B.SCALE_MAX, 8, (1 << 23) + 3, False), (B.NORM_QUOT, B.SCALE_MAX, 8, 1 << 23, False),
     (B.NORM_SUB, B.SCALE_L2, 4, (1 << 24) + 3, True), (B.NORM_NONE, B.SCALE_L2, 4, (1 << 24) + 3, True),
-    (B.NORM_SUB, B.SCALE_L2, 3, 1 << 25, False)])
+    (B.NORM_SUB, B.SCALE_L2, 3, 1 << 25, False),
+    # beyond 2^33 gradients: rows of whole tiles with the largest-magnitude scale only
+    (B.NORM_SUB, B.SCALE_MAX, 8, (1 << 30) - 1, True), (B.NORM_SUB, B.SCALE_MAX, 8, (1 << 30) + 1, False),
+    (B.NORM_SUB, B.SCALE_L2, 8, 1 << 30, True), (B.NORM_NONE, B.SCALE_L2, 9, 1 << 30, False),
+    (B.NORM_SUB, B.SCALE_MAX, 9, 1 << 30, True)])
 def test_which_configurations_hold_slots(norm, scale, M, d, held):
     share = slots(norm=norm, scale=scale, M=M, d=d)
     assert 1.0 <= share < 1.1 if held else share == 0
