@@ -168,20 +168,24 @@ def test_same_codes_as_the_two_pass_coder_on_shorter_rows():
     short_ctx.close()
 
 
-def test_whole_iteration_with_gradients_from_the_caller():
-    # tng_step on gradients handed in by the caller (no problem attached): its encode part takes the same path,
-    # the decode part updates the iterate and refreshes the reference in place; two iterations, the second from
+@pytest.mark.parametrize("M,d,scale", [
+    (8, 1 << 23, B.SCALE_MAX),  # 5 to 16 workers, up to 2^27 elements: one launch after the scale pass, no slots
+    (4, 1 << 24, B.SCALE_MAX), (4, (1 << 24) + 4099, B.SCALE_MAX), (17, 1 << 23, B.SCALE_MAX),  # slots, then decode
+    (4, 1 << 24, B.SCALE_L2), (8, (1 << 23) + 5, B.SCALE_L2),  # the same for the l2 scale, whatever the workers
+    (1, 1 << 26, B.SCALE_MAX)])  # the separate passes, encode by the slots
+def test_whole_iteration_with_gradients_from_the_caller(M, d, scale):
+    # tng_step on gradients handed in by the caller (no problem attached), on each side of its rule for the slots: the
+    # decode part updates the iterate and refreshes the reference in place; two iterations, the second from
     # the state the first one left
-    M, d = 8, 1 << 23
     g, gref, _ = _inputs(M, d, seed=41)
-    ctx = B.Context(d=d, M=M, bits=2, norm=B.NORM_SUB, ref_policy=B.REF_LAST_AVG, ref_period=2, seed=12, lr=0.05,
+    ctx = B.Context(d=d, M=M, bits=2, norm=B.NORM_SUB, scale=scale, ref_policy=B.REF_LAST_AVG, ref_period=2, seed=12, lr=0.05,
                     problem=B.PROB_EXTERNAL, device=DEV)
     cfg = oracle_cfg(ctx)
     buf = buffers(ctx)
     w = torch.randn(d, generator=torch.Generator(device=DEV).manual_seed(5), device=DEV)
     gref = gref.clone()
     for it in range(2):
-        say(f"candidates case whole iteration: it={it}")
+        say(f"candidates case whole iteration: d={d} M={M} scale={scale} it={it}")
         gi = g if it == 0 else (g * 0.5 + torch.roll(g, 1, dims=0) * 0.5).contiguous()
         w0, r0 = w.cpu().numpy(), gref.cpu().numpy()
         ctx.step(it, w, gref, gi, buf["codes"], buf["scales"], buf["vbar"])
