@@ -32,7 +32,7 @@ struct tng_ctx {
   float* history;         // [ref_window][d] ring of decoded averages (window-average reference)
   float* parts;           // dense problem: partial gradients [M][splits][d] of the one-pass kernels, or null
   uint32_t* check;        // CSR problem: flag word of tng_validate_csr, then uint64[M] entry counts at +256 bytes
-  double* sums;           // chunk and group sums of the order-pinned row sums (mean reference, l2 scale)
+  double* sums;           // chunk sums of the order-pinned row sums (mean reference, l2 scale)
   void* cand;             // scratch of the ternary coder that reads g once (candidate slots), or null
   std::vector<hipEvent_t> prof;  // optional timing events, 5 per slot
   uint32_t prof_slots;
@@ -206,8 +206,9 @@ bool single_pass_ok(const tng_ctx* ctx, const float* g, const float* gref, const
 
 // The scale pass.  fused_rows > 0: a gradient kernel has already left that many rows of partial maxima in the
 // workspace, only their reduction remains.  On return *rows is the number of rows of partial maxima whose reduction
-// is left to the next launch (0: scales is complete; the pass leaves at most max_left of its own), and, if slots_ok,
-// *by_candidates tells that the candidate slots hold what the quantise pass needs.
+// is left to the next launch (0: scales is complete; the pass leaves at most max_left of its own), and *by_candidates
+// tells that the candidate slots hold what the quantise pass needs.  slots_ok: whether they may be used with the
+// largest-magnitude scale; with the l2 scale they are wherever there are any.
 tng_status scale_impl(tng_ctx* ctx, uint32_t iter, const float* g, const float* gref, const uint32_t* codes,
                       float* scales, uint32_t fused_rows, uint32_t max_left, bool slots_ok, uint32_t* rows,
                       bool* by_candidates) {
@@ -690,7 +691,8 @@ tng_status tng_step(tng_ctx* ctx, uint32_t iter, float* w, float* gref, float* g
     bool by_candidates = false;
     // The candidate slots save the second read of g, one launch the second trip of the codes and the reference: at 2^26
     // to 2^27 gradients the latter is ahead with 5 to 16 workers (d = 2^24, M = 8: 244 against 287 us; d = 2^25, M = 8:
-    // 504 against 498; d = 2^24, M = 4: 164 against 152).
+    // 504 against 498; d = 2^24, M = 4: 164 against 152).  With the l2 scale, under which hardly an element is a candidate, the
+    // slots are (d = 2^23, M = 8: 150 against 125; d = 2^24, M = 8: 281 against 223, M = 5: 224 against 178).
     const bool slots_ok = c.M <= 4 || c.M > 16 || (uint64_t)c.M * c.d > (1ull << 27);
     s = scale_impl(ctx, iter, g, gref, codes, scales, fused_rows, tng::quantize_decode_rows(ctx->shape), slots_ok, &rows,
                    &by_candidates);

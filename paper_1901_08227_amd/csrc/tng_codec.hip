@@ -2066,7 +2066,7 @@ hipError_t absmax_vec_launch(const CodecShape& c, const float* g, const float* g
 
 // Scratch of the ternary coder that reads g once: the word that says whether the slots are used, the
 // sample's maxima [M], the sample pass's partial maxima [kAbsmaxMaxBlocks][M], the overflow counts of the
-// scale pass's workgroups (as many), the slots [M][d / 1024] of 1 KiB.
+// scale pass's workgroups (as many), the slots [M][d / 1024] of 512 bytes.
 struct CandidateScratch {
   uint32_t* use_slots;
   float* sample_max;
@@ -2353,8 +2353,7 @@ hipError_t launch_absmax(const CodecShape& c, const float* g, const float* gref,
 
 size_t tree_sum_scratch(uint64_t d, uint32_t M) {
   const uint64_t nchunks = (d + kTreeChunk - 1) / kTreeChunk;
-  const uint64_t ngroups = (nchunks + kTreeGroup - 1) / kTreeGroup;
-  return (size_t)((2 * nchunks + ngroups) * M);  // chunk sums, chunk (min, max) pairs, group sums
+  return (size_t)(2 * nchunks * M);  // chunk sums, chunk (min, max) pairs
 }
 
 namespace {
