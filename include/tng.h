@@ -113,9 +113,14 @@ typedef struct {
 uint64_t tng_words_per_row(uint64_t d, uint32_t bits);
 
 /* Device scratch bytes tng_create needs for this configuration; 0 if the configuration is invalid.
- * (For 2-bit codes with the largest-magnitude scale and TNG_NORM_NONE / TNG_NORM_SUB over 2^26 elements or
- * more, d a multiple of 1024, this includes M * d / 2 bytes: tng_normalize_encode then reads g once and
- * keeps the few elements that can code non-zero there between its two passes; same codes, bit for bit.) */
+ * For 2-bit codes over 2^26 elements or more, in rows of 2^19 or more, this includes about M * d / 2 bytes of slots:
+ * tng_normalize_encode then reads g once and keeps the few elements that can code non-zero there between its two passes;
+ * same codes, bit for bit.  That is so
+ *   - with the largest-magnitude scale and TNG_NORM_SUB, and with TNG_NORM_NONE if d is a multiple of 1024;
+ *   - with the l2 scale, four workers or more, and TNG_NORM_SUB or TNG_NORM_NONE;
+ * but with the l2 scale, or with d no multiple of 1024, only up to 2^33 elements.  tng_step leaves the slots alone where one
+ * pass after the scales is faster (largest-magnitude scale, 5 to 16 workers, up to 2^27 elements); the workspace holds them
+ * all the same. */
 size_t tng_workspace_bytes(const tng_config* cfg);
 
 /* Creates a context.  cfg: host.  workspace: device, 256-byte aligned, at least

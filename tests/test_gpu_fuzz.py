@@ -22,7 +22,7 @@ def _case(rng):
     elif kind == 2:
         d = 4096 * tiles + 4 * int(rng.integers(1, 1024))  # vector path, code rows not 16-byte aligned
     elif kind == 3:
-        d = 4096 * tiles + int(rng.integers(1, 4096))      # any d: element-at-a-time kernels when d % 4 != 0
+        d = 4096 * tiles + int(rng.integers(1, 4096))      # any d: a ragged last tile, float4s that end past the row when d % 4 != 0
     else:
         d = int(rng.integers(1, 300))
     M = int(rng.choice([1, 2, 3, 4, 5, 8, 12, 16, 17, 24]))
