@@ -273,8 +273,9 @@ def whole_iteration_benchmarks(torch, B, synth, dev, steps, warmup, with_oracle=
     ctx.set_logreg_dense([X[m] for m in range(M)], [y[m] for m in range(M)])
     ms = time_steps(torch, ctx, step_state(torch, ctx, torch.zeros(d, device=dev)), steps * 4, warmup)
     orc = (logistic_oracle(ctx, X, y, n, d), "same shape") if with_oracle else None
-    record("dense logistic d=1000 M=4 B=64 ternary sub", ms, step_bytes("dense", M, d, ctx.words, batch),
-           "3 kernel launches per iteration, 1 MB of minibatch rows: bound by launch latency, not by memory", orc,
+    # eight workgroups per worker take eight rows each and keep them on chip
+    record("dense logistic d=1000 M=4 B=64 ternary sub", ms, step_bytes("dense", M, d, ctx.words, batch, row_splits=8),
+           "2 kernel launches per iteration, 1 MB of minibatch rows: bound by launch latency, not by memory", orc,
            bound="launch latency")
     ctx.close()
     del X, y

@@ -2353,7 +2353,9 @@ hipError_t launch_absmax(const CodecShape& c, const float* g, const float* gref,
 
 size_t tree_sum_scratch(uint64_t d, uint32_t M) {
   const uint64_t nchunks = (d + kTreeChunk - 1) / kTreeChunk;
-  return (size_t)(2 * nchunks * M);  // chunk sums, chunk (min, max) pairs
+  const uint64_t ngroups = (nchunks + kTreeGroup - 1) / kTreeGroup;
+  // chunk sums, chunk (min, max) pairs; a word per group, unused (the group sums stay on chip), keeps the workspace's size
+  return (size_t)((2 * nchunks + ngroups) * M);
 }
 
 namespace {
