@@ -722,10 +722,20 @@ __global__ __launch_bounds__(kBlock) void logreg_dense_parts_kernel(const float*
 // ------------------------------------------------------------------------------------------
 constexpr int kCsrThreads = 1024;  // 16 wavefronts
 constexpr int kCsrRows = 512;      // minibatch rows staged in LDS per trip
-constexpr int kCsrLanes = 32;      // lanes that share one row segment (mean segment: 16 entries at 0.1 % density)
-constexpr int kCsrUnroll = 16;     // row segments in flight per lane group
+// A lane takes two entries of a row segment at once (16 bytes of pairs), and few lanes share a segment.  What bounds these
+// passes, next to the bytes, is how many instructions a wavefront issues per entry: with an entry per lane, 32 lanes to a
+// segment and a branch around every load and use, the dot products took 600 vector and 850 scalar instructions per
+// wavefront and 512 rows, about two thirds of their time, and the segments' loads by themselves ran 25 to 30 % slower than
+// with 16 bytes per lane (1.21 -> 0.92 ms for the segments of 2^14 columns, 64 workers, 512 rows of 16777 pairs).  Iteration
+// at d = 2^24, M = 64, B = 512, 0.1 % density 4160 -> 3726 us (dot products 1160 -> 930, gradient 1975 -> 1890, which the LDS
+// bounds: its atomic adds and write-out keep it busy for three quarters of the time); d = 2^16, M = 8 19.1 -> 18.1.
+constexpr int kCsrLanes = 8;                  // lanes that share one row segment
+constexpr int kCsrUnroll = 4;                 // row segments per lane group and trip
+constexpr uint32_t kCsrStep = 2 * kCsrLanes;  // entries that a load of each lane covers
+constexpr int kCsrLoads = 2;                  // such loads per segment of a tile (mean segment: 16 entries at 0.1 % density)
+constexpr int kCsrWideLoads = 3;              // the same for two tiles
 constexpr uint32_t kCsrGroups = kCsrThreads / kCsrLanes;
-static_assert(kCsrGroups * kCsrUnroll == kCsrRows, "one sweep of the lane groups covers one trip");
+static_assert(kCsrGroups * kCsrUnroll == kCsrRows && kCsrRows <= kCsrThreads, "one sweep of the lane groups covers one trip");
 
 // The stored entries of one worker's shard, in either of the two layouts the library takes: separate
 // column and value arrays, or one array of (column, value) pairs.  With pairs a row segment of a
@@ -734,6 +744,13 @@ static_assert(kCsrGroups * kCsrUnroll == kCsrRows, "one sweep of the lane groups
 // memory lines they touch, so one piece of twice the length moves the same entries in about two
 // thirds of the line traffic, with half the load instructions.
 typedef int v2i_t __attribute__((ext_vector_type(2)));
+typedef int v2i_u_t __attribute__((ext_vector_type(2), aligned(4)));
+typedef float v2f_u_t __attribute__((ext_vector_type(2), aligned(4)));
+typedef int v4i_u_t __attribute__((ext_vector_type(4), aligned(8)));
+struct CsrTwo {
+  int32_t col[2];
+  float val[2];
+};
 // Which column tile (of n, one per workgroup along x) workgroup bx takes.  Workgroups are handed to the
 // eight compute dies in turn (bx mod 8), each die with an L2 of its own: die k gets the k-th eighth of the
 // tiles, in order, so that the workgroups running side by side on a die are on ADJACENT tiles and the memory
@@ -761,19 +778,26 @@ struct CsrEntries {
       val = v[pos];
     }
   }
-  // The same without a branch: entry pos if on, else whatever lies at dummy (any 8 valid bytes, 8-byte aligned).
-  __device__ __forceinline__ void load_or(bool on, int64_t pos, const void* dummy, int32_t& col, float& val) const {
+  // Entries pos and pos + 1.
+  __device__ __forceinline__ CsrTwo load2(int64_t pos) const {
     if (PAIRS) {
-      const GlobalPtr<v2i_t> at = on ? reinterpret_cast<GlobalPtr<v2i_t>>(c) + pos : (GlobalPtr<v2i_t>)dummy;
-      const v2i_t p = *at;
-      col = p.x;
-      val = __int_as_float(p.y);
-    } else {
-      const GlobalPtr<int32_t> ac = on ? c + pos : (GlobalPtr<int32_t>)dummy;
-      const GlobalPtr<float> av = on ? v + pos : (GlobalPtr<float>)dummy;
-      col = *ac;
-      val = *av;
+      const v4i_u_t p = *reinterpret_cast<GlobalPtr<v4i_u_t>>(c + 2 * pos);
+      return CsrTwo{{p.x, p.z}, {__int_as_float(p.y), __int_as_float(p.w)}};
     }
+    const v2i_u_t ci = *reinterpret_cast<GlobalPtr<v2i_u_t>>(c + pos);
+    const v2f_u_t vi = *reinterpret_cast<GlobalPtr<v2f_u_t>>(v + pos);
+    return CsrTwo{{ci.x, ci.y}, {vi.x, vi.y}};
+  }
+  // The position that load2 reads dummy at (16 valid bytes, 8-byte aligned), for segments without entries; two arrays have
+  // no such position: they are read at dummy by load2_any.
+  __device__ __forceinline__ int64_t position_of(const void* dummy) const {
+    return PAIRS ? ((int64_t)reinterpret_cast<uintptr_t>(dummy) - (int64_t)reinterpret_cast<uintptr_t>((const int32_t*)c)) / 8 : 0;
+  }
+  __device__ __forceinline__ CsrTwo load2_any(bool any, int64_t pos, const void* dummy) const {
+    if (PAIRS) return load2(pos);
+    const v2i_u_t ci = *(any ? reinterpret_cast<GlobalPtr<v2i_u_t>>(c + pos) : (GlobalPtr<v2i_u_t>)dummy);
+    const v2f_u_t vi = *(any ? reinterpret_cast<GlobalPtr<v2f_u_t>>(v + pos) : (GlobalPtr<v2f_u_t>)dummy);
+    return CsrTwo{{ci.x, ci.y}, {vi.x, vi.y}};
   }
 };
 
@@ -905,41 +929,137 @@ __global__ __launch_bounds__(kBlock) void csr_gather_bounds_kernel(const int64_t
   }
 }
 
-// Stages, for minibatch rows first .. first+count-1 of worker m, the entry range of the row that
-// falls into tile t (absolute positions).
-__device__ __forceinline__ void csr_stage_segments(const int64_t* __restrict__ rowbase,
-                                                   const uint32_t* __restrict__ bounds, uint32_t m, uint32_t batch,
-                                                   uint32_t ntiles, uint32_t t, uint32_t first, uint32_t count,
-                                                   int64_t* sLo, uint32_t* sLen) {
-  const uint32_t* __restrict__ b = bounds + ((uint64_t)m * (ntiles + 1) + t) * batch + first;
-  const int64_t* __restrict__ base = rowbase + (uint64_t)m * batch + first;
-  for (uint32_t j = threadIdx.x; j < count; j += kCsrThreads) {
-    const uint32_t lo = b[j], hi = b[batch + j];
-    sLo[j] = base[j] + lo;
-    sLen[j] = hi - lo;
-  }
-}
-
-// The first lane-width of entries of kCsrUnroll row segments, all loads issued before any is used.
-struct CsrBatch {
-  uint32_t len[kCsrUnroll];
-  int32_t col[kCsrUnroll];
-  float val[kCsrUnroll];
+// What the lanes need of one row segment, staged in LDS by a thread per row: an even number of entries from pos on, and the
+// factor of the row.  A segment of odd length is taken with the entry before it, which is skipped (it is some other
+// segment's: reading one past the end could leave the array); only the array's very first entry has none before it and is
+// taken by itself (kCsrHead).
+struct __align__(16) CsrSeg {
+  int64_t pos;
+  uint32_t n;  // entries, kCsrSkip, kCsrHead
+  float r;
 };
+constexpr uint32_t kCsrSkip = 0x80000000u, kCsrHead = 0x40000000u, kCsrCount = 0x3FFFFFFFu;
 
 template <bool PAIRS>
-__device__ __forceinline__ void csr_load_batch(const CsrEntries<PAIRS>& e, const int64_t* sLo, const uint32_t* sLen,
-                                               uint32_t j0, uint32_t count, uint32_t gl, CsrBatch& b) {
+__device__ __forceinline__ CsrSeg csr_segment(const CsrEntries<PAIRS>& e, int64_t start, uint32_t len, float r, const void* dummy) {
+  const bool odd = (len & 1u) != 0, head = odd && start == 0;
+  const uint32_t n = odd ? (head ? len - 1 : len + 1) : len;
+  CsrSeg s;
+  s.pos = n == 0 ? e.position_of(dummy) : odd ? (head ? 1 : start - 1) : start;
+  s.n = n | (head ? kCsrHead : odd ? kCsrSkip : 0u);
+  s.r = r;
+  return s;
+}
+
+// Stages minibatch rows first .. first + kCsrRows - 1 of worker m in tile t (those past the minibatch without entries).
+template <bool PAIRS>
+__device__ __forceinline__ void csr_stage_segments(const CsrEntries<PAIRS>& e, const int64_t* __restrict__ rowbase,
+                                                   const uint32_t* __restrict__ bounds, const float* __restrict__ resid,
+                                                   uint32_t m, uint32_t batch, uint32_t ntiles, uint32_t t,
+                                                   uint32_t first, CsrSeg* seg) {
+  if (threadIdx.x >= (uint32_t)kCsrRows) return;
+  const uint32_t j = min(first + threadIdx.x, batch - 1);
+  const uint32_t* __restrict__ b = bounds + ((uint64_t)m * (ntiles + 1) + t) * batch + j;
+  const uint64_t o = (uint64_t)m * batch + j;
+  const uint32_t lo = b[0], hi = b[batch];
+  const float r = resid != nullptr ? resid[o] : 0.f;
+  seg[threadIdx.x] = csr_segment(e, rowbase[o] + lo, first + threadIdx.x < batch ? hi - lo : 0u, r, rowbase + (uint64_t)m * batch);
+}
+
+// The first Q kCsrStep entries of U row segments.
+template <int U, int Q>
+struct CsrBatch {
+  uint32_t n[U];
+  float r[U];
+  CsrTwo two[U][Q];
+};
+
+// All loads are issued before any is used and none sits under a condition (the compiler cannot count such loads and makes
+// every later wait a wait for all of them): lanes beyond the end of a segment read its last pair again.
+template <bool PAIRS, int U, int Q>
+__device__ __forceinline__ void csr_request(const CsrEntries<PAIRS>& e, const CsrSeg* seg, uint32_t gl, const void* dummy,
+                                            CsrBatch<U, Q>& b) {
 #pragma unroll
-  for (int u = 0; u < kCsrUnroll; ++u) {
-    const uint32_t j = j0 + u;
-    b.len[u] = j < count ? sLen[j] : 0u;
-    b.col[u] = 0;
-    b.val[u] = 0.f;
-    if (gl < b.len[u]) e.load(sLo[j] + gl, b.col[u], b.val[u]);
+  for (int u = 0; u < U; ++u) {
+    const CsrSeg s = seg[u];
+    b.n[u] = s.n;
+    b.r[u] = s.r;
+    const uint32_t n = s.n & kCsrCount, last = n != 0 ? n - 2 : 0u;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) b.two[u][q] = e.load2_any(n != 0, s.pos + min(2 * gl + q * kCsrStep, last), dummy);
   }
 }
 
+// use(whether, column, value, u) for the lane's entries of the batch and of what is behind it; entries that are not the
+// lane's come with whether = false (and anything for column and value).
+template <bool PAIRS, int U, int Q, typename F>
+__device__ __forceinline__ void csr_use(const CsrEntries<PAIRS>& e, const CsrSeg* seg, uint32_t gl, const void* dummy,
+                                        const CsrBatch<U, Q>& b, const F& use) {
+  uint32_t longest = 0, any = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const uint32_t n = b.n[u] & kCsrCount;
+    longest = max(longest, n);
+    any |= b.n[u];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const bool in = 2 * gl + q * kCsrStep < n;
+      const bool skip = q == 0 && gl == 0 && (b.n[u] & kCsrSkip) != 0;
+      use(in && !skip, b.two[u][q].col[0], b.two[u][q].val[0], u);
+      use(in, b.two[u][q].col[1], b.two[u][q].val[1], u);
+    }
+  }
+  for (uint32_t k = Q * kCsrStep; __builtin_amdgcn_ballot_w64(longest > k) != 0ull; k += kCsrStep) {
+    CsrTwo two[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t n = b.n[u] & kCsrCount;
+      two[u] = e.load2_any(n != 0, seg[u].pos + min(2 * gl + k, n != 0 ? n - 2 : 0u), dummy);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool in = 2 * gl + k < (b.n[u] & kCsrCount);
+      use(in, two[u].col[0], two[u].val[0], u);
+      use(in, two[u].col[1], two[u].val[1], u);
+    }
+  }
+  if (__builtin_amdgcn_ballot_w64((any & kCsrHead) != 0) != 0ull) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (gl == 0 && (b.n[u] & kCsrHead) != 0) {
+        int32_t c;
+        float v;
+        e.load(0, c, v);
+        use(true, c, v, u);
+      }
+    }
+  }
+}
+
+// U sums over the kCsrLanes lanes of a group (2 or 4 sums): lanes exchange halves until each has one sum left, which is then
+// added over the lanes that share it.  Lane gl then has sum
+// gl U / kCsrLanes.
+template <int CTRL>
+__device__ __forceinline__ float csr_lane_move(float v) {
+  return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xF, 0xF, false));
+}
+template <int U>
+__device__ __forceinline__ float csr_group_sums(const float (&acc)[U], uint32_t gl) {
+  static_assert(kCsrLanes == 8 && (U == 2 || U == 4), "the exchange below");
+  constexpr int kMirror = 0x141, kSwap2 = 0x4E, kSwap1 = 0xB1;  // row_half_mirror, quad_perm [2, 3, 0, 1] and [1, 0, 3, 2]
+  float r[U];
+  const bool upper = gl >= 4;
+#pragma unroll
+  for (int k = 0; k < U / 2; ++k)
+    r[k] = (upper ? acc[k + U / 2] : acc[k]) + csr_lane_move<kMirror>(upper ? acc[k] : acc[k + U / 2]);
+  if (U == 4) {
+    const bool odd = (gl & 2u) != 0;
+    r[0] = (odd ? r[1] : r[0]) + csr_lane_move<kSwap2>(odd ? r[0] : r[1]);
+  } else {
+    r[0] += csr_lane_move<kSwap2>(r[0]);
+  }
+  return r[0] + csr_lane_move<kSwap1>(r[0]);
+}
 template <bool PAIRS>
 __global__ __launch_bounds__(kCsrThreads) void csr_z_kernel(const int32_t* const* __restrict__ cols,
                                                             const float* const* __restrict__ vals,
@@ -949,8 +1069,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_z_kernel(const int32_t* const
                                                             uint64_t d, uint32_t batch, uint32_t ntiles,
                                                             uint32_t tile_shift) {
   extern __shared__ float wtile[];  // w over the tile's columns
-  __shared__ __align__(16) int64_t sLo[kCsrRows];
-  __shared__ __align__(16) uint32_t sLen[kCsrRows];
+  __shared__ CsrSeg seg[kCsrRows];
   // workers vary fastest across the grid: the workgroups that run side by side share one tile of w
   const uint32_t m = blockIdx.x, t = blockIdx.y;
   const uint32_t T = 1u << tile_shift;
@@ -971,48 +1090,35 @@ __global__ __launch_bounds__(kCsrThreads) void csr_z_kernel(const int32_t* const
   }
   const CsrEntries<PAIRS> e(cols[m], vals[m]);
   const uint32_t group = threadIdx.x / kCsrLanes, gl = threadIdx.x % kCsrLanes;
+  const void* dummy = rowbase + (uint64_t)m * batch;
   for (uint32_t first = 0; first < batch; first += kCsrRows) {
-    const uint32_t count = min((uint32_t)kCsrRows, batch - first);
     __syncthreads();
-    csr_stage_segments(rowbase, bounds, m, batch, ntiles, t, first, count, sLo, sLen);
+    csr_stage_segments(e, rowbase, bounds, nullptr, m, batch, ntiles, t, first, seg);
     __syncthreads();
     const uint32_t j0 = group * kCsrUnroll;
-    CsrBatch b;
-    csr_load_batch(e, sLo, sLen, j0, count, gl, b);
-    float acc[kCsrUnroll];
-#pragma unroll
-    for (int u = 0; u < kCsrUnroll; ++u) {
-      acc[u] = gl < b.len[u] ? b.val[u] * wtile[(uint32_t)b.col[u] - (uint32_t)c0] : 0.f;
-      for (uint32_t k = gl + kCsrLanes; k < b.len[u]; k += kCsrLanes) {  // rare: segments longer than the lane group
-        int32_t ck;
-        float vk;
-        e.load(sLo[j0 + u] + k, ck, vk);
-        acc[u] = __builtin_fmaf(vk, wtile[(uint32_t)ck - (uint32_t)c0], acc[u]);
-      }
-    }
-    // 16 sums over 32 lanes by halving: after the four exchange steps lane l holds the partial sum
-    // of segment (bit4 bit3 bit2 bit1 of l) over the lanes that share those bits.
-    static_assert(kCsrUnroll == 16 && kCsrLanes == 32, "the exchange pattern below is for 16 sums over 32 lanes");
-    float r8[8], r4[4], r2[2];
-    const bool b4 = (gl & 16) != 0, b3 = (gl & 8) != 0, b2 = (gl & 4) != 0, b1 = (gl & 2) != 0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) r8[k] = (b4 ? acc[k + 8] : acc[k]) + __shfl_xor(b4 ? acc[k] : acc[k + 8], 16, kWave);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) r4[k] = (b3 ? r8[k + 4] : r8[k]) + __shfl_xor(b3 ? r8[k] : r8[k + 4], 8, kWave);
-#pragma unroll
-    for (int k = 0; k < 2; ++k) r2[k] = (b2 ? r4[k + 2] : r4[k]) + __shfl_xor(b2 ? r4[k] : r4[k + 2], 4, kWave);
-    float r1 = (b1 ? r2[1] : r2[0]) + __shfl_xor(b1 ? r2[0] : r2[1], 2, kWave);
-    r1 += __shfl_xor(r1, 1, kWave);
-    const uint32_t u = (b4 ? 8u : 0u) + (b3 ? 4u : 0u) + (b2 ? 2u : 0u) + (b1 ? 1u : 0u);
-    if ((gl & 1u) == 0u && j0 + u < count) zpart[first + j0 + u] = r1;
+    CsrBatch<kCsrUnroll, kCsrLoads> b;
+    csr_request(e, seg + j0, gl, dummy, b);
+    float acc[kCsrUnroll] = {};
+    csr_use(e, seg + j0, gl, dummy, b, [&](bool in, int32_t c, float v, int u) {
+      acc[u] = __builtin_fmaf(in ? v : 0.f, wtile[in ? (uint32_t)c - (uint32_t)c0 : 0u], acc[u]);
+    });
+    const float sum = csr_group_sums(acc, gl);
+    const uint32_t i = first + j0 + gl / (kCsrLanes / kCsrUnroll);
+    if (gl % (kCsrLanes / kCsrUnroll) == 0 && i < batch) zpart[i] = sum;
   }
 }
 
-// The same pass with two adjacent tiles of w (2^15 columns, 128 KiB) in LDS and two loads per lane and
+// Workgroup barrier that orders LDS traffic only: global loads and stores still in flight are not
+// waited for (__syncthreads would wait until every one of them has come back).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// The same pass with two adjacent tiles of w (2^15 columns, 128 KiB) in LDS and twice the lanes per
 // row: the row segments are twice as long, so fewer of the 128-byte memory lines they touch are
 // partial ones.  (Random contiguous segments deliver 2.2 TB/s of useful bytes at 64 bytes per
 // segment and 3.2 TB/s at 128; this pass is bound by exactly that.)  One partial sum per row and pair
 // of tiles: zparts[m][pair][i].
+constexpr int kCsrHalfUnroll = kCsrUnroll / 2;
+constexpr uint32_t kCsrHalf = kCsrRows / 2;  // rows of a trip taken at a time
 template <bool PAIRS>
 __global__ __launch_bounds__(kCsrThreads) void csr_z_wide_kernel(const int32_t* const* __restrict__ cols,
                                                                  const float* const* __restrict__ vals,
@@ -1023,8 +1129,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_z_wide_kernel(const int32_t* 
                                                                  uint32_t batch, uint32_t ntiles, uint32_t npairs,
                                                                  uint32_t M, uint32_t workers_per_block) {
   extern __shared__ float wtile[];  // w over the columns of both tiles
-  __shared__ __align__(16) int64_t sLoBuf[2][kCsrRows];  // segment starts and lengths, this step's and the next one's
-  __shared__ __align__(16) uint32_t sLenBuf[2][kCsrRows];
+  __shared__ CsrSeg seg[3][kCsrRows];  // of the last step, this one and the next one
   const uint32_t pair = tile_of_workgroup(blockIdx.x, npairs);
   const uint32_t t_lo = 2 * pair, t_hi = min(2 * pair + 2, ntiles);
   constexpr uint32_t T = 2u << kCsrTileShift;
@@ -1045,10 +1150,10 @@ __global__ __launch_bounds__(kCsrThreads) void csr_z_wide_kernel(const int32_t* 
     for (uint32_t j = threadIdx.x; j < T; j += kCsrThreads) wtile[j] = c0 + j < d ? w[c0 + j] : 0.f;
   }
   const uint32_t group = threadIdx.x / kCsrLanes, gl = threadIdx.x % kCsrLanes;
-  const uint32_t j0 = group * kCsrUnroll;
-  // The tiles of w serve several workers in turn.  A step is one trip of kCsrRows minibatch rows of one
-  // worker; the segment bounds of the next step are fetched while this step's entries are on their
-  // way (every thread fetches, the row index clamped, so that no load sits under a condition).
+  // The tiles of w serve several workers in turn.  A step is one trip of kCsrRows minibatch rows of one worker, taken in two
+  // halves that alternate: while the entries of one are worked on, those of the other are on their way.  The segment bounds
+  // of the next step are fetched during this one (every thread fetches, the row index clamped, so that no load sits
+  // under a condition).
   static_assert(kCsrThreads >= kCsrRows, "one thread per staged row");
   const uint32_t m_first = blockIdx.y * workers_per_block, m_last = min(m_first + workers_per_block, M);
   const uint32_t trips = (batch + kCsrRows - 1) / kCsrRows;
@@ -1059,74 +1164,47 @@ __global__ __launch_bounds__(kCsrThreads) void csr_z_wide_kernel(const int32_t* 
     const uint32_t* __restrict__ b = bounds + (uint64_t)m * (ntiles + 1) * batch;
     const uint32_t lo = b[(uint64_t)t_lo * batch + j], hi = b[(uint64_t)t_hi * batch + j];
     start = rowbase[(uint64_t)m * batch + j] + lo;
-    length = hi - lo;
+    length = first + threadIdx.x < batch ? hi - lo : 0u;
+  };
+  auto entries = [&](uint32_t step) { return CsrEntries<PAIRS>(cols[m_first + step / trips], vals[m_first + step / trips]); };
+  auto dummy = [&](uint32_t step) { return rowbase + (uint64_t)(m_first + step / trips) * batch; };
+  auto stage = [&](uint32_t step, uint32_t buf, int64_t start, uint32_t length) {
+    if (threadIdx.x < (uint32_t)kCsrRows) seg[buf][threadIdx.x] = csr_segment(entries(step), start, length, 0.f, dummy(step));
+  };
+  typedef CsrBatch<kCsrHalfUnroll, kCsrWideLoads> Half;
+  auto request = [&](uint32_t step, uint32_t buf, uint32_t half, Half& b) {
+    csr_request(entries(step), seg[buf] + half * kCsrHalf + group * kCsrHalfUnroll, gl, dummy(step), b);
+  };
+  auto dot = [&](uint32_t step, uint32_t buf, uint32_t half, const Half& b) {
+    const uint32_t j0 = half * kCsrHalf + group * kCsrHalfUnroll;
+    float acc[kCsrHalfUnroll] = {};
+    csr_use(entries(step), seg[buf] + j0, gl, dummy(step), b, [&](bool in, int32_t c, float v, int u) {
+      acc[u] = __builtin_fmaf(in ? v : 0.f, wtile[in ? (uint32_t)c - (uint32_t)c0 : 0u], acc[u]);
+    });
+    const float sum = csr_group_sums(acc, gl);
+    const uint32_t i = (step % trips) * kCsrRows + j0 + gl / (kCsrLanes / kCsrHalfUnroll);
+    if (gl % (kCsrLanes / kCsrHalfUnroll) == 0 && i < batch)
+      zparts[((uint64_t)(m_first + step / trips) * npairs + pair) * batch + i] = sum;
   };
   int64_t next_start;
   uint32_t next_len;
   fetch_bounds(0, next_start, next_len);
-  if (threadIdx.x < (uint32_t)kCsrRows) {
-    sLoBuf[0][threadIdx.x] = next_start;
-    sLenBuf[0][threadIdx.x] = next_len;
-  }
+  stage(0, 0, next_start, next_len);
+  __syncthreads();
+  Half a, b;
+  request(0, 0, 0, a);
+  uint32_t buf = 0;
   for (uint32_t step = 0; step < steps; ++step) {
-  {
-    const uint32_t m = m_first + step / trips, first = (step % trips) * kCsrRows;
-    float* __restrict__ zpart = zparts + ((uint64_t)m * npairs + pair) * batch;
-    const CsrEntries<PAIRS> e(cols[m], vals[m]);
-    const uint32_t count = min((uint32_t)kCsrRows, batch - first);
-    const int64_t* sLo = sLoBuf[step & 1];
-    const uint32_t* sLen = sLenBuf[step & 1];
-    __syncthreads();  // this step's bounds are in place, the other buffer is free
-    fetch_bounds(min(step + 1, steps - 1), next_start, next_len);
-    uint32_t len[kCsrUnroll];
-    int32_t col[kCsrUnroll][2];
-    float val[kCsrUnroll][2];
-#pragma unroll
-    for (int u = 0; u < kCsrUnroll; ++u) {  // all loads are issued before any is used
-      const uint32_t j = j0 + u;
-      len[u] = j < count ? sLen[j] : 0u;
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        col[u][q] = 0;
-        val[u][q] = 0.f;
-        if (gl + (uint32_t)q * kCsrLanes < len[u]) e.load(sLo[j] + gl + q * kCsrLanes, col[u][q], val[u][q]);
-      }
-    }
-    float acc[kCsrUnroll];
-#pragma unroll
-    for (int u = 0; u < kCsrUnroll; ++u) {
-      acc[u] = gl < len[u] ? val[u][0] * wtile[(uint32_t)col[u][0] - (uint32_t)c0] : 0.f;
-      if (gl + kCsrLanes < len[u]) acc[u] = __builtin_fmaf(val[u][1], wtile[(uint32_t)col[u][1] - (uint32_t)c0], acc[u]);
-    }
-#pragma unroll
-    for (int u = 0; u < kCsrUnroll; ++u) {
-      if (len[u] > 2u * kCsrLanes) {  // rare: longer than what the registers hold
-        const int64_t lo = sLo[j0 + u];
-        for (uint32_t k = gl + 2 * kCsrLanes; k < len[u]; k += kCsrLanes) {
-          int32_t ck;
-          float vk;
-          e.load(lo + k, ck, vk);
-          acc[u] = __builtin_fmaf(vk, wtile[(uint32_t)ck - (uint32_t)c0], acc[u]);
-        }
-      }
-    }
-    float r8[8], r4[4], r2[2];
-    const bool b4 = (gl & 16) != 0, b3 = (gl & 8) != 0, b2 = (gl & 4) != 0, b1 = (gl & 2) != 0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) r8[k] = (b4 ? acc[k + 8] : acc[k]) + __shfl_xor(b4 ? acc[k] : acc[k + 8], 16, kWave);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) r4[k] = (b3 ? r8[k + 4] : r8[k]) + __shfl_xor(b3 ? r8[k] : r8[k + 4], 8, kWave);
-#pragma unroll
-    for (int k = 0; k < 2; ++k) r2[k] = (b2 ? r4[k + 2] : r4[k]) + __shfl_xor(b2 ? r4[k] : r4[k + 2], 4, kWave);
-    float r1 = (b1 ? r2[1] : r2[0]) + __shfl_xor(b1 ? r2[0] : r2[1], 2, kWave);
-    r1 += __shfl_xor(r1, 1, kWave);
-    const uint32_t u = (b4 ? 8u : 0u) + (b3 ? 4u : 0u) + (b2 ? 2u : 0u) + (b1 ? 1u : 0u);
-    if ((gl & 1u) == 0u && j0 + u < count) zpart[first + j0 + u] = r1;
-    if (threadIdx.x < (uint32_t)kCsrRows) {
-      sLoBuf[(step + 1) & 1][threadIdx.x] = next_start;
-      sLenBuf[(step + 1) & 1][threadIdx.x] = next_len;
-    }
-  }
+    const uint32_t buf_next = buf == 2 ? 0 : buf + 1;
+    const uint32_t next = min(step + 1, steps - 1);  // past the last step its bounds again, of which nothing is made
+    fetch_bounds(next, next_start, next_len);
+    request(step, buf, 1, b);
+    dot(step, buf, 0, a);
+    stage(next, buf_next, next_start, next_len);
+    lds_barrier();  // the next step's bounds are in place
+    request(next, buf_next, 0, a);
+    dot(step, buf, 1, b);
+    buf = buf_next;
   }
 }
 
@@ -1196,9 +1274,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_kernel(const int32_t* co
                                                                uint64_t d, uint32_t batch, uint32_t ntiles,
                                                                uint32_t tile_shift, float l2, ScaleFusion fuse) {
   extern __shared__ double gtile[];  // g over the tile's columns, accumulated in fp64
-  __shared__ __align__(16) int64_t sLo[kCsrRows];
-  __shared__ __align__(16) uint32_t sLen[kCsrRows];
-  __shared__ float sR[kCsrRows];
+  __shared__ CsrSeg seg[kCsrRows];
   __shared__ float red[kCsrThreads / kWave];
   const uint32_t m = blockIdx.x, t = blockIdx.y;
   const uint32_t T = 1u << tile_shift;
@@ -1213,35 +1289,17 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_kernel(const int32_t* co
   }
   const CsrEntries<PAIRS> e(cols[m], vals[m]);
   const uint32_t group = threadIdx.x / kCsrLanes, gl = threadIdx.x % kCsrLanes;
+  const void* dummy = rowbase + (uint64_t)m * batch;
   for (uint32_t first = 0; first < batch; first += kCsrRows) {
-    const uint32_t count = min((uint32_t)kCsrRows, batch - first);
     __syncthreads();
-    csr_stage_segments(rowbase, bounds, m, batch, ntiles, t, first, count, sLo, sLen);
-    for (uint32_t j = threadIdx.x; j < count; j += kCsrThreads) sR[j] = resid[(uint64_t)m * batch + first + j];
+    csr_stage_segments(e, rowbase, bounds, resid, m, batch, ntiles, t, first, seg);
     __syncthreads();
     const uint32_t j0 = group * kCsrUnroll;
-    CsrBatch b;
-    csr_load_batch(e, sLo, sLen, j0, count, gl, b);
-    // LDS operations complete in order, so a read issued after an atomic add waits for it: the
-    // residuals are read before the first add and the adds go out back to back.
-    float r[kCsrUnroll];
-#pragma unroll
-    for (int u = 0; u < kCsrUnroll; ++u) r[u] = b.len[u] != 0 ? sR[j0 + u] : 0.f;
-#pragma unroll
-    for (int u = 0; u < kCsrUnroll; ++u)
-      if (gl < b.len[u]) atomicAdd(&gtile[(uint32_t)b.col[u] - (uint32_t)c0], (double)(r[u] * b.val[u]));
-#pragma unroll
-    for (int u = 0; u < kCsrUnroll; ++u) {
-      if (b.len[u] > (uint32_t)kCsrLanes) {  // rare: segments longer than the lane group
-        const int64_t lo = sLo[j0 + u];
-        for (uint32_t k = gl + kCsrLanes; k < b.len[u]; k += kCsrLanes) {
-          int32_t ck;
-          float vk;
-          e.load(lo + k, ck, vk);
-          atomicAdd(&gtile[(uint32_t)ck - (uint32_t)c0], (double)(r[u] * vk));
-        }
-      }
-    }
+    CsrBatch<kCsrUnroll, kCsrLoads> b;
+    csr_request(e, seg + j0, gl, dummy, b);
+    csr_use(e, seg + j0, gl, dummy, b, [&](bool in, int32_t c, float v, int u) {
+      if (in) atomicAdd(&gtile[(uint32_t)c - (uint32_t)c0], (double)(b.r[u] * v));
+    });
   }
   float* __restrict__ out = g + (uint64_t)m * d;
   if (FUSE) {
@@ -1282,10 +1340,6 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_kernel(const int32_t* co
   }
 }
 
-// Workgroup barrier that orders LDS traffic only: global loads and stores still in flight are not
-// waited for (__syncthreads would wait until every one of them has come back).
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // The gradient pass with the fused scale pass for the common case -- full tiles, no l2 term, at most
 // kCsrRows minibatch rows, 16-byte aligned rows of g -- as a software pipeline over a run of tiles of one
 // worker.  With one 128 KiB workgroup per compute unit nothing else hides a tile's chain of
@@ -1306,9 +1360,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_run_kernel(const int32_t
                                                                    float* __restrict__ g, uint64_t d, uint32_t batch,
                                                                    uint32_t ntiles, ScaleFusion fuse) {
   extern __shared__ double gtile[];  // g over the tile's columns, accumulated in fp64
-  __shared__ __align__(16) int64_t sLoBuf[2][kCsrRows];
-  __shared__ __align__(16) uint32_t sLenBuf[2][kCsrRows];
-  __shared__ float sR[kCsrRows];
+  __shared__ CsrSeg seg[2][kCsrRows];
   __shared__ float red[kCsrThreads / kWave];
   constexpr uint32_t T = 1u << kCsrTileShift;
   constexpr int kPer = (int)(T / (4 * kCsrThreads));
@@ -1324,39 +1376,22 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_run_kernel(const int32_t
   const uint32_t* __restrict__ b = bounds + (uint64_t)m * (ntiles + 1) * batch + row;
   const int64_t base = rowbase[(uint64_t)m * batch + row];
   const bool has_row = threadIdx.x < batch;
+  const float res = resid[(uint64_t)m * batch + row];
+  const CsrEntries<PAIRS> e(cols[m], vals[m]);
+  const void* dummy = rowbase + (uint64_t)m * batch;  // (the workspace goes on behind the last row's)
+  auto stage = [&](uint32_t buf, int64_t start, uint32_t len) {
+    if (threadIdx.x < (uint32_t)kCsrRows) seg[buf][threadIdx.x] = csr_segment(e, start, len, res, dummy);
+  };
   {
     const uint32_t lo = b[(uint64_t)t_first * batch], hi = b[(uint64_t)(t_first + 1) * batch];
     for (uint32_t j = threadIdx.x; j < T; j += kCsrThreads) gtile[j] = 0.0;
-    if (threadIdx.x < (uint32_t)kCsrRows) {
-      sR[threadIdx.x] = has_row ? resid[(uint64_t)m * batch + threadIdx.x] : 0.f;
-      sLoBuf[0][threadIdx.x] = base + lo;
-      sLenBuf[0][threadIdx.x] = has_row ? hi - lo : 0u;
-    }
+    stage(0, base + lo, has_row ? hi - lo : 0u);
   }
-  const CsrEntries<PAIRS> e(cols[m], vals[m]);
   const uint32_t group = threadIdx.x / kCsrLanes, gl = threadIdx.x % kCsrLanes;
   const uint32_t j0 = group * kCsrUnroll;
   float* __restrict__ out = g + (uint64_t)m * d;
-  int32_t ncol[kCsrUnroll];
-  float nval[kCsrUnroll];
-  uint32_t nmask = 0;  // bit u: this lane holds an entry of segment u
-  uint32_t nlong = 0;  // bit u: segment u is longer than the lane group
-  // The first lane-width of entries of the group's segments.  Lanes beyond a segment's length read a
-  // harmless valid address (the worker's first row start) instead of skipping the load: the compiler
-  // cannot count loads that sit under a condition, and would then make every later wait a wait for all.
-  const void* dummy = rowbase + (uint64_t)m * batch;
-  auto request = [&](uint32_t buf) {
-    nmask = 0;
-    nlong = 0;
-#pragma unroll
-    for (int u = 0; u < kCsrUnroll; ++u) {
-      const uint32_t len = sLenBuf[buf][j0 + u];
-      const bool on = gl < len;
-      e.load_or(on, sLoBuf[buf][j0 + u] + gl, dummy, ncol[u], nval[u]);
-      nmask |= on ? 1u << u : 0u;
-      nlong |= len > (uint32_t)kCsrLanes ? 1u << u : 0u;
-    }
-  };
+  CsrBatch<kCsrUnroll, kCsrLoads> next;
+  auto request = [&](uint32_t buf) { csr_request(e, seg[buf] + j0, gl, dummy, next); };
   auto store_maximum = [&](uint32_t t) {  // by thread 0, once red holds tile t's wavefront maxima
     float mx = red[0];
 #pragma unroll
@@ -1370,32 +1405,10 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_run_kernel(const int32_t
     const bool more = t + stride < ntiles;
     const uint32_t tn = more ? t + stride : t;
     const uint32_t nlo = b[(uint64_t)tn * batch], nhi = b[(uint64_t)(tn + 1) * batch];
-    // LDS operations complete in order: the residuals are read before the first add
-    float r[kCsrUnroll];
-#pragma unroll
-    for (int u = 0; u < kCsrUnroll; ++u) r[u] = sR[j0 + u];
-#pragma unroll
-    for (int u = 0; u < kCsrUnroll; ++u)
-      if ((nmask >> u) & 1u) atomicAdd(&gtile[(uint32_t)ncol[u] - (uint32_t)c0], (double)(r[u] * nval[u]));
-    if (nlong != 0) {  // rare: segments longer than the lane group
-#pragma unroll
-      for (int u = 0; u < kCsrUnroll; ++u) {
-        if ((nlong >> u) & 1u) {
-          const uint32_t len = sLenBuf[cur][j0 + u];
-          const int64_t lo = sLoBuf[cur][j0 + u];
-          for (uint32_t k = gl + kCsrLanes; k < len; k += kCsrLanes) {
-            int32_t ck;
-            float vk;
-            e.load(lo + k, ck, vk);
-            atomicAdd(&gtile[(uint32_t)ck - (uint32_t)c0], (double)(r[u] * vk));
-          }
-        }
-      }
-    }
-    if (threadIdx.x < (uint32_t)kCsrRows) {
-      sLoBuf[cur ^ 1u][threadIdx.x] = base + nlo;
-      sLenBuf[cur ^ 1u][threadIdx.x] = (has_row && more) ? nhi - nlo : 0u;
-    }
+    csr_use(e, seg[cur] + j0, gl, dummy, next, [&](bool in, int32_t c, float v, int u) {
+      if (in) atomicAdd(&gtile[(uint32_t)c - (uint32_t)c0], (double)(next.r[u] * v));
+    });
+    stage(cur ^ 1u, base + nlo, (has_row && more) ? nhi - nlo : 0u);
     lds_barrier();  // every add of tile t has been made; the segments of tile t+1 are staged
     if (t > t_first && threadIdx.x == 0) store_maximum(t - stride);  // older than the request below: need not be counted
     // the reference of the thread's columns for the fused scale pass, asked for ahead of the entries (loads
@@ -1453,9 +1466,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_workers_kernel(const int
                                                                        uint32_t ntiles, uint32_t M, uint32_t per_group,
                                                                        ScaleFusion fuse) {
   extern __shared__ double gtile[];  // g over the tile's columns, accumulated in fp64
-  __shared__ __align__(16) int64_t sLoBuf[2][kCsrRows];
-  __shared__ __align__(16) uint32_t sLenBuf[2][kCsrRows];
-  __shared__ float sRBuf[2][kCsrRows];
+  __shared__ CsrSeg seg[2][kCsrRows];
   __shared__ float red[2][kCsrThreads / kWave];  // by parity of the round: read in the round after it was written
   constexpr uint32_t T = 1u << kCsrTileShift;
   constexpr int kPer = (int)(T / (4 * kCsrThreads));
@@ -1473,16 +1484,16 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_workers_kernel(const int
   auto bounds_of = [&](uint32_t m) { return as_global(bounds + (uint64_t)m * per_worker); };
   auto rowbase_of = [&](uint32_t m) { return as_global(rowbase + (uint64_t)m * batch); };
   auto resid_of = [&](uint32_t m) { return as_global(resid + (uint64_t)m * batch); };
+  auto dummy_of = [&](uint32_t m) { return rowbase + (uint64_t)m * batch; };
+  auto stage = [&](const CsrEntries<PAIRS>& e, uint32_t m, uint32_t buf, int64_t start, uint32_t len, float r) {
+    if (threadIdx.x < (uint32_t)kCsrRows) seg[buf][threadIdx.x] = csr_segment(e, start, len, r, dummy_of(m));
+  };
   {
     const uint32_t lo = bounds_of(m_first)[tb_row], hi = bounds_of(m_first)[tb_row + batch];
     const int64_t base = rowbase_of(m_first)[row];
     const float res = resid_of(m_first)[row];
     for (uint32_t j = threadIdx.x; j < T; j += kCsrThreads) gtile[j] = 0.0;
-    if (threadIdx.x < (uint32_t)kCsrRows) {
-      sRBuf[0][threadIdx.x] = has_row ? res : 0.f;
-      sLoBuf[0][threadIdx.x] = base + lo;
-      sLenBuf[0][threadIdx.x] = has_row ? hi - lo : 0u;
-    }
+    stage(CsrEntries<PAIRS>(cols[m_first], vals[m_first]), m_first, 0, base + lo, has_row ? hi - lo : 0u, res);
   }
   // the reference of the thread's columns: the same for every worker
   float4 r1[kPer], r2[kPer];
@@ -1491,25 +1502,9 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_workers_kernel(const int
     load_refs4_t<NORM>(fuse, c0 / 4 + (uint32_t)k * kCsrThreads + threadIdx.x, r1[k], r2[k]);
   const uint32_t group = threadIdx.x / kCsrLanes, gl = threadIdx.x % kCsrLanes;
   const uint32_t j0 = group * kCsrUnroll;
-  int32_t ncol[kCsrUnroll];
-  float nval[kCsrUnroll];
-  uint32_t nmask = 0;  // bit u: this lane holds an entry of segment u
-  uint32_t nlong = 0;  // bit u: segment u is longer than the lane group
-  // entries of worker mr's segments staged in buffer buf; lanes beyond a segment read the worker's first
-  // row start instead (a load, never a branch)
-  auto request = [&](const CsrEntries<PAIRS>& e, uint32_t mr, uint32_t buf) {
-    const void* dummy = rowbase + (uint64_t)mr * batch;
-    nmask = 0;
-    nlong = 0;
-#pragma unroll
-    for (int u = 0; u < kCsrUnroll; ++u) {
-      const uint32_t len = sLenBuf[buf][j0 + u];
-      const bool on = gl < len;
-      e.load_or(on, sLoBuf[buf][j0 + u] + gl, dummy, ncol[u], nval[u]);
-      nmask |= on ? 1u << u : 0u;
-      nlong |= len > (uint32_t)kCsrLanes ? 1u << u : 0u;
-    }
-  };
+  CsrBatch<kCsrUnroll, kCsrLoads> next;
+  // entries of worker mr's segments staged in buffer buf
+  auto request = [&](const CsrEntries<PAIRS>& e, uint32_t mr, uint32_t buf) { csr_request(e, seg[buf] + j0, gl, dummy_of(mr), next); };
   auto store_maximum = [&](uint32_t m) {  // by thread 0, once red holds worker m's wavefront maxima
     const float* rm = red[(m - m_first) & 1u];
     float mx = rm[0];
@@ -1527,36 +1522,10 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_workers_kernel(const int
     const int64_t nbase = rowbase_of(mn)[row];
     const float nres = resid_of(mn)[row];
     const CsrEntries<PAIRS> e(cols[m], vals[m]), en(cols[mn], vals[mn]);
-    // LDS operations complete in order: the residuals are read before the first add
-    float r[kCsrUnroll];
-#pragma unroll
-    for (int u = 0; u < kCsrUnroll; ++u) r[u] = sRBuf[cur][j0 + u];
-#pragma unroll
-    for (int u = 0; u < kCsrUnroll; ++u) {
-      if ((nmask >> u) & 1u) atomicAdd(&gtile[(uint32_t)ncol[u] - (uint32_t)c0], (double)(r[u] * nval[u]));
-      // four adds at a time: all sixteen addresses and binary64 terms at once do not fit next to the reference
-      if (u % 4 == 3) asm volatile("" ::: "memory");
-    }
-    if (nlong != 0) {  // rare: segments longer than the lane group
-#pragma unroll
-      for (int u = 0; u < kCsrUnroll; ++u) {
-        if ((nlong >> u) & 1u) {
-          const uint32_t len = sLenBuf[cur][j0 + u];
-          const int64_t lo = sLoBuf[cur][j0 + u];
-          for (uint32_t k = gl + kCsrLanes; k < len; k += kCsrLanes) {
-            int32_t ck;
-            float vk;
-            e.load(lo + k, ck, vk);
-            atomicAdd(&gtile[(uint32_t)ck - (uint32_t)c0], (double)(r[u] * vk));
-          }
-        }
-      }
-    }
-    if (threadIdx.x < (uint32_t)kCsrRows) {
-      sRBuf[cur ^ 1u][threadIdx.x] = has_row ? nres : 0.f;
-      sLoBuf[cur ^ 1u][threadIdx.x] = nbase + nlo;
-      sLenBuf[cur ^ 1u][threadIdx.x] = (has_row && more) ? nhi - nlo : 0u;
-    }
+    csr_use(e, seg[cur] + j0, gl, dummy_of(m), next, [&](bool in, int32_t c, float v, int u) {
+      if (in) atomicAdd(&gtile[(uint32_t)c - (uint32_t)c0], (double)(next.r[u] * v));
+    });
+    stage(en, mn, cur ^ 1u, nbase + nlo, (has_row && more) ? nhi - nlo : 0u, nres);
     lds_barrier();  // every add of worker m has been made; the segments of worker m+1 are staged
     if (m > m_first && threadIdx.x == 0) store_maximum(m - 1);  // older than the request below: need not be counted
     request(en, mn, cur ^ 1u);  // before the stores below
@@ -1672,9 +1641,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_sub_kernel(const int32_t
                                                                    uint32_t tile_shift, uint32_t sub_shift, float l2,
                                                                    bool fused, ScaleFusion fuse) {
   extern __shared__ double gtile[];  // g over the workgroup's columns, accumulated in fp64
-  __shared__ __align__(16) int64_t sLo[kCsrRows];
-  __shared__ __align__(16) uint32_t sLen[kCsrRows];
-  __shared__ float sR[kCsrRows];
+  __shared__ CsrSeg seg[kCsrRows];
   __shared__ float red[kCsrThreads / kWave];
   const uint32_t m = blockIdx.y;
   const uint32_t T = 1u << sub_shift;
@@ -1683,37 +1650,18 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_sub_kernel(const int32_t
   for (uint32_t j = threadIdx.x; j < T; j += kCsrThreads) gtile[j] = 0.0;
   const CsrEntries<PAIRS> e(cols[m], vals[m]);
   const uint32_t group = threadIdx.x / kCsrLanes, gl = threadIdx.x % kCsrLanes;
-  auto add = [&](int32_t c, float v, float r) {
-    const uint32_t at = (uint32_t)c - c0;  // (columns left of c0 wrap to far beyond T)
-    if (at < T) atomicAdd(&gtile[at], (double)(r * v));
-  };
+  const void* dummy = rowbase + (uint64_t)m * batch;
   for (uint32_t first = 0; first < batch; first += kCsrRows) {
-    const uint32_t count = min((uint32_t)kCsrRows, batch - first);
     __syncthreads();
-    csr_stage_segments(rowbase, bounds, m, batch, ntiles, t, first, count, sLo, sLen);
-    for (uint32_t j = threadIdx.x; j < count; j += kCsrThreads) sR[j] = resid[(uint64_t)m * batch + first + j];
+    csr_stage_segments(e, rowbase, bounds, resid, m, batch, ntiles, t, first, seg);
     __syncthreads();
     const uint32_t j0 = group * kCsrUnroll;
-    CsrBatch b;
-    csr_load_batch(e, sLo, sLen, j0, count, gl, b);
-    float r[kCsrUnroll];
-#pragma unroll
-    for (int u = 0; u < kCsrUnroll; ++u) r[u] = b.len[u] != 0 ? sR[j0 + u] : 0.f;
-#pragma unroll
-    for (int u = 0; u < kCsrUnroll; ++u)
-      if (gl < b.len[u]) add(b.col[u], b.val[u], r[u]);
-#pragma unroll
-    for (int u = 0; u < kCsrUnroll; ++u) {
-      if (b.len[u] > (uint32_t)kCsrLanes) {  // segments longer than the lane group
-        const int64_t lo = sLo[j0 + u];
-        for (uint32_t k = gl + kCsrLanes; k < b.len[u]; k += kCsrLanes) {
-          int32_t ck;
-          float vk;
-          e.load(lo + k, ck, vk);
-          add(ck, vk, r[u]);
-        }
-      }
-    }
+    CsrBatch<kCsrUnroll, kCsrLoads> b;
+    csr_request(e, seg + j0, gl, dummy, b);
+    csr_use(e, seg + j0, gl, dummy, b, [&](bool in, int32_t c, float v, int u) {
+      const uint32_t at = (uint32_t)c - c0;  // (columns left of c0 wrap to far beyond T)
+      if (in && at < T) atomicAdd(&gtile[at], (double)(b.r[u] * v));
+    });
   }
   __syncthreads();
   float* __restrict__ out = g + (uint64_t)m * d;
