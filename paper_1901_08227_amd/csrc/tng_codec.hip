@@ -421,11 +421,7 @@ __device__ __forceinline__ void quantize_worker_tile(const QuantLane<NORM>& q, c
   for (int j = 0; j < kLoadsPerLane; ++j) {
     const U32x4 rnd = philox4x32_10((uint32_t)q.iv[j], m, iter, 0u, k0, k1);
     const float4 v = normalize4<NORM, RECIP>(x[j], q.rt[j], mu);
-    const uint32_t c0 = quantize_code<BITS>(v.x, inv_r, rnd.x);
-    const uint32_t c1 = quantize_code<BITS>(v.y, inv_r, rnd.y);
-    const uint32_t c2 = quantize_code<BITS>(v.z, inv_r, rnd.z);
-    const uint32_t c3 = quantize_code<BITS>(v.w, inv_r, rnd.w);
-    frag[j] = c0 | (c1 << BITS) | (c2 << (2 * BITS)) | (c3 << (3 * BITS));
+    frag[j] = quantize4<BITS>(v, inv_r, rnd);
   }
 }
 
@@ -1109,7 +1105,7 @@ __global__ __launch_bounds__(kBlock) void quantize_candidates_kernel(
           const uint32_t word = sel == 0u ? rnd.x : sel == 1u ? rnd.y : sel == 2u ? rnd.z : rnd.w;
           float r1 = 0.f;
           if (NORM == kNormSub) r1 = reinterpret_cast<const float*>(ref4)[coord];
-          code = quantize_code<2>(normalize_w<NORM>(g.base[(uint64_t)m * g.pitch + coord], r1, 1.f, 0.f), inv_r, word);
+          code = ternary_code(normalize_w<NORM>(g.base[(uint64_t)m * g.pitch + coord], r1, 1.f, 0.f), inv_r, word);
         }
         if (code != 0u) atomicOr(&lds.b32[slot][wave][pos >> 4], code << (2u * (pos & 15u)));
       };
@@ -1340,11 +1336,7 @@ __global__ __launch_bounds__(kBlock) void quantize_decode_kernel(
         if (R != 0.f) {
           const float inv_r = 1.0f / R, step = R / S;
           const U32x4 rnd = philox4x32_10((uint32_t)q, m, iter, 0u, k0, k1);
-          const uint32_t c0 = quantize_and_value<BITS>(v.x, inv_r, rnd.x, R, step, val.x);
-          const uint32_t c1 = quantize_and_value<BITS>(v.y, inv_r, rnd.y, R, step, val.y);
-          const uint32_t c2 = quantize_and_value<BITS>(v.z, inv_r, rnd.z, R, step, val.z);
-          const uint32_t c3 = quantize_and_value<BITS>(v.w, inv_r, rnd.w, R, step, val.w);
-          frag = c0 | (c1 << BITS) | (c2 << (2 * BITS)) | (c3 << (3 * BITS));
+          frag = quantize4_and_values<BITS>(v, inv_r, rnd, R, step, val);
         }
         if (BITS == 2)
           lds.b8[mm][wave][lane] = (uint8_t)frag;
@@ -1449,11 +1441,7 @@ __global__ __launch_bounds__(kBlock) void quantize_decode_split_kernel(
           const float inv_r = 1.0f / R;
           const U32x4 rnd = philox4x32_10((uint32_t)q, m, iter, 0u, k0, k1);
           const float4 v = normalize4<NORM, false>(x[i], rt, NORM == kNormMean ? means[m] : 0.f);
-          const uint32_t c0 = quantize_code<BITS>(v.x, inv_r, rnd.x);
-          const uint32_t c1 = quantize_code<BITS>(v.y, inv_r, rnd.y);
-          const uint32_t c2 = quantize_code<BITS>(v.z, inv_r, rnd.z);
-          const uint32_t c3 = quantize_code<BITS>(v.w, inv_r, rnd.w);
-          frag = c0 | (c1 << BITS) | (c2 << (2 * BITS)) | (c3 << (3 * BITS));
+          frag = quantize4<BITS>(v, inv_r, rnd);
         }
         if (BITS == 2)
           buf.b8[m][lane] = (uint8_t)frag;
@@ -1562,11 +1550,7 @@ __global__ __launch_bounds__(kBlock) void single_pass_kernel(
       if (active && R != 0.f) {
         const float inv_r = 1.0f / R;
         const U32x4 rnd = philox4x32_10((uint32_t)q, (uint32_t)mm, iter, 0u, k0, k1);
-        const uint32_t c0 = quantize_code<BITS>(normalize<NORM>(x[mm].x, rt.r1.x, rt.r2.x), inv_r, rnd.x);
-        const uint32_t c1 = quantize_code<BITS>(normalize<NORM>(x[mm].y, rt.r1.y, rt.r2.y), inv_r, rnd.y);
-        const uint32_t c2 = quantize_code<BITS>(normalize<NORM>(x[mm].z, rt.r1.z, rt.r2.z), inv_r, rnd.z);
-        const uint32_t c3 = quantize_code<BITS>(normalize<NORM>(x[mm].w, rt.r1.w, rt.r2.w), inv_r, rnd.w);
-        frag[mm] = c0 | (c1 << BITS) | (c2 << (2 * BITS)) | (c3 << (3 * BITS));
+        frag[mm] = quantize4<BITS>(normalize4<NORM, false>(x[mm], rt, 0.f), inv_r, rnd);
       }
       if (BITS == 2) {
         buf.b8[mm][threadIdx.x] = (uint8_t)frag[mm];

@@ -451,11 +451,7 @@ __global__ __launch_bounds__(kSmallThreads) void logreg_dense_small_finish_kerne
     constexpr float LEVELS = (float)((1 << (BITS - 1)) - 1);
     const float inv_r = 1.0f / R, step = R / LEVELS;
     const U32x4 rnd = philox4x32_10(q, m, iter, 0u, k0, k1);
-    const uint32_t c0 = quantize_and_value<BITS>(v.x, inv_r, rnd.x, R, step, val.x);
-    const uint32_t c1 = quantize_and_value<BITS>(v.y, inv_r, rnd.y, R, step, val.y);
-    const uint32_t c2 = quantize_and_value<BITS>(v.z, inv_r, rnd.z, R, step, val.z);
-    const uint32_t c3 = quantize_and_value<BITS>(v.w, inv_r, rnd.w, R, step, val.w);
-    const uint32_t frag = c0 | (c1 << BITS) | (c2 << (2 * BITS)) | (c3 << (3 * BITS));
+    const uint32_t frag = quantize4_and_values<BITS>(v, inv_r, rnd, R, step, val);
     if (BITS == 2)
       reinterpret_cast<lds_byte*>(packed + m * words)[q] = (uint8_t)frag;
     else
