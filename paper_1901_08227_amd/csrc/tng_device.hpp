@@ -73,6 +73,15 @@ __device__ __forceinline__ void store4_any(float* p, uint64_t i, const float4& x
   reinterpret_cast<v4f_u_t*>(p)[i] = v;
 }
 
+__device__ __forceinline__ void store4_stream_any(float* p, uint64_t i, const float4& x) {
+  v4f_u_t v;
+  v.x = x.x;
+  v.y = x.y;
+  v.z = x.z;
+  v.w = x.w;
+  __builtin_nontemporal_store(v, reinterpret_cast<v4f_u_t*>(p) + i);
+}
+
 // Elements e0 .. e0 + 3 as an ordinary (cached) load.
 __device__ __forceinline__ float4 load4_at(const float* p, uint64_t e0) {
   const v4f_u_t v = *reinterpret_cast<const v4f_u_t*>(p + e0);
@@ -139,6 +148,40 @@ __device__ __forceinline__ U32x4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_
     c2 = n2;
     k0 += 0x9E3779B9u;
     k1 += 0xBB67AE85u;
+  }
+  return U32x4{c0, c1, c2, c3};
+}
+
+// The same block in two parts, for kernels that draw it for several workers: c0 = block, c1 = worker, c2 = iter, c3 = 0.  The
+// worker enters the first round in one word that is the same for the whole wavefront and reaches the lane's own words in
+// the second, so what follows from the block alone is kept (16 bytes), and a worker's draw is 32 instructions instead of 38.
+struct PhiloxBlock {
+  uint32_t c3, c1, hi, lo;  // words 3 of round 1 and 1 of round 2, and the product of round 3
+};
+__device__ __forceinline__ PhiloxBlock philox_block(uint32_t block, uint32_t iter, uint32_t k0, uint32_t k1) {
+  constexpr uint32_t A = 0xD2511F53u, B = 0xCD9E8D57u;
+  const uint64_t pa = (uint64_t)A * block;
+  const uint64_t pb = (uint64_t)B * ((uint32_t)(pa >> 32) ^ k1);
+  const uint64_t pc = (uint64_t)A * xor3((uint32_t)(pb >> 32), (uint32_t)((uint64_t)B * iter), k0 + 0x9E3779B9u);
+  return PhiloxBlock{(uint32_t)pa, (uint32_t)pb, (uint32_t)(pc >> 32), (uint32_t)pc};
+}
+__device__ __forceinline__ U32x4 philox_draw(const PhiloxBlock& b, uint32_t worker, uint32_t iter, uint32_t k0, uint32_t k1) {
+  constexpr uint32_t A = 0xD2511F53u, B = 0xCD9E8D57u, KA = 0x9E3779B9u, KB = 0xBB67AE85u;
+  const uint64_t pw = (uint64_t)A * ((uint32_t)(((uint64_t)B * iter) >> 32) ^ worker ^ k0);  // the same for the wavefront
+  const uint64_t p3 = (uint64_t)B * (b.c3 ^ ((uint32_t)(pw >> 32) ^ (k1 + KB)));
+  k0 += 2u * KA;
+  k1 += 2u * KB;
+  uint32_t c0 = xor3((uint32_t)(p3 >> 32), b.c1, k0), c1 = (uint32_t)p3, c2 = b.hi ^ ((uint32_t)pw ^ k1), c3 = b.lo;
+#pragma unroll
+  for (int r = 3; r < 10; ++r) {
+    k0 += KA;
+    k1 += KB;
+    const uint64_t pa = (uint64_t)A * c0, pb = (uint64_t)B * c2;
+    const uint32_t n0 = xor3((uint32_t)(pb >> 32), c1, k0), n2 = xor3((uint32_t)(pa >> 32), c3, k1);
+    c1 = (uint32_t)pb;
+    c3 = (uint32_t)pa;
+    c0 = n0;
+    c2 = n2;
   }
   return U32x4{c0, c1, c2, c3};
 }
