@@ -47,9 +47,9 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
   return s;
 }
 
-// Maximum over the workgroup (any size up to 1024 threads); valid in thread 0.  red: 16 floats of LDS.
+// Maximum of non-negative values over the workgroup (any size up to 1024 threads); valid in thread 0.  red: 16 floats of LDS.
 __device__ __forceinline__ float block_max(float v, float* red) {
-  v = wave_max(v);
+  v = wave_max_nonneg(v);
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   __syncthreads();  // red may still be read from an earlier call
   if (lane == 0) red[wave] = v;
@@ -88,6 +88,15 @@ __device__ __forceinline__ void load_refs4_t(const ScaleFusion& f, uint64_t q, f
   r2 = make_float4(1.f, 1.f, 1.f, 1.f);
   if (NORM != kNormNone) r1 = reinterpret_cast<const float4*>(f.gref)[q];
   if (NORM == kNormComb) r2 = reinterpret_cast<const float4*>(f.gref2)[q];
+}
+
+// The same of elements e0 .. e0 + 3 of d; past the end such that a gradient of 0 normalises to 0.
+template <int NORM>
+__device__ __forceinline__ void load_refs4_end(const ScaleFusion& f, uint64_t e0, uint64_t d, float4& r1, float4& r2) {
+  r1 = make_float4(0.f, 0.f, 0.f, 0.f);
+  r2 = make_float4(1.f, 1.f, 1.f, 1.f);
+  if (NORM != kNormNone) r1 = load4_within(f.gref, e0, d, NORM == kNormQuot ? 1.f : 0.f);
+  if (NORM == kNormComb) r2 = load4_within(f.gref2, e0, d, 1.f);
 }
 
 template <int NORM>
@@ -1336,6 +1345,24 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_kernel(const int32_t* co
   }
 }
 
+// Where the pipelined kernels below keep column c of a tile (2^kCsrTileShift columns, from a multiple of that on): the four
+// columns of a thread's float4 as two pairs, the first pairs of all threads in the lower half of the tile, the second in
+// the upper, so that the lanes of a wavefront read and clear 16 bytes each next to one another (with the columns in order they
+// are 32 bytes apart and meet on half of the banks).
+__device__ __forceinline__ uint32_t csr_slot(uint32_t c) {
+  constexpr uint32_t T = 1u << kCsrTileShift;
+  return ((c >> 1) & (T / 2 - 2)) | (c & 1u) | ((c & 2u) * (T / 4));
+}
+// Columns 4 q .. 4 q + 3 of the tile, which are cleared.
+__device__ __forceinline__ float4 csr_take4(double* gtile, uint32_t q) {
+  typedef double v2d_t __attribute__((ext_vector_type(2)));
+  v2d_t* lower = reinterpret_cast<v2d_t*>(gtile) + q;
+  v2d_t* upper = lower + (1u << kCsrTileShift) / 4;
+  const v2d_t a = *lower, b = *upper;
+  *lower = *upper = v2d_t{0.0, 0.0};
+  return make_float4((float)a.x, (float)a.y, (float)b.x, (float)b.y);
+}
+
 // The gradient pass with the fused scale pass for the common case -- full tiles, no l2 term, at most
 // kCsrRows minibatch rows, 16-byte aligned rows of g -- as a software pipeline over a run of tiles of one
 // worker.  With one 128 KiB workgroup per compute unit nothing else hides a tile's chain of
@@ -1402,7 +1429,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_run_kernel(const int32_t
     const uint32_t tn = more ? t + stride : t;
     const uint32_t nlo = b[(uint64_t)tn * batch], nhi = b[(uint64_t)(tn + 1) * batch];
     csr_use(e, seg[cur] + j0, gl, dummy, next, [&](bool in, int32_t c, float v, int u) {
-      if (in) atomicAdd(&gtile[(uint32_t)c - (uint32_t)c0], (double)(next.r[u] * v));
+      if (in) atomicAdd(&gtile[csr_slot((uint32_t)c)], (double)(next.r[u] * v));
     });
     stage(cur ^ 1u, base + nlo, (has_row && more) ? nhi - nlo : 0u);
     lds_barrier();  // every add of tile t has been made; the segments of tile t+1 are staged
@@ -1420,9 +1447,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_run_kernel(const int32_t
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
       const uint32_t q = (uint32_t)k * kCsrThreads + threadIdx.x;
-      const float4 o = make_float4((float)gtile[4 * q], (float)gtile[4 * q + 1], (float)gtile[4 * q + 2],
-                                   (float)gtile[4 * q + 3]);
-      gtile[4 * q] = gtile[4 * q + 1] = gtile[4 * q + 2] = gtile[4 * q + 3] = 0.0;
+      const float4 o = csr_take4(gtile, q);
       store_stream(out4 + q, o);
       amax = fmaxf(amax, absmax4_t<NORM>(fuse, o, r1[k], r2[k]));
     }
@@ -1452,7 +1477,11 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_run_kernel(const int32_t
 // in a kernel bound by how fast a compute unit issues them; gradient pass 2.34 -> 2.13 ms at d = 2^24).
 // Workgroups that run side by side are on adjacent tiles of the same worker, so the memory lines shared
 // by the end of one tile's row segment and the start of the next tile's are still fetched once.
-template <bool PAIRS, int NORM>
+// FULL: d is a multiple of the tile; else rows of g start at any 4-byte boundary and the last tile reaches past their end.
+// (Iterations with the tile's columns in csr_slot's order and every length of rows here, at 0.1 % density, B = 512: d = 2^24, M =
+// 32 2158 -> 1941 us with the entries two to a lane; d = 2^24 - 5, which took a workgroup per tile and worker and a scale pass
+// before, 2890 -> 2065; d = 5000001, M = 16 483 -> 370; d = 1000003, M = 8 75 -> 61.)
+template <bool PAIRS, int NORM, bool FULL>
 __global__ __launch_bounds__(kCsrThreads) void csr_grad_workers_kernel(const int32_t* const* __restrict__ cols,
                                                                        const float* const* __restrict__ vals,
                                                                        const int64_t* __restrict__ rowbase,
@@ -1470,6 +1499,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_workers_kernel(const int
   const uint32_t m_first = blockIdx.y * per_group;
   const uint32_t m_end = min(m_first + per_group, M);
   const uint64_t c0 = (uint64_t)t << kCsrTileShift;
+  const bool whole = FULL || c0 + T <= d;
   const uint32_t row = min(threadIdx.x, batch - 1);  // every thread fetches its row's data: no load under a condition
   const bool has_row = threadIdx.x < batch;
   // Per-worker arrays are addressed as (wavefront-uniform start of the worker's part) + (the thread's 32-bit
@@ -1495,7 +1525,10 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_workers_kernel(const int
   float4 r1[kPer], r2[kPer];
 #pragma unroll
   for (int k = 0; k < kPer; ++k)
-    load_refs4_t<NORM>(fuse, c0 / 4 + (uint32_t)k * kCsrThreads + threadIdx.x, r1[k], r2[k]);
+    if (whole)
+      load_refs4_t<NORM>(fuse, c0 / 4 + (uint32_t)k * kCsrThreads + threadIdx.x, r1[k], r2[k]);
+    else
+      load_refs4_end<NORM>(fuse, c0 + 4 * ((uint32_t)k * kCsrThreads + threadIdx.x), d, r1[k], r2[k]);
   const uint32_t group = threadIdx.x / kCsrLanes, gl = threadIdx.x % kCsrLanes;
   const uint32_t j0 = group * kCsrUnroll;
   CsrBatch<kCsrUnroll, kCsrLoads> next;
@@ -1519,21 +1552,25 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_workers_kernel(const int
     const float nres = resid_of(mn)[row];
     const CsrEntries<PAIRS> e(cols[m], vals[m]), en(cols[mn], vals[mn]);
     csr_use(e, seg[cur] + j0, gl, dummy_of(m), next, [&](bool in, int32_t c, float v, int u) {
-      if (in) atomicAdd(&gtile[(uint32_t)c - (uint32_t)c0], (double)(next.r[u] * v));
+      if (in) atomicAdd(&gtile[csr_slot((uint32_t)c)], (double)(next.r[u] * v));
     });
     stage(en, mn, cur ^ 1u, nbase + nlo, (has_row && more) ? nhi - nlo : 0u, nres);
     lds_barrier();  // every add of worker m has been made; the segments of worker m+1 are staged
     if (m > m_first && threadIdx.x == 0) store_maximum(m - 1);  // older than the request below: need not be counted
     request(en, mn, cur ^ 1u);  // before the stores below
-    float4* __restrict__ out4 = reinterpret_cast<float4*>(g + (uint64_t)m * d + c0);
+    float* __restrict__ out = g + (uint64_t)m * d + c0;
+    float4* __restrict__ out4 = reinterpret_cast<float4*>(out);
     float amax = 0.f;
 #pragma unroll
     for (int k = 0; k < kPer; ++k) {
       const uint32_t q = (uint32_t)k * kCsrThreads + threadIdx.x;
-      const float4 o = make_float4((float)gtile[4 * q], (float)gtile[4 * q + 1], (float)gtile[4 * q + 2],
-                                   (float)gtile[4 * q + 3]);
-      gtile[4 * q] = gtile[4 * q + 1] = gtile[4 * q + 2] = gtile[4 * q + 3] = 0.0;
-      store_stream(out4 + q, o);
+      const float4 o = csr_take4(gtile, q);
+      if (FULL)
+        store_stream(out4 + q, o);
+      else if (whole)
+        store4_stream_any(out, q, o);
+      else
+        store4_within(out, 4 * q, d - c0, o);
       amax = fmaxf(amax, absmax4_t<NORM>(fuse, o, r1[k], r2[k]));
     }
     amax = wave_max_nonneg(amax);
@@ -2122,20 +2159,22 @@ hipError_t csr_grad_launches(const LogregData& p, uint64_t d, uint32_t M, uint32
     std::lock_guard<std::mutex> attr_lock(attr_mutex);
     if (!attr_done[dev]) {
       const int lds_double = (int)(sizeof(double) << kCsrTileShift);
-      const void* big_lds[] = {reinterpret_cast<const void*>(csr_grad_kernel<false, PAIRS>),
+      const void* big_lds[] = {reinterpret_cast<const void*>(csr_z_wide_kernel<PAIRS>),
+                               reinterpret_cast<const void*>(csr_grad_kernel<false, PAIRS>),
                                reinterpret_cast<const void*>(csr_grad_kernel<true, PAIRS>),
                                reinterpret_cast<const void*>(csr_grad_run_kernel<PAIRS, kNormNone>),
                                reinterpret_cast<const void*>(csr_grad_run_kernel<PAIRS, kNormSub>),
                                reinterpret_cast<const void*>(csr_grad_run_kernel<PAIRS, kNormQuot>),
                                reinterpret_cast<const void*>(csr_grad_run_kernel<PAIRS, kNormComb>),
-                               reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormNone>),
-                               reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormSub>),
-                               reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormQuot>),
-                               reinterpret_cast<const void*>(csr_z_wide_kernel<PAIRS>)};
-      const int bytes[] = {lds_double, lds_double, lds_double, lds_double, lds_double, lds_double, lds_double,
-                           lds_double, lds_double, (int)(2 * sizeof(float) << kCsrTileShift)};
-      for (int k = 0; k < 10; ++k) {
-        const hipError_t e = hipFuncSetAttribute(big_lds[k], hipFuncAttributeMaxDynamicSharedMemorySize, bytes[k]);
+                               reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormNone, true>),
+                               reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormSub, true>),
+                               reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormQuot, true>),
+                               reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormNone, false>),
+                               reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormSub, false>),
+                               reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormQuot, false>)};
+      static_assert(2 * sizeof(float) == sizeof(double), "two tiles of w are as large as one of g");
+      for (const void* kernel : big_lds) {
+        const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds_double);
         if (e != hipSuccess) return e;
       }
       attr_done[dev] = true;
@@ -2164,19 +2203,22 @@ hipError_t csr_grad_launches(const LogregData& p, uint64_t d, uint32_t M, uint32
   hipLaunchKernelGGL(csr_z_reduce_kernel, dim3((batch + kReduceRows - 1) / kReduceRows, M), dim3(kBlock), 0, s, zpart, p.y, idx,
                      z, batch, nparts, inv_b);
   // The scale pass rides along when every tile is a full one and the write-out is the plain one.
-  if (fuse != nullptr && fused_rows != nullptr && shift == kCsrTileShift && d % (1ull << kCsrTileShift) == 0 &&
+  const bool full = d % (1ull << kCsrTileShift) == 0;
+  // (the combined form keeps two references per column: they do not fit next to the pipeline's registers)
+  const bool by_workers = fuse != nullptr && batch <= (uint32_t)kCsrRows && M >= 2 && fuse->norm != kNormComb;
+  if (fuse != nullptr && fused_rows != nullptr && shift == kCsrTileShift && (full || by_workers) &&
       l2 == 0.f && ntiles <= kAbsmaxMaxBlocks && aligned16(g) && aligned16(fuse->gref) && aligned16(fuse->gref2)) {
-    // (the combined form keeps two references per column: they do not fit next to the pipeline's registers)
-    if (batch <= (uint32_t)kCsrRows && M >= 2 && fuse->norm != kNormComb) {
+    if (by_workers) {
       // a workgroup per tile and group of workers: groups as long as 1024 workgroups (four per compute unit)
       // remain -- per iteration at d = 2^24, 64 workers: 4.69 ms with groups of 8, 4.61 with 16, 4.57 with
       // 32, 4.54 with all 64 (4.76 with the kernel that runs over tiles)
       uint32_t per_group = 64;
       while (per_group > 2 && (uint64_t)ntiles * ((M + per_group - 1) / per_group) < 1024) per_group /= 2;
       const dim3 grid(ntiles, (M + per_group - 1) / per_group);
-#define TNG_WORKERS(NORM)                                                                                              \
-  hipLaunchKernelGGL((csr_grad_workers_kernel<PAIRS, NORM>), grid, dim3(kCsrThreads), lds_g, s, p.col, p.val, rowbase, \
-                     bounds, z, g, d, batch, ntiles, M, per_group, *fuse)
+#define TNG_WORKERS(NORM)                                                                                                \
+  hipLaunchKernelGGL((full ? csr_grad_workers_kernel<PAIRS, NORM, true> : csr_grad_workers_kernel<PAIRS, NORM, false>), \
+                     grid, dim3(kCsrThreads), lds_g, s, p.col, p.val, rowbase, bounds, z, g, d, batch, ntiles, M,       \
+                     per_group, *fuse)
       switch (fuse->norm) {
         case kNormSub: TNG_WORKERS(kNormSub); break;
         case kNormQuot: TNG_WORKERS(kNormQuot); break;
