@@ -254,9 +254,8 @@ tng_status quantize_impl(tng_ctx* ctx, uint32_t iter, const float* g, const floa
 
 tng_status encode_impl(tng_ctx* ctx, uint32_t iter, const float* g, const float* gref, uint32_t* codes,
                        float* scales, uint32_t fused_rows = 0) {
-  if (fused_rows == 0 && single_pass_ok(ctx, g, gref, nullptr, nullptr, nullptr))  // tiny problems: one launch
-    return hip_status(tng::launch_single_pass(ctx->shape, iter, g, gref, ctx->gref2, scales, codes, false, nullptr,
-                                              nullptr, 0.f, nullptr, ctx->stream));
+  if (fused_rows == 0 && ctx->prof_slots == 0 && tng::encode_row_applies(ctx->shape))  // short rows: one launch
+    return hip_status(tng::launch_encode_row(ctx->shape, iter, g, gref, ctx->gref2, scales, codes, ctx->stream));
   const uint64_t call = ctx->enc_calls++;
   uint32_t rows = 0;
   bool by_candidates = false;
@@ -683,8 +682,8 @@ tng_status tng_step(tng_ctx* ctx, uint32_t iter, float* w, float* gref, float* g
     if (s != TNG_OK) return s;
   }
   if (fused_rows == 0 && single_pass_ok(ctx, g, gref, vbar, w, ref_out)) {  // tiny problems: scales and the rest in one launch
-    s = hip_status(tng::launch_single_pass(ctx->shape, iter, g, gref, ctx->gref2, scales, codes, true, vbar, w, c.lr,
-                                           ref_out, ctx->stream));
+    s = hip_status(tng::launch_single_pass(ctx->shape, iter, g, gref, ctx->gref2, scales, codes, vbar, w, c.lr, ref_out,
+                                           ctx->stream));
     if (s != TNG_OK) return s;
   } else if (ctx->prof_slots == 0 && tng::quantize_decode_applies(ctx->shape, fused_rows > 0)) {
     uint32_t rows = 0;

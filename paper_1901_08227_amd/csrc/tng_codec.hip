@@ -1479,8 +1479,8 @@ __global__ __launch_bounds__(kBlock) void quantize_decode_split_kernel(
 }
 
 // ------------------------------------------------------------------------------------------
-// One workgroup for tiny problems (d <= 4 * kBlock): scale, quantise and pack, and (DECODE) the
-// server side as well, in one launch.
+// One workgroup for tiny problems (d <= 4 * kBlock): scale, quantise and pack, and the server side as
+// well, in one launch.
 //
 // A thread owns one float4 of coordinates of every worker (M <= MC rows in registers), so once the
 // M scales are known -- a workgroup reduction -- it can code its values, and since it then holds all
@@ -1495,7 +1495,7 @@ __global__ __launch_bounds__(kBlock) void quantize_decode_split_kernel(
 // ------------------------------------------------------------------------------------------
 constexpr int kSinglePassMaxWorkers = 16;
 
-template <int NORM, int BITS, int MC, bool DECODE>
+template <int NORM, int BITS, int MC>
 __global__ __launch_bounds__(kBlock) void single_pass_kernel(
     GradRows g, const float4* ref4, const float4* __restrict__ ref24, float* __restrict__ scales,
     uint32_t* __restrict__ codes, uint64_t nvec, uint64_t words, uint32_t M, float eps, uint32_t k0, uint32_t k1,
@@ -1573,7 +1573,7 @@ __global__ __launch_bounds__(kBlock) void single_pass_kernel(
     if (wi < words) store_word_through(codes + (uint64_t)mm * words + wi, buf.b32[mm][j]);
   }
 
-  if (DECODE && active) {
+  if (active) {
     float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int mm = 0; mm < MC; ++mm) {
@@ -1592,17 +1592,92 @@ __global__ __launch_bounds__(kBlock) void single_pass_kernel(
     o.z = denormalize<NORM>(acc.z * inv_m, rt.r1.z, rt.r2.z);
     o.w = denormalize<NORM>(acc.w * inv_m, rt.r1.w, rt.r2.w);
     store_stream(vbar4 + q, o);
-    if (w4 != nullptr) {
-      float4 w = load_stream(w4 + q);
-      const float px = lr * o.x, py = lr * o.y, pz = lr * o.z, pw = lr * o.w;
-      w.x = w.x - px;
-      w.y = w.y - py;
-      w.z = w.z - pz;
-      w.w = w.w - pw;
-      w4[q] = w;
-    }
+    float4 w = load_stream(w4 + q);
+    const float px = lr * o.x, py = lr * o.y, pz = lr * o.z, pw = lr * o.w;
+    w.x = w.x - px;
+    w.y = w.y - py;
+    w.z = w.z - pz;
+    w.w = w.w - pw;
+    w4[q] = w;
     if (refout4 != nullptr) refout4[q] = o;
   }
+}
+
+// ------------------------------------------------------------------------------------------
+// Short rows: scale, quantise and pack in one launch.  A workgroup codes kRowTile elements of one worker, and takes the
+// maximum of the worker's whole row by itself, out of the L2: at these lengths that is less than a launch between two passes
+// costs.
+// ------------------------------------------------------------------------------------------
+constexpr int kRowThreads = 1024;
+constexpr uint32_t kRowTile = 4 * kRowThreads;
+
+template <int NORM, int BITS>
+__global__ __launch_bounds__(kRowThreads) void encode_row_kernel(GradRows g, const float4* __restrict__ ref4,
+                                                                 const float4* __restrict__ ref24,
+                                                                 float* __restrict__ scales, uint32_t* __restrict__ codes,
+                                                                 uint32_t d, uint32_t words, float eps, uint32_t k0,
+                                                                 uint32_t k1, uint32_t iter) {
+  constexpr uint32_t kWords = kRowTile * BITS / 32;  // packed words per workgroup
+  constexpr int U = 4;
+  __shared__ float red[kRowThreads / kWave];
+  __shared__ union {
+    lds_u8 b8[kRowThreads];
+    lds_u16 b16[kRowThreads];
+    lds_u32 b32[kWords];
+  } buf;
+  const uint32_t m = blockIdx.y, t = threadIdx.x;
+  const uint32_t q = blockIdx.x * kRowThreads + t;  // the thread's float4
+  const uint32_t whole = d / 4;
+  RefTile<NORM> rt;
+  float4 x;
+  if (q < whole) {
+    rt.template load<false>(ref4, ref24, q, eps);
+    const v4f_u_t v = g.row(m)[q];
+    x = make_float4(v.x, v.y, v.z, v.w);
+  } else {  // at or past the end of the row
+    rt.load_ragged(ref4, ref24, q, d, eps);
+    x = load_row_ragged(g, m, q, d, 0.f);
+  }
+  float4 v = normalize4<NORM, false>(x, rt, 0.f);
+  float amax = max3_abs(v.z, v.w, max3_abs(v.x, v.y, 0.f));
+  if (gridDim.x > 1) {  // the other tiles' elements (and these again: no harm to a maximum)
+    for (uint32_t i0 = t; i0 < whole; i0 += U * kRowThreads) {
+      float4 xo[U];
+      RefTile<NORM> ro[U];
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const uint32_t i = min(i0 + (uint32_t)k * kRowThreads, whole - 1);
+        const v4f_u_t e = g.row(m)[i];
+        xo[k] = make_float4(e.x, e.y, e.z, e.w);
+        ro[k].template load<false>(ref4, ref24, i, eps);
+      }
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const float4 n = normalize4<NORM, false>(xo[k], ro[k], 0.f);
+        amax = max3_abs(n.z, n.w, max3_abs(n.x, n.y, amax));
+      }
+    }
+    const uint32_t e = 4 * whole + t;
+    if (e < d) {
+      float r1, r2;
+      load_ref_scalar<NORM>(reinterpret_cast<const float*>(ref4), reinterpret_cast<const float*>(ref24), e, eps, r1, r2);
+      amax = fmaxf(amax, fabsf(normalize<NORM>(g.base[(uint64_t)m * g.pitch + e], r1, r2)));
+    }
+  }
+  amax = wave_max_nonneg(amax);
+  if (t % kWave == 0) red[t / kWave] = amax;
+  __syncthreads();
+  amax = wave_max_nonneg(red[t % (kRowThreads / kWave)]);
+  const float R = amax < FLT_MIN ? 0.f : amax;
+  if (blockIdx.x == 0 && t == 0) scales[m] = R;
+  const uint32_t frag = quantize4<BITS>(v, R != 0.f ? 1.0f / R : 0.f, philox4x32_10(q, m, iter, 0u, k0, k1));
+  if (BITS == 2)
+    buf.b8[t] = (uint8_t)frag;
+  else
+    buf.b16[t] = (uint16_t)frag;
+  __syncthreads();
+  const uint32_t at = blockIdx.x * kWords + t;
+  if (t < kWords && at < words) store_word_through(codes + (uint64_t)m * words + at, buf.b32[t]);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2607,24 +2682,17 @@ hipError_t launch_quantize_decode(const CodecShape& c, uint32_t iter, const floa
 namespace {
 template <int NORM, int BITS>
 hipError_t single_pass_dispatch(const CodecShape& c, uint32_t iter, const float* g, const float* gref,
-                                const float* gref2, float* scales, uint32_t* codes, bool decode, float* vbar,
-                                float* w, float lr, float* ref_out, hipStream_t s) {
-#define TNG_SP(MC, DEC)                                                                                             \
-  hipLaunchKernelGGL((single_pass_kernel<NORM, BITS, MC, DEC>), dim3(1), dim3(kBlock), 0, s, GradRows{g, c.d},       \
+                                const float* gref2, float* scales, uint32_t* codes, float* vbar, float* w, float lr,
+                                float* ref_out, hipStream_t s) {
+#define TNG_SP(MC)                                                                                                  \
+  hipLaunchKernelGGL((single_pass_kernel<NORM, BITS, MC>), dim3(1), dim3(kBlock), 0, s, GradRows{g, c.d},       \
                      reinterpret_cast<const float4*>(gref), reinterpret_cast<const float4*>(gref2), scales, codes,   \
                      c.d / 4, c.words, c.M, c.eps, c.k0, c.k1, iter, reinterpret_cast<float4*>(vbar),                \
                      reinterpret_cast<float4*>(w), reinterpret_cast<float4*>(ref_out), 1.0f / (float)c.M, lr)
-  if (c.M <= 8) {
-    if (decode) {
-      TNG_SP(8, true);
-    } else {
-      TNG_SP(8, false);
-    }
-  } else if (decode) {
-    TNG_SP(16, true);
-  } else {
-    TNG_SP(16, false);
-  }
+  if (c.M <= 8)
+    TNG_SP(8);
+  else
+    TNG_SP(16);
 #undef TNG_SP
   return hipGetLastError();
 }
@@ -2638,12 +2706,12 @@ bool single_pass_applies(const CodecShape& c, const float* g, const float* gref,
 }
 
 hipError_t launch_single_pass(const CodecShape& c, uint32_t iter, const float* g, const float* gref, const float* gref2,
-                              float* scales, uint32_t* codes, bool decode, float* vbar, float* w, float lr,
-                              float* ref_out, hipStream_t s) {
+                              float* scales, uint32_t* codes, float* vbar, float* w, float lr, float* ref_out,
+                              hipStream_t s) {
   if (!single_pass_applies(c, g, gref, gref2, vbar, w, ref_out)) return hipErrorInvalidValue;
 #define TNG_SPD(NORM, R1, R2)                                                                                        \
-  return c.bits == 2 ? single_pass_dispatch<NORM, 2>(c, iter, g, R1, R2, scales, codes, decode, vbar, w, lr, ref_out, s) \
-                     : single_pass_dispatch<NORM, 4>(c, iter, g, R1, R2, scales, codes, decode, vbar, w, lr, ref_out, s)
+  return c.bits == 2 ? single_pass_dispatch<NORM, 2>(c, iter, g, R1, R2, scales, codes, vbar, w, lr, ref_out, s) \
+                     : single_pass_dispatch<NORM, 4>(c, iter, g, R1, R2, scales, codes, vbar, w, lr, ref_out, s)
   switch (c.norm) {
     case kNormNone: TNG_SPD(kNormNone, nullptr, nullptr);
     case kNormSub: TNG_SPD(kNormSub, gref, nullptr);
@@ -2651,6 +2719,37 @@ hipError_t launch_single_pass(const CodecShape& c, uint32_t iter, const float* g
     default: TNG_SPD(kNormComb, gref, gref2);
   }
 #undef TNG_SPD
+}
+
+// Rows of one tile, any number of them; longer rows while the workgroups, each of which reads its whole row, are one round of
+// the compute units, up to 2^16 elements, half as many where each is divided by a reference.  Encode + decode, two passes
+// against this one: d = 1000, M = 64 17.7 -> 14.5 us; d = 4096, M = 8 12.6 -> 10.0; d = 25000, M = 4, 4-bit 12.7 -> 10.2; d =
+// 25001, M = 7, quotient 12.7 -> 10.1; d = 65536, M = 8 12.5 -> 10.3; d = 32768, M = 8, combined form 12.8 -> 11.0, M = 32 12.8
+// -> 12.5; beyond the line d = 65536, M = 32 (512 workgroups) 13.4 -> 21.0, d = 131072, M = 8 12.7 -> 16.3.
+constexpr uint64_t kRowMax = 1u << 16;
+constexpr uint64_t kRowGroups = 256;
+bool encode_row_applies(const CodecShape& c) {
+  if (c.norm == kNormMean || c.scale_l2) return false;
+  if (c.d <= kRowTile) return true;
+  const bool divides = c.norm == kNormQuot || c.norm == kNormComb;
+  return c.d <= (divides ? kRowMax / 2 : kRowMax) && (c.d + kRowTile - 1) / kRowTile * c.M <= kRowGroups;
+}
+
+hipError_t launch_encode_row(const CodecShape& c, uint32_t iter, const float* g, const float* gref, const float* gref2,
+                             float* scales, uint32_t* codes, hipStream_t s) {
+  const dim3 grid((uint32_t)((c.d + kRowTile - 1) / kRowTile), c.M);
+#define TNG_ROW(NORM)                                                                                                        \
+  hipLaunchKernelGGL((c.bits == 2 ? encode_row_kernel<NORM, 2> : encode_row_kernel<NORM, 4>), grid, dim3(kRowThreads), 0, s, \
+                     GradRows{g, c.d}, reinterpret_cast<const float4*>(gref), reinterpret_cast<const float4*>(gref2),        \
+                     scales, codes, (uint32_t)c.d, (uint32_t)c.words, c.eps, c.k0, c.k1, iter)
+  switch (c.norm) {
+    case kNormNone: TNG_ROW(kNormNone); break;
+    case kNormSub: TNG_ROW(kNormSub); break;
+    case kNormQuot: TNG_ROW(kNormQuot); break;
+    default: TNG_ROW(kNormComb); break;
+  }
+#undef TNG_ROW
+  return hipGetLastError();
 }
 
 hipError_t launch_decode(const CodecShape& c, const uint32_t* codes, const float* scales, const float* gref,

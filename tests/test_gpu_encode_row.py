@@ -1,0 +1,37 @@
+"""Short rows, scaled, quantised and packed in one launch: at the edges of a workgroup's tile, of a row and of the rule, against
+the oracle; rows start at any 4-byte boundary, the largest element is put into the first, the last and a middle tile."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import tng_oracle as O
+from gpu_util import DEV, make_ctx, oracle_cfg, u32
+from paper_1901_08227_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,M", [(1, 3), (3, 2), (5, 300), (4095, 3), (4096, 2), (4097, 5), (8191, 2), (25001, 7), (32768, 2),
+                                 (32769, 3), (65535, 2), (65536, 16), (65537, 2), (20000, 52)])
+@pytest.mark.parametrize("bits,norm", [(2, B.NORM_SUB), (4, B.NORM_QUOT), (4, B.NORM_NONE), (2, B.NORM_COMB)])
+def test_encode_of_short_rows(d, M, bits, norm):
+    gen = torch.Generator(device=DEV).manual_seed(d + M)
+    g = torch.randn((M, d), device=DEV, generator=gen)
+    gref = 0.5 * torch.randn(d, device=DEV, generator=gen)
+    gref2 = torch.rand(d, device=DEV, generator=gen) + 0.5
+    for m, e in enumerate((0, d - 1, d // 2)):
+        if m < M:
+            g[m, e] = 50.0
+    if M > 3:
+        g[3] = gref if norm == B.NORM_SUB else 0.0  # a row whose scale is 0
+    ctx = make_ctx(d, M, bits, norm, seed=d)
+    if norm == B.NORM_COMB:
+        ctx.set_second_reference(gref2)
+    codes = torch.full((M, ctx.words), -1, dtype=torch.int32, device=DEV)
+    scales = torch.full((M,), -1.0, device=DEV)
+    ctx.normalize_encode(9, g, gref, codes, scales)
+    torch.cuda.synchronize()
+    c, s = O.normalize_encode(oracle_cfg(ctx), 9, g.cpu().numpy(), gref.cpu().numpy(), gref2.cpu().numpy())
+    assert np.array_equal(scales.cpu().numpy(), s)
+    assert np.array_equal(u32(codes), c)
+    ctx.close()
