@@ -1253,11 +1253,16 @@ __global__ __launch_bounds__(kBlock) void decode_vec_kernel(
 // d = 2^18, M = 8 16.6 -> 9.6; d = 2^20, M = 8 24.4 -> 24.5; d = 4e6, M = 8 82.6 -> 70.8; d = 2^24, M = 64, 4-bit
 // 1792 -> 1673.
 // The scales come from the partial maxima of the scale pass (partials[rows][M], reduced by every workgroup for
-// itself: rows * M <= kTailPartials floats, a few KiB out of the L2) or, rows == 0, from scales.
+// itself: rows * M floats out of the L2) or, rows == 0, from scales.  32 KiB of them cost a workgroup less than the
+// launch that would reduce them once (about 4 us) up to 1024 workgroups of the kernel below; beyond those 8 KiB do
+// (kTailPartialsLong).  Iterations, own launch / here: Rosenbrock, d = 2^20, M = 8 26.2 / 25.2 us, M = 7 23.1 / 22.8; given
+// gradients, d = 2^20, M = 8 22.6 / 20.8, M = 16, 4-bit 34.5 / 33.2; d = 2^18, M = 64 29.6 / 28.5; d = 4e6, M = 8 67.8 / 68.4, d =
+// 2^22, M = 8, quotient 72.6 / 73.4.
 // ------------------------------------------------------------------------------------------
 constexpr int kTailWorkers = 8;
 constexpr uint32_t kTailMaxWorkers = 64;
-constexpr uint32_t kTailPartials = 2048;
+constexpr uint32_t kTailPartials = 8192, kTailPartialsLong = 2048;
+constexpr uint32_t kTailFewPartials = 1024;  // up to here single loads: at a few hundred the exchange between lanes costs 0.5 us
 
 // What the coder needs of a worker: its scale R, 1 / R and R / S, and its mean.  Of R = 0 all are 0, under which every element
 // codes to level 0.  Made once per workgroup: the two divisions by every lane for every worker were a seventh of the kernel's
@@ -1275,12 +1280,48 @@ __device__ __forceinline__ void tail_workers(TailWorker* sWorker, float* scales,
   if (rows != 0) {
     if (threadIdx.x < M) top[threadIdx.x] = 0u;
     __syncthreads();
-    const uint32_t used = kBlock / M * M;  // a thread stays with one worker
-    if (threadIdx.x < used) {
-      float v = 0.f;
-#pragma unroll 8
-      for (uint32_t i = threadIdx.x; i < rows * M; i += used) v = fmaxf(v, partials[i]);
-      atomicMax(&top[threadIdx.x % M], __float_as_uint(v < FLT_MIN ? 0.f : v));
+    const uint32_t n = rows * M;
+    if (n > kTailFewPartials && (M & (M - 1)) == 0 && n % 4 == 0) {  // all of a thread's float4 belong to the same four workers
+      static_assert(kTailFewPartials >= 4 * kBlock, "every thread has a float4");
+      const uint32_t n4 = n / 4, last = (n4 - 1 - threadIdx.x) / kBlock;
+      const float4* p = reinterpret_cast<const float4*>(partials) + threadIdx.x;
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (uint32_t k0 = 0; k0 * kBlock < n4; k0 += 4) {  // (eight at a time: a wavefront less per SIMD, by registers)
+        float4 x[4];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) x[k] = p[min(k0 + k, last) * kBlock];  // past the end the last one again
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k)
+          v = make_float4(fmaxf(v.x, x[k].x), fmaxf(v.y, x[k].y), fmaxf(v.z, x[k].z), fmaxf(v.w, x[k].w));
+      }
+      const uint32_t apart = max(M / 4, 4u);  // lanes that far apart hold the same workers: few are left to meet in LDS
+      for (uint32_t off = kWave / 2; off >= apart; off /= 2) {
+        v.x = fmaxf(v.x, __shfl_xor(v.x, (int)off));
+        v.y = fmaxf(v.y, __shfl_xor(v.y, (int)off));
+        v.z = fmaxf(v.z, __shfl_xor(v.z, (int)off));
+        v.w = fmaxf(v.w, __shfl_xor(v.w, (int)off));
+      }
+      if (threadIdx.x % kWave < apart) {
+        const float vv[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (uint32_t c = 0; c < 4; ++c)
+          atomicMax(&top[(4 * threadIdx.x + c) % M], __float_as_uint(vv[c] < FLT_MIN ? 0.f : vv[c]));
+      }
+    } else {
+      const uint32_t used = kBlock / M * M;  // a thread stays with one worker
+      if (threadIdx.x < min(used, n)) {
+        float v = 0.f;
+        const uint32_t last = (n - 1 - threadIdx.x) / used;
+        const float* p = partials + threadIdx.x;
+        for (uint32_t k0 = 0; k0 <= last; k0 += 8) {
+          float x[8];
+#pragma unroll
+          for (uint32_t k = 0; k < 8; ++k) x[k] = p[min(k0 + k, last) * used];
+#pragma unroll
+          for (uint32_t k = 0; k < 8; ++k) v = fmaxf(v, x[k]);
+        }
+        atomicMax(&top[threadIdx.x % M], __float_as_uint(v < FLT_MIN ? 0.f : v));
+      }
     }
     __syncthreads();
   }
@@ -2653,7 +2694,9 @@ bool quantize_decode_applies(const CodecShape& c, bool maxima_left) {
   return c.M > 2 || c.d <= (1u << 20);
 }
 
-uint32_t quantize_decode_rows(const CodecShape& c) { return kTailPartials / c.M; }
+uint32_t quantize_decode_rows(const CodecShape& c) {
+  return (c.d <= (1u << 20) ? kTailPartials : kTailPartialsLong) / c.M;
+}
 
 hipError_t launch_quantize_decode(const CodecShape& c, uint32_t iter, const float* g, const float* gref,
                                   const float* gref2, float* scales, uint32_t* codes, const float* partials,

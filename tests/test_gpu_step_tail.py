@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from oracle import tng_oracle as O
-from gpu_util import DEV, buffers, make_ctx, oracle_cfg, u32
+from gpu_util import DEV, buffers, make_ctx, oracle_cfg, oracle_step_threaded, u32
 from paper_1901_08227_amd import binding as B
 from test_gpu_codec import _inputs
 
@@ -39,3 +39,27 @@ def test_step_equals_the_oracle(d, M):
         for name, a, b in zip(("iterate", "reference", "codes", "scales", "average"), got, want):
             assert np.array_equal(a, b), f"d={d} M={M} norm={norm} scale={scale} bits={bits}: {name}"
         ctx.close()
+
+
+# Partial maxima (about d / 4096 rows of M) on both sides of where they are fetched as float4 (1024, workers a power of two)
+# and of where a launch of their own reduces them (8192 up to d = 2^20, then 2048).
+@pytest.mark.parametrize("d,M", [(1 << 18, 16), ((1 << 18) + 1024, 16), (70001, 64), (1 << 20, 4), ((1 << 20) + 5, 4), ((1 << 17) + 1, 64),
+                                 (1 << 20, 13), ((1 << 20) + 1, 13), (1 << 20, 32), (400003, 12), (1 << 22, 2), ((1 << 21) + 4, 4)])
+def test_step_scales_from_many_partial_maxima(d, M):
+    rng = torch.Generator().manual_seed(d + M)
+    g = torch.randn(M, d, generator=rng) * 0.01
+    at = torch.randint(0, d, (M,), generator=rng)
+    at[0], at[M - 1] = d - 1, 0
+    g[torch.arange(M), at] = torch.linspace(-3.0, 4.0, M) + 0.125  # a worker's largest element: one partial maximum has it
+    gref = torch.randn(d, generator=rng) * 0.01
+    print(f"partial maxima d={d} M={M}", flush=True)
+    ctx = make_ctx(d, M, 2, B.NORM_SUB, seed=d, lr=0.05, ref_period=1, problem=B.PROB_EXTERNAL)
+    buf = buffers(ctx)
+    w, gr, gd = torch.linspace(-1.0, 1.0, d, device=DEV), gref.to(DEV), g.to(DEV)
+    want = oracle_step_threaded(oracle_cfg(ctx), 3, w.cpu().numpy(), gref.numpy(), g.numpy())
+    ctx.step(3, w, gr, gd, buf["codes"], buf["scales"], buf["vbar"])
+    torch.cuda.synchronize()
+    got = (w.cpu().numpy(), gr.cpu().numpy(), u32(buf["codes"]), buf["scales"].cpu().numpy(), buf["vbar"].cpu().numpy())
+    for name, a, b in zip(("iterate", "reference", "codes", "scales", "average"), got, want):
+        assert np.array_equal(a, b), f"d={d} M={M}: {name}"
+    ctx.close()
