@@ -487,186 +487,170 @@ __global__ __launch_bounds__(kSmallThreads) void logreg_dense_small_finish_kerne
   }
 }
 
-// One pass over the minibatch rows for wide dense problems (4096 <= d / 4 <= 16384 float4 columns): a
-// workgroup takes whole rows, one at a time, and KEEPS the row on chip between the two uses it has -- the
-// dot product z = x . w, and, once sigma(z) - y is known, the accumulation r x into the workgroup's
-// partial gradient -- so that X_B is read from memory once instead of twice (the separate residual and
-// accumulation passes each stream it at 6.2 TB/s, which is all the memory system gives; re-reading a
-// block right after it was read, out of the 256 MB last-level cache, measured no faster than HBM).
-// A row of up to 256 KiB fits neither store alone: each of the 512 threads (one workgroup per compute
-// unit, so 256 registers per thread) parks NL = min(NV, 16) float4 of the row in LDS (128 KiB per
-// workgroup; a thread reads back only what it wrote) and holds the other NV - NL in registers, next to its
-// NV float4 of partial gradient.  The LDS half is loaded from memory straight into LDS, so that the whole
-// row is requested at once.
-// The workgroups of a worker split its minibatch rows; their partial gradients go to scratch
-// parts[m][s][d] and logreg_dense_parts_kernel adds them in workgroup order.
-constexpr int kRowsThreads = 512;
-constexpr int kRowsWaves = kRowsThreads / kWave;
-// 16 bytes per lane from memory straight into LDS: lane l of the wavefront writes the l-th 16 bytes behind
-// dst, which is the same for the whole wavefront; counted by vmcnt like any load.  Non-temporal (policy bit
-// 2): the row is read once.  (The builtin exists in the device pass only.)
-constexpr int kRowsStagger = 55;  // s_sleep units of 64 clocks: about 1.7 microseconds
-typedef __attribute__((address_space(3))) void* LdsPtr;
-__device__ __forceinline__ void load16_to_lds(GlobalPtr<v4f_t> src, LdsPtr dst) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 2);
-#endif
+// ------------------------------------------------------------------------------------------
+// Dense problems of up to 32 K columns: the rows are read once here too.  A workgroup takes several of its worker's
+// minibatch rows at a time, all their loads in flight together, and holds them in registers, NV float4 columns a thread, from
+// the dot products to the accumulation into its partial gradient; w and the partial gradient stay in registers as well.
+// logreg_dense_mid_parts_kernel adds the S partial gradients of a worker (parts[m][s][ceil(d / 4)] float4).
+// Bound by memory where the rows are many (d = 16000, M = 32, B = 512: 1 GiB of rows in an iteration of 174 us, 6.4 TB/s in this
+// kernel) and by latency where a workgroup has one trip.  Iterations, the residual and the accumulation pass (rows read
+// twice) / this: d = 10007, M = 8, B = 128 26.6 / 24.0 us, M = 32, B = 512 231 / 122; d = 16000, M = 32, B = 512 324 / 174;
+// d = 5003, M = 16, B = 512 70.9 / 44.6; d = 2048, M = 32, B = 256 34.1 / 24.1; d = 1000, M = 32, B = 512 42.3 / 26.9; d = 300,
+// M = 20, B = 64 16.5 / 14.6.
+// Up to 4 float4 columns a thread two workgroups share a compute unit (128 registers), one fetching while the other
+// computes; beyond, one with twice the registers and four rows at a time is faster (d = 10007, M = 8, B = 128 24.0, two of three
+// rows each 26.7; d = 16000, M = 16, B = 512 95.8, two of one row 106).  Beyond 16 K columns the workgroup has 1024 threads and
+// takes one or two rows.  There, and at 16 K, rows went through LDS and registers one at a time, or twice through memory
+// where d was no multiple of 4: d = 32768, M = 16, B = 512 223 / 178, d = 32765 355 / 184, d = 20000, M = 16, B = 200 94.8 / 60.2,
+// d = 16384, M = 16, B = 512 136 / 98; their partial gradients were a chain of up to 256 loads, d = 32768, M = 1, B = 512 146 / 32.4.
+// ------------------------------------------------------------------------------------------
+constexpr int kMidThreads = 512, kMidThreadsLong = 1024;
+constexpr uint64_t kMidMostColumns = 16 * 1024;  // for kMidThreads: 8 float4 a thread
+constexpr int dense_mid_rows(int t, int nv) {    // rows at a time
+  return t == kMidThreadsLong ? (nv <= 5 ? 2 : 1) : nv <= 2 ? 8 : 4;
 }
-constexpr int kRowsLds = 16;  // float4 per thread kept in LDS
-template <int NV, bool FULL>
-__global__ __launch_bounds__(kRowsThreads) void logreg_dense_rows_kernel(const float* const* __restrict__ Xs,
-                                                                         const float* const* __restrict__ ys,
-                                                                         const uint64_t* __restrict__ n_rows,
-                                                                         uint32_t* __restrict__ idx,
-                                                                         const float* __restrict__ w,
-                                                                         float* __restrict__ parts, uint64_t d,
-                                                                         uint32_t batch, uint32_t k0, uint32_t k1,
-                                                                         uint32_t iter) {
-  constexpr int NL = NV < kRowsLds ? NV : kRowsLds;
-  constexpr int NR = NV - NL;
-  constexpr int TR = 4;                // float4 of the LDS half read back at a time when the row is added
-  constexpr int TW = NV < 8 ? NV : 8;  // float4 of w on their way at a time
-  static_assert(NL % TR == 0 && NL % TW == 0 && NR % TW == 0, "both halves are worked through in whole batches");
-  constexpr int kWaitVmem = 0x0F70;         // s_waitcnt vmcnt(0)
-  constexpr int kWaitLds = 0xC07F;          // s_waitcnt lgkmcnt(0)
-  extern __shared__ float4 rowl[];  // [NL][kRowsThreads]
-  __shared__ float red[2][kRowsWaves];
+constexpr int dense_mid_per_unit(int t, int nv) { return t != kMidThreadsLong && nv <= 4 ? 2 : 1; }  // workgroups per compute unit
+inline int dense_mid_threads(uint64_t d) { return d <= 4 * kBlock ? kBlock : d <= kMidMostColumns ? kMidThreads : kMidThreadsLong; }
+inline int dense_mid_columns(uint64_t d) {
+  const uint64_t t = (uint64_t)dense_mid_threads(d);
+  return (int)(((d + 3) / 4 + t - 1) / t);
+}
+template <int T, int NV>
+__global__ __launch_bounds__(T, T / 256 * dense_mid_per_unit(T, NV)) void logreg_dense_mid_kernel(const float* const* __restrict__ Xs,
+                                                                const float* const* __restrict__ ys,
+                                                                const uint64_t* __restrict__ n_rows,
+                                                                uint32_t* __restrict__ idx, const float* __restrict__ w,
+                                                                float4* __restrict__ parts, uint32_t d, uint32_t batch,
+                                                                uint32_t k0, uint32_t k1, uint32_t iter) {
+  constexpr int R = dense_mid_rows(T, NV);
+  __shared__ float red[2][R][T / kWave];
   const uint32_t m = blockIdx.y, s = blockIdx.x, S = gridDim.x, t = threadIdx.x;
-  const uint32_t wave_first = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t / kWave)) * kWave;  // a scalar
-  const uint32_t nvec = (uint32_t)(d / 4);
-  const GlobalPtr<float> X = as_global(Xs[m]);
-  const GlobalPtr<float> y = as_global(ys[m]);
+  const uint32_t nvec = (d + 3) / 4;
+  const GlobalPtr<float> X = as_global(Xs[m]), y = as_global(ys[m]);
   const uint64_t n = n_rows[m];
-  const float4* __restrict__ w4 = reinterpret_cast<const float4*>(w);
-  // float4 column k of the thread: LDS half first (k < NL), register half after; clamped so that every load
-  // is unconditional (FULL: d / 4 = NV * 512, nothing to clamp or mask)
-  // (the thread index goes through an opaque copy per use site: otherwise the compiler computes all NV
-  // column addresses of x and of w once, ahead of the row loop, and keeps them in 3 NV registers)
-  auto opaque_t = [&]() {
-    uint32_t v = t;
-    asm volatile("" : "+v"(v));
-    return v;
-  };
-  auto column_of = [&](uint32_t tt, int k) {
-    return FULL ? tt + (uint32_t)k * kRowsThreads : min(tt + (uint32_t)k * kRowsThreads, nvec - 1);
-  };
-  auto column = [&](int k) { return column_of(t, k); };
-  auto live = [&](int k) { return FULL || t + (uint32_t)k * kRowsThreads < nvec; };
-  const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
-  float4 acc[NV];
+  // All float4 but the last of a thread lie inside the row ((NV - 1) T < ceil(d / 4) <= NV T); the last may repeat columns of its
+  // neighbour's, and idle threads fetch the row's last columns.
+  const uint32_t q_last = t + (uint32_t)(NV - 1) * T;
+  const uint32_t c_first = 4 * t, c_last = (uint32_t)first_column(min(q_last, nvec - 1), d);
+  const uint32_t repeated = q_last < nvec ? 4 * q_last - c_last : 4u;  // of its four columns: they count once in the dot product
+  auto columns = [&](auto row, int k) { return k < NV - 1 ? row + 4 * k * T + c_first : row + c_last; };
+  float4 wv[NV], acc[NV];
 #pragma unroll
-  for (int k = 0; k < NV; ++k) acc[k] = zero4;
-  // A row is fetched (memory busy, arithmetic idle) and then worked on (the reverse), and workgroups that start
-  // together stay in step: every compute unit fetches at once and the memory system idles while all of them
-  // compute.  A quarter of the workgroups therefore starts at once and the others 1.7, 3.4 and 5.1 microseconds
-  // later (about the length of the arithmetic on a row), so that the fetches of some fall into the arithmetic of
-  // the others.  Measured at d = 2^16, M = 16, B = 256: iteration 0.236 -> 0.224 ms, this kernel 200
-  // microseconds (with twice the delay 0.230 ms; with eight steps of 0.7 microseconds 204 microseconds).
-  for (uint32_t q = (blockIdx.x + blockIdx.y * gridDim.x) % 4u; q > 0; --q) __builtin_amdgcn_s_sleep(kRowsStagger);
-  uint32_t parity = 0;
-  for (uint32_t i = s; i < batch; i += S, parity ^= 1u) {
-    const uint32_t row = minibatch_row(k0, k1, iter, m, i, n);
-    if (t == 0) idx[(uint64_t)m * batch + i] = row;
-    const GlobalPtr<float> x = X + (uint64_t)row * d;
-    // Requests of a row, in the order in which they come back: the first batch of w (out of the caches), the
-    // register half, then the LDS half, which goes from memory straight into LDS (16 bytes per lane, lane l of
-    // a wavefront to the l-th float4 behind the wavefront's address: each thread's own slot) -- so the whole
-    // row, 256 KiB at d = 2^16, is in flight at once and no register carries the LDS half.
-    float4 wa[TW];
-    {
-      const uint32_t tt = opaque_t();
-#pragma unroll
-      for (int k = 0; k < TW; ++k) wa[k] = w4[column_of(tt, k)];
-    }
-    float4 xr[NR > 0 ? NR : 1];
-    {
-      const uint32_t tt = opaque_t();
-#pragma unroll
-      for (int k = 0; k < NR; ++k) xr[k] = load4_stream(x, column_of(tt, NL + k));
-    }
-    {
-      const uint32_t tt = opaque_t();
-#pragma unroll
-      for (int k = 0; k < NL; ++k)
-        load16_to_lds(reinterpret_cast<GlobalPtr<v4f_t>>(x) + column_of(tt, k),
-                      (LdsPtr)(rowl + k * kRowsThreads + wave_first));
-    }
-    __builtin_amdgcn_s_waitcnt(kWaitVmem);  // everything requested above has arrived, the LDS half in LDS
-    asm volatile("" ::: "memory");
-    float z0 = 0.f, z1 = 0.f, z2 = 0.f, z3 = 0.f;
-#pragma unroll
-    for (int k0b = 0; k0b < NL; k0b += TW) {
-      if (k0b > 0) {
-        const uint32_t tt = opaque_t();
-#pragma unroll
-        for (int k = 0; k < TW; ++k) wa[k] = w4[column_of(tt, k0b + k)];
-      }
-      const uint32_t tt = opaque_t();
-#pragma unroll
-      for (int k = 0; k < TW; ++k) {
-        const float4 xl = rowl[(k0b + k) * kRowsThreads + tt];
-        const float4 xv = live(k0b + k) ? xl : zero4;
-        z0 = __builtin_fmaf(xv.x, wa[k].x, z0);
-        z1 = __builtin_fmaf(xv.y, wa[k].y, z1);
-        z2 = __builtin_fmaf(xv.z, wa[k].z, z2);
-        z3 = __builtin_fmaf(xv.w, wa[k].w, z3);
-      }
-      asm volatile("" ::: "memory");  // keeps the next batch's loads behind this batch's use: registers are the scarce thing here
-    }
-#pragma unroll
-    for (int k0b = 0; k0b < NR; k0b += TW) {
-      const uint32_t tt = opaque_t();
-#pragma unroll
-      for (int k = 0; k < TW; ++k) wa[k] = w4[column_of(tt, NL + k0b + k)];
-#pragma unroll
-      for (int k = 0; k < TW; ++k) {
-        if (!live(NL + k0b + k)) xr[k0b + k] = zero4;
-        z0 = __builtin_fmaf(xr[k0b + k].x, wa[k].x, z0);
-        z1 = __builtin_fmaf(xr[k0b + k].y, wa[k].y, z1);
-        z2 = __builtin_fmaf(xr[k0b + k].z, wa[k].z, z2);
-        z3 = __builtin_fmaf(xr[k0b + k].w, wa[k].w, z3);
-      }
-      asm volatile("" ::: "memory");
-    }
-    // z over the workgroup (two sets of slots alternate, so that one barrier per row is enough)
-    const float zw = wave_sum((z0 + z1) + (z2 + z3));
-    if (t % kWave == 0) red[parity][t / kWave] = zw;
-    __syncthreads();
-    float z = red[parity][0];
-#pragma unroll
-    for (int k = 1; k < kRowsWaves; ++k) z += red[parity][k];
-    const float r = logistic_residual(z, y[row]);
-#pragma unroll
-    for (int k = 0; k < NR; ++k) {
-      acc[NL + k].x = __builtin_fmaf(r, xr[k].x, acc[NL + k].x);
-      acc[NL + k].y = __builtin_fmaf(r, xr[k].y, acc[NL + k].y);
-      acc[NL + k].z = __builtin_fmaf(r, xr[k].z, acc[NL + k].z);
-      acc[NL + k].w = __builtin_fmaf(r, xr[k].w, acc[NL + k].w);
-    }
-#pragma unroll
-    for (int k0b = 0; k0b < NL; k0b += TR) {
-      const uint32_t tt = opaque_t();
-#pragma unroll
-      for (int k = k0b; k < k0b + TR; ++k) {
-        const float4 xl = rowl[k * kRowsThreads + tt];
-        const float4 xv = live(k) ? xl : zero4;
-        acc[k].x = __builtin_fmaf(r, xv.x, acc[k].x);
-        acc[k].y = __builtin_fmaf(r, xv.y, acc[k].y);
-        acc[k].z = __builtin_fmaf(r, xv.z, acc[k].z);
-        acc[k].w = __builtin_fmaf(r, xv.w, acc[k].w);
-      }
-      asm volatile("" ::: "memory");
-    }
-    __builtin_amdgcn_s_waitcnt(kWaitLds);  // this row's LDS reads are done before the next row's loads write there
-    asm volatile("" ::: "memory");
+  for (int k = 0; k < NV; ++k) {
+    wv[k] = load4_at(columns(w, k), 0);
+    acc[k] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
-  float4* __restrict__ out = reinterpret_cast<float4*>(parts + ((uint64_t)m * S + s) * d);
+  if (repeated > 0) wv[NV - 1].x = 0.f;
+  if (repeated > 1) wv[NV - 1].y = 0.f;
+  if (repeated > 2) wv[NV - 1].z = 0.f;
+  if (repeated > 3) wv[NV - 1].w = 0.f;
+  uint32_t parity = 0;
+  for (uint32_t i0 = s; i0 < batch; i0 += S * R, parity ^= 1u) {
+    // lane r draws row r of the trip; a short last trip fetches its first row in place of those that it lacks
+    const uint32_t mine = i0 + (t % kWave % R) * S;
+    const uint32_t drawn = minibatch_row(k0, k1, iter, m, mine < batch ? mine : i0, n);
+    if (t < (uint32_t)R && mine < batch) idx[(uint64_t)m * batch + mine] = drawn;
+    const float label = y[drawn];
+    float4 x[R][NV];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const GlobalPtr<float> row = X + (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)drawn, r) * d;
+#pragma unroll
+      for (int k = 0; k < NV; ++k) x[r][k] = load4_stream_any(columns(row, k), 0);
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      float z0 = 0.f, z1 = 0.f, z2 = 0.f, z3 = 0.f;
+#pragma unroll
+      for (int k = 0; k < NV; ++k) {
+        z0 = __builtin_fmaf(x[r][k].x, wv[k].x, z0);
+        z1 = __builtin_fmaf(x[r][k].y, wv[k].y, z1);
+        z2 = __builtin_fmaf(x[r][k].z, wv[k].z, z2);
+        z3 = __builtin_fmaf(x[r][k].w, wv[k].w, z3);
+      }
+      const float z = wave_sum_uniform((z0 + z1) + (z2 + z3));
+      if (t % kWave == 0) red[parity][r][t / kWave] = z;
+    }
+    __syncthreads();  // (two sets of slots alternate: one barrier per trip is enough)
+    // lane r of every wavefront makes the residual of row r
+    float z = red[parity][t % kWave % R][0];
+#pragma unroll
+    for (int k = 1; k < T / kWave; ++k) z += red[parity][t % kWave % R][k];
+    const float residual = logistic_residual(z, label);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      if (i0 + (uint32_t)r * S >= batch) break;
+      const float res = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(residual), r));
+#pragma unroll
+      for (int k = 0; k < NV; ++k) {
+        acc[k].x = __builtin_fmaf(res, x[r][k].x, acc[k].x);
+        acc[k].y = __builtin_fmaf(res, x[r][k].y, acc[k].y);
+        acc[k].z = __builtin_fmaf(res, x[r][k].z, acc[k].z);
+        acc[k].w = __builtin_fmaf(res, x[r][k].w, acc[k].w);
+      }
+    }
+  }
+  float4* out = parts + ((uint64_t)m * S + s) * nvec;
 #pragma unroll
   for (int k = 0; k < NV; ++k)
-    if (live(k)) store_stream(out + column(k), acc[k]);
+    if (k < NV - 1 || q_last < nvec) out[t + (uint32_t)k * T] = acc[k];
 }
 
-// g_m = (1/B) (sum over the S partial gradients of worker m, in order) + l2 w; FUSE as in logreg_dense_grad_kernel.
+// g_m = (1/B) (sum over the S partial gradients of worker m) + l2 w.  kMidCols float4 columns a workgroup; the partial gradients
+// are dealt to its row groups, whose sums are added in order (a thread per column is a chain of up to 256 loads: d = 2^16, M = 1,
+// B = 512 160 us, 58 this way).
+constexpr int kMidCols = 32, kMidGroups = kBlock / kMidCols;
+template <bool FUSE>
+__global__ __launch_bounds__(kBlock) void logreg_dense_mid_parts_kernel(
+    const float4* __restrict__ parts, const float* __restrict__ w, float* __restrict__ g, uint64_t d, uint32_t S, float inv_b,
+    float l2, ScaleFusion fuse) {
+  __shared__ float4 sums[kMidGroups - 1][kMidCols];
+  __shared__ float red[16];
+  const uint32_t m = blockIdx.y, tx = threadIdx.x % kMidCols, rg = threadIdx.x / kMidCols;
+  const uint32_t nvec = (uint32_t)((d + 3) / 4), index = blockIdx.x * kMidCols + tx;
+  const bool active = index < nvec;
+  const float4* p = parts + (uint64_t)m * S * nvec + min(index, nvec - 1);
+  const uint64_t col = first_column(min(index, nvec - 1), d);
+  const float4 wv = load4_at(w, col);
+  float4 r1 = make_float4(0.f, 0.f, 0.f, 0.f), r2 = r1;
+  if (FUSE) load_refs4(fuse, col, r1, r2);
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 8
+  for (uint32_t s = rg; s < S; s += kMidGroups) {
+    const float4 v = p[(uint64_t)s * nvec];
+    acc.x += v.x;
+    acc.y += v.y;
+    acc.z += v.z;
+    acc.w += v.w;
+  }
+  if (rg > 0) sums[rg - 1][tx] = acc;
+  __syncthreads();
+  float amax = 0.f;
+  if (active && rg == 0) {
+#pragma unroll
+    for (int k = 0; k < kMidGroups - 1; ++k) {
+      const float4 v = sums[k][tx];
+      acc.x += v.x;
+      acc.y += v.y;
+      acc.z += v.z;
+      acc.w += v.w;
+    }
+    float4 o;
+    o.x = __builtin_fmaf(l2, wv.x, acc.x * inv_b);
+    o.y = __builtin_fmaf(l2, wv.y, acc.y * inv_b);
+    o.z = __builtin_fmaf(l2, wv.z, acc.z * inv_b);
+    o.w = __builtin_fmaf(l2, wv.w, acc.w * inv_b);
+    store4_any(g + (uint64_t)m * d + col, 0, o);
+    if (FUSE) amax = absmax4(fuse, o, r1, r2);
+  }
+  if (FUSE) {
+    amax = block_max(amax, red);
+    if (threadIdx.x == 0) fuse.partials[(uint64_t)blockIdx.x * gridDim.y + m] = amax;
+  }
+}
+
+// The same with a thread per column, for few partial gradients of many columns in whole float4: fewer partial maxima are left
+// to the tail (d = 2^16, M = 16, B = 256: 219.5 us in groups of 32 columns, 216.4).
 template <bool FUSE>
 __global__ __launch_bounds__(kBlock) void logreg_dense_parts_kernel(const float* __restrict__ parts,
                                                                     const float* __restrict__ w, float* __restrict__ g,
@@ -704,6 +688,173 @@ __global__ __launch_bounds__(kBlock) void logreg_dense_parts_kernel(const float*
     amax = block_max(amax, red);
     if (threadIdx.x == 0) fuse.partials[(uint64_t)blockIdx.x * gridDim.y + m] = amax;
   }
+}
+
+// One pass over the minibatch rows of dense problems of 64 K columns: a workgroup takes whole rows, one at a time, and
+// KEEPS the row on chip between the two uses it has -- the
+// dot product z = x . w, and, once sigma(z) - y is known, the accumulation r x into the workgroup's
+// partial gradient -- so that X_B is read from memory once instead of twice (the separate residual and
+// accumulation passes each stream it at 6.2 TB/s, which is all the memory system gives; re-reading a
+// block right after it was read, out of the 256 MB last-level cache, measured no faster than HBM).
+// A row of 256 KiB fits neither store alone: each of the 512 threads (one workgroup per compute
+// unit, so 256 registers per thread) parks NL = 16 float4 of the row in LDS (128 KiB per
+// workgroup; a thread reads back only what it wrote) and holds the other NR = 16 in registers, next to its
+// NV float4 of partial gradient.  The LDS half is loaded from memory straight into LDS, so that the whole
+// row is requested at once.
+// The workgroups of a worker split its minibatch rows; their partial gradients go to scratch
+// parts[m][s][d], and dense_parts_launch has them added.
+constexpr int kRowsThreads = 512;
+constexpr int kRowsWaves = kRowsThreads / kWave;
+// 16 bytes per lane from memory straight into LDS: lane l of the wavefront writes the l-th 16 bytes behind
+// dst, which is the same for the whole wavefront; counted by vmcnt like any load.  Non-temporal (policy bit
+// 2): the row is read once.  (The builtin exists in the device pass only.)
+constexpr int kRowsStagger = 55;  // s_sleep units of 64 clocks: about 1.7 microseconds
+typedef __attribute__((address_space(3))) void* LdsPtr;
+__device__ __forceinline__ void load16_to_lds(GlobalPtr<v4f_t> src, LdsPtr dst) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 2);
+#endif
+}
+constexpr int kRowsLds = 16;  // float4 per thread kept in LDS
+constexpr uint64_t kRowsColumns = 1 << 16;
+__global__ __launch_bounds__(kRowsThreads) void logreg_dense_rows_kernel(const float* const* __restrict__ Xs,
+                                                                         const float* const* __restrict__ ys,
+                                                                         const uint64_t* __restrict__ n_rows,
+                                                                         uint32_t* __restrict__ idx,
+                                                                         const float* __restrict__ w,
+                                                                         float* __restrict__ parts, uint64_t d,
+                                                                         uint32_t batch, uint32_t k0, uint32_t k1,
+                                                                         uint32_t iter) {
+  constexpr int NV = (int)(kRowsColumns / (4 * kRowsThreads)), NL = kRowsLds, NR = NV - NL;
+  constexpr int TR = 4;  // float4 of the LDS half read back at a time when the row is added
+  constexpr int TW = 8;  // float4 of w on their way at a time
+  static_assert(NL % TR == 0 && NL % TW == 0 && NR % TW == 0, "both halves are worked through in whole batches");
+  constexpr int kWaitVmem = 0x0F70;         // s_waitcnt vmcnt(0)
+  constexpr int kWaitLds = 0xC07F;          // s_waitcnt lgkmcnt(0)
+  extern __shared__ float4 rowl[];  // [NL][kRowsThreads]
+  __shared__ float red[2][kRowsWaves];
+  const uint32_t m = blockIdx.y, s = blockIdx.x, S = gridDim.x, t = threadIdx.x;
+  const uint32_t wave_first = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t / kWave)) * kWave;  // a scalar
+  const GlobalPtr<float> X = as_global(Xs[m]);
+  const GlobalPtr<float> y = as_global(ys[m]);
+  const uint64_t n = n_rows[m];
+  const float4* __restrict__ w4 = reinterpret_cast<const float4*>(w);
+  // float4 column k of the thread: LDS half first (k < NL), register half after
+  // (the thread index goes through an opaque copy per use site: otherwise the compiler computes all NV
+  // column addresses of x and of w once, ahead of the row loop, and keeps them in 3 NV registers)
+  auto opaque_t = [&]() {
+    uint32_t v = t;
+    asm volatile("" : "+v"(v));
+    return v;
+  };
+  auto column_of = [&](uint32_t tt, int k) { return tt + (uint32_t)k * kRowsThreads; };
+  float4 acc[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) acc[k] = make_float4(0.f, 0.f, 0.f, 0.f);
+  // A row is fetched (memory busy, arithmetic idle) and then worked on (the reverse), and workgroups that start
+  // together stay in step: every compute unit fetches at once and the memory system idles while all of them
+  // compute.  A quarter of the workgroups therefore starts at once and the others 1.7, 3.4 and 5.1 microseconds
+  // later (about the length of the arithmetic on a row), so that the fetches of some fall into the arithmetic of
+  // the others.  Measured at d = 2^16, M = 16, B = 256: iteration 0.236 -> 0.224 ms, this kernel 200
+  // microseconds (with twice the delay 0.230 ms; with eight steps of 0.7 microseconds 204 microseconds).
+  for (uint32_t q = (blockIdx.x + blockIdx.y * gridDim.x) % 4u; q > 0; --q) __builtin_amdgcn_s_sleep(kRowsStagger);
+  uint32_t parity = 0;
+  for (uint32_t i = s; i < batch; i += S, parity ^= 1u) {
+    const uint32_t row = minibatch_row(k0, k1, iter, m, i, n);
+    if (t == 0) idx[(uint64_t)m * batch + i] = row;
+    const GlobalPtr<float> x = X + (uint64_t)row * d;
+    // Requests of a row, in the order in which they come back: the first batch of w (out of the caches), the
+    // register half, then the LDS half, which goes from memory straight into LDS (16 bytes per lane, lane l of
+    // a wavefront to the l-th float4 behind the wavefront's address: each thread's own slot) -- so the whole
+    // row, 256 KiB at d = 2^16, is in flight at once and no register carries the LDS half.
+    float4 wa[TW];
+    {
+      const uint32_t tt = opaque_t();
+#pragma unroll
+      for (int k = 0; k < TW; ++k) wa[k] = w4[column_of(tt, k)];
+    }
+    float4 xr[NR];
+    {
+      const uint32_t tt = opaque_t();
+#pragma unroll
+      for (int k = 0; k < NR; ++k) xr[k] = load4_stream(x, column_of(tt, NL + k));
+    }
+    {
+      const uint32_t tt = opaque_t();
+#pragma unroll
+      for (int k = 0; k < NL; ++k)
+        load16_to_lds(reinterpret_cast<GlobalPtr<v4f_t>>(x) + column_of(tt, k),
+                      (LdsPtr)(rowl + k * kRowsThreads + wave_first));
+    }
+    __builtin_amdgcn_s_waitcnt(kWaitVmem);  // everything requested above has arrived, the LDS half in LDS
+    asm volatile("" ::: "memory");
+    float z0 = 0.f, z1 = 0.f, z2 = 0.f, z3 = 0.f;
+#pragma unroll
+    for (int k0b = 0; k0b < NL; k0b += TW) {
+      if (k0b > 0) {
+        const uint32_t tt = opaque_t();
+#pragma unroll
+        for (int k = 0; k < TW; ++k) wa[k] = w4[column_of(tt, k0b + k)];
+      }
+      const uint32_t tt = opaque_t();
+#pragma unroll
+      for (int k = 0; k < TW; ++k) {
+        const float4 xv = rowl[(k0b + k) * kRowsThreads + tt];
+        z0 = __builtin_fmaf(xv.x, wa[k].x, z0);
+        z1 = __builtin_fmaf(xv.y, wa[k].y, z1);
+        z2 = __builtin_fmaf(xv.z, wa[k].z, z2);
+        z3 = __builtin_fmaf(xv.w, wa[k].w, z3);
+      }
+      asm volatile("" ::: "memory");  // keeps the next batch's loads behind this batch's use: registers are the scarce thing here
+    }
+#pragma unroll
+    for (int k0b = 0; k0b < NR; k0b += TW) {
+      const uint32_t tt = opaque_t();
+#pragma unroll
+      for (int k = 0; k < TW; ++k) wa[k] = w4[column_of(tt, NL + k0b + k)];
+#pragma unroll
+      for (int k = 0; k < TW; ++k) {
+        z0 = __builtin_fmaf(xr[k0b + k].x, wa[k].x, z0);
+        z1 = __builtin_fmaf(xr[k0b + k].y, wa[k].y, z1);
+        z2 = __builtin_fmaf(xr[k0b + k].z, wa[k].z, z2);
+        z3 = __builtin_fmaf(xr[k0b + k].w, wa[k].w, z3);
+      }
+      asm volatile("" ::: "memory");
+    }
+    // z over the workgroup (two sets of slots alternate, so that one barrier per row is enough)
+    const float zw = wave_sum((z0 + z1) + (z2 + z3));
+    if (t % kWave == 0) red[parity][t / kWave] = zw;
+    __syncthreads();
+    float z = red[parity][0];
+#pragma unroll
+    for (int k = 1; k < kRowsWaves; ++k) z += red[parity][k];
+    const float r = logistic_residual(z, y[row]);
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+      acc[NL + k].x = __builtin_fmaf(r, xr[k].x, acc[NL + k].x);
+      acc[NL + k].y = __builtin_fmaf(r, xr[k].y, acc[NL + k].y);
+      acc[NL + k].z = __builtin_fmaf(r, xr[k].z, acc[NL + k].z);
+      acc[NL + k].w = __builtin_fmaf(r, xr[k].w, acc[NL + k].w);
+    }
+#pragma unroll
+    for (int k0b = 0; k0b < NL; k0b += TR) {
+      const uint32_t tt = opaque_t();
+#pragma unroll
+      for (int k = k0b; k < k0b + TR; ++k) {
+        const float4 xv = rowl[k * kRowsThreads + tt];
+        acc[k].x = __builtin_fmaf(r, xv.x, acc[k].x);
+        acc[k].y = __builtin_fmaf(r, xv.y, acc[k].y);
+        acc[k].z = __builtin_fmaf(r, xv.z, acc[k].z);
+        acc[k].w = __builtin_fmaf(r, xv.w, acc[k].w);
+      }
+      asm volatile("" ::: "memory");
+    }
+    __builtin_amdgcn_s_waitcnt(kWaitLds);  // this row's LDS reads are done before the next row's loads write there
+    asm volatile("" ::: "memory");
+  }
+  float4* __restrict__ out = reinterpret_cast<float4*>(parts + ((uint64_t)m * S + s) * d);
+#pragma unroll
+  for (int k = 0; k < NV; ++k) store_stream(out + column_of(t, k), acc[k]);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1889,11 +2040,9 @@ hipError_t launch_minibatch_indices(uint32_t k0, uint32_t k1, uint32_t iter, uin
 }
 
 uint32_t dense_row_splits(uint64_t d, uint32_t M, uint32_t batch) {
-  // one pass over whole rows kept on chip: rows of 16 K to 64 K columns (shorter ones leave the threads too
-  // little to do, longer ones do not fit), 16-byte aligned, and enough rows for two or more per workgroup
-  // (between 32 K and 64 K columns only the full width: the masked form of the widest variant does not fit the
-  // register file)
-  if (d % 4 != 0 || d < 16384 || (d > 32768 && d != 65536) || (uint64_t)M * batch < 512) return 0;
+  // one pass over whole rows kept on chip by registers and LDS together: 64 K columns (between 32 K and 64 K only the full
+  // width: a masked form does not fit the register file) and enough rows for two or more per workgroup
+  if (d != kRowsColumns || (uint64_t)M * batch < 512) return 0;
   uint32_t S = 256 / (M < 256 ? M : 256);
   S = S < 1 ? 1 : S;
   return S < batch ? S : batch;
@@ -1905,9 +2054,24 @@ uint32_t dense_small_splits(uint64_t d, uint32_t M, uint32_t batch) {
   return trips < 32 ? trips : 32;
 }
 
+// Workgroups per worker: as many as the chip holds at once, fewer where the rows do not fill their trips.  Minibatches of few
+// rows stay with the two passes, whose launches are as short (d = 10240, M = 8, B = 8 13.6 / 14.0 us; d = 3000, M = 8,
+// B = 16 13.7 / 14.0; d = 16000, M = 32, B = 8 22.8 / 24.1; on the other side d = 5000, M = 16, B = 16 16.6 / 15.1; beyond 16 K
+// columns, where the partial gradients are longer, d = 30000, M = 4, B = 100 30.5 / 31.8, d = 32767, M = 32, B = 16 42.4 / 45.0; on the
+// other side d = 32768, M = 32, B = 32 53.7 / 43.4).
+uint32_t dense_mid_splits(uint64_t d, uint32_t M, uint32_t batch) {
+  if (d < 4 || d > 32 * 1024 || (M > 256 && d < kMidMostColumns) || dense_small_splits(d, M, batch) != 0) return 0;
+  if (d > kMidMostColumns ? batch < 32 || (uint64_t)M * batch < 512 : batch < 16 || (batch < 32 && (uint64_t)M * batch < 256)) return 0;
+  const int T = dense_mid_threads(d), nv = dense_mid_columns(d);
+  const uint32_t fill = 256u * (uint32_t)dense_mid_per_unit(T, nv);
+  const uint64_t rows = (uint64_t)dense_mid_rows(T, nv), most = M < fill ? fill / M : 1u;
+  const uint64_t trips = (batch + rows * most - 1) / (rows * most);
+  return (uint32_t)((batch + rows * trips - 1) / (rows * trips));
+}
+
 size_t dense_parts_floats(uint64_t d, uint32_t M, uint32_t batch) {
-  const uint32_t small = dense_small_splits(d, M, batch);
-  if (small != 0) return (size_t)small * M * ((d + 3) / 4 * 4);
+  const uint32_t small = dense_small_splits(d, M, batch), mid = dense_mid_splits(d, M, batch);
+  if (small + mid != 0) return (size_t)(small + mid) * M * ((d + 3) / 4 * 4);
   return (size_t)dense_row_splits(d, M, batch) * M * d;
 }
 
@@ -1916,6 +2080,25 @@ hipError_t dense_small_rows_launch(const LogregData& p, uint64_t d, uint32_t M, 
                                    uint32_t iter, uint32_t* idx, float* parts, const float* w, hipStream_t s) {
   hipLaunchKernelGGL(logreg_dense_small_kernel, dim3(dense_small_splits(d, M, batch), M), dim3(kBlock), 0, s, p.X, p.y,
                      p.n_rows, idx, w, reinterpret_cast<float4*>(parts), (uint32_t)d, batch, k0, k1, iter);
+  return hipGetLastError();
+}
+hipError_t dense_parts_launch(const float* parts, uint64_t d, uint32_t M, uint32_t batch, uint32_t S, float l2,
+                                  const float* w, float* g, const ScaleFusion* fuse, uint32_t* fused_rows, hipStream_t s) {
+  const uint64_t nvec = (d + 3) / 4;
+  const bool by_column = d % 4 == 0 && S <= 16 && nvec * M >= 1u << 16 && aligned16(w) && aligned16(g);
+  const uint32_t cols = by_column ? kBlock : kMidCols;
+  const dim3 grid((uint32_t)((nvec + cols - 1) / cols), M);
+  const bool fused = fuse != nullptr && fused_rows != nullptr;  // (at most 512 rows of partial maxima)
+  const float inv_b = 1.0f / (float)batch;
+  if (by_column) {
+    auto kernel = fused ? logreg_dense_parts_kernel<true> : logreg_dense_parts_kernel<false>;
+    hipLaunchKernelGGL(kernel, grid, dim3(kBlock), 0, s, parts, w, g, d, S, inv_b, l2, fused ? *fuse : ScaleFusion{});
+  } else {
+    auto kernel = fused ? logreg_dense_mid_parts_kernel<true> : logreg_dense_mid_parts_kernel<false>;
+    hipLaunchKernelGGL(kernel, grid, dim3(kBlock), 0, s, reinterpret_cast<const float4*>(parts), w, g, d, S, inv_b, l2,
+                       fused ? *fuse : ScaleFusion{});
+  }
+  if (fused) *fused_rows = grid.x;
   return hipGetLastError();
 }
 }  // namespace
@@ -1962,15 +2145,7 @@ hipError_t launch_logreg_dense_grad(const LogregData& p, uint64_t d, uint32_t M,
   }
   const uint32_t S = parts != nullptr && aligned16(w) && aligned16(g) ? dense_row_splits(d, M, batch) : 0;
   if (S != 0) {
-    const int nv = d <= 16384 ? 8 : d <= 32768 ? 16 : 32;
-    const bool full = d / 4 == (uint64_t)nv * kRowsThreads;
-    const size_t lds = (size_t)(nv < kRowsLds ? nv : kRowsLds) * kRowsThreads * sizeof(float4);
-    const void* fns[] = {reinterpret_cast<const void*>(logreg_dense_rows_kernel<8, false>),
-                         reinterpret_cast<const void*>(logreg_dense_rows_kernel<8, true>),
-                         reinterpret_cast<const void*>(logreg_dense_rows_kernel<16, false>),
-                         reinterpret_cast<const void*>(logreg_dense_rows_kernel<16, true>),
-                         reinterpret_cast<const void*>(logreg_dense_rows_kernel<32, true>),  // 32 float4 per thread:
-                         reinterpret_cast<const void*>(logreg_dense_rows_kernel<32, true>)};  // d = 2^16 only, always full
+    constexpr int kLds = kRowsLds * kRowsThreads * (int)sizeof(float4);
     {  // 128 KiB of dynamic LDS: raised once per device
       static std::mutex attr_mutex;
       static bool attr_done[64] = {};
@@ -1978,31 +2153,50 @@ hipError_t launch_logreg_dense_grad(const LogregData& p, uint64_t d, uint32_t M,
       if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return hipErrorInvalidDevice;
       std::lock_guard<std::mutex> attr_lock(attr_mutex);
       if (!attr_done[dev]) {
-        for (const void* fn : fns) {
-          const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                   kRowsLds * kRowsThreads * (int)sizeof(float4));
-          if (e != hipSuccess) return e;
-        }
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(logreg_dense_rows_kernel),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+        if (e != hipSuccess) return e;
         attr_done[dev] = true;
       }
     }
-    const dim3 grid(S, M);
-    void* args[] = {(void*)&p.X, (void*)&p.y, (void*)&p.n_rows, (void*)&idx, (void*)&w, (void*)&parts,
-                    (void*)&d,   (void*)&batch, (void*)&k0, (void*)&k1, (void*)&iter};
-    const int which = (nv == 8 ? 0 : nv == 16 ? 2 : 4) + (full ? 1 : 0);
-    const hipError_t el = hipLaunchKernel(fns[which], grid, dim3(kRowsThreads), args, lds, s);
+    hipLaunchKernelGGL(logreg_dense_rows_kernel, dim3(S, M), dim3(kRowsThreads), kLds, s, p.X, p.y, p.n_rows, idx, w, parts, d,
+                       batch, k0, k1, iter);
+    const hipError_t el = hipGetLastError();
     if (el != hipSuccess) return el;
-    const float inv_batch = 1.0f / (float)batch;
-    dim3 grid_p((uint32_t)((d / 4 + kBlock - 1) / kBlock), M);
-    if (fuse != nullptr && fused_rows != nullptr && grid_p.x <= kAbsmaxMaxBlocks && aligned16(fuse->gref) &&
-        aligned16(fuse->gref2)) {
-      hipLaunchKernelGGL(logreg_dense_parts_kernel<true>, grid_p, dim3(kBlock), 0, s, parts, w, g, d, S, inv_batch, l2, *fuse);
-      *fused_rows = grid_p.x;
+    return dense_parts_launch(parts, d, M, batch, S, l2, w, g, fuse, fused_rows, s);
+  }
+  const uint32_t mid = parts != nullptr ? dense_mid_splits(d, M, batch) : 0;
+  if (mid != 0) {
+    const dim3 grid(mid, M);
+#define TNG_MID(T, NV)                                                                                         \
+  hipLaunchKernelGGL((logreg_dense_mid_kernel<T, NV>), grid, dim3(T), 0, s, p.X, p.y, p.n_rows, idx, w,        \
+                     reinterpret_cast<float4*>(parts), (uint32_t)d, batch, k0, k1, iter)
+    const int nv = dense_mid_columns(d);
+    if (dense_mid_threads(d) == kBlock) {
+      TNG_MID(kBlock, 1);
+    } else if (dense_mid_threads(d) == kMidThreadsLong) {
+      switch (nv) {
+        case 5: TNG_MID(kMidThreadsLong, 5); break;
+        case 6: TNG_MID(kMidThreadsLong, 6); break;
+        case 7: TNG_MID(kMidThreadsLong, 7); break;
+        default: TNG_MID(kMidThreadsLong, 8); break;
+      }
     } else {
-      hipLaunchKernelGGL(logreg_dense_parts_kernel<false>, grid_p, dim3(kBlock), 0, s, parts, w, g, d, S, inv_batch, l2,
-                         ScaleFusion{});
+      switch (nv) {
+        case 1: TNG_MID(kMidThreads, 1); break;
+        case 2: TNG_MID(kMidThreads, 2); break;
+        case 3: TNG_MID(kMidThreads, 3); break;
+        case 4: TNG_MID(kMidThreads, 4); break;
+        case 5: TNG_MID(kMidThreads, 5); break;
+        case 6: TNG_MID(kMidThreads, 6); break;
+        case 7: TNG_MID(kMidThreads, 7); break;
+        default: TNG_MID(kMidThreads, 8); break;
+      }
     }
-    return hipGetLastError();
+#undef TNG_MID
+    const hipError_t el = hipGetLastError();
+    if (el != hipSuccess) return el;
+    return dense_parts_launch(parts, d, M, batch, mid, l2, w, g, fuse, fused_rows, s);
   }
   // Rows of X and of g start at any 4-byte boundary when d is not a multiple of 4: the vector kernels
   // read and write them with 16-byte accesses that assume no more.
@@ -2022,7 +2216,8 @@ hipError_t launch_logreg_dense_grad(const LogregData& p, uint64_t d, uint32_t M,
     const bool can_fuse = fuse != nullptr && fused_rows != nullptr && grid_g.x <= kAbsmaxMaxBlocks;
     // A thread per float4 column leaves loads too few and chains of dependent rows too long where the columns of all
     // workers are few: the rows are split between row groups then, in blocks of 32, 64 or 128 columns as there are
-    // more of them.  Iterations with blocks of 32 / 64 / 128 / 256 columns / unsplit: d = 1500, M = 4, B = 64 13.9 /
+    // more of them (few minibatch rows, or more workers or columns than the rows in registers are for).  Iterations by these
+    // passes with blocks of 32 / 64 / 128 / 256 columns / unsplit: d = 1500, M = 4, B = 64 13.9 /
     // 14.7 / 14.9 / 17.1 / - us; d = 2048, M = 32, B = 256 35.8 / 34.6 / 36.9 / 45.3 / -; d = 10007, M = 8, B = 128
     // 31.4 / 28.0 / 26.5 / 31.0 / -; M = 32, B = 512 249 / 230 / 231 / 248 / 243; d = 65535, M = 16, B = 200 362 /
     // 326 / 323 / 321 / 318; few rows to split: d = 65535, M = 4, B = 16 39 / 31 / 28.0 / 27.9 / 27.2.

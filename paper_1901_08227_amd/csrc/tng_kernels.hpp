@@ -136,6 +136,7 @@ hipError_t launch_minibatch_indices(uint32_t k0, uint32_t k1, uint32_t iter, uin
 // kernels for wide rows and for tiny problems), or nullptr; the splits are 0 where those kernels do not apply.
 uint32_t dense_row_splits(uint64_t d, uint32_t M, uint32_t batch);
 uint32_t dense_small_splits(uint64_t d, uint32_t M, uint32_t batch);
+uint32_t dense_mid_splits(uint64_t d, uint32_t M, uint32_t batch);
 size_t dense_parts_floats(uint64_t d, uint32_t M, uint32_t batch);
 // A whole iteration of a tiny dense problem (dense_small_splits != 0, largest-magnitude scale, no per-worker mean) in two
 // launches: the gradient of launch_logreg_dense_grad, then scales, codes, average and updates.

@@ -1,0 +1,21 @@
+"""Dense gradients whose rows are read once and held in registers: every number of float4 columns per thread at its edges, odd
+lengths, short last trips of rows, one workgroup per worker and many, and both sides of the rule that chooses, against the
+oracle."""
+import pytest
+
+from paper_1901_08227_amd import binding as B
+from test_gpu_step import _dense_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,M,batch,l2", [
+    (5, 60, 33, 1e-3), (1023, 5, 32, 0.0), (1024, 6, 57, 0.0), (1025, 3, 67, 1e-3), (2048, 3, 40, 0.0), (2049, 4, 100, 1e-3),
+    (4096, 2, 33, 0.0), (4099, 17, 16, 0.0), (6143, 2, 65, 1e-3), (8191, 1, 311, 0.0), (8193, 3, 37, 1e-3), (10240, 2, 130, 0.0),
+    (10241, 2, 32, 0.0), (12291, 1, 99, 1e-3), (14337, 2, 36, 0.0), (16382, 1, 300, 1e-3), (300, 256, 16, 0.0),
+    (300, 257, 16, 0.0), (5000, 8, 31, 0.0), (5000, 9, 31, 0.0), (2500, 70, 40, 0.0),
+    (16384, 1, 40, 0.0), (16384, 300, 3, 0.0), (16385, 5, 110, 1e-3), (20481, 8, 64, 0.0), (24577, 3, 171, 0.0), (28673, 2, 257, 1e-3),
+    (32767, 1, 513, 0.0), (32768, 9, 65, 0.0), (32769, 1, 512, 0.0), (16388, 260, 33, 0.0), (65536, 2, 300, 1e-3)])
+def test_rows_held_in_registers(d, M, batch, l2):
+    print(f"dense rows in registers d={d} M={M} B={batch}", flush=True)
+    _dense_case(M, 40, d, batch, 2, B.NORM_SUB, 4, seed=d, l2=l2)
