@@ -540,10 +540,6 @@ __global__ __launch_bounds__(T, T / 256 * dense_mid_per_unit(T, NV)) void logreg
     wv[k] = load4_at(columns(w, k), 0);
     acc[k] = make_float4(0.f, 0.f, 0.f, 0.f);
   }
-  if (repeated > 0) wv[NV - 1].x = 0.f;
-  if (repeated > 1) wv[NV - 1].y = 0.f;
-  if (repeated > 2) wv[NV - 1].z = 0.f;
-  if (repeated > 3) wv[NV - 1].w = 0.f;
   uint32_t parity = 0;
   for (uint32_t i0 = s; i0 < batch; i0 += S * R, parity ^= 1u) {
     // lane r draws row r of the trip; a short last trip fetches its first row in place of those that it lacks
@@ -562,12 +558,17 @@ __global__ __launch_bounds__(T, T / 256 * dense_mid_per_unit(T, NV)) void logreg
     for (int r = 0; r < R; ++r) {
       float z0 = 0.f, z1 = 0.f, z2 = 0.f, z3 = 0.f;
 #pragma unroll
-      for (int k = 0; k < NV; ++k) {
+      for (int k = 0; k < NV - 1; ++k) {
         z0 = __builtin_fmaf(x[r][k].x, wv[k].x, z0);
         z1 = __builtin_fmaf(x[r][k].y, wv[k].y, z1);
         z2 = __builtin_fmaf(x[r][k].z, wv[k].z, z2);
         z3 = __builtin_fmaf(x[r][k].w, wv[k].w, z3);
       }
+      const float4 xl = x[r][NV - 1], wl = wv[NV - 1];  // (left out by choice, not by a factor of 0: an infinite x would make it NaN)
+      z0 = repeated > 0 ? z0 : __builtin_fmaf(xl.x, wl.x, z0);
+      z1 = repeated > 1 ? z1 : __builtin_fmaf(xl.y, wl.y, z1);
+      z2 = repeated > 2 ? z2 : __builtin_fmaf(xl.z, wl.z, z2);
+      z3 = repeated > 3 ? z3 : __builtin_fmaf(xl.w, wl.w, z3);
       const float z = wave_sum_uniform((z0 + z1) + (z2 + z3));
       if (t % kWave == 0) red[parity][r][t / kWave] = z;
     }

@@ -2,8 +2,11 @@
 lengths, short last trips of rows, one workgroup per worker and many, and both sides of the rule that chooses, against the
 oracle."""
 import pytest
+import torch
 
+from gpu_util import DEV, make_ctx
 from paper_1901_08227_amd import binding as B
+from paper_1901_08227_amd import synth
 from test_gpu_step import _dense_case
 
 pytestmark = pytest.mark.gpu
@@ -19,3 +22,22 @@ pytestmark = pytest.mark.gpu
 def test_rows_held_in_registers(d, M, batch, l2):
     print(f"dense rows in registers d={d} M={M} B={batch}", flush=True)
     _dense_case(M, 40, d, batch, 2, B.NORM_SUB, 4, seed=d, l2=l2)
+
+
+# An infinite element in the last columns, which threads without columns of their own and the last float4 fetch again: its row's
+# dot product is infinite, the residual 0 or 1 in size, and only its own column is touched by it.
+@pytest.mark.parametrize("d,M", [(301, 20), (1030, 3), (5003, 2), (9000, 2), (20002, 16)])
+def test_infinite_element_touches_its_column_only(d, M):
+    X, y, w_star = synth.logreg_dense(M, 40, d, seed=d, device=DEV)
+    X[:, :, d - 2] = float("inf")
+    y.zero_()
+    w = w_star.contiguous()
+    w[d - 2] = 1.0  # z = +infinity: residual 1
+    print(f"dense rows in registers, infinite element d={d} M={M}", flush=True)
+    ctx = make_ctx(d, M, 2, B.NORM_SUB, seed=d, batch=64, problem=B.PROB_LOGREG_DENSE)
+    ctx.set_logreg_dense([X[m] for m in range(M)], [y[m] for m in range(M)])
+    g = torch.zeros((M, d), device=DEV)
+    ctx.local_grad(3, w, g)
+    finite = torch.isfinite(g)
+    assert not finite[:, d - 2].any() and finite.sum().item() == M * (d - 1)
+    ctx.close()
