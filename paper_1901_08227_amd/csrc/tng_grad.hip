@@ -2058,11 +2058,11 @@ uint32_t dense_small_splits(uint64_t d, uint32_t M, uint32_t batch) {
 // Workgroups per worker: as many as the chip holds at once, fewer where the rows do not fill their trips.  Minibatches of few
 // rows stay with the two passes, whose launches are as short (d = 10240, M = 8, B = 8 13.6 / 14.0 us; d = 3000, M = 8,
 // B = 16 13.7 / 14.0; d = 16000, M = 32, B = 8 22.8 / 24.1; on the other side d = 5000, M = 16, B = 16 16.6 / 15.1; beyond 16 K
-// columns, where the partial gradients are longer, d = 30000, M = 4, B = 100 30.5 / 31.8, d = 32767, M = 32, B = 16 42.4 / 45.0; on the
-// other side d = 32768, M = 32, B = 32 53.7 / 43.4).
+// columns, where the partial gradients are longer, d = 30000, M = 4, B = 100 30.5 / 31.8, d = 16385, M = 32, B = 16 26.8 / 29.1; on the
+// other side d = 20000, M = 32, B = 16 37.9 / 28.5, d = 24577, M = 22, B = 24 35.6 / 34.3, d = 32768, M = 32, B = 32 53.7 / 43.4).
 uint32_t dense_mid_splits(uint64_t d, uint32_t M, uint32_t batch) {
   if (d < 4 || d > 32 * 1024 || (M > 256 && d < kMidMostColumns) || dense_small_splits(d, M, batch) != 0) return 0;
-  if (d > kMidMostColumns ? batch < 32 || (uint64_t)M * batch < 512 : batch < 16 || (batch < 32 && (uint64_t)M * batch < 256)) return 0;
+  if (d > kMidMostColumns ? batch < (d % 4 == 0 ? 16u : 24u) || (uint64_t)M * batch < 512 : batch < 16 || (batch < 32 && (uint64_t)M * batch < 256)) return 0;
   const int T = dense_mid_threads(d), nv = dense_mid_columns(d);
   const uint32_t fill = 256u * (uint32_t)dense_mid_per_unit(T, nv);
   const uint64_t rows = (uint64_t)dense_mid_rows(T, nv), most = M < fill ? fill / M : 1u;
