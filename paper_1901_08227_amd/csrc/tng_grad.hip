@@ -1088,8 +1088,8 @@ __global__ __launch_bounds__(kBlock) void csr_gather_bounds_kernel(const int64_t
 
 // What the lanes need of one row segment, staged in LDS by a thread per row: an even number of entries from pos on, and the
 // factor of the row.  A segment of odd length is taken with the entry before it, which is skipped (it is some other
-// segment's: reading one past the end could leave the array); only the array's very first entry has none before it and is
-// taken by itself (kCsrHead).
+// segment's: reading one past the end could leave the array); only a segment at the very start of the array has none before it:
+// its last entry is taken by itself (kCsrHead).
 struct __align__(16) CsrSeg {
   int64_t pos;
   uint32_t n;  // entries, kCsrSkip, kCsrHead
@@ -1102,7 +1102,7 @@ __device__ __forceinline__ CsrSeg csr_segment(const CsrEntries<PAIRS>& e, int64_
   const bool odd = (len & 1u) != 0, head = odd && start == 0;
   const uint32_t n = odd ? (head ? len - 1 : len + 1) : len;
   CsrSeg s;
-  s.pos = n == 0 ? e.position_of(dummy) : odd ? (head ? 1 : start - 1) : start;
+  s.pos = n == 0 ? e.position_of(dummy) : odd && !head ? start - 1 : start;
   s.n = n | (head ? kCsrHead : odd ? kCsrSkip : 0u);
   s.r = r;
   return s;
@@ -1147,9 +1147,10 @@ __device__ __forceinline__ void csr_request(const CsrEntries<PAIRS>& e, const Cs
   }
 }
 
-// use(whether, column, value, u) for the lane's entries of the batch and of what is behind it; entries that are not the
-// lane's come with whether = false (and anything for column and value).
-template <bool PAIRS, int U, int Q, typename F>
+// use(whether, column, value, u, c) for the lane's entries of the batch and of what is behind it; entries that are not the
+// lane's come with whether = false (and anything for column and value).  c = 0 .. 3 says which entries of every 2 kCsrStep these
+// are: the first or second of the lane's two, in an even or odd load.  LOADS per segment and trip behind the batch.
+template <int LOADS, bool PAIRS, int U, int Q, typename F>
 __device__ __forceinline__ void csr_use(const CsrEntries<PAIRS>& e, const CsrSeg* seg, uint32_t gl, const void* dummy,
                                         const CsrBatch<U, Q>& b, const F& use) {
   uint32_t longest = 0, any = 0;
@@ -1162,61 +1163,93 @@ __device__ __forceinline__ void csr_use(const CsrEntries<PAIRS>& e, const CsrSeg
     for (int q = 0; q < Q; ++q) {
       const bool in = 2 * gl + q * kCsrStep < n;
       const bool skip = q == 0 && gl == 0 && (b.n[u] & kCsrSkip) != 0;
-      use(in && !skip, b.two[u][q].col[0], b.two[u][q].val[0], u);
-      use(in, b.two[u][q].col[1], b.two[u][q].val[1], u);
+      use(in && !skip, b.two[u][q].col[0], b.two[u][q].val[0], u, 2 * (q & 1));
+      use(in, b.two[u][q].col[1], b.two[u][q].val[1], u, 2 * (q & 1) + 1);
     }
   }
-  for (uint32_t k = Q * kCsrStep; __builtin_amdgcn_ballot_w64(longest > k) != 0ull; k += kCsrStep) {
-    CsrTwo two[U];
+  for (uint32_t k = Q * kCsrStep; __builtin_amdgcn_ballot_w64(longest > k) != 0ull; k += LOADS * kCsrStep) {
+    CsrTwo two[U][LOADS];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint32_t n = b.n[u] & kCsrCount;
-      two[u] = e.load2_any(n != 0, seg[u].pos + min(2 * gl + k, n != 0 ? n - 2 : 0u), dummy);
+#pragma unroll
+      for (int q = 0; q < LOADS; ++q)
+        two[u][q] = e.load2_any(n != 0, seg[u].pos + min(2 * gl + k + q * kCsrStep, n != 0 ? n - 2 : 0u), dummy);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const bool in = 2 * gl + k < (b.n[u] & kCsrCount);
-      use(in, two[u].col[0], two[u].val[0], u);
-      use(in, two[u].col[1], two[u].val[1], u);
+#pragma unroll
+      for (int q = 0; q < LOADS; ++q) {
+        const bool in = 2 * gl + k + q * kCsrStep < (b.n[u] & kCsrCount);
+        use(in, two[u][q].col[0], two[u][q].val[0], u, 2 * ((Q + q) & 1));
+        use(in, two[u][q].col[1], two[u][q].val[1], u, 2 * ((Q + q) & 1) + 1);
+      }
     }
   }
   if (__builtin_amdgcn_ballot_w64((any & kCsrHead) != 0) != 0ull) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (gl == 0 && (b.n[u] & kCsrHead) != 0) {
+      const uint32_t at = b.n[u] & kCsrCount;
+      if (2 * gl == at % kCsrStep && (b.n[u] & kCsrHead) != 0) {
         int32_t c;
         float v;
-        e.load(0, c, v);
-        use(true, c, v, u);
+        e.load(at, c, v);
+        use(at / kCsrStep % 2 == 0, c, v, u, 0);
+        use(at / kCsrStep % 2 == 1, c, v, u, 2);
       }
     }
   }
 }
 
-// U sums over the kCsrLanes lanes of a group (2 or 4 sums): lanes exchange halves until each has one sum left, which is then
-// added over the lanes that share it.  Lane gl then has sum
-// gl U / kCsrLanes.
+// The dot products of U row segments with the tile of w.  An entry's place in its segment modulo 2 kCsrStep = 32 says which of 32
+// running sums it goes to, in order; those are added in pairs 16 places apart, then 8, 4, 2 and 1.  (What matters is that the
+// chains are of at most 2^tile_shift / 32 products.  With one sum per lane they were four times as long, and the error of z
+// against 64 bits 1.1 times as large at 64 entries per segment, twice at 4096.)  The places 16 apart are in the lane, as are
+// those 1 apart; in between, lane pairs exchange halves of what they have until each has one sum left.  A segment with an entry
+// skipped in front of it has every place shifted by one, under which the pairs stay what they are.
 template <int CTRL>
 __device__ __forceinline__ float csr_lane_move(float v) {
   return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xF, 0xF, false));
 }
+// Which of the group's places a lane takes: those of lanes 0 .. 3 as they come and those of lanes 4 .. 7 the other way round, so that
+// the mirror image of a lane is the one that is 8 entries apart.
+__device__ __forceinline__ uint32_t csr_place(uint32_t gl) { return gl < 4 ? gl : 11 - gl; }
+// Lane gl is left with sum gl U / kCsrLanes.
 template <int U>
-__device__ __forceinline__ float csr_group_sums(const float (&acc)[U], uint32_t gl) {
+__device__ __forceinline__ float csr_group_sums(const float (&acc)[U][4], uint32_t gl) {
   static_assert(kCsrLanes == 8 && (U == 2 || U == 4), "the exchange below");
   constexpr int kMirror = 0x141, kSwap2 = 0x4E, kSwap1 = 0xB1;  // row_half_mirror, quad_perm [2, 3, 0, 1] and [1, 0, 3, 2]
-  float r[U];
-  const bool upper = gl >= 4;
+  const bool b4 = (gl & 4u) != 0, b2 = (gl & 2u) != 0, b1 = (gl & 1u) != 0;
+  float r[U / 2][2];
 #pragma unroll
-  for (int k = 0; k < U / 2; ++k)
-    r[k] = (upper ? acc[k + U / 2] : acc[k]) + csr_lane_move<kMirror>(upper ? acc[k] : acc[k + U / 2]);
-  if (U == 4) {
-    const bool odd = (gl & 2u) != 0;
-    r[0] = (odd ? r[1] : r[0]) + csr_lane_move<kSwap2>(odd ? r[0] : r[1]);
-  } else {
-    r[0] += csr_lane_move<kSwap2>(r[0]);
+  for (int k = 0; k < U / 2; ++k) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const float lower = acc[k][c] + acc[k][c + 2], upper = acc[k + U / 2][c] + acc[k + U / 2][c + 2];
+      r[k][c] = (b4 ? upper : lower) + csr_lane_move<kMirror>(b4 ? lower : upper);
+    }
   }
-  return r[0] + csr_lane_move<kSwap1>(r[0]);
+  if (U == 4) {
+    float s[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) s[c] = (b2 ? r[U / 2 - 1][c] : r[0][c]) + csr_lane_move<kSwap2>(b2 ? r[0][c] : r[U / 2 - 1][c]);
+    const float t = (b1 ? s[1] : s[0]) + csr_lane_move<kSwap1>(b1 ? s[0] : s[1]);
+    return t + csr_lane_move<kSwap1>(t);
+  }
+  float t = (b2 ? r[0][1] : r[0][0]) + csr_lane_move<kSwap2>(b2 ? r[0][0] : r[0][1]);
+  t += csr_lane_move<kSwap1>(t);
+  return t + csr_lane_move<kSwap2>(t);
 }
+template <bool PAIRS, int U, int Q>
+__device__ __forceinline__ float csr_dot(const CsrEntries<PAIRS>& e, const CsrSeg* seg, uint32_t gl, const void* dummy,
+                                         const CsrBatch<U, Q>& b, const float* wtile, uint64_t c0) {
+  float acc[U][4] = {};
+  csr_use<2>(e, seg, csr_place(gl), dummy, b, [&](bool in, int32_t c, float v, int u, int a) {
+    acc[u][a] = __builtin_fmaf(in ? v : 0.f, wtile[in ? (uint32_t)c - (uint32_t)c0 : 0u], acc[u][a]);
+  });
+  return csr_group_sums(acc, gl);
+}
+
 template <bool PAIRS>
 __global__ __launch_bounds__(kCsrThreads) void csr_z_kernel(const int32_t* const* __restrict__ cols,
                                                             const float* const* __restrict__ vals,
@@ -1254,12 +1287,8 @@ __global__ __launch_bounds__(kCsrThreads) void csr_z_kernel(const int32_t* const
     __syncthreads();
     const uint32_t j0 = group * kCsrUnroll;
     CsrBatch<kCsrUnroll, kCsrLoads> b;
-    csr_request(e, seg + j0, gl, dummy, b);
-    float acc[kCsrUnroll] = {};
-    csr_use(e, seg + j0, gl, dummy, b, [&](bool in, int32_t c, float v, int u) {
-      acc[u] = __builtin_fmaf(in ? v : 0.f, wtile[in ? (uint32_t)c - (uint32_t)c0 : 0u], acc[u]);
-    });
-    const float sum = csr_group_sums(acc, gl);
+    csr_request(e, seg + j0, csr_place(gl), dummy, b);
+    const float sum = csr_dot(e, seg + j0, gl, dummy, b, wtile, c0);
     const uint32_t i = first + j0 + gl / (kCsrLanes / kCsrUnroll);
     if (gl % (kCsrLanes / kCsrUnroll) == 0 && i < batch) zpart[i] = sum;
   }
@@ -1330,15 +1359,11 @@ __global__ __launch_bounds__(kCsrThreads) void csr_z_wide_kernel(const int32_t* 
   };
   typedef CsrBatch<kCsrHalfUnroll, kCsrWideLoads> Half;
   auto request = [&](uint32_t step, uint32_t buf, uint32_t half, Half& b) {
-    csr_request(entries(step), seg[buf] + half * kCsrHalf + group * kCsrHalfUnroll, gl, dummy(step), b);
+    csr_request(entries(step), seg[buf] + half * kCsrHalf + group * kCsrHalfUnroll, csr_place(gl), dummy(step), b);
   };
   auto dot = [&](uint32_t step, uint32_t buf, uint32_t half, const Half& b) {
     const uint32_t j0 = half * kCsrHalf + group * kCsrHalfUnroll;
-    float acc[kCsrHalfUnroll] = {};
-    csr_use(entries(step), seg[buf] + j0, gl, dummy(step), b, [&](bool in, int32_t c, float v, int u) {
-      acc[u] = __builtin_fmaf(in ? v : 0.f, wtile[in ? (uint32_t)c - (uint32_t)c0 : 0u], acc[u]);
-    });
-    const float sum = csr_group_sums(acc, gl);
+    const float sum = csr_dot(entries(step), seg[buf] + j0, gl, dummy(step), b, wtile, c0);
     const uint32_t i = (step % trips) * kCsrRows + j0 + gl / (kCsrLanes / kCsrHalfUnroll);
     if (gl % (kCsrLanes / kCsrHalfUnroll) == 0 && i < batch)
       zparts[((uint64_t)(m_first + step / trips) * npairs + pair) * batch + i] = sum;
@@ -1454,7 +1479,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_kernel(const int32_t* co
     const uint32_t j0 = group * kCsrUnroll;
     CsrBatch<kCsrUnroll, kCsrLoads> b;
     csr_request(e, seg + j0, gl, dummy, b);
-    csr_use(e, seg + j0, gl, dummy, b, [&](bool in, int32_t c, float v, int u) {
+    csr_use<1>(e, seg + j0, gl, dummy, b, [&](bool in, int32_t c, float v, int u, int) {
       if (in) atomicAdd(&gtile[(uint32_t)c - (uint32_t)c0], (double)(b.r[u] * v));
     });
   }
@@ -1580,7 +1605,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_run_kernel(const int32_t
     const bool more = t + stride < ntiles;
     const uint32_t tn = more ? t + stride : t;
     const uint32_t nlo = b[(uint64_t)tn * batch], nhi = b[(uint64_t)(tn + 1) * batch];
-    csr_use(e, seg[cur] + j0, gl, dummy, next, [&](bool in, int32_t c, float v, int u) {
+    csr_use<1>(e, seg[cur] + j0, gl, dummy, next, [&](bool in, int32_t c, float v, int u, int) {
       if (in) atomicAdd(&gtile[csr_slot((uint32_t)c)], (double)(next.r[u] * v));
     });
     stage(cur ^ 1u, base + nlo, (has_row && more) ? nhi - nlo : 0u);
@@ -1703,7 +1728,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_workers_kernel(const int
     const int64_t nbase = rowbase_of(mn)[row];
     const float nres = resid_of(mn)[row];
     const CsrEntries<PAIRS> e(cols[m], vals[m]), en(cols[mn], vals[mn]);
-    csr_use(e, seg[cur] + j0, gl, dummy_of(m), next, [&](bool in, int32_t c, float v, int u) {
+    csr_use<1>(e, seg[cur] + j0, gl, dummy_of(m), next, [&](bool in, int32_t c, float v, int u, int) {
       if (in) atomicAdd(&gtile[csr_slot((uint32_t)c)], (double)(next.r[u] * v));
     });
     stage(en, mn, cur ^ 1u, nbase + nlo, (has_row && more) ? nhi - nlo : 0u, nres);
@@ -1843,7 +1868,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_sub_kernel(const int32_t
     const uint32_t j0 = group * kCsrUnroll;
     CsrBatch<kCsrUnroll, kCsrLoads> b;
     csr_request(e, seg + j0, gl, dummy, b);
-    csr_use(e, seg + j0, gl, dummy, b, [&](bool in, int32_t c, float v, int u) {
+    csr_use<1>(e, seg + j0, gl, dummy, b, [&](bool in, int32_t c, float v, int u, int) {
       const uint32_t at = (uint32_t)c - c0;  // (columns left of c0 wrap to far beyond T)
       if (in && at < T) atomicAdd(&gtile[at], (double)(b.r[u] * v));
     });
