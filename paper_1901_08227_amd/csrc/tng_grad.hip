@@ -1561,7 +1561,9 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_run_kernel(const int32_t
                                                                    uint32_t ntiles, ScaleFusion fuse) {
   extern __shared__ double gtile[];  // g over the tile's columns, accumulated in fp64
   __shared__ CsrSeg seg[2][kCsrRows];
-  __shared__ float red[kCsrThreads / kWave];
+  // By parity of the round: read behind the next round's first barrier, where wavefronts that are ahead already store their own maxima
+  // of that round.
+  __shared__ float red[2][kCsrThreads / kWave];
   constexpr uint32_t T = 1u << kCsrTileShift;
   constexpr int kPer = (int)(T / (4 * kCsrThreads));
   const uint32_t m = blockIdx.x;
@@ -1592,14 +1594,15 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_run_kernel(const int32_t
   float* __restrict__ out = g + (uint64_t)m * d;
   CsrBatch<kCsrUnroll, kCsrLoads> next;
   auto request = [&](uint32_t buf) { csr_request(e, seg[buf] + j0, gl, dummy, next); };
-  auto store_maximum = [&](uint32_t t) {  // by thread 0, once red holds tile t's wavefront maxima
-    float mx = red[0];
+  auto parity = [&](uint32_t t) { return ((t - t_first) / stride) & 1u; };
+  auto store_maximum = [&](uint32_t t, uint32_t p) {  // by thread 0, once red[p] holds tile t's wavefront maxima
+    float mx = red[p][0];
 #pragma unroll
-    for (int k = 1; k < kCsrThreads / kWave; ++k) mx = fmaxf(mx, red[k]);
+    for (int k = 1; k < kCsrThreads / kWave; ++k) mx = fmaxf(mx, red[p][k]);
     fuse.partials[(uint64_t)t * gridDim.x + m] = mx;
   };
   auto round = [&](uint32_t t) {
-    const uint32_t cur = ((t - t_first) / stride) & 1u;
+    const uint32_t cur = parity(t);
     const uint64_t c0 = (uint64_t)t << kCsrTileShift;
     // bounds of the workgroup's next tile (clamped: a fetch, never a branch); past its last tile the lengths become 0
     const bool more = t + stride < ntiles;
@@ -1610,7 +1613,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_run_kernel(const int32_t
     });
     stage(cur ^ 1u, base + nlo, (has_row && more) ? nhi - nlo : 0u);
     lds_barrier();  // every add of tile t has been made; the segments of tile t+1 are staged
-    if (t > t_first && threadIdx.x == 0) store_maximum(t - stride);  // older than the request below: need not be counted
+    if (t > t_first && threadIdx.x == 0) store_maximum(t - stride, cur ^ 1u);  // older than the request below: need not be counted
     // the reference of the thread's columns for the fused scale pass, asked for ahead of the entries (loads
     // come back in order: asked for after them, its arrival would be theirs); the kind of normalisation is a
     // template argument so that no branch surrounds these loads either
@@ -1629,7 +1632,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_run_kernel(const int32_t
       amax = fmaxf(amax, absmax4_t<NORM>(fuse, o, r1[k], r2[k]));
     }
     amax = wave_max_nonneg(amax);
-    if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = amax;
+    if (threadIdx.x % kWave == 0) red[cur][threadIdx.x / kWave] = amax;
     lds_barrier();  // the tile is clear again; red is complete
   };
   lds_barrier();
@@ -1642,7 +1645,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_run_kernel(const int32_t
     round(t);
     t_last = t;
   }
-  if (threadIdx.x == 0) store_maximum(t_last);
+  if (threadIdx.x == 0) store_maximum(t_last, parity(t_last));
 }
 
 // The same pipeline turned by ninety degrees: a workgroup stays on ONE column tile and takes the workers

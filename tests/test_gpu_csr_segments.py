@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from oracle import tng_oracle as O
-from gpu_util import DEV, grad_close, logistic_condition_csr, make_ctx, set_csr
+from gpu_util import DEV, buffers, grad_close, logistic_condition_csr, make_ctx, set_csr
 from paper_1901_08227_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -56,4 +56,31 @@ def test_segment_lengths(M, d, pairs, l2, norm):
         ids = O.minibatch_indices(seed, 2, m, batch, n)
         ref = O.grad_logreg_csr(*host, w0, ids, d, l2)
         assert grad_close(g[m].cpu().numpy(), ref, logistic_condition_csr(*host, w0, ids, d, l2)), f"worker {m}"
+    ctx.close()
+
+
+# A workgroup of the pipeline over tiles stores a tile's maximum while its wavefronts are already at the next one's: the scale is
+# the one of the gradient that was written, wherever the row's largest entry lies (first, last and any tile between, any wavefront's columns).
+@pytest.mark.parametrize("M,norm", [(1, B.NORM_NONE), (1, B.NORM_SUB), (1, B.NORM_QUOT), (2, B.NORM_COMB)])
+def test_scales_of_the_pipeline_over_tiles(M, norm):
+    ntiles, n, batch, seed = 130, 12, 3, 5
+    d, rng = ntiles * TILE, np.random.default_rng(5)
+    col = np.concatenate([np.concatenate([t * TILE + np.sort(rng.choice(TILE, 30, replace=False)) for t in range(ntiles)])
+                          for _ in range(n)]).astype(np.int32)
+    val = rng.uniform(0.5, 1.0, len(col)).astype(np.float32)
+    for i in range(n):
+        val[i * 30 * ntiles + (0, 30 * ntiles - 1, *rng.integers(0, 30 * ntiles, n - 2))[i]] = 50.0
+    row = tuple(torch.from_numpy(a).to(DEV) for a in (np.arange(n + 1, dtype=np.int64) * 30 * ntiles, col, val, np.zeros(n, np.float32)))
+    ctx = make_ctx(d, M, 4, norm, seed=seed, lr=0.0, batch=batch, problem=B.PROB_LOGREG_CSR)
+    set_csr(ctx, [row] * M, True)
+    gref, gref2 = torch.full((d,), 1e-3, device=DEV), torch.ones(d, device=DEV)
+    ctx.set_second_reference(gref2)
+    buf = buffers(ctx)
+    for it in range(12):
+        ref = gref.clone()
+        ctx.step(it, torch.zeros(d, device=DEV), ref, buf["g"], buf["codes"], buf["scales"], buf["vbar"])
+        g = buf["g"].cpu().numpy()
+        want = [O.scale_of(O.normalize(g[m], gref.cpu().numpy(), norm, float(ctx.cfg.quot_eps), gref2.cpu().numpy()), O.SCALE_MAX)
+                for m in range(M)]
+        assert np.array_equal(buf["scales"].cpu().numpy(), np.array(want, np.float32)), f"iteration {it}"
     ctx.close()
