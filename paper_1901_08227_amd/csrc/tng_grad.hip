@@ -1245,7 +1245,9 @@ __device__ __forceinline__ float csr_dot(const CsrEntries<PAIRS>& e, const CsrSe
                                          const CsrBatch<U, Q>& b, const float* wtile, uint64_t c0) {
   float acc[U][4] = {};
   csr_use<2>(e, seg, csr_place(gl), dummy, b, [&](bool in, int32_t c, float v, int u, int a) {
-    acc[u][a] = __builtin_fmaf(in ? v : 0.f, wtile[in ? (uint32_t)c - (uint32_t)c0 : 0u], acc[u][a]);
+    // (left out by choice, not by a factor of 0: the tile's first column may be infinite)
+    const float sum = __builtin_fmaf(v, wtile[in ? (uint32_t)c - (uint32_t)c0 : 0u], acc[u][a]);
+    acc[u][a] = in ? sum : acc[u][a];
   });
   return csr_group_sums(acc, gl);
 }

@@ -78,3 +78,25 @@ def test_order_of_the_sums(d, M, width, pairs):
         got = g[m].cpu().numpy()[cols].astype(np.float64) / vals
         off = np.abs(got / np.exp(np.float64(z)) - 1.0).max()
         assert off <= 8 * 2.0 ** -24, f"worker {m}, {len(cols)} entries: {off}"
+
+
+# Columns that no row stores may hold anything: lanes without an entry of their own must not bring them into a sum.
+@pytest.mark.parametrize("d,M", [(1 << 17, 17), ((1 << 17) + 5, 17), (TILE, 130), (300, 7000), (1 << 16, 3)])
+@pytest.mark.parametrize("pairs", [True, False])
+def test_columns_without_entries_are_not_read_into_the_sums(d, M, pairs):
+    n, batch, rng = 6, 9, np.random.default_rng(d)
+    rows = [np.sort(rng.choice(np.arange(1, min(d, TILE)), k, replace=False)) for k in (1, 2, 17, 33, 64, 199)]
+    rows = [np.concatenate([r + t for t in range(0, d, TILE) if t + r[-1] < d]).astype(np.int32) for r in rows]
+    ptr = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int64)
+    shard = tuple(torch.from_numpy(a).to(DEV) for a in (ptr, np.concatenate(rows), rng.standard_normal(ptr[-1]).astype(np.float32),
+                                                        np.zeros(n, np.float32)))
+    ctx = make_ctx(d, M, 2, B.NORM_SUB, seed=7, batch=batch, problem=B.PROB_LOGREG_CSR)
+    set_csr(ctx, [shard] * M, pairs)
+    w = 0.1 * torch.randn(d, device=DEV)
+    g = []
+    for filling in (1.0, float("inf"), float("nan")):
+        w[::TILE] = filling
+        g.append(torch.empty((M, d), device=DEV))
+        ctx.local_grad(1, w, g[-1])
+    ctx.close()
+    assert torch.isfinite(g[0]).all() and torch.equal(g[0], g[1]) and torch.equal(g[0], g[2])
