@@ -1389,7 +1389,8 @@ __global__ __launch_bounds__(kBlock) void quantize_decode_kernel(
         const TailWorker wk = sWorker[m];
         const float4 v = normalize4<NORM, RECIP>(x[mm], rt, wk.mu);
         float4 val;  // what the server decodes
-        const uint32_t frag = quantize4_and_values<BITS>(v, wk.inv_r, philox_draw(block, m, iter, k0, k1), wk.r, wk.step, val);
+        uint32_t frag = quantize4_and_values<BITS>(v, wk.inv_r, philox_draw(block, m, iter, k0, k1), wk.r, wk.step, val);
+        if (BITS == 4 && wk.r == 0.f) frag = 0u;  // (a row without a number in it)
         if (BITS == 2)
           lds.b8[mm][wave][lane] = (uint8_t)frag;
         else
@@ -1490,7 +1491,8 @@ __global__ __launch_bounds__(kBlock) void quantize_decode_split_kernel(
       if (m < M) {
         const TailWorker wk = sWorker[m];
         const float4 v = normalize4<NORM, false>(x[i], rt, wk.mu);
-        const uint32_t frag = quantize4<BITS>(v, wk.inv_r, philox_draw(block, m, iter, k0, k1));
+        uint32_t frag = quantize4<BITS>(v, wk.inv_r, philox_draw(block, m, iter, k0, k1));
+        if (BITS == 4 && wk.r == 0.f) frag = 0u;  // (a row without a number in it)
         if (BITS == 2)
           buf.b8[m][lane] = (uint8_t)frag;
         else
@@ -1711,7 +1713,7 @@ __global__ __launch_bounds__(kRowThreads) void encode_row_kernel(GradRows g, con
   amax = wave_max_nonneg(red[t % (kRowThreads / kWave)]);
   const float R = amax < FLT_MIN ? 0.f : amax;
   if (blockIdx.x == 0 && t == 0) scales[m] = R;
-  const uint32_t frag = quantize4<BITS>(v, R != 0.f ? 1.0f / R : 0.f, philox4x32_10(q, m, iter, 0u, k0, k1));
+  const uint32_t frag = R != 0.f ? quantize4<BITS>(v, 1.0f / R, philox4x32_10(q, m, iter, 0u, k0, k1)) : 0u;
   if (BITS == 2)
     buf.b8[t] = (uint8_t)frag;
   else

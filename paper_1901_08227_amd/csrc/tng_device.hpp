@@ -280,10 +280,14 @@ __device__ __forceinline__ uint32_t shift_in(uint32_t acc, uint32_t x, uint32_t 
   return __builtin_amdgcn_alignbit(acc, x, 32u - bits);
 }
 
+// Gradients are assumed finite.  What is no number all the same -- such an element, or an infinite one under the infinite scale
+// that it makes -- is no probability and codes to level 0 with two bits; with four it takes the top level, min(NaN, 1) being 1,
+// and is negative only if it is less than 0.  Every path codes it alike, and a code and the value averaged for it belong together.
+
 // BITS = 2: a number that is negative if and only if the element codes non-zero, u < |v| inv_r (the difference of two
-// binary32 numbers has its sign after rounding, too).
+// binary32 numbers has its sign after rounding, too).  The clamp, which comes with the product, takes NaN to 0.
 __device__ __forceinline__ float draw_minus_probability(float v, float inv_r, uint32_t word) {
-  return __builtin_fmaf((float)(word >> 8), 0x1p-24f, -(fabsf(v) * inv_r));
+  return __builtin_fmaf((float)(word >> 8), 0x1p-24f, -__builtin_amdgcn_fmed3f(fabsf(v) * inv_r, 0.0f, 1.0f));
 }
 
 // BITS = 4: 2^28 times the level, plus something below 2^28.  With X = 2^24 x (the factor is a power of two: the product
@@ -291,9 +295,15 @@ __device__ __forceinline__ float draw_minus_probability(float v, float inv_r, ui
 // word >> 8, the level floor(x) + [U 2^-24 < x - floor(x)] is floor((ceil(X) + 2^24 - 1 - U) / 2^24); 16 times that, the low
 // bits of the word only make the sum smaller, by less than 16.
 __device__ __forceinline__ uint32_t level_in_top_bits(float v, float inv_r, uint32_t word) {
-  const float t = __builtin_amdgcn_fmed3f(fabsf(v) * inv_r, 0.0f, 1.0f);
+  const float t = fminf(fabsf(v) * inv_r, 1.0f);
   const uint32_t c = (uint32_t)ceilf(t * (7.0f * 0x1p24f));
   return ((c << 4) + 0x0FFFFFFFu) - (word >> 4);
+}
+
+// Its sign bit is that of v, but clear where v is NaN (level 0 has no sign, so two bits need no care).
+template <int BITS>
+__device__ __forceinline__ float signed_like(float v) {
+  return BITS == 2 ? v : fminf(v, __builtin_huge_valf());
 }
 
 __device__ __forceinline__ uint32_t ternary_code(float v, float inv_r, uint32_t word) {
@@ -309,7 +319,7 @@ __device__ __forceinline__ uint32_t quantize4(const float4& v, float inv_r, cons
 #pragma unroll
   for (int c = 3; c >= 0; --c) {
     l = shift_in(l, BITS == 2 ? __float_as_uint(draw_minus_probability(x[c], inv_r, w[c])) : level_in_top_bits(x[c], inv_r, w[c]), BITS);
-    s = shift_in(s, __float_as_uint(x[c]), BITS);
+    s = shift_in(s, __float_as_uint(signed_like<BITS>(x[c])), BITS);
   }
   if (BITS == 2) {
     l &= 0xAAu;
@@ -328,15 +338,16 @@ __device__ __forceinline__ uint32_t quantize4_and_values(const float4& v, float 
   uint32_t l = 0u, s = 0u;
 #pragma unroll
   for (int c = 3; c >= 0; --c) {
-    s = shift_in(s, __float_as_uint(x[c]), BITS);
+    const float sx = signed_like<BITS>(x[c]);
+    s = shift_in(s, __float_as_uint(sx), BITS);
     if (BITS == 2) {
       const float d = draw_minus_probability(x[c], inv_r, w[c]);
       l = shift_in(l, __float_as_uint(d), BITS);
-      y[c] = d < 0.f ? copysignf(r, x[c]) : 0.f;
+      y[c] = d < 0.f ? copysignf(r, sx) : 0.f;
     } else {
       const uint32_t t = level_in_top_bits(x[c], inv_r, w[c]);
       l = shift_in(l, t, BITS);
-      y[c] = copysignf(t >= 0x70000000u ? r : step * (float)(t >> 28), x[c]);
+      y[c] = copysignf(t >= 0x70000000u ? r : step * (float)(t >> 28), sx);
     }
   }
   val = make_float4(y[0], y[1], y[2], y[3]);

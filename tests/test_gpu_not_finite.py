@@ -1,0 +1,78 @@
+"""Elements of a gradient that are infinite or no number: every path gives them the same codes (two bits: level 0; four: the top
+level, negative only below 0), rows without a number code to 0, and what an iteration averages is what its codes decode to."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import tng_oracle as O
+from gpu_util import DEV, buffers, make_ctx, u32
+from paper_1901_08227_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def plant(g, kinds):
+    """Row m gets kind m: odd ends, a middle and every 97th element; kind "all": a row without a number."""
+    for m, kind in enumerate(kinds):
+        if kind == "all":
+            g[m] = -np.nan
+        elif kind is not None:
+            g[m, 5::97] = kind
+            g[m, -1] = g[m, g.shape[1] // 2] = kind
+
+
+def expected(g, gref, seed, it, bits):
+    S, codes, scales = np.float32(2 ** (bits - 1) - 1), [], []
+    with np.errstate(all="ignore"):
+        for m in range(len(g)):
+            v = g[m] - gref
+            R = np.fmax.reduce(np.abs(v), initial=np.float32(0.0))
+            R = R if R >= O.FLT_MIN else np.float32(0.0)
+            u = O.uniform_from_word(O.quant_draw_words(seed, it, m, len(v)))
+            if R == 0.0:
+                level = np.zeros(len(v), np.uint32)
+            else:
+                p = np.abs(v) * (np.float32(1.0) / R)
+                if bits == 2:
+                    level = (u < p).astype(np.uint32)
+                else:
+                    x = np.fmin(p, np.float32(1.0)) * S
+                    lo = np.floor(x)
+                    level = lo.astype(np.uint32) + (u < x - lo)
+            codes.append(O.pack(level, (v < 0) & (level != 0), bits))
+            scales.append(R)
+    return np.stack(codes), np.array(scales, np.float32)
+
+
+NAN, NNAN, INF = np.float32(np.nan), np.float32(-np.nan), np.float32(np.inf)
+KINDS = [NAN, NNAN, INF, -INF, "all", None]
+
+
+# one launch, rows longer than it takes (two passes; candidate slots with two bits), one workgroup, tails of an iteration with
+# one and with many wavefronts for the workers, and one with more workers than they take
+@pytest.mark.parametrize("d,M", [(1000, 6), (1003, 6), (4097, 7), (30001, 6), (1 << 18, 8), ((1 << 18) + 5, 6), (1 << 21, 6),
+                                 ((1 << 21) + 1027, 7), (5000, 64), (5000, 66)])
+@pytest.mark.parametrize("bits", [2, 4])
+def test_not_finite(d, M, bits):
+    print(f"not finite d={d} M={M} bits={bits}", flush=True)
+    rng = np.random.default_rng(d)
+    g = rng.standard_normal((M, d), dtype=np.float32)
+    gref = (0.5 * rng.standard_normal(d)).astype(np.float32)
+    plant(g, KINDS)
+    want, scales = expected(g, gref, 3, 4, bits)
+    ctx = make_ctx(d, M, bits, B.NORM_SUB, seed=3, lr=0.1, ref_policy=B.REF_ZERO)
+    buf, dev = buffers(ctx), torch.from_numpy(gref).to(DEV)
+    ctx.normalize_encode(4, torch.from_numpy(g).to(DEV), dev, buf["codes"], buf["scales"])
+    assert np.array_equal(buf["scales"].cpu().numpy(), scales)
+    bad = np.nonzero(u32(buf["codes"]) != want)
+    assert len(bad[0]) == 0, f"encode: {len(bad[0])} words, first {bad[0][0]}, {bad[1][0]}"
+    average = torch.empty(d, device=DEV)
+    ctx.decode_aggregate(buf["codes"], buf["scales"], dev, average)
+    buf["g"].copy_(torch.from_numpy(g))
+    buf["codes"].fill_(-1)
+    ctx.step(4, torch.zeros(d, device=DEV), dev.clone(), buf["g"], buf["codes"], buf["scales"], buf["vbar"])
+    assert np.array_equal(buf["scales"].cpu().numpy(), scales)
+    bad = np.nonzero(u32(buf["codes"]) != want)
+    assert len(bad[0]) == 0, f"step: {len(bad[0])} words, first {bad[0][0]}, {bad[1][0]}"
+    assert np.array_equal(buf["vbar"].cpu().numpy(), average.cpu().numpy(), equal_nan=True)
+    ctx.close()
