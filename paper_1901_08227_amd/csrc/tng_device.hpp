@@ -368,9 +368,10 @@ __device__ __forceinline__ float wave_max(float v) {
 // the data-parallel lane moves of the vector unit: within rows of 16 lanes by quad swaps and mirrors, then
 // lane 15 of a row into the next row, lane 31 into the upper half; lane 63 holds the result.  Six
 // instructions and a read of lane 63, no LDS round trips (wave_max above makes six of them).  The values
-// are compared as integers, which for non-negative floats is the same order.
+// are compared as integers, which for non-negative floats is the same order; as integers a NaN would be the largest, so it is
+// taken to 0 first, as fmaxf does.
 __device__ __forceinline__ float wave_max_nonneg(float x) {
-  int v = (int)__float_as_uint(x);
+  int v = (int)__float_as_uint(fmaxf(x, 0.f));
   v = max(v, __builtin_amdgcn_update_dpp(v, v, 0xB1, 0xF, 0xF, false));   // quad_perm: [1, 0, 3, 2]
   v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x4E, 0xF, 0xF, false));   // quad_perm: [2, 3, 0, 1]
   v = max(v, __builtin_amdgcn_update_dpp(v, v, 0x141, 0xF, 0xF, false));  // row_half_mirror

@@ -76,3 +76,23 @@ def test_not_finite(d, M, bits):
     assert len(bad[0]) == 0, f"step: {len(bad[0])} words, first {bad[0][0]}, {bad[1][0]}"
     assert np.array_equal(buf["vbar"].cpu().numpy(), average.cpu().numpy(), equal_nan=True)
     ctx.close()
+
+
+# Eight columns that are infinite in every row make NaN of the gradient there (0 times infinity where the residual is 0) and leave
+# the rest of it alone: the scale is the largest of the rest, which lies next to them, in each kernel that leaves maxima.
+@pytest.mark.parametrize("d,M,batch", [(1000, 4, 64), (1003, 3, 20), (5003, 3, 40), (5000, 3, 8), (9001, 2, 6), (20002, 16, 40),
+                                       (65536, 2, 300), (65540, 2, 9)])
+def test_maxima_of_gradients_with_nan(d, M, batch):
+    rng = np.random.default_rng(d)
+    n, a, b = 16, d // 2 // 8 * 8, d // 2 // 8 * 8 + 8
+    X, w = rng.standard_normal((n, d), dtype=np.float32), np.full(d, 1e-3, np.float32)
+    X[:, a:b], X[:, a - 1], X[:, b] = np.inf, 40.0, -30.0
+    y = np.arange(n, dtype=np.float32) % 2  # z = infinity: residuals 1 and 0
+    ctx = make_ctx(d, M, 4, B.NORM_SUB, seed=1, lr=0.0, batch=batch, problem=B.PROB_LOGREG_DENSE, ref_policy=B.REF_ZERO)
+    ctx.set_logreg_dense([torch.from_numpy(X).to(DEV)] * M, [torch.from_numpy(y).to(DEV)] * M)
+    buf = buffers(ctx)
+    ctx.step(1, torch.from_numpy(w).to(DEV), torch.zeros(d, device=DEV), buf["g"], buf["codes"], buf["scales"], buf["vbar"])
+    g = buf["g"].cpu().numpy()
+    assert np.isnan(g[:, a:b]).all() and np.isfinite(np.delete(g, np.s_[a:b], axis=1)).all()
+    assert np.array_equal(buf["scales"].cpu().numpy(), np.fmax.reduce(np.abs(g), axis=1))
+    ctx.close()
