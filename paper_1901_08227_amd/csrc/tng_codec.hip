@@ -2766,16 +2766,22 @@ hipError_t launch_single_pass(const CodecShape& c, uint32_t iter, const float* g
 #undef TNG_SPD
 }
 
-// Rows of one tile, any number of them; longer rows while the workgroups, each of which reads its whole row, are one round of
-// the compute units, up to 2^16 elements, half as many where each is divided by a reference.  Encode + decode, two passes
-// against this one: d = 1000, M = 64 17.7 -> 14.5 us; d = 4096, M = 8 12.6 -> 10.0; d = 25000, M = 4, 4-bit 12.7 -> 10.2; d =
-// 25001, M = 7, quotient 12.7 -> 10.1; d = 65536, M = 8 12.5 -> 10.3; d = 32768, M = 8, combined form 12.8 -> 11.0, M = 32 12.8
-// -> 12.5; beyond the line d = 65536, M = 32 (512 workgroups) 13.4 -> 21.0, d = 131072, M = 8 12.7 -> 16.3.
+// Rows of one tile; longer rows while the workgroups, each of which reads its whole row, are one round of the compute units, up to
+// 2^16 elements, half as many where each is divided by a reference.  Encode + decode, two passes against this one: d = 1000, M =
+// 64 17.7 -> 14.5 us; d = 4096, M = 8 12.6 -> 10.0; d = 25000, M = 4, 4-bit 12.7 -> 10.2; d = 25001, M = 7, quotient 12.7 -> 10.1; d =
+// 65536, M = 8 12.5 -> 10.3; d = 32768, M = 8, combined form 12.8 -> 11.0, M = 32 12.8 -> 12.5; beyond the line d = 65536, M = 32 (512
+// workgroups) 13.4 -> 21.0, d = 131072, M = 8 12.7 -> 16.3.
+// A workgroup costs the same however much of its tile the row fills (4.6 ns of the chip), so many rows have to fill it.  Encode of
+// two bits / four with the quotient, two passes against this one: d = 4096, M = 2048 13.4 -> 10.9 / 18.0 -> 13.3, M = 16384 95.9 ->
+// 82.6 / 110 -> 95.5; d = 1000, M = 1024 9.4 -> 7.0 / 10.1 -> 8.5; d = 4, M = 1024 8.8 -> 7.6 / 8.8 -> 9.0; beyond the line d = 4,
+// M = 2048 9.7 -> 12.5 / 11.5 -> 15.3, M = 65535 118 -> 305 / 158 -> 383; d = 2048, M = 2048 9.9 -> 11.5 / 13.6 -> 13.8, M = 16384
+// 58.7 -> 74.0 / 75.9 -> 93.5; d = 1000, M = 16384 72.2 -> 77.1 / 70.8 -> 96.9.
 constexpr uint64_t kRowMax = 1u << 16;
 constexpr uint64_t kRowGroups = 256;
+constexpr uint32_t kRowFew = 1024;
 bool encode_row_applies(const CodecShape& c) {
   if (c.norm == kNormMean || c.scale_l2) return false;
-  if (c.d <= kRowTile) return true;
+  if (c.d <= kRowTile) return c.M <= kRowFew || c.d > kRowTile / 4 * 3;
   const bool divides = c.norm == kNormQuot || c.norm == kNormComb;
   return c.d <= (divides ? kRowMax / 2 : kRowMax) && (c.d + kRowTile - 1) / kRowTile * c.M <= kRowGroups;
 }

@@ -35,3 +35,42 @@ def test_encode_of_short_rows(d, M, bits, norm):
     assert np.array_equal(scales.cpu().numpy(), s)
     assert np.array_equal(u32(codes), c)
     ctx.close()
+
+
+def encode_time(ctx, g, gref, codes, scales):
+    """Microseconds of an encode call, the shortest of seven times twenty."""
+    best = float("inf")
+    for _ in range(7):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        for it in range(20):
+            ctx.normalize_encode(it, g, gref, codes, scales)
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) * 50)
+    return best
+
+
+# More rows than the one launch takes, and the last numbers and lengths that it does take.
+@pytest.mark.parametrize("d,M", [(5, 1024), (5, 1025), (3072, 1025), (3073, 1025), (1000, 1500), (4, 65535)])
+@pytest.mark.parametrize("bits,norm", [(2, B.NORM_SUB), (4, B.NORM_QUOT)])
+def test_encode_of_many_short_rows(d, M, bits, norm):
+    test_encode_of_short_rows(d, M, bits, norm)
+
+
+# A workgroup to each of many short rows takes two and a half times as long as the passes that the timing hook marks.
+@pytest.mark.parametrize("d,M", [(4, 65535), (256, 16384)])
+def test_many_short_rows_take_no_longer_than_separate_passes(d, M):
+    import bench
+    ctx = make_ctx(d, M, 2, B.NORM_SUB, seed=d)
+    g, gref = torch.randn((M, d), device=DEV), torch.randn(d, device=DEV)
+    codes, scales = torch.empty((M, ctx.words), dtype=torch.int32, device=DEV), torch.empty(M, device=DEV)
+    plain = encode_time(ctx, g, gref, codes, scales)
+    events = bench.HipEvents(5)
+    ctx.set_profile_events(events.ev, 1)
+    separate = encode_time(ctx, g, gref, codes, scales)
+    ctx.set_profile_events(None, 0)
+    ctx.close()
+    events.destroy()
+    print(f"encode d={d} M={M}: {plain:.1f} us, separate passes {separate:.1f} us", flush=True)
+    assert plain < 1.4 * separate
