@@ -41,3 +41,32 @@ def test_infinite_element_touches_its_column_only(d, M):
     finite = torch.isfinite(g)
     assert not finite[:, d - 2].any() and finite.sum().item() == M * (d - 1)
     ctx.close()
+
+
+# Few rows of many workers from 16 K columns on: both sides of the rule, and that these read their rows once (the two passes that a
+# length that is no multiple of 4 has there take 1.6 times as long).
+@pytest.mark.parametrize("d,M,batch", [(16384, 128, 4), (16384, 130, 3), (20000, 64, 8), (20001, 64, 8), (24576, 73, 7), (32768, 40, 13)])
+def test_few_rows_of_many_workers(d, M, batch):
+    print(f"few rows of many workers d={d} M={M} B={batch}", flush=True)
+    _dense_case(M, 20, d, batch, 2, B.NORM_SUB, 2, seed=d)
+
+
+def test_few_rows_of_many_workers_are_read_once():
+    M, n, batch, best = 256, 16, 15, {}
+    for d in (32768, 32767):
+        X = [torch.randn((n, d), device=DEV) for _ in range(M)]
+        ctx = make_ctx(d, M, 2, B.NORM_SUB, seed=1, batch=batch, problem=B.PROB_LOGREG_DENSE)
+        ctx.set_logreg_dense(X, [torch.zeros(n, device=DEV)] * M)
+        w, g = 0.01 * torch.randn(d, device=DEV), torch.empty((M, d), device=DEV)
+        best[d] = float("inf")
+        for _ in range(7):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for it in range(10):
+                ctx.local_grad(it, w, g)
+            b.record()
+            torch.cuda.synchronize()
+            best[d] = min(best[d], 100 * a.elapsed_time(b))
+        ctx.close()
+    print(f"dense gradients M={M} B={batch}: d=32768 {best[32768]:.1f} us, d=32767 {best[32767]:.1f} us", flush=True)
+    assert best[32768] < 0.8 * best[32767]
