@@ -2090,13 +2090,15 @@ uint32_t dense_small_splits(uint64_t d, uint32_t M, uint32_t batch) {
 // B = 16 13.7 / 14.0; d = 16000, M = 32, B = 8 22.8 / 24.1; on the other side d = 5000, M = 16, B = 16 16.6 / 15.1; beyond 16 K
 // columns, where the partial gradients are longer, d = 30000, M = 4, B = 100 30.5 / 31.8, d = 16385, M = 32, B = 16 26.8 / 29.1; on the
 // other side d = 20000, M = 32, B = 16 37.9 / 28.5, d = 24577, M = 22, B = 24 35.6 / 34.3, d = 32768, M = 32, B = 32 53.7 / 43.4).
+// At 16 K columns themselves, where the two passes cost no more than at 12 K, more rows are wanted: M = 1, B = 32 14.6 / 15.8, M = 4, B = 64
+// 17.3 / 18.2, M = 8, B = 32 17.4 / 18.3; on the other side M = 9, B = 32 19.4 / 19.2, M = 2, B = 200 21.7 / 20.7, M = 8, B = 48 20.8 / 19.8.
 // Whole float4 from 16 K columns on: three rows of many workers are enough.  Iterations, the two passes / this: d = 32768, M = 256,
 // B = 15 220 / 150, B = 4 112 / 95.9; M = 512, B = 4 210 / 180; d = 16384, M = 512, B = 4 152 / 139; d = 20000, M = 128, B = 4 52.8 /
 // 48.9; d = 24576, M = 64, B = 8 32.4 / 34.0, B = 12 40.3 / 36.8; beyond the line d = 16384, M = 512, B = 2 132 / 136, B = 1 122 / 131.
 uint32_t dense_mid_splits(uint64_t d, uint32_t M, uint32_t batch) {
   if (d < 4 || d > 32 * 1024 || (M > 256 && d < kMidMostColumns) || dense_small_splits(d, M, batch) != 0) return 0;
   const uint64_t drawn = (uint64_t)M * batch;
-  const bool many = batch >= 32 || (batch >= 16 && drawn >= 256);  // of up to 16 K columns
+  const bool many = d < kMidMostColumns ? batch >= 32 || (batch >= 16 && drawn >= 256) : batch >= 16 && drawn > 256;
   const bool long_rows = drawn >= 512 && batch >= (d % 4 == 0 ? 3u : 24u);  // of 16 K and more
   if (!(d <= kMidMostColumns && many) && !(d >= kMidMostColumns && long_rows)) return 0;
   const int T = dense_mid_threads(d), nv = dense_mid_columns(d);
