@@ -80,3 +80,15 @@ def test_chains_of_long_rows(M, batch):
     bound = (0.25 * z * (512 + d / 2 ** 15 + 32) + 8 * abs(want)) * 2.0 ** -24
     worst = np.abs(g.cpu().numpy().astype(np.float64) - want).max()
     assert worst <= bound, f"{worst} > {bound}"
+
+
+# The pipeline over workers where d is no multiple of a tile: rows of g at every 4-byte phase (odd lengths and numbers of workers), a
+# last tile of one, two, three and many columns, groups of workers that do not come out even, each kind of normalisation it takes.
+@pytest.mark.parametrize("d,M,batch,norm,index,pairs", [
+    ((1 << 18) + 1, 9, 40, B.NORM_SUB, True, True), ((1 << 18) + 2, 9, 33, B.NORM_QUOT, False, True),
+    ((13 << 14) + 3, 11, 512, B.NORM_NONE, True, False), ((1 << 17) + 5, 17, 70, B.NORM_SUB, True, False),
+    ((1 << 17) + 4, 17, 5, B.NORM_QUOT, True, True), ((1 << 18) - 1, 9, 40, B.NORM_NONE, False, True),
+    ((1 << 20) + 1, 3, 20, B.NORM_SUB, True, True), ((1 << 15) + 3, 70, 30, B.NORM_QUOT, False, False),
+    (16385, 129, 3, B.NORM_SUB, True, True)])
+def test_workers_in_turn_on_ragged_tiles(d, M, batch, norm, index, pairs):
+    test_gradient_and_step(d, M, batch, norm, 0.0, index, pairs)
