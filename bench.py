@@ -290,7 +290,7 @@ def whole_iteration_benchmarks(torch, B, synth, dev, steps, warmup, with_oracle=
     if with_oracle:
         x0, nz = synth.rosenbrock_start(d, 1, device=dev).cpu().numpy(), noises[0].cpu().numpy()
         orc = (oracle_step_seconds(ctx, lambda O: [O.grad_rosenbrock(x0, nz[m]) for m in range(M)], x0), "same shape")
-    cache_note = ("3 launches; the 32 MiB of gradients written by one kernel are read by the next out of the 256 MB "
+    cache_note = ("2 launches; the 32 MiB of gradients written by one kernel are read by the next out of the 256 MB "
                   "last-level cache: bound by launches and cache, not an HBM figure")
     record("Rosenbrock chain d=2^20 M=8 ternary sub", ms, step_bytes("rosenbrock", M, d, ctx.words, noise_tensor=True),
            "noise tensors of 8 iterations resident; " + cache_note, orc, bound="launch latency and last-level cache")

@@ -1088,7 +1088,7 @@ __global__ __launch_bounds__(kBlock) void quantize_candidates_kernel(
         const uint32_t pos = e & kCandPosMask;
         // The entry brackets tau = |v| / u: its significand was cut to 13 bits twice (the value's, then tau's own)
         // and its arithmetic is good to 2^-22, so tau lies in [lo (1 - 2^-22), hi (1 + 2^-13 + 2^-21)].
-        // quantize_code's level [u < fl(|v| fl(1 / R))] is 1 for R <= tau (1 - 2^-21) and 0 for R >= tau (1 + 2^-21)
+        // ternary_code's level [u < fl(|v| fl(1 / R))] is 1 for R <= tau (1 - 2^-21) and 0 for R >= tau (1 + 2^-21)
         // (the two roundings move |v| / R by less than 2^-22 relatively, 1 / R > 2^126 included), so only a scale
         // inside the widened bracket -- three candidates in ten thousand -- needs the value and the draw.
         const float lo = __uint_as_float(e & 0x7FFFFC00u), hi = __uint_as_float((e & 0x7FFFFC00u) | kCandPosMask);
@@ -1264,7 +1264,7 @@ constexpr uint32_t kTailMaxWorkers = 64;
 constexpr uint32_t kTailPartials = 8192, kTailPartialsLong = 2048;
 constexpr uint32_t kTailFewPartials = 1024;  // up to here single loads: at a few hundred the exchange between lanes costs 0.5 us
 
-// What the coder needs of a worker: its scale R, 1 / R and R / S, and its mean.  Of R = 0 all are 0, under which every element
+// What the coder needs of a worker: its scale R, 1 / R and R / S, and its mean.  Of R = 0 all are 0, under which every number
 // codes to level 0.  Made once per workgroup: the two divisions by every lane for every worker were a seventh of the kernel's
 // instructions.  With that and the part of a draw that is the same for all workers made once (philox_block), the tail of the
 // Rosenbrock iteration at d = 2^20, M = 8 takes 11.8 us for 13.6, given gradients of d = 4e6, M = 8, quotient 71.1 for 74.2.

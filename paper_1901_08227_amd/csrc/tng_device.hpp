@@ -272,10 +272,11 @@ __device__ __forceinline__ float decode_code(uint32_t code, float r, float step)
 // = |v|/R):  t = min(|v| inv_r, 1), x = t S, level = floor(x) + [u < x - floor(x)], u the 24-bit draw; one rounding per
 // operation.  With S = 1 that is level = [u < |v| inv_r].  A code is level | sign << (BITS - 1), the sign cleared at level 0.
 //
-// The functions below take that in fewer operations, bit for bit: the kernels that draw and round 10^9 elements are as much
-// bound by the vector unit as by memory (4-bit quantise pass of Eq. 2 at d = 2^27, M = 8: 32 instructions per element, ten of
-// them the draw, 27 this way; encode + decode 1856 -> 1831 us, the iteration of the Rosenbrock chain 28.97 -> 28.61).  Levels and signs of four elements are gathered by shifting the top bits of
-// one word into the lower end of another, an instruction per element, and the signs of level 0 are cleared for all four at once.
+// The functions below take that in fewer operations, bit for bit (4-bit quantise pass of Eq. 2 at d = 2^27, M = 8: 31.8 vector
+// instructions per element, ten of them the draw, 28.8 this way; encode + decode 1858 -> 1850 us, which is within what two runs
+// differ by: that pass is at the memory's rate; the iteration of the Rosenbrock chain 28.97 -> 28.61).  Levels and signs of four
+// elements are gathered by shifting the top bits of one word into the lower end of another, an instruction per element, and the
+// signs of level 0 are cleared for all four at once.
 __device__ __forceinline__ uint32_t shift_in(uint32_t acc, uint32_t x, uint32_t bits) {  // acc << bits | top bits of x
   return __builtin_amdgcn_alignbit(acc, x, 32u - bits);
 }
@@ -301,6 +302,8 @@ __device__ __forceinline__ uint32_t level_in_top_bits(float v, float inv_r, uint
 }
 
 // Its sign bit is that of v, but clear where v is NaN (level 0 has no sign, so two bits need no care).
+// (Three instructions per element with the min() of the level, one of which makes a signalling NaN quiet; without that one, by an
+// instruction written out, the quotient form spills five registers and encode + decode at d = 2^27, M = 8 takes 1 % longer.)
 template <int BITS>
 __device__ __forceinline__ float signed_like(float v) {
   return BITS == 2 ? v : fminf(v, __builtin_huge_valf());

@@ -494,12 +494,13 @@ __global__ __launch_bounds__(kSmallThreads) void logreg_dense_small_finish_kerne
 // logreg_dense_mid_parts_kernel adds the S partial gradients of a worker (parts[m][s][ceil(d / 4)] float4).
 // Bound by memory where the rows are many (d = 16000, M = 32, B = 512: 1 GiB of rows in an iteration of 174 us, 6.4 TB/s in this
 // kernel) and by latency where a workgroup has one trip.  Iterations, the residual and the accumulation pass (rows read
-// twice) / this: d = 10007, M = 8, B = 128 26.6 / 24.0 us, M = 32, B = 512 231 / 122; d = 16000, M = 32, B = 512 324 / 174;
+// twice) / this: d = 10007, M = 8, B = 128 26.9 / 20.9 us, M = 32, B = 512 231 / 122; d = 16000, M = 32, B = 512 324 / 174;
 // d = 5003, M = 16, B = 512 70.9 / 44.6; d = 2048, M = 32, B = 256 34.1 / 24.1; d = 1000, M = 32, B = 512 42.3 / 26.9; d = 300,
 // M = 20, B = 64 16.5 / 14.6.
 // Up to 4 float4 columns a thread two workgroups share a compute unit (128 registers), one fetching while the other
-// computes; beyond, one with twice the registers and four rows at a time is faster (d = 10007, M = 8, B = 128 24.0, two of three
-// rows each 26.7; d = 16000, M = 16, B = 512 95.8, two of one row 106).  Beyond 16 K columns the workgroup has 1024 threads and
+// computes; beyond, one with twice the registers and four rows at a time is faster (with the partial gradients added by a
+// thread per column still: d = 10007, M = 8, B = 128 24.0, two of three rows each 26.7; d = 16000, M = 16, B = 512 95.8, two of one row
+// 106).  Beyond 16 K columns the workgroup has 1024 threads and
 // takes one or two rows.  There, and at 16 K, rows went through LDS and registers one at a time, or twice through memory
 // where d was no multiple of 4: d = 32768, M = 16, B = 512 223 / 178, d = 32765 355 / 184, d = 20000, M = 16, B = 200 94.8 / 60.2,
 // d = 16384, M = 16, B = 512 136 / 98; their partial gradients were a chain of up to 256 loads, d = 32768, M = 1, B = 512 146 / 32.4.
@@ -884,8 +885,8 @@ constexpr int kCsrRows = 512;      // minibatch rows staged in LDS per trip
 // segment and a branch around every load and use, the dot products took 600 vector and 850 scalar instructions per
 // wavefront and 512 rows, about two thirds of their time, and the segments' loads by themselves ran 25 to 30 % slower than
 // with 16 bytes per lane (1.21 -> 0.92 ms for the segments of 2^14 columns, 64 workers, 512 rows of 16777 pairs).  Iteration
-// at d = 2^24, M = 64, B = 512, 0.1 % density 4160 -> 3726 us (dot products 1160 -> 930, gradient 1975 -> 1890, which the LDS
-// bounds: its atomic adds and write-out keep it busy for three quarters of the time); d = 2^16, M = 8 19.1 -> 18.1.
+// at d = 2^24, M = 64, B = 512, 0.1 % density 4276 -> 3899 us (dot products 1180 -> 959, gradient 2055 -> 1903, which the LDS
+// bounds: its atomic adds and write-out keep it busy for three quarters of the time); d = 2^16, M = 8 19.1 -> 17.8.
 constexpr int kCsrLanes = 8;                  // lanes that share one row segment
 constexpr int kCsrUnroll = 4;                 // row segments per lane group and trip
 constexpr uint32_t kCsrStep = 2 * kCsrLanes;  // entries that a load of each lane covers
@@ -1300,8 +1301,8 @@ __global__ __launch_bounds__(kCsrThreads) void csr_z_kernel(const int32_t* const
 // waited for (__syncthreads would wait until every one of them has come back).
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// The same pass with two adjacent tiles of w (2^15 columns, 128 KiB) in LDS and twice the lanes per
-// row: the row segments are twice as long, so fewer of the 128-byte memory lines they touch are
+// The same pass with two adjacent tiles of w (2^15 columns, 128 KiB) in LDS and kCsrWideLoads loads per
+// segment: the row segments are twice as long, so fewer of the 128-byte memory lines they touch are
 // partial ones.  (Random contiguous segments deliver 2.2 TB/s of useful bytes at 64 bytes per
 // segment and 3.2 TB/s at 128; this pass is bound by exactly that.)  One partial sum per row and pair
 // of tiles: zparts[m][pair][i].
@@ -1552,7 +1553,8 @@ __device__ __forceinline__ float4 csr_take4(double* gtile, uint32_t q) {
 //   out: loads and stores retire through one in-order counter, so the wait for those entries at the
 //   top of the next round only has to leave the (younger) stores outstanding, and the write-out, the
 //   clearing of the tile and the stores' acknowledgement all run under the entries' latency.
-// The barriers order LDS traffic only.  Lanes beyond a segment's length carry an invalid column.
+// The barriers order LDS traffic only.  Lanes beyond a segment's length hold its last pair once more, which csr_use tells
+// them to leave out.
 template <bool PAIRS, int NORM>
 __global__ __launch_bounds__(kCsrThreads) void csr_grad_run_kernel(const int32_t* const* __restrict__ cols,
                                                                    const float* const* __restrict__ vals,
@@ -1776,8 +1778,8 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_workers_kernel(const int
 // workgroups as fill the chip: each owns 2^sub_shift columns of a tile in LDS and reads the tile's whole row
 // segments (out of the L2: 2^(tile_shift - sub_shift) workgroups read the same ones), adding those that are its own.
 // ------------------------------------------------------------------------------------------
-// WAVES: wavefronts per row.  A lane adds at most kCsrChain products in a row, as many as in a tile of the other
-// dot-product passes: a row of 2^20 entries would be chains of 2^14 otherwise.
+// WAVES: wavefronts per row.  A lane adds at most kCsrChain products in a row, as many as a running sum of the other
+// dot-product passes has in a tile: a row of 2^20 entries would be chains of 2^14 otherwise.
 constexpr uint32_t kCsrChain = 512;
 template <bool PAIRS, bool INDEX, int WAVES>
 __global__ __launch_bounds__(WAVES == 1 ? kBlock : WAVES * kWave) void csr_rows_kernel(const int64_t* const* __restrict__ rowptrs,
