@@ -1040,8 +1040,15 @@ __global__ __launch_bounds__(kBlock) void absmax_finish_vote_kernel(const float*
 // The packed codes of a tile from its slots.  One wavefront per tile as in the quantiser; the words of a
 // worker are cleared in LDS, the candidates' codes are or-ed in, and all workers' words are written at the
 // end as the quantiser writes them.
+// What bounds it: slots read and codes written, a wavefront waiting for its tile's slots once, so the wavefronts in flight
+// count: eight per SIMD (64 registers), the rare paths behind the loop over the workers and there only once.  At d = 2^27,
+// M = 8 (0.27 GB of slot lines, 0.27 GB of codes) 148 us with the counts fetched by loads of their own (a third line
+// of every slot), the rare paths inside the loop and six wavefronts; 130 without the third line; 125 with eight wavefronts
+// (4.3 TB/s).  d = 2^24, M = 16, l2 scale (slots all but empty): 37 -> 28.  Two tiles a wavefront, all their slots
+// requested at once: 131; wavefronts that walk the tiles and request the next one's slots before this one's work: 156 to 177.
+// Groups of five workers where those divide M (as in absmax_select_kernel): d = 2^25 + 3, M = 5 32.1 us, 28.0 so.
 template <int NORM, int MC>
-__global__ __launch_bounds__(kBlock) void quantize_candidates_kernel(
+__global__ __launch_bounds__(kBlock, 8) void quantize_candidates_kernel(
     GradRows g, const float4* __restrict__ ref4, const float4* __restrict__ ref24, const float* __restrict__ scales,
     const uint32_t* __restrict__ slots, uint32_t* __restrict__ codes, uint64_t d, uint64_t words, uint64_t slot_tiles,
     uint32_t M, float eps, uint32_t k0, uint32_t k1, uint32_t iter, const uint32_t* __restrict__ use_slots,
@@ -1058,71 +1065,101 @@ __global__ __launch_bounds__(kBlock) void quantize_candidates_kernel(
   const uint64_t tile = (uint64_t)blockIdx.x * kWavesPerBlock + wave;
   if (tile >= ntiles) return;  // whole wavefronts; nothing below meets the other wavefronts
   const uint64_t word_base = tile * WPW;
-  // Counts and the first 64 words of all the workers' slots are requested at once (a slot rarely holds
-  // more: the rest is fetched when its count says so), so that the workgroup waits for memory once and not
+  // The count and the first 63 candidates of all the workers' slots are requested at once, two whole lines each (a slot
+  // rarely holds more: the rest is fetched when its count says so), so that the wavefront waits for memory once and not
   // once per worker.  Words past a slot's count are whatever an earlier call left there and are not used.
-  uint32_t cnt[MC];
-  uint32_t first[MC];
+  uint32_t first[MC], ok[MC];
+  float R[MC];
 #pragma unroll
   for (int mm = 0; mm < MC; ++mm) {
     const uint32_t m = min(m0 + (uint32_t)mm, M - 1);
-    const uint32_t* __restrict__ sl = slots + ((uint64_t)m * ntiles + tile) * kSlotEntries;
-    cnt[mm] = sl[0];
-    first[mm] = sl[1 + lane];
+    first[mm] = slots[((uint64_t)m * ntiles + tile) * kSlotEntries + (uint32_t)lane];
+    R[mm] = scales[m];
+    ok[mm] = select_ok[m];
   }
 #pragma unroll
-  for (int mm = 0; mm < MC; ++mm) {
-    const uint32_t m = m0 + (uint32_t)mm;
-    if (m >= m_end) break;
-    const int slot = mm;
-    const float R = scales[m];
-    const uint32_t* __restrict__ sl = slots + ((uint64_t)m * ntiles + tile) * kSlotEntries;
-    // (a worker whose row the sample found too dense has no slots, and a tile beyond the last whole chunk of the l2
-    // scale's sums has none: they take the ordinary path)
-    const uint32_t n = R == 0.f ? 0u : select_ok[m] != 0u && tile < slot_tiles ? cnt[mm] : (uint32_t)kCandCap + 1u;
-    if (n <= (uint32_t)kCandCap) {
-      lds.b32[slot][wave][lane] = 0u;
-      wave_lds_fence();
-      const float inv_r = R == 0.f ? 0.f : 1.0f / R;
-      auto code_one = [&](uint32_t e) {
-        const uint32_t pos = e & kCandPosMask;
-        // The entry brackets tau = |v| / u: its significand was cut to 13 bits twice (the value's, then tau's own)
-        // and its arithmetic is good to 2^-22, so tau lies in [lo (1 - 2^-22), hi (1 + 2^-13 + 2^-21)].
-        // ternary_code's level [u < fl(|v| fl(1 / R))] is 1 for R <= tau (1 - 2^-21) and 0 for R >= tau (1 + 2^-21)
-        // (the two roundings move |v| / R by less than 2^-22 relatively, 1 / R > 2^126 included), so only a scale
-        // inside the widened bracket -- three candidates in ten thousand -- needs the value and the draw.
-        const float lo = __uint_as_float(e & 0x7FFFFC00u), hi = __uint_as_float((e & 0x7FFFFC00u) | kCandPosMask);
-        const bool bounded = (e & 0x7F800000u) != 0x7F800000u;  // u = 0: tau is infinite or no number
-        uint32_t code;
-        if (bounded && R <= lo * (1.0f - 0x1p-19f)) {
-          code = 1u | ((e >> 31) << 1);
-        } else if (R >= hi * (1.0f + 0x1p-12f)) {  // (false where tau is not bounded)
-          code = 0u;
-        } else {
-          const uint64_t coord = tile * (uint64_t)(kWave * L * 4) + pos;
-          const U32x4 rnd = philox4x32_10((uint32_t)(coord >> 2), m, iter, 0u, k0, k1);
-          const uint32_t sel = pos & 3u;
-          const uint32_t word = sel == 0u ? rnd.x : sel == 1u ? rnd.y : sel == 2u ? rnd.z : rnd.w;
-          float r1 = 0.f;
-          if (NORM == kNormSub) r1 = reinterpret_cast<const float*>(ref4)[coord];
-          code = ternary_code(normalize_w<NORM>(g.base[(uint64_t)m * g.pitch + coord], r1, 1.f, 0.f), inv_r, word);
-        }
-        if (code != 0u) atomicOr(&lds.b32[slot][wave][pos >> 4], code << (2u * (pos & 15u)));
-      };
-      if ((uint32_t)lane < n) code_one(first[mm]);
-      if (n > (uint32_t)kWave && (uint32_t)(kWave + lane) < n) code_one(sl[1 + kWave + lane]);
-    } else {  // the slot overflowed: this worker's tile goes through the ordinary path
-      QuantLane<NORM> q;
+  for (int mm = 0; mm < MC; ++mm) lds.b32[mm][wave][lane] = 0u;
+  wave_lds_fence();
+  // The entry brackets tau = |v| / u: its significand was cut to 13 bits twice (the value's, then tau's own) and its
+  // arithmetic is good to 2^-22, so tau lies in [lo (1 - 2^-22), hi (1 + 2^-13 + 2^-21)].  ternary_code's level
+  // [u < fl(|v| fl(1 / R))] is 1 for R <= tau (1 - 2^-21) and 0 for R >= tau (1 + 2^-21) (the two roundings move |v| / R by
+  // less than 2^-22 relatively, 1 / R > 2^126 included), so only a scale inside the widened bracket -- three candidates in
+  // ten thousand -- needs the value and the draw.
+  auto codes_one = [&](uint32_t e, float r) {  // (u = 0: tau is infinite or no number, and not bounded)
+    return (int)((e & 0x7F800000u) != 0x7F800000u) & (int)(r <= __uint_as_float(e & 0x7FFFFC00u) * (1.0f - 0x1p-19f));
+  };
+  auto codes_zero = [&](uint32_t e, float r) {  // (false where tau is not bounded)
+    return (int)(r >= __uint_as_float((e & 0x7FFFFC00u) | kCandPosMask) * (1.0f + 0x1p-12f));
+  };
+  auto put = [&](uint32_t slot, uint32_t e, uint32_t code) {
+    atomicOr(&lds.b32[slot][wave][(e & kCandPosMask) >> 4], code << (2u * (e & 15u)));
+  };
+  // Bit mm: worker m0 + mm has more candidates than are in first[mm], or no slot here (its row is too dense for slots,
+  // this one overflowed, or the tile lies beyond the last whole chunk of the l2 scale's sums); in undecided, this lane's
+  // candidate of that worker needs its value.  All three are rare and come after the loop, in code that is there once and
+  // not once per worker.
+  uint32_t long_slots = 0u, no_slots = 0u, undecided = 0u;
 #pragma unroll
-      for (int j = 0; j < L; ++j) {
-        q.iv[j] = tile * (kWave * L) + (uint64_t)j * kWave + lane;
-        q.rt[j].load(ref4, ref24, q.iv[j], eps);
+  for (int mm = 0; mm < MC; ++mm) {
+    const uint32_t e = first[mm], n = __builtin_amdgcn_readfirstlane(e);
+    const bool live = m0 + (uint32_t)mm < m_end && R[mm] != 0.f;  // (R = 0: every element codes to 0)
+    const bool slot = ok[mm] != 0u && tile < slot_tiles && n <= (uint32_t)kCandCap;
+    no_slots |= (live && !slot ? 1u : 0u) << mm;
+    long_slots |= (live && slot && n >= (uint32_t)kWave ? 1u : 0u) << mm;
+    const int in = (uint32_t)lane - 1u < (live && slot ? n : 0u);  // (lane 0 holds the count)
+    const int one = in & codes_one(e, R[mm]);
+    if (one) put((uint32_t)mm, e, 1u | ((e >> 31) << 1));
+    undecided |= (uint32_t)(in & ~one & ~codes_zero(e, R[mm])) << mm;
+  }
+  auto code_from_value = [&](uint32_t mm, uint32_t m, uint32_t e, float r) {
+    const uint32_t pos = e & kCandPosMask;
+    const uint64_t coord = tile * (uint64_t)(kWave * L * 4) + pos;
+    const U32x4 rnd = philox4x32_10((uint32_t)(coord >> 2), m, iter, 0u, k0, k1);
+    const uint32_t sel = pos & 3u;
+    const uint32_t word = sel == 0u ? rnd.x : sel == 1u ? rnd.y : sel == 2u ? rnd.z : rnd.w;
+    float r1 = 0.f;
+    if (NORM == kNormSub) r1 = reinterpret_cast<const float*>(ref4)[coord];
+    const uint32_t code = ternary_code(normalize_w<NORM>(g.base[(uint64_t)m * g.pitch + coord], r1, 1.f, 0.f), 1.0f / r, word);
+    if (code != 0u) put(mm, e, code);
+  };
+  if (long_slots != 0u || __builtin_amdgcn_ballot_w64(undecided != 0u) != 0ull) {
+#pragma unroll 1
+    for (uint32_t mm = 0; mm < m_end - m0; ++mm) {
+      const bool longer = ((long_slots >> mm) & 1u) != 0u;
+      const int open = (int)(undecided >> mm) & 1;
+      if (!longer && __builtin_amdgcn_ballot_w64(open) == 0ull) continue;
+      const uint32_t m = m0 + mm;
+      const uint32_t* __restrict__ sl = slots + ((uint64_t)m * ntiles + tile) * kSlotEntries;
+      const uint32_t n = sl[0], e0 = sl[lane], e1 = sl[kWave + lane];
+      const float r = scales[m];
+      const int in = (int)longer & (int)((uint32_t)(kWave + lane) <= n), one = in & codes_one(e1, r);
+      if (one) put(mm, e1, 1u | ((e1 >> 31) << 1));
+      const int open1 = in & ~one & ~codes_zero(e1, r);
+#pragma unroll 1
+      for (int k = 0; k < 2; ++k)
+        if (k == 0 ? open : open1) code_from_value(mm, m, k == 0 ? e0 : e1, r);
+    }
+  }
+#pragma unroll 1
+  for (uint32_t mm = 0; no_slots >> mm != 0u; ++mm) {  // these workers' tiles go through the ordinary path
+    if (((no_slots >> mm) & 1u) == 0u) continue;
+    const uint32_t m = m0 + mm;
+    const float inv_r = 1.0f / scales[m];
+#pragma unroll 1
+    for (int j = 0; j < L; j += 2) {  // (two float4 at a time: all four need more than the 64 registers of eight wavefronts)
+      const uint64_t iv = tile * (kWave * L) + (uint64_t)(j * kWave + lane);
+      const v4f_u_t* row = g.row(m) + iv;
+      float4 v[2] = {load_row_stream(row), load_row_stream(row + kWave)};
+      RefTile<NORM> rt[2];
+      rt[0].load(ref4, ref24, iv, eps);
+      rt[1].load(ref4, ref24, iv + kWave, eps);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) v[k] = normalize4<NORM, false>(v[k], rt[k], 0.f);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const U32x4 rnd = philox4x32_10((uint32_t)iv + (uint32_t)(k * kWave), m, iter, 0u, k0, k1);
+        lds.b8[mm][wave][(j + k) * kWave + lane] = (uint8_t)quantize4<2>(v[k], inv_r, rnd);
       }
-      float4 x[L];
-      uint32_t frag[L];
-      load_worker_tile<NORM>(q, g, m, x);
-      quantize_worker_tile<NORM, 2, false>(q, x, R, 0.f, m, iter, k0, k1, frag);
-      store_packed<2, WPW, MC, true>(lds, slot, wave, lane, frag, codes, word_base, words);
     }
   }
   flush_packed<WPW, MC>(lds, wave, lane, codes, words, word_base, m0, m_end - m0);
@@ -2109,8 +2146,8 @@ inline uint32_t div_up_u32(uint64_t a, uint64_t b) {
 // short).  A group reads the shared reference once, so fewer groups mean less traffic; a short group
 // costs the scale pass repeated loads of its last row (cache hits: repeat_cost 0.3 of a row there,
 // nothing in the quantiser, which stops at the last worker).  At least 2048 workgroups are kept to
-// fill 256 compute units.  fives: groups of 5 as well, for absmax_select_kernel, where the reference and five rows are two
-// rounds of its three buffers; chosen for 5, 9, 10, 17 to 20 and 25 workers of long rows (encode + decode at d = 2^25: M = 5 293 us
+// fill 256 compute units.  fives: groups of 5 as well, for the two kernels that work with candidate slots (in
+// absmax_select_kernel the reference and five rows are two rounds of its three buffers); chosen for 5, 9, 10, 17 to 20 and 25 workers of long rows (encode + decode at d = 2^25: M = 5 293 us
 // in a group of 8, 250 in one of 5; M = 9 450 in groups of 4, 414 in groups of 5; M = 10 476 / 433; d = 2^24: M = 20
 // 425 / 411, M = 25 534 in groups of 8, 515).
 inline int pick_workers_per_block(uint32_t M, uint64_t tiles, double repeat_cost, int mc_max = 8, bool fives = false) {
@@ -2270,8 +2307,8 @@ hipError_t quantize_candidates_dispatch(const CodecShape& c, uint32_t iter, cons
                                         uint32_t* codes, hipStream_t s) {
   const uint64_t tiles = (c.d / kWaveTileElements + kWavesPerBlock - 1) / kWavesPerBlock;  // workgroups of 4 wavefront tiles
   const uint64_t slot_tiles = c.scale_l2 ? c.d / kTreeChunk * (kTreeChunk / kWaveTileElements) : c.d / kWaveTileElements;
-  const int mc = pick_workers_per_block(c.M, tiles, 0.0, 8);  // (no reference to share between more: M = 16, d = 2^24 387 us
-                                                                       // per iteration with 16, 373 with 8)
+  const int mc = pick_workers_per_block(c.M, tiles, 0.01, 8, true);  // (no reference to share between more; as
+                                                                             // absmax_select_kernel's but for the cost of a repeated row)
 #define TNG_QC(MC)                                                                                                   \
   hipLaunchKernelGGL((quantize_candidates_kernel<NORM, MC>),                                                           \
                      dim3((uint32_t)tiles, (c.M + MC - 1) / MC), dim3(kBlock), 0,             \
@@ -2279,6 +2316,7 @@ hipError_t quantize_candidates_dispatch(const CodecShape& c, uint32_t iter, cons
                      scales, cs.slots, codes, c.d, c.words, slot_tiles, c.M, c.eps, c.k0, c.k1, iter, cs.use_slots, cs.select_ok)
   switch (mc) {
     case 8: TNG_QC(8); break;
+    case 5: TNG_QC(5); break;
     case 4: TNG_QC(4); break;
     case 2: TNG_QC(2); break;
     default: TNG_QC(1); break;

@@ -226,3 +226,21 @@ def test_seeded_shapes_and_distributions(case):
     norm = B.NORM_SUB if case % 2 == 0 else B.NORM_NONE
     g = (v + gref[None, :]).contiguous() if norm == B.NORM_SUB else v.contiguous()
     _check(M, d, norm, g, gref, gref, int(rng.integers(0, 1000)), f"seeded {case} (kind {kind})", seed=int(rng.integers(0, 2 ** 40)))
+
+
+def test_slots_filled_to_their_edges():
+    # tiles that hold exactly k candidates: the quantise pass takes the first 63 with the count, the next 64 by a second
+    # load, and codes a tile with more than 127 from g
+    M, d = 5, 14 * (1 << 20)
+    gen = torch.Generator(device=DEV).manual_seed(8)
+    v = torch.zeros((M, d), device=DEV)
+    v[:, ::1024 * 128] = 1.0  # every tile of the sample: its largest element is the row's
+    counts = (1, 2, 62, 63, 64, 65, 126, 127, 128, 129)
+    for m in range(M):
+        for i, k in enumerate(counts):
+            tile = 1 + 3 * i + 31 * m
+            at = torch.randperm(1024, generator=gen, device=DEV)[:k] + 1024 * tile
+            v[m, at] = torch.randint(0, 2, (k,), generator=gen, device=DEV).float() * 2 - 1
+    gref = torch.zeros(d, device=DEV)
+    codes, scales = _check(M, d, B.NORM_SUB, v, gref, gref, 6, "slots filled to their edges")
+    assert np.all(scales == 1.0)
