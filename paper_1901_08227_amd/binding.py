@@ -1,5 +1,6 @@
 """ctypes binding of libtng (include/tng.h).  Argument marshalling only: every step of the
-iteration runs in the HIP kernels of the library; torch tensors are used as device memory.
+iteration runs in the HIP kernels of the library; torch tensors are used as device memory.  The calls of
+a training loop are marshalled by a native function (csrc/tng_call.cpp) where their arguments are plain.
 
 The module-level functions carry the names of the C entry points and take a context handle
 plus torch CUDA tensors; `Context` owns the workspace and keeps problem data alive.
@@ -8,12 +9,15 @@ There is no fallback: if the built library is missing, loading raises.
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libtng.so")
+CALL_PATH = os.path.join(_HERE, "tng_call.so")
 
 TNG_OK = 0
 TNG_ERR_INVALID_ARG, TNG_ERR_BAD_STATE, TNG_ERR_WORKSPACE, TNG_ERR_UNSUPPORTED, TNG_ERR_HIP = 1, 2, 3, 4, 5
@@ -42,11 +46,23 @@ class TngError(RuntimeError):
 
 
 _lib = None
+_call = None      # the extension's call(); loaded with the library
+_address = None   # {entry point: its address} of those that go through it
+
+
+def _load_call():
+    """tng_call.call; raises if it has not been built."""
+    if not os.path.exists(CALL_PATH):
+        raise RuntimeError(f"libtng is not built: {CALL_PATH} is missing; run __graft_entry__.build()")
+    loader = importlib.machinery.ExtensionFileLoader("tng_call", CALL_PATH)
+    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("tng_call", loader))
+    loader.exec_module(module)
+    return module.call
 
 
 def lib() -> ctypes.CDLL:
     """The loaded library; raises if it has not been built (python -m paper_1901_08227_amd.build)."""
-    global _lib
+    global _lib, _call, _address
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(f"libtng is not built: {LIB_PATH} is missing; run __graft_entry__.build()")
@@ -85,6 +101,10 @@ def lib() -> ctypes.CDLL:
         for name, argtypes in sigs.items():
             fn = getattr(L, name)
             fn.restype, fn.argtypes = ctypes.c_int, argtypes
+        _call = _load_call()
+        _address = {name: ctypes.cast(getattr(L, name), vp).value
+                    for name in ("tng_local_grad", "tng_normalize_encode", "tng_decode_aggregate", "tng_update_reference",
+                                 "tng_step")}
         _lib = L
     return _lib
 
@@ -271,31 +291,49 @@ class Context:
         _check(lib().tng_minibatch_indices(self.handle, it, _ptr(idx, torch.int32, self.M * self.batch, "idx")),
                "tng_minibatch_indices")
 
+    # (each first by the native function; None: not a plain case, ctypes converts the arguments or says what is wrong)
     def local_grad(self, it, w, g):
-        _check(lib().tng_local_grad(self.handle, it, _ptr(w, torch.float32, self.d, "w"),
-                                    _ptr(g, torch.float32, self.M * self.d, "g")), "tng_local_grad")
+        status = _call(_address["tng_local_grad"], self.handle.value, it, "dg", self.d, self.M, self.words, w, g)
+        if status is None:
+            status = lib().tng_local_grad(self.handle, it, _ptr(w, torch.float32, self.d, "w"),
+                                          _ptr(g, torch.float32, self.M * self.d, "g"))
+        _check(status, "tng_local_grad")
 
     def normalize_encode(self, it, g, gref, codes, scales):
-        _check(lib().tng_normalize_encode(
-            self.handle, it, _ptr(g, torch.float32, self.M * self.d, "g"), _ptr(gref, torch.float32, self.d, "gref"),
-            _ptr(codes, torch.int32, self.M * self.words, "codes"), _ptr(scales, torch.float32, self.M, "scales")),
-            "tng_normalize_encode")
+        status = _call(_address["tng_normalize_encode"], self.handle.value, it, "gdcs", self.d, self.M, self.words, g, gref,
+                       codes, scales)
+        if status is None:
+            status = lib().tng_normalize_encode(
+                self.handle, it, _ptr(g, torch.float32, self.M * self.d, "g"), _ptr(gref, torch.float32, self.d, "gref"),
+                _ptr(codes, torch.int32, self.M * self.words, "codes"), _ptr(scales, torch.float32, self.M, "scales"))
+        _check(status, "tng_normalize_encode")
 
     def decode_aggregate(self, codes, scales, gref, vbar):
-        _check(lib().tng_decode_aggregate(
-            self.handle, _ptr(codes, torch.int32, self.M * self.words, "codes"),
-            _ptr(scales, torch.float32, self.M, "scales"), _ptr(gref, torch.float32, self.d, "gref"),
-            _ptr(vbar, torch.float32, self.d, "vbar")), "tng_decode_aggregate")
+        status = _call(_address["tng_decode_aggregate"], self.handle.value, None, "csdd", self.d, self.M, self.words, codes,
+                       scales, gref, vbar)
+        if status is None:
+            status = lib().tng_decode_aggregate(
+                self.handle, _ptr(codes, torch.int32, self.M * self.words, "codes"),
+                _ptr(scales, torch.float32, self.M, "scales"), _ptr(gref, torch.float32, self.d, "gref"),
+                _ptr(vbar, torch.float32, self.d, "vbar"))
+        _check(status, "tng_decode_aggregate")
 
     def update_reference(self, it, vbar, gref):
-        _check(lib().tng_update_reference(self.handle, it, _ptr(vbar, torch.float32, self.d, "vbar"),
-                                          _ptr(gref, torch.float32, self.d, "gref")), "tng_update_reference")
+        status = _call(_address["tng_update_reference"], self.handle.value, it, "dd", self.d, self.M, self.words, vbar, gref)
+        if status is None:
+            status = lib().tng_update_reference(self.handle, it, _ptr(vbar, torch.float32, self.d, "vbar"),
+                                                _ptr(gref, torch.float32, self.d, "gref"))
+        _check(status, "tng_update_reference")
 
     def step(self, it, w, gref, g, codes, scales, vbar):
-        _check(lib().tng_step(
-            self.handle, it, _ptr(w, torch.float32, self.d, "w"), _ptr(gref, torch.float32, self.d, "gref"),
-            _ptr(g, torch.float32, self.M * self.d, "g"), _ptr(codes, torch.int32, self.M * self.words, "codes"),
-            _ptr(scales, torch.float32, self.M, "scales"), _ptr(vbar, torch.float32, self.d, "vbar")), "tng_step")
+        status = _call(_address["tng_step"], self.handle.value, it, "ddgcsd", self.d, self.M, self.words, w, gref, g, codes,
+                       scales, vbar)
+        if status is None:
+            status = lib().tng_step(
+                self.handle, it, _ptr(w, torch.float32, self.d, "w"), _ptr(gref, torch.float32, self.d, "gref"),
+                _ptr(g, torch.float32, self.M * self.d, "g"), _ptr(codes, torch.int32, self.M * self.words, "codes"),
+                _ptr(scales, torch.float32, self.M, "scales"), _ptr(vbar, torch.float32, self.d, "vbar"))
+        _check(status, "tng_step")
 
 
 # Module-level spellings of the C entry points (same names, same argument order).

@@ -1,4 +1,4 @@
-"""Builds libtng.so for gfx950 with hipcc, in-tree (next to this file).
+"""Builds libtng.so for gfx950 with hipcc and the binding's call extension tng_call.so with g++, in-tree (next to this file).
 
 Flags that matter for reproducible codes: -ffp-contract=off keeps every fp32 operation of the
 normalise / threshold / decode path a separately rounded IEEE operation (hipcc would otherwise
@@ -13,6 +13,7 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 import tempfile
 from concurrent.futures import ThreadPoolExecutor
 
@@ -20,6 +21,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtng.so")
+CALL = os.path.join(HERE, "tng_call.so")
 SOURCES = ["tng_api.hip", "tng_codec.hip", "tng_grad.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -27,6 +29,18 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function", "-Wno-unknown-attributes",
 ]
+
+
+def call_command() -> list:
+    """The compiler line of the call extension: host code against the installed torch and Python headers."""
+    import torch
+
+    torch_dir = os.path.dirname(torch.__file__)
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            "-isystem", os.path.join(torch_dir, "include"), "-isystem", sysconfig.get_paths()["include"],
+            os.path.join(CSRC, "tng_call.cpp"), "-L", os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10",
+            "-o", CALL]
 
 
 def build(verbose: bool = True) -> str:
@@ -41,8 +55,16 @@ def build(verbose: bool = True) -> str:
             subprocess.run(cmd, check=True)
             return obj
 
-        with ThreadPoolExecutor(max_workers=len(SOURCES)) as pool:
+        def build_call():
+            cmd = call_command()
+            if verbose:
+                print(" ".join(cmd), flush=True)
+            subprocess.run(cmd, check=True)
+
+        with ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as pool:
+            call = pool.submit(build_call)
             objs = list(pool.map(compile_one, SOURCES))
+            call.result()
         cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
         if verbose:
             print(" ".join(cmd), flush=True)

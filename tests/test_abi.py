@@ -181,3 +181,29 @@ def test_binding_refuses_cpu_tensors():
     import torch
     with pytest.raises(TypeError):
         B._ptr(torch.zeros(4), torch.float32, 4, "g")
+
+
+def test_native_call_leaves_what_is_not_plain_to_ctypes():
+    import numpy as np
+    import torch
+    B.lib()
+    count = ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_void_p, ctypes.c_uint32, ctypes.c_void_p, ctypes.c_void_p)
+    seen = []
+    entry = count(lambda h, it, a, b: seen.append((h, it, a, b)) or 7)
+    at = ctypes.cast(entry, ctypes.c_void_p).value
+    # None is a null pointer, an iteration number is taken modulo 2^32 (as ctypes does)
+    assert B._call(at, 4096, 5, "dg", 4, 2, 1, None, None) == 7
+    assert B._call(at, 4096, -1, "dg", 4, 2, 1, None, None) == 7
+    assert B._call(at, 4096, (1 << 32) + 3, "dg", 4, 2, 1, None, None) == 7
+    assert seen == [(4096, 5, None, None), (4096, (1 << 32) - 1, None, None), (4096, 3, None, None)]
+    del seen[:]
+    # nothing is called with a host tensor, a list, a subclass, a closed context or an iteration that is no plain int
+    t = torch.zeros(8)
+    for a, b, h, it in ((t, None, 4096, 0), ([1.0], None, 4096, 0), (None, np.zeros(8), 4096, 0),
+                        (torch.nn.Parameter(t), None, 4096, 0), (t.to("meta"), None, 4096, 0), (None, None, None, 0),
+                        (None, None, 4096, 1.0), (None, None, 4096, True), (None, None, 4096, np.int64(1))):
+        assert B._call(at, h, it, "dg", 4, 2, 1, a, b) is None
+    assert seen == []
+    for bad in (("d", None, None), ("ddd", None, None), (b"dg", None, None)):
+        with pytest.raises(TypeError):
+            B._call(at, 4096, 0, bad[0], 4, 2, 1, *bad[1:])
