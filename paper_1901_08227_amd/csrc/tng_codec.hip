@@ -671,6 +671,8 @@ constexpr int kCandCap = 127;         // candidates a slot holds; word 0 of a sl
 constexpr int kSlotEntries = 128;     // 32-bit words per slot: 512 bytes per worker and wavefront tile
 constexpr uint32_t kSampleStride = 128;  // the sample: every 128th wavefront tile of a row
 constexpr uint32_t kCandPosMask = 0x3FFu;  // low 10 bits of a candidate word: position within the tile
+constexpr uint32_t kChunkPosMask = 0xFFFu;  // the l2 scale's slots are per worker and chunk of four tiles: 12 bits
+constexpr uint32_t kNoSlot = 255u;         // in the place of such a slot's count: it overflowed, or the row has none
 
 // The sample of a row taken before the scale pass: over every kSampleStride-th wavefront tile, the largest
 // |v| (the lower bound R^ of the row's scale) and the sum of |v|.  Their ratio, mean |v| / R^, is the share
@@ -804,9 +806,9 @@ __device__ __forceinline__ float candidate_factor(float r_hat) {
   return r_hat >= 0x1p-90f ? (1.0f / r_hat) * (0x1p32f * (1.0f + 0x1p-20f)) : INFINITY;
 }
 
-// The candidates of one float4 per lane (load j of the tile) go behind the base - 1 staged before.  FEW: candidates
+// The candidates of one float4 per lane (load j of the tile) go to number base of the staging area and behind it.  FEW: candidates
 // are rare, most float4 of a whole wavefront hold none.
-template <bool FEW>
+template <bool FEW, uint32_t POS_MASK>
 __device__ __forceinline__ void stage_candidates(uint32_t* stage, uint32_t* draws, const float4& v, const U32x4& rnd,
                                                  float c1, int j, int lane, uint32_t& base) {
   const float vv[4] = {v.x, v.y, v.z, v.w};
@@ -824,9 +826,70 @@ __device__ __forceinline__ void stage_candidates(uint32_t* stage, uint32_t* draw
     // condition would end the basic block at every element, and the sixteen elements of a lane could not
     // overlap.  Candidates beyond the slot's capacity (the slot is then not used) share one word.
     const uint32_t at = cand[c] ? min(pos, kStageSink) : kStageDump + (uint32_t)lane;
-    stage[at] = (__float_as_uint(vv[c]) & ~kCandPosMask) | (uint32_t)(256 * j + c) | 4u * (uint32_t)lane;
+    stage[at] = (__float_as_uint(vv[c]) & ~POS_MASK) | (uint32_t)(256 * j + c) | 4u * (uint32_t)lane;
     draws[at] = rr[c];
     base += (uint32_t)__builtin_popcountll(mask);
+  }
+}
+
+// What goes into the slot for a candidate is not v but tau = |v| / u (u its 24-bit draw), the scale up to which it codes
+// non-zero, to what its position leaves of the significand: the quantise pass then compares the row's scale with tau and
+// needs neither the draw nor the value.  u = 0 gives an infinite tau (or none, for v = 0), which the quantise pass takes
+// as "look at the value".
+template <uint32_t POS_MASK>
+__device__ __forceinline__ uint32_t slot_entry(uint32_t value_word, uint32_t draw) {
+  constexpr uint32_t kMagnitude = 0x7FFFFFFFu & ~POS_MASK;
+  const float tau = __uint_as_float(value_word & kMagnitude) * (__builtin_amdgcn_rcpf((float)(draw >> 8)) * 0x1p24f);
+  return (__float_as_uint(tau) & kMagnitude) | (value_word & (0x80000000u | POS_MASK));
+}
+
+// How it reads there.  The entry brackets tau: its significand was cut to K = 23 - (bits of the position) bits twice (the
+// value's, then tau's own) and its arithmetic is good to 2^-22, so tau lies in [lo (1 - 2^-22), hi (1 + 2^-K + 2^-21)].
+// ternary_code's level [u < fl(|v| fl(1 / R))] is 1 for R <= tau (1 - 2^-21) and 0 for R >= tau (1 + 2^-21) (the two
+// roundings move |v| / R by less than 2^-22 relatively, 1 / R > 2^126 included), so only a scale inside the widened bracket
+// -- three candidates in ten thousand with 13 bits, a dozen with 11 -- needs the value and the draw.
+template <uint32_t POS_MASK>
+__device__ __forceinline__ int entry_codes_one(uint32_t e, float r) {  // (u = 0: tau is infinite or no number, and not bounded)
+  return (int)((e & 0x7F800000u) != 0x7F800000u) & (int)(r <= __uint_as_float(e & 0x7FFFFFFFu & ~POS_MASK) * (1.0f - 0x1p-19f));
+}
+template <uint32_t POS_MASK>
+__device__ __forceinline__ int entry_codes_zero(uint32_t e, float r) {  // (false where tau is not bounded)
+  constexpr float kAbove = POS_MASK == kCandPosMask ? 1.0f + 0x1p-12f : 1.0f + 0x1p-10f;
+  return (int)(r >= __uint_as_float((e & 0x7FFFFFFFu) | POS_MASK) * kAbove);
+}
+// The code of element coord of worker m from its value.
+template <int NORM>
+__device__ __forceinline__ uint32_t code_of_element(const GradRows& g, const float4* ref4, uint64_t coord, uint32_t m, float r,
+                                                    uint32_t iter, uint32_t k0, uint32_t k1) {
+  const U32x4 rnd = philox4x32_10((uint32_t)(coord >> 2), m, iter, 0u, k0, k1);
+  const uint32_t sel = (uint32_t)coord & 3u;
+  const uint32_t word = sel == 0u ? rnd.x : sel == 1u ? rnd.y : sel == 2u ? rnd.z : rnd.w;
+  float r1 = 0.f;
+  if (NORM == kNormSub) r1 = reinterpret_cast<const float*>(ref4)[coord];
+  return ternary_code(normalize_w<NORM>(g.base[(uint64_t)m * g.pitch + coord], r1, 1.f, 0.f), 1.0f / r, word);
+}
+// The codes of a wavefront's tile of worker m, which has no slot, into its 64 words of LDS.  (Two float4 at a time: all four
+// need more than the 64 registers of eight wavefronts per SIMD.)
+template <int NORM>
+__device__ __forceinline__ void code_tile(lds_u8* bytes, const GradRows& g, const float4* ref4, const float4* ref24, uint64_t tile,
+                                          uint32_t m, int lane, float r, float eps, uint32_t iter, uint32_t k0, uint32_t k1) {
+  constexpr int L = kLoadsPerLane;
+  const float inv_r = 1.0f / r;
+#pragma unroll 1
+  for (int j = 0; j < L; j += 2) {
+    const uint64_t iv = tile * (kWave * L) + (uint64_t)(j * kWave + lane);
+    const v4f_u_t* row = g.row(m) + iv;
+    float4 v[2] = {load_row_stream(row), load_row_stream(row + kWave)};
+    RefTile<NORM> rt[2];
+    rt[0].load(ref4, ref24, iv, eps);
+    rt[1].load(ref4, ref24, iv + kWave, eps);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) v[k] = normalize4<NORM, false>(v[k], rt[k], 0.f);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const U32x4 rnd = philox4x32_10((uint32_t)iv + (uint32_t)(k * kWave), m, iter, 0u, k0, k1);
+      bytes[(j + k) * kWave + lane] = (uint8_t)quantize4<2>(v[k], inv_r, rnd);
+    }
   }
 }
 
@@ -842,19 +905,11 @@ __device__ __forceinline__ bool write_slot(uint32_t* stage, const uint32_t* draw
   const bool fits = base <= (uint32_t)kSlotEntries;
   const uint32_t used = fits ? base : 1u;
   if (2u * (uint32_t)lane < used) {  // one store instruction covers the slot: 8 bytes per lane, device-coherent policy
-    // What goes into the slot for a candidate is not v but tau = |v| / u (u its 24-bit draw), the scale up
-    // to which it codes non-zero, to 13 bits of the significand: the quantise pass then compares the row's
-    // scale with tau and needs neither the draw nor the value.  The reciprocal is taken here, for the two
-    // candidates of the lane, not for every element of the tile.  u = 0 gives an infinite tau (or none, for
-    // v = 0), which the quantise pass takes as "look at the value".
+    // The reciprocals are taken here, for the two candidates of the lane, not for every element of the tile.
     const uint2 vw = *reinterpret_cast<const uint2*>(&stage[2 * lane]);
     const uint2 dw = *reinterpret_cast<const uint2*>(&draws[2 * lane]);
-    auto entry = [](uint32_t value_word, uint32_t draw) {
-      const float tau = __uint_as_float(value_word & 0x7FFFFC00u) * (__builtin_amdgcn_rcpf((float)(draw >> 8)) * 0x1p24f);
-      return (__float_as_uint(tau) & 0x7FFFFC00u) | (value_word & 0x800003FFu);
-    };
-    const uint32_t e0 = lane == 0 ? vw.x : entry(vw.x, dw.x);  // word 0 of the slot is the count
-    const uint64_t two = ((uint64_t)entry(vw.y, dw.y) << 32) | e0;
+    const uint32_t e0 = lane == 0 ? vw.x : slot_entry<kCandPosMask>(vw.x, dw.x);  // word 0 of the slot is the count
+    const uint64_t two = ((uint64_t)slot_entry<kCandPosMask>(vw.y, dw.y) << 32) | e0;
     uint64_t* slot = reinterpret_cast<uint64_t*>(slot_words);
     __hip_atomic_store(slot + (uint32_t)lane, two, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
@@ -942,7 +997,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
       amax = max3_abs(v.z, v.w, max3_abs(v.x, v.y, amax));
       const uint64_t iv = tile * kWaveTile + (uint64_t)(j * kWave + lane);
       const U32x4 rnd = philox4x32_10((uint32_t)iv, m, iter, 0u, k0, k1);
-      stage_candidates<false>(stage[wave], draws[wave], v, rnd, c1[mm], j, lane, base);
+      stage_candidates<false, kCandPosMask>(stage[wave], draws[wave], v, rnd, c1[mm], j, lane, base);
     }
     mx[mm] = fmaxf(mx[mm], amax);
     if (!write_slot(stage[wave], draws[wave], base, lane, slots + ((uint64_t)m * ntiles + tile) * kSlotEntries)) nover += 1u;
@@ -1014,27 +1069,32 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
   }
 }
 
-// The reduction of the scale pass's partial maxima (workgroups 0 .. finish - 1, one per worker: M, or 0 where the scale
-// is no maximum) and, in one more
-// workgroup, whether the slots are worth using: at most one tile in fifty may have overflowed (such tiles go
-// through a plain, unpipelined form of the ordinary path).  use_slots[0] = 1 or 0.
-__global__ __launch_bounds__(kBlock) void absmax_finish_vote_kernel(const float* __restrict__ partials, uint32_t nblocks,
-                                                                    uint32_t M, uint32_t finish, float* __restrict__ scales,
-                                                                    const uint32_t* __restrict__ overflowed, uint32_t n,
-                                                                    uint64_t tiles_in_all,
-                                                                    uint32_t* __restrict__ use_slots) {
-  if (blockIdx.x < finish) {
-    absmax_finish_worker(partials, nblocks, M, scales, blockIdx.x);
-    return;
-  }
+// Whether the slots are worth using, by one workgroup: at most one in fifty may have overflowed (such tiles go through a
+// plain, unpipelined form of the ordinary path).  use_slots[0] = 1 or 0.
+struct SlotVote {
+  const uint32_t* overflowed;  // n counts
+  uint32_t n;
+  uint64_t slots_in_all;
+  uint32_t* use_slots;
+};
+__device__ __forceinline__ void vote_on_slots(const SlotVote& v) {
   __shared__ unsigned long long sum;
   if (threadIdx.x == 0) sum = 0ull;
   __syncthreads();
   unsigned long long mine = 0;
-  for (uint32_t i = threadIdx.x; i < n; i += kBlock) mine += overflowed[i];
+  for (uint32_t i = threadIdx.x; i < v.n; i += kBlock) mine += v.overflowed[i];
   atomicAdd(&sum, mine);
   __syncthreads();
-  if (threadIdx.x == 0) use_slots[0] = sum * 50ull <= tiles_in_all ? 1u : 0u;
+  if (threadIdx.x == 0) v.use_slots[0] = sum * 50ull <= v.slots_in_all ? 1u : 0u;
+}
+
+// The reduction of the scale pass's partial maxima (workgroups 0 .. M - 1, one per worker) and the vote.
+__global__ __launch_bounds__(kBlock) void absmax_finish_vote_kernel(const float* __restrict__ partials, uint32_t nblocks,
+                                                                    uint32_t M, float* __restrict__ scales, SlotVote vote) {
+  if (blockIdx.x < M)
+    absmax_finish_worker(partials, nblocks, M, scales, blockIdx.x);
+  else
+    vote_on_slots(vote);
 }
 
 // The packed codes of a tile from its slots.  One wavefront per tile as in the quantiser; the words of a
@@ -1050,8 +1110,8 @@ __global__ __launch_bounds__(kBlock) void absmax_finish_vote_kernel(const float*
 template <int NORM, int MC>
 __global__ __launch_bounds__(kBlock, 8) void quantize_candidates_kernel(
     GradRows g, const float4* __restrict__ ref4, const float4* __restrict__ ref24, const float* __restrict__ scales,
-    const uint32_t* __restrict__ slots, uint32_t* __restrict__ codes, uint64_t d, uint64_t words, uint64_t slot_tiles,
-    uint32_t M, float eps, uint32_t k0, uint32_t k1, uint32_t iter, const uint32_t* __restrict__ use_slots,
+    const uint32_t* __restrict__ slots, uint32_t* __restrict__ codes, uint64_t d, uint64_t words, uint32_t M,
+    float eps, uint32_t k0, uint32_t k1, uint32_t iter, const uint32_t* __restrict__ use_slots,
     const uint32_t* __restrict__ select_ok) {
   constexpr int L = kLoadsPerLane;
   constexpr int WPW = kWave * L * 4 * 2 / 32;  // 64 packed words per wavefront tile
@@ -1080,48 +1140,25 @@ __global__ __launch_bounds__(kBlock, 8) void quantize_candidates_kernel(
 #pragma unroll
   for (int mm = 0; mm < MC; ++mm) lds.b32[mm][wave][lane] = 0u;
   wave_lds_fence();
-  // The entry brackets tau = |v| / u: its significand was cut to 13 bits twice (the value's, then tau's own) and its
-  // arithmetic is good to 2^-22, so tau lies in [lo (1 - 2^-22), hi (1 + 2^-13 + 2^-21)].  ternary_code's level
-  // [u < fl(|v| fl(1 / R))] is 1 for R <= tau (1 - 2^-21) and 0 for R >= tau (1 + 2^-21) (the two roundings move |v| / R by
-  // less than 2^-22 relatively, 1 / R > 2^126 included), so only a scale inside the widened bracket -- three candidates in
-  // ten thousand -- needs the value and the draw.
-  auto codes_one = [&](uint32_t e, float r) {  // (u = 0: tau is infinite or no number, and not bounded)
-    return (int)((e & 0x7F800000u) != 0x7F800000u) & (int)(r <= __uint_as_float(e & 0x7FFFFC00u) * (1.0f - 0x1p-19f));
-  };
-  auto codes_zero = [&](uint32_t e, float r) {  // (false where tau is not bounded)
-    return (int)(r >= __uint_as_float((e & 0x7FFFFC00u) | kCandPosMask) * (1.0f + 0x1p-12f));
-  };
   auto put = [&](uint32_t slot, uint32_t e, uint32_t code) {
     atomicOr(&lds.b32[slot][wave][(e & kCandPosMask) >> 4], code << (2u * (e & 15u)));
   };
   // Bit mm: worker m0 + mm has more candidates than are in first[mm], or no slot here (its row is too dense for slots,
-  // this one overflowed, or the tile lies beyond the last whole chunk of the l2 scale's sums); in undecided, this lane's
-  // candidate of that worker needs its value.  All three are rare and come after the loop, in code that is there once and
+  // or this one overflowed); in undecided, this lane's candidate of that worker needs its value.  All three are rare and come after the loop, in code that is there once and
   // not once per worker.
   uint32_t long_slots = 0u, no_slots = 0u, undecided = 0u;
 #pragma unroll
   for (int mm = 0; mm < MC; ++mm) {
     const uint32_t e = first[mm], n = __builtin_amdgcn_readfirstlane(e);
     const bool live = m0 + (uint32_t)mm < m_end && R[mm] != 0.f;  // (R = 0: every element codes to 0)
-    const bool slot = ok[mm] != 0u && tile < slot_tiles && n <= (uint32_t)kCandCap;
+    const bool slot = ok[mm] != 0u && n <= (uint32_t)kCandCap;
     no_slots |= (live && !slot ? 1u : 0u) << mm;
     long_slots |= (live && slot && n >= (uint32_t)kWave ? 1u : 0u) << mm;
     const int in = (uint32_t)lane - 1u < (live && slot ? n : 0u);  // (lane 0 holds the count)
-    const int one = in & codes_one(e, R[mm]);
+    const int one = in & entry_codes_one<kCandPosMask>(e, R[mm]);
     if (one) put((uint32_t)mm, e, 1u | ((e >> 31) << 1));
-    undecided |= (uint32_t)(in & ~one & ~codes_zero(e, R[mm])) << mm;
+    undecided |= (uint32_t)(in & ~one & ~entry_codes_zero<kCandPosMask>(e, R[mm])) << mm;
   }
-  auto code_from_value = [&](uint32_t mm, uint32_t m, uint32_t e, float r) {
-    const uint32_t pos = e & kCandPosMask;
-    const uint64_t coord = tile * (uint64_t)(kWave * L * 4) + pos;
-    const U32x4 rnd = philox4x32_10((uint32_t)(coord >> 2), m, iter, 0u, k0, k1);
-    const uint32_t sel = pos & 3u;
-    const uint32_t word = sel == 0u ? rnd.x : sel == 1u ? rnd.y : sel == 2u ? rnd.z : rnd.w;
-    float r1 = 0.f;
-    if (NORM == kNormSub) r1 = reinterpret_cast<const float*>(ref4)[coord];
-    const uint32_t code = ternary_code(normalize_w<NORM>(g.base[(uint64_t)m * g.pitch + coord], r1, 1.f, 0.f), 1.0f / r, word);
-    if (code != 0u) put(mm, e, code);
-  };
   if (long_slots != 0u || __builtin_amdgcn_ballot_w64(undecided != 0u) != 0ull) {
 #pragma unroll 1
     for (uint32_t mm = 0; mm < m_end - m0; ++mm) {
@@ -1132,35 +1169,23 @@ __global__ __launch_bounds__(kBlock, 8) void quantize_candidates_kernel(
       const uint32_t* __restrict__ sl = slots + ((uint64_t)m * ntiles + tile) * kSlotEntries;
       const uint32_t n = sl[0], e0 = sl[lane], e1 = sl[kWave + lane];
       const float r = scales[m];
-      const int in = (int)longer & (int)((uint32_t)(kWave + lane) <= n), one = in & codes_one(e1, r);
+      const int in = (int)longer & (int)((uint32_t)(kWave + lane) <= n), one = in & entry_codes_one<kCandPosMask>(e1, r);
       if (one) put(mm, e1, 1u | ((e1 >> 31) << 1));
-      const int open1 = in & ~one & ~codes_zero(e1, r);
+      const int open1 = in & ~one & ~entry_codes_zero<kCandPosMask>(e1, r);
 #pragma unroll 1
       for (int k = 0; k < 2; ++k)
-        if (k == 0 ? open : open1) code_from_value(mm, m, k == 0 ? e0 : e1, r);
+        if (k == 0 ? open : open1) {
+          const uint32_t e = k == 0 ? e0 : e1;
+          const uint32_t code = code_of_element<NORM>(g, ref4, tile * kWaveTileElements + (e & kCandPosMask), m, r, iter, k0, k1);
+          if (code != 0u) put(mm, e, code);
+        }
     }
   }
 #pragma unroll 1
   for (uint32_t mm = 0; no_slots >> mm != 0u; ++mm) {  // these workers' tiles go through the ordinary path
     if (((no_slots >> mm) & 1u) == 0u) continue;
     const uint32_t m = m0 + mm;
-    const float inv_r = 1.0f / scales[m];
-#pragma unroll 1
-    for (int j = 0; j < L; j += 2) {  // (two float4 at a time: all four need more than the 64 registers of eight wavefronts)
-      const uint64_t iv = tile * (kWave * L) + (uint64_t)(j * kWave + lane);
-      const v4f_u_t* row = g.row(m) + iv;
-      float4 v[2] = {load_row_stream(row), load_row_stream(row + kWave)};
-      RefTile<NORM> rt[2];
-      rt[0].load(ref4, ref24, iv, eps);
-      rt[1].load(ref4, ref24, iv + kWave, eps);
-#pragma unroll
-      for (int k = 0; k < 2; ++k) v[k] = normalize4<NORM, false>(v[k], rt[k], 0.f);
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        const U32x4 rnd = philox4x32_10((uint32_t)iv + (uint32_t)(k * kWave), m, iter, 0u, k0, k1);
-        lds.b8[mm][wave][(j + k) * kWave + lane] = (uint8_t)quantize4<2>(v[k], inv_r, rnd);
-      }
-    }
+    code_tile<NORM>(lds.b8[mm][wave], g, ref4, ref24, tile, m, lane, scales[m], eps, iter, k0, k1);
   }
   flush_packed<WPW, MC>(lds, wave, lane, codes, words, word_base, m0, m_end - m0);
 }
@@ -1946,16 +1971,20 @@ __global__ __launch_bounds__(kBlock) void l2_chunk_kernel(GradRows g, const floa
 // absmax_select_kernel; here hardly an element is one: the scale is sqrt(d) times the typical |v|).  A workgroup takes
 // a chunk of up to kL2SelectWorkers workers, its wavefronts a worker each in turn; the chunk's reference is in LDS, and the
 // lane sums of all workers are added up in order at the end, a worker per lane (by one lane per worker and wavefront, as
-// above, these additions are as many instructions as all others).  Encode + decode at d = 2^24, M = 16: 500 us by two
-// passes, 366 this way (this kernel 255 for 1.14 GB: the vector unit's time for draws, squares and tests as much as
-// memory's).  A wavefront's fetches, a tile of a worker each, rotate
+// above, these additions are as many instructions as all others).  A wavefront's fetches, a tile of a worker each, rotate
 // through three buffers.
+// A slot is per worker and chunk (its candidates gathered over the four tiles), written only if it holds something, and
+// the counts of the workgroup's workers are one word: a slot per tile, its count in it, was a quarter of a million writes of 8
+// bytes among the reads at d = 2^24, M = 16, and cost this kernel 20 of its 260 us and the quantise pass half its time.
+// Encode + decode there: 500 us by two passes, 345 with a slot per tile, 303 this way (this kernel 234 to 250 for 1.14 GB: the
+// vector unit's time for draws, squares and tests, 160 us, as much as memory's, 181).
 constexpr int kL2SelectWorkers = 8;
 template <int NORM>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) void l2_select_kernel(
-    GradRows g, const float4* __restrict__ ref4, double* __restrict__ chunk_sums, uint64_t ntiles, uint64_t nchunks,
+    GradRows g, const float4* __restrict__ ref4, double* __restrict__ chunk_sums, uint64_t chunks, uint64_t nchunks,
     uint32_t M, const float* __restrict__ sample_max, const uint32_t* __restrict__ select_ok,
-    uint32_t* __restrict__ slots, uint32_t* __restrict__ overflowed, uint32_t k0, uint32_t k1, uint32_t iter) {
+    uint32_t* __restrict__ slots, uint64_t* __restrict__ counts, uint32_t* __restrict__ overflowed, uint32_t k0, uint32_t k1,
+    uint32_t iter) {
   static_assert(NORM == kNormNone || NORM == kNormSub, "the coder that reads g once: no divisor reference");
   constexpr int L = kLoadsPerLane;                       // rows of 64 float4 per tile
   constexpr int T = kTreeChunk / (int)kWaveTileElements;  // tiles per chunk
@@ -1965,7 +1994,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
   __shared__ __attribute__((aligned(16))) uint32_t draws[kWavesPerBlock][kStageWords];
   __shared__ __attribute__((aligned(16))) float4 refs[NORM == kNormSub ? V : 1];
   __shared__ __attribute__((aligned(16))) double sums[kL2SelectWorkers][kSumStride];
-  __shared__ uint32_t over[kWavesPerBlock];
+  __shared__ uint8_t found[kL2SelectWorkers];  // candidates of each worker in this chunk, or kNoSlot
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = threadIdx.x % kWave;
   const uint64_t chunk = blockIdx.x;
   const uint32_t m0 = blockIdx.y * kL2SelectWorkers;
@@ -1991,18 +2020,18 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
     request(b1, 1);
   }
   __syncthreads();  // the reference is in LDS
-  uint32_t nover = 0;
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   float c1 = 0.f;
   bool select = false;
+  uint32_t base = 0;  // candidates of the worker so far
   auto work = [&](const float4 (&x)[L], uint32_t item) {
     const uint32_t mm = (uint32_t)wave + item / T * kWavesPerBlock, m = m0 + mm, t = item % T;
     if (t == 0) {
       acc[0] = acc[1] = acc[2] = acc[3] = 0.0;
       c1 = candidate_factor(sample_max[m]);
       select = select_ok[m] != 0u;
+      base = 0;
     }
-    uint32_t base = 1;  // word 0 of the slot is the count
 #pragma unroll
     for (int j = 0; j < L; ++j) {
       float4 v = x[j];
@@ -2018,12 +2047,22 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
       acc[3] = __builtin_fma(t3, t3, acc[3]);
       if (select) {  // (the same for the whole wavefront)
         const U32x4 rnd = philox4x32_10((uint32_t)(chunk * V) + at, m, iter, 0u, k0, k1);
-        stage_candidates<true>(stage[wave], draws[wave], v, rnd, c1, j, lane, base);
+        stage_candidates<true, kChunkPosMask>(stage[wave], draws[wave], v, rnd, c1, (int)t * L + j, lane, base);
       }
     }
-    if (!select || !write_slot(stage[wave], draws[wave], base, lane, slots + ((uint64_t)m * ntiles + chunk * T + t) * kSlotEntries))
-      nover += 1u;
     if (t == T - 1) {
+      const bool fits = select && base <= (uint32_t)kSlotEntries;
+      if (lane == 0) found[mm] = (uint8_t)(fits ? base : kNoSlot);
+      wave_lds_fence();
+      if (fits && 2u * (uint32_t)lane < base) {  // 8 bytes per lane, the last one whatever the staging area holds
+        const uint2 vw = *reinterpret_cast<const uint2*>(&stage[wave][2 * lane]);
+        const uint2 dw = *reinterpret_cast<const uint2*>(&draws[wave][2 * lane]);
+        uint64_t* slot = reinterpret_cast<uint64_t*>(slots + ((uint64_t)m * chunks + chunk) * kSlotEntries);
+        __hip_atomic_store(slot + (uint32_t)lane,
+                           ((uint64_t)slot_entry<kChunkPosMask>(vw.y, dw.y) << 32) | slot_entry<kChunkPosMask>(vw.x, dw.x),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      wave_lds_fence();
 #pragma unroll
       for (int i = 0; i < 4; ++i) sums[mm][4 * lane + i] = acc[i];
     }
@@ -2036,7 +2075,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
     request(b1, i + 4);
     if (i + 2 < items) work(b2, i + 2);
   }
-  if (lane == 0) over[wave] = nover;
   __syncthreads();
   if (threadIdx.x < count) {
     double total = 0.0;
@@ -2044,12 +2082,115 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
     for (int j = 0; j < kTreeLanes; ++j) total = total + sums[threadIdx.x][j];
     chunk_sums[(uint64_t)(m0 + threadIdx.x) * nchunks + chunk] = total;
   }
-  if (threadIdx.x == 0) {
-    uint32_t total = 0;
+  if (threadIdx.x == kWave) {  // (not the wavefront that adds the lane sums)
+    uint64_t all = 0;
+    uint32_t without = 0;
 #pragma unroll
-    for (int k = 0; k < kWavesPerBlock; ++k) total += over[k];
-    if (total != 0u) atomicAdd(&overflowed[blockIdx.x % kL2OverflowCounts], total);
+    for (int k = 0; k < kL2SelectWorkers; ++k) {
+      const uint32_t n = (uint32_t)k < count ? found[k] : 0u;
+      all |= (uint64_t)n << (8 * k);
+      without += n == kNoSlot ? 1u : 0u;
+    }
+    __hip_atomic_store(counts + (uint64_t)blockIdx.y * chunks + chunk, all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (without != 0u) atomicAdd(&overflowed[blockIdx.x % kL2OverflowCounts], without);
   }
+}
+
+// The same for the l2 scale, whose slots are per worker and chunk of four tiles and all but empty: hardly an element is a
+// candidate (a row expects at most sqrt(d) R / R^ of them, the 1-norm over the 2-norm).  The counts of eight workers lie in
+// eight bytes of their own, so that a pass over slots without candidates is a pass over 1/512 of their bytes and the
+// write-out.  A wavefront takes a chunk of kL2QuantWorkers workers, all their first 32 entries requested at once; tiles
+// behind the last whole chunk (at most three; the ragged one is the ordinary quantiser's) have no slots and are the last
+// row of workgroups'.
+// d = 2^24, M = 16 (67 MB of codes): 28 us with a slot per tile, 16 this way (13 at the least, 5.2 TB/s).
+constexpr int kL2QuantWorkers = 4;
+template <int NORM>
+__global__ __launch_bounds__(kBlock, 8) void quantize_l2_candidates_kernel(
+    GradRows g, const float4* __restrict__ ref4, const float* __restrict__ scales, const uint32_t* __restrict__ slots,
+    const uint8_t* __restrict__ counts, uint32_t* __restrict__ codes, uint64_t d, uint64_t words, uint64_t chunks, uint32_t M,
+    uint32_t k0, uint32_t k1, uint32_t iter, const uint32_t* __restrict__ use_slots) {
+  constexpr int MC = kL2QuantWorkers;
+  constexpr int T = kTreeChunk / (int)kWaveTileElements;  // tiles per chunk
+  constexpr int W = kTreeChunk / 16;                      // packed words per chunk: four a lane
+  static_assert(W == 4 * kWave, "one 16-byte store per worker");
+  static_assert(kL2SelectWorkers == 8 && kL2SelectWorkers % MC == 0, "the counts of eight workers are one 64-bit word");
+  __shared__ __attribute__((aligned(16))) FragmentBuffer<W, MC> lds;
+  if (use_slots[0] == 0u) return;  // too many slots overflowed: the ordinary quantiser runs instead
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = threadIdx.x % kWave;
+  const uint32_t m0 = blockIdx.y * MC, count = min((uint32_t)MC, M - m0);
+  const uint64_t chunk = (uint64_t)blockIdx.x * kWavesPerBlock + wave;
+  if (chunk >= chunks) {  // (whole wavefronts; nothing below meets the others)
+    const uint64_t tile = chunks * T + (chunk - chunks);
+    if (tile >= d / kWaveTileElements) return;
+    for (uint32_t mm = 0; mm < count; ++mm) {
+      const float r = scales[m0 + mm];
+      lds.b32[0][wave][lane] = 0u;
+      wave_lds_fence();
+      if (r != 0.f) code_tile<NORM>(lds.b8[0][wave], g, ref4, nullptr, tile, m0 + mm, lane, r, 0.f, iter, k0, k1);
+      wave_lds_fence();
+      store_word_through(codes + (uint64_t)(m0 + mm) * words + tile * kWave + (uint32_t)lane, lds.b32[0][wave][lane]);
+      wave_lds_fence();
+    }
+    return;
+  }
+  constexpr uint32_t kGroup = kL2SelectWorkers;
+  uint32_t first[MC];
+  float R[MC];
+#pragma unroll
+  for (int mm = 0; mm < MC; ++mm) {
+    const uint32_t m = min(m0 + (uint32_t)mm, M - 1);
+    first[mm] = slots[((uint64_t)m * chunks + chunk) * kSlotEntries + ((uint32_t)lane & 31u)];
+    R[mm] = scales[m];
+  }
+  const uint32_t four = *reinterpret_cast<const uint32_t*>(counts + ((uint64_t)(m0 / kGroup) * chunks + chunk) * kGroup + m0 % kGroup);
+#pragma unroll
+  for (int mm = 0; mm < MC; ++mm)
+    *reinterpret_cast<v4u_t*>(&lds.b32[mm][wave][4 * lane]) = v4u_t{0u, 0u, 0u, 0u};
+  wave_lds_fence();
+  auto put = [&](uint32_t slot, uint32_t e, uint32_t code) {
+    atomicOr(&lds.b32[slot][wave][(e & kChunkPosMask) >> 4], code << (2u * (e & 15u)));
+  };
+  // (rare, and behind the loop, as in quantize_candidates_kernel)
+  uint32_t long_slots = 0u, no_slots = 0u, undecided = 0u;
+#pragma unroll
+  for (int mm = 0; mm < MC; ++mm) {
+    const uint32_t e = first[mm], n = __builtin_amdgcn_readfirstlane(four >> (8 * mm)) & 255u;
+    const bool live = (uint32_t)mm < count && R[mm] != 0.f;  // (R = 0: every element codes to 0)
+    no_slots |= (live && n == kNoSlot ? 1u : 0u) << mm;
+    long_slots |= (live && n != kNoSlot && n > 32u ? 1u : 0u) << mm;
+    const int in = (uint32_t)lane < (live && n != kNoSlot ? min(n, 32u) : 0u);
+    const int one = in & entry_codes_one<kChunkPosMask>(e, R[mm]);
+    if (one) put((uint32_t)mm, e, 1u | ((e >> 31) << 1));
+    undecided |= (uint32_t)(in & ~one & ~entry_codes_zero<kChunkPosMask>(e, R[mm])) << mm;
+  }
+  if (long_slots != 0u || no_slots != 0u || __builtin_amdgcn_ballot_w64(undecided != 0u) != 0ull) {
+#pragma unroll 1
+    for (uint32_t mm = 0; mm < count; ++mm) {
+      const uint32_t m = m0 + mm;
+      const float r = scales[m];
+      if (((no_slots >> mm) & 1u) != 0u) {
+#pragma unroll 1
+        for (uint32_t t = 0; t < (uint32_t)T; ++t)
+          code_tile<NORM>(lds.b8[mm][wave] + t * (kWave * 4), g, ref4, nullptr, chunk * T + t, m, lane, r, 0.f, iter, k0, k1);
+        continue;
+      }
+      const bool longer = ((long_slots >> mm) & 1u) != 0u;
+      if (!longer && __builtin_amdgcn_ballot_w64((int)(undecided >> mm) & 1) == 0ull) continue;
+      const uint32_t* __restrict__ sl = slots + ((uint64_t)m * chunks + chunk) * kSlotEntries;
+      const uint32_t n = counts[((uint64_t)(m / kGroup) * chunks + chunk) * kGroup + m % kGroup];
+#pragma unroll 1
+      for (uint32_t i = (uint32_t)lane; i < n; i += kWave) {  // all of them once more: or-ing a code in twice changes nothing
+        const uint32_t e = sl[i];
+        uint32_t code = 1u | ((e >> 31) << 1);
+        if (!entry_codes_one<kChunkPosMask>(e, r))
+          code = entry_codes_zero<kChunkPosMask>(e, r)
+                     ? 0u
+                     : code_of_element<NORM>(g, ref4, chunk * kTreeChunk + (e & kChunkPosMask), m, r, iter, k0, k1);
+        if (code != 0u) put(mm, e, code);
+      }
+    }
+  }
+  flush_packed<W, MC>(lds, wave, lane, codes, words, chunk * W, m0, count);
 }
 
 // One workgroup per worker: the chunk sums come to LDS GROUPS groups at a time, in whole lines (a thread per
@@ -2064,8 +2205,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
 template <bool MEAN, int GROUPS>
 __global__ __launch_bounds__(kBlock) void tree_finish_kernel(const double* __restrict__ chunk_sums,
                                                              const float2* __restrict__ chunk_minmax,
-                                                             uint64_t nchunks, uint64_t ngroups, uint64_t d,
-                                                             float* __restrict__ out, float* __restrict__ scales) {
+                                                             uint64_t nchunks, uint64_t ngroups, uint64_t d, uint32_t M,
+                                                             float* __restrict__ out, float* __restrict__ scales, SlotVote vote) {
+  if (blockIdx.x >= M) {  // (behind l2_select_kernel only)
+    vote_on_slots(vote);
+    return;
+  }
   constexpr int kLoads = GROUPS < 16 ? GROUPS : 16;  // in flight per thread
   __shared__ float red_lo[kWavesPerBlock], red_hi[kWavesPerBlock];
   __shared__ double part[GROUPS][kTreeGroup + 1];  // (one of padding: the groups' threads read different banks)
@@ -2245,6 +2390,12 @@ inline CandidateScratch candidate_scratch(const CodecShape& c, void* scratch) {
   return cs;
 }
 
+// The l2 scale's counts: a byte per worker and chunk, eight workers to a word, [ceil(M / 8)][chunks].  Its slots, one per
+// worker and chunk, take a quarter of the room of one per tile; the counts lie behind them.
+inline uint64_t* l2_slot_counts(const CodecShape& c, const CandidateScratch& cs) {
+  return reinterpret_cast<uint64_t*>(cs.slots + (uint64_t)c.M * (c.d / kTreeChunk) * kSlotEntries);
+}
+
 // The sample: every kSampleStride-th whole wavefront tile of every row.
 template <int NORM, bool L2>
 hipError_t sample_launch(const CodecShape& c, const float* g, const float* gref, const CandidateScratch& cs, hipStream_t s) {
@@ -2290,9 +2441,8 @@ hipError_t absmax_candidates_dispatch(const CodecShape& c, uint32_t iter, const 
 #undef TNG_SELECT
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(absmax_finish_vote_kernel, dim3(c.M + 1), dim3(kBlock), 0, s, partials, nblocks, c.M, c.M, scales,
-                     cs.overflowed, nblocks * ((c.M + (uint32_t)mc - 1) / (uint32_t)mc),
-                     (uint64_t)c.M * (nvec / (kWave * kAbsmaxLoads)), cs.use_slots);
+  const SlotVote vote{cs.overflowed, nblocks * ((c.M + (uint32_t)mc - 1) / (uint32_t)mc), (uint64_t)c.M * row_tiles, cs.use_slots};
+  hipLaunchKernelGGL(absmax_finish_vote_kernel, dim3(c.M + 1), dim3(kBlock), 0, s, partials, nblocks, c.M, scales, vote);
   return hipGetLastError();
 }
 
@@ -2306,15 +2456,21 @@ hipError_t quantize_candidates_dispatch(const CodecShape& c, uint32_t iter, cons
                                         const float* gref2, const float* scales, const CandidateScratch& cs,
                                         uint32_t* codes, hipStream_t s) {
   const uint64_t tiles = (c.d / kWaveTileElements + kWavesPerBlock - 1) / kWavesPerBlock;  // workgroups of 4 wavefront tiles
-  const uint64_t slot_tiles = c.scale_l2 ? c.d / kTreeChunk * (kTreeChunk / kWaveTileElements) : c.d / kWaveTileElements;
   const int mc = pick_workers_per_block(c.M, tiles, 0.01, 8, true);  // (no reference to share between more; as
                                                                              // absmax_select_kernel's but for the cost of a repeated row)
 #define TNG_QC(MC)                                                                                                   \
   hipLaunchKernelGGL((quantize_candidates_kernel<NORM, MC>),                                                           \
                      dim3((uint32_t)tiles, (c.M + MC - 1) / MC), dim3(kBlock), 0,             \
                      s, GradRows{g, c.d}, reinterpret_cast<const float4*>(gref), reinterpret_cast<const float4*>(gref2), \
-                     scales, cs.slots, codes, c.d, c.words, slot_tiles, c.M, c.eps, c.k0, c.k1, iter, cs.use_slots, cs.select_ok)
-  switch (mc) {
+                     scales, cs.slots, codes, c.d, c.words, c.M, c.eps, c.k0, c.k1, iter, cs.use_slots, cs.select_ok)
+  if (c.scale_l2 != 0) {
+    const uint64_t chunks = c.d / kTreeChunk, loose = c.d / kWaveTileElements % (kTreeChunk / kWaveTileElements);
+    hipLaunchKernelGGL(quantize_l2_candidates_kernel<NORM>,
+                       dim3((uint32_t)((chunks + loose + kWavesPerBlock - 1) / kWavesPerBlock), (c.M + kL2QuantWorkers - 1) / kL2QuantWorkers),
+                       dim3(kBlock), 0, s, GradRows{g, c.d}, reinterpret_cast<const float4*>(gref), scales, cs.slots,
+                       reinterpret_cast<const uint8_t*>(l2_slot_counts(c, cs)), codes, c.d, c.words, chunks, c.M, c.k0, c.k1, iter,
+                       cs.use_slots);
+  } else switch (mc) {
     case 8: TNG_QC(8); break;
     case 5: TNG_QC(5); break;
     case 4: TNG_QC(4); break;
@@ -2519,12 +2675,12 @@ hipError_t l2_last_chunk_launch(const CodecShape& c, const float* g, const float
 // The row sums from the chunk sums.
 template <bool MEAN>
 hipError_t tree_finish_launch(const CodecShape& c, double* sums, const float2* minmax, uint64_t nchunks, uint64_t ngroups,
-                              float* out, float* scales, hipStream_t s) {
+                              float* out, float* scales, hipStream_t s, const SlotVote& vote = {}) {
   auto kernel = ngroups == 1   ? tree_finish_kernel<MEAN, 1>
                 : ngroups <= 16 ? tree_finish_kernel<MEAN, 16>
                                 : tree_finish_kernel<MEAN, 64>;
-  hipLaunchKernelGGL(kernel, dim3(c.M), dim3(kBlock), 0, s, sums, minmax, nchunks, ngroups, c.d, out,
-                     scales);
+  hipLaunchKernelGGL(kernel, dim3(c.M + (vote.use_slots != nullptr ? 1u : 0u)), dim3(kBlock), 0, s, sums, minmax, nchunks,
+                     ngroups, c.d, c.M, out, scales, vote);
   return hipGetLastError();
 }
 
@@ -2595,19 +2751,17 @@ hipError_t l2_candidates_launch(const CodecShape& c, uint32_t iter, const float*
   if (e != hipSuccess) return e;
   const dim3 grid((uint32_t)whole, (c.M + kL2SelectWorkers - 1) / kL2SelectWorkers);
   hipLaunchKernelGGL(l2_select_kernel<NORM>, grid, dim3(kBlock), 0, s, GradRows{g, c.d},
-                     reinterpret_cast<const float4*>(gref), sums, c.d / kWaveTileElements, nchunks, c.M, cs.sample_max,
-                     cs.select_ok, cs.slots, cs.overflowed, c.k0, c.k1, iter);
+                     reinterpret_cast<const float4*>(gref), sums, whole, nchunks, c.M, cs.sample_max, cs.select_ok, cs.slots,
+                     l2_slot_counts(c, cs), cs.overflowed, c.k0, c.k1, iter);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (whole < nchunks) {
     e = l2_last_chunk_launch<NORM>(c, g, gref, nullptr, sums, whole, nchunks, s);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(absmax_finish_vote_kernel, dim3(1), dim3(kBlock), 0, s, nullptr, 0u, c.M, 0u, scales, cs.overflowed,
-                     kL2OverflowCounts, (uint64_t)c.M * whole * (kTreeChunk / kWaveTileElements), cs.use_slots);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return tree_finish_launch<false>(c, sums, nullptr, nchunks, ngroups, scales, nullptr, s);
+  // (and, in one more workgroup of the same launch, the vote)
+  return tree_finish_launch<false>(c, sums, nullptr, nchunks, ngroups, scales, nullptr, s,
+                                   SlotVote{cs.overflowed, kL2OverflowCounts, (uint64_t)c.M * whole, cs.use_slots});
 }
 }  // namespace
 

@@ -68,6 +68,25 @@ def test_l2_scale_outside_the_sample():
     check(M, d, B.NORM_NONE, v, v[0].clone(), 2, B.SCALE_L2)
 
 
+@pytest.mark.parametrize("d", [(1 << 24) + 4096 + 3 * 1024, (1 << 24) + 1024 + 7])
+def test_l2_slots_filled_to_their_edges(d):
+    # chunks that hold exactly k candidates (the rows are zero where the sample looks, so every other element is one): the
+    # quantise pass takes the first 32 at once, all of up to 128 again, and codes a chunk with more from g; whole tiles behind
+    # the last whole chunk have no slots
+    M = 5
+    gen = torch.Generator(device=DEV).manual_seed(9)
+    v = torch.zeros((M, d), device=DEV)
+    for m in range(M):
+        for i, k in enumerate((1, 2, 31, 32, 33, 64, 127, 128, 129)):
+            at = torch.randperm(4096, generator=gen, device=DEV)[:k] + 4096 * (1 + 32 * i + 5 * m)
+            v[m, at] = torch.randn(k, generator=gen, device=DEV)
+        v[m, -3500:] = 2 * torch.randn(3500, generator=gen, device=DEV)
+    for m in range(M):
+        whole = v[m, :d // 1024 * 1024].view(-1, 1024)
+        whole[::128] = 0.0
+    check(M, d, B.NORM_SUB, v, torch.zeros(d, device=DEV), 7, B.SCALE_L2)
+
+
 @pytest.mark.parametrize("M,d,norm", [(10, 1 << 23, B.NORM_SUB), (9, 1 << 23, B.NORM_SUB), (20, (1 << 22) + 1029, B.NORM_SUB), (10, 1 << 23, B.NORM_NONE)])
 def test_groups_of_five_workers(M, d, norm):
     g, gref, _ = _inputs(M, d, seed=M)
