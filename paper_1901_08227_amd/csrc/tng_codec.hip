@@ -443,6 +443,14 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// A workgroup barrier behind which LDS is up to date and loads from global memory stay in flight (__syncthreads lets no
+// memory operation pass, and the compiler waits for all of them).
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Fragment (j, lane) is fragment number 64 j + lane of the wavefront's packed output: write the
 // fragments to LDS at that index, read whole words back, store them contiguously.
 // DEFER: the words stay in LDS slot `slot` (one slot per worker of the workgroup) and are written by
@@ -1317,9 +1325,15 @@ __global__ __launch_bounds__(kBlock) void decode_vec_kernel(
 // The scales come from the partial maxima of the scale pass (partials[rows][M], reduced by every workgroup for
 // itself: rows * M floats out of the L2) or, rows == 0, from scales.  32 KiB of them cost a workgroup less than the
 // launch that would reduce them once (about 4 us) up to 1024 workgroups of the kernel below; beyond those 8 KiB do
-// (kTailPartialsLong).  Iterations, own launch / here: Rosenbrock, d = 2^20, M = 8 26.2 / 25.2 us, M = 7 23.1 / 22.8; given
-// gradients, d = 2^20, M = 8 22.6 / 20.8, M = 16, 4-bit 34.5 / 33.2; d = 2^18, M = 64 29.6 / 28.5; d = 4e6, M = 8 67.8 / 68.4, d =
-// 2^22, M = 8, quotient 72.6 / 73.4.
+// (kTailPartialsLong; the scale pass then takes fewer workgroups where it can, see absmax_vec_launch).  Iterations, own
+// launch / here: Rosenbrock, d = 2^20, M = 8 26.2 / 25.2 us, M = 7 23.1 / 22.8; given gradients, d = 2^20, M = 8 22.6 / 20.8, M =
+// 16, 4-bit 34.5 / 33.2; d = 2^18, M = 64 29.6 / 28.5; d = 4e6, M = 8 with 8 KiB 70.0 / 65.0.
+// What a wavefront waits for comes in the order in which it asked: first what makes the scales, then the reference, then the
+// workers' rows, each of which is coded while the ones behind it are on their way.  (The scales behind the rows, and whole and
+// ragged wavefronts in one body: every wavefront waited for all of its rows first.  This kernel, before / after: d = 2^22, M = 8,
+// quotient 48.0 / 45.0 us; d = 2e6, M = 8, 4-bit 24.6 / 23.6; d = 8e6, M = 4, 4-bit 57 / 55; d = 4e6, M = 8 38.9 / 38.1.)  Not where
+// many partial maxima would come ahead of the rows, up to d = 2^20, where all wavefronts run at once (iteration of the
+// Rosenbrock chain, d = 2^20, M = 8 25.3 / 25.4 us, M = 7 22.9 / 23.3).
 // ------------------------------------------------------------------------------------------
 constexpr int kTailWorkers = 8;
 constexpr uint32_t kTailMaxWorkers = 64;
@@ -1334,29 +1348,47 @@ struct __align__(16) TailWorker {
   float r, inv_r, step, mu;
 };
 
-// The M <= kTailMaxWorkers workers' records; the first workgroup publishes the scales.
-template <int NORM, int BITS>
-__device__ __forceinline__ void tail_workers(TailWorker* sWorker, float* scales, const float* partials, uint32_t rows,
+// What a thread contributes to the workers' records, requested ahead of the rows of the gradients: loads return in order, so
+// behind them the first worker's arithmetic would wait for the last worker's row.
+constexpr int kTailLate = -1;
+template <int EARLY>
+struct TailOperands {
+  float r, mu;  // scale and mean of worker threadIdx.x (rows == 0 or the mean reference)
+  float4 top[EARLY > 0 ? EARLY : 1];  // EARLY: the thread's partial maxima, of the same four workers each
+};
+// EARLY: float4 a thread, where M is a power of two and kTailFewPartials < rows * M <= EARLY * 4 * kBlock, whole float4; 0: the
+// scales are there; kTailLate: nothing is asked for ahead of the rows.
+template <int NORM, int EARLY>
+__device__ __forceinline__ void tail_request(TailOperands<EARLY>& t, const float* scales, const float* partials, uint32_t rows,
                                              uint32_t M, const float* __restrict__ means) {
-  __shared__ uint32_t top[kTailMaxWorkers];  // as bits: non-negative floats are ordered as integers
-  if (rows != 0) {
+  const uint32_t m = min(threadIdx.x, M - 1);
+  t.r = EARLY > 0 ? 0.f : scales[m];
+  t.mu = NORM == kNormMean ? means[m] : 0.f;
+  static_assert(kTailFewPartials >= 4 * kBlock, "every thread has a float4");
+  const uint32_t last = (rows * M / 4 - 1 - threadIdx.x) / kBlock;
+  const float4* p = reinterpret_cast<const float4*>(partials) + threadIdx.x;
+#pragma unroll
+  for (int k = 0; k < EARLY; ++k) t.top[k] = p[min((uint32_t)k, last) * kBlock];  // past the end the last one again
+}
+
+// The M <= kTailMaxWorkers workers' records; the first workgroup publishes the scales.
+template <int NORM, int BITS, int EARLY>
+__device__ __forceinline__ void tail_workers(TailWorker* sWorker, uint32_t* top, float* scales, const float* partials, uint32_t rows,
+                                             uint32_t M, const TailOperands<EARLY>& mine) {
+  // top: as bits, non-negative floats are ordered as integers
+  auto meet_here = [] {
+    if (EARLY == kTailLate)
+      __syncthreads();
+    else
+      lds_barrier();
+  };
+  const bool from_partials = EARLY > 0 || (EARLY < 0 && rows != 0);
+  if (from_partials) {
     if (threadIdx.x < M) top[threadIdx.x] = 0u;
-    __syncthreads();
+    meet_here();
     const uint32_t n = rows * M;
-    if (n > kTailFewPartials && (M & (M - 1)) == 0 && n % 4 == 0) {  // all of a thread's float4 belong to the same four workers
-      static_assert(kTailFewPartials >= 4 * kBlock, "every thread has a float4");
-      const uint32_t n4 = n / 4, last = (n4 - 1 - threadIdx.x) / kBlock;
-      const float4* p = reinterpret_cast<const float4*>(partials) + threadIdx.x;
-      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-      for (uint32_t k0 = 0; k0 * kBlock < n4; k0 += 4) {  // (eight at a time: a wavefront less per SIMD, by registers)
-        float4 x[4];
-#pragma unroll
-        for (uint32_t k = 0; k < 4; ++k) x[k] = p[min(k0 + k, last) * kBlock];  // past the end the last one again
-#pragma unroll
-        for (uint32_t k = 0; k < 4; ++k)
-          v = make_float4(fmaxf(v.x, x[k].x), fmaxf(v.y, x[k].y), fmaxf(v.z, x[k].z), fmaxf(v.w, x[k].w));
-      }
-      const uint32_t apart = max(M / 4, 4u);  // lanes that far apart hold the same workers: few are left to meet in LDS
+    const uint32_t apart = max(M / 4, 4u);  // lanes that far apart hold the same workers: few are left to meet in LDS
+    auto meet = [&](float4 v) {
       for (uint32_t off = kWave / 2; off >= apart; off /= 2) {
         v.x = fmaxf(v.x, __shfl_xor(v.x, (int)off));
         v.y = fmaxf(v.y, __shfl_xor(v.y, (int)off));
@@ -1369,6 +1401,27 @@ __device__ __forceinline__ void tail_workers(TailWorker* sWorker, float* scales,
         for (uint32_t c = 0; c < 4; ++c)
           atomicMax(&top[(4 * threadIdx.x + c) % M], __float_as_uint(vv[c] < FLT_MIN ? 0.f : vv[c]));
       }
+    };
+    if (EARLY > 0) {
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int k = 0; k < EARLY; ++k)
+        v = make_float4(fmaxf(v.x, mine.top[k].x), fmaxf(v.y, mine.top[k].y), fmaxf(v.z, mine.top[k].z), fmaxf(v.w, mine.top[k].w));
+      meet(v);
+    } else if (n > kTailFewPartials && (M & (M - 1)) == 0 && n % 4 == 0) {  // all of a thread's float4 belong to the same four workers
+      static_assert(kTailFewPartials >= 4 * kBlock, "every thread has a float4");
+      const uint32_t n4 = n / 4, last = (n4 - 1 - threadIdx.x) / kBlock;
+      const float4* p = reinterpret_cast<const float4*>(partials) + threadIdx.x;
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (uint32_t k0 = 0; k0 * kBlock < n4; k0 += 4) {  // (eight at a time: a wavefront less per SIMD, by registers)
+        float4 x[4];
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) x[k] = p[min(k0 + k, last) * kBlock];  // past the end the last one again
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k)
+          v = make_float4(fmaxf(v.x, x[k].x), fmaxf(v.y, x[k].y), fmaxf(v.z, x[k].z), fmaxf(v.w, x[k].w));
+      }
+      meet(v);
     } else {
       const uint32_t used = kBlock / M * M;  // a thread stays with one worker
       if (threadIdx.x < min(used, n)) {
@@ -1385,32 +1438,40 @@ __device__ __forceinline__ void tail_workers(TailWorker* sWorker, float* scales,
         atomicMax(&top[threadIdx.x % M], __float_as_uint(v < FLT_MIN ? 0.f : v));
       }
     }
-    __syncthreads();
+    meet_here();
   }
   if (threadIdx.x < M) {
-    const float r = rows != 0 ? __uint_as_float(top[threadIdx.x]) : scales[threadIdx.x];
+    const float r = from_partials ? __uint_as_float(top[threadIdx.x]) : mine.r;
     constexpr float S = (float)((1 << (BITS - 1)) - 1);
-    sWorker[threadIdx.x] = TailWorker{r, r != 0.f ? 1.0f / r : 0.f, r / S, NORM == kNormMean ? means[threadIdx.x] : 0.f};
-    if (rows != 0 && blockIdx.x == 0) scales[threadIdx.x] = r;
+    sWorker[threadIdx.x] = TailWorker{r, r != 0.f ? 1.0f / r : 0.f, r / S, mine.mu};
+    if (from_partials && blockIdx.x == 0) scales[threadIdx.x] = r;
   }
-  __syncthreads();
+  meet_here();
 }
 
 template <int NORM, int BITS>
-__global__ __launch_bounds__(kBlock) void quantize_decode_kernel(
-    GradRows g, const float4* ref4, const float4* __restrict__ ref24, float* __restrict__ scales,
-    uint32_t* __restrict__ codes, uint64_t d, uint64_t words, uint32_t M, float eps, uint32_t k0, uint32_t k1,
-    uint32_t iter, const float* __restrict__ means, const float* __restrict__ partials, uint32_t rows,
-    float4* __restrict__ vbar4, float4* w4, float* refout, float inv_m, float lr) {
+struct TailLds {
+  FragmentBuffer<kWave * 4 * BITS / 32, kTailWorkers> fragments;
+  TailWorker worker[kTailMaxWorkers];
+  uint32_t top[kTailMaxWorkers];
+};
+
+// MIXED: some of the workgroup's coordinates may lie past the end of the row.  (Where whole and ragged wavefronts share one
+// body, the compiler cannot count the loads in flight where their paths join, and waits for all of them before the first
+// worker's arithmetic.)
+template <int NORM, int BITS, bool MIXED, int EARLY>
+__device__ __forceinline__ void quantize_decode_body(
+    TailLds<NORM, BITS>& lds, const GradRows& g, const float4* ref4, const float4* __restrict__ ref24, float* __restrict__ scales,
+    uint32_t* __restrict__ codes, uint64_t d, uint64_t words, uint32_t M, float eps, uint32_t k0, uint32_t k1, uint32_t iter,
+    const float* __restrict__ means, const float* __restrict__ partials, uint32_t rows, float4* vbar4, float4* w4, float* refout, float inv_m, float lr) {
   constexpr int MC = kTailWorkers;
   constexpr int WPW = kWave * 4 * BITS / 32;  // packed words per wavefront and worker
   constexpr bool RECIP = NORM == kNormQuot || NORM == kNormComb;
-  __shared__ FragmentBuffer<WPW, MC> lds;
-  __shared__ TailWorker sWorker[kTailMaxWorkers];
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const uint64_t q = (uint64_t)blockIdx.x * kBlock + threadIdx.x;  // the thread's float4
   const uint64_t wave_tile = (uint64_t)blockIdx.x * kWavesPerBlock + wave;
-  const bool whole = (wave_tile + 1) * (kWave * 4) <= d;  // the wavefront's 256 coordinates lie inside the row
+
+  const bool whole = !MIXED || (wave_tile + 1) * (kWave * 4) <= d;  // the wavefront's 256 coordinates lie inside the row
 
   float4 x[MC];
   auto load_rows = [&](uint32_t m0) {  // rows past M repeat the last one: no load under a condition
@@ -1425,38 +1486,40 @@ __global__ __launch_bounds__(kBlock) void quantize_decode_kernel(
       }
     }
   };
-  load_rows(0);
+  TailOperands<EARLY> mine{};
   RefTile<NORM> rt;
-  float4 w = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (whole) {
+  if (EARLY != kTailLate)
+    tail_request<NORM, EARLY>(mine, scales, partials, rows, M, means);
+  else
+    load_rows(0);
+  if (whole)
     rt.load(ref4, ref24, q, eps);
-    w = load_stream(w4 + q);
-  } else {
+  else
     rt.load_ragged(ref4, ref24, q, d, eps);
-    w = load4_within(reinterpret_cast<const float*>(w4), 4 * q, d, 0.f);
-  }
+  if (EARLY != kTailLate) load_rows(0);
+  float4 w = whole ? load_stream(w4 + q) : load4_within(reinterpret_cast<const float*>(w4), 4 * q, d, 0.f);
+  if (EARLY == kTailLate && (rows == 0 || NORM == kNormMean)) tail_request<NORM, EARLY>(mine, scales, partials, rows, M, means);
 
-  tail_workers<NORM, BITS>(sWorker, scales, partials, rows, M, means);
+  tail_workers<NORM, BITS, EARLY>(lds.worker, lds.top, scales, partials, rows, M, mine);
   rt.reciprocals();
   const PhiloxBlock block = philox_block((uint32_t)q, iter, k0, k1);
 
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (uint32_t m0 = 0; m0 < M; m0 += MC) {
-    if (m0 != 0) load_rows(m0);
+  for (uint32_t m0 = 0;;) {  // (the rows are the last loads both here and at the end of a trip: counted alike)
     const uint32_t count = min((uint32_t)MC, M - m0);
 #pragma unroll
     for (int mm = 0; mm < MC; ++mm) {
       if ((uint32_t)mm < count) {
         const uint32_t m = m0 + (uint32_t)mm;
-        const TailWorker wk = sWorker[m];
+        const TailWorker wk = lds.worker[m];
         const float4 v = normalize4<NORM, RECIP>(x[mm], rt, wk.mu);
         float4 val;  // what the server decodes
         uint32_t frag = quantize4_and_values<BITS>(v, wk.inv_r, philox_draw(block, m, iter, k0, k1), wk.r, wk.step, val);
         if (BITS == 4 && wk.r == 0.f) frag = 0u;  // (a row without a number in it)
         if (BITS == 2)
-          lds.b8[mm][wave][lane] = (uint8_t)frag;
+          lds.fragments.b8[mm][wave][lane] = (uint8_t)frag;
         else
-          lds.b16[mm][wave][lane] = (uint16_t)frag;
+          lds.fragments.b16[mm][wave][lane] = (uint16_t)frag;
         if (NORM == kNormMean) val = make_float4(wk.mu + val.x, wk.mu + val.y, wk.mu + val.z, wk.mu + val.w);
         acc.x = acc.x + val.x;  // in worker order
         acc.y = acc.y + val.y;
@@ -1468,9 +1531,12 @@ __global__ __launch_bounds__(kBlock) void quantize_decode_kernel(
     for (uint32_t i = (uint32_t)lane; i < count * WPW; i += kWave) {
       const uint32_t mm = i / WPW, j = i % WPW;
       const uint64_t wi = wave_tile * WPW + j;
-      if (wi < words) store_word_through(codes + (uint64_t)(m0 + mm) * words + wi, lds.b32[mm][wave][j]);
+      if (wi < words) store_word_through(codes + (uint64_t)(m0 + mm) * words + wi, lds.fragments.b32[mm][wave][j]);
     }
     wave_lds_fence();
+    m0 += MC;
+    if (m0 >= M) break;
+    load_rows(m0);
   }
 
   float4 o;
@@ -1493,6 +1559,23 @@ __global__ __launch_bounds__(kBlock) void quantize_decode_kernel(
   if (refout != nullptr) store4_within(refout, 4 * q, d, o);  // (a slot of the history ring starts at any 4-byte boundary)
 }
 
+template <int NORM, int BITS, int EARLY>
+__global__ __launch_bounds__(kBlock, NORM == kNormQuot || NORM == kNormComb || EARLY > 2 ? 4 : 5) void quantize_decode_kernel(
+    GradRows g, const float4* ref4, const float4* __restrict__ ref24, float* __restrict__ scales,
+    uint32_t* __restrict__ codes, uint64_t d, uint64_t words, uint32_t M, float eps, uint32_t k0, uint32_t k1,
+    uint32_t iter, const float* __restrict__ means, const float* __restrict__ partials, uint32_t rows,
+    float4* __restrict__ vbar4, float4* w4, float* refout, float inv_m, float lr) {
+  __shared__ __attribute__((aligned(16))) TailLds<NORM, BITS> lds;
+#define TNG_BODY(MIXED, REQUESTED)                                                                                            \
+  quantize_decode_body<NORM, BITS, MIXED, REQUESTED>(lds, g, ref4, ref24, scales, codes, d, words, M, eps, k0, k1, iter, means, \
+                                                  partials, rows, vbar4, w4, refout, inv_m, lr)
+  if (EARLY != kTailLate && (uint64_t)blockIdx.x * (4 * kBlock) + 4 * kBlock <= d)
+    TNG_BODY(false, EARLY);
+  else
+    TNG_BODY(true, kTailLate);
+#undef TNG_BODY
+}
+
 // The same where the coordinates alone leave the chip idle: a workgroup takes 256 coordinates, its wavefronts a
 // worker each in turn (a wavefront of the kernel above walks all M workers, 0.6 us each), and once the codes of
 // all workers are in LDS every thread decodes one coordinate, in worker order, by a table of the values.
@@ -1512,6 +1595,7 @@ __global__ __launch_bounds__(kBlock) void quantize_decode_split_kernel(
     lds_u32 b32[kTailMaxWorkers][WPW];
   } buf;
   __shared__ TailWorker sWorker[kTailMaxWorkers];
+  __shared__ uint32_t top[kTailMaxWorkers];
   __shared__ float table[kTailMaxWorkers * TAB];
   // (the wavefront's number as a value that is the same in every lane: its workers' parts of the draws are then scalar)
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = threadIdx.x % kWave;
@@ -1537,7 +1621,9 @@ __global__ __launch_bounds__(kBlock) void quantize_decode_split_kernel(
   float r1, r2;
   load_ref_scalar<NORM>(ref, ref2, ec, eps, r1, r2);
   const float w0 = w[ec];
-  tail_workers<NORM, BITS>(sWorker, scales, partials, rows, M, means);
+  TailOperands<kTailLate> mine{};
+  if (rows == 0 || NORM == kNormMean) tail_request<NORM, kTailLate>(mine, scales, partials, rows, M, means);
+  tail_workers<NORM, BITS, kTailLate>(sWorker, top, scales, partials, rows, M, mine);
   for (uint32_t i = threadIdx.x; i < M * TAB; i += kBlock) {
     const TailWorker wk = sWorker[i / TAB];
     const float val = decode_code<BITS>(i % TAB, wk.r, wk.step);
@@ -2341,14 +2427,21 @@ inline uint32_t workgroups_per_group(uint32_t main_blocks, uint32_t tail, uint32
   return tail == 0 || groups == 1 || n < 64 ? n : (n + kGroupMultiple - 1) / kGroupMultiple * kGroupMultiple;
 }
 
+// Where the next launch can reduce max_left rows of partial maxima by itself, no more workgroups than leave that many, if these
+// still fill the chip: its own launch for the reduction costs 5 us, and workgroups that walk a few tiles beat twice the number
+// that take one (given gradients d = 4e6, M = 8: 980 rows of four groups and the reduction 28.8 + 4.9 us, 256 rows 26.4; d = 2e6,
+// M = 8 16.4 + 4.7, 14.3).  Not for worker counts that are no power of two, whose maxima the next launch has to read one by
+// one (d = 3e6, M = 7, combined form 62.1 us with the reduction's launch, 64.8 without).
+constexpr uint32_t kAbsmaxFewBlocks = 960;
 template <int NORM, int MC>
 hipError_t absmax_vec_launch(const CodecShape& c, const float* g, const float* gref, const float* gref2,
-                             float* partials, uint32_t* nblocks, hipStream_t s) {
-  const uint32_t tail = tail_workgroups(c.d, MC);
+                             float* partials, uint32_t max_left, uint32_t* nblocks, hipStream_t s) {
+  const uint32_t tail = tail_workgroups(c.d, MC), groups = (c.M + MC - 1) / MC;
   const uint64_t per_y = (c.d / kWaveTileElements + kWavesPerBlock - 1) / kWavesPerBlock;
-  const uint32_t main_blocks = (uint32_t)(per_y < kAbsmaxMaxBlocks - tail ? per_y : kAbsmaxMaxBlocks - tail);
+  uint32_t main_blocks = (uint32_t)(per_y < kAbsmaxMaxBlocks - tail ? per_y : kAbsmaxMaxBlocks - tail);
+  if (main_blocks + tail > max_left && max_left > tail && (max_left - tail) * groups >= kAbsmaxFewBlocks && (c.M & (c.M - 1)) == 0)
+    main_blocks = max_left - tail;
   *nblocks = main_blocks + tail;
-  const uint32_t groups = (c.M + MC - 1) / MC;
   const dim3 grid(workgroups_per_group(main_blocks, tail, groups), groups);
   hipLaunchKernelGGL((absmax_vec_kernel<NORM, MC>), grid, dim3(kBlock), 0, s, GradRows{g, c.d}, reinterpret_cast<const float4*>(gref),
                      reinterpret_cast<const float4*>(gref2), partials, c.d, main_blocks, c.M, c.eps, c.means);
@@ -2492,10 +2585,10 @@ hipError_t absmax_dispatch(const CodecShape& c, const float* g, const float* gre
   uint32_t nblocks = 0;
   hipError_t e;
   switch (pick_workers_per_block(c.M, div_up_u32(c.d, (uint64_t)kBlock * kAbsmaxLoads * 4), 0.3)) {
-    case 8: e = absmax_vec_launch<NORM, 8>(c, g, gref, gref2, partials, &nblocks, s); break;
-    case 4: e = absmax_vec_launch<NORM, 4>(c, g, gref, gref2, partials, &nblocks, s); break;
-    case 2: e = absmax_vec_launch<NORM, 2>(c, g, gref, gref2, partials, &nblocks, s); break;
-    default: e = absmax_vec_launch<NORM, 1>(c, g, gref, gref2, partials, &nblocks, s); break;
+    case 8: e = absmax_vec_launch<NORM, 8>(c, g, gref, gref2, partials, max_left, &nblocks, s); break;
+    case 4: e = absmax_vec_launch<NORM, 4>(c, g, gref, gref2, partials, max_left, &nblocks, s); break;
+    case 2: e = absmax_vec_launch<NORM, 2>(c, g, gref, gref2, partials, max_left, &nblocks, s); break;
+    default: e = absmax_vec_launch<NORM, 1>(c, g, gref, gref2, partials, max_left, &nblocks, s); break;
   }
   if (e != hipSuccess) return e;
   if (nblocks <= max_left) {
@@ -2862,7 +2955,13 @@ hipError_t quantize_decode_dispatch(const CodecShape& c, uint32_t iter, const fl
     return hipGetLastError();
   }
   const uint32_t blocks = (uint32_t)(((c.d + 3) / 4 + kBlock - 1) / kBlock);
-  hipLaunchKernelGGL((quantize_decode_kernel<NORM, BITS>), dim3(blocks), dim3(kBlock), 0, s, GradRows{g, c.d},
+  const uint32_t n = rows * c.M;
+  auto kernel = rows == 0 ? quantize_decode_kernel<NORM, BITS, 0>
+                : n <= kTailFewPartials || n > kTailPartials || (c.M & (c.M - 1)) != 0 || n % 4 != 0
+                    ? quantize_decode_kernel<NORM, BITS, kTailLate>
+                : n <= kTailPartialsLong ? quantize_decode_kernel<NORM, BITS, kTailPartialsLong / (4 * kBlock)>
+                                         : quantize_decode_kernel<NORM, BITS, kTailPartials / (4 * kBlock)>;
+  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), 0, s, GradRows{g, c.d},
                      reinterpret_cast<const float4*>(gref), reinterpret_cast<const float4*>(gref2), scales, codes, c.d,
                      c.words, c.M, c.eps, c.k0, c.k1, iter, c.means, partials, rows, reinterpret_cast<float4*>(vbar),
                      reinterpret_cast<float4*>(w), ref_out, 1.0f / (float)c.M, lr);

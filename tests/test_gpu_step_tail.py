@@ -63,3 +63,10 @@ def test_step_scales_from_many_partial_maxima(d, M):
     for name, a, b in zip(("iterate", "reference", "codes", "scales", "average"), got, want):
         assert np.array_equal(a, b), f"d={d} M={M}: {name}"
     ctx.close()
+
+
+# The scale pass held to 2048 partial maxima (workers a power of two, beyond d = 2^20): a workgroup walks one to four tiles,
+# the last of them short, and the ragged tile has a row of its own; M = 7 keeps the launch that reduces them.
+@pytest.mark.parametrize("d,M", [((1 << 20) + 1028, 8), (1500003, 8), (1 << 22, 8), (1500004, 7)])
+def test_step_scales_from_a_scale_pass_of_few_workgroups(d, M):
+    test_step_scales_from_many_partial_maxima(d, M)
