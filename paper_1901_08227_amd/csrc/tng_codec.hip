@@ -2433,6 +2433,13 @@ inline uint32_t workgroups_per_group(uint32_t main_blocks, uint32_t tail, uint32
 // M = 8 16.4 + 4.7, 14.3).  Not for worker counts that are no power of two, whose maxima the next launch has to read one by
 // one (d = 3e6, M = 7, combined form 62.1 us with the reduction's launch, 64.8 without).
 constexpr uint32_t kAbsmaxFewBlocks = 960;
+// One group of workers: 1024 workgroups (four a compute unit) that walk the tiles instead of up to 4096, whose last round is
+// short.  Encode + decode, before / after: d = 2^25, M = 1, 4-bit 137.8 / 133.6 us; d = 2e7, M = 2, no normalisation 71.8 / 68.5;
+// d = 2^24, M = 4, 4-bit 150.6 / 148.0; d = 2^25, M = 8, combined form 546.9 / 543.9; iterations d = 2^24, M = 8 244.4 / 241.8.  Beyond
+// kAbsmaxLongTiles workgroups' worth of tiles there are rounds enough (d = 2^27, M = 8, quotient 1840 / 1845); several groups
+// that walk apart re-read the reference (d = 2^24, M = 9 286 / 297; d = 10^6, M = 32 65 / 68.7).
+constexpr uint32_t kAbsmaxWalkers = 1024;
+constexpr uint64_t kAbsmaxLongTiles = 16384;
 template <int NORM, int MC>
 hipError_t absmax_vec_launch(const CodecShape& c, const float* g, const float* gref, const float* gref2,
                              float* partials, uint32_t max_left, uint32_t* nblocks, hipStream_t s) {
@@ -2441,6 +2448,8 @@ hipError_t absmax_vec_launch(const CodecShape& c, const float* g, const float* g
   uint32_t main_blocks = (uint32_t)(per_y < kAbsmaxMaxBlocks - tail ? per_y : kAbsmaxMaxBlocks - tail);
   if (main_blocks + tail > max_left && max_left > tail && (max_left - tail) * groups >= kAbsmaxFewBlocks && (c.M & (c.M - 1)) == 0)
     main_blocks = max_left - tail;
+  else if (groups == 1 && main_blocks > kAbsmaxWalkers && per_y <= kAbsmaxLongTiles)
+    main_blocks = kAbsmaxWalkers;
   *nblocks = main_blocks + tail;
   const dim3 grid(workgroups_per_group(main_blocks, tail, groups), groups);
   hipLaunchKernelGGL((absmax_vec_kernel<NORM, MC>), grid, dim3(kBlock), 0, s, GradRows{g, c.d}, reinterpret_cast<const float4*>(gref),

@@ -1,8 +1,9 @@
 """The ragged last wavefront tile (1024 coordinates) of a row in the scale, quantise and decode kernels: it has
 workgroups of its own, a worker per wavefront, next to whole tiles that take 1 to 16 workers per workgroup."""
 import pytest
+import torch
 
-from gpu_util import make_ctx
+from gpu_util import DEV, buffers, make_ctx
 from paper_1901_08227_amd import binding as B
 from test_gpu_codec import NORMS, _check_encode_decode, _inputs
 
@@ -27,3 +28,19 @@ def test_ragged_tail_behind_grouped_workers(M, log2d):
         ctx = make_ctx(d, M, bits, norm, seed=M)
         _check_encode_decode(ctx, 1, g, gref, gref2, "grouped workers")
         ctx.close()
+
+
+# The scale pass of one group of workers: 1024 workgroups from 4096 * 1024 coordinates on, which walk the tiles (the last trip short, a
+# ragged tile behind it); the largest element in the last whole tile and in the ragged one.
+@pytest.mark.parametrize("d,M,at", [((1 << 22) + 4096, 1, (1 << 22) + 4095), ((1 << 23) + 3 * 4096 + 1029, 1, (1 << 23) + 3 * 4096 + 1028),
+                                    ((1 << 23) + 1024 + 3, 2, (1 << 23) + 1023)])
+def test_scale_pass_that_walks_the_tiles(d, M, at):
+    gen = torch.Generator(device=DEV).manual_seed(d)
+    g = torch.randn((M, d), generator=gen, device=DEV).clamp_(-4, 4)
+    gref = torch.zeros(d, device=DEV)
+    g[M - 1, at] = -7.5
+    ctx = make_ctx(d, M, 4, B.NORM_SUB, seed=3)
+    buf = buffers(ctx)
+    ctx.normalize_encode(1, g, gref, buf["codes"], buf["scales"])
+    assert torch.equal(buf["scales"], g.abs().amax(dim=1)) and float(buf["scales"][M - 1]) == 7.5
+    ctx.close()
