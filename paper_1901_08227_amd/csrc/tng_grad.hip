@@ -401,7 +401,7 @@ __global__ __launch_bounds__(kBlock) void logreg_dense_small_kernel(const float*
 typedef uint8_t __attribute__((may_alias)) lds_byte;
 typedef uint16_t __attribute__((may_alias)) lds_half;
 constexpr uint32_t kSmallThreads = 1024;
-template <int NORM, int BITS, bool STEP>
+template <int NORM, int BITS, bool STEP, bool EIGHTS>
 __global__ __launch_bounds__(kSmallThreads) void logreg_dense_small_finish_kernel(
     const float4* __restrict__ parts, uint32_t S, float* w, float* __restrict__ g, uint32_t d, uint32_t M, float inv_b,
     float l2, const float* gref, const float* gref2, float eps, float* __restrict__ scales, uint32_t* __restrict__ codes,
@@ -414,7 +414,7 @@ __global__ __launch_bounds__(kSmallThreads) void logreg_dense_small_finish_kerne
   const bool active = t < M * nvec;
   const uint32_t m = active ? t / nvec : M - 1, q = active ? t % nvec : nvec - 1;
   if (STEP) packed[t] = top[t] = 0u;
-  // The parts are added in order.  Whole eights of them (most minibatches: 57 to 64, 121 to 128, 185 to 192 and more than 248
+  // The parts are added in order.  Whole eights of them (EIGHTS; most minibatches: 57 to 64, 121 to 128, 185 to 192 and more than 248
   // rows) eight at a time, the iterate and the references asked for behind the last eight; otherwise the first one and then
   // eight at a time and the rest.  (d = 1000, M = 4: 8 parts 12.6 -> 12.2 us per iteration, 32 parts 17.7 -> 17.4; d = 69, M = 5, 32
   // parts 14.5 -> 13.9.  A last batch that repeats its last part instead of being shorter: d = 300, M = 4, 25 parts 11.9 -> 12.6.
@@ -422,13 +422,12 @@ __global__ __launch_bounds__(kSmallThreads) void logreg_dense_small_finish_kerne
   const float4* part = parts + (uint64_t)m * S * nvec + q;
   float4 acc, wv, r1 = make_float4(0.f, 0.f, 0.f, 0.f), r2 = make_float4(1.f, 1.f, 1.f, 1.f);
   auto add = [&](const float4& v) { acc = make_float4(acc.x + v.x, acc.y + v.y, acc.z + v.z, acc.w + v.w); };
-  auto operands = [&] {
-    wv = load4_within(w, 4 * q, d, 0.f);
+  auto references = [&] {
     if (STEP && (NORM == kNormSub || NORM == kNormComb)) r1 = load4_within(gref, 4 * q, d, 0.f);
     if (STEP && NORM == kNormQuot) r1 = load4_within(gref, 4 * q, d, 1.f);
     if (STEP && NORM == kNormComb) r2 = load4_within(gref2, 4 * q, d, 1.f);
   };
-  if (S % 8 == 0) {
+  if (EIGHTS) {
     acc = make_float4(-0.f, -0.f, -0.f, -0.f);  // (-0 + x is x, the sign of a zero included)
     float4 v[8];
     for (uint32_t s = 8; s < S; s += 8, part += 8 * nvec) {
@@ -439,20 +438,22 @@ __global__ __launch_bounds__(kSmallThreads) void logreg_dense_small_finish_kerne
     }
 #pragma unroll
     for (uint32_t k = 0; k < 8; ++k) v[k] = part[k * nvec];
-    operands();
+    wv = load4_within(w, 4 * q, d, 0.f);
+    references();
 #pragma unroll
     for (uint32_t k = 0; k < 8; ++k) add(v[k]);
   } else {
-    acc = part[0];
+    acc = parts[(uint64_t)m * S * nvec + q];
 #pragma unroll 8
-    for (uint32_t s = 1; s < S; ++s) add(part[s * nvec]);
-    operands();
+    for (uint32_t s = 1; s < S; ++s) add(parts[((uint64_t)m * S + s) * nvec + q]);
+    wv = load4_within(w, 4 * q, d, 0.f);
   }
   const float4 o = make_float4(__builtin_fmaf(l2, wv.x, acc.x * inv_b), __builtin_fmaf(l2, wv.y, acc.y * inv_b),
                                __builtin_fmaf(l2, wv.z, acc.z * inv_b), __builtin_fmaf(l2, wv.w, acc.w * inv_b));
   if (active) store4_within(g + (uint64_t)m * d, 4 * q, d, o);
   if (!STEP) return;
 
+  if (!EIGHTS) references();
   if (NORM == kNormQuot) r1 = make_float4(clamp_ref(r1.x, eps), clamp_ref(r1.y, eps), clamp_ref(r1.z, eps), clamp_ref(r1.w, eps));
   if (NORM == kNormComb) r2 = make_float4(clamp_ref(r2.x, eps), clamp_ref(r2.y, eps), clamp_ref(r2.z, eps), clamp_ref(r2.w, eps));
   const float4 v = make_float4(normalize<NORM>(o.x, r1.x, r2.x), normalize<NORM>(o.y, r1.y, r2.y),
@@ -2168,8 +2169,10 @@ hipError_t launch_dense_small_step(const LogregData& p, const CodecShape& c, uin
   if (e != hipSuccess) return e;
 #define TNG_SMALL(NORM)                                                                                              \
   do {                                                                                                               \
-    auto kernel = c.bits == 2 ? logreg_dense_small_finish_kernel<NORM, 2, true>                                      \
-                              : logreg_dense_small_finish_kernel<NORM, 4, true>;                                     \
+    auto kernel = S % 8 == 0 ? c.bits == 2 ? logreg_dense_small_finish_kernel<NORM, 2, true, true>                   \
+                                           : logreg_dense_small_finish_kernel<NORM, 4, true, true>                   \
+                  : c.bits == 2 ? logreg_dense_small_finish_kernel<NORM, 2, true, false>                             \
+                                : logreg_dense_small_finish_kernel<NORM, 4, true, false>;                            \
     hipLaunchKernelGGL(kernel, dim3(1), dim3(kSmallThreads), 0, s, reinterpret_cast<const float4*>(parts), S, w, g,  \
                        (uint32_t)c.d, c.M, 1.0f / (float)batch, l2, gref, gref2, c.eps, scales, codes,               \
                        (uint32_t)c.words, c.k0, c.k1, iter, vbar, ref_out, 1.0f / (float)c.M, lr);                   \
@@ -2193,7 +2196,9 @@ hipError_t launch_logreg_dense_grad(const LogregData& p, uint64_t d, uint32_t M,
   if (small != 0) {  // the gradient that launch_dense_small_step makes, bit for bit
     const hipError_t e = dense_small_rows_launch(p, d, M, batch, k0, k1, iter, idx, parts, w, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((logreg_dense_small_finish_kernel<kNormNone, 2, false>), dim3(1), dim3(kSmallThreads), 0, s,
+    auto kernel = small % 8 == 0 ? logreg_dense_small_finish_kernel<kNormNone, 2, false, true>
+                                 : logreg_dense_small_finish_kernel<kNormNone, 2, false, false>;
+    hipLaunchKernelGGL(kernel, dim3(1), dim3(kSmallThreads), 0, s,
                        reinterpret_cast<const float4*>(parts), small, const_cast<float*>(w), g, (uint32_t)d, M,
                        1.0f / (float)batch, l2, nullptr, nullptr, 0.f, nullptr, nullptr, 0u, k0, k1, iter, nullptr, nullptr,
                        0.f, 0.f);
