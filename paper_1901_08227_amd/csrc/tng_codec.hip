@@ -851,19 +851,22 @@ __device__ __forceinline__ uint32_t slot_entry(uint32_t value_word, uint32_t dra
   return (__float_as_uint(tau) & kMagnitude) | (value_word & (0x80000000u | POS_MASK));
 }
 
-// How it reads there.  The entry brackets tau: its significand was cut to K = 23 - (bits of the position) bits twice (the
-// value's, then tau's own) and its arithmetic is good to 2^-22, so tau lies in [lo (1 - 2^-22), hi (1 + 2^-K + 2^-21)].
+// How it reads there.  The entry of a normal value brackets tau: its significand was cut to K = 23 - (bits of the position) bits
+// twice (the value's, then tau's own) and its arithmetic is good to 2^-22, so tau lies in [lo (1 - 2^-22), hi (1 + 2^-K + 2^-21)].
 // ternary_code's level [u < fl(|v| fl(1 / R))] is 1 for R <= tau (1 - 2^-21) and 0 for R >= tau (1 + 2^-21) (the two
 // roundings move |v| / R by less than 2^-22 relatively, 1 / R > 2^126 included), so only a scale inside the widened bracket
 // -- three candidates in ten thousand with 13 bits, a dozen with 11 -- needs the value and the draw.
+// Of a value below the smallest normal number the cut may take half or all, so its tau has no such upper end, but it is below 2^-126 /
+// 2^-24: only a scale of 2^-101 and more is above every such tau, and under a smaller one nothing codes 0 unseen.  (The lower
+// end holds: the cut only lowers it, and a product that rounds coarsely is below every scale that is not 0.)
 template <uint32_t POS_MASK>
-__device__ __forceinline__ int entry_codes_one(uint32_t e, float r) {  // (u = 0: tau is infinite or no number, and not bounded)
+__device__ __forceinline__ int entry_codes_one(uint32_t e, float r) {  // (false where tau is infinite or no number: not bounded)
   return (int)((e & 0x7F800000u) != 0x7F800000u) & (int)(r <= __uint_as_float(e & 0x7FFFFFFFu & ~POS_MASK) * (1.0f - 0x1p-19f));
 }
 template <uint32_t POS_MASK>
 __device__ __forceinline__ int entry_codes_zero(uint32_t e, float r) {  // (false where tau is not bounded)
   constexpr float kAbove = POS_MASK == kCandPosMask ? 1.0f + 0x1p-12f : 1.0f + 0x1p-10f;
-  return (int)(r >= __uint_as_float((e & 0x7FFFFFFFu) | POS_MASK) * kAbove);
+  return (int)(r >= 0x1p-101f) & (int)(r >= __uint_as_float((e & 0x7FFFFFFFu) | POS_MASK) * kAbove);
 }
 // The code of element coord of worker m from its value.
 template <int NORM>

@@ -18,6 +18,7 @@ through exact rational arithmetic), on random operands and on draws placed right
 import fractions
 
 import numpy as np
+import pytest
 
 F32 = np.float32
 TWO32P = F32(2.0 ** 32 + 2.0 ** 12)  # 2^32 (1 + 2^-20), a binary32 number
@@ -159,3 +160,54 @@ def test_the_bracket_of_a_kept_element_decides_from_the_safe_side():
                 # and between the thresholds lies only a sliver of the scales: what goes back to the value
                 both = ok1 & ok0 & (lo > 0)
                 assert np.all(r_zero[both] <= lo[both] * F32(1.0 + 2.0 ** -11))
+
+
+def slot_entry(absv, word, pos_bits, rcp_ulps):
+    """The magnitude bits of a slot entry that leaves pos_bits to the position: 10 in a slot per tile, 12 in one per chunk."""
+    keep = np.uint32(0x7FFFFFFF & ~((1 << pos_bits) - 1))
+    with np.errstate(divide="ignore", over="ignore", invalid="ignore"):
+        rc = (F32(1.0) / (word >> np.uint32(8)).astype(F32)).astype(F32)
+        for _ in range(abs(rcp_ulps)):
+            rc = np.nextafter(rc, F32(np.inf) if rcp_ulps > 0 else F32(0.0)).astype(F32)
+        tau = ((absv.view(np.uint32) & keep).view(F32) * (rc * F32(2.0 ** 24)).astype(F32)).astype(F32)
+    return tau.view(np.uint32) & keep
+
+
+def decided(entry, pos_bits, R):
+    """(level 1 for sure, level 0 for sure) of an entry under the scale R, as the quantise pass decides."""
+    lo, hi = entry.view(F32), (entry | np.uint32((1 << pos_bits) - 1)).view(F32)
+    above = F32(1.0 + 2.0 ** -12) if pos_bits == 10 else F32(1.0 + 2.0 ** -10)
+    with np.errstate(over="ignore", invalid="ignore"):
+        bounded = (entry & np.uint32(0x7F800000)) != np.uint32(0x7F800000)
+        return (bounded & (R <= (lo * F32(1.0 - 2.0 ** -19)).astype(F32)),
+                (R >= F32(2.0 ** -101)) & (R >= (hi * above).astype(F32)))
+
+
+@pytest.mark.parametrize("pos_bits", [10, 12])
+@pytest.mark.parametrize("values", ["ordinary", "near the smallest normal number", "subnormal"])
+def test_entries_of_either_width_decide_from_the_safe_side(pos_bits, values):
+    rng = np.random.default_rng(29)
+    n = 400_000
+    if values == "ordinary":
+        absv = np.abs(rng.standard_normal(n) * 10.0 ** rng.uniform(-5, 1, n)).astype(F32)
+    elif values == "subnormal":
+        absv = (np.uint32(1) << rng.integers(0, 23, n).astype(np.uint32)) - np.uint32(1) + rng.integers(0, 2, n).astype(np.uint32)
+        absv = absv.astype(np.uint32).view(F32)
+    else:
+        absv = (np.uint32(0x00800000) + rng.integers(0, 1 << 14, n).astype(np.uint32)).view(F32)
+    k = (rng.integers(1, 2 ** 24, n) >> rng.integers(0, 24, n)).astype(np.uint32)  # draws of every size, u = 0 among them
+    word = (k << np.uint32(8)) | rng.integers(0, 256, n).astype(np.uint32)
+    # scales on both sides of |v| / u, from far away to a few units of either threshold
+    with np.errstate(divide="ignore", over="ignore"):
+        at = absv.astype(np.float64) * 2.0 ** 24 / np.maximum(k, 1)
+        R = (at * (1.0 + rng.choice([-1.0, 1.0], n) * 2.0 ** rng.uniform(-24, -1, n))).astype(F32)
+    R = np.maximum(np.where(np.isfinite(R), R, F32(2.0 ** 127)), F32(2.0 ** -126)).astype(F32)  # (a smaller scale is taken as 0)
+    lv = level(word, absv, R)
+    assert 0.1 < np.mean(lv) < 0.9
+    for ulps in (-1, 0, 1):
+        one, zero = decided(slot_entry(absv, word, pos_bits, ulps), pos_bits, R)
+        assert np.all(lv[one]), "decided 1 where the level is 0"
+        assert not np.any(lv[zero & ~one]), "decided 0 where the level is 1"
+    if values == "ordinary":  # what goes back to the value: a sliver of the scales, 2^-12 and 2^-10 of one on either side of tau
+        far = np.abs(R.astype(np.float64) / at - 1.0) > 2.0 ** (-10 if pos_bits == 10 else -8)
+        assert np.all((one | zero)[far & (k > 0) & (R >= F32(2.0 ** -101))])

@@ -87,6 +87,24 @@ def test_l2_slots_filled_to_their_edges(d):
     check(M, d, B.NORM_SUB, v, torch.zeros(d, device=DEV), 7, B.SCALE_L2)
 
 
+@pytest.mark.parametrize("scale", [B.SCALE_MAX, B.SCALE_L2])
+def test_rows_below_the_smallest_normal_number(scale):
+    # Rows that are zero where the sample looks (no bound: every non-zero element is a candidate) and hold a hundred values of 0x7FF
+    # or 0x1FFF units of 2^-149 per tile (a few dozen per chunk with the l2 scale) under a scale of 2^-124: of 2^24 draws 512 or
+    # 2048 code non-zero only by the bits that an entry has no room for, so hundreds of elements of a row tell.
+    M, d, per = 4, 1 << 24, 100 if scale == B.SCALE_MAX else 25
+    gen = torch.Generator(device=DEV).manual_seed(13)
+    bits = torch.zeros((M, d // 1024, 1024), dtype=torch.int32, device=DEV)
+    for m in range(M):
+        at = torch.rand((d // 1024, 1024), generator=gen, device=DEV).topk(per, dim=1).indices
+        sign = torch.randint(0, 2, at.shape, generator=gen, device=DEV, dtype=torch.int32) << 31
+        bits[m].scatter_(1, at, sign | (0x7FF, 0x1FFF, 0x5FF, 0x1801)[m])
+    bits[:, ::128] = 0
+    bits[:, 5, 77] = (127 - 124) << 23
+    v = bits.view(M, d).view(torch.float32)
+    check(M, d, B.NORM_SUB, v, torch.zeros(d, device=DEV), 3, scale)
+
+
 @pytest.mark.parametrize("M,d,norm", [(10, 1 << 23, B.NORM_SUB), (9, 1 << 23, B.NORM_SUB), (20, (1 << 22) + 1029, B.NORM_SUB), (10, 1 << 23, B.NORM_NONE)])
 def test_groups_of_five_workers(M, d, norm):
     g, gref, _ = _inputs(M, d, seed=M)
