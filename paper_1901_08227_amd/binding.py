@@ -309,7 +309,7 @@ class Context:
         _check(status, "tng_normalize_encode")
 
     def decode_aggregate(self, codes, scales, gref, vbar):
-        status = _call(_address["tng_decode_aggregate"], self.handle.value, None, "csdd", self.d, self.M, self.words, codes,
+        status = _call(_address["tng_decode_aggregate"], self.handle.value, None, "-csdd", self.d, self.M, self.words, codes,
                        scales, gref, vbar)
         if status is None:
             status = lib().tng_decode_aggregate(

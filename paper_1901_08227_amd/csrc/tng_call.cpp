@@ -4,10 +4,10 @@
 //
 //   call(address, handle, iter, kinds, d, M, words, tensor, ...) -> status, or None
 //
-// address: of the entry point; iter: None where it takes none; kinds: a letter per tensor, d float32[d], g float32[M d],
-// c int32[M words], s float32[M].  None says that an argument is not a plain case (no tensor, another type, too short, a tensor
-// subclass or a wrapper without storage): nothing was called, and the caller goes the way through ctypes, which raises what there
-// is to raise.
+// address: of the entry point; kinds: a letter per tensor, d float32[d], g float32[M d], c int32[M words], s float32[M], behind a
+// '-' for an entry point that takes no iteration number (iter is then not looked at).  None says that an argument is not a plain
+// case (no tensor, another type, too short, a tensor subclass or a wrapper without storage, an iteration that is no int):
+// nothing was called, and the caller goes the way through ctypes, which raises what there is to raise.
 #include <Python.h>
 
 #include <ATen/core/Tensor.h>
@@ -43,15 +43,16 @@ PyObject* call(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
   const Py_ssize_t n = nargs - kFixed;
   const char* kinds = nullptr;
   if (n < 2 || n > kMaxTensors || !PyUnicode_Check(args[3]) || (kinds = PyUnicode_AsUTF8(args[3])) == nullptr ||
-      PyUnicode_GET_LENGTH(args[3]) != n) {
+      PyUnicode_GET_LENGTH(args[3]) != n + (kinds[0] == '-')) {
     if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, "call: a letter per tensor, 2 to 6 tensors");
     return nullptr;
   }
-  // (anything but a plain int as handle or iteration goes through ctypes, which converts or refuses it)
-  if (!PyLong_CheckExact(args[1]) || (args[2] != Py_None && !PyLong_CheckExact(args[2]))) Py_RETURN_NONE;
+  const bool with_iter = kinds[0] != '-';
+  if (!with_iter) ++kinds;
+  // (anything but a plain int as handle or iteration, None too, goes through ctypes, which converts or refuses it)
+  if (!PyLong_CheckExact(args[1]) || (with_iter && !PyLong_CheckExact(args[2]))) Py_RETURN_NONE;
   const uintptr_t f = (uintptr_t)PyLong_AsUnsignedLongLong(args[0]);
   void* h = reinterpret_cast<void*>((uintptr_t)PyLong_AsUnsignedLongLong(args[1]));
-  const bool with_iter = args[2] != Py_None;
   const uint32_t iter = with_iter ? (uint32_t)PyLong_AsUnsignedLongMask(args[2]) : 0u;  // (as ctypes does)
   const int64_t d = PyLong_AsLongLong(args[4]), M = PyLong_AsLongLong(args[5]), words = PyLong_AsLongLong(args[6]);
   if (PyErr_Occurred()) return nullptr;

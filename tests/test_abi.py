@@ -207,3 +207,23 @@ def test_native_call_leaves_what_is_not_plain_to_ctypes():
     for bad in (("d", None, None), ("ddd", None, None), (b"dg", None, None)):
         with pytest.raises(TypeError):
             B._call(at, 4096, 0, bad[0], 4, 2, 1, *bad[1:])
+
+
+def test_an_iteration_that_is_none_reaches_no_entry_point(monkeypatch):
+    # (only tng_decode_aggregate takes no iteration; the others called without theirs would take the first pointer for it)
+    B.lib()
+    seen = []
+    entry = ctypes.CFUNCTYPE(ctypes.c_int, *[ctypes.c_void_p] * 7)(lambda *a: seen.append(a) or 0)
+    at = ctypes.cast(entry, ctypes.c_void_p).value
+    monkeypatch.setattr(B, "_address", dict.fromkeys(B._address, at))
+    ctx = object.__new__(B.Context)
+    ctx.handle, ctx.d, ctx.M, ctx.words = ctypes.c_void_p(4096), 4, 2, 1
+    try:
+        for call, n in ((ctx.local_grad, 2), (ctx.normalize_encode, 4), (ctx.update_reference, 2), (ctx.step, 6)):
+            with pytest.raises(ctypes.ArgumentError):
+                call(None, *[None] * n)
+        assert seen == []
+        ctx.decode_aggregate(None, None, None, None)
+        assert len(seen) == 1 and seen[0][:5] == (4096, None, None, None, None)
+    finally:
+        ctx.handle = ctypes.c_void_p()  # (nothing to destroy)
