@@ -4,7 +4,8 @@ a training loop are marshalled by a native function (csrc/tng_call.cpp) where th
 
 The module-level functions carry the names of the C entry points and take a context handle
 plus torch CUDA tensors; `Context` owns the workspace and keeps problem data alive.
-There is no fallback: if the built library is missing, loading raises.
+There is no fallback for the library: if it has not been built, loading raises.  Without the native function, or with one that
+was built for another torch or Python, the calls all go through ctypes.
 """
 from __future__ import annotations
 
@@ -14,6 +15,8 @@ import importlib.util
 import os
 
 import torch
+
+from . import build
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libtng.so")
@@ -46,18 +49,26 @@ class TngError(RuntimeError):
 
 
 _lib = None
-_call = None      # the extension's call(); loaded with the library
+_call = None      # the extension's call() or _through_ctypes; set with the library
 _address = None   # {entry point: its address} of those that go through it
 
 
+def _through_ctypes(*_):
+    """In the place of tng_call.call: no case is plain."""
+    return None
+
+
 def _load_call():
-    """tng_call.call; raises if it has not been built."""
+    """tng_call.call of the built extension; _through_ctypes where there is none that fits this torch and Python."""
     if not os.path.exists(CALL_PATH):
-        raise RuntimeError(f"libtng is not built: {CALL_PATH} is missing; run __graft_entry__.build()")
-    loader = importlib.machinery.ExtensionFileLoader("tng_call", CALL_PATH)
-    module = importlib.util.module_from_spec(importlib.util.spec_from_loader("tng_call", loader))
-    loader.exec_module(module)
-    return module.call
+        return _through_ctypes
+    try:
+        loader = importlib.machinery.ExtensionFileLoader("tng_call", CALL_PATH)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("tng_call", loader))
+        loader.exec_module(module)
+    except ImportError:
+        return _through_ctypes
+    return module.call if getattr(module, "built_for", None) == build.call_target() else _through_ctypes
 
 
 def lib() -> ctypes.CDLL:

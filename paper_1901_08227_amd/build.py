@@ -31,16 +31,39 @@ FLAGS = [
 ]
 
 
+def call_target() -> str:
+    """What the call extension is compiled for, and only used with: its calls depend on the layout of both."""
+    import torch
+
+    return f"torch {torch.__version__}, {sys.implementation.cache_tag}"
+
+
 def call_command() -> list:
     """The compiler line of the call extension: host code against the installed torch and Python headers."""
     import torch
 
     torch_dir = os.path.dirname(torch.__file__)
     return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
-            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DTNG_BUILT_FOR="{call_target()}"',
             "-isystem", os.path.join(torch_dir, "include"), "-isystem", sysconfig.get_paths()["include"],
             os.path.join(CSRC, "tng_call.cpp"), "-L", os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10",
             "-o", CALL]
+
+
+def build_call(verbose: bool = True) -> bool:
+    """Builds the call extension.  Without a compiler or headers for it there is none, and the binding's calls all go through
+    ctypes: the same results, 0.5 to 0.7 us of host time more per tensor."""
+    try:
+        cmd = call_command()
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.run(cmd, check=True)
+        return True
+    except (ImportError, OSError, subprocess.CalledProcessError) as e:
+        print(f"tng_call.so was not built, calls go through ctypes: {e}", file=sys.stderr, flush=True)
+        if os.path.exists(CALL):
+            os.remove(CALL)
+        return False
 
 
 def build(verbose: bool = True) -> str:
@@ -55,14 +78,8 @@ def build(verbose: bool = True) -> str:
             subprocess.run(cmd, check=True)
             return obj
 
-        def build_call():
-            cmd = call_command()
-            if verbose:
-                print(" ".join(cmd), flush=True)
-            subprocess.run(cmd, check=True)
-
         with ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as pool:
-            call = pool.submit(build_call)
+            call = pool.submit(build_call, verbose)
             objs = list(pool.map(compile_one, SOURCES))
             call.result()
         cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]

@@ -83,4 +83,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "tng_call", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit_tng_call() { return PyModule_Create(&module); }
+// built_for: the torch and Python that this was compiled for (the binding uses it with no other).
+PyMODINIT_FUNC PyInit_tng_call() {
+  PyObject* m = PyModule_Create(&module);
+  if (m != nullptr && PyModule_AddStringConstant(m, "built_for", TNG_BUILT_FOR) != 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
+}

@@ -227,3 +227,34 @@ def test_an_iteration_that_is_none_reaches_no_entry_point(monkeypatch):
         assert len(seen) == 1 and seen[0][:5] == (4096, None, None, None, None)
     finally:
         ctx.handle = ctypes.c_void_p()  # (nothing to destroy)
+
+
+def test_without_a_native_function_that_fits_calls_go_through_ctypes(monkeypatch, tmp_path):
+    from paper_1901_08227_amd import build
+    B.lib()
+    assert B._call is not B._through_ctypes  # (built here)
+    with monkeypatch.context() as mp:  # built for another torch
+        mp.setattr(build, "call_target", lambda: "torch 1.0, cpython-27")
+        assert B._load_call() is B._through_ctypes
+    with monkeypatch.context() as mp:  # no library
+        mp.setattr(B, "CALL_PATH", str(tmp_path / "tng_call.so"))
+        assert B._load_call() is B._through_ctypes
+        (tmp_path / "tng_call.so").write_text("not a library")
+        assert B._load_call() is B._through_ctypes
+    monkeypatch.setattr(B, "_call", B._through_ctypes)
+    ctx = object.__new__(B.Context)
+    ctx.handle, ctx.d, ctx.M, ctx.words = ctypes.c_void_p(), 4, 2, 1
+    for call in (lambda: ctx.step(0, *[None] * 6), lambda: ctx.decode_aggregate(*[None] * 4), lambda: ctx.local_grad(0, None, None)):
+        with pytest.raises(B.TngError) as e:  # the entry point was called, and refuses the null context
+            call()
+        assert e.value.status == B.TNG_ERR_INVALID_ARG
+
+
+def test_build_without_a_host_compiler(monkeypatch, tmp_path, capsys):
+    from paper_1901_08227_amd import build
+    stale = tmp_path / "tng_call.so"
+    stale.write_text("an earlier one")
+    monkeypatch.setattr(build, "CALL", str(stale))
+    monkeypatch.setenv("CXX", str(tmp_path / "no-compiler"))
+    assert build.build_call(verbose=False) is False
+    assert not stale.exists() and "ctypes" in capsys.readouterr().err
