@@ -1080,12 +1080,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
   }
 }
 
-// Whether the slots are worth using, by one workgroup: at most one in fifty may have overflowed (such tiles go through a
-// plain, unpipelined form of the ordinary path).  use_slots[0] = 1 or 0.
+// Whether the slots are worth using, by one workgroup: at most one per fifty tiles may have overflowed (what they hold goes
+// through a plain, unpipelined form of the ordinary path).  use_slots[0] = 1 or 0.  Of the l2 scale's slots, four tiles each, that is
+// two in 25, so that tiles which overflow one here and one there still count as one in fifty: rows of M = 16, d = 2^22 (encode, us)
+// whose one to three tiles in a hundred that are not zero are seldom in the sample 93 with a slot per tile, 115 with one slot in
+// fifty, 86 to 92 so; d = 2^23 162 / 218 / 145; M = 64, d = 2^20 89 / 109 / 83.
 struct SlotVote {
   const uint32_t* overflowed;  // n counts
   uint32_t n;
-  uint64_t slots_in_all;
+  uint64_t tiles_in_all;
   uint32_t* use_slots;
 };
 __device__ __forceinline__ void vote_on_slots(const SlotVote& v) {
@@ -1096,7 +1099,7 @@ __device__ __forceinline__ void vote_on_slots(const SlotVote& v) {
   for (uint32_t i = threadIdx.x; i < v.n; i += kBlock) mine += v.overflowed[i];
   atomicAdd(&sum, mine);
   __syncthreads();
-  if (threadIdx.x == 0) v.use_slots[0] = sum * 50ull <= v.slots_in_all ? 1u : 0u;
+  if (threadIdx.x == 0) v.use_slots[0] = sum * 50ull <= v.tiles_in_all ? 1u : 0u;
 }
 
 // The reduction of the scale pass's partial maxima (workgroups 0 .. M - 1, one per worker) and the vote.
@@ -2866,7 +2869,8 @@ hipError_t l2_candidates_launch(const CodecShape& c, uint32_t iter, const float*
   }
   // (and, in one more workgroup of the same launch, the vote)
   return tree_finish_launch<false>(c, sums, nullptr, nchunks, ngroups, scales, nullptr, s,
-                                   SlotVote{cs.overflowed, kL2OverflowCounts, (uint64_t)c.M * whole, cs.use_slots});
+                                   SlotVote{cs.overflowed, kL2OverflowCounts,
+                                            (uint64_t)c.M * whole * (kTreeChunk / kWaveTileElements), cs.use_slots});
 }
 }  // namespace
 

@@ -87,6 +87,32 @@ def test_l2_slots_filled_to_their_edges(d):
     check(M, d, B.NORM_SUB, v, torch.zeros(d, device=DEV), 7, B.SCALE_L2)
 
 
+# Rows that are zero where the sample looks: every other element is a candidate.  share of the groups of four tiles hold `tiles` tiles
+# with `each` candidates (and the rest nothing); the slots are used unless more than one per fifty tiles overflow.
+@pytest.mark.parametrize("scale,share,tiles,each,used", [(B.SCALE_L2, 0.04, 1, 1024, 1), (B.SCALE_L2, 0.075, 1, 1024, 1),
+                                                         (B.SCALE_L2, 0.09, 1, 1024, 0), (B.SCALE_MAX, 0.04, 1, 1024, 1),
+                                                         (B.SCALE_MAX, 0.04, 3, 1024, 0), (B.SCALE_MAX, 0.3, 4, 127, 1)])
+def test_which_rows_the_slots_are_used_for(scale, share, tiles, each, used):
+    M, d = 16, 1 << 22
+    gen = torch.Generator(device=DEV).manual_seed(17)
+    v = torch.zeros((M, d // 4096, 4, 1024), device=DEV)
+    groups = torch.arange(d // 4096, device=DEV)
+    groups = groups[groups % 32 != 0]
+    for m in range(M):
+        some = groups[torch.randperm(len(groups), generator=gen, device=DEV)[:int(share * (d // 4096))]]
+        v[m, some, :tiles, :each] = torch.randn((len(some), tiles, each), generator=gen, device=DEV)
+    v = v.view(M, d)
+    check(M, d, B.NORM_SUB, v, torch.zeros(d, device=DEV), 3, scale)
+    ctx = make_ctx(d, M, 2, B.NORM_SUB, seed=d, scale=scale)
+    buf = buffers(ctx)
+    ctx.normalize_encode(3, v, torch.zeros(d, device=DEV), buf["codes"], buf["scales"])
+    four_bits = B.TngConfig.from_buffer_copy(ctx.cfg)
+    four_bits.bits = 4
+    at = B.tng_workspace_bytes(four_bits)  # without slots: where they begin, the vote in front
+    assert int(ctx.workspace[at:at + 4].view(torch.int32)[0]) == used
+    ctx.close()
+
+
 @pytest.mark.parametrize("scale", [B.SCALE_MAX, B.SCALE_L2])
 def test_rows_below_the_smallest_normal_number(scale):
     # Rows that are zero where the sample looks (no bound: every non-zero element is a candidate) and hold a hundred values of 0x7FF
