@@ -680,7 +680,9 @@ constexpr int kSlotEntries = 128;     // 32-bit words per slot: 512 bytes per wo
 constexpr uint32_t kSampleStride = 128;  // the sample: every 128th wavefront tile of a row
 constexpr uint32_t kCandPosMask = 0x3FFu;  // low 10 bits of a candidate word: position within the tile
 constexpr uint32_t kChunkPosMask = 0xFFFu;  // the l2 scale's slots are per worker and chunk of four tiles: 12 bits
-constexpr uint32_t kNoSlot = 255u;         // in the place of such a slot's count: it overflowed, or the row has none
+constexpr int kL2SlotEntries = 448;         // 32-bit words of such a slot, all of them candidates
+constexpr uint32_t kNoSlot = 255u;          // in the place of its count (a byte, in pairs): it overflowed, or the row has none
+static_assert(kL2SlotEntries / 2 < (int)kNoSlot, "the count fits a byte");
 
 // The sample of a row taken before the scale pass: over every kSampleStride-th wavefront tile, the largest
 // |v| (the lower bound R^ of the row's scale) and the sum of |v|.  Their ratio, mean |v| / R^, is the share
@@ -688,7 +690,8 @@ constexpr uint32_t kNoSlot = 255u;         // in the place of such a slot's coun
 // beforehand whether the slots can hold them.  One worker per workgroup row (blockIdx.y); partial results per
 // workgroup, reduced by sample_finish_kernel.
 constexpr uint32_t kL2OverflowCounts = kBlock;  // counters that the workgroups of l2_select_kernel share
-constexpr float kDenseLimit = 0.10f;  // 1024 elements x 0.10 + two standard deviations fill a slot of kCandCap
+// 1024 elements x 0.10 + two standard deviations fill a slot of kCandCap, 4096 x 0.10 + two one of kL2SlotEntries
+constexpr float kDenseLimit = 0.10f;
 // L2: the bound is of the row's 2-norm instead, from the sum of squares over the sample in binary64 (the partial
 // results are the workgroups' own norms).
 template <int NORM, bool L2>
@@ -800,7 +803,12 @@ __global__ __launch_bounds__(kBlock) void sample_finish_kernel(const float* __re
 // Staging of one worker's candidates in a wavefront tile: the count and up to kCandCap candidates (value word and
 // draw), one word that takes everything beyond the capacity, then a word per lane for the elements that are no
 // candidates.
-constexpr uint32_t kStageSink = kSlotEntries, kStageDump = kSlotEntries + 2, kStageWords = kStageDump + kWave;
+constexpr uint32_t kStageSink = kSlotEntries, kStageWords = kStageSink + 2 + kWave;
+// Of the l2 scale, where candidates gather over a chunk: the staging area is written out at the end of a tile that leaves more than
+// kL2FlushAt in it, so that every tile finds room for as many as a slot per tile held.  (Four workgroups a compute unit: 40.6 of
+// 40.9 KB of LDS each.)
+constexpr uint32_t kL2FlushAt = 48, kL2StageSink = kL2FlushAt + kSlotEntries, kL2StageWords = kL2StageSink + 2 + kWave;
+static_assert(kL2StageWords % 2 == 0, "read in pairs");
 
 // The lower bound R^ of a worker's scale, as the factor of the candidates' test
 //   u < fl(|v| fl(1 / R^)),  u = (word >> 8) 2^-24,
@@ -816,7 +824,7 @@ __device__ __forceinline__ float candidate_factor(float r_hat) {
 
 // The candidates of one float4 per lane (load j of the tile) go to number base of the staging area and behind it.  FEW: candidates
 // are rare, most float4 of a whole wavefront hold none.
-template <bool FEW, uint32_t POS_MASK>
+template <bool FEW, uint32_t POS_MASK, uint32_t SINK>
 __device__ __forceinline__ void stage_candidates(uint32_t* stage, uint32_t* draws, const float4& v, const U32x4& rnd,
                                                  float c1, int j, int lane, uint32_t& base) {
   const float vv[4] = {v.x, v.y, v.z, v.w};
@@ -833,7 +841,7 @@ __device__ __forceinline__ void stage_candidates(uint32_t* stage, uint32_t* draw
     // Every lane writes, the others into a word of their own behind the candidates': a store under a
     // condition would end the basic block at every element, and the sixteen elements of a lane could not
     // overlap.  Candidates beyond the slot's capacity (the slot is then not used) share one word.
-    const uint32_t at = cand[c] ? min(pos, kStageSink) : kStageDump + (uint32_t)lane;
+    const uint32_t at = cand[c] ? min(pos, SINK) : SINK + 2 + (uint32_t)lane;
     stage[at] = (__float_as_uint(vv[c]) & ~POS_MASK) | (uint32_t)(256 * j + c) | 4u * (uint32_t)lane;
     draws[at] = rr[c];
     base += (uint32_t)__builtin_popcountll(mask);
@@ -1008,7 +1016,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
       amax = max3_abs(v.z, v.w, max3_abs(v.x, v.y, amax));
       const uint64_t iv = tile * kWaveTile + (uint64_t)(j * kWave + lane);
       const U32x4 rnd = philox4x32_10((uint32_t)iv, m, iter, 0u, k0, k1);
-      stage_candidates<false, kCandPosMask>(stage[wave], draws[wave], v, rnd, c1[mm], j, lane, base);
+      stage_candidates<false, kCandPosMask, kStageSink>(stage[wave], draws[wave], v, rnd, c1[mm], j, lane, base);
     }
     mx[mm] = fmaxf(mx[mm], amax);
     if (!write_slot(stage[wave], draws[wave], base, lane, slots + ((uint64_t)m * ntiles + tile) * kSlotEntries)) nover += 1u;
@@ -2065,10 +2073,13 @@ __global__ __launch_bounds__(kBlock) void l2_chunk_kernel(GradRows g, const floa
 // lane sums of all workers are added up in order at the end, a worker per lane (by one lane per worker and wavefront, as
 // above, these additions are as many instructions as all others).  A wavefront's fetches, a tile of a worker each, rotate
 // through three buffers.
-// A slot is per worker and chunk (its candidates gathered over the four tiles), written only if it holds something, and
-// the counts of the workgroup's workers are one word: a slot per tile, its count in it, was a quarter of a million writes of 8
-// bytes among the reads at d = 2^24, M = 16, and cost this kernel 20 of its 260 us and the quantise pass half its time.
-// Encode + decode there: 500 us by two passes, 345 with a slot per tile, 303 this way (this kernel 234 to 250 for 1.14 GB: the
+// A slot is per worker and chunk (its candidates gathered over the four tiles, written out earlier only where they are many),
+// touched only if it holds something, and the counts of the workgroup's workers are one word: a slot per tile, its count in it, was
+// a quarter of a million writes of 8 bytes among the reads at d = 2^24, M = 16, and cost this kernel 20 of its 260 us and the
+// quantise pass half its time.  It holds what the slots of four tiles would, near enough: rows whose magnitude varies along them
+// (log-normal by 4096 elements, M = 64, d = 2^20, sigma 0.7 / 1.0 / 1.5) encode in 96 / 96 / 97 us with a slot per tile, 97 / 101 / 121
+// with one of 128 entries per chunk (their chunks overflow), 90 / 92 / 97 so.
+// Encode + decode there: 500 us by two passes, 345 with a slot per tile, 306 this way (this kernel 236 to 250 for 1.14 GB: the
 // vector unit's time for draws, squares and tests, 160 us, as much as memory's, 181).
 constexpr int kL2SelectWorkers = 8;
 template <int NORM>
@@ -2082,11 +2093,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
   constexpr int T = kTreeChunk / (int)kWaveTileElements;  // tiles per chunk
   constexpr int V = kTreeChunk / 4;                      // float4 per chunk
   constexpr int kSumStride = kTreeLanes + 2;             // two binary64 of padding: the lanes' reads fall on different banks
-  __shared__ __attribute__((aligned(16))) uint32_t stage[kWavesPerBlock][kStageWords];
-  __shared__ __attribute__((aligned(16))) uint32_t draws[kWavesPerBlock][kStageWords];
+  __shared__ __attribute__((aligned(16))) uint32_t stage[kWavesPerBlock][kL2StageWords];
+  __shared__ __attribute__((aligned(16))) uint32_t draws[kWavesPerBlock][kL2StageWords];
   __shared__ __attribute__((aligned(16))) float4 refs[NORM == kNormSub ? V : 1];
   __shared__ __attribute__((aligned(16))) double sums[kL2SelectWorkers][kSumStride];
-  __shared__ uint8_t found[kL2SelectWorkers];  // candidates of each worker in this chunk, or kNoSlot
+  __shared__ uint8_t found[kL2SelectWorkers];  // candidates of each worker in this chunk, in pairs, or kNoSlot
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = threadIdx.x % kWave;
   const uint64_t chunk = blockIdx.x;
   const uint32_t m0 = blockIdx.y * kL2SelectWorkers;
@@ -2114,15 +2125,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
   __syncthreads();  // the reference is in LDS
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
   float c1 = 0.f;
-  bool select = false;
-  uint32_t base = 0;  // candidates of the worker so far
+  bool select = false, fits = false;
+  uint32_t base = 0, written = 0;  // candidates of the worker in the staging area, and in its slot
   auto work = [&](const float4 (&x)[L], uint32_t item) {
     const uint32_t mm = (uint32_t)wave + item / T * kWavesPerBlock, m = m0 + mm, t = item % T;
     if (t == 0) {
       acc[0] = acc[1] = acc[2] = acc[3] = 0.0;
       c1 = candidate_factor(sample_max[m]);
       select = select_ok[m] != 0u;
-      base = 0;
+      fits = select;
+      base = written = 0;
     }
 #pragma unroll
     for (int j = 0; j < L; ++j) {
@@ -2139,22 +2151,35 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
       acc[3] = __builtin_fma(t3, t3, acc[3]);
       if (select) {  // (the same for the whole wavefront)
         const U32x4 rnd = philox4x32_10((uint32_t)(chunk * V) + at, m, iter, 0u, k0, k1);
-        stage_candidates<true, kChunkPosMask>(stage[wave], draws[wave], v, rnd, c1, (int)t * L + j, lane, base);
+        stage_candidates<true, kChunkPosMask, kL2StageSink>(stage[wave], draws[wave], v, rnd, c1, (int)t * L + j, lane, base);
       }
     }
+    // The staged candidates to the worker's slot, 8 bytes per lane, twice where there may be more than two per lane.  (Encode +
+    // decode, d = 2^24, M = 16: 302.9 us with slots of 128 and no early write-out, 306.4 with a loop over the pairs, 305.7 so.)
+    auto write_out = [&](bool twice) {
+      const uint32_t used = (base + 1) & ~1u;
+      fits = fits && base <= kL2StageSink && written + used <= (uint32_t)kL2SlotEntries;
+      uint64_t* slot = reinterpret_cast<uint64_t*>(slots + ((uint64_t)m * chunks + chunk) * kL2SlotEntries + written);
+      auto pair = [&](uint32_t i) {
+        const uint2 vw = *reinterpret_cast<const uint2*>(&stage[wave][2 * i]);
+        const uint2 dw = *reinterpret_cast<const uint2*>(&draws[wave][2 * i]);
+        // (an odd one out is followed by an entry that codes nothing: tau = 0)
+        const uint32_t second = 2 * i + 1 < base ? slot_entry<kChunkPosMask>(vw.y, dw.y) : 0u;
+        __hip_atomic_store(slot + i, ((uint64_t)second << 32) | slot_entry<kChunkPosMask>(vw.x, dw.x), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+      };
+      wave_lds_fence();
+      if (fits && 2 * (uint32_t)lane < base) pair((uint32_t)lane);
+      if (twice && fits && 2 * (uint32_t)(lane + kWave) < base) pair((uint32_t)(lane + kWave));
+      wave_lds_fence();
+      written += used;
+      base = 0;
+    };
+    static_assert(kL2FlushAt <= 2 * kWave && kL2StageSink <= 4 * kWave, "two entries a lane, or four");
+    if (__builtin_expect(base > kL2FlushAt, 0)) write_out(true);  // (the same for the whole wavefront)
     if (t == T - 1) {
-      const bool fits = select && base <= (uint32_t)kSlotEntries;
-      if (lane == 0) found[mm] = (uint8_t)(fits ? base : kNoSlot);
-      wave_lds_fence();
-      if (fits && 2u * (uint32_t)lane < base) {  // 8 bytes per lane, the last one whatever the staging area holds
-        const uint2 vw = *reinterpret_cast<const uint2*>(&stage[wave][2 * lane]);
-        const uint2 dw = *reinterpret_cast<const uint2*>(&draws[wave][2 * lane]);
-        uint64_t* slot = reinterpret_cast<uint64_t*>(slots + ((uint64_t)m * chunks + chunk) * kSlotEntries);
-        __hip_atomic_store(slot + (uint32_t)lane,
-                           ((uint64_t)slot_entry<kChunkPosMask>(vw.y, dw.y) << 32) | slot_entry<kChunkPosMask>(vw.x, dw.x),
-                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      wave_lds_fence();
+      write_out(false);
+      if (lane == 0) found[mm] = (uint8_t)(fits ? written / 2 : kNoSlot);
 #pragma unroll
       for (int i = 0; i < 4; ++i) sums[mm][4 * lane + i] = acc[i];
     }
@@ -2190,10 +2215,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
 
 // The same for the l2 scale, whose slots are per worker and chunk of four tiles and all but empty: hardly an element is a
 // candidate (a row expects at most sqrt(d) R / R^ of them, the 1-norm over the 2-norm).  The counts of eight workers lie in
-// eight bytes of their own, so that a pass over slots without candidates is a pass over 1/512 of their bytes and the
-// write-out.  A wavefront takes a chunk of kL2QuantWorkers workers, all their first 32 entries requested at once; tiles
-// behind the last whole chunk (at most three; the ragged one is the ordinary quantiser's) have no slots and are the last
-// row of workgroups'.
+// eight bytes of their own, so that nothing is written to a slot without candidates; of every slot one line is read.  A wavefront
+// takes a chunk of kL2QuantWorkers workers, all their first 32 entries requested at once; tiles behind the last whole chunk (at
+// most three; the ragged one is the ordinary quantiser's) have no slots and are the last row of workgroups'.
 // d = 2^24, M = 16 (67 MB of codes): 28 us with a slot per tile, 16 this way (13 at the least, 5.2 TB/s).
 constexpr int kL2QuantWorkers = 4;
 template <int NORM>
@@ -2231,7 +2255,7 @@ __global__ __launch_bounds__(kBlock, 8) void quantize_l2_candidates_kernel(
 #pragma unroll
   for (int mm = 0; mm < MC; ++mm) {
     const uint32_t m = min(m0 + (uint32_t)mm, M - 1);
-    first[mm] = slots[((uint64_t)m * chunks + chunk) * kSlotEntries + ((uint32_t)lane & 31u)];
+    first[mm] = slots[((uint64_t)m * chunks + chunk) * kL2SlotEntries + ((uint32_t)lane & 31u)];
     R[mm] = scales[m];
   }
   const uint32_t four = *reinterpret_cast<const uint32_t*>(counts + ((uint64_t)(m0 / kGroup) * chunks + chunk) * kGroup + m0 % kGroup);
@@ -2246,11 +2270,11 @@ __global__ __launch_bounds__(kBlock, 8) void quantize_l2_candidates_kernel(
   uint32_t long_slots = 0u, no_slots = 0u, undecided = 0u;
 #pragma unroll
   for (int mm = 0; mm < MC; ++mm) {
-    const uint32_t e = first[mm], n = __builtin_amdgcn_readfirstlane(four >> (8 * mm)) & 255u;
+    const uint32_t e = first[mm], pairs = __builtin_amdgcn_readfirstlane(four >> (8 * mm)) & 255u;
     const bool live = (uint32_t)mm < count && R[mm] != 0.f;  // (R = 0: every element codes to 0)
-    no_slots |= (live && n == kNoSlot ? 1u : 0u) << mm;
-    long_slots |= (live && n != kNoSlot && n > 32u ? 1u : 0u) << mm;
-    const int in = (uint32_t)lane < (live && n != kNoSlot ? min(n, 32u) : 0u);
+    no_slots |= (live && pairs == kNoSlot ? 1u : 0u) << mm;
+    long_slots |= (live && pairs != kNoSlot && pairs > 16u ? 1u : 0u) << mm;
+    const int in = (uint32_t)lane < (live && pairs != kNoSlot ? min(2 * pairs, 32u) : 0u);
     const int one = in & entry_codes_one<kChunkPosMask>(e, R[mm]);
     if (one) put((uint32_t)mm, e, 1u | ((e >> 31) << 1));
     undecided |= (uint32_t)(in & ~one & ~entry_codes_zero<kChunkPosMask>(e, R[mm])) << mm;
@@ -2268,8 +2292,8 @@ __global__ __launch_bounds__(kBlock, 8) void quantize_l2_candidates_kernel(
       }
       const bool longer = ((long_slots >> mm) & 1u) != 0u;
       if (!longer && __builtin_amdgcn_ballot_w64((int)(undecided >> mm) & 1) == 0ull) continue;
-      const uint32_t* __restrict__ sl = slots + ((uint64_t)m * chunks + chunk) * kSlotEntries;
-      const uint32_t n = counts[((uint64_t)(m / kGroup) * chunks + chunk) * kGroup + m % kGroup];
+      const uint32_t* __restrict__ sl = slots + ((uint64_t)m * chunks + chunk) * kL2SlotEntries;
+      const uint32_t n = 2u * counts[((uint64_t)(m / kGroup) * chunks + chunk) * kGroup + m % kGroup];
 #pragma unroll 1
       for (uint32_t i = (uint32_t)lane; i < n; i += kWave) {  // all of them once more: or-ing a code in twice changes nothing
         const uint32_t e = sl[i];
@@ -2465,7 +2489,8 @@ hipError_t absmax_vec_launch(const CodecShape& c, const float* g, const float* g
 
 // Scratch of the ternary coder that reads g once: the word that says whether the slots are used, the
 // sample's maxima [M], the sample pass's partial maxima [kAbsmaxMaxBlocks][M], the overflow counts of the
-// scale pass's workgroups (as many), the slots [M][d / 1024] of 512 bytes.
+// scale pass's workgroups (as many), the slots [M][d / 1024] of 512 bytes (of the l2 scale: [M][d / 4096] of 1792 bytes, and
+// their counts).
 struct CandidateScratch {
   uint32_t* use_slots;
   float* sample_max;
@@ -2498,10 +2523,13 @@ inline CandidateScratch candidate_scratch(const CodecShape& c, void* scratch) {
   return cs;
 }
 
-// The l2 scale's counts: a byte per worker and chunk, eight workers to a word, [ceil(M / 8)][chunks].  Its slots, one per
-// worker and chunk, take a quarter of the room of one per tile; the counts lie behind them.
+// The l2 scale's counts: a byte per worker and chunk, eight workers to a word, [ceil(M / 8)][chunks].  They lie behind its slots,
+// one per worker and chunk, in the room of one per tile.
 inline uint64_t* l2_slot_counts(const CodecShape& c, const CandidateScratch& cs) {
-  return reinterpret_cast<uint64_t*>(cs.slots + (uint64_t)c.M * (c.d / kTreeChunk) * kSlotEntries);
+  constexpr int kTileSlots = kTreeChunk / (int)kWaveTileElements * kSlotEntries;
+  static_assert(kL2SlotEntries * sizeof(uint32_t) + 8 <= kTileSlots * sizeof(uint32_t) && kL2SlotEntries % 32 == 0,
+                "with 8 bytes of counts per worker it fits, and slots are whole lines of 128 bytes");
+  return reinterpret_cast<uint64_t*>(cs.slots + (uint64_t)c.M * (c.d / kTreeChunk) * kL2SlotEntries);
 }
 
 // The sample: every kSampleStride-th whole wavefront tile of every row.

@@ -87,11 +87,36 @@ def test_l2_slots_filled_to_their_edges(d):
     check(M, d, B.NORM_SUB, v, torch.zeros(d, device=DEV), 7, B.SCALE_L2)
 
 
+def test_l2_slots_filled_tile_by_tile():
+    # candidates per tile of a chunk: up to 48 wait in the staging area for the tiles behind, a tile finds room for 128, a slot holds
+    # 448 with odd numbers rounded up to pairs; one too many of any and the chunk is coded from g
+    M, d = 5, 1 << 24
+    gen = torch.Generator(device=DEV).manual_seed(10)
+    v = torch.zeros((M, d), device=DEV)
+    fills = ((48, 128, 0, 0), (48, 129, 0, 0), (49, 128, 1, 0), (0, 0, 0, 128), (0, 0, 0, 176), (0, 0, 0, 177), (112, 112, 112, 112),
+             (112, 112, 112, 113), (111, 111, 111, 111), (111, 111, 111, 113), (1, 1, 1, 1), (49, 49, 49, 49), (47, 2, 0, 31), (17, 17, 1, 0))
+    for m in range(M):
+        for i, fill in enumerate(fills):
+            for t, k in enumerate(fill):
+                at = torch.randperm(1024, generator=gen, device=DEV)[:k] + 4096 * (1 + 32 * i + 5 * m) + 1024 * t
+                v[m, at] = torch.randn(k, generator=gen, device=DEV)
+    check(M, d, B.NORM_SUB, v, torch.zeros(d, device=DEV), 8, B.SCALE_L2)
+
+
+def test_l2_scale_of_rows_that_are_not_zero_in_runs():
+    # three tiles in a hundred hold everything: some fifty candidates in each, hundreds where two or more share a chunk
+    M, d = 16, 1 << 22
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    v = torch.randn((M, d), generator=gen, device=DEV)
+    v.view(M, -1, 1024).mul_((torch.rand((M, d // 1024, 1), generator=gen, device=DEV) < 0.03).float())
+    check(M, d, B.NORM_SUB, v, torch.zeros(d, device=DEV), 9, B.SCALE_L2)
+
+
 # Rows that are zero where the sample looks: every other element is a candidate.  share of the groups of four tiles hold `tiles` tiles
 # with `each` candidates (and the rest nothing); the slots are used unless more than one per fifty tiles overflow.
-@pytest.mark.parametrize("scale,share,tiles,each,used", [(B.SCALE_L2, 0.04, 1, 1024, 1), (B.SCALE_L2, 0.075, 1, 1024, 1),
-                                                         (B.SCALE_L2, 0.09, 1, 1024, 0), (B.SCALE_MAX, 0.04, 1, 1024, 1),
-                                                         (B.SCALE_MAX, 0.04, 3, 1024, 0), (B.SCALE_MAX, 0.3, 4, 127, 1)])
+@pytest.mark.parametrize("scale,share,tiles,each,used", [
+    (B.SCALE_L2, 0.04, 1, 1024, 1), (B.SCALE_L2, 0.075, 1, 1024, 1), (B.SCALE_L2, 0.09, 1, 1024, 0), (B.SCALE_L2, 0.3, 4, 112, 1),
+    (B.SCALE_L2, 0.3, 4, 113, 0), (B.SCALE_MAX, 0.04, 1, 1024, 1), (B.SCALE_MAX, 0.04, 3, 1024, 0), (B.SCALE_MAX, 0.3, 4, 127, 1)])
 def test_which_rows_the_slots_are_used_for(scale, share, tiles, each, used):
     M, d = 16, 1 << 22
     gen = torch.Generator(device=DEV).manual_seed(17)
