@@ -206,11 +206,11 @@ bool single_pass_ok(const tng_ctx* ctx, const float* g, const float* gref, const
 
 // The scale pass.  fused_rows > 0: a gradient kernel has already left that many rows of partial maxima in the
 // workspace, only their reduction remains.  On return *rows is the number of rows of partial maxima whose reduction
-// is left to the next launch (0: scales is complete; the pass leaves at most max_left of its own), and *by_candidates
-// tells that the candidate slots hold what the quantise pass needs.  slots_ok: whether they may be used with the
+// is left to the next launch (0: scales is complete; the pass leaves at most max_left of its own, with hold by taking fewer
+// workgroups), and *by_candidates tells that the candidate slots hold what the quantise pass needs.  slots_ok: whether they may be used with the
 // largest-magnitude scale; with the l2 scale they are wherever there are any.
 tng_status scale_impl(tng_ctx* ctx, uint32_t iter, const float* g, const float* gref, const uint32_t* codes,
-                      float* scales, uint32_t fused_rows, uint32_t max_left, bool slots_ok, uint32_t* rows,
+                      float* scales, uint32_t fused_rows, uint32_t max_left, bool hold, bool slots_ok, uint32_t* rows,
                       bool* by_candidates) {
   hipError_t e = hipSuccess;
   *rows = 0;
@@ -238,7 +238,7 @@ tng_status scale_impl(tng_ctx* ctx, uint32_t iter, const float* g, const float* 
     e = tng::launch_absmax_candidates(ctx->shape, iter, g, gref, ctx->gref2, ctx->partials, ctx->cand, scales,
                                       ctx->stream);
   } else {
-    e = tng::launch_absmax(ctx->shape, g, gref, ctx->gref2, ctx->partials, scales, max_left, rows, ctx->stream);
+    e = tng::launch_absmax(ctx->shape, g, gref, ctx->gref2, ctx->partials, scales, max_left, hold, rows, ctx->stream);
   }
   return hip_status(e);
 }
@@ -260,8 +260,8 @@ tng_status encode_impl(tng_ctx* ctx, uint32_t iter, const float* g, const float*
   uint32_t rows = 0;
   bool by_candidates = false;
   mark(ctx, call, 0);
-  tng_status s = scale_impl(ctx, iter, g, gref, codes, scales, fused_rows, tng::quantize_fused_rows(ctx->shape), true, &rows,
-                            &by_candidates);
+  tng_status s = scale_impl(ctx, iter, g, gref, codes, scales, fused_rows, tng::quantize_fused_rows(ctx->shape), false, true,
+                            &rows, &by_candidates);
   if (s != TNG_OK) return s;
   mark(ctx, call, 1);
   s = quantize_impl(ctx, iter, g, gref, codes, scales, rows, by_candidates);
@@ -693,8 +693,8 @@ tng_status tng_step(tng_ctx* ctx, uint32_t iter, float* w, float* gref, float* g
     // 504 against 498; d = 2^24, M = 4: 164 against 152).  With the l2 scale, under which hardly an element is a candidate, the
     // slots are (d = 2^23, M = 8: 150 against 125; d = 2^24, M = 8: 281 against 223, M = 5: 224 against 178).
     const bool slots_ok = c.M <= 4 || c.M > 16 || (uint64_t)c.M * c.d > (1ull << 27);
-    s = scale_impl(ctx, iter, g, gref, codes, scales, fused_rows, tng::quantize_decode_rows(ctx->shape), slots_ok, &rows,
-                   &by_candidates);
+    s = scale_impl(ctx, iter, g, gref, codes, scales, fused_rows, tng::quantize_decode_rows(ctx->shape), true, slots_ok,
+                   &rows, &by_candidates);
     if (s != TNG_OK) return s;
     if (by_candidates) {
       s = quantize_impl(ctx, iter, g, gref, codes, scales, rows, true);

@@ -2457,11 +2457,13 @@ inline uint32_t workgroups_per_group(uint32_t main_blocks, uint32_t tail, uint32
   return tail == 0 || groups == 1 || n < 64 ? n : (n + kGroupMultiple - 1) / kGroupMultiple * kGroupMultiple;
 }
 
-// Where the next launch can reduce max_left rows of partial maxima by itself, no more workgroups than leave that many, if these
-// still fill the chip: its own launch for the reduction costs 5 us, and workgroups that walk a few tiles beat twice the number
-// that take one (given gradients d = 4e6, M = 8: 980 rows of four groups and the reduction 28.8 + 4.9 us, 256 rows 26.4; d = 2e6,
-// M = 8 16.4 + 4.7, 14.3).  Not for worker counts that are no power of two, whose maxima the next launch has to read one by
-// one (d = 3e6, M = 7, combined form 62.1 us with the reduction's launch, 64.8 without).
+// hold: where the one-launch tail can reduce max_left rows of partial maxima by itself, no more workgroups than leave that many, if
+// these still fill the chip: a launch of its own for the reduction costs 5 us, and workgroups that walk a few tiles beat twice the
+// number that take one (given gradients d = 4e6, M = 8: 980 rows of four groups and the reduction 28.8 + 4.9 us, 256 rows 26.4; d =
+// 2e6, M = 8 16.4 + 4.7, 14.3).  Not for worker counts that are no power of two, whose maxima the next launch has to read one by
+// one (d = 3e6, M = 7, combined form 62.1 us with the reduction's launch, 64.8 without).  Not ahead of the
+// quantiser, every wavefront of which would read all those rows (encode M = 64, d = 163840 18.4 us with the reduction's launch, 21.7
+// held to 25 rows; 4-bit, quotient 21.7 / 25.6; M = 128, d = 98304 21.3 / 23.7; M = 32, d = 220004 15.7 / 16.5).
 constexpr uint32_t kAbsmaxFewBlocks = 960;
 // One group of workers: 1024 workgroups (four a compute unit) that walk the tiles instead of up to 4096, whose last round is
 // short.  Encode + decode, before / after: d = 2^25, M = 1, 4-bit 137.8 / 133.6 us; d = 2e7, M = 2, no normalisation 71.8 / 68.5;
@@ -2472,12 +2474,13 @@ constexpr uint32_t kAbsmaxWalkers = 1024;
 constexpr uint64_t kAbsmaxLongTiles = 16384;
 template <int NORM, int MC>
 hipError_t absmax_vec_launch(const CodecShape& c, const float* g, const float* gref, const float* gref2,
-                             float* partials, uint32_t max_left, uint32_t* nblocks, hipStream_t s) {
+                             float* partials, uint32_t max_left, bool hold, uint32_t* nblocks, hipStream_t s) {
   const uint32_t tail = tail_workgroups(c.d, MC), groups = (c.M + MC - 1) / MC;
   const uint64_t per_y = (c.d / kWaveTileElements + kWavesPerBlock - 1) / kWavesPerBlock;
   uint32_t main_blocks = (uint32_t)(per_y < kAbsmaxMaxBlocks - tail ? per_y : kAbsmaxMaxBlocks - tail);
-  if (main_blocks + tail > max_left && max_left > tail && (max_left - tail) * groups >= kAbsmaxFewBlocks && (c.M & (c.M - 1)) == 0)
-    main_blocks = max_left - tail;
+  const uint32_t limit = max_left > tail ? max_left - tail : 0u;
+  if (hold && main_blocks > limit && limit * groups >= kAbsmaxFewBlocks && (c.M & (c.M - 1)) == 0)
+    main_blocks = limit;
   else if (groups == 1 && main_blocks > kAbsmaxWalkers && per_y <= kAbsmaxLongTiles)
     main_blocks = kAbsmaxWalkers;
   *nblocks = main_blocks + tail;
@@ -2624,14 +2627,15 @@ hipError_t quantize_candidates_dispatch(const CodecShape& c, uint32_t iter, cons
 
 template <int NORM>
 hipError_t absmax_dispatch(const CodecShape& c, const float* g, const float* gref, const float* gref2,
-                           float* partials, float* scales, uint32_t max_left, uint32_t* left_rows, hipStream_t s) {
+                           float* partials, float* scales, uint32_t max_left, bool hold, uint32_t* left_rows,
+                           hipStream_t s) {
   uint32_t nblocks = 0;
   hipError_t e;
   switch (pick_workers_per_block(c.M, div_up_u32(c.d, (uint64_t)kBlock * kAbsmaxLoads * 4), 0.3)) {
-    case 8: e = absmax_vec_launch<NORM, 8>(c, g, gref, gref2, partials, max_left, &nblocks, s); break;
-    case 4: e = absmax_vec_launch<NORM, 4>(c, g, gref, gref2, partials, max_left, &nblocks, s); break;
-    case 2: e = absmax_vec_launch<NORM, 2>(c, g, gref, gref2, partials, max_left, &nblocks, s); break;
-    default: e = absmax_vec_launch<NORM, 1>(c, g, gref, gref2, partials, max_left, &nblocks, s); break;
+    case 8: e = absmax_vec_launch<NORM, 8>(c, g, gref, gref2, partials, max_left, hold, &nblocks, s); break;
+    case 4: e = absmax_vec_launch<NORM, 4>(c, g, gref, gref2, partials, max_left, hold, &nblocks, s); break;
+    case 2: e = absmax_vec_launch<NORM, 2>(c, g, gref, gref2, partials, max_left, hold, &nblocks, s); break;
+    default: e = absmax_vec_launch<NORM, 1>(c, g, gref, gref2, partials, max_left, hold, &nblocks, s); break;
   }
   if (e != hipSuccess) return e;
   if (nblocks <= max_left) {
@@ -2779,14 +2783,15 @@ hipError_t launch_absmax_finish(const float* partials, uint32_t nblocks, uint32_
 }
 
 hipError_t launch_absmax(const CodecShape& c, const float* g, const float* gref, const float* gref2,
-                         float* partials, float* scales, uint32_t max_left, uint32_t* left_rows, hipStream_t s) {
+                         float* partials, float* scales, uint32_t max_left, bool hold, uint32_t* left_rows,
+                         hipStream_t s) {
   *left_rows = 0;
   switch (c.norm) {
-    case kNormNone: return absmax_dispatch<kNormNone>(c, g, nullptr, nullptr, partials, scales, max_left, left_rows, s);
-    case kNormSub: return absmax_dispatch<kNormSub>(c, g, gref, nullptr, partials, scales, max_left, left_rows, s);
-    case kNormQuot: return absmax_dispatch<kNormQuot>(c, g, gref, nullptr, partials, scales, max_left, left_rows, s);
-    case kNormMean: return absmax_dispatch<kNormMean>(c, g, nullptr, nullptr, partials, scales, max_left, left_rows, s);
-    default: return absmax_dispatch<kNormComb>(c, g, gref, gref2, partials, scales, max_left, left_rows, s);
+    case kNormNone: return absmax_dispatch<kNormNone>(c, g, nullptr, nullptr, partials, scales, max_left, hold, left_rows, s);
+    case kNormSub: return absmax_dispatch<kNormSub>(c, g, gref, nullptr, partials, scales, max_left, hold, left_rows, s);
+    case kNormQuot: return absmax_dispatch<kNormQuot>(c, g, gref, nullptr, partials, scales, max_left, hold, left_rows, s);
+    case kNormMean: return absmax_dispatch<kNormMean>(c, g, nullptr, nullptr, partials, scales, max_left, hold, left_rows, s);
+    default: return absmax_dispatch<kNormComb>(c, g, gref, gref2, partials, scales, max_left, hold, left_rows, s);
   }
 }
 

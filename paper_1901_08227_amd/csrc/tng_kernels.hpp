@@ -31,9 +31,10 @@ constexpr uint32_t kAbsmaxMaxBlocks = 4096;
 
 // scales[m] = max_e |normalize(g[m][e])|, 0 when below FLT_MIN.  partials: device scratch of
 // kAbsmaxMaxBlocks * M floats.  Two launches: partial maxima per workgroup, then one reduction; where the partial
-// maxima are at most max_left rows, the reduction is left to the next launch (*left_rows rows, else 0).
-hipError_t launch_absmax(const CodecShape& c, const float* g, const float* gref, const float* gref2,
-                         float* partials, float* scales, uint32_t max_left, uint32_t* left_rows, hipStream_t s);
+// maxima are at most max_left rows, the reduction is left to the next launch (*left_rows rows, else 0).  hold: the pass may take
+// fewer workgroups to leave no more than that.
+hipError_t launch_absmax(const CodecShape& c, const float* g, const float* gref, const float* gref2, float* partials,
+                         float* scales, uint32_t max_left, bool hold, uint32_t* left_rows, hipStream_t s);
 // Order-pinned float64 sums per worker (4096-element chunks of 256 strided lanes, chunks in groups of
 // 256, everything added in index order).  sums: device scratch of tree_sum_scratch(d, M) doubles.
 // launch_worker_means: means[m] = float(sum_e g[m][e] / d); if scales != nullptr also

@@ -44,3 +44,17 @@ def test_scale_pass_that_walks_the_tiles(d, M, at):
     ctx.normalize_encode(1, g, gref, buf["codes"], buf["scales"])
     assert torch.equal(buf["scales"], g.abs().amax(dim=1)) and float(buf["scales"][M - 1]) == 7.5
     ctx.close()
+
+
+# Encode of short rows of many workers: every tile keeps a workgroup of its own (the scale pass is held to fewer only ahead of the
+# one-launch tail), seen by the rows of partial maxima at the head of a workspace that holds no problem data.
+@pytest.mark.parametrize("d,M", [(163840, 64), (98304, 128), (190000, 32), (266243, 16)])
+def test_scale_pass_ahead_of_the_quantiser(d, M):
+    gen = torch.Generator(device=DEV).manual_seed(d)
+    g, gref = torch.randn((M, d), generator=gen, device=DEV), torch.zeros(d, device=DEV)
+    g[M - 1, d - 1] = -9.0
+    ctx = make_ctx(d, M, 2, B.NORM_SUB, seed=3)
+    _check_encode_decode(ctx, 1, g, gref, gref, "many workers")
+    rows = ctx.workspace[:4 * 4096 * M].view(torch.float32).view(4096, M)
+    assert int((rows.amax(dim=1) > 0).sum()) >= d // 4096
+    ctx.close()
