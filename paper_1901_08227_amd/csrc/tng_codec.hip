@@ -2461,7 +2461,10 @@ inline uint32_t workgroups_per_group(uint32_t main_blocks, uint32_t tail, uint32
 // these still fill the chip: a launch of its own for the reduction costs 5 us, and workgroups that walk a few tiles beat twice the
 // number that take one (given gradients d = 4e6, M = 8: 980 rows of four groups and the reduction 28.8 + 4.9 us, 256 rows 26.4; d =
 // 2e6, M = 8 16.4 + 4.7, 14.3).  Not for worker counts that are no power of two, whose maxima the next launch has to read one by
-// one (d = 3e6, M = 7, combined form 62.1 us with the reduction's launch, 64.8 without).  Not ahead of the
+// one (d = 3e6, M = 7, combined form 62.1 us with the reduction's launch, 64.8 without).  With eight groups, where a few of that many
+// workgroups would have a second tile, half as many with two each up to 1.6 tiles a workgroup, in whole eights (one per die; iterations
+// M = 8, reduction's launch / max_left / half, us: d = 1.1e6 21.9 / 23.2 / 21.2, combined form 29.3 / 34.4 / 28.6; d = 1.5e6 27.2 / 26.7 /
+// 25.6 and 35.6 / 39.0 / 34.8; at d = 1.7e6 28.6 held to max_left, 30.1 with half).  Not ahead of the
 // quantiser, every wavefront of which would read all those rows (encode M = 64, d = 163840 18.4 us with the reduction's launch, 21.7
 // held to 25 rows; 4-bit, quotient 21.7 / 25.6; M = 128, d = 98304 21.3 / 23.7; M = 32, d = 220004 15.7 / 16.5).
 constexpr uint32_t kAbsmaxFewBlocks = 960;
@@ -2480,7 +2483,7 @@ hipError_t absmax_vec_launch(const CodecShape& c, const float* g, const float* g
   uint32_t main_blocks = (uint32_t)(per_y < kAbsmaxMaxBlocks - tail ? per_y : kAbsmaxMaxBlocks - tail);
   const uint32_t limit = max_left > tail ? max_left - tail : 0u;
   if (hold && main_blocks > limit && limit * groups >= kAbsmaxFewBlocks && (c.M & (c.M - 1)) == 0)
-    main_blocks = limit;
+    main_blocks = groups > 4 && 5 * per_y <= 8 * limit ? (((uint32_t)per_y + 1) / 2 + tail + 7) / 8 * 8 - tail : limit;
   else if (groups == 1 && main_blocks > kAbsmaxWalkers && per_y <= kAbsmaxLongTiles)
     main_blocks = kAbsmaxWalkers;
   *nblocks = main_blocks + tail;

@@ -70,3 +70,9 @@ def test_step_scales_from_many_partial_maxima(d, M):
 @pytest.mark.parametrize("d,M", [((1 << 20) + 1028, 8), (1500003, 8), (1 << 22, 8), (1500004, 7)])
 def test_step_scales_from_a_scale_pass_of_few_workgroups(d, M):
     test_step_scales_from_many_partial_maxima(d, M)
+
+
+# ... and to half as many workgroups as tiles up to 1.6 tiles for each of those 2048 / M, of two tiles each (the last one short).
+@pytest.mark.parametrize("d", [(1 << 20) + 4096, 1100000, 1250003, 1671168, 1671169])
+def test_step_scales_from_a_scale_pass_of_half_the_tiles(d):
+    test_step_scales_from_many_partial_maxima(d, 8)
