@@ -3000,6 +3000,7 @@ template <int NORM, int BITS>
 hipError_t quantize_decode_dispatch(const CodecShape& c, uint32_t iter, const float* g, const float* gref,
                                     const float* gref2, float* scales, uint32_t* codes, const float* partials,
                                     uint32_t rows, float* vbar, float* w, float lr, float* ref_out, hipStream_t s) {
+  if (NORM == kNormMean && rows != 0) return hipErrorInvalidValue;  // (that scale comes with the mean, complete)
   if (tail_by_wavefronts(c)) {
     hipLaunchKernelGGL((quantize_decode_split_kernel<NORM, BITS>), dim3((uint32_t)((c.d + kBlock - 1) / kBlock)),
                        dim3(kBlock), 0, s, GradRows{g, c.d}, gref, gref2, scales, codes, c.d, c.words, c.M, c.eps, c.k0,
@@ -3008,11 +3009,15 @@ hipError_t quantize_decode_dispatch(const CodecShape& c, uint32_t iter, const fl
   }
   const uint32_t blocks = (uint32_t)(((c.d + 3) / 4 + kBlock - 1) / kBlock);
   const uint32_t n = rows * c.M;
-  auto kernel = rows == 0 ? quantize_decode_kernel<NORM, BITS, 0>
-                : n <= kTailFewPartials || n > kTailPartials || (c.M & (c.M - 1)) != 0 || n % 4 != 0
-                    ? quantize_decode_kernel<NORM, BITS, kTailLate>
-                : n <= kTailPartialsLong ? quantize_decode_kernel<NORM, BITS, kTailPartialsLong / (4 * kBlock)>
-                                         : quantize_decode_kernel<NORM, BITS, kTailPartials / (4 * kBlock)>;
+  auto kernel = quantize_decode_kernel<NORM, BITS, 0>;
+  if constexpr (NORM != kNormMean) {
+    if (n > kTailPartials || (rows != 0 && (n <= kTailFewPartials || (c.M & (c.M - 1)) != 0 || n % 4 != 0)))
+      kernel = quantize_decode_kernel<NORM, BITS, kTailLate>;
+    else if (n > kTailPartialsLong)
+      kernel = quantize_decode_kernel<NORM, BITS, kTailPartials / (4 * kBlock)>;
+    else if (rows != 0)
+      kernel = quantize_decode_kernel<NORM, BITS, kTailPartialsLong / (4 * kBlock)>;
+  }
   hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kBlock), 0, s, GradRows{g, c.d},
                      reinterpret_cast<const float4*>(gref), reinterpret_cast<const float4*>(gref2), scales, codes, c.d,
                      c.words, c.M, c.eps, c.k0, c.k1, iter, c.means, partials, rows, reinterpret_cast<float4*>(vbar),
