@@ -1345,9 +1345,11 @@ __global__ __launch_bounds__(kBlock) void decode_vec_kernel(
 // What a wavefront waits for comes in the order in which it asked: first what makes the scales, then the reference, then the
 // workers' rows, each of which is coded while the ones behind it are on their way.  (The scales behind the rows, and whole and
 // ragged wavefronts in one body: every wavefront waited for all of its rows first.  This kernel, before / after: d = 2^22, M = 8,
-// quotient 48.0 / 45.0 us; d = 2e6, M = 8, 4-bit 24.6 / 23.6; d = 8e6, M = 4, 4-bit 57 / 55; d = 4e6, M = 8 38.9 / 38.1.)  Not where
-// many partial maxima would come ahead of the rows, up to d = 2^20, where all wavefronts run at once (iteration of the
-// Rosenbrock chain, d = 2^20, M = 8 25.3 / 25.4 us, M = 7 22.9 / 23.3).
+// quotient 48.0 / 45.0 us; d = 2e6, M = 8, 4-bit 24.6 / 23.6; d = 8e6, M = 4, 4-bit 57 / 55; d = 4e6, M = 8 38.9 / 38.1.)  So too where
+// the maxima are many, up to d = 2^20, eight float4 a thread (iterations, behind the rows / ahead of them: Rosenbrock chain, d = 2^20,
+// M = 8 25.6 / 25.1 us, 4-bit, quotient 31.9 / 30.0; given gradients, d = 2^20, M = 16, quotient 38.5 / 37.0, combined form 42.6 / 41.1;
+// d = 528384, M = 16 23.0 / 22.4), but not where they are few or would be read one by one (M no power of two: Rosenbrock, d = 2^20, M =
+// 7 22.9 / 23.3).
 // ------------------------------------------------------------------------------------------
 constexpr int kTailWorkers = 8;
 constexpr uint32_t kTailMaxWorkers = 64;

@@ -76,3 +76,10 @@ def test_step_scales_from_a_scale_pass_of_few_workgroups(d, M):
 @pytest.mark.parametrize("d", [(1 << 20) + 4096, 1100000, 1250003, 1671168, 1671169])
 def test_step_scales_from_a_scale_pass_of_half_the_tiles(d):
     test_step_scales_from_many_partial_maxima(d, 8)
+
+
+# 2048 to 8192 partial maxima of a power of two workers, eight float4 a thread of which the last ones repeat: whole workgroups only,
+# and a last one that is not (it reduces the same maxima by the other path).
+@pytest.mark.parametrize("d", [(1 << 19) + 4096, 700416, 700003, (1 << 20) - 4])
+def test_step_scales_from_partial_maxima_requested_ahead_of_the_rows(d):
+    test_step_scales_from_many_partial_maxima(d, 16)
