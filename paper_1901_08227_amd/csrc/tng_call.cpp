@@ -6,8 +6,8 @@
 //
 // address: of the entry point; kinds: a letter per tensor, d float32[d], g float32[M d], c int32[M words], s float32[M], behind a
 // '-' for an entry point that takes no iteration number (iter is then not looked at).  None says that an argument is not a plain
-// case (no tensor, another type, too short, a tensor subclass or a wrapper without storage, an iteration that is no int):
-// nothing was called, and the caller goes the way through ctypes, which raises what there is to raise.
+// case (no tensor, another type, too short, a tensor subclass other than Parameter or a wrapper without storage, an iteration that
+// is no int): nothing was called, and the caller goes the way through ctypes, which raises what there is to raise.
 #include <Python.h>
 
 #include <ATen/core/Tensor.h>
