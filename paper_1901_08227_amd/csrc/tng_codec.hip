@@ -668,7 +668,8 @@ __global__ __launch_bounds__(kBlock, NORM == kNormComb || (NORM == kNormQuot && 
 // and 0 for every R above it (thresholds widened by what the roundings can move); the few elements whose
 // bracket contains R (three candidates in ten thousand) are fetched from g and coded from the value and its
 // draw.  Everything else is cleared, and the words are packed.  A slot that overflowed (a tile with more
-// than kCandCap candidates) sends its tile through the ordinary path.  The codes are those of the two-pass
+// than kCandCap candidates) sends its tile through the ordinary path.  (With the l2 scale a slot is per worker and chunk of
+// four tiles: 12 bits of position, 11 of tau's significand; see l2_select_kernel.)  The codes are those of the two-pass
 // coder bit for bit; what changes is that g is read once: 4 + 4/M bytes per element instead of 8 + 8/M.
 // Used for 2-bit codes when the row is long enough for the second read to come from
 // memory; the ragged last tile of a row has no slots, the scale pass and the ordinary quantiser take it in
@@ -1358,8 +1359,8 @@ constexpr uint32_t kTailFewPartials = 1024;  // up to here single loads: at a fe
 
 // What the coder needs of a worker: its scale R, 1 / R and R / S, and its mean.  Of R = 0 all are 0, under which every number
 // codes to level 0.  Made once per workgroup: the two divisions by every lane for every worker were a seventh of the kernel's
-// instructions.  With that and the part of a draw that is the same for all workers made once (philox_block), the tail of the
-// Rosenbrock iteration at d = 2^20, M = 8 takes 11.8 us for 13.6, given gradients of d = 4e6, M = 8, quotient 71.1 for 74.2.
+// instructions.  With that and the part of a draw that is the same for all workers made once (philox_block), the Rosenbrock
+// iteration at d = 2^20, M = 8 went from 28.6 to 27.9 us, given gradients of d = 4e6, M = 8, quotient from 74.2 to 71.1.
 struct __align__(16) TailWorker {
   float r, inv_r, step, mu;
 };

@@ -901,8 +901,10 @@ constexpr int kCsrRows = 512;      // minibatch rows staged in LDS per trip
 // segment and a branch around every load and use, the dot products took 600 vector and 850 scalar instructions per
 // wavefront and 512 rows, about two thirds of their time, and the segments' loads by themselves ran 25 to 30 % slower than
 // with 16 bytes per lane (1.21 -> 0.92 ms for the segments of 2^14 columns, 64 workers, 512 rows of 16777 pairs).  Iteration
-// at d = 2^24, M = 64, B = 512, 0.1 % density 4276 -> 3899 us (dot products 1180 -> 959, gradient 2055 -> 1903, which the LDS
-// bounds: its atomic adds and write-out keep it busy for three quarters of the time); d = 2^16, M = 8 19.1 -> 17.8.
+// at d = 2^24, M = 64, B = 512, 0.1 % density 4276 -> 3899 us (dot products 1180 -> 959, gradient 2055 -> 1903); d = 2^16, M = 8 19.1 ->
+// 17.8.  By the counters no unit bounds the gradient pass there: its LDS is active 36 % of the clocks (a sixth of that bank
+// conflicts), the vector unit issues 29 %, memory moves 4.7 TB/s; its wavefronts wait for memory counters and barriers 39 % of their
+// time and to issue 47 %.
 constexpr int kCsrLanes = 8;                  // lanes that share one row segment
 constexpr int kCsrUnroll = 4;                 // row segments per lane group and trip
 constexpr uint32_t kCsrStep = 2 * kCsrLanes;  // entries that a load of each lane covers

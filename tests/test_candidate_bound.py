@@ -7,7 +7,9 @@ c1 = fl(fl(1 / R^) (2^32 + 2^12)); everything that fails it is coded 0 without b
 quantise pass sees a kept element only as a bracket [lo, hi] around tau = |v| / u, the scale up to which the
 element codes non-zero (13 bits of the value's significand, a reciprocal good to one unit in the last place,
 13 bits of the quotient's significand), and decides from the row's scale alone: level 1 for
-R <= lo (1 - 2^-19), level 0 for R >= hi (1 + 2^-12), the value itself in between.  Both steps are only right if
+R <= lo (1 - 2^-19), level 0 for R >= hi (1 + 2^-12), the value itself in between; with 11 bits (the l2 scale's slots) level 0 for
+R >= hi (1 + 2^-10), and level 0 never under a scale below 2^-101, where the value may be a subnormal number whose cut significand
+bounds nothing.  Both steps are only right if
 
   (1) an element that fails the test has level 0 for every R >= R^, and
   (2) the level is 1 at every scale below the bracket's lower threshold and 0 at every scale above the upper one.

@@ -71,8 +71,8 @@ def test_l2_scale_outside_the_sample():
 @pytest.mark.parametrize("d", [(1 << 24) + 4096 + 3 * 1024, (1 << 24) + 1024 + 7])
 def test_l2_slots_filled_to_their_edges(d):
     # chunks that hold exactly k candidates (the rows are zero where the sample looks, so every other element is one): the
-    # quantise pass takes the first 32 at once, all of up to 128 again, and codes a chunk with more from g; whole tiles behind
-    # the last whole chunk have no slots
+    # quantise pass takes the first 32 at once, and all of them in a loop where there are more; whole tiles behind the last whole
+    # chunk have no slots
     M = 5
     gen = torch.Generator(device=DEV).manual_seed(9)
     v = torch.zeros((M, d), device=DEV)
