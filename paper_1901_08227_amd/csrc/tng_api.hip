@@ -207,8 +207,8 @@ bool single_pass_ok(const tng_ctx* ctx, const float* g, const float* gref, const
 // The scale pass.  fused_rows > 0: a gradient kernel has already left that many rows of partial maxima in the
 // workspace, only their reduction remains.  On return *rows is the number of rows of partial maxima whose reduction
 // is left to the next launch (0: scales is complete; the pass leaves at most max_left of its own, with hold by taking fewer
-// workgroups), and *by_candidates tells that the candidate slots hold what the quantise pass needs.  slots_ok: whether they may be used with the
-// largest-magnitude scale; with the l2 scale they are wherever there are any.
+// workgroups), and *by_candidates tells that the candidate slots hold what the quantise pass needs.  slots_ok: whether they may be
+// used with the largest-magnitude scale; with the l2 scale they are wherever there are any.
 tng_status scale_impl(tng_ctx* ctx, uint32_t iter, const float* g, const float* gref, const uint32_t* codes,
                       float* scales, uint32_t fused_rows, uint32_t max_left, bool hold, bool slots_ok, uint32_t* rows,
                       bool* by_candidates) {
