@@ -222,8 +222,8 @@ __device__ __forceinline__ void block_max_to_partials(float (&mx)[MC], uint32_t 
 
 // scales[m] = max over the nblocks partial maxima of worker m; a maximum below the smallest normal
 // number is taken as 0.  One workgroup per worker.
-__device__ __forceinline__ void absmax_finish_worker(const float* __restrict__ partials, uint32_t nblocks, uint32_t M,
-                                                     float* __restrict__ scales, uint32_t m) {
+__device__ __forceinline__ float absmax_finish_worker(const float* __restrict__ partials, uint32_t nblocks, uint32_t M,
+                                                      float* __restrict__ scales, uint32_t m) {
   __shared__ float red[kWavesPerBlock];
   float v = 0.f;
   for (uint32_t b = threadIdx.x; b < nblocks; b += kBlock) v = fmaxf(v, partials[(uint64_t)b * M + m]);
@@ -233,8 +233,10 @@ __device__ __forceinline__ void absmax_finish_worker(const float* __restrict__ p
   if (threadIdx.x == 0) {
 #pragma unroll
     for (int k = 1; k < kWavesPerBlock; ++k) v = fmaxf(v, red[k]);
-    scales[m] = v < FLT_MIN ? 0.f : v;
+    v = v < FLT_MIN ? 0.f : v;
+    scales[m] = v;
   }
+  return v;  // (thread 0's)
 }
 __global__ __launch_bounds__(kBlock) void absmax_finish_kernel(const float* __restrict__ partials, uint32_t nblocks,
                                                                uint32_t M, float* __restrict__ scales) {
@@ -486,6 +488,9 @@ typedef uint32_t v4u_t __attribute__((ext_vector_type(4)));
 // memory counters (the wavefront ends), and the trailing no-op covers the cycle in which the data
 // registers must stay untouched.  Measured against 4-byte sc1 stores issued per worker: quantise pass
 // 0.834 -> 0.806 ms; the same with non-temporal or plain 16-byte stores: 0.84 / 0.88 ms.
+__device__ __forceinline__ void store4_through(uint32_t* dst, const v4u_t& w4) {
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(dst), "v"(w4) : "memory");
+}
 template <int WPW, int SLOTS>
 __device__ __forceinline__ void flush_packed(FragmentBuffer<WPW, SLOTS>& lds, int wave, int lane,
                                              uint32_t* __restrict__ codes, uint64_t words, uint64_t word_base,
@@ -499,8 +504,7 @@ __device__ __forceinline__ void flush_packed(FragmentBuffer<WPW, SLOTS>& lds, in
     const uint32_t r = (uint32_t)(r0 + lane / LPR);
     if (r < count) {
       const v4u_t w4 = *reinterpret_cast<const v4u_t*>(&lds.b32[r][wave][4 * quad]);
-      v4u_t* dst = reinterpret_cast<v4u_t*>(codes + (uint64_t)(m0 + r) * words + word_base) + quad;
-      asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(dst), "v"(w4) : "memory");
+      store4_through(codes + (uint64_t)(m0 + r) * words + word_base + 4 * quad, w4);
     }
   }
 }
@@ -659,31 +663,34 @@ __global__ __launch_bounds__(kBlock, NORM == kNormComb || (NORM == kNormQuot && 
 // R^ <= R at hand: fl(1 / R^) >= fl(1 / R) (the correctly rounded quotient is monotone) and
 // fl(|v| x) is monotone in x, so  u >= fl(|v| fl(1 / R^))  implies  u >= fl(|v| fl(1 / R)):  level 0
 // whatever R turns out to be.  The elements that fail this test -- the candidates -- are kept in a slot per
-// worker and wavefront tile, one 32-bit word each: the sign of the normalised value, the position within the
-// tile in the low 10 bits, and in between tau = |v| / u -- the scale up to which the element codes non-zero --
-// to 13 bits of its significand.  R^ is the maximum over a sample of the row taken beforehand (one tile in
+// worker and wavefront tile.  R^ is the maximum over a sample of the row taken beforehand (one tile in
 // kSampleStride); a row whose sample says that its candidates will not fit the slots is left to the
-// ordinary path.  The quantise pass then reads the slots instead of g and compares the row's scale with
-// the entry: the level [u < fl(|v| fl(1 / R))] is 1 for every R below the bracket that the entry gives for tau
-// and 0 for every R above it (thresholds widened by what the roundings can move); the few elements whose
-// bracket contains R (three candidates in ten thousand) are fetched from g and coded from the value and its
+// ordinary path.  The quantise pass then reads the slots instead of g.  An entry is half a word: the sign, the position within the
+// 256 elements of one of the tile's four loads, and in 7 bits a bin of x = u R^ / |v|: the element codes non-zero if x is below
+// rho = R^ / R, and only the few elements in the bin of rho (bin_entry below) are fetched from g and coded from the value and its
 // draw.  Everything else is cleared, and the words are packed.  A slot that overflowed (a tile with more
-// than kCandCap candidates) sends its tile through the ordinary path.  (With the l2 scale a slot is per worker and chunk of
-// four tiles: 12 bits of position, 11 of tau's significand; see l2_select_kernel.)  The codes are those of the two-pass
+// than 126 candidates) sends its tile through the ordinary path.  Where the sample gives no bound (it is all zeros) an entry is
+// a word: the sign, the position in 10 bits, and tau = |v| / u -- the scale up to which the element codes non-zero -- to 13 bits of its
+// significand (slot_entry).  With the l2 scale a slot is per worker and chunk of
+// four tiles: words of 12 bits of position and 11 of tau's significand; see l2_select_kernel.  The codes are those of the two-pass
 // coder bit for bit; what changes is that g is read once: 4 + 4/M bytes per element instead of 8 + 8/M.
 // Used for 2-bit codes when the row is long enough for the second read to come from
 // memory; the ragged last tile of a row has no slots, the scale pass and the ordinary quantiser take it in
 // workgroups of their own (encode + decode at d = 2^25 + 3, M = 5: 333 us by two passes, 262 this way; d = 2^26 + 1, M = 1:
 // 263 / 225).
 // ------------------------------------------------------------------------------------------
-constexpr int kCandCap = 127;         // candidates a slot holds; word 0 of a slot is their count
+constexpr int kCandCap = 127;         // candidates a slot of words holds; word 0 of a slot is their count
 constexpr int kSlotEntries = 128;     // 32-bit words per slot: 512 bytes per worker and wavefront tile
+constexpr uint32_t kSlotLine = 32;    // words of its first line, which is written and read in one piece
 constexpr uint32_t kSampleStride = 128;  // the sample: every 128th wavefront tile of a row
 constexpr uint32_t kCandPosMask = 0x3FFu;  // low 10 bits of a candidate word: position within the tile
 constexpr uint32_t kChunkPosMask = 0xFFFu;  // the l2 scale's slots are per worker and chunk of four tiles: 12 bits
 constexpr int kL2SlotEntries = 448;         // 32-bit words of such a slot, all of them candidates
 constexpr uint32_t kNoSlot = 255u;          // in the place of its count (a byte, in pairs): it overflowed, or the row has none
 static_assert(kL2SlotEntries / 2 < (int)kNoSlot, "the count fits a byte");
+constexpr float kBoundMin = 0x1p-90f;  // below, the sample gives no bound
+// What a worker's slots hold: nothing (too dense), words (tau), or bins of u R^ / |v|, two to a word.
+constexpr uint32_t kFormNone = 0u, kFormWords = 1u, kFormBins = 2u;
 
 // The sample of a row taken before the scale pass: over every kSampleStride-th wavefront tile, the largest
 // |v| (the lower bound R^ of the row's scale) and the sum of |v|.  Their ratio, mean |v| / R^, is the share
@@ -797,7 +804,7 @@ __global__ __launch_bounds__(kBlock) void sample_finish_kernel(const float* __re
     if (L2) mx = (float)sqrt(sq) * (1.0f - 0x1p-10f);
     sample_max[m] = mx < FLT_MIN ? 0.f : mx;
     // (a sum that is no number, or an infinite one, compares false: the slots are then not used)
-    select_ok[m] = sm <= kDenseLimit * sampled * mx ? 1u : 0u;
+    select_ok[m] = sm <= kDenseLimit * sampled * mx ? (L2 || mx < kBoundMin ? kFormWords : kFormBins) : kFormNone;
   }
 }
 
@@ -805,6 +812,7 @@ __global__ __launch_bounds__(kBlock) void sample_finish_kernel(const float* __re
 // draw), one word that takes everything beyond the capacity, then a word per lane for the elements that are no
 // candidates.
 constexpr uint32_t kStageSink = kSlotEntries, kStageWords = kStageSink + 2 + kWave;
+static_assert(kStageWords <= 255, "a candidate's two words by one instruction");
 // Of the l2 scale, where candidates gather over a chunk: the staging area is written out at the end of a tile that leaves more than
 // kL2FlushAt in it, so that every tile finds room for as many as a slot per tile held.  (Four workgroups a compute unit: 40.6 of
 // 40.9 KB of LDS each.)
@@ -820,7 +828,7 @@ static_assert(kL2StageWords % 2 == 0, "read in pairs");
 // quantise pass codes a candidate exactly, so more is harmless.  Below 2^-90 no bound is claimed (c1 would
 // overflow): every non-zero element is a candidate.
 __device__ __forceinline__ float candidate_factor(float r_hat) {
-  return r_hat >= 0x1p-90f ? (1.0f / r_hat) * (0x1p32f * (1.0f + 0x1p-20f)) : INFINITY;
+  return r_hat >= kBoundMin ? (1.0f / r_hat) * (0x1p32f * (1.0f + 0x1p-20f)) : INFINITY;
 }
 
 // The candidates of one float4 per lane (load j of the tile) go to number base of the staging area and behind it.  FEW: candidates
@@ -877,6 +885,45 @@ __device__ __forceinline__ int entry_codes_zero(uint32_t e, float r) {  // (fals
   constexpr float kAbove = POS_MASK == kCandPosMask ? 1.0f + 0x1p-12f : 1.0f + 0x1p-10f;
   return (int)(r >= 0x1p-101f) & (int)(r >= __uint_as_float((e & 0x7FFFFFFFu) | POS_MASK) * kAbove);
 }
+// With a bound R^ the entries are half as long.  x = u R^ / |v| is uniform on (0, 1) over the candidates, so each has the same chance to
+// lie in the bin of rho and to need its value.  Bins grow with x, 208 to 1 above a half, where rho mostly is (0.8 to 0.9 in Gaussian
+// rows, 0.55 to 0.9 where |v| falls off exponentially), and 44 to 1 below.  Bin 0: u = 0, or no number -- look at the value; 127 is
+// none's.  The entry: the bin, the position within the tile's 256 elements of one load, the sign.
+// (Writes next to the reads cost several times their bytes: at d = 2^27, M = 8 the scale pass takes 767 us without them, 831 with 8
+// bytes a slot, 910 with slots of words, 200 bytes on average, 836 with one whole line of 128 bytes each.  That all of one line is
+// written, and lines lie next to each other, is a part of it: half-words in slots 512 bytes apart 886.)
+constexpr int kBinShift = 9;
+constexpr uint32_t kNoEntry = 0xFFFFu;  // bin 127: behind the last entry
+__device__ __forceinline__ uint32_t bin_of(float x) {
+  const float y = fmaxf(__builtin_fmaf(x, 44.0f, 1.0f), __builtin_fmaf(x, 208.0f, -81.0f));
+  return x > 0.f ? (uint32_t)fminf(y, 126.0f) : 0u;
+}
+__device__ __forceinline__ uint32_t bin_entry(uint32_t value_word, uint32_t draw, float c1) {
+  const float a = __uint_as_float(value_word & 0x7FFFFFFFu & ~kCandPosMask);
+  const float x = (float)(draw & 0xFFFFFF00u) * __builtin_amdgcn_rcpf(a * c1);
+  return (bin_of(x) << kBinShift) | (__builtin_amdgcn_alignbit(value_word, value_word, 31) & 0x1FFu);
+}
+// The x of an entry is good to 2^-12.9 upwards (the cut of |v|) and 2^-19 downwards (c1, the reciprocal), ternary_code's roundings move its
+// level by 2^-21: below the bin of rho (1 - 2^-18) the level is 1, above the bin of rho (1 + 2^-12) it is 0.
+__device__ __forceinline__ uint32_t bin_limits(float r_hat, float r) {
+  const float rho = r_hat / r;
+  const uint32_t below = bin_of(rho * (1.0f - 0x1p-18f)), above = rho >= 0.f ? bin_of(rho * (1.0f + 0x1p-12f)) : 126u;
+  return (below << 8) | (above << 16);
+}
+// The first lines of the slots of all of a worker's tiles lie next to each other, and behind them the rest of each.
+struct Slot {
+  uint32_t *line, *rest;
+  __device__ __forceinline__ Slot(uint32_t* slots, uint64_t ntiles, uint32_t m, uint64_t tile) {
+    uint32_t* worker = slots + (uint64_t)m * ntiles * kSlotEntries;
+    line = worker + tile * kSlotLine;
+    rest = worker + ntiles * kSlotLine + tile * (kSlotEntries - kSlotLine);
+  }
+  // half-words 64 k to 64 k + 63
+  __device__ __forceinline__ uint16_t* halves(int k) const { return reinterpret_cast<uint16_t*>(k == 0 ? line : rest); }
+};
+__device__ __forceinline__ void store_half_through(uint16_t* p, uint32_t v) {
+  __hip_atomic_store(p, (uint16_t)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 // The code of element coord of worker m from its value.
 template <int NORM>
 __device__ __forceinline__ uint32_t code_of_element(const GradRows& g, const float4* ref4, uint64_t coord, uint32_t m, float r,
@@ -913,25 +960,44 @@ __device__ __forceinline__ void code_tile(lds_u8* bytes, const GradRows& g, cons
   }
 }
 
-// The staged candidates (base - 1 of them) to their slot; false where they do not fit (only the count is written).
-__device__ __forceinline__ bool write_slot(uint32_t* stage, const uint32_t* draws, uint32_t base, int lane, uint32_t* slot_words) {
-  if (lane == 0) stage[0] = base - 1;  // candidates found (more than kCandCap: the slot is not used)
+// The candidates of one float4 per lane as stage_candidates stages them, but for the load's place in the position, in straight
+// code: a select on "candidate" becomes a branch, which ends the basic block at every element, unless the instruction is written out.
+// at: LDS address of the next free word of the staging area (the draws lie kStageWords words behind); idle: a lane's own word behind it, for
+// its elements that are no candidates; full: where at stops.
+__device__ __forceinline__ void stage_straight(uint32_t idle, uint32_t full, const float4& v, const U32x4& rnd, float c1, int lane, uint32_t& at) {
+  typedef uint32_t __attribute__((address_space(3))) lds_word;
+  const float vv[4] = {v.x, v.y, v.z, v.w};
+  const uint32_t rr[4] = {rnd.x, rnd.y, rnd.z, rnd.w};
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const uint64_t mask = __builtin_amdgcn_ballot_w64((float)rr[c] < __builtin_fmaf(fabsf(vv[c]), c1, 258.0f));
+    const uint32_t before = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+    const uint32_t own = (before << 2) + at;
+    uint32_t to;
+    asm("v_cndmask_b32 %0, %1, %2, %3" : "=v"(to) : "v"(idle), "v"(own), "s"(mask));
+    lds_word* p = (lds_word*)(uintptr_t)to;
+    p[0] = (__float_as_uint(vv[c]) & ~kCandPosMask) | (uint32_t)c | 4u * (uint32_t)lane;  // (the load is told by the head)
+    p[kStageWords] = rr[c];
+    at = min(at + 4u * (uint32_t)__builtin_popcountll(mask), full);
+  }
+}
+
+// The staged candidates to their slot; false where they do not fit (only the count is written).  Words: the count, then
+// an entry each.  Bins: half-words, the first two of which hold, a byte each, the number of half-words in use and how many come before
+// the entries of the tile's second, third and fourth 256 elements (starts), whose positions then need 8 bits; kNoEntry behind the last.
+__device__ __forceinline__ bool write_slot(const uint32_t* stage, const uint32_t* draws, uint32_t base, uint32_t starts, bool bins, float c1,
+                                           int lane, const Slot& slot) {
   wave_lds_fence();
-  // Words to write, the count included (8 bytes per lane, the last one whatever the staging area holds);
-  // of a slot that overflowed only the count.  (The slots cost about 0.15 ms per launch -- 0.2 GB next to
-  // 4.8 GB of reads -- and pieces rounded up to whole 128-byte lines, 16-byte stores or a quarter fewer bytes
-  // all measured the same; half of it remains when the stores never leave the caches.  The cache policy does
-  // matter: plain stores +0.03 ms, non-temporal ones +0.08 ms.)
   const bool fits = base <= (uint32_t)kSlotEntries;
-  const uint32_t used = fits ? base : 1u;
-  if (2u * (uint32_t)lane < used) {  // one store instruction covers the slot: 8 bytes per lane, device-coherent policy
-    // The reciprocals are taken here, for the two candidates of the lane, not for every element of the tile.
-    const uint2 vw = *reinterpret_cast<const uint2*>(&stage[2 * lane]);
-    const uint2 dw = *reinterpret_cast<const uint2*>(&draws[2 * lane]);
-    const uint32_t e0 = lane == 0 ? vw.x : slot_entry<kCandPosMask>(vw.x, dw.x);  // word 0 of the slot is the count
-    const uint64_t two = ((uint64_t)slot_entry<kCandPosMask>(vw.y, dw.y) << 32) | e0;
-    uint64_t* slot = reinterpret_cast<uint64_t*>(slot_words);
-    __hip_atomic_store(slot + (uint32_t)lane, two, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (bins) {
+    const uint32_t head = min(base, 255u) | starts, e = bin_entry(stage[lane], draws[lane], c1);
+    store_half_through(slot.halves(0) + (uint32_t)lane, lane < 2 ? head >> (16 * lane) : (uint32_t)lane < base ? e : kNoEntry);
+    if (base > (uint32_t)kWave && fits)
+      store_half_through(slot.halves(1) + (uint32_t)lane, (uint32_t)(kWave + lane) < base ? bin_entry(stage[kWave + lane], draws[kWave + lane], c1) : kNoEntry);
+  } else {
+#pragma unroll 1
+    for (uint32_t i = (uint32_t)lane; i < (fits ? base : 1u); i += kWave)
+      store_word_through((i < kSlotLine ? slot.line : slot.rest - kSlotLine) + i, i == 0u ? base - 1u : slot_entry<kCandPosMask>(stage[i], draws[i]));
   }
   wave_lds_fence();
   return fits;
@@ -958,15 +1024,17 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
   // in flight per wavefront.  (Measured 2 % faster than two buffers that drained at the end of every tile:
   // the pass is bound neither by the depth of its prefetch nor by its arithmetic.)
   constexpr int kItems = (MC + 1 + 2) / 3 * 3;
-  __shared__ __attribute__((aligned(16))) uint32_t stage[kWavesPerBlock][kStageWords];
-  __shared__ __attribute__((aligned(16))) uint32_t draws[kWavesPerBlock][kStageWords];
+  __shared__ __attribute__((aligned(16))) uint32_t stages[kWavesPerBlock][2][kStageWords];
   __shared__ __attribute__((aligned(16))) float4 refs[kWavesPerBlock][L][kWave];
   __shared__ uint32_t over[kWavesPerBlock];
+  __shared__ float factor[kWavesPerBlock][MC];
   // the wavefront's number as a value the compiler knows to be the same in every lane: tile numbers, row and
   // slot addresses are then scalar, and a lane's own part of every address is one 32-bit offset
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = threadIdx.x % kWave;
   const uint32_t m0 = blockIdx.y * MC;
   const uint32_t count = min((uint32_t)MC, M - m0);
+  uint32_t* stage = stages[wave][0];
+  uint32_t* draws = stages[wave][1];
   uint32_t nover = 0;  // slots of this wavefront that overflowed
   float mx[MC];
 #pragma unroll
@@ -981,18 +1049,20 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
     if (threadIdx.x == 0) overflowed[(uint64_t)blockIdx.y * gridDim.x + blockIdx.x] = 0u;
     return;
   }
-  float c1[MC];
-  bool select[MC];  // the sample found the worker's row too dense for the slots: only its maximum is taken
-#pragma unroll
-  for (int mm = 0; mm < MC; ++mm) {
-    c1[mm] = candidate_factor(sample_max[min(m0 + (uint32_t)mm, M - 1)]);
-    select[mm] = select_ok[min(m0 + (uint32_t)mm, M - 1)] != 0u;
-  }
+  // A lane per worker: the factors go to LDS, and a bit tells of which the sample found the row too dense for the slots (only its
+  // maximum is taken).  A factor and a flag per worker in registers spilled.
+  const uint32_t own = min(m0 + (uint32_t)min(lane, MC - 1), M - 1);
+  if (lane < MC) factor[wave][lane] = candidate_factor(sample_max[own]);
+  const uint32_t own_form = select_ok[own];
+  const uint32_t dense = (uint32_t)__builtin_amdgcn_ballot_w64(own_form == kFormNone);
+  const uint32_t words = (uint32_t)__builtin_amdgcn_ballot_w64(own_form == kFormWords);
+  wave_lds_fence();
   // one worker's part of the tile: its maximum, and its candidates into the slot
   auto worker = [&](const float4 (&x)[L], int mm, uint64_t tile) {
-    const uint32_t m = m0 + (uint32_t)mm;
+    uint32_t m = m0 + (uint32_t)mm;
+    int own = lane;
     float amax = 0.f;
-    if (!select[mm]) {  // (the same for the whole wavefront)
+    if ((dense >> mm) & 1u) {  // (the same for the whole wavefront)
 #pragma unroll
       for (int j = 0; j < L; ++j) {
         float4 v = x[j];
@@ -1006,7 +1076,39 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
       nover += 1u;  // counts as a slot that is not used
       return;
     }
-    uint32_t base = 1;  // word 0 of the slot is the count
+    // what follows from m or the lane alone is made per tile: kept for all workers, or for both forms of this loop, it spilled
+    asm volatile("" : "+s"(m), "+v"(own));
+    const float c1 = factor[wave][mm];
+    const bool bins = ((words >> mm) & 1u) == 0u;
+    uint32_t base = bins ? 2u : 1u, starts = 0u;  // half-words 0 and 1 of the slot tell how many, or word 0
+#pragma unroll
+    for (int j = 0; j < L; ++j) {
+      float4 v = x[j];
+      if (NORM == kNormSub) {
+        const float4 r = refs[wave][j][own];
+        v = make_float4(x[j].x - r.x, x[j].y - r.y, x[j].z - r.z, x[j].w - r.w);
+      }
+      amax = max3_abs(v.z, v.w, max3_abs(v.x, v.y, amax));
+      const uint64_t iv = tile * kWaveTile + (uint64_t)(j * kWave + own);
+      const U32x4 rnd = philox4x32_10((uint32_t)iv, m, iter, 0u, k0, k1);
+      stage_candidates<false, kCandPosMask, kStageSink>(stage, draws, v, rnd, c1, j, own, base);
+      if (j + 1 < L) starts |= base << (8 * (j + 1));
+    }
+    static_assert(L == 4, "three starts");
+    mx[mm] = fmaxf(mx[mm], amax);
+    if (!write_slot(stage, draws, base, starts, bins, c1, own, Slot(slots, ntiles, m, tile))) nover += 1u;
+  };
+  // The same without a branch, where all workers of the group are there and have slots of bins: every item then issues the same loads and
+  // stores, and the waits can be counted exactly (with a branch around the store they also waited for the store before and the
+  // rows of the next item; 914 -> 900 us at d = 2^27, M = 8 with slots of words, a fifth fewer vector instructions).
+  const uint32_t stage_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint32_t*)stage;
+  const uint32_t idle = stage_at + 4u * (kStageSink + 2 + (uint32_t)lane);
+  auto worker_straight = [&](const float4 (&x)[L], int mm, uint64_t tile) {
+    uint32_t m = m0 + (uint32_t)mm;
+    asm volatile("" : "+s"(m));
+    float amax = 0.f;
+    uint32_t at = stage_at + 8u, head = 0u;
+    const float c1 = factor[wave][mm];
 #pragma unroll
     for (int j = 0; j < L; ++j) {
       float4 v = x[j];
@@ -1015,12 +1117,23 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
         v = make_float4(x[j].x - r.x, x[j].y - r.y, x[j].z - r.z, x[j].w - r.w);
       }
       amax = max3_abs(v.z, v.w, max3_abs(v.x, v.y, amax));
-      const uint64_t iv = tile * kWaveTile + (uint64_t)(j * kWave + lane);
-      const U32x4 rnd = philox4x32_10((uint32_t)iv, m, iter, 0u, k0, k1);
-      stage_candidates<false, kCandPosMask, kStageSink>(stage[wave], draws[wave], v, rnd, c1[mm], j, lane, base);
+      const U32x4 rnd = philox4x32_10((uint32_t)(tile * kWaveTile) + (uint32_t)(j * kWave + lane), m, iter, 0u, k0, k1);
+      stage_straight(idle, stage_at + 4u * (kStageSink + 2), v, rnd, c1, lane, at);
+      head |= ((at - stage_at) >> 2) << (j + 1 < L ? 8 * (j + 1) : 0);
     }
     mx[mm] = fmaxf(mx[mm], amax);
-    if (!write_slot(stage[wave], draws[wave], base, lane, slots + ((uint64_t)m * ntiles + tile) * kSlotEntries)) nover += 1u;
+    const uint32_t base = (at - stage_at) >> 2;
+    wave_lds_fence();
+    // One store of the whole line, whatever the count (two lanes hold the head): under a condition, or of a length of its own, the waits for
+    // the rows that follow could not be counted.
+    const Slot slot(slots, ntiles, m, tile);
+    const uint32_t e = bin_entry(stage[lane], draws[lane], c1);
+    store_half_through(slot.halves(0) + (uint32_t)lane, lane < 2 ? head >> (16 * lane) : (uint32_t)lane < base ? e : kNoEntry);
+    if (__builtin_expect(base > (uint32_t)kWave, 0)) {
+      nover += base > (uint32_t)kSlotEntries ? 1u : 0u;
+      store_half_through(slot.halves(1) + (uint32_t)lane, (uint32_t)(kWave + lane) < base ? bin_entry(stage[kWave + lane], draws[kWave + lane], c1) : kNoEntry);
+    }
+    wave_lds_fence();
   };
   // Every request is made whatever the tile (a load under a branch could not be counted by the waits that
   // follow it): past the wavefront's last tile all lanes read the first float4 of this tile's part again.
@@ -1031,12 +1144,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
         for (int j = 0; j < L; ++j) b[j] = load_stream(ref4 + t * kWaveTile + ((uint32_t)(j * kWave + lane) & keep));
       }
     } else if (item <= MC) {
-      const v4f_u_t* row = g.row(min(m0 + (uint32_t)(item - 1), M - 1));
+      uint32_t m = min(m0 + (uint32_t)(item - 1), M - 1);
+      asm volatile("" : "+s"(m));  // (as above)
+      const v4f_u_t* row = g.row(m);
 #pragma unroll
       for (int j = 0; j < L; ++j) b[j] = load_row_stream(row + t * kWaveTile + ((uint32_t)(j * kWave + lane) & keep));
     }
   };
-  auto work = [&](const float4 (&b)[L], int item, uint64_t tile) {
+  auto work = [&](const float4 (&b)[L], int item, uint64_t tile, bool straight) {
     if (item == 0) {
       if (NORM == kNormSub) {
 #pragma unroll
@@ -1044,12 +1159,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
         wave_lds_fence();
       }
     } else if (item <= MC) {
-      if ((uint32_t)(item - 1) < count) worker(b, item - 1, tile);
+      if (straight)
+        worker_straight(b, item - 1, tile);
+      else if ((uint32_t)(item - 1) < count)
+        worker(b, item - 1, tile);
     }
   };
   const uint64_t stride = (uint64_t)main_blocks * kWavesPerBlock;
   uint64_t tile = (uint64_t)blockIdx.x * kWavesPerBlock + wave;
-  if (tile < ntiles) {
+  auto tiles = [&](auto STRAIGHT) {
+    constexpr bool straight = decltype(STRAIGHT)::value;
     float4 b0[L], b1[L], b2[L];
     request(b0, 0, tile, ~0u);
     request(b1, 1, tile, ~0u);
@@ -1062,7 +1181,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
         constexpr int i = decltype(I)::value;
         constexpr bool wraps = i + 2 >= kItems;
         request(into, wraps ? i + 2 - kItems : i + 2, wraps ? t_next : tile, wraps ? keep_next : ~0u);
-        work(from, i, tile);
+        work(from, i, tile, straight);
       };
       step(std::integral_constant<int, 0>{}, b2, b0);
       step(std::integral_constant<int, 1>{}, b0, b1);
@@ -1078,6 +1197,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
         step(std::integral_constant<int, 8>{}, b1, b2);
       }
     }
+  };
+  if (tile < ntiles) {
+    if (count == (uint32_t)MC && (dense | words) == 0u)
+      tiles(std::true_type{});
+    else
+      tiles(std::false_type{});
   }
   if (lane == 0) over[wave] = nover;
   block_max_to_partials<MC>(mx, m0, M, partials);  // has a workgroup barrier after its own LDS writes
@@ -1113,104 +1238,170 @@ __device__ __forceinline__ void vote_on_slots(const SlotVote& v) {
 
 // The reduction of the scale pass's partial maxima (workgroups 0 .. M - 1, one per worker) and the vote.
 __global__ __launch_bounds__(kBlock) void absmax_finish_vote_kernel(const float* __restrict__ partials, uint32_t nblocks,
-                                                                    uint32_t M, float* __restrict__ scales, SlotVote vote) {
-  if (blockIdx.x < M)
-    absmax_finish_worker(partials, nblocks, M, scales, blockIdx.x);
-  else
+                                                                    uint32_t M, float* __restrict__ scales,
+                                                                    const float* __restrict__ sample_max,
+                                                                    uint32_t* __restrict__ select_ok, SlotVote vote) {
+  if (blockIdx.x < M) {
+    const float r = absmax_finish_worker(partials, nblocks, M, scales, blockIdx.x);
+    // for the quantise pass: the bins of the worker's slots whose elements code non-zero, and zero
+    if (threadIdx.x == 0) select_ok[blockIdx.x] |= bin_limits(sample_max[blockIdx.x], r);
+  } else {
     vote_on_slots(vote);
+  }
 }
 
-// The packed codes of a tile from its slots.  One wavefront per tile as in the quantiser; the words of a
-// worker are cleared in LDS, the candidates' codes are or-ed in, and all workers' words are written at the
-// end as the quantiser writes them.
-// What bounds it: slots read and codes written, a wavefront waiting for its tile's slots once, so the wavefronts in flight
-// count: eight per SIMD (64 registers), the rare paths behind the loop over the workers and there only once.  At d = 2^27,
-// M = 8 (0.27 GB of slot lines, 0.27 GB of codes) 148 us with the counts fetched by loads of their own (a third line
-// of every slot), the rare paths inside the loop and six wavefronts; 130 without the third line; 125 with eight wavefronts
-// (4.3 TB/s).  d = 2^24, M = 16, l2 scale (slots all but empty): 37 -> 28.  Two tiles a wavefront, all their slots
-// requested at once: 131; wavefronts that walk the tiles and request the next one's slots before this one's work: 156 to 177.
-// Groups of five workers where those divide M (as in absmax_select_kernel): d = 2^25 + 3, M = 5 32.1 us, 28.0 so.
+// The packed codes of a tile from its slots.  A wavefront takes eight rows, a worker's tile each (five where groups of five workers
+// divide M, as in absmax_select_kernel), eight lanes to a row; the words of a row are cleared in LDS, the candidates' codes are or-ed
+// in, and all rows' words are written at the end as the quantiser writes them.
+// What bounds it: slots read and codes written (0.13 + 0.27 GB at d = 2^27, M = 8: 66 us without what follows), and vector instructions for
+// the elements that need their value (1.9 a wavefront there) and second lines (a fifth of the wavefronts).  So all of a wavefront's
+// slots come by one load, what belongs to a row sits in its lanes, and the rare paths are behind the main one, there only once, eight
+// wavefronts to a SIMD (64 registers).  At d = 2^27, M = 8 123 us with slots of words, a step per worker with all lanes on it; 173 so with
+// half-words (530 vector and 640 scalar instructions a wavefront, the vector unit all but full); 98 now.  The draws of elements that need
+// their value in scalar instructions: 115.  Eight tiles of one worker by a wavefront each: d = 2^26, M = 1 27.5 us, 16 so.
+constexpr int quantize_tiles(int mc) { return mc > 4 ? 1 : 8 / mc; }  // tiles that a wavefront takes
 template <int NORM, int MC>
 __global__ __launch_bounds__(kBlock, 8) void quantize_candidates_kernel(
     GradRows g, const float4* __restrict__ ref4, const float4* __restrict__ ref24, const float* __restrict__ scales,
     const uint32_t* __restrict__ slots, uint32_t* __restrict__ codes, uint64_t d, uint64_t words, uint32_t M,
     float eps, uint32_t k0, uint32_t k1, uint32_t iter, const uint32_t* __restrict__ use_slots,
     const uint32_t* __restrict__ select_ok) {
-  constexpr int L = kLoadsPerLane;
-  constexpr int WPW = kWave * L * 4 * 2 / 32;  // 64 packed words per wavefront tile
-  static_assert(WPW == kWave, "one word per lane");
-  __shared__ __attribute__((aligned(16))) FragmentBuffer<WPW, MC> lds;
+  constexpr int WPW = (int)kWaveTileElements * 2 / 32;  // 64 packed words per row
+  constexpr int T = quantize_tiles(MC), ROWS = MC * T;  // a row: a worker's tile
+  constexpr int kLanes = 8, X = (int)kSlotLine / kLanes, E = 2 * X;  // lanes per row, words and half-words of the line in each
+  static_assert(ROWS * kLanes <= kWave && WPW == kWave && X == 4, "16 bytes of a row's line per lane");
+  __shared__ __attribute__((aligned(16))) FragmentBuffer<WPW, ROWS> lds;
   if (use_slots[0] == 0u) return;  // too many tiles overflowed: the ordinary quantiser runs instead
-  const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = threadIdx.x % kWave;
   const uint64_t ntiles = d / kWaveTileElements;
-  const uint32_t m0 = blockIdx.y * MC;
-  const uint32_t m_end = min(m0 + MC, M);
-  const uint64_t tile = (uint64_t)blockIdx.x * kWavesPerBlock + wave;
-  if (tile >= ntiles) return;  // whole wavefronts; nothing below meets the other wavefronts
-  const uint64_t word_base = tile * WPW;
-  // The count and the first 63 candidates of all the workers' slots are requested at once, two whole lines each (a slot
-  // rarely holds more: the rest is fetched when its count says so), so that the wavefront waits for memory once and not
-  // once per worker.  Words past a slot's count are whatever an earlier call left there and are not used.
-  uint32_t first[MC], ok[MC];
-  float R[MC];
+  const uint32_t m0 = blockIdx.y * MC, count = min((uint32_t)MC, M - m0);
+  const uint64_t t0 = ((uint64_t)blockIdx.x * kWavesPerBlock + wave) * T;
+  if (t0 >= ntiles) return;  // whole wavefronts; nothing below meets the other wavefronts
+  auto tile_of = [&](uint32_t row) { return T == 1 ? t0 : min(t0 + row / MC, ntiles - 1); };
+  auto worker_of = [&](uint32_t row) { return min(m0 + (T == 1 ? row : row % MC), M - 1); };
+  auto is_live = [&](uint32_t row) { return row < (uint32_t)ROWS && (T == 1 ? row : row % MC) < count && (T == 1 || t0 + row / MC < ntiles); };
+  auto slot_of = [&](uint32_t row) { return Slot(const_cast<uint32_t*>(slots), ntiles, worker_of(row), tile_of(row)); };
+  // The first lines of all the slots (62 candidates of a row with a bound each) come by one load, and a lane has its row's limits and
+  // what it needs of the head in registers of its own.
+  const uint32_t row = min((uint32_t)(lane / kLanes), (uint32_t)ROWS - 1), part = (uint32_t)(lane % kLanes);
+  const bool live = is_live((uint32_t)(lane / kLanes));
+  const v4u_t line = reinterpret_cast<const v4u_t*>(slot_of(row).line)[part];
+  const float r = scales[worker_of(row)];
+  const uint32_t limits = select_ok[worker_of(row)];
 #pragma unroll
-  for (int mm = 0; mm < MC; ++mm) {
-    const uint32_t m = min(m0 + (uint32_t)mm, M - 1);
-    first[mm] = slots[((uint64_t)m * ntiles + tile) * kSlotEntries + (uint32_t)lane];
-    R[mm] = scales[m];
-    ok[mm] = select_ok[m];
-  }
-#pragma unroll
-  for (int mm = 0; mm < MC; ++mm) lds.b32[mm][wave][lane] = 0u;
+  for (int k = 0; k < ROWS; ++k) lds.b32[k][wave][lane] = 0u;
   wave_lds_fence();
-  auto put = [&](uint32_t slot, uint32_t e, uint32_t code) {
-    atomicOr(&lds.b32[slot][wave][(e & kCandPosMask) >> 4], code << (2u * (e & 15u)));
+  const uint32_t head = (uint32_t)__shfl((int)line[0], lane - (int)part), end = head & 255u;
+  uint32_t x[X] = {part == 0 ? ~0u : line[0], line[1], line[2], line[3]};  // (the head is no entry)
+  const bool bins = live && (limits & 255u) == kFormBins && end <= (uint32_t)kSlotEntries;
+  const uint32_t below = bins ? max((limits >> 8) & 255u, 1u) - 1u : 0u, above = bins ? (limits >> 16) + 1u : 0u;
+  // Codes are or-ed in as one bit, the low one of a code that is positive and the high one of a code that is negative.
+  auto put = [&](uint32_t to, uint32_t pos, uint32_t code) { atomicOr(&lds.b32[to][wave][pos >> 4], code << (2u * (pos & 15u))); };
+  // An element of each lane where `open`, coded from its value.
+  auto settle = [&](bool open, uint32_t to, float scale, uint32_t pos) {
+    const uint32_t of = worker_of(to);
+    const uint64_t coord = tile_of(to) * kWaveTileElements + (open ? pos : 0u);
+    const float value = g.base[(uint64_t)of * g.pitch + coord], ref = NORM == kNormSub ? reinterpret_cast<const float*>(ref4)[coord] : 0.f;
+    const U32x4 rnd = philox4x32_10((uint32_t)(coord >> 2), of, iter, 0u, k0, k1);
+    const uint32_t low = (pos & 1u) != 0u ? rnd.y : rnd.x, high = (pos & 1u) != 0u ? rnd.w : rnd.z;
+    if (open) put(to, pos, ternary_code(normalize_w<NORM>(value, ref, 1.f, 0.f), 1.0f / scale, (pos & 2u) != 0u ? high : low));
   };
-  // Bit mm: worker m0 + mm has more candidates than are in first[mm], or no slot here (its row is too dense for slots,
-  // or this one overflowed); in undecided, this lane's candidate of that worker needs its value.  All three are rare and come after the loop, in code that is there once and
-  // not once per worker.
-  uint32_t long_slots = 0u, no_slots = 0u, undecided = 0u;
+  // which of the tile's four loads half-words first to first + 7 of a slot belong to, four bits each
+  auto loads_from = [](uint32_t of, uint32_t first) {
+    uint32_t loads = 0u;
 #pragma unroll
-  for (int mm = 0; mm < MC; ++mm) {
-    const uint32_t e = first[mm], n = __builtin_amdgcn_readfirstlane(e);
-    const bool live = m0 + (uint32_t)mm < m_end && R[mm] != 0.f;  // (R = 0: every element codes to 0)
-    const bool slot = ok[mm] != 0u && n <= (uint32_t)kCandCap;
-    no_slots |= (live && !slot ? 1u : 0u) << mm;
-    long_slots |= (live && slot && n >= (uint32_t)kWave ? 1u : 0u) << mm;
-    const int in = (uint32_t)lane - 1u < (live && slot ? n : 0u);  // (lane 0 holds the count)
-    const int one = in & entry_codes_one<kCandPosMask>(e, R[mm]);
-    if (one) put((uint32_t)mm, e, 1u | ((e >> 31) << 1));
-    undecided |= (uint32_t)(in & ~one & ~entry_codes_zero<kCandPosMask>(e, R[mm])) << mm;
+    for (int t = 1; t < 4; ++t) {
+      const int ahead = max((int)((of >> (8 * t)) & 255u) - (int)first, 0);
+      loads += ahead < 8 ? 0x11111111u << (4 * ahead) : 0u;
+    }
+    return loads;
+  };
+  const uint32_t loads = loads_from(head, E * part);
+  uint64_t open[E], any = 0ull;
+#pragma unroll
+  for (int c = 0; c < E; ++c) {
+    const uint32_t e = c % 2 == 0 ? x[c / 2] & 0xFFFFu : x[c / 2] >> 16;
+    const bool one = e - (1u << kBinShift) < below << kBinShift;
+    open[c] = __builtin_amdgcn_ballot_w64(e < above << kBinShift) & ~__builtin_amdgcn_ballot_w64(one);
+    any |= open[c];
+    if (one) atomicOr(&lds.b32[row][wave][((e >> 5) & 15u) + 16u * ((loads >> (4 * c)) & 3u)], 1u << (e & 31u));
   }
-  if (long_slots != 0u || __builtin_amdgcn_ballot_w64(undecided != 0u) != 0ull) {
+  if (any != 0ull) {  // a lane's elements one after the other, those of the other lanes at the same time
+    uint32_t undecided = 0u;
+#pragma unroll
+    for (int c = 0; c < E; ++c) undecided |= __builtin_amdgcn_inverse_ballot_w64(open[c]) ? 1u << c : 0u;
+    do {
+      const uint32_t c = (uint32_t)__builtin_ctz(undecided | 256u) & 7u;
+      uint32_t e = x[0];
+#pragma unroll
+      for (int i = 1; i < X; ++i) e = c / 2 == (uint32_t)i ? x[i] : e;
+      settle(undecided != 0u, row, r, ((e >> (16 * (c & 1u) + 1)) & 255u) + 256u * ((loads >> (4 * c)) & 3u));
+      undecided &= undecided - 1u;
+    } while (__builtin_amdgcn_ballot_w64(undecided != 0u) != 0ull);
+  }
+  // The second lines, a row at a time.
+  uint64_t longer = __builtin_amdgcn_ballot_w64(bins && end > (uint32_t)kWave && part == 0);
 #pragma unroll 1
-    for (uint32_t mm = 0; mm < m_end - m0; ++mm) {
-      const bool longer = ((long_slots >> mm) & 1u) != 0u;
-      const int open = (int)(undecided >> mm) & 1;
-      if (!longer && __builtin_amdgcn_ballot_w64(open) == 0ull) continue;
-      const uint32_t m = m0 + mm;
-      const uint32_t* __restrict__ sl = slots + ((uint64_t)m * ntiles + tile) * kSlotEntries;
-      const uint32_t n = sl[0], e0 = sl[lane], e1 = sl[kWave + lane];
-      const float r = scales[m];
-      const int in = (int)longer & (int)((uint32_t)(kWave + lane) <= n), one = in & entry_codes_one<kCandPosMask>(e1, r);
-      if (one) put(mm, e1, 1u | ((e1 >> 31) << 1));
-      const int open1 = in & ~one & ~entry_codes_zero<kCandPosMask>(e1, r);
+  for (; longer != 0ull; longer &= longer - 1ull) {
+    const int l = __builtin_ctzll(longer);
+    const uint32_t to = (uint32_t)l / kLanes, e = slot_of(to).halves(1)[lane];
+    const uint32_t low = __builtin_amdgcn_readlane(below, l) << kBinShift, high = __builtin_amdgcn_readlane(above, l) << kBinShift;
+    const uint32_t pos = ((e >> 1) & 255u) + 256u * (loads_from(__builtin_amdgcn_readlane(head, l), (uint32_t)(kWave + lane)) & 3u);
+    const bool one = e - (1u << kBinShift) < low, left = !one && e < high;
+    if (one) put(to, pos, 1u << (e & 1u));
+    if (__builtin_amdgcn_ballot_w64(left) != 0ull) settle(left, to, scales[worker_of(to)], pos);
+  }
+  // Rows without a bound: slots of words.
+  const bool other = live && !bins && r != 0.f;  // (R = 0: every element codes to 0)
+  const bool wide = other && (limits & 255u) == kFormWords && head <= (uint32_t)kCandCap;
+  if (__builtin_amdgcn_ballot_w64(wide) != 0ull) {
+    auto code = [&](uint32_t to, uint32_t e, int in, float scale) {  // whether the element needs its value
+      const int one = in & entry_codes_one<kCandPosMask>(e, scale);
+      if (one) put(to, e & kCandPosMask, 1u | ((e >> 30) & 2u));
+      return in & ~one & ~entry_codes_zero<kCandPosMask>(e, scale);
+    };
+    uint32_t undecided = 0u;
+#pragma unroll
+    for (int c = 0; c < X; ++c) undecided |= (uint32_t)code(row, x[c], (int)wide & (int)(X * part + c - 1u < head), r) << c;
+    while (__builtin_amdgcn_ballot_w64(undecided != 0u) != 0ull) {
+      const uint32_t c = (uint32_t)__builtin_ctz(undecided | 8u);
+      uint32_t e = x[0];
+#pragma unroll
+      for (int i = 1; i < X; ++i) e = c == (uint32_t)i ? x[i] : e;
+      settle(undecided != 0u, row, r, e & kCandPosMask);
+      undecided &= undecided - 1u;
+    }
+    uint64_t more = __builtin_amdgcn_ballot_w64(wide && head >= kSlotLine && part == 0);
 #pragma unroll 1
-      for (int k = 0; k < 2; ++k)
-        if (k == 0 ? open : open1) {
-          const uint32_t e = k == 0 ? e0 : e1;
-          const uint32_t code = code_of_element<NORM>(g, ref4, tile * kWaveTileElements + (e & kCandPosMask), m, r, iter, k0, k1);
-          if (code != 0u) put(mm, e, code);
-        }
+    for (; more != 0ull; more &= more - 1ull) {
+      const int l = __builtin_ctzll(more);
+      const uint32_t to = (uint32_t)l / kLanes, n = __builtin_amdgcn_readlane(head, l);
+      const float scale = scales[worker_of(to)];
+#pragma unroll 1
+      for (uint32_t i0 = kSlotLine; i0 <= n; i0 += kWave) {
+        const uint32_t i = min(i0 + (uint32_t)lane, (uint32_t)kSlotEntries - 1), e = slot_of(to).rest[i - kSlotLine];
+        const int left = code(to, e, i0 + (uint32_t)lane <= n, scale);
+        if (__builtin_amdgcn_ballot_w64(left != 0) != 0ull) settle(left != 0, to, scale, e & kCandPosMask);
+      }
     }
   }
+  // Rows too dense for slots, and slots that overflowed: the ordinary way.
+  uint64_t none = __builtin_amdgcn_ballot_w64(other && !wide && part == 0);
 #pragma unroll 1
-  for (uint32_t mm = 0; no_slots >> mm != 0u; ++mm) {  // these workers' tiles go through the ordinary path
-    if (((no_slots >> mm) & 1u) == 0u) continue;
-    const uint32_t m = m0 + mm;
-    code_tile<NORM>(lds.b8[mm][wave], g, ref4, ref24, tile, m, lane, scales[m], eps, iter, k0, k1);
+  for (; none != 0ull; none &= none - 1ull) {
+    const uint32_t to = (uint32_t)__builtin_ctzll(none) / kLanes;
+    code_tile<NORM>(lds.b8[to][wave], g, ref4, ref24, tile_of(to), worker_of(to), lane, scales[worker_of(to)], eps, iter, k0, k1);
   }
-  flush_packed<WPW, MC>(lds, wave, lane, codes, words, word_base, m0, m_end - m0);
+  wave_lds_fence();
+  constexpr int kStore = WPW / 4;  // lanes that store a row, 16 bytes each
+#pragma unroll
+  for (int k = 0; k < ROWS; k += kWave / kStore) {
+    const uint32_t from = (uint32_t)(k + lane / kStore);
+    if (!is_live(from)) continue;
+    v4u_t w4 = *reinterpret_cast<const v4u_t*>(&lds.b32[from][wave][4 * (lane % kStore)]);
+    w4 |= (w4 >> 1) & 0x55555555u;  // (leaves whole codes as they are)
+    store4_through(codes + (uint64_t)worker_of(from) * words + tile_of(from) * WPW + 4 * (lane % kStore), w4);
+  }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2587,7 +2778,8 @@ hipError_t absmax_candidates_dispatch(const CodecShape& c, uint32_t iter, const 
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   const SlotVote vote{cs.overflowed, nblocks * ((c.M + (uint32_t)mc - 1) / (uint32_t)mc), (uint64_t)c.M * row_tiles, cs.use_slots};
-  hipLaunchKernelGGL(absmax_finish_vote_kernel, dim3(c.M + 1), dim3(kBlock), 0, s, partials, nblocks, c.M, scales, vote);
+  hipLaunchKernelGGL(absmax_finish_vote_kernel, dim3(c.M + 1), dim3(kBlock), 0, s, partials, nblocks, c.M, scales, cs.sample_max,
+                     cs.select_ok, vote);
   return hipGetLastError();
 }
 
@@ -2605,7 +2797,7 @@ hipError_t quantize_candidates_dispatch(const CodecShape& c, uint32_t iter, cons
                                                                              // absmax_select_kernel's but for the cost of a repeated row)
 #define TNG_QC(MC)                                                                                                   \
   hipLaunchKernelGGL((quantize_candidates_kernel<NORM, MC>),                                                           \
-                     dim3((uint32_t)tiles, (c.M + MC - 1) / MC), dim3(kBlock), 0,             \
+                     dim3((uint32_t)((tiles + quantize_tiles(MC) - 1) / quantize_tiles(MC)), (c.M + MC - 1) / MC), dim3(kBlock), 0, \
                      s, GradRows{g, c.d}, reinterpret_cast<const float4*>(gref), reinterpret_cast<const float4*>(gref2), \
                      scales, cs.slots, codes, c.d, c.words, c.M, c.eps, c.k0, c.k1, iter, cs.use_slots, cs.select_ok)
   if (c.scale_l2 != 0) {
