@@ -221,26 +221,36 @@ __device__ __forceinline__ void block_max_to_partials(float (&mx)[MC], uint32_t 
 }
 
 // scales[m] = max over the nblocks partial maxima of worker m; a maximum below the smallest normal
-// number is taken as 0.  One workgroup per worker.
+// number is taken as 0.  One workgroup per worker, a large one for many rows: a thread has four loads at most, all in flight together (4095
+// rows of 8 workers: 7.4 us with 256 threads, 4.5 to 6.3 with 1024).
+constexpr uint32_t kFinishLarge = 1024;
+__host__ inline uint32_t finish_threads(uint32_t nblocks) { return nblocks > kFinishLarge ? kFinishLarge : (uint32_t)kBlock; }
+template <int THREADS>
 __device__ __forceinline__ float absmax_finish_worker(const float* __restrict__ partials, uint32_t nblocks, uint32_t M,
                                                       float* __restrict__ scales, uint32_t m) {
-  __shared__ float red[kWavesPerBlock];
+  constexpr int kWaves = THREADS / kWave;
+  __shared__ float red[kWaves];
   float v = 0.f;
-  for (uint32_t b = threadIdx.x; b < nblocks; b += kBlock) v = fmaxf(v, partials[(uint64_t)b * M + m]);
+  for (uint32_t b0 = threadIdx.x; b0 < nblocks; b0 += 4 * THREADS) {
+    float p[4];  // (past the last row the last one again)
+#pragma unroll
+    for (int k = 0; k < 4; ++k) p[k] = partials[(uint64_t)min(b0 + (uint32_t)(k * THREADS), nblocks - 1) * M + m];
+    v = fmaxf(fmaxf(v, fmaxf(p[0], p[1])), fmaxf(p[2], p[3]));
+  }
   v = wave_max_nonneg(v);
   if (threadIdx.x % kWave == 0) red[threadIdx.x / kWave] = v;
   __syncthreads();
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int k = 1; k < kWavesPerBlock; ++k) v = fmaxf(v, red[k]);
+  if (threadIdx.x < (uint32_t)kWave) {
+    v = wave_max_nonneg(red[threadIdx.x % kWaves]);
     v = v < FLT_MIN ? 0.f : v;
-    scales[m] = v;
+    if (threadIdx.x == 0) scales[m] = v;
   }
-  return v;  // (thread 0's)
+  return v;  // (the first wavefront's)
 }
-__global__ __launch_bounds__(kBlock) void absmax_finish_kernel(const float* __restrict__ partials, uint32_t nblocks,
-                                                               uint32_t M, float* __restrict__ scales) {
-  absmax_finish_worker(partials, nblocks, M, scales, blockIdx.x);
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void absmax_finish_kernel(const float* __restrict__ partials, uint32_t nblocks, uint32_t M,
+                                                                float* __restrict__ scales) {
+  absmax_finish_worker<THREADS>(partials, nblocks, M, scales, blockIdx.x);
 }
 
 // The M gradient rows as the vector kernels read them.  Row m starts m * pitch floats into the array;
@@ -702,22 +712,24 @@ constexpr uint32_t kL2OverflowCounts = kBlock;  // counters that the workgroups 
 constexpr float kDenseLimit = 0.10f;
 // L2: the bound is of the row's 2-norm instead, from the sum of squares over the sample in binary64 (the partial
 // results are the workgroups' own norms).
+constexpr int kSampleThreads = 1024, kSampleWaves = kSampleThreads / kWave;  // (few, large workgroups: few partial results)
+constexpr uint32_t kSampleRows = 64;  // workgroups per worker at most
 template <int NORM, bool L2>
-__global__ __launch_bounds__(kBlock) void sample_stats_kernel(GradRows g, const float4* __restrict__ ref4,
+__global__ __launch_bounds__(kSampleThreads) void sample_stats_kernel(GradRows g, const float4* __restrict__ ref4,
                                                               float* __restrict__ part_max,
                                                               float* __restrict__ part_sum, uint64_t nvec, uint32_t M) {
   constexpr int L = kAbsmaxLoads;
   constexpr uint64_t kWaveTile = (uint64_t)kWave * L;
-  __shared__ float red[2][kWavesPerBlock];
+  __shared__ float red[2][kSampleWaves];
   const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
   const uint32_t m = blockIdx.y;
   const uint64_t ntiles = nvec / kWaveTile;  // whole tiles only
   const v4f_u_t* row = g.row(m);
-  __shared__ double squares[kWavesPerBlock];
+  __shared__ double squares[kSampleWaves];
   float amax = 0.f, asum = 0.f;
   double sq = 0.0;
-  for (uint64_t tile = ((uint64_t)blockIdx.x * kWavesPerBlock + wave) * kSampleStride; tile < ntiles;
-       tile += (uint64_t)gridDim.x * kWavesPerBlock * kSampleStride) {
+  for (uint64_t tile = ((uint64_t)blockIdx.x * kSampleWaves + wave) * kSampleStride; tile < ntiles;
+       tile += (uint64_t)gridDim.x * kSampleWaves * kSampleStride) {
     float4 x[L], r[L];
 #pragma unroll
     for (int j = 0; j < L; ++j) {
@@ -749,7 +761,7 @@ __global__ __launch_bounds__(kBlock) void sample_stats_kernel(GradRows g, const 
   if (threadIdx.x == 0) {
     float mx = red[0][0], sm = red[1][0];
 #pragma unroll
-    for (int k = 1; k < kWavesPerBlock; ++k) {
+    for (int k = 1; k < kSampleWaves; ++k) {
       mx = fmaxf(mx, red[0][k]);
       sm += red[1][k];
       sq += squares[k];
@@ -760,51 +772,49 @@ __global__ __launch_bounds__(kBlock) void sample_stats_kernel(GradRows g, const 
   }
 }
 
-// sample_max[m] = R^ of worker m (0 when below the smallest normal number, as for a scale), and
-// select_ok[m] = 1 when the sample says that the row's candidates fit the slots, else 0: the scale pass then
+// R^ of a row (0 when below the smallest normal number, as for a scale) from the sample's maximum, and what its slots are to hold:
+// nothing where the sum of |v| over the sample says that its candidates would not fit: the scale pass then
 // takes that worker's part as an ordinary scale pass and the quantise pass takes its tiles through the
-// ordinary path, without the slots.  sampled = elements of a row in the sample.  One workgroup per worker.
-// L2: R^ is the norm of the workgroups' norms, made smaller by 2^-10 of itself, which is more than all roundings on the way
-// here and in the row's own ordered sum can come to.
-template <bool L2>
+// ordinary path, without the slots.  sampled = elements of a row in the sample.  (A sum that is no number, or an infinite one, compares
+// false.)
+__device__ __forceinline__ uint32_t form_of_slots(float r_hat, float sum, float sampled) {
+  return sum <= kDenseLimit * sampled * r_hat ? (r_hat < kBoundMin ? kFormWords : kFormBins) : kFormNone;
+}
+
+// The same for the l2 scale, a launch of its own, one workgroup per worker: R^ is the norm of the workgroups' norms, made smaller by 2^-10
+// of itself, which is more than all roundings on the way here and in the row's own ordered sum can come to.
 __global__ __launch_bounds__(kBlock) void sample_finish_kernel(const float* __restrict__ part_max,
                                                                const float* __restrict__ part_sum, uint32_t nblocks,
                                                                uint32_t M, float sampled, float* __restrict__ sample_max,
                                                                uint32_t* __restrict__ select_ok,
                                                                uint32_t* __restrict__ overflowed) {
-  if (L2 && blockIdx.x == 0) overflowed[threadIdx.x] = 0u;  // l2_select_kernel adds to these
-  __shared__ float red[2][kWavesPerBlock];
+  if (blockIdx.x == 0) overflowed[threadIdx.x] = 0u;  // l2_select_kernel adds to these
+  __shared__ float red[kWavesPerBlock];
   __shared__ double squares[kWavesPerBlock];
   const uint32_t m = blockIdx.x;
-  float mx = 0.f, sm = 0.f;
+  float sm = 0.f;
   double sq = 0.0;
   for (uint32_t b = threadIdx.x; b < nblocks; b += kBlock) {
     const float p = part_max[(uint64_t)b * M + m];
-    mx = fmaxf(mx, p);
     sq += (double)p * p;
     sm += part_sum[(uint64_t)b * M + m];
   }
-  mx = wave_max(mx);
   sm = wave_sum(sm);
-  if (L2)
-    for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off, kWave);
+  for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off, kWave);
   if (threadIdx.x % kWave == 0) {
-    red[0][threadIdx.x / kWave] = mx;
-    red[1][threadIdx.x / kWave] = sm;
+    red[threadIdx.x / kWave] = sm;
     squares[threadIdx.x / kWave] = sq;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
 #pragma unroll
     for (int k = 1; k < kWavesPerBlock; ++k) {
-      mx = fmaxf(mx, red[0][k]);
-      sm += red[1][k];
+      sm += red[k];
       sq += squares[k];
     }
-    if (L2) mx = (float)sqrt(sq) * (1.0f - 0x1p-10f);
+    const float mx = (float)sqrt(sq) * (1.0f - 0x1p-10f);
     sample_max[m] = mx < FLT_MIN ? 0.f : mx;
-    // (a sum that is no number, or an infinite one, compares false: the slots are then not used)
-    select_ok[m] = sm <= kDenseLimit * sampled * mx ? (L2 || mx < kBoundMin ? kFormWords : kFormBins) : kFormNone;
+    select_ok[m] = form_of_slots(mx, sm, sampled);
   }
 }
 
@@ -1007,8 +1017,9 @@ template <int NORM, int MC>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) void absmax_select_kernel(GradRows g, const float4* __restrict__ ref4,
                                                                const float4* __restrict__ ref24, float* partials,
                                                                uint64_t d, uint32_t main_blocks, uint32_t M, float eps,
-                                                               const float* __restrict__ sample_max,
-                                                               const uint32_t* __restrict__ select_ok,
+                                                               const float* __restrict__ part_max, const float* __restrict__ part_sum,
+                                                               uint32_t nsample, float sampled, float* __restrict__ sample_max,
+                                                               uint32_t* __restrict__ select_ok,
                                                                uint32_t* __restrict__ slots,
                                                                uint32_t* __restrict__ overflowed, uint32_t k0,
                                                                uint32_t k1, uint32_t iter) {
@@ -1051,9 +1062,35 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
   }
   // A lane per worker: the factors go to LDS, and a bit tells of which the sample found the row too dense for the slots (only its
   // maximum is taken).  A factor and a flag per worker in registers spilled.
-  const uint32_t own = min(m0 + (uint32_t)min(lane, MC - 1), M - 1);
-  if (lane < MC) factor[wave][lane] = candidate_factor(sample_max[own]);
-  const uint32_t own_form = select_ok[own];
+  // The sample's partial results are reduced by every wavefront for itself, W workers side by side, all loads in flight together (a launch of its
+  // own between the sample and this kernel: encode + decode d = 2^25 + 3, M = 5 2.5 us more, M = 8, no normalisation 6).
+  constexpr int W = MC > 4 ? 8 : MC, kSteps = (int)kSampleRows * W / kWave;
+  const uint32_t own = min(m0 + (uint32_t)min(lane % W, MC - 1), M - 1);
+  float r_hat = 0.f, sum = 0.f;
+  float pm[kSteps], ps[kSteps];
+#pragma unroll
+  for (int k = 0; k < kSteps; ++k) {
+    const uint64_t at = (uint64_t)min((uint32_t)(k * (kWave / W) + lane / W), nsample - 1) * M + own;
+    pm[k] = part_max[at];
+    ps[k] = part_sum[at];
+  }
+#pragma unroll
+  for (int k = 0; k < kSteps; ++k) {
+    r_hat = fmaxf(r_hat, pm[k]);
+    sum += (uint32_t)(k * (kWave / W) + lane / W) < nsample ? ps[k] : 0.f;
+  }
+#pragma unroll
+  for (int off = W; off < kWave; off <<= 1) {
+    r_hat = fmaxf(r_hat, __shfl_xor(r_hat, off, kWave));
+    sum += __shfl_xor(sum, off, kWave);
+  }
+  r_hat = r_hat < FLT_MIN ? 0.f : r_hat;
+  const uint32_t own_form = form_of_slots(r_hat, sum, sampled);
+  if (lane < MC) factor[wave][lane] = candidate_factor(r_hat);
+  if (blockIdx.x == 0 && threadIdx.x < (uint32_t)MC && m0 + threadIdx.x < M) {  // for the kernels that follow
+    sample_max[own] = r_hat;
+    select_ok[own] = own_form;
+  }
   const uint32_t dense = (uint32_t)__builtin_amdgcn_ballot_w64(own_form == kFormNone);
   const uint32_t words = (uint32_t)__builtin_amdgcn_ballot_w64(own_form == kFormWords);
   wave_lds_fence();
@@ -1225,28 +1262,31 @@ struct SlotVote {
   uint64_t tiles_in_all;
   uint32_t* use_slots;
 };
+template <int THREADS>
 __device__ __forceinline__ void vote_on_slots(const SlotVote& v) {
   __shared__ unsigned long long sum;
   if (threadIdx.x == 0) sum = 0ull;
   __syncthreads();
   unsigned long long mine = 0;
-  for (uint32_t i = threadIdx.x; i < v.n; i += kBlock) mine += v.overflowed[i];
+#pragma unroll 4
+  for (uint32_t i = threadIdx.x; i < v.n; i += THREADS) mine += v.overflowed[i];
   atomicAdd(&sum, mine);
   __syncthreads();
   if (threadIdx.x == 0) v.use_slots[0] = sum * 50ull <= v.tiles_in_all ? 1u : 0u;
 }
 
 // The reduction of the scale pass's partial maxima (workgroups 0 .. M - 1, one per worker) and the vote.
-__global__ __launch_bounds__(kBlock) void absmax_finish_vote_kernel(const float* __restrict__ partials, uint32_t nblocks,
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void absmax_finish_vote_kernel(const float* __restrict__ partials, uint32_t nblocks,
                                                                     uint32_t M, float* __restrict__ scales,
                                                                     const float* __restrict__ sample_max,
                                                                     uint32_t* __restrict__ select_ok, SlotVote vote) {
   if (blockIdx.x < M) {
-    const float r = absmax_finish_worker(partials, nblocks, M, scales, blockIdx.x);
+    const float r = absmax_finish_worker<THREADS>(partials, nblocks, M, scales, blockIdx.x);
     // for the quantise pass: the bins of the worker's slots whose elements code non-zero, and zero
     if (threadIdx.x == 0) select_ok[blockIdx.x] |= bin_limits(sample_max[blockIdx.x], r);
   } else {
-    vote_on_slots(vote);
+    vote_on_slots<THREADS>(vote);
   }
 }
 
@@ -2518,7 +2558,7 @@ __global__ __launch_bounds__(kBlock) void tree_finish_kernel(const double* __res
                                                              uint64_t nchunks, uint64_t ngroups, uint64_t d, uint32_t M,
                                                              float* __restrict__ out, float* __restrict__ scales, SlotVote vote) {
   if (blockIdx.x >= M) {  // (behind l2_select_kernel only)
-    vote_on_slots(vote);
+    vote_on_slots<kBlock>(vote);
     return;
   }
   constexpr int kLoads = GROUPS < 16 ? GROUPS : 16;  // in flight per thread
@@ -2734,16 +2774,15 @@ inline uint64_t* l2_slot_counts(const CodecShape& c, const CandidateScratch& cs)
 
 // The sample: every kSampleStride-th whole wavefront tile of every row.
 template <int NORM, bool L2>
-hipError_t sample_launch(const CodecShape& c, const float* g, const float* gref, const CandidateScratch& cs, hipStream_t s) {
+hipError_t sample_launch(const CodecShape& c, const float* g, const float* gref, const CandidateScratch& cs, uint32_t* rows,
+                         float* sampled, hipStream_t s) {
   const uint64_t sample_tiles = (c.d / kWaveTileElements + kSampleStride - 1) / kSampleStride;
-  uint32_t nsample = div_up_u32(sample_tiles, kWavesPerBlock);
-  if (nsample > kAbsmaxMaxBlocks) nsample = kAbsmaxMaxBlocks;
-  hipLaunchKernelGGL((sample_stats_kernel<NORM, L2>), dim3(nsample, c.M), dim3(kBlock), 0, s, GradRows{g, c.d},
+  uint32_t nsample = div_up_u32(sample_tiles, kSampleWaves);
+  if (nsample > kSampleRows) nsample = kSampleRows;
+  *rows = nsample;
+  *sampled = (float)(sample_tiles * kWaveTileElements);
+  hipLaunchKernelGGL((sample_stats_kernel<NORM, L2>), dim3(nsample, c.M), dim3(kSampleThreads), 0, s, GradRows{g, c.d},
                      reinterpret_cast<const float4*>(gref), cs.sample_partials, cs.sample_sums, c.d / 4, c.M);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(sample_finish_kernel<L2>, dim3(c.M), dim3(kBlock), 0, s, cs.sample_partials, cs.sample_sums, nsample,
-                     c.M, (float)(sample_tiles * kWaveTileElements), cs.sample_max, cs.select_ok, cs.overflowed);
   return hipGetLastError();
 }
 
@@ -2755,7 +2794,9 @@ hipError_t absmax_candidates_dispatch(const CodecShape& c, uint32_t iter, const 
   const int mc = pick_workers_per_block(c.M, (nvec + kBlock * kAbsmaxLoads - 1) / (kBlock * kAbsmaxLoads), 0.3, 8, true);
   uint32_t nblocks = 0;
   hipError_t e;
-  e = sample_launch<NORM, false>(c, g, gref, cs, s);
+  uint32_t nsample = 0;
+  float sampled = 0.f;
+  e = sample_launch<NORM, false>(c, g, gref, cs, &nsample, &sampled, s);
   if (e != hipSuccess) return e;
   const uint64_t row_tiles = c.d / kWaveTileElements;
   const uint32_t tail = tail_workgroups(c.d, mc);
@@ -2766,7 +2807,8 @@ hipError_t absmax_candidates_dispatch(const CodecShape& c, uint32_t iter, const 
 #define TNG_SELECT(MC)                                                                                              \
   hipLaunchKernelGGL((absmax_select_kernel<NORM, MC>), dim3(nblocks, (c.M + MC - 1) / MC), dim3(kBlock), 0, s,      \
                      GradRows{g, c.d}, reinterpret_cast<const float4*>(gref), reinterpret_cast<const float4*>(gref2), \
-                     partials, c.d, main_blocks, c.M, c.eps, cs.sample_max, cs.select_ok, cs.slots, cs.overflowed, c.k0, c.k1, iter)
+                     partials, c.d, main_blocks, c.M, c.eps, cs.sample_partials, cs.sample_sums, nsample, sampled, cs.sample_max, cs.select_ok, cs.slots, cs.overflowed, \
+                     c.k0, c.k1, iter)
   switch (mc) {
     case 8: TNG_SELECT(8); break;
     case 5: TNG_SELECT(5); break;
@@ -2778,7 +2820,8 @@ hipError_t absmax_candidates_dispatch(const CodecShape& c, uint32_t iter, const 
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   const SlotVote vote{cs.overflowed, nblocks * ((c.M + (uint32_t)mc - 1) / (uint32_t)mc), (uint64_t)c.M * row_tiles, cs.use_slots};
-  hipLaunchKernelGGL(absmax_finish_vote_kernel, dim3(c.M + 1), dim3(kBlock), 0, s, partials, nblocks, c.M, scales, cs.sample_max,
+  const uint32_t threads = finish_threads(nblocks);
+  hipLaunchKernelGGL((threads == kFinishLarge ? absmax_finish_vote_kernel<kFinishLarge> : absmax_finish_vote_kernel<kBlock>), dim3(c.M + 1), dim3(threads), 0, s, partials, nblocks, c.M, scales, cs.sample_max,
                      cs.select_ok, vote);
   return hipGetLastError();
 }
@@ -2840,8 +2883,7 @@ hipError_t absmax_dispatch(const CodecShape& c, const float* g, const float* gre
     *left_rows = nblocks;
     return hipSuccess;
   }
-  hipLaunchKernelGGL(absmax_finish_kernel, dim3(c.M), dim3(kBlock), 0, s, partials, nblocks, c.M, scales);
-  return hipGetLastError();
+  return launch_absmax_finish(partials, nblocks, c.M, scales, s);
 }
 
 template <int NORM, int BITS, int MC, bool FUSED>
@@ -2882,8 +2924,7 @@ hipError_t quantize_dispatch(const CodecShape& c, uint32_t iter, const float* g,
   const int mc = quantize_workers_per_block(c);
   FusedScale fs{partials, fused_rows, scales};
   if (fused_rows > fused_scale_rows(c)) {
-    hipLaunchKernelGGL(absmax_finish_kernel, dim3(c.M), dim3(kBlock), 0, s, partials, fused_rows, c.M, scales);
-    const hipError_t e = hipGetLastError();
+    const hipError_t e = launch_absmax_finish(partials, fused_rows, c.M, scales, s);
     if (e != hipSuccess) return e;
     fs.rows = 0;
   }
@@ -2976,7 +3017,9 @@ hipError_t launch_rng_draws(uint32_t k0, uint32_t k1, uint32_t iter, uint32_t wo
 }
 
 hipError_t launch_absmax_finish(const float* partials, uint32_t nblocks, uint32_t M, float* scales, hipStream_t s) {
-  hipLaunchKernelGGL(absmax_finish_kernel, dim3(M), dim3(kBlock), 0, s, partials, nblocks, M, scales);
+  const uint32_t threads = finish_threads(nblocks);
+  hipLaunchKernelGGL((threads == kFinishLarge ? absmax_finish_kernel<kFinishLarge> : absmax_finish_kernel<kBlock>), dim3(M), dim3(threads), 0, s, partials,
+                     nblocks, M, scales);
   return hipGetLastError();
 }
 
@@ -3086,7 +3129,13 @@ hipError_t l2_candidates_launch(const CodecShape& c, uint32_t iter, const float*
                                 const CandidateScratch& cs, float* scales, hipStream_t s) {
   const uint64_t nchunks = (c.d + kTreeChunk - 1) / kTreeChunk, ngroups = (nchunks + kTreeGroup - 1) / kTreeGroup;
   const uint64_t whole = c.d / kTreeChunk;  // chunks that lie inside the rows entirely
-  hipError_t e = sample_launch<NORM, true>(c, g, gref, cs, s);
+  uint32_t nsample = 0;
+  float sampled = 0.f;
+  hipError_t e = sample_launch<NORM, true>(c, g, gref, cs, &nsample, &sampled, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(sample_finish_kernel, dim3(c.M), dim3(kBlock), 0, s, cs.sample_partials, cs.sample_sums, nsample, c.M, sampled,
+                     cs.sample_max, cs.select_ok, cs.overflowed);
+  e = hipGetLastError();
   if (e != hipSuccess) return e;
   const dim3 grid((uint32_t)whole, (c.M + kL2SelectWorkers - 1) / kL2SelectWorkers);
   hipLaunchKernelGGL(l2_select_kernel<NORM>, grid, dim3(kBlock), 0, s, GradRows{g, c.d},
