@@ -902,9 +902,7 @@ constexpr int kCsrRows = 512;      // minibatch rows staged in LDS per trip
 // wavefront and 512 rows, about two thirds of their time, and the segments' loads by themselves ran 25 to 30 % slower than
 // with 16 bytes per lane (1.21 -> 0.92 ms for the segments of 2^14 columns, 64 workers, 512 rows of 16777 pairs).  Iteration
 // at d = 2^24, M = 64, B = 512, 0.1 % density 4276 -> 3899 us (dot products 1180 -> 959, gradient 2055 -> 1903); d = 2^16, M = 8 19.1 ->
-// 17.8.  By the counters no unit bounds the gradient pass there: its LDS is active 36 % of the clocks (a sixth of that bank
-// conflicts), the vector unit issues 29 %, memory moves 4.7 TB/s; its wavefronts wait for memory counters and barriers 39 % of their
-// time and to issue 47 %.
+// 17.8.  What the gradient pass then waited for was its own order, see csr_grad_workers_kernel.
 constexpr int kCsrLanes = 8;                  // lanes that share one row segment
 constexpr int kCsrUnroll = 4;                 // row segments per lane group and trip
 constexpr uint32_t kCsrStep = 2 * kCsrLanes;  // entries that a load of each lane covers
@@ -1166,6 +1164,10 @@ __device__ __forceinline__ void csr_request(const CsrEntries<PAIRS>& e, const Cs
   }
 }
 
+// A load on a rare path has to end there: one that no lane used would count as under way where the paths join again, and the first
+// instruction behind that writes to its registers would wait for every load in flight.
+__device__ __forceinline__ void csr_arrived(const CsrTwo& e) { asm volatile("" : : "v"(e.col[0]), "v"(e.val[0]), "v"(e.col[1]), "v"(e.val[1])); }
+
 // use(whether, column, value, u, c) for the lane's entries of the batch and of what is behind it; entries that are not the
 // lane's come with whether = false (and anything for column and value).  c = 0 .. 3 says which entries of every 2 kCsrStep these
 // are: the first or second of the lane's two, in an even or odd load.  LOADS per segment and trip behind the batch.
@@ -1202,6 +1204,7 @@ __device__ __forceinline__ void csr_use(const CsrEntries<PAIRS>& e, const CsrSeg
         const bool in = 2 * gl + k + q * kCsrStep < (b.n[u] & kCsrCount);
         use(in, two[u][q].col[0], two[u][q].val[0], u, 2 * ((Q + q) & 1));
         use(in, two[u][q].col[1], two[u][q].val[1], u, 2 * ((Q + q) & 1) + 1);
+        csr_arrived(two[u][q]);
       }
     }
   }
@@ -1215,6 +1218,7 @@ __device__ __forceinline__ void csr_use(const CsrEntries<PAIRS>& e, const CsrSeg
         e.load(at, c, v);
         use(at / kCsrStep % 2 == 0, c, v, u, 0);
         use(at / kCsrStep % 2 == 1, c, v, u, 2);
+        asm volatile("" : : "v"(c), "v"(v));  // (as csr_arrived)
       }
     }
   }
@@ -1236,34 +1240,41 @@ __device__ __forceinline__ uint32_t csr_place(uint32_t gl) { return gl < 4 ? gl 
 // Lane gl is left with sum gl U / kCsrLanes.
 template <int U>
 __device__ __forceinline__ float csr_group_sums(const float (&acc)[U][4], uint32_t gl) {
-  static_assert(kCsrLanes == 8 && (U == 2 || U == 4), "the exchange below");
+  static_assert(kCsrLanes == 8 && (U == 1 || U == 4), "the exchange below");
   constexpr int kMirror = 0x141, kSwap2 = 0x4E, kSwap1 = 0xB1;  // row_half_mirror, quad_perm [2, 3, 0, 1] and [1, 0, 3, 2]
-  const bool b4 = (gl & 4u) != 0, b2 = (gl & 2u) != 0, b1 = (gl & 1u) != 0;
-  float r[U / 2][2];
-#pragma unroll
-  for (int k = 0; k < U / 2; ++k) {
+  if constexpr (U == 1) {
+    float t[2];
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-      const float lower = acc[k][c] + acc[k][c + 2], upper = acc[k + U / 2][c] + acc[k + U / 2][c + 2];
-      r[k][c] = (b4 ? upper : lower) + csr_lane_move<kMirror>(b4 ? lower : upper);
+      t[c] = acc[0][c] + acc[0][c + 2];
+      t[c] += csr_lane_move<kMirror>(t[c]);
+      t[c] += csr_lane_move<kSwap2>(t[c]);
+      t[c] += csr_lane_move<kSwap1>(t[c]);
     }
-  }
-  if (U == 4) {
+    return t[0] + t[1];
+  } else {
+    const bool b4 = (gl & 4u) != 0, b2 = (gl & 2u) != 0, b1 = (gl & 1u) != 0;
+    float r[U / 2][2];
+#pragma unroll
+    for (int k = 0; k < U / 2; ++k) {
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const float lower = acc[k][c] + acc[k][c + 2], upper = acc[k + U / 2][c] + acc[k + U / 2][c + 2];
+        r[k][c] = (b4 ? upper : lower) + csr_lane_move<kMirror>(b4 ? lower : upper);
+      }
+    }
     float s[2];
 #pragma unroll
     for (int c = 0; c < 2; ++c) s[c] = (b2 ? r[U / 2 - 1][c] : r[0][c]) + csr_lane_move<kSwap2>(b2 ? r[0][c] : r[U / 2 - 1][c]);
     const float t = (b1 ? s[1] : s[0]) + csr_lane_move<kSwap1>(b1 ? s[0] : s[1]);
     return t + csr_lane_move<kSwap1>(t);
   }
-  float t = (b2 ? r[0][1] : r[0][0]) + csr_lane_move<kSwap2>(b2 ? r[0][0] : r[0][1]);
-  t += csr_lane_move<kSwap1>(t);
-  return t + csr_lane_move<kSwap2>(t);
 }
 template <bool PAIRS, int U, int Q>
 __device__ __forceinline__ float csr_dot(const CsrEntries<PAIRS>& e, const CsrSeg* seg, uint32_t gl, const void* dummy,
                                          const CsrBatch<U, Q>& b, const float* wtile, uint64_t c0) {
   float acc[U][4] = {};
-  csr_use<2>(e, seg, csr_place(gl), dummy, b, [&](bool in, int32_t c, float v, int u, int a) {
+  csr_use<U == 1 ? 4 : 2>(e, seg, csr_place(gl), dummy, b, [&](bool in, int32_t c, float v, int u, int a) {
     // (left out by choice, not by a factor of 0: the tile's first column may be infinite)
     const float sum = __builtin_fmaf(v, wtile[in ? (uint32_t)c - (uint32_t)c0 : 0u], acc[u][a]);
     acc[u][a] = in ? sum : acc[u][a];
@@ -1324,9 +1335,13 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // partial ones.  (Random contiguous segments deliver 2.2 TB/s of useful bytes at 64 bytes per
 // segment and 3.2 TB/s at 128; this pass is bound by exactly that.)  One partial sum per row and pair
 // of tiles: zparts[m][pair][i].
-constexpr int kCsrHalfUnroll = kCsrUnroll / 2;
-constexpr uint32_t kCsrHalf = kCsrRows / 2;  // rows of a trip taken at a time
-template <bool PAIRS>
+//
+// A trip is P pieces of kCsrGroups rows, a segment per lane group: as many as the minibatch fills, up to four (csr_pieces), so that small
+// ones do not go through pieces of empty segments (iterations M = 8, d = 2^23, B = 64 252 us with four of them, 199 with one; M = 3, d = 2^22, B =
+// 200 77.0 / 71.9).  All pieces but one are on their way while one is worked on: at d = 2^24, M = 64, B = 512 959 us with two
+// halves of which one is asked for ahead of the other's arithmetic, 928 with each asked for behind its own, 923 with four pieces.
+inline int csr_pieces(uint32_t batch) { return batch <= kCsrGroups ? 1 : batch <= 2 * kCsrGroups ? 2 : 4; }
+template <bool PAIRS, int P>
 __global__ __launch_bounds__(kCsrThreads) void csr_z_wide_kernel(const int32_t* const* __restrict__ cols,
                                                                  const float* const* __restrict__ vals,
                                                                  const int64_t* __restrict__ rowbase,
@@ -1335,8 +1350,9 @@ __global__ __launch_bounds__(kCsrThreads) void csr_z_wide_kernel(const int32_t* 
                                                                  float* __restrict__ zparts, uint64_t d,
                                                                  uint32_t batch, uint32_t ntiles, uint32_t npairs,
                                                                  uint32_t M, uint32_t workers_per_block) {
+  constexpr int kRows = P * (int)kCsrGroups;
   extern __shared__ float wtile[];  // w over the columns of both tiles
-  __shared__ CsrSeg seg[3][kCsrRows];  // of the last step, this one and the next one
+  __shared__ CsrSeg seg[3][kRows];  // of this step, the next one and the one after it
   const uint32_t pair = tile_of_workgroup(blockIdx.x, npairs);
   const uint32_t t_lo = 2 * pair, t_hi = min(2 * pair + 2, ntiles);
   constexpr uint32_t T = 2u << kCsrTileShift;
@@ -1357,57 +1373,66 @@ __global__ __launch_bounds__(kCsrThreads) void csr_z_wide_kernel(const int32_t* 
     for (uint32_t j = threadIdx.x; j < T; j += kCsrThreads) wtile[j] = c0 + j < d ? w[c0 + j] : 0.f;
   }
   const uint32_t group = threadIdx.x / kCsrLanes, gl = threadIdx.x % kCsrLanes;
-  // The tiles of w serve several workers in turn.  A step is one trip of kCsrRows minibatch rows of one worker, taken in two
-  // halves that alternate: while the entries of one are worked on, those of the other are on their way.  The segment bounds
-  // of the next step are fetched during this one (every thread fetches, the row index clamped, so that no load sits
-  // under a condition).
-  static_assert(kCsrThreads >= kCsrRows, "one thread per staged row");
+  // The tiles of w serve several workers in turn.  A step is one trip of kRows minibatch rows of one worker, taken in
+  // pieces: a piece is asked for again, of the next step, as soon as it has been worked on, so that all others are on their way while one
+  // is worked on.  The segment bounds of the step after the next one are staged during this one (every thread fetches, the row
+  // index clamped, so that no load sits under a condition); past the last step the segments are empty.
+  static_assert(kCsrThreads >= kRows, "one thread per staged row");
   const uint32_t m_first = blockIdx.y * workers_per_block, m_last = min(m_first + workers_per_block, M);
-  const uint32_t trips = (batch + kCsrRows - 1) / kCsrRows;
+  const uint32_t trips = (batch + kRows - 1) / kRows;
   const uint32_t steps = (m_last - m_first) * trips;
-  auto fetch_bounds = [&](uint32_t step, int64_t& start, uint32_t& length) {
-    const uint32_t m = m_first + step / trips, first = (step % trips) * kCsrRows;
-    const uint32_t j = first + min(threadIdx.x, min((uint32_t)kCsrRows, batch - first) - 1u);
+  uint32_t lo, hi;
+  int64_t base;
+  auto worker = [&](uint32_t step) { return m_first + min(step, steps - 1) / trips; };
+  auto first_of = [&](uint32_t step) { return min(step, steps - 1) % trips * kRows; };
+  auto fetch = [&](uint32_t step) {
+    const uint32_t m = worker(step), first = first_of(step);
+    const uint32_t j = first + min(threadIdx.x, min((uint32_t)kRows, batch - first) - 1u);
     const uint32_t* __restrict__ b = bounds + (uint64_t)m * (ntiles + 1) * batch;
-    const uint32_t lo = b[(uint64_t)t_lo * batch + j], hi = b[(uint64_t)t_hi * batch + j];
-    start = rowbase[(uint64_t)m * batch + j] + lo;
-    length = first + threadIdx.x < batch ? hi - lo : 0u;
+    lo = b[(uint64_t)t_lo * batch + j];
+    hi = b[(uint64_t)t_hi * batch + j];
+    base = rowbase[(uint64_t)m * batch + j];
   };
-  auto entries = [&](uint32_t step) { return CsrEntries<PAIRS>(cols[m_first + step / trips], vals[m_first + step / trips]); };
-  auto dummy = [&](uint32_t step) { return rowbase + (uint64_t)(m_first + step / trips) * batch; };
-  auto stage = [&](uint32_t step, uint32_t buf, int64_t start, uint32_t length) {
-    if (threadIdx.x < (uint32_t)kCsrRows) seg[buf][threadIdx.x] = csr_segment(entries(step), start, length, 0.f, dummy(step));
+  auto entries = [&](uint32_t step) { return CsrEntries<PAIRS>(cols[worker(step)], vals[worker(step)]); };
+  auto dummy = [&](uint32_t step) { return rowbase + (uint64_t)worker(step) * batch; };
+  auto stage = [&](uint32_t step, uint32_t buf) {
+    if (threadIdx.x < (uint32_t)kRows)
+      seg[buf][threadIdx.x] = csr_segment(entries(step), base + lo, step < steps && first_of(step) + threadIdx.x < batch ? hi - lo : 0u, 0.f, dummy(step));
   };
-  typedef CsrBatch<kCsrHalfUnroll, kCsrWideLoads> Half;
-  auto request = [&](uint32_t step, uint32_t buf, uint32_t half, Half& b) {
-    csr_request(entries(step), seg[buf] + half * kCsrHalf + group * kCsrHalfUnroll, csr_place(gl), dummy(step), b);
+  typedef CsrBatch<1, kCsrWideLoads> Piece;
+  Piece pieces[P];
+  auto request = [&](uint32_t step, uint32_t buf, int k) {
+    csr_request(entries(step), seg[buf] + k * (int)kCsrGroups + group, csr_place(gl), dummy(step), pieces[k]);
   };
-  auto dot = [&](uint32_t step, uint32_t buf, uint32_t half, const Half& b) {
-    const uint32_t j0 = half * kCsrHalf + group * kCsrHalfUnroll;
-    const float sum = csr_dot(entries(step), seg[buf] + j0, gl, dummy(step), b, wtile, c0);
-    const uint32_t i = (step % trips) * kCsrRows + j0 + gl / (kCsrLanes / kCsrHalfUnroll);
-    if (gl % (kCsrLanes / kCsrHalfUnroll) == 0 && i < batch)
-      zparts[((uint64_t)(m_first + step / trips) * npairs + pair) * batch + i] = sum;
+  auto dot = [&](uint32_t step, uint32_t buf, int k) {
+    const uint32_t j0 = k * (int)kCsrGroups + group;
+    const float sum = csr_dot(entries(step), seg[buf] + j0, gl, dummy(step), pieces[k], wtile, c0);
+    const uint32_t i = first_of(step) + j0;
+    if (gl == 0 && i < batch)
+      zparts[((uint64_t)worker(step) * npairs + pair) * batch + i] = sum;
   };
-  int64_t next_start;
-  uint32_t next_len;
-  fetch_bounds(0, next_start, next_len);
-  stage(0, 0, next_start, next_len);
+  fetch(0);
+  stage(0, 0);
+  fetch(1);
+  stage(1, 1);
+  fetch(2);
   __syncthreads();
-  Half a, b;
-  request(0, 0, 0, a);
+#pragma unroll
+  for (int k = 0; k < P; ++k) request(0, 0, k);
   uint32_t buf = 0;
   for (uint32_t step = 0; step < steps; ++step) {
-    const uint32_t buf_next = buf == 2 ? 0 : buf + 1;
-    const uint32_t next = min(step + 1, steps - 1);  // past the last step its bounds again, of which nothing is made
-    fetch_bounds(next, next_start, next_len);
-    request(step, buf, 1, b);
-    dot(step, buf, 0, a);
-    stage(next, buf_next, next_start, next_len);
-    lds_barrier();  // the next step's bounds are in place
-    request(next, buf_next, 0, a);
-    dot(step, buf, 1, b);
-    buf = buf_next;
+    const uint32_t next = buf == 2 ? 0 : buf + 1, after = next == 2 ? 0 : next + 1;
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+      dot(step, buf, k);
+      request(step + 1, next, k);
+      if (k == 0) {
+        stage(step + 2, after);
+        fetch(step + 3);
+      }
+    }
+    lds_barrier();  // the bounds of step + 2 are in place
+    buf = next;
   }
 }
 
@@ -1683,7 +1708,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_run_kernel(const int32_t
 // (Iterations with the tile's columns in csr_slot's order and every length of rows here, at 0.1 % density, B = 512: d = 2^24, M =
 // 32 2158 -> 1941 us with the entries two to a lane; d = 2^24 - 5, which took a workgroup per tile and worker and a scale pass
 // before, 2890 -> 2065; d = 5000001, M = 16 483 -> 370; d = 1000003, M = 8 75 -> 61.)
-template <bool PAIRS, int NORM, bool FULL>
+template <bool PAIRS, int NORM, bool FULL, int P>
 __global__ __launch_bounds__(kCsrThreads) void csr_grad_workers_kernel(const int32_t* const* __restrict__ cols,
                                                                        const float* const* __restrict__ vals,
                                                                        const int64_t* __restrict__ rowbase,
@@ -1692,8 +1717,9 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_workers_kernel(const int
                                                                        float* __restrict__ g, uint64_t d, uint32_t batch,
                                                                        uint32_t ntiles, uint32_t M, uint32_t per_group,
                                                                        ScaleFusion fuse) {
+  constexpr int kRows = P * (int)kCsrGroups;  // (the whole minibatch)
   extern __shared__ double gtile[];  // g over the tile's columns, accumulated in fp64
-  __shared__ CsrSeg seg[2][kCsrRows];
+  __shared__ CsrSeg seg[3][kRows];  // of this worker, the next one and the one after it
   __shared__ float red[2][kCsrThreads / kWave];  // by parity of the round: read in the round after it was written
   constexpr uint32_t T = 1u << kCsrTileShift;
   constexpr int kPer = (int)(T / (4 * kCsrThreads));
@@ -1713,16 +1739,28 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_workers_kernel(const int
   auto rowbase_of = [&](uint32_t m) { return as_global(rowbase + (uint64_t)m * batch); };
   auto resid_of = [&](uint32_t m) { return as_global(resid + (uint64_t)m * batch); };
   auto dummy_of = [&](uint32_t m) { return rowbase + (uint64_t)m * batch; };
-  auto stage = [&](const CsrEntries<PAIRS>& e, uint32_t m, uint32_t buf, int64_t start, uint32_t len, float r) {
-    if (threadIdx.x < (uint32_t)kCsrRows) seg[buf][threadIdx.x] = csr_segment(e, start, len, r, dummy_of(m));
+  auto stage = [&](uint32_t m, uint32_t buf, int64_t start, uint32_t len, float r) {
+    if (threadIdx.x < (uint32_t)kRows) seg[buf][threadIdx.x] = csr_segment(CsrEntries<PAIRS>(cols[m], vals[m]), start, len, r, dummy_of(m));
   };
-  {
-    const uint32_t lo = bounds_of(m_first)[tb_row], hi = bounds_of(m_first)[tb_row + batch];
-    const int64_t base = rowbase_of(m_first)[row];
-    const float res = resid_of(m_first)[row];
-    for (uint32_t j = threadIdx.x; j < T; j += kCsrThreads) gtile[j] = 0.0;
-    stage(CsrEntries<PAIRS>(cols[m_first], vals[m_first]), m_first, 0, base + lo, has_row ? hi - lo : 0u, res);
-  }
+  // what a worker's round needs (worker index clamped: a fetch, never a branch)
+  uint32_t flo, fhi;
+  int64_t fbase;
+  float fres;
+  auto fetch = [&](uint32_t m) {
+    const uint32_t mc = min(m, m_end - 1);
+    flo = bounds_of(mc)[tb_row];
+    fhi = bounds_of(mc)[tb_row + batch];
+    fbase = rowbase_of(mc)[row];
+    fres = resid_of(mc)[row];
+  };
+  auto stage_fetched = [&](uint32_t m, uint32_t buf) {  // past the last worker the lengths are 0
+    stage(min(m, m_end - 1), buf, fbase + flo, has_row && m < m_end ? fhi - flo : 0u, fres);
+  };
+  fetch(m_first);
+  for (uint32_t j = threadIdx.x; j < T; j += kCsrThreads) gtile[j] = 0.0;
+  stage_fetched(m_first, 0);
+  fetch(m_first + 1);
+  stage_fetched(m_first + 1, 1);
   // the reference of the thread's columns: the same for every worker
   float4 r1[kPer], r2[kPer];
 #pragma unroll
@@ -1732,10 +1770,23 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_workers_kernel(const int
     else
       load_refs4_end<NORM>(fuse, c0 + 4 * ((uint32_t)k * kCsrThreads + threadIdx.x), d, r1[k], r2[k]);
   const uint32_t group = threadIdx.x / kCsrLanes, gl = threadIdx.x % kCsrLanes;
-  const uint32_t j0 = group * kCsrUnroll;
-  CsrBatch<kCsrUnroll, kCsrLoads> next;
-  // entries of worker mr's segments staged in buffer buf
-  auto request = [&](const CsrEntries<PAIRS>& e, uint32_t mr, uint32_t buf) { csr_request(e, seg[buf] + j0, gl, dummy_of(mr), next); };
+  // A worker's segments are taken in pieces: a piece is asked for again, of the next worker, as soon as it has been added, so that the entries
+  // of all others are on their way meanwhile, behind the barriers and during the write-out.  (All of a worker's entries asked for behind
+  // the barrier that ends the adds: none are on their way during the adds.  d = 2^24, M = 64, B = 512: 1900 us, of which 675 go with the stores and
+  // 130 with the adds; two halves 1650, four pieces 1624.  Waiting for the stores less, by an order in which the bounds are asked for ahead of them,
+  // made that form slower, 1990: reads and writes mixed cost more than apart.)
+  typedef CsrBatch<1, kCsrLoads> Piece;
+  Piece pieces[P];
+  auto at = [&](uint32_t buf, int k) { return seg[buf] + k * (int)kCsrGroups + group; };
+  auto request = [&](uint32_t m, uint32_t buf, int k) {
+    const uint32_t mc = min(m, m_end - 1);
+    csr_request(CsrEntries<PAIRS>(cols[mc], vals[mc]), at(buf, k), gl, dummy_of(mc), pieces[k]);
+  };
+  auto add = [&](uint32_t m, uint32_t buf, int k) {
+    csr_use<4>(CsrEntries<PAIRS>(cols[m], vals[m]), at(buf, k), gl, dummy_of(m), pieces[k], [&](bool in, int32_t c, float v, int u, int) {
+      if (in) atomicAdd(&gtile[csr_slot((uint32_t)c)], (double)(pieces[k].r[u] * v));
+    });
+  };
   auto store_maximum = [&](uint32_t m) {  // by thread 0, once red holds worker m's wavefront maxima
     const float* rm = red[(m - m_first) & 1u];
     float mx = rm[0];
@@ -1743,23 +1794,19 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_workers_kernel(const int
     for (int k = 1; k < kCsrThreads / kWave; ++k) mx = fmaxf(mx, rm[k]);
     fuse.partials[(uint64_t)t * M + m] = mx;
   };
+  uint32_t buf = 0;
   auto round = [&](uint32_t m) {
-    const uint32_t cur = (m - m_first) & 1u;
-    // what the next worker's round needs (worker index clamped: a fetch, never a branch); past the last
-    // worker the lengths become 0
-    const bool more = m + 1 < m_end;
-    const uint32_t mn = more ? m + 1 : m;
-    const uint32_t nlo = bounds_of(mn)[tb_row], nhi = bounds_of(mn)[tb_row + batch];
-    const int64_t nbase = rowbase_of(mn)[row];
-    const float nres = resid_of(mn)[row];
-    const CsrEntries<PAIRS> e(cols[m], vals[m]), en(cols[mn], vals[mn]);
-    csr_use<1>(e, seg[cur] + j0, gl, dummy_of(m), next, [&](bool in, int32_t c, float v, int u, int) {
-      if (in) atomicAdd(&gtile[csr_slot((uint32_t)c)], (double)(next.r[u] * v));
-    });
-    stage(en, mn, cur ^ 1u, nbase + nlo, (has_row && more) ? nhi - nlo : 0u, nres);
-    lds_barrier();  // every add of worker m has been made; the segments of worker m+1 are staged
-    if (m > m_first && threadIdx.x == 0) store_maximum(m - 1);  // older than the request below: need not be counted
-    request(en, mn, cur ^ 1u);  // before the stores below
+    const uint32_t cur = (m - m_first) & 1u, next = buf == 2 ? 0 : buf + 1, after = next == 2 ? 0 : next + 1;
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+      add(m, buf, k);
+      request(m + 1, next, k);
+      if (k == 0) stage_fetched(m + 2, after);
+    }
+    fetch(m + 3);
+    lds_barrier();  // every add of worker m has been made; the segments of worker m + 2 are staged
+    if (m > m_first && threadIdx.x == 0) store_maximum(m - 1);
+    buf = next;
     float* __restrict__ out = g + (uint64_t)m * d + c0;
     float4* __restrict__ out4 = reinterpret_cast<float4*>(out);
     float amax = 0.f;
@@ -1779,8 +1826,10 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_workers_kernel(const int
     if (threadIdx.x % kWave == 0) red[cur][threadIdx.x / kWave] = amax;
     lds_barrier();  // the tile is clear again; red is complete
   };
+  fetch(m_first + 2);
   lds_barrier();
-  request(CsrEntries<PAIRS>(cols[m_first], vals[m_first]), m_first, 0);
+#pragma unroll
+  for (int k = 0; k < P; ++k) request(m_first, 0, k);
   // the first round stands apart from the loop, as in the kernel above
   round(m_first);
   for (uint32_t m = m_first + 1; m < m_end; ++m) round(m);
@@ -2417,19 +2466,21 @@ hipError_t csr_grad_launches(const LogregData& p, uint64_t d, uint32_t M, uint32
     std::lock_guard<std::mutex> attr_lock(attr_mutex);
     if (!attr_done[dev]) {
       const int lds_double = (int)(sizeof(double) << kCsrTileShift);
-      const void* big_lds[] = {reinterpret_cast<const void*>(csr_z_wide_kernel<PAIRS>),
+#define TNG_ALL_PIECES(P)                                                                                                            \
+  reinterpret_cast<const void*>(csr_z_wide_kernel<PAIRS, P>), reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormNone, true, P>), \
+      reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormSub, true, P>),                                              \
+      reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormQuot, true, P>),                                             \
+      reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormNone, false, P>),                                            \
+      reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormSub, false, P>),                                             \
+      reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormQuot, false, P>)
+      const void* big_lds[] = {TNG_ALL_PIECES(1), TNG_ALL_PIECES(2), TNG_ALL_PIECES(4),
                                reinterpret_cast<const void*>(csr_grad_kernel<false, PAIRS>),
                                reinterpret_cast<const void*>(csr_grad_kernel<true, PAIRS>),
                                reinterpret_cast<const void*>(csr_grad_run_kernel<PAIRS, kNormNone>),
                                reinterpret_cast<const void*>(csr_grad_run_kernel<PAIRS, kNormSub>),
                                reinterpret_cast<const void*>(csr_grad_run_kernel<PAIRS, kNormQuot>),
-                               reinterpret_cast<const void*>(csr_grad_run_kernel<PAIRS, kNormComb>),
-                               reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormNone, true>),
-                               reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormSub, true>),
-                               reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormQuot, true>),
-                               reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormNone, false>),
-                               reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormSub, false>),
-                               reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormQuot, false>)};
+                               reinterpret_cast<const void*>(csr_grad_run_kernel<PAIRS, kNormComb>)};
+#undef TNG_ALL_PIECES
       static_assert(2 * sizeof(float) == sizeof(double), "two tiles of w are as large as one of g");
       for (const void* kernel : big_lds) {
         const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds_double);
@@ -2452,7 +2503,9 @@ hipError_t csr_grad_launches(const LogregData& p, uint64_t d, uint32_t M, uint32
     uint32_t wpb = 1;  // workers per workgroup while 1024 workgroups remain (per iteration at d = 2^24, 64 workers:
                        // 4.538 ms with 8 per workgroup, 4.531 with 16, 4.519 with 32)
     while (wpb < 32 && wpb * 2 <= M && (uint64_t)nparts * (M / (wpb * 2)) >= 1024) wpb *= 2;
-    hipLaunchKernelGGL(csr_z_wide_kernel<PAIRS>, dim3(nparts, (M + wpb - 1) / wpb), dim3(kCsrThreads), 2 * lds_w, s, p.col,
+    const int pieces = csr_pieces(batch);
+    auto kernel = pieces == 1 ? csr_z_wide_kernel<PAIRS, 1> : pieces == 2 ? csr_z_wide_kernel<PAIRS, 2> : csr_z_wide_kernel<PAIRS, 4>;
+    hipLaunchKernelGGL(kernel, dim3(nparts, (M + wpb - 1) / wpb), dim3(kCsrThreads), 2 * lds_w, s, p.col,
                        p.val, rowbase, bounds, w, zpart, d, batch, ntiles, nparts, M, wpb);
   } else {
     hipLaunchKernelGGL(csr_z_kernel<PAIRS>, dim3(M, ntiles), dim3(kCsrThreads), lds_w, s, p.col, p.val, rowbase, bounds, w,
@@ -2473,8 +2526,10 @@ hipError_t csr_grad_launches(const LogregData& p, uint64_t d, uint32_t M, uint32
       uint32_t per_group = 64;
       while (per_group > 2 && (uint64_t)ntiles * ((M + per_group - 1) / per_group) < 1024) per_group /= 2;
       const dim3 grid(ntiles, (M + per_group - 1) / per_group);
+      const int pieces = csr_pieces(batch);
+#define TNG_WORKERS_P(NORM, P) (full ? csr_grad_workers_kernel<PAIRS, NORM, true, P> : csr_grad_workers_kernel<PAIRS, NORM, false, P>)
 #define TNG_WORKERS(NORM)                                                                                                \
-  hipLaunchKernelGGL((full ? csr_grad_workers_kernel<PAIRS, NORM, true> : csr_grad_workers_kernel<PAIRS, NORM, false>), \
+  hipLaunchKernelGGL((pieces == 1 ? TNG_WORKERS_P(NORM, 1) : pieces == 2 ? TNG_WORKERS_P(NORM, 2) : TNG_WORKERS_P(NORM, 4)), \
                      grid, dim3(kCsrThreads), lds_g, s, p.col, p.val, rowbase, bounds, z, g, d, batch, ntiles, M,       \
                      per_group, *fuse)
       switch (fuse->norm) {
@@ -2483,6 +2538,7 @@ hipError_t csr_grad_launches(const LogregData& p, uint64_t d, uint32_t M, uint32
         default: TNG_WORKERS(kNormNone); break;
       }
 #undef TNG_WORKERS
+#undef TNG_WORKERS_P
     } else if (batch <= (uint32_t)kCsrRows) {
       const uint32_t run = kCsrRun;
       const dim3 grid(M, (ntiles + run - 1) / run);
