@@ -706,7 +706,7 @@ constexpr uint32_t kFormNone = 0u, kFormWords = 1u, kFormBins = 2u;
 // |v| (the lower bound R^ of the row's scale) and the sum of |v|.  Their ratio, mean |v| / R^, is the share
 // of the row's elements that will be candidates -- P(u < |v| / R^) averaged over the elements -- so it tells
 // beforehand whether the slots can hold them.  One worker per workgroup row (blockIdx.y); partial results per
-// workgroup, reduced by sample_finish_kernel.
+// workgroup, reduced by the wavefronts of absmax_select_kernel that use them (for the l2 norm by sample_finish_kernel).
 constexpr uint32_t kL2OverflowCounts = kBlock;  // counters that the workgroups of l2_select_kernel share
 // 1024 elements x 0.10 + two standard deviations fill a slot of kCandCap, 4096 x 0.10 + two one of kL2SlotEntries
 constexpr float kDenseLimit = 0.10f;
@@ -1298,7 +1298,7 @@ __global__ __launch_bounds__(THREADS) void absmax_finish_vote_kernel(const float
 // slots come by one load, what belongs to a row sits in its lanes, and the rare paths are behind the main one, there only once, eight
 // wavefronts to a SIMD (64 registers).  At d = 2^27, M = 8 123 us with slots of words, a step per worker with all lanes on it; 173 so with
 // half-words (530 vector and 640 scalar instructions a wavefront, the vector unit all but full); 98 now.  The draws of elements that need
-// their value in scalar instructions: 115.  Eight tiles of one worker by a wavefront each: d = 2^26, M = 1 27.5 us, 16 so.
+// their value in scalar instructions: 115.
 constexpr int quantize_tiles(int mc) { return mc > 4 ? 1 : 8 / mc; }  // tiles that a wavefront takes
 template <int NORM, int MC>
 __global__ __launch_bounds__(kBlock, 8) void quantize_candidates_kernel(
