@@ -1357,6 +1357,35 @@ __global__ __launch_bounds__(kCsrThreads) void csr_z_wide_kernel(const int32_t* 
   const uint32_t t_lo = 2 * pair, t_hi = min(2 * pair + 2, ntiles);
   constexpr uint32_t T = 2u << kCsrTileShift;
   const uint64_t c0 = (uint64_t)t_lo << kCsrTileShift;
+  // The tiles of w serve several workers in turn.  A step is one trip of kRows minibatch rows of one worker, taken in
+  // pieces: a piece is asked for again, of the next step, as soon as it has been worked on, so that all others are on their way while one
+  // is worked on.  The segment bounds are fetched three steps ahead and staged two ahead (every thread fetches, the row
+  // index clamped, so that no load sits under a condition); past the last step the segments are empty.
+  static_assert(kCsrThreads >= kRows, "one thread per staged row");
+  const uint32_t m_first = blockIdx.y * workers_per_block, m_last = min(m_first + workers_per_block, M);
+  const uint32_t trips = (batch + kRows - 1) / kRows;
+  const uint32_t steps = (m_last - m_first) * trips;
+  struct Bounds {
+    uint32_t lo, hi;
+    int64_t base;
+  };
+  auto worker = [&](uint32_t step) { return m_first + min(step, steps - 1) / trips; };
+  auto first_of = [&](uint32_t step) { return min(step, steps - 1) % trips * kRows; };
+  auto fetch = [&](uint32_t step) {
+    Bounds f;
+    const uint32_t m = worker(step), first = first_of(step);
+    const uint32_t j = first + min(threadIdx.x, min((uint32_t)kRows, batch - first) - 1u);
+    const uint32_t* __restrict__ b = bounds + (uint64_t)m * (ntiles + 1) * batch;
+    f.lo = b[(uint64_t)t_lo * batch + j];
+    f.hi = b[(uint64_t)t_hi * batch + j];
+    f.base = rowbase[(uint64_t)m * batch + j];
+    return f;
+  };
+  // Those of the first three steps are asked for together, ahead of the tiles of w: one after the other behind the tiles, each with its
+  // wait, they held up the workgroups of few steps (iterations at d = 2^20, M = 8, B = 512 48.7 -> 48.2 us, B = 1000 64.3 -> 63.4; d = 2^22,
+  // M = 8, B = 512 143.8 -> 142.3, with the same order in the gradient pass).
+  const Bounds first_step = fetch(0), second_step = fetch(1);
+  Bounds fetched = fetch(2);
   if (c0 + T <= d && (reinterpret_cast<uintptr_t>(w) & 15u) == 0) {
     constexpr int kVec = (int)(T / (4 * kCsrThreads));  // 8 float4 per thread, four in flight at a time
     const float4* __restrict__ w4 = reinterpret_cast<const float4*>(w + c0);
@@ -1373,31 +1402,11 @@ __global__ __launch_bounds__(kCsrThreads) void csr_z_wide_kernel(const int32_t* 
     for (uint32_t j = threadIdx.x; j < T; j += kCsrThreads) wtile[j] = c0 + j < d ? w[c0 + j] : 0.f;
   }
   const uint32_t group = threadIdx.x / kCsrLanes, gl = threadIdx.x % kCsrLanes;
-  // The tiles of w serve several workers in turn.  A step is one trip of kRows minibatch rows of one worker, taken in
-  // pieces: a piece is asked for again, of the next step, as soon as it has been worked on, so that all others are on their way while one
-  // is worked on.  The segment bounds of the step after the next one are staged during this one (every thread fetches, the row
-  // index clamped, so that no load sits under a condition); past the last step the segments are empty.
-  static_assert(kCsrThreads >= kRows, "one thread per staged row");
-  const uint32_t m_first = blockIdx.y * workers_per_block, m_last = min(m_first + workers_per_block, M);
-  const uint32_t trips = (batch + kRows - 1) / kRows;
-  const uint32_t steps = (m_last - m_first) * trips;
-  uint32_t lo, hi;
-  int64_t base;
-  auto worker = [&](uint32_t step) { return m_first + min(step, steps - 1) / trips; };
-  auto first_of = [&](uint32_t step) { return min(step, steps - 1) % trips * kRows; };
-  auto fetch = [&](uint32_t step) {
-    const uint32_t m = worker(step), first = first_of(step);
-    const uint32_t j = first + min(threadIdx.x, min((uint32_t)kRows, batch - first) - 1u);
-    const uint32_t* __restrict__ b = bounds + (uint64_t)m * (ntiles + 1) * batch;
-    lo = b[(uint64_t)t_lo * batch + j];
-    hi = b[(uint64_t)t_hi * batch + j];
-    base = rowbase[(uint64_t)m * batch + j];
-  };
   auto entries = [&](uint32_t step) { return CsrEntries<PAIRS>(cols[worker(step)], vals[worker(step)]); };
   auto dummy = [&](uint32_t step) { return rowbase + (uint64_t)worker(step) * batch; };
-  auto stage = [&](uint32_t step, uint32_t buf) {
+  auto stage = [&](uint32_t step, uint32_t buf, const Bounds& f) {
     if (threadIdx.x < (uint32_t)kRows)
-      seg[buf][threadIdx.x] = csr_segment(entries(step), base + lo, step < steps && first_of(step) + threadIdx.x < batch ? hi - lo : 0u, 0.f, dummy(step));
+      seg[buf][threadIdx.x] = csr_segment(entries(step), f.base + f.lo, step < steps && first_of(step) + threadIdx.x < batch ? f.hi - f.lo : 0u, 0.f, dummy(step));
   };
   typedef CsrBatch<1, kCsrWideLoads> Piece;
   Piece pieces[P];
@@ -1411,11 +1420,8 @@ __global__ __launch_bounds__(kCsrThreads) void csr_z_wide_kernel(const int32_t* 
     if (gl == 0 && i < batch)
       zparts[((uint64_t)worker(step) * npairs + pair) * batch + i] = sum;
   };
-  fetch(0);
-  stage(0, 0);
-  fetch(1);
-  stage(1, 1);
-  fetch(2);
+  stage(0, 0, first_step);
+  stage(1, 1, second_step);
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < P; ++k) request(0, 0, k);
@@ -1427,8 +1433,8 @@ __global__ __launch_bounds__(kCsrThreads) void csr_z_wide_kernel(const int32_t* 
       dot(step, buf, k);
       request(step + 1, next, k);
       if (k == 0) {
-        stage(step + 2, after);
-        fetch(step + 3);
+        stage(step + 2, after, fetched);
+        fetched = fetch(step + 3);
       }
     }
     lds_barrier();  // the bounds of step + 2 are in place
@@ -1743,24 +1749,25 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_workers_kernel(const int
     if (threadIdx.x < (uint32_t)kRows) seg[buf][threadIdx.x] = csr_segment(CsrEntries<PAIRS>(cols[m], vals[m]), start, len, r, dummy_of(m));
   };
   // what a worker's round needs (worker index clamped: a fetch, never a branch)
-  uint32_t flo, fhi;
-  int64_t fbase;
-  float fres;
+  struct Row {
+    uint32_t lo, hi;
+    int64_t base;
+    float res;
+  };
   auto fetch = [&](uint32_t m) {
     const uint32_t mc = min(m, m_end - 1);
-    flo = bounds_of(mc)[tb_row];
-    fhi = bounds_of(mc)[tb_row + batch];
-    fbase = rowbase_of(mc)[row];
-    fres = resid_of(mc)[row];
+    return Row{bounds_of(mc)[tb_row], bounds_of(mc)[tb_row + batch], rowbase_of(mc)[row], resid_of(mc)[row]};
   };
-  auto stage_fetched = [&](uint32_t m, uint32_t buf) {  // past the last worker the lengths are 0
-    stage(min(m, m_end - 1), buf, fbase + flo, has_row && m < m_end ? fhi - flo : 0u, fres);
+  auto stage_fetched = [&](uint32_t m, uint32_t buf, const Row& f) {  // past the last worker the lengths are 0
+    stage(min(m, m_end - 1), buf, f.base + f.lo, has_row && m < m_end ? f.hi - f.lo : 0u, f.res);
   };
-  fetch(m_first);
+  // Those of the first workers are asked for together: one after the other, each with its wait, they held up a group of two workers
+  // (d = 2^20, M = 8, B = 257 13.7 -> 13.2 us).
+  const Row first_worker = fetch(m_first), second_worker = fetch(m_first + 1);
+  Row fetched = fetch(m_first + 2);
   for (uint32_t j = threadIdx.x; j < T; j += kCsrThreads) gtile[j] = 0.0;
-  stage_fetched(m_first, 0);
-  fetch(m_first + 1);
-  stage_fetched(m_first + 1, 1);
+  stage_fetched(m_first, 0, first_worker);
+  stage_fetched(m_first + 1, 1, second_worker);
   // the reference of the thread's columns: the same for every worker
   float4 r1[kPer], r2[kPer];
 #pragma unroll
@@ -1801,9 +1808,9 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_workers_kernel(const int
     for (int k = 0; k < P; ++k) {
       add(m, buf, k);
       request(m + 1, next, k);
-      if (k == 0) stage_fetched(m + 2, after);
+      if (k == 0) stage_fetched(m + 2, after, fetched);
     }
-    fetch(m + 3);
+    fetched = fetch(m + 3);
     lds_barrier();  // every add of worker m has been made; the segments of worker m + 2 are staged
     if (m > m_first && threadIdx.x == 0) store_maximum(m - 1);
     buf = next;
@@ -1826,7 +1833,6 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_workers_kernel(const int
     if (threadIdx.x % kWave == 0) red[cur][threadIdx.x / kWave] = amax;
     lds_barrier();  // the tile is clear again; red is complete
   };
-  fetch(m_first + 2);
   lds_barrier();
 #pragma unroll
   for (int k = 0; k < P; ++k) request(m_first, 0, k);
