@@ -1240,7 +1240,7 @@ __device__ __forceinline__ uint32_t csr_place(uint32_t gl) { return gl < 4 ? gl 
 // Lane gl is left with sum gl U / kCsrLanes.
 template <int U>
 __device__ __forceinline__ float csr_group_sums(const float (&acc)[U][4], uint32_t gl) {
-  static_assert(kCsrLanes == 8 && (U == 1 || U == 4), "the exchange below");
+  static_assert(kCsrLanes == 8 && (U == 1 || U == 2 || U == 4), "the exchange below");
   constexpr int kMirror = 0x141, kSwap2 = 0x4E, kSwap1 = 0xB1;  // row_half_mirror, quad_perm [2, 3, 0, 1] and [1, 0, 3, 2]
   if constexpr (U == 1) {
     float t[2];
@@ -1263,11 +1263,17 @@ __device__ __forceinline__ float csr_group_sums(const float (&acc)[U][4], uint32
         r[k][c] = (b4 ? upper : lower) + csr_lane_move<kMirror>(b4 ? lower : upper);
       }
     }
-    float s[2];
+    if constexpr (U == 2) {
+      float t = (b2 ? r[0][1] : r[0][0]) + csr_lane_move<kSwap2>(b2 ? r[0][0] : r[0][1]);
+      t += csr_lane_move<kSwap1>(t);
+      return t + csr_lane_move<kSwap2>(t);
+    } else {
+      float s[2];
 #pragma unroll
-    for (int c = 0; c < 2; ++c) s[c] = (b2 ? r[U / 2 - 1][c] : r[0][c]) + csr_lane_move<kSwap2>(b2 ? r[0][c] : r[U / 2 - 1][c]);
-    const float t = (b1 ? s[1] : s[0]) + csr_lane_move<kSwap1>(b1 ? s[0] : s[1]);
-    return t + csr_lane_move<kSwap1>(t);
+      for (int c = 0; c < 2; ++c) s[c] = (b2 ? r[1][c] : r[0][c]) + csr_lane_move<kSwap2>(b2 ? r[0][c] : r[1][c]);
+      const float t = (b1 ? s[1] : s[0]) + csr_lane_move<kSwap1>(b1 ? s[0] : s[1]);
+      return t + csr_lane_move<kSwap1>(t);
+    }
   }
 }
 template <bool PAIRS, int U, int Q>
@@ -1336,12 +1342,15 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // segment and 3.2 TB/s at 128; this pass is bound by exactly that.)  One partial sum per row and pair
 // of tiles: zparts[m][pair][i].
 //
-// A trip is P pieces of kCsrGroups rows, a segment per lane group: as many as the minibatch fills, up to four (csr_pieces), so that small
+// A trip is P pieces of U segments per lane group: one segment while one or two such pieces hold the minibatch (csr_pieces), so that small
 // ones do not go through pieces of empty segments (iterations M = 8, d = 2^23, B = 64 252 us with four of them, 199 with one; M = 3, d = 2^22, B =
-// 200 77.0 / 71.9).  All pieces but one are on their way while one is worked on: at d = 2^24, M = 64, B = 512 959 us with two
-// halves of which one is asked for ahead of the other's arithmetic, 928 with each asked for behind its own, 923 with four pieces.
+// 200 77.0 / 71.9), else two pieces of two.  All pieces but one are on their way while one is worked on: at d = 2^24, M = 64, B = 512 959 us
+// with two halves of which one is asked for ahead of the other's arithmetic, 928 with each asked for behind its own, 923 with four pieces of
+// one segment (iterations alike: 3296 / 3295).  Where most segments are empty the pass is bound by its vector instructions, of which
+// four pieces have more, and by what a step costs by itself: d = 2^22, M = 64, 40 entries a row 100 us with four pieces and two divisions
+// and four loads a step, 92 with a step carried along, 89 so; d = 2^21, M = 32, 20 entries a row 38.1 / 37.1 / 36.3.
 inline int csr_pieces(uint32_t batch) { return batch <= kCsrGroups ? 1 : batch <= 2 * kCsrGroups ? 2 : 4; }
-template <bool PAIRS, int P>
+template <bool PAIRS, int P, int U>
 __global__ __launch_bounds__(kCsrThreads) void csr_z_wide_kernel(const int32_t* const* __restrict__ cols,
                                                                  const float* const* __restrict__ vals,
                                                                  const int64_t* __restrict__ rowbase,
@@ -1350,7 +1359,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_z_wide_kernel(const int32_t* 
                                                                  float* __restrict__ zparts, uint64_t d,
                                                                  uint32_t batch, uint32_t ntiles, uint32_t npairs,
                                                                  uint32_t M, uint32_t workers_per_block) {
-  constexpr int kRows = P * (int)kCsrGroups;
+  constexpr int kPieceRows = U * (int)kCsrGroups, kRows = P * kPieceRows;
   extern __shared__ float wtile[];  // w over the columns of both tiles
   __shared__ CsrSeg seg[3][kRows];  // of this step, the next one and the one after it
   const uint32_t pair = tile_of_workgroup(blockIdx.x, npairs);
@@ -1363,29 +1372,31 @@ __global__ __launch_bounds__(kCsrThreads) void csr_z_wide_kernel(const int32_t* 
   // index clamped, so that no load sits under a condition); past the last step the segments are empty.
   static_assert(kCsrThreads >= kRows, "one thread per staged row");
   const uint32_t m_first = blockIdx.y * workers_per_block, m_last = min(m_first + workers_per_block, M);
-  const uint32_t trips = (batch + kRows - 1) / kRows;
-  const uint32_t steps = (m_last - m_first) * trips;
+  struct Step {  // (carried along: made from a number it was a division and two loads for each of the four in the loop)
+    uint32_t m, first;  // worker, first row; past the last step m_last and above
+    CsrEntries<PAIRS> e;
+    const int64_t* rowbase;
+  };
+  auto step_at = [&](uint32_t m, uint32_t first) {
+    const uint32_t mc = min(m, m_last - 1);
+    return Step{m, first, CsrEntries<PAIRS>(cols[mc], vals[mc]), rowbase + (uint64_t)mc * batch};
+  };
+  auto behind = [&](const Step& s) { return s.first + kRows < batch ? step_at(s.m, s.first + kRows) : step_at(s.m + 1, 0); };
   struct Bounds {
     uint32_t lo, hi;
     int64_t base;
   };
-  auto worker = [&](uint32_t step) { return m_first + min(step, steps - 1) / trips; };
-  auto first_of = [&](uint32_t step) { return min(step, steps - 1) % trips * kRows; };
-  auto fetch = [&](uint32_t step) {
-    Bounds f;
-    const uint32_t m = worker(step), first = first_of(step);
-    const uint32_t j = first + min(threadIdx.x, min((uint32_t)kRows, batch - first) - 1u);
-    const uint32_t* __restrict__ b = bounds + (uint64_t)m * (ntiles + 1) * batch;
-    f.lo = b[(uint64_t)t_lo * batch + j];
-    f.hi = b[(uint64_t)t_hi * batch + j];
-    f.base = rowbase[(uint64_t)m * batch + j];
-    return f;
+  auto fetch = [&](const Step& s) {
+    const uint32_t j = s.first + min(threadIdx.x, min((uint32_t)kRows, batch - s.first) - 1u);
+    const uint32_t* __restrict__ b = bounds + (uint64_t)min(s.m, m_last - 1) * (ntiles + 1) * batch;
+    return Bounds{b[(uint64_t)t_lo * batch + j], b[(uint64_t)t_hi * batch + j], s.rowbase[j]};
   };
   // Those of the first three steps are asked for together, ahead of the tiles of w: one after the other behind the tiles, each with its
   // wait, they held up the workgroups of few steps (iterations at d = 2^20, M = 8, B = 512 48.7 -> 48.2 us, B = 1000 64.3 -> 63.4; d = 2^22,
   // M = 8, B = 512 143.8 -> 142.3, with the same order in the gradient pass).
-  const Bounds first_step = fetch(0), second_step = fetch(1);
-  Bounds fetched = fetch(2);
+  Step now = step_at(m_first, 0), next = behind(now), third = behind(next);
+  const Bounds first_bounds = fetch(now), second_bounds = fetch(next);
+  Bounds fetched = fetch(third);
   if (c0 + T <= d && (reinterpret_cast<uintptr_t>(w) & 15u) == 0) {
     constexpr int kVec = (int)(T / (4 * kCsrThreads));  // 8 float4 per thread, four in flight at a time
     const float4* __restrict__ w4 = reinterpret_cast<const float4*>(w + c0);
@@ -1402,43 +1413,44 @@ __global__ __launch_bounds__(kCsrThreads) void csr_z_wide_kernel(const int32_t* 
     for (uint32_t j = threadIdx.x; j < T; j += kCsrThreads) wtile[j] = c0 + j < d ? w[c0 + j] : 0.f;
   }
   const uint32_t group = threadIdx.x / kCsrLanes, gl = threadIdx.x % kCsrLanes;
-  auto entries = [&](uint32_t step) { return CsrEntries<PAIRS>(cols[worker(step)], vals[worker(step)]); };
-  auto dummy = [&](uint32_t step) { return rowbase + (uint64_t)worker(step) * batch; };
-  auto stage = [&](uint32_t step, uint32_t buf, const Bounds& f) {
+  auto stage = [&](const Step& s, uint32_t buf, const Bounds& f) {
     if (threadIdx.x < (uint32_t)kRows)
-      seg[buf][threadIdx.x] = csr_segment(entries(step), f.base + f.lo, step < steps && first_of(step) + threadIdx.x < batch ? f.hi - f.lo : 0u, 0.f, dummy(step));
+      seg[buf][threadIdx.x] = csr_segment(s.e, f.base + f.lo, s.m < m_last && s.first + threadIdx.x < batch ? f.hi - f.lo : 0u, 0.f, s.rowbase);
   };
-  typedef CsrBatch<1, kCsrWideLoads> Piece;
+  typedef CsrBatch<U, kCsrWideLoads> Piece;
   Piece pieces[P];
-  auto request = [&](uint32_t step, uint32_t buf, int k) {
-    csr_request(entries(step), seg[buf] + k * (int)kCsrGroups + group, csr_place(gl), dummy(step), pieces[k]);
+  auto request = [&](const Step& s, uint32_t buf, int k) {
+    csr_request(s.e, seg[buf] + k * kPieceRows + group * U, csr_place(gl), s.rowbase, pieces[k]);
   };
-  auto dot = [&](uint32_t step, uint32_t buf, int k) {
-    const uint32_t j0 = k * (int)kCsrGroups + group;
-    const float sum = csr_dot(entries(step), seg[buf] + j0, gl, dummy(step), pieces[k], wtile, c0);
-    const uint32_t i = first_of(step) + j0;
-    if (gl == 0 && i < batch)
-      zparts[((uint64_t)worker(step) * npairs + pair) * batch + i] = sum;
+  auto dot = [&](const Step& s, uint32_t buf, int k) {
+    const uint32_t j0 = k * kPieceRows + group * U;
+    const float sum = csr_dot(s.e, seg[buf] + j0, gl, s.rowbase, pieces[k], wtile, c0);
+    const uint32_t i = s.first + j0 + gl / (kCsrLanes / U);
+    if (gl % (kCsrLanes / U) == 0 && i < batch) zparts[((uint64_t)s.m * npairs + pair) * batch + i] = sum;
   };
-  stage(0, 0, first_step);
-  stage(1, 1, second_step);
+  stage(now, 0, first_bounds);
+  stage(next, 1, second_bounds);
   __syncthreads();
 #pragma unroll
-  for (int k = 0; k < P; ++k) request(0, 0, k);
+  for (int k = 0; k < P; ++k) request(now, 0, k);
   uint32_t buf = 0;
-  for (uint32_t step = 0; step < steps; ++step) {
-    const uint32_t next = buf == 2 ? 0 : buf + 1, after = next == 2 ? 0 : next + 1;
+  while (now.m < m_last) {
+    const uint32_t buf1 = buf == 2 ? 0 : buf + 1, buf2 = buf1 == 2 ? 0 : buf1 + 1;
+    const Step fourth = behind(third);
 #pragma unroll
     for (int k = 0; k < P; ++k) {
-      dot(step, buf, k);
-      request(step + 1, next, k);
+      dot(now, buf, k);
+      request(next, buf1, k);
       if (k == 0) {
-        stage(step + 2, after, fetched);
-        fetched = fetch(step + 3);
+        stage(third, buf2, fetched);
+        fetched = fetch(fourth);
       }
     }
-    lds_barrier();  // the bounds of step + 2 are in place
-    buf = next;
+    lds_barrier();  // the bounds of the third step are in place
+    buf = buf1;
+    now = next;
+    next = third;
+    third = fourth;
   }
 }
 
@@ -2473,13 +2485,16 @@ hipError_t csr_grad_launches(const LogregData& p, uint64_t d, uint32_t M, uint32
     if (!attr_done[dev]) {
       const int lds_double = (int)(sizeof(double) << kCsrTileShift);
 #define TNG_ALL_PIECES(P)                                                                                                            \
-  reinterpret_cast<const void*>(csr_z_wide_kernel<PAIRS, P>), reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormNone, true, P>), \
+  reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormNone, true, P>),                                             \
       reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormSub, true, P>),                                              \
       reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormQuot, true, P>),                                             \
       reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormNone, false, P>),                                            \
       reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormSub, false, P>),                                             \
       reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormQuot, false, P>)
       const void* big_lds[] = {TNG_ALL_PIECES(1), TNG_ALL_PIECES(2), TNG_ALL_PIECES(4),
+                               reinterpret_cast<const void*>(csr_z_wide_kernel<PAIRS, 1, 1>),
+                               reinterpret_cast<const void*>(csr_z_wide_kernel<PAIRS, 2, 1>),
+                               reinterpret_cast<const void*>(csr_z_wide_kernel<PAIRS, 2, 2>),
                                reinterpret_cast<const void*>(csr_grad_kernel<false, PAIRS>),
                                reinterpret_cast<const void*>(csr_grad_kernel<true, PAIRS>),
                                reinterpret_cast<const void*>(csr_grad_run_kernel<PAIRS, kNormNone>),
@@ -2510,7 +2525,7 @@ hipError_t csr_grad_launches(const LogregData& p, uint64_t d, uint32_t M, uint32
                        // 4.538 ms with 8 per workgroup, 4.531 with 16, 4.519 with 32)
     while (wpb < 32 && wpb * 2 <= M && (uint64_t)nparts * (M / (wpb * 2)) >= 1024) wpb *= 2;
     const int pieces = csr_pieces(batch);
-    auto kernel = pieces == 1 ? csr_z_wide_kernel<PAIRS, 1> : pieces == 2 ? csr_z_wide_kernel<PAIRS, 2> : csr_z_wide_kernel<PAIRS, 4>;
+    auto kernel = pieces == 1 ? csr_z_wide_kernel<PAIRS, 1, 1> : pieces == 2 ? csr_z_wide_kernel<PAIRS, 2, 1> : csr_z_wide_kernel<PAIRS, 2, 2>;
     hipLaunchKernelGGL(kernel, dim3(nparts, (M + wpb - 1) / wpb), dim3(kCsrThreads), 2 * lds_w, s, p.col,
                        p.val, rowbase, bounds, w, zpart, d, batch, ntiles, nparts, M, wpb);
   } else {
