@@ -1290,16 +1290,15 @@ __global__ __launch_bounds__(THREADS) void absmax_finish_vote_kernel(const float
   }
 }
 
-// The packed codes of a tile from its slots.  A wavefront takes eight rows, a worker's tile each (five where groups of five workers
-// divide M, as in absmax_select_kernel), eight lanes to a row; the words of a row are cleared in LDS, the candidates' codes are or-ed
-// in, and all rows' words are written at the end as the quantiser writes them.
+// The packed codes of a tile from its slots.  A wavefront takes eight rows, a worker's tile each, eight lanes to a row; the words of a row
+// are cleared in LDS, the candidates' codes are or-ed in, and all rows' words are written at the end as the quantiser writes them.
 // What bounds it: slots read and codes written (0.13 + 0.27 GB at d = 2^27, M = 8: 66 us without what follows), and vector instructions for
 // the elements that need their value (1.9 a wavefront there) and second lines (a fifth of the wavefronts).  So all of a wavefront's
 // slots come by one load, what belongs to a row sits in its lanes, and the rare paths are behind the main one, there only once, eight
 // wavefronts to a SIMD (64 registers).  At d = 2^27, M = 8 123 us with slots of words, a step per worker with all lanes on it; 173 so with
 // half-words (530 vector and 640 scalar instructions a wavefront, the vector unit all but full); 98 now.  The draws of elements that need
 // their value in scalar instructions: 115.
-constexpr int quantize_tiles(int mc) { return mc > 4 ? 1 : 8 / mc; }  // tiles that a wavefront takes
+constexpr int quantize_tiles(int mc) { return 8 / mc; }  // tiles that a wavefront takes
 template <int NORM, int MC>
 __global__ __launch_bounds__(kBlock, 8) void quantize_candidates_kernel(
     GradRows g, const float4* __restrict__ ref4, const float4* __restrict__ ref24, const float* __restrict__ scales,
@@ -1309,7 +1308,7 @@ __global__ __launch_bounds__(kBlock, 8) void quantize_candidates_kernel(
   constexpr int WPW = (int)kWaveTileElements * 2 / 32;  // 64 packed words per row
   constexpr int T = quantize_tiles(MC), ROWS = MC * T;  // a row: a worker's tile
   constexpr int kLanes = 8, X = (int)kSlotLine / kLanes, E = 2 * X;  // lanes per row, words and half-words of the line in each
-  static_assert(ROWS * kLanes <= kWave && WPW == kWave && X == 4, "16 bytes of a row's line per lane");
+  static_assert(ROWS * kLanes == kWave && WPW == kWave && X == 4, "16 bytes of a row's line per lane");
   __shared__ __attribute__((aligned(16))) FragmentBuffer<WPW, ROWS> lds;
   if (use_slots[0] == 0u) return;  // too many tiles overflowed: the ordinary quantiser runs instead
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = threadIdx.x % kWave;
@@ -1319,12 +1318,12 @@ __global__ __launch_bounds__(kBlock, 8) void quantize_candidates_kernel(
   if (t0 >= ntiles) return;  // whole wavefronts; nothing below meets the other wavefronts
   auto tile_of = [&](uint32_t row) { return T == 1 ? t0 : min(t0 + row / MC, ntiles - 1); };
   auto worker_of = [&](uint32_t row) { return min(m0 + (T == 1 ? row : row % MC), M - 1); };
-  auto is_live = [&](uint32_t row) { return row < (uint32_t)ROWS && (T == 1 ? row : row % MC) < count && (T == 1 || t0 + row / MC < ntiles); };
+  auto is_live = [&](uint32_t row) { return (T == 1 ? row : row % MC) < count && (T == 1 || t0 + row / MC < ntiles); };
   auto slot_of = [&](uint32_t row) { return Slot(const_cast<uint32_t*>(slots), ntiles, worker_of(row), tile_of(row)); };
   // The first lines of all the slots (62 candidates of a row with a bound each) come by one load, and a lane has its row's limits and
   // what it needs of the head in registers of its own.
-  const uint32_t row = min((uint32_t)(lane / kLanes), (uint32_t)ROWS - 1), part = (uint32_t)(lane % kLanes);
-  const bool live = is_live((uint32_t)(lane / kLanes));
+  const uint32_t row = (uint32_t)(lane / kLanes), part = (uint32_t)(lane % kLanes);
+  const bool live = is_live(row);
   const v4u_t line = reinterpret_cast<const v4u_t*>(slot_of(row).line)[part];
   const float r = scales[worker_of(row)];
   const uint32_t limits = select_ok[worker_of(row)];
@@ -2865,8 +2864,11 @@ hipError_t quantize_candidates_dispatch(const CodecShape& c, uint32_t iter, cons
                                         const float* gref2, const float* scales, const CandidateScratch& cs,
                                         uint32_t* codes, hipStream_t s) {
   const uint64_t tiles = (c.d / kWaveTileElements + kWavesPerBlock - 1) / kWavesPerBlock;  // workgroups of 4 wavefront tiles
-  const int mc = pick_workers_per_block(c.M, tiles, 0.01, 8, true);  // (no reference to share between more; as
-                                                                             // absmax_select_kernel's but for the cost of a repeated row)
+  // As absmax_select_kernel's but for the cost of a repeated row, and where that would be groups of five (5, 9 and 10 workers), tiles of one
+  // worker at a time: five rows left 24 lanes of a wavefront idle (this pass at d = 2^25 + 3, M = 5 30.9 -> 26.3 us; encode + decode 246.1 ->
+  // 240.6; d = 14912512, M = 9 193.8 -> 189.3; d = 13421568, M = 10 180.0 -> 178.1).  For other worker counts one at a time is 1 % ahead or
+  // behind (M = 8: d = 2^27 1196 -> 1182, d = 2^23 103.0 -> 103.7; M = 33, d = 2033664 101.0 -> 102.5).
+  const int fives = pick_workers_per_block(c.M, tiles, 0.01, 8, true), mc = fives == 5 ? 1 : fives;
 #define TNG_QC(MC)                                                                                                   \
   hipLaunchKernelGGL((quantize_candidates_kernel<NORM, MC>),                                                           \
                      dim3((uint32_t)((tiles + quantize_tiles(MC) - 1) / quantize_tiles(MC)), (c.M + MC - 1) / MC), dim3(kBlock), 0, \
@@ -2881,7 +2883,6 @@ hipError_t quantize_candidates_dispatch(const CodecShape& c, uint32_t iter, cons
                        cs.use_slots);
   } else switch (mc) {
     case 8: TNG_QC(8); break;
-    case 5: TNG_QC(5); break;
     case 4: TNG_QC(4); break;
     case 2: TNG_QC(2); break;
     default: TNG_QC(1); break;
