@@ -229,13 +229,13 @@ def test_seeded_shapes_and_distributions(case):
 
 
 def test_slots_filled_to_their_edges():
-    # tiles that hold exactly k candidates: the quantise pass takes the first 63 with the count, the next 64 by a second
-    # load, and codes a tile with more than 127 from g
+    # tiles that hold exactly k candidates: the quantise pass takes the first 62 with their number, the next 64 by a second
+    # load, and codes a tile with more than 126 from g
     M, d = 5, 14 * (1 << 20)
     gen = torch.Generator(device=DEV).manual_seed(8)
     v = torch.zeros((M, d), device=DEV)
     v[:, ::1024 * 128] = 1.0  # every tile of the sample: its largest element is the row's
-    counts = (1, 2, 62, 63, 64, 65, 126, 127, 128, 129)
+    counts = (1, 2, 61, 62, 63, 64, 65, 125, 126, 127, 128, 129)
     for m in range(M):
         for i, k in enumerate(counts):
             tile = 1 + 3 * i + 31 * m
