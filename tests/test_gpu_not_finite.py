@@ -48,8 +48,8 @@ NAN, NNAN, INF = np.float32(np.nan), np.float32(-np.nan), np.float32(np.inf)
 KINDS = [NAN, NNAN, INF, -INF, "all", None]
 
 
-# one launch, rows longer than it takes (two passes; candidate slots with two bits), one workgroup, tails of an iteration with
-# one and with many wavefronts for the workers, and one with more workers than they take
+# one launch, rows longer than it takes (two passes), one workgroup, tails of an iteration with one and with many wavefronts for the
+# workers, and one with more workers than they take
 @pytest.mark.parametrize("d,M", [(1000, 6), (1003, 6), (4097, 7), (30001, 6), (1 << 18, 8), ((1 << 18) + 5, 6), (1 << 21, 6),
                                  ((1 << 21) + 1027, 7), (5000, 64), (5000, 66)])
 @pytest.mark.parametrize("bits", [2, 4])
@@ -75,6 +75,40 @@ def test_not_finite(d, M, bits):
     bad = np.nonzero(u32(buf["codes"]) != want)
     assert len(bad[0]) == 0, f"step: {len(bad[0])} words, first {bad[0][0]}, {bad[1][0]}"
     assert np.array_equal(buf["vbar"].cpu().numpy(), average.cpu().numpy(), equal_nan=True)
+    ctx.close()
+
+
+# The candidate slots (two bits, 2^26 elements and more).  In the tiles of the sample (every 128th of 1024 elements) a number that is none
+# leaves the row to the ordinary path and an infinite one makes the bound infinite; elsewhere they meet slots that have a bound.  Rows that
+# all have slots go through the scale pass's loop without branches, next to others through the one with them.
+OUT, SAMPLED = (1024 * 5 + 3, 1024 * 5 + 700, 1024 * 300 + 64, -1), (0, 1024 * 128 + 511, 1024 * 256 + 1023)
+
+
+@pytest.mark.parametrize("M,d,plants", [
+    (8, 1 << 23, [(NAN, None), (NNAN, None), (INF, None), (-INF, None), (None, INF), (NAN, -INF), (INF, INF), (None, None)]),
+    (8, (1 << 23) + 1027, [(None, NAN), (INF, NNAN), ("all", None), (NAN, None), (INF, None), (None, -INF), (NAN, INF), (None, None)]),
+    (5, 13108 * 1024, [(NAN, None), (INF, None), (NNAN, INF), (None, -INF), (None, None)]),
+    (1, (1 << 26) + 1024, [(NAN, None)]), (1, (1 << 26) + 1024, [(-INF, None)])])
+def test_not_finite_in_slots(M, d, plants):
+    print(f"not finite in slots d={d} M={M}", flush=True)
+    rng = np.random.default_rng(M)
+    gref = rng.standard_normal(d, dtype=np.float32)
+    g = np.stack([gref + np.float32(0.3) * rng.standard_normal(d, dtype=np.float32) * np.abs(gref) for _ in range(M)])
+    for m, (out, sampled) in enumerate(plants):
+        if isinstance(out, str):
+            g[m] = NAN
+            continue
+        for value, at in ((out, OUT), (sampled, SAMPLED)):
+            if value is not None:
+                g[m, list(at)] = value
+    want, scales = expected(g, gref, 3, 4, 2)
+    assert all(np.isinf(s) == (INF in np.abs([p for p in kinds if not isinstance(p, str) and p is not None])) for s, kinds in zip(scales, plants))
+    ctx = make_ctx(d, M, 2, B.NORM_SUB, seed=3)
+    buf = buffers(ctx)
+    ctx.normalize_encode(4, torch.from_numpy(g).to(DEV), torch.from_numpy(gref).to(DEV), buf["codes"], buf["scales"])
+    assert np.array_equal(buf["scales"].cpu().numpy(), scales)
+    bad = np.nonzero(u32(buf["codes"]) != want)
+    assert len(bad[0]) == 0, f"{len(bad[0])} words, first {bad[0][0]}, {bad[1][0]}"
     ctx.close()
 
 
