@@ -688,9 +688,13 @@ tng_status tng_step(tng_ctx* ctx, uint32_t iter, float* w, float* gref, float* g
   } else if (ctx->prof_slots == 0 && tng::quantize_decode_applies(ctx->shape, fused_rows > 0)) {
     uint32_t rows = 0;
     bool by_candidates = false;
-    // The candidate slots save the second read of g, one launch the second trip of the codes and the reference: at 2^26
-    // to 2^27 gradients the latter is ahead with 5 to 16 workers (d = 2^24, M = 8: 244 against 287 us; d = 2^25, M = 8:
-    // 504 against 498; d = 2^24, M = 4: 164 against 152).  With the l2 scale, under which hardly an element is a candidate, the
+    // The candidate slots save the second read of g where the rows fit them, one launch saves the second trip of the codes and the
+    // reference.  Slots against one launch, us, where the rows fit / where all are too dense: d = 2^24, M = 5 149 against 156 / 189 against 160;
+    // M = 8 194 against 226 / 261 against 222; d = 2^23, M = 16 176 against 219 / 231 against 217; d = 2^24, M = 4 135 against 144 / 165 against
+    // 142, M = 16 319 against 419 / 451 against 419; d = 2^25, M = 8 361 against 459 / 509 against 452.  So it is the rows that decide and no
+    // size does.  A reference that is refreshed in every iteration leaves the codes' noise in the rows, which makes them too dense after a few
+    // (d = 2^24, M = 8 283 against 241 then).  The line is where with 8 workers the slots begin to gain more than they can lose: one launch up to
+    // 2^27 gradients of 5 to 16 workers.  With the l2 scale, under which hardly an element is a candidate, the
     // slots are (d = 2^23, M = 8: 150 against 125; d = 2^24, M = 8: 281 against 223, M = 5: 224 against 178).
     const bool slots_ok = c.M <= 4 || c.M > 16 || (uint64_t)c.M * c.d > (1ull << 27);
     s = scale_impl(ctx, iter, g, gref, codes, scales, fused_rows, tng::quantize_decode_rows(ctx->shape), true, slots_ok,
