@@ -1715,8 +1715,9 @@ __global__ __launch_bounds__(kCsrThreads) void csr_grad_run_kernel(const int32_t
 
 // The same pipeline turned by ninety degrees: a workgroup stays on ONE column tile and takes the workers
 // m_first .. m_end - 1 in turn.  What a round needs of its worker -- segment bounds, row starts and
-// residuals of the minibatch rows, the shard's entry array -- is fetched during the round before, as the
-// next tile's bounds are above; what belongs to the tile -- the reference of the thread's columns for the
+// residuals of the minibatch rows, the shard's entry array -- is fetched three rounds ahead and staged in LDS two
+// ahead, its entries are asked for one ahead.  Three buffers do: what round m stages (of worker m + 2) takes the place of worker m - 1's,
+// which was last read before the first barrier of round m - 1.  What belongs to the tile -- the reference of the thread's columns for the
 // fused scale pass -- is fetched once and stays in registers, where the kernel above asks for it again
 // every round (64 workers: the reference read 64 times over, a quarter more load instructions per round
 // in a kernel bound by how fast a compute unit issues them; gradient pass 2.34 -> 2.13 ms at d = 2^24).
