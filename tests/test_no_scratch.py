@@ -1,6 +1,7 @@
 """No kernel of the built library uses scratch memory: a spilled register is reloaded from there, and in the pipelined
 loops such a reload waits for every load in flight.  Read from the kernel descriptors of the library's gfx950 code
-(the 64-byte objects <kernel>.kd of an AMDGPU code object; their second 32-bit word is the scratch size per lane)."""
+(the 64-byte objects <kernel>.kd of an AMDGPU code object; their second 32-bit word is the scratch size per lane).  Scalar registers
+that the compiler keeps in lanes of vector registers go to no memory and are not seen here."""
 import os
 import struct
 
