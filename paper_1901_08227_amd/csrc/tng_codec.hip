@@ -679,15 +679,15 @@ __global__ __launch_bounds__(kBlock, NORM == kNormComb || (NORM == kNormQuot && 
 // 256 elements of one of the tile's four loads, and in 7 bits a bin of x = u R^ / |v|: the element codes non-zero if x is below
 // rho = R^ / R, and only the few elements in the bin of rho (bin_entry below) are fetched from g and coded from the value and its
 // draw.  Everything else is cleared, and the words are packed.  A slot that overflowed (a tile with more
-// than 126 candidates) sends its tile through the ordinary path.  Where the sample gives no bound (it is all zeros) an entry is
-// a word: the sign, the position in 10 bits, and tau = |v| / u -- the scale up to which the element codes non-zero -- to 13 bits of its
+// than 126 candidates) sends its tile through the ordinary path.  Where the sample gives no bound (its maximum is below 2^-90, zero
+// included) an entry is a word: the sign, the position in 10 bits, and tau = |v| / u -- the scale up to which the element codes non-zero -- to 13 bits of its
 // significand (slot_entry).  With the l2 scale a slot is per worker and chunk of
 // four tiles: words of 12 bits of position and 11 of tau's significand; see l2_select_kernel.  The codes are those of the two-pass
 // coder bit for bit; what changes is that g is read once: 4 + 4/M bytes per element instead of 8 + 8/M.
 // Used for 2-bit codes when the row is long enough for the second read to come from
 // memory; the ragged last tile of a row has no slots, the scale pass and the ordinary quantiser take it in
-// workgroups of their own (encode + decode at d = 2^25 + 3, M = 5: 333 us by two passes, 262 this way; d = 2^26 + 1, M = 1:
-// 263 / 225).
+// workgroups of their own (encode + decode at d = 2^25 + 3, M = 5: 312 us by two passes, 238 this way; d = 2^26 + 1, M = 1:
+// 255 / 208).
 // ------------------------------------------------------------------------------------------
 constexpr int kCandCap = 127;         // candidates a slot of words holds; word 0 of a slot is their count
 constexpr int kSlotEntries = 128;     // 32-bit words per slot: 512 bytes per worker and wavefront tile
@@ -775,8 +775,9 @@ __global__ __launch_bounds__(kSampleThreads) void sample_stats_kernel(GradRows g
 // R^ of a row (0 when below the smallest normal number, as for a scale) from the sample's maximum, and what its slots are to hold:
 // nothing where the sum of |v| over the sample says that its candidates would not fit: the scale pass then
 // takes that worker's part as an ordinary scale pass and the quantise pass takes its tiles through the
-// ordinary path, without the slots.  sampled = elements of a row in the sample.  (A sum that is no number, or an infinite one, compares
-// false.)
+// ordinary path, without the slots.  sampled = elements of a row in the sample.  (A sum that is no number compares false.  An infinite one
+// compares true under an infinite maximum: the row's scale is then infinite, none of its elements is a candidate and all code to 0, as they
+// do from the value.)
 __device__ __forceinline__ uint32_t form_of_slots(float r_hat, float sum, float sampled) {
   return sum <= kDenseLimit * sampled * r_hat ? (r_hat < kBoundMin ? kFormWords : kFormBins) : kFormNone;
 }
@@ -1061,7 +1062,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
     return;
   }
   // A lane per worker: the factors go to LDS, and a bit tells of which the sample found the row too dense for the slots (only its
-  // maximum is taken).  A factor and a flag per worker in registers spilled.
+  // maximum is taken).  (A factor and a flag per worker in registers spilled to memory.)
   // The sample's partial results are reduced by every wavefront for itself, W workers side by side, all loads in flight together (a launch of its
   // own between the sample and this kernel: encode + decode d = 2^25 + 3, M = 5 2.5 us more, M = 8, no normalisation 6).
   constexpr int W = MC > 4 ? 8 : MC, kSteps = (int)kSampleRows * W / kWave;
@@ -1113,7 +1114,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
       nover += 1u;  // counts as a slot that is not used
       return;
     }
-    // what follows from m or the lane alone is made per tile: kept for all workers, or for both forms of this loop, it spilled
+    // what follows from m or the lane alone is made per tile: kept for all workers, or for both forms of this loop, it spilled to memory (68
+    // scalar registers of groups of eight, 45 of five, 34 of four and 20 of two are kept in lanes of vector registers even so; 40, 7, 0 and 0 with
+    // this form alone)
     asm volatile("" : "+s"(m), "+v"(own));
     const float c1 = factor[wave][mm];
     const bool bins = ((words >> mm) & 1u) == 0u;
@@ -1137,7 +1140,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) 
   };
   // The same without a branch, where all workers of the group are there and have slots of bins: every item then issues the same loads and
   // stores, and the waits can be counted exactly (with a branch around the store they also waited for the store before and the
-  // rows of the next item; 914 -> 900 us at d = 2^27, M = 8 with slots of words, a fifth fewer vector instructions).
+  // rows of the next item; 914 -> 900 us at d = 2^27, M = 8 with slots of words, a fifth fewer vector instructions).  Short groups, and
+  // those with a row that is too dense or has no bound, keep the form above; with it the half-words still gain a little (encode + decode with
+  // slots of words / now: d = 2^25, M = 3 197 / 192 us; d = 2^24, M = 6 167 / 161, M = 7 176 / 169, M = 9 212 / 206; d = 2^23, M = 11 145 / 138; one
+  // of eight rows too dense, d = 2^24 265 / 261; next to d = 2^24, M = 8 184 / 173 without branches).
   const uint32_t stage_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint32_t*)stage;
   const uint32_t idle = stage_at + 4u * (kStageSink + 2 + (uint32_t)lane);
   auto worker_straight = [&](const float4 (&x)[L], int mm, uint64_t tile) {
@@ -1452,7 +1458,8 @@ __global__ __launch_bounds__(kBlock, 8) void quantize_candidates_kernel(
 // of them with coalesced streaming loads, kDecodeWorkers workers at a time, and the words are
 // re-read from LDS as the 8- or 16-bit fragment belonging to each of the thread's float4 slots.
 // A code is turned into its value by a per-worker table in LDS (2^BITS entries), which also maps
-// the unused "sign with level 0" pattern to +0.
+// the unused "sign with level 0" pattern to +0; two bits of long rows under finite scales are signed units times the scale
+// (kUnits below).
 constexpr int kDecodeLoads = 4;
 constexpr int kDecodeWorkers = 8;
 
@@ -1470,7 +1477,10 @@ __global__ __launch_bounds__(kBlock) void decode_vec_kernel(
   constexpr float S = (float)((1 << (BITS - 1)) - 1);
   // Two bits are -1, 0 or 1 as a signed number, times R exactly: one rounding with the addition, as by the table, which is left
   // to scales that are not finite (0 times R is then no number) and to means.  Three vector instructions an element and worker instead of
-  // four and a read of LDS: 16 workers of 2^24 coordinates 40.1 -> 36.8 us, five of 2^25 + 3 52.5 -> 50.3, eight of 2^27 the same (bytes).
+  // four and a read of LDS, which shows where many workers make the pass one of arithmetic: table / units, us, each in two processes (whose times
+  // differ by up to 2 us with one and the same kernel, so each is compared with its like): d = 2^23, M = 64 57.3 and 58.4 / 52.0 and
+  // 53.2; d = 2^24, M = 33 58.3 and 59.7 / 54.6 and 56.2, M = 16 36.7 and 38.1 / 35.7 and 37.7; d = 2^25 + 3, M = 5 51.9 and 53.1 / 51.4 and
+  // 52.8; d = 2^27, M = 8 189.8 and 191.9 / 189.0 and 189.9.
   constexpr bool kUnits = BITS == 2 && V > 1 && NORM != kNormMean;
   __shared__ union {
     lds_u32 b32[MCH][WORDS];
