@@ -1342,14 +1342,18 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // segment and 3.2 TB/s at 128; this pass is bound by exactly that.)  One partial sum per row and pair
 // of tiles: zparts[m][pair][i].
 //
-// A trip is P pieces of U segments per lane group: one segment while one or two such pieces hold the minibatch (csr_pieces), so that small
-// ones do not go through pieces of empty segments (iterations M = 8, d = 2^23, B = 64 252 us with four of them, 199 with one; M = 3, d = 2^22, B =
-// 200 77.0 / 71.9), else two pieces of two.  All pieces but one are on their way while one is worked on: at d = 2^24, M = 64, B = 512 959 us
+// A trip is P pieces of U segments per lane group: one segment while up to three such pieces hold a trip's part of the minibatch (csr_pieces),
+// so that it does not go through pieces of empty segments (iterations M = 8, d = 2^23, B = 64 252 us with four of them, 199 with one; M = 3, d =
+// 2^22, B = 200 77.0 / 71.9 with two; with three here and in the gradient pass instead of two of two and four d = 2^22, M = 9, B = 257 209 / 200; d =
+// 2^24, M = 8, B = 260 461 / 449; 40 entries a row, d = 2^22, M = 32, B = 260 296 / 280; 400, B = 700 488 / 479), else two pieces of two.  All pieces but one are on their way while one is worked on: at d = 2^24, M = 64, B = 512 959 us
 // with two halves of which one is asked for ahead of the other's arithmetic, 928 with each asked for behind its own, 923 with four pieces of
 // one segment (iterations alike: 3296 / 3295).  Where most segments are empty the pass is bound by its vector instructions, of which
 // four pieces have more, and by what a step costs by itself: d = 2^22, M = 64, 40 entries a row 100 us with four pieces and two divisions
 // and four loads a step, 92 with a step carried along, 89 so; d = 2^21, M = 32, 20 entries a row 38.1 / 37.1 / 36.3.
-inline int csr_pieces(uint32_t batch) { return batch <= kCsrGroups ? 1 : batch <= 2 * kCsrGroups ? 2 : 4; }
+inline int csr_pieces(uint32_t batch) {  // of the minibatch in as few trips as there have to be, dealt out evenly
+  const uint32_t trips = (batch + kCsrRows - 1) / kCsrRows, rows = (batch + trips - 1) / trips;
+  return (int)((rows + kCsrGroups - 1) / kCsrGroups);
+}
 template <bool PAIRS, int P, int U>
 __global__ __launch_bounds__(kCsrThreads) void csr_z_wide_kernel(const int32_t* const* __restrict__ cols,
                                                                  const float* const* __restrict__ vals,
@@ -2492,9 +2496,10 @@ hipError_t csr_grad_launches(const LogregData& p, uint64_t d, uint32_t M, uint32
       reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormNone, false, P>),                                            \
       reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormSub, false, P>),                                             \
       reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormQuot, false, P>)
-      const void* big_lds[] = {TNG_ALL_PIECES(1), TNG_ALL_PIECES(2), TNG_ALL_PIECES(4),
+      const void* big_lds[] = {TNG_ALL_PIECES(1), TNG_ALL_PIECES(2), TNG_ALL_PIECES(3), TNG_ALL_PIECES(4),
                                reinterpret_cast<const void*>(csr_z_wide_kernel<PAIRS, 1, 1>),
                                reinterpret_cast<const void*>(csr_z_wide_kernel<PAIRS, 2, 1>),
+                               reinterpret_cast<const void*>(csr_z_wide_kernel<PAIRS, 3, 1>),
                                reinterpret_cast<const void*>(csr_z_wide_kernel<PAIRS, 2, 2>),
                                reinterpret_cast<const void*>(csr_grad_kernel<false, PAIRS>),
                                reinterpret_cast<const void*>(csr_grad_kernel<true, PAIRS>),
@@ -2526,7 +2531,10 @@ hipError_t csr_grad_launches(const LogregData& p, uint64_t d, uint32_t M, uint32
                        // 4.538 ms with 8 per workgroup, 4.531 with 16, 4.519 with 32)
     while (wpb < 32 && wpb * 2 <= M && (uint64_t)nparts * (M / (wpb * 2)) >= 1024) wpb *= 2;
     const int pieces = csr_pieces(batch);
-    auto kernel = pieces == 1 ? csr_z_wide_kernel<PAIRS, 1, 1> : pieces == 2 ? csr_z_wide_kernel<PAIRS, 2, 1> : csr_z_wide_kernel<PAIRS, 2, 2>;
+    auto kernel = pieces == 1   ? csr_z_wide_kernel<PAIRS, 1, 1>
+                  : pieces == 2 ? csr_z_wide_kernel<PAIRS, 2, 1>
+                  : pieces == 3 ? csr_z_wide_kernel<PAIRS, 3, 1>
+                                : csr_z_wide_kernel<PAIRS, 2, 2>;
     hipLaunchKernelGGL(kernel, dim3(nparts, (M + wpb - 1) / wpb), dim3(kCsrThreads), 2 * lds_w, s, p.col,
                        p.val, rowbase, bounds, w, zpart, d, batch, ntiles, nparts, M, wpb);
   } else {
@@ -2551,7 +2559,10 @@ hipError_t csr_grad_launches(const LogregData& p, uint64_t d, uint32_t M, uint32
       const int pieces = csr_pieces(batch);
 #define TNG_WORKERS_P(NORM, P) (full ? csr_grad_workers_kernel<PAIRS, NORM, true, P> : csr_grad_workers_kernel<PAIRS, NORM, false, P>)
 #define TNG_WORKERS(NORM)                                                                                                \
-  hipLaunchKernelGGL((pieces == 1 ? TNG_WORKERS_P(NORM, 1) : pieces == 2 ? TNG_WORKERS_P(NORM, 2) : TNG_WORKERS_P(NORM, 4)), \
+  hipLaunchKernelGGL((pieces == 1   ? TNG_WORKERS_P(NORM, 1)                                                             \
+                      : pieces == 2 ? TNG_WORKERS_P(NORM, 2)                                                             \
+                      : pieces == 3 ? TNG_WORKERS_P(NORM, 3)                                                             \
+                                    : TNG_WORKERS_P(NORM, 4)),                                                           \
                      grid, dim3(kCsrThreads), lds_g, s, p.col, p.val, rowbase, bounds, z, g, d, batch, ntiles, M,       \
                      per_group, *fuse)
       switch (fuse->norm) {

@@ -1,5 +1,5 @@
 """Sparse logistic gradient by column tiles, minibatches around the ends of the pieces of 128 and 256 rows in which the two passes take them
-(one, two or four pieces a trip, up to four trips of one worker), segments of every length, rows of any length and whole tiles; and
+(one to four pieces a trip, up to four trips of one worker), segments of every length, rows of any length and whole tiles; and
 workgroups that turn the ring of three staged rounds more than once: nine workers of a tile in the gradient pass, four in the dot
 products.  Against the oracle; scales from the gradient that was written."""
 from concurrent.futures import ThreadPoolExecutor
@@ -16,7 +16,7 @@ from test_gpu_csr_segments import TILE, shard
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("batch", [1, 2, 127, 128, 129, 255, 256, 257, 385, 511, 512, 513, 640, 1700])
+@pytest.mark.parametrize("batch", [1, 2, 127, 128, 129, 255, 256, 257, 383, 384, 385, 511, 512, 513, 640, 768, 769, 1700])
 @pytest.mark.parametrize("M,d,pairs,norm", [(17, 8 * TILE, True, B.NORM_SUB), (33, 5 * TILE - 7, False, B.NORM_NONE)])
 def test_minibatches_around_the_ends_of_a_piece(batch, M, d, pairs, norm):
     n, seed = 40, 7
@@ -39,7 +39,8 @@ def test_minibatches_around_the_ends_of_a_piece(batch, M, d, pairs, norm):
 
 
 @pytest.mark.parametrize("d,batch,pairs,norm", [(1 << 24, 200, True, B.NORM_SUB), ((1 << 24) - 9, 100, False, B.NORM_NONE),
-                                                ((1 << 24) - 9, 200, True, B.NORM_QUOT), ((1 << 24) - 9, 400, False, B.NORM_SUB)])
+                                                ((1 << 24) - 9, 200, True, B.NORM_QUOT), ((1 << 24) - 9, 400, False, B.NORM_SUB),
+                                                (1 << 24, 300, False, B.NORM_NONE), ((1 << 24) - 9, 384, True, B.NORM_SUB)])
 def test_rounds_of_a_workgroup(d, batch, pairs, norm):
     M, n, seed = 9, 24, 11
     rng, rows = np.random.default_rng(d + batch), []
