@@ -1345,16 +1345,19 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // A trip is P pieces of U segments per lane group: one segment while up to three such pieces hold a trip's part of the minibatch (csr_pieces),
 // so that it does not go through pieces of empty segments (iterations M = 8, d = 2^23, B = 64 252 us with four of them, 199 with one; M = 3, d =
 // 2^22, B = 200 77.0 / 71.9 with two; with three here and in the gradient pass instead of two of two and four d = 2^22, M = 9, B = 257 209 / 200; d =
-// 2^24, M = 8, B = 260 461 / 449; 40 entries a row, d = 2^22, M = 32, B = 260 296 / 280; 400, B = 700 488 / 479), else two pieces of two.  All pieces but one are on their way while one is worked on: at d = 2^24, M = 64, B = 512 959 us
-// with two halves of which one is asked for ahead of the other's arithmetic, 928 with each asked for behind its own, 923 with four pieces of
+// 2^24, M = 8, B = 260 461 / 449; 40 entries a row, d = 2^22, M = 32, B = 260 296 / 280; 400, B = 700 488 / 479), else two pieces of two.  All pieces but one
+// are on their way while one is worked on: at d = 2^24, M = 64, B = 512 959 us with two halves of which one is asked for ahead of the other's arithmetic, 928 with each asked for behind its own, 923 with four pieces of
 // one segment (iterations alike: 3296 / 3295).  Where most segments are empty the pass is bound by its vector instructions, of which
 // four pieces have more, and by what a step costs by itself: d = 2^22, M = 64, 40 entries a row 100 us with four pieces and two divisions
 // and four loads a step, 92 with a step carried along, 89 so; d = 2^21, M = 32, 20 entries a row 38.1 / 37.1 / 36.3.
+// ONE: a workgroup has one step (one worker, one trip) and asks for nothing ahead, which would be two rounds of bounds and one of entries that
+// are not there: d = 2^21, M = 4, 200 entries a row, B = 512 12.4 us, of the iteration's 52.5, and 49.6 this way; d = 2^24, M = 3, B = 512 294 / 283;
+// d = 2^22, M = 8, 40 entries a row, B = 512 116 / 110.
 inline int csr_pieces(uint32_t batch) {  // of the minibatch in as few trips as there have to be, dealt out evenly
   const uint32_t trips = (batch + kCsrRows - 1) / kCsrRows, rows = (batch + trips - 1) / trips;
   return (int)((rows + kCsrGroups - 1) / kCsrGroups);
 }
-template <bool PAIRS, int P, int U>
+template <bool PAIRS, int P, int U, bool ONE>
 __global__ __launch_bounds__(kCsrThreads) void csr_z_wide_kernel(const int32_t* const* __restrict__ cols,
                                                                  const float* const* __restrict__ vals,
                                                                  const int64_t* __restrict__ rowbase,
@@ -1365,7 +1368,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_z_wide_kernel(const int32_t* 
                                                                  uint32_t M, uint32_t workers_per_block) {
   constexpr int kPieceRows = U * (int)kCsrGroups, kRows = P * kPieceRows;
   extern __shared__ float wtile[];  // w over the columns of both tiles
-  __shared__ CsrSeg seg[3][kRows];  // of this step, the next one and the one after it
+  __shared__ CsrSeg seg[ONE ? 1 : 3][kRows];  // of this step, the next one and the one after it
   const uint32_t pair = tile_of_workgroup(blockIdx.x, npairs);
   const uint32_t t_lo = 2 * pair, t_hi = min(2 * pair + 2, ntiles);
   constexpr uint32_t T = 2u << kCsrTileShift;
@@ -1398,9 +1401,9 @@ __global__ __launch_bounds__(kCsrThreads) void csr_z_wide_kernel(const int32_t* 
   // Those of the first three steps are asked for together, ahead of the tiles of w: one after the other behind the tiles, each with its
   // wait, they held up the workgroups of few steps (iterations at d = 2^20, M = 8, B = 512 48.7 -> 48.2 us, B = 1000 64.3 -> 63.4; d = 2^22,
   // M = 8, B = 512 143.8 -> 142.3, with the same order in the gradient pass).
-  Step now = step_at(m_first, 0), next = behind(now), third = behind(next);
-  const Bounds first_bounds = fetch(now), second_bounds = fetch(next);
-  Bounds fetched = fetch(third);
+  Step now = step_at(m_first, 0), next = ONE ? now : behind(now), third = ONE ? now : behind(next);
+  const Bounds first_bounds = fetch(now), second_bounds = ONE ? first_bounds : fetch(next);
+  Bounds fetched = ONE ? first_bounds : fetch(third);
   if (c0 + T <= d && (reinterpret_cast<uintptr_t>(w) & 15u) == 0) {
     constexpr int kVec = (int)(T / (4 * kCsrThreads));  // 8 float4 per thread, four in flight at a time
     const float4* __restrict__ w4 = reinterpret_cast<const float4*>(w + c0);
@@ -1433,10 +1436,15 @@ __global__ __launch_bounds__(kCsrThreads) void csr_z_wide_kernel(const int32_t* 
     if (gl % (kCsrLanes / U) == 0 && i < batch) zparts[((uint64_t)s.m * npairs + pair) * batch + i] = sum;
   };
   stage(now, 0, first_bounds);
-  stage(next, 1, second_bounds);
+  if (!ONE) stage(next, 1, second_bounds);
   __syncthreads();
 #pragma unroll
   for (int k = 0; k < P; ++k) request(now, 0, k);
+  if (ONE) {
+#pragma unroll
+    for (int k = 0; k < P; ++k) dot(now, 0, k);
+    return;
+  }
   uint32_t buf = 0;
   while (now.m < m_last) {
     const uint32_t buf1 = buf == 2 ? 0 : buf + 1, buf2 = buf1 == 2 ? 0 : buf1 + 1;
@@ -2496,11 +2504,10 @@ hipError_t csr_grad_launches(const LogregData& p, uint64_t d, uint32_t M, uint32
       reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormNone, false, P>),                                            \
       reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormSub, false, P>),                                             \
       reinterpret_cast<const void*>(csr_grad_workers_kernel<PAIRS, kNormQuot, false, P>)
+#define TNG_Z_WIDE(P, U) \
+  reinterpret_cast<const void*>(csr_z_wide_kernel<PAIRS, P, U, true>), reinterpret_cast<const void*>(csr_z_wide_kernel<PAIRS, P, U, false>)
       const void* big_lds[] = {TNG_ALL_PIECES(1), TNG_ALL_PIECES(2), TNG_ALL_PIECES(3), TNG_ALL_PIECES(4),
-                               reinterpret_cast<const void*>(csr_z_wide_kernel<PAIRS, 1, 1>),
-                               reinterpret_cast<const void*>(csr_z_wide_kernel<PAIRS, 2, 1>),
-                               reinterpret_cast<const void*>(csr_z_wide_kernel<PAIRS, 3, 1>),
-                               reinterpret_cast<const void*>(csr_z_wide_kernel<PAIRS, 2, 2>),
+                               TNG_Z_WIDE(1, 1), TNG_Z_WIDE(2, 1), TNG_Z_WIDE(3, 1), TNG_Z_WIDE(2, 2),
                                reinterpret_cast<const void*>(csr_grad_kernel<false, PAIRS>),
                                reinterpret_cast<const void*>(csr_grad_kernel<true, PAIRS>),
                                reinterpret_cast<const void*>(csr_grad_run_kernel<PAIRS, kNormNone>),
@@ -2508,6 +2515,7 @@ hipError_t csr_grad_launches(const LogregData& p, uint64_t d, uint32_t M, uint32
                                reinterpret_cast<const void*>(csr_grad_run_kernel<PAIRS, kNormQuot>),
                                reinterpret_cast<const void*>(csr_grad_run_kernel<PAIRS, kNormComb>)};
 #undef TNG_ALL_PIECES
+#undef TNG_Z_WIDE
       static_assert(2 * sizeof(float) == sizeof(double), "two tiles of w are as large as one of g");
       for (const void* kernel : big_lds) {
         const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds_double);
@@ -2531,10 +2539,10 @@ hipError_t csr_grad_launches(const LogregData& p, uint64_t d, uint32_t M, uint32
                        // 4.538 ms with 8 per workgroup, 4.531 with 16, 4.519 with 32)
     while (wpb < 32 && wpb * 2 <= M && (uint64_t)nparts * (M / (wpb * 2)) >= 1024) wpb *= 2;
     const int pieces = csr_pieces(batch);
-    auto kernel = pieces == 1   ? csr_z_wide_kernel<PAIRS, 1, 1>
-                  : pieces == 2 ? csr_z_wide_kernel<PAIRS, 2, 1>
-                  : pieces == 3 ? csr_z_wide_kernel<PAIRS, 3, 1>
-                                : csr_z_wide_kernel<PAIRS, 2, 2>;
+    const bool one = wpb == 1 && batch <= (uint32_t)kCsrRows;  // one step per workgroup
+#define TNG_Z_WIDE(P, U) (one ? csr_z_wide_kernel<PAIRS, P, U, true> : csr_z_wide_kernel<PAIRS, P, U, false>)
+    auto kernel = pieces == 1 ? TNG_Z_WIDE(1, 1) : pieces == 2 ? TNG_Z_WIDE(2, 1) : pieces == 3 ? TNG_Z_WIDE(3, 1) : TNG_Z_WIDE(2, 2);
+#undef TNG_Z_WIDE
     hipLaunchKernelGGL(kernel, dim3(nparts, (M + wpb - 1) / wpb), dim3(kCsrThreads), 2 * lds_w, s, p.col,
                        p.val, rowbase, bounds, w, zpart, d, batch, ntiles, nparts, M, wpb);
   } else {
