@@ -1342,17 +1342,18 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 // segment and 3.2 TB/s at 128; this pass is bound by exactly that.)  One partial sum per row and pair
 // of tiles: zparts[m][pair][i].
 //
-// A trip is P pieces of U segments per lane group: one segment while up to three such pieces hold a trip's part of the minibatch (csr_pieces),
-// so that it does not go through pieces of empty segments (iterations M = 8, d = 2^23, B = 64 252 us with four of them, 199 with one; M = 3, d =
-// 2^22, B = 200 77.0 / 71.9 with two; with three here and in the gradient pass instead of two of two and four d = 2^22, M = 9, B = 257 209 / 200; d =
-// 2^24, M = 8, B = 260 461 / 449; 40 entries a row, d = 2^22, M = 32, B = 260 296 / 280; 400, B = 700 488 / 479), else two pieces of two.  All pieces but one
-// are on their way while one is worked on: at d = 2^24, M = 64, B = 512 959 us with two halves of which one is asked for ahead of the other's arithmetic, 928 with each asked for behind its own, 923 with four pieces of
-// one segment (iterations alike: 3296 / 3295).  Where most segments are empty the pass is bound by its vector instructions, of which
-// four pieces have more, and by what a step costs by itself: d = 2^22, M = 64, 40 entries a row 100 us with four pieces and two divisions
-// and four loads a step, 92 with a step carried along, 89 so; d = 2^21, M = 32, 20 entries a row 38.1 / 37.1 / 36.3.
-// ONE: a workgroup has one step (one worker, one trip) and asks for nothing ahead, which would be two rounds of bounds and one of entries that
-// are not there: d = 2^21, M = 4, 200 entries a row, B = 512 12.4 us, of the iteration's 52.5, and 49.6 this way; d = 2^24, M = 3, B = 512 294 / 283;
-// d = 2^22, M = 8, 40 entries a row, B = 512 116 / 110.
+// A trip is P pieces of U segments per lane group: one segment while up to three such pieces hold a trip's part of the minibatch
+// (csr_pieces), so that it does not go through pieces of empty segments (iterations M = 8, d = 2^23, B = 64 252 us with four of them, 199
+// with one; M = 3, d = 2^22, B = 200 77.0 / 71.9 with two; with three here and in the gradient pass instead of two of two and four d =
+// 2^22, M = 9, B = 257 209 / 200; d = 2^24, M = 8, B = 260 461 / 449; 40 entries a row, d = 2^22, M = 32, B = 260 296 / 280; 400, B = 700
+// 488 / 479), else two pieces of two.  All pieces but one are on their way while one is worked on: at d = 2^24, M = 64, B = 512 959 us with
+// two halves of which one is asked for ahead of the other's arithmetic, 928 with each asked for behind its own, 923 with four pieces of one
+// segment (iterations alike: 3296 / 3295).  Where most segments are empty the pass is bound by its vector instructions, of which four
+// pieces have more, and by what a step costs by itself: d = 2^22, M = 64, 40 entries a row 100 us with four pieces and two divisions and
+// four loads a step, 92 with a step carried along, 89 so; d = 2^21, M = 32, 20 entries a row 38.1 / 37.1 / 36.3.
+// ONE: a workgroup has one step (one worker, one trip) and asks for nothing ahead, which would be two rounds of bounds and one of entries
+// that are not there: d = 2^21, M = 4, 200 entries a row, B = 512 12.4 us, of the iteration's 52.5, and 49.6 this way; d = 2^24, M = 3, B =
+// 512 294 / 283; d = 2^22, M = 8, 40 entries a row, B = 512 116 / 110.
 inline int csr_pieces(uint32_t batch) {  // of the minibatch in as few trips as there have to be, dealt out evenly
   const uint32_t trips = (batch + kCsrRows - 1) / kCsrRows, rows = (batch + trips - 1) / trips;
   return (int)((rows + kCsrGroups - 1) / kCsrGroups);
